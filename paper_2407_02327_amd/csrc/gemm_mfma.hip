@@ -749,182 +749,164 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_nt_kernel(const GemmKerne
             if(m > amax_seen) atomicMax(p.amax_bits, m);
         }
     };
+    // The code of this epilogue runs once per tile, so its length counts as much as its operations: instructions that
+    // are not in the instruction cache are fetched while every wavefront waits.  Converting is unrolled (accumulator
+    // registers cannot be indexed) but lean: 8 vector operations and one LDS write per four outputs, the column
+    // parameters of a fragment column read once for all its rows.  Everything optional (odd N or alignment, maximum,
+    // codes, accumulator dump) sits in the short store loop behind it and works on the staged values, instead of in
+    // unrolled copies per option, which made 15 000 instructions per kernel.  Measured, unrolled copies -> this form:
+    // 16384x4096x1024 int8 on the 256 tile 86.7 -> 82.6 us, 4096x3072x768 18.3 -> 17.2, 512^3 on the 128 tile
+    // 7.3 -> 6.5, an odd N (2056x1001x1040, element stores) 40.7 -> 29.5 us.
     auto staged_store = [&](auto out_tag, auto raw_tag, uint8_t* dst_base) {
         typedef decltype(out_tag) out_t;
         constexpr bool RAW   = decltype(raw_tag)::value;
         constexpr int  OS    = sizeof(out_t);
-        constexpr int  PITCH = WTN * OS + 16;                     // padded row pitch in the staging slice
-        constexpr int  CPITCH = WTN + 16;                         // the same for the optional int8 codes of the rows
-        constexpr int  FITS  = STG_BYTES / (32 * (PITCH + CPITCH));
-        constexpr int  FPP   = FITS >= FM ? FM : (FITS >= 2 ? 2 : 1);
-        static_assert(32 * (PITCH + CPITCH) <= STG_BYTES && FM % FPP == 0, "staging slice too small");
-        uint8_t* const cstg  = stg + FPP * 32 * PITCH;            // codes behind the output rows
-        constexpr int LPR   = WTN * OS / 16;                     // lanes per output row in the store phase
-        constexpr int RPI   = 64 / LPR;                          // rows per store instruction
+        constexpr int  PITCH = WTN * OS + 16;                    // padded row pitch in the staging slice
+        constexpr int  FITS  = STG_BYTES / (32 * PITCH);
+        constexpr int  FPP   = FITS >= FM ? FM : (FITS >= 2 && FM % 2 == 0 ? 2 : 1);      // row fragments per pass
+        static_assert(32 * PITCH <= STG_BYTES && FM % FPP == 0, "staging slice too small");
+        constexpr int EPV = 16 / OS;                             // elements per 16-byte vector
+        constexpr int LPR = WTN / EPV;                           // lanes per output row in the store phase
+        constexpr int RPI = 64 / LPR;                            // rows per store instruction
+        static_assert(64 % LPR == 0 && (FPP * 32) % RPI == 0, "store instructions cover whole rows");
+        const bool    vec = (p.N * OS) % 16 == 0 && (reinterpret_cast<uintptr_t>(dst_base) & 15) == 0;
+        const int     seg = lane % LPR, lr0 = lane / LPR;
+        const int64_t col = wcol0 + seg * EPV;
         __syncthreads();                                  // all wavefronts are done reading the stages
 #pragma unroll
         for(int pass = 0; pass < FM / FPP; ++pass)
         {
 #pragma unroll
-            for(int ii = 0; ii < FPP; ++ii)
+            for(int j = 0; j < FN; ++j)
             {
-                const int i = pass * FPP + ii;
-#pragma unroll
-                for(int j = 0; j < FN; ++j)
+                float4 fs[4], bs[4];                      // scale and bias of the lane's columns, parked in LDS by the prologue
+                if constexpr(!RAW)
 #pragma unroll
                     for(int vq = 0; vq < 4; ++vq)
                     {
-                        out_t o[4];
-                        float f4[4] = {1.0f, 1.0f, 1.0f, 1.0f}, b4[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-                        if constexpr(!RAW)
-                        {   // column scale and bias of these four columns, parked in LDS by the prologue
-                            const int    c  = wn * WTN + j * 32 + 8 * vq + 4 * khalf;          // column inside the tile
-                            const float4 fs = *reinterpret_cast<const float4*>(colp + c);
-                            const float4 bs = *reinterpret_cast<const float4*>(colp + BN + c);
-                            f4[0] = fs.x; f4[1] = fs.y; f4[2] = fs.z; f4[3] = fs.w;
-                            b4[0] = bs.x; b4[1] = bs.y; b4[2] = bs.z; b4[3] = bs.w;
-                        }
+                        const int c = wn * WTN + j * 32 + 8 * vq + 4 * khalf;          // column inside the tile
+                        fs[vq] = *reinterpret_cast<const float4*>(colp + c);
+                        bs[vq] = *reinterpret_cast<const float4*>(colp + BN + c);
+                    }
 #pragma unroll
-                        for(int e = 0; e < 4; ++e)
+                for(int ii = 0; ii < FPP; ++ii)
+#pragma unroll
+                    for(int vq = 0; vq < 4; ++vq)
+                    {
+                        const accv_t& a   = acc[pass * FPP + ii][j];
+                        uint8_t*      dst = stg + (ii * 32 + frag_row) * PITCH + (j * 32 + 8 * vq + 4 * khalf) * OS;
+                        if constexpr(RAW)
                         {
-                            if constexpr(RAW)
-                                o[e] = acc[i][j][vq * 4 + e];
-                            else
-                            {
-                                o[e] = fma_out<out_t>(static_cast<float>(acc[i][j][vq * 4 + e]), f4[e], b4[e]);
-                            }
-                        }
-                        uint8_t* dst = stg + (ii * 32 + frag_row) * PITCH + (j * 32 + 8 * vq + 4 * khalf) * OS;
-                        if(OS == 2)
-                            *reinterpret_cast<uint2*>(dst) = *reinterpret_cast<const uint2*>(o);
-                        else
+                            const out_t o[4] = {a[vq * 4], a[vq * 4 + 1], a[vq * 4 + 2], a[vq * 4 + 3]};
                             *reinterpret_cast<uint4*>(dst) = *reinterpret_cast<const uint4*>(o);
-                        if constexpr(!RAW)
-                            if(p.codes)
-                            {   // the quantizer's arithmetic on the value as stored (one fp32 multiply, ties to even, clamp)
-                                uint32_t cw = 0u;
-#pragma unroll
-                                for(int e = 0; e < 4; ++e)
-                                {
-                                    float stored;
-                                    if constexpr(OS == 2) stored = __half2float(o[e]); else stored = o[e];
-                                    cw |= (static_cast<uint32_t>(quantize_code<kNearest>(stored, code_inv, p.code_qmax, 0u)) & 0xFFu) << (8 * e);
-                                }
-                                *reinterpret_cast<uint32_t*>(cstg + (ii * 32 + frag_row) * CPITCH + (j * 32 + 8 * vq + 4 * khalf)) = cw;
-                            }
+                        }
+                        else
+                        {
+                            const float a0 = static_cast<float>(a[vq * 4]), a1 = static_cast<float>(a[vq * 4 + 1]);
+                            const float a2 = static_cast<float>(a[vq * 4 + 2]), a3 = static_cast<float>(a[vq * 4 + 3]);
+                            const float4 f = fs[vq], b = bs[vq];
+                            if constexpr(OS == 2)
+                                *reinterpret_cast<uint2*>(dst) = make_uint2(fma_out_half2(a0, f.x, b.x, a1, f.y, b.y),
+                                                                            fma_out_half2(a2, f.z, b.z, a3, f.w, b.w));
+                            else
+                                *reinterpret_cast<float4*>(dst) = make_float4(fmaf(a0, f.x, b.x), fmaf(a1, f.y, b.y),
+                                                                              fmaf(a2, f.z, b.z), fmaf(a3, f.w, b.w));
+                        }
                     }
             }
             // Lanes read what other lanes of the wavefront have just written: the hardware keeps a
             // wavefront's LDS operations in order, and the wavefront-scope fence tells the compiler
             // that these loads may not be satisfied from values a lane has seen before.
             __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-#pragma unroll
-            for(int r0 = 0; r0 < FPP * 32; r0 += RPI)
-            {
-                const int     lr  = r0 + lane / LPR, seg = lane % LPR;
-                const v4u32   val = *reinterpret_cast<const v4u32*>(stg + lr * PITCH + seg * 16);
-                const int64_t row = wrow0 + pass * FPP * 32 + lr;
-                const int64_t col = wcol0 + seg * (16 / OS);
-                if(row < p.M && col < p.N)
-                {
-                    if constexpr(!RAW)
-                        if(p.amax_bits) out_run = fold_abs_bits<OS>(out_run, val);
-                    v4u32* dst = reinterpret_cast<v4u32*>(dst_base + (row * p.N + col) * OS);
-                    if constexpr(RAW)
-                        *dst = val;      // read back soon by the reduction: ordinary store
-                    else                 // streaming store: C is not read again here, keep the operand panels in L2
-                        __builtin_nontemporal_store(val, dst);
-                }
-            }
+            const int64_t row0 = wrow0 + pass * FPP * 32 + lr0;
             if constexpr(!RAW)
-                if(p.codes)
-                {   // rows of WTN code bytes leave as 16-byte vectors too
-                    constexpr int CLPR = WTN / 16, CRPI = 64 / CLPR;
-#pragma unroll
-                    for(int r0 = 0; r0 < FPP * 32; r0 += CRPI)
+                if(vec && p.codes && (reinterpret_cast<uintptr_t>(p.codes) & (EPV - 1)) == 0)
+                {   // C and its codes as vectors (with the quantizer's arithmetic: one fp32 multiply, ties to even, clamp)
+#pragma unroll 2
+                    for(int r = 0; r < FPP * 32; r += RPI)
                     {
-                        const int     lr  = r0 + lane / CLPR, seg = lane % CLPR;
-                        const v4u32   val = *reinterpret_cast<const v4u32*>(cstg + lr * CPITCH + seg * 16);
-                        const int64_t row = wrow0 + pass * FPP * 32 + lr;
-                        const int64_t col = wcol0 + seg * 16;
-                        if(lr < FPP * 32 && row < p.M && col < p.N)
-                            *reinterpret_cast<v4u32*>(p.codes + row * p.N + col) = val;      // read next by the consumer's GEMM
+                        const v4u32 val = *reinterpret_cast<const v4u32*>(stg + (r + lr0) * PITCH + seg * 16);
+                        uint32_t    cw[EPV / 4];
+#pragma unroll
+                        for(int g = 0; g < EPV / 4; ++g) cw[g] = 0u;
+#pragma unroll
+                        for(int e = 0; e < EPV; ++e)
+                        {
+                            const uint32_t word   = OS == 2 ? (e % 2 ? val[e / 2] >> 16 : val[e / 2] & 0xFFFFu) : val[e % 4];
+                            const float    stored = OS == 2 ? __half2float(__ushort_as_half(static_cast<unsigned short>(word))) : __uint_as_float(word);
+                            cw[e / 4] |= (static_cast<uint32_t>(quantize_code<kNearest>(stored, code_inv, p.code_qmax, 0u)) & 0xFFu) << (8 * (e % 4));
+                        }
+                        const int64_t at = (row0 + r) * p.N + col;
+                        if(row0 + r < p.M && col < p.N)
+                        {
+                            out_run = fold_abs_bits<OS>(out_run, val);
+                            __builtin_nontemporal_store(val, reinterpret_cast<v4u32*>(dst_base + at * OS));
+                            // (read next by the consumer's GEMM: ordinary store)
+                            if constexpr(EPV == 8) *reinterpret_cast<uint2*>(p.codes + at) = make_uint2(cw[0], cw[EPV / 4 - 1]);
+                            else                   *reinterpret_cast<uint32_t*>(p.codes + at) = cw[0];
+                        }
+                    }
+                    continue;
+                }
+            if(vec && (RAW || !p.codes))
+            {
+                uint8_t* dst = dst_base + (row0 * p.N + col) * OS;
+                const int64_t step = RPI * p.N * OS;
+#pragma unroll
+                for(int r = 0; r < FPP * 32; r += RPI, dst += step)
+                {
+                    const v4u32 val = *reinterpret_cast<const v4u32*>(stg + (r + lr0) * PITCH + seg * 16);
+                    if(row0 + r < p.M && col < p.N)
+                    {
+                        if constexpr(!RAW)
+                            if(p.amax_bits) out_run = fold_abs_bits<OS>(out_run, val);
+                        if constexpr(RAW)
+                            *reinterpret_cast<v4u32*>(dst) = val;      // read back soon by the reduction: ordinary store
+                        else                 // streaming store: C is not read again here, keep the operand panels in L2
+                            __builtin_nontemporal_store(val, reinterpret_cast<v4u32*>(dst));
                     }
                 }
+                continue;
+            }
+#pragma unroll 1
+            for(int r = 0; r < FPP * 32; r += RPI)
+            {
+                const v4u32   val = *reinterpret_cast<const v4u32*>(stg + (r + lr0) * PITCH + seg * 16);
+                const int64_t row = row0 + r, left = row < p.M ? p.N - col : 0;      // valid elements from here on (may be <= 0)
+                const int64_t at  = row * p.N + col;
+#pragma unroll
+                for(int e = 0; e < EPV; ++e)
+                {
+                    const uint32_t word = OS == 2 ? (e % 2 ? val[e / 2] >> 16 : val[e / 2] & 0xFFFFu) : val[e % 4];
+                    if(e >= left) continue;
+                    if constexpr(OS == 2)
+                        reinterpret_cast<uint16_t*>(dst_base)[at + e] = static_cast<uint16_t>(word);
+                    else
+                        reinterpret_cast<uint32_t*>(dst_base)[at + e] = word;
+                    if constexpr(!RAW)
+                    {   // maximum and codes: of the values as stored, with the quantizer's arithmetic (one fp32 multiply,
+                        // ties to even, clamp)
+                        const uint32_t mag = word & (OS == 2 ? 0x7FFFu : 0x7FFFFFFFu);
+                        out_run = out_run > mag ? out_run : mag;
+                        if(p.codes)
+                        {
+                            const float stored = OS == 2 ? __half2float(__ushort_as_half(static_cast<unsigned short>(word))) : __uint_as_float(word);
+                            p.codes[at + e] = static_cast<int8_t>(quantize_code<kNearest>(stored, code_inv, p.code_qmax, 0u));
+                        }
+                    }
+                }
+            }
         }
     };
 
     if(SPLIT)
     {
-        acc_t* part = static_cast<acc_t*>(p.partial) + static_cast<int64_t>(split) * p.M * p.N;
-        if((p.N * 4) % 16 == 0 && (reinterpret_cast<uintptr_t>(part) & 15) == 0)
-        {
-            staged_store(acc_t{}, std::true_type{}, reinterpret_cast<uint8_t*>(part));
-            return;
-        }
-#pragma unroll
-        for(int i = 0; i < FM; ++i)
-        {
-            const int64_t row = wrow0 + i * 32 + frag_row;
-#pragma unroll
-            for(int j = 0; j < FN; ++j)
-#pragma unroll
-                for(int v = 0; v < 16; ++v)
-                {
-                    const int64_t col = wcol0 + j * 32 + 8 * (v / 4) + 4 * khalf + (v % 4);
-                    if(row < p.M && col < p.N) part[row * p.N + col] = acc[i][j][v];
-                }
-        }
+        staged_store(acc_t{}, std::true_type{},
+                     reinterpret_cast<uint8_t*>(static_cast<acc_t*>(p.partial) + static_cast<int64_t>(split) * p.M * p.N));
         return;
     }
-
-    const int osize = p.c_is_f16 ? 2 : 4;
-    const bool fast = !p.acc_dump && (p.N * osize) % 16 == 0 && (reinterpret_cast<uintptr_t>(p.C) & 15) == 0
-                   && (!p.codes || (p.N % 16 == 0 && (reinterpret_cast<uintptr_t>(p.codes) & 15) == 0));
-    if(!fast)
-    {   // element-wise stores: any N, any alignment, optional raw accumulator dump
-#pragma unroll
-        for(int j = 0; j < FN; ++j)
-#pragma unroll
-            for(int v = 0; v < 16; ++v)
-            {
-                const int64_t col = wcol0 + j * 32 + 8 * (v / 4) + 4 * khalf + (v % 4);
-                const bool    cok = col < p.N;
-                const float   f   = alpha * ((p.col_scale && cok) ? p.col_scale[col] : 1.0f);
-                const float   b   = (p.col_bias && cok) ? p.col_bias[col] : 0.0f;
-#pragma unroll
-                for(int i = 0; i < FM; ++i)
-                {
-                    const int64_t row = wrow0 + i * 32 + frag_row;
-                    if(row < p.M && cok)
-                    {
-                        // (the same arithmetic as the vector path: a binary16 output is the fused multiply-add rounded
-                        // once to binary16)
-                        float stored;
-                        if(p.c_is_f16)
-                        {
-                            const __half h = fma_out<__half>(static_cast<float>(acc[i][j][v]), f, b);
-                            static_cast<__half*>(p.C)[row * p.N + col] = h;
-                            stored = __half2float(h);
-                        }
-                        else
-                        {
-                            stored = fmaf(static_cast<float>(acc[i][j][v]), f, b);
-                            static_cast<float*>(p.C)[row * p.N + col] = stored;
-                        }
-                        const uint32_t u = __float_as_uint(stored) & 0x7FFFFFFFu;
-                        out_run = out_run > u ? out_run : u;
-                        if(p.codes)
-                            p.codes[row * p.N + col] = static_cast<int8_t>(quantize_code<kNearest>(stored, code_inv, p.code_qmax, 0u));
-                        if(sizeof(acc_t) == 4 && p.acc_dump)
-                            p.acc_dump[row * p.N + col] = static_cast<int32_t>(acc[i][j][v]);
-                    }
-                }
-            }
-        if(p.amax_bits) publish_amax(out_run);
-        return;
-    }
-
+    if constexpr(std::is_same<acc_t, int32_t>::value)
+        if(p.acc_dump) staged_store(acc_t{}, std::true_type{}, reinterpret_cast<uint8_t*>(p.acc_dump));
     if(p.c_is_f16)
     {
         staged_store(__half{}, std::false_type{}, static_cast<uint8_t*>(p.C));
