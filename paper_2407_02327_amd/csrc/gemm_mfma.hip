@@ -192,6 +192,13 @@ __device__ __forceinline__ void dma_issue(const uint8_t* sbase, uint32_t voff, u
                                      (__attribute__((address_space(3))) void*)(lds_mid + dma_lds_shift<D, DPW>()), 16, IMM, 0);
 }
 
+// The same for one 4-byte column parameter per lane.
+__device__ __forceinline__ void column_param_issue(const float* src, uint8_t* lds_dst)
+{
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
+                                     (__attribute__((address_space(3))) void*)lds_dst, 4, 0, 0);
+}
+
 template <int DPW, int... Ds>
 __device__ __forceinline__ void dma_sequence(std::integer_sequence<int, Ds...>, const uint8_t* sbase,
                                              const uint32_t (&voff)[DPW], uint8_t* lds_mid)
@@ -215,6 +222,8 @@ __device__ __forceinline__ void dma_sequence_tail(std::integer_sequence<int, Ds.
 // neighbouring pixel (same image, inside the border) or, for padding and for chunks past the end
 // of K, 16 zero bytes from a constant block.
 __device__ uint4 g_zero_chunk;     // never written: static storage starts at zero
+
+__device__ const float g_one = 1.0f;     // stands in for an absent scale
 
 struct ConvTap { int delta[2]; int dh[2]; int dw[2]; bool valid[2]; };     // per chunk parity of the lane
 
@@ -345,6 +354,23 @@ template <int ESZ, int RB> __device__ __forceinline__ int tn_swizzle(int row)
     if constexpr(ESZ == 1) return 2 * ((row / (16 / CPR)) % (CPR / 2));
     else                   return RB >= 256 ? 4 * (row % 4) : 4 * ((row / 2) % 2);
 }
+// Workgroup barrier behind a wait for this wavefront's LDS operations only (the compiler's __syncthreads would also
+// wait for every vector-memory operation in flight, i.e. drain the queue of direct loads).
+__device__ __forceinline__ void wg_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+// at most N of this wavefront's vector-memory operations still in flight
+template <int N> __device__ __forceinline__ void wait_direct_loads()
+{
+    static_assert(N >= 0 && N <= 63, "the vector-memory counter holds 63");
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+// the direct loads of at most min(n, N) K tiles (DPW instructions each) still in flight
+template <int DPW, int N> __device__ __forceinline__ void wait_tiles(int n)
+{
+    if constexpr(N == 0) wait_direct_loads<0>();
+    else if(n >= N)      wait_direct_loads<N * DPW>();
+    else                 wait_tiles<DPW, N - 1>(n);
+}
+__device__ __forceinline__ void lds_write_b32(uint32_t addr, uint32_t v) { asm volatile("ds_write_b32 %0, %1" ::"v"(addr), "v"(v) : "memory"); }
 template <int F, int... Is>
 __device__ __forceinline__ void frag_reads(v4i32 (&dst)[F], uint32_t addr, std::integer_sequence<int, Is...>)
 {
@@ -360,7 +386,7 @@ __device__ __forceinline__ void frag_reads(v4i32 (&dst)[F], uint32_t addr, std::
 // matrix instruction wants; two reads make a lane's 16 operand bytes.  16-byte chunks are XOR-swizzled per row so
 // that the lanes of one access pass touch all banks once.  Everything behind the fragments
 // (matrix instructions, epilogue, split K) is shared with the NT form.  Kb is the contraction length P here.
-template <typename TR, int BM, int BN, int WGM, int WGN, bool SPLIT, bool CONV = false, bool TN = false>
+template <typename TR, int BM, int BN, int WGM, int WGN, int ST, bool SPLIT, bool CONV = false, bool TN = false>
 __global__ __launch_bounds__(64 * WGM * WGN) void gemm_nt_kernel(const GemmKernelArgs p)
 {
     static_assert(!(SPLIT && CONV && !TN), "the implicit patch matrix of the forward is not combined with split K");
@@ -465,14 +491,6 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_nt_kernel(const GemmKerne
             int64_t   lrow  = srow - (is_a ? 0 : BM);
             if(lrow >= rows_left) lrow = rows_left - 1;
             voff[d] = static_cast<uint32_t>(lrow * p.Kb + chunk * 16 + kDmaBias - imm[d]);
-            if(!CONV && p.remap_C > 0 && !is_a)
-            {   // offset from p.B itself (the base below is not advanced to this tile's rows)
-                const int64_t row = n0 + lrow;
-                const int     tap = static_cast<int>(row / p.remap_C), c = static_cast<int>(row - static_cast<int64_t>(tap) * p.remap_C);
-                const int     kh = (tap * 11) >> 5, kw = tap - 3 * kh;          // tap / 3 for tap < 12
-                voff[d] = static_cast<uint32_t>(static_cast<int64_t>(kw * p.remap_C + c) * p.Kb + (kh - 1) * p.remap_shift
-                                                + chunk * 16 + kDmaBias - imm[d]);
-            }
             if constexpr(CONVA)
                 if(is_a)
                 {   // A side: voff holds the byte offset of output pixel m in the NHWC tensor instead
@@ -482,6 +500,22 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_nt_kernel(const GemmKerne
                 }
             if(d < 2) gchunk[d] = chunk * 16;
         }
+        if constexpr(!CONV && !TN)
+            if(p.remap_C > 0 && !is_a)
+            {   // offset from p.B itself (the base below is not advanced to this tile's rows); in a block of its own, so
+                // that the ordinary kernel's first instructions are not spread over these divisions
+#pragma unroll
+                for(int d = 0; d < DPW; ++d)
+                {
+                    const int      lrow = (wave * DPW + d) * 8 + lane / 8 - BM;
+                    const uint32_t row  = static_cast<uint32_t>(n0 + (lrow < rows_left ? lrow : rows_left - 1));
+                    const int      tap  = static_cast<int>(row / static_cast<uint32_t>(p.remap_C));
+                    const int      c    = static_cast<int>(row) - tap * p.remap_C;
+                    const int      kh = (tap * 11) >> 5, kw = tap - 3 * kh;      // tap / 3 for tap < 12
+                    voff[d] = static_cast<uint32_t>(static_cast<int64_t>(kw * p.remap_C + c) * p.Kb + (kh - 1) * p.remap_shift
+                                                    + gchunk[d & 1] + kDmaBias - imm[d]);
+                }
+            }
     }
     // the panel base as two scalar registers (the wavefront index is uniform, so is the choice of panel)
     const uint64_t gbits = reinterpret_cast<uint64_t>(gbase) - kDmaBias;
@@ -538,8 +572,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_nt_kernel(const GemmKerne
     // Waits for this wavefront's direct loads and for its outstanding fragment reads (the barrier hands the
     // stage they read to the next direct load, and the compiler does not see those reads), zero-fills its
     // out-of-K chunks, then joins the block.
-    auto land = [&](int stage, int kt) {
-        __builtin_amdgcn_s_waitcnt(0x0070);                       // vmcnt(0), lgkmcnt(0)
+    auto zero_tail = [&](int stage, int kt) {
         if(!TN && kt == tail_kt)
         {
             const int64_t kb = static_cast<int64_t>(kt) * kRowBytes;
@@ -549,7 +582,13 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_nt_kernel(const GemmKerne
                     *reinterpret_cast<uint4*>(lds + stage * STAGE_BYTES + (wave * DPW + d) * 1024 + lane * 16)
                         = make_uint4(0, 0, 0, 0);
         }
-        __syncthreads();
+    };
+    auto land = [&](int stage, int kt) {
+        // direct loads retire in order: tile kt has landed when at most the loads of the tiles requested behind it
+        // (up to ST - 2 of them; fewer at the end of K) are outstanding
+        wait_tiles<DPW, ST - 2>(kt_end - 1 - kt);
+        zero_tail(stage, kt);
+        wg_barrier();
     };
 
     accv_t acc[FM][FN];
@@ -628,7 +667,6 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_nt_kernel(const GemmKerne
     constexpr int kReadsPerSet  = TN ? 2 * (FM + FN) : FM + FN;
     static_assert(kReadsPerSet <= 15, "the LDS counter holds 15");
     constexpr int kWaitOlderSet = 0xC07F | (kReadsPerSet << 8);
-    constexpr int kWaitAllLds   = 0xC07F;                         // lgkmcnt(0)
     static_assert(FM + FN <= 15, "the LDS counter holds 15");
     auto mma = [&](auto buf_tag) {
         constexpr int buf = decltype(buf_tag)::value;
@@ -653,9 +691,8 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_nt_kernel(const GemmKerne
     // below), (3) reads chunk 0 of the next tile, (4) issues chunk 3, whose operands are already
     // in registers, and (5) reads chunk 1 of the next tile: barrier release, LDS latency and a
     // whole K tile of memory latency hide behind matrix work.
-    // Per-column epilogue parameters of this tile (alpha * column scale, column bias) are parked
-    // in LDS behind the stages while the first direct loads are in flight; the epilogue reads them
-    // back with a few 16-byte LDS reads instead of waiting on global memory.
+    // The column scales and biases of this tile are fetched by direct loads as well, in front of the first K tile, and
+    // wait in LDS behind the stages for the epilogue.
     // The direct loads of a K tile are not requested by all wavefronts at once.  A compute unit takes such an
     // instruction (1 KB) at about 64 bytes per clock, and a wavefront issues nothing else while its loads
     // queue up: with every wavefront requesting right behind the barrier, both wavefronts of every SIMD sit
@@ -664,36 +701,35 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_nt_kernel(const GemmKerne
     // 3 instead: while one wavefront of a SIMD queues loads, its sibling issues matrix instructions
     // (launched alone: 4-10 % fewer cycles per launch on every tile shape, int8 and binary16).
     const bool late_loader = wave >= WGM * WGN / 2;
-    float* colp = reinterpret_cast<float*>(lds + 2 * STAGE_BYTES);       // [2][BN]: scale, bias
-    float  alpha = 1.0f, cp_scale = 1.0f, cp_bias = 0.0f;
-    if(!SPLIT)
-    {
-        if(p.s0) alpha *= *p.s0;
-        if(p.s1) alpha *= *p.s1;
-        const int64_t col = n0 + tid;
-        const bool    cok = tid < BN && col < p.N;
-        cp_scale = alpha * ((p.col_scale && cok) ? p.col_scale[col] : 1.0f);
-        cp_bias  = (p.col_bias && cok) ? p.col_bias[col] : 0.0f;
-    }
-    const uint32_t amax_seen = (!SPLIT && p.amax_bits) ? __hip_atomic_load(p.amax_bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
-    const float    code_inv  = (!SPLIT && p.codes) ? *p.code_inv : 0.0f;
+    float* colp = reinterpret_cast<float*>(lds + ST * STAGE_BYTES);       // [2][BN]: scale, bias
     const bool any_k = kt_begin < kt_end;
-    if(any_k) dma(0, kt_begin);
-    if(!SPLIT && tid < BN)
+    // (scalar loads: in front of the first direct load, used by the epilogue)
+    const float scale0 = *(!SPLIT && p.s0 ? p.s0 : &g_one), scale1 = *(!SPLIT && p.s1 ? p.s1 : &g_one);
+    const float code_inv = *(!SPLIT && p.codes ? p.code_inv : &g_one);
+    // Nothing in front of the K loop waits for global memory except the K loop's own wait for tile 0: column parameters
+    // and as many K tiles as there are stages are requested back to back (a load into a register here would make the
+    // compiler drain the queue before its use).
+    if(!SPLIT && wave < BN / 64)
     {
-        colp[tid]      = cp_scale;
-        colp[BN + tid] = cp_bias;
+        const int64_t col = n0 + tid < p.N ? n0 + tid : p.N - 1;       // columns past N: any valid one, never stored
+        if(p.col_scale) column_param_issue(p.col_scale + col, lds + ST * STAGE_BYTES + wave * 256);
+        if(p.col_bias) column_param_issue(p.col_bias + col, lds + ST * STAGE_BYTES + BN * 4 + wave * 256);
     }
+#pragma unroll
+    for(int t = 0; t < ST; ++t)
+        if(kt_begin + t < kt_end) dma(t, kt_begin + t);
     if(any_k)
     {
-        land(0, kt_begin);
-        if(kt_begin + 1 < kt_end) dma(1, kt_begin + 1);
+        wait_tiles<DPW, ST - 1>(kt_end - 1 - kt_begin);      // tile 0; up to ST - 1 tiles are requested behind it
+        zero_tail(0, kt_begin);
+        wg_barrier();
         load_frags(set0, 0, 0);
         load_frags(set1, 0, 1);
+        int stage = 0;
         for(int kt = kt_begin; kt < kt_end; ++kt)
         {
-            const int  stage = (kt - kt_begin) & 1;
             const bool more  = kt + 1 < kt_end;
+            const int  next  = stage + 1 < ST ? stage + 1 : 0;
             __builtin_amdgcn_s_waitcnt(kWaitOlderSet);
             mma(set0);
             load_frags(set0, stage, 2);
@@ -702,19 +738,36 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_nt_kernel(const GemmKerne
             load_frags(set1, stage, 3);
             __builtin_amdgcn_s_waitcnt(kWaitOlderSet);
             mma(set0);
-            if(more) land(stage ^ 1, kt + 1);
+            if(more) land(next, kt + 1);
             // without a next tile the reads below fetch chunks 0 and 1 of the current stage again: in bounds, unused
-            const int  nstage  = more ? (stage ^ 1) : stage;
-            const bool request = kt + 2 < kt_end;
-            if(request && !late_loader) dma(stage, kt + 2);
+            const int  nstage  = more ? next : stage;
+            const bool request = kt + ST < kt_end;
+            if(request && !late_loader) dma(stage, kt + ST);
             load_frags(set0, nstage, 0);
             __builtin_amdgcn_s_waitcnt(kWaitOlderSet);
             mma(set1);
-            if(request && late_loader) dma(stage, kt + 2);
+            if(request && late_loader) dma(stage, kt + ST);
             load_frags(set1, nstage, 1);
+            stage = next;
         }
-        __builtin_amdgcn_s_waitcnt(kWaitAllLds);     // the unused reads of the last trip land before the registers are reused
     }
+    // The unused reads of the last trip land before their registers are reused: naming the registers behind the wait
+    // keeps the compiler from handing them out in front of it.
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    if(any_k)
+#pragma unroll
+        for(int b = 0; b < 2; ++b)
+        {
+#pragma unroll
+            for(int f = 0; f < FM; ++f) asm volatile("" : "+v"(af[b][f]));
+#pragma unroll
+            for(int f = 0; f < FN; ++f) asm volatile("" : "+v"(bf[b][f]));
+        }
+
+    else
+        wait_direct_loads<0>();                  // the column parameters
+    const float    alpha     = scale0 * scale1;
+    const uint32_t amax_seen = (!SPLIT && p.amax_bits) ? __hip_atomic_load(p.amax_bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
 
     // ---- epilogue.  The B fragment is the matrix instruction's first operand, so a lane holds
     //      C^T fragments: lane -> output row m = lane%32 of the fragment; register v -> output
@@ -730,7 +783,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_nt_kernel(const GemmKerne
     uint32_t out_run = 0u;     // running maximum of |C| of this lane (packed like the output type)
     // one atomic maximum per workgroup at most: lanes -> wavefront (shuffles) -> workgroup (LDS slots behind the
     // column parameters).  Atomics on one word retire about 10 ns apart, so a workgroup skips its own when the
-    // word, as read at the start of the kernel (`amax_seen`: possibly stale, never too large), already covers it.
+    // word, as read in front of the stores (`amax_seen`: possibly stale, never too large), already covers it.
     auto publish_amax = [&](uint32_t bits_f32) {
 #pragma unroll
         for(int off = 32; off >= 1; off >>= 1)
@@ -779,14 +832,17 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_nt_kernel(const GemmKerne
 #pragma unroll
             for(int j = 0; j < FN; ++j)
             {
-                float4 fs[4], bs[4];                      // scale and bias of the lane's columns, parked in LDS by the prologue
+                float4 fs[4], bs[4];                      // scale and bias of the lane's columns (alpha * column scale, as one product)
                 if constexpr(!RAW)
 #pragma unroll
                     for(int vq = 0; vq < 4; ++vq)
                     {
                         const int c = wn * WTN + j * 32 + 8 * vq + 4 * khalf;          // column inside the tile
-                        fs[vq] = *reinterpret_cast<const float4*>(colp + c);
-                        bs[vq] = *reinterpret_cast<const float4*>(colp + BN + c);
+                        const float4 cs = *reinterpret_cast<const float4*>(colp + c);
+                        const float4 cb = *reinterpret_cast<const float4*>(colp + BN + c);
+                        fs[vq] = p.col_scale ? make_float4(alpha * cs.x, alpha * cs.y, alpha * cs.z, alpha * cs.w)
+                                             : make_float4(alpha, alpha, alpha, alpha);
+                        bs[vq] = p.col_bias ? cb : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
                     }
 #pragma unroll
                 for(int ii = 0; ii < FPP; ++ii)
@@ -935,7 +991,6 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_nt_kernel(const GemmKerne
 //   * barriers are bare s_barrier instructions behind an LDS wait (the compiler's __syncthreads would wait for
 //     every vector-memory operation of the wavefront, stores included), and every LDS access behind the first
 //     store is written as an instruction for the same reason.
-__device__ __forceinline__ void wg_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 __device__ __forceinline__ void wait_lds_all() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); __builtin_amdgcn_sched_barrier(0); }
 // LDS accesses as instructions; OFF is the instruction's immediate byte offset (16 bits)
 template <int OFF> __device__ __forceinline__ void lds_write_b64(uint32_t addr, const v2u32& v)
@@ -943,7 +998,6 @@ template <int OFF> __device__ __forceinline__ void lds_write_b64(uint32_t addr, 
     static_assert(OFF >= 0 && OFF < 65536, "immediate offset");
     asm volatile("ds_write_b64 %0, %1 offset:%2" ::"v"(addr), "v"(v), "n"(OFF) : "memory");
 }
-__device__ __forceinline__ void lds_write_b32(uint32_t addr, uint32_t v) { asm volatile("ds_write_b32 %0, %1" ::"v"(addr), "v"(v) : "memory"); }
 template <int OFF> __device__ __forceinline__ void lds_read_b128(v4u32& d, uint32_t addr)
 {
     static_assert(OFF >= 0 && OFF < 65536, "immediate offset");
@@ -1357,10 +1411,10 @@ inline int current_device_slot()
     return (hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < kMaxDevices) ? dev : -1;
 }
 
-template <typename TR, int BM, int BN, int WGM, int WGN>
+template <typename TR, int BM, int BN, int WGM, int WGN, int ST>
 hipError_t launch_tile(const GemmKernelArgs& a, int splits, hipStream_t st, bool tn = false)
 {
-    constexpr size_t lds_bytes = 2 * static_cast<size_t>(BM + BN) * kRowBytes + 2 * BN * sizeof(float) + 64;   // + amax slots
+    constexpr size_t lds_bytes = ST * static_cast<size_t>(BM + BN) * kRowBytes + 2 * BN * sizeof(float) + 64;   // + amax slots
     const dim3       grid(static_cast<unsigned>(a.tiles_m * a.tiles_n), static_cast<unsigned>(splits));
     const dim3       block(64 * WGM * WGN);
     static bool      attr_set[kMaxDevices][7] = {};   // per instantiation and device; benign if set twice
@@ -1374,16 +1428,16 @@ hipError_t launch_tile(const GemmKernelArgs& a, int splits, hipStream_t st, bool
         if(tn)
         {
             if(conv)
-                fn = splits > 1 ? reinterpret_cast<const void*>(&gemm_nt_kernel<TR, BM, BN, WGM, WGN, true, true, true>)
-                                : reinterpret_cast<const void*>(&gemm_nt_kernel<TR, BM, BN, WGM, WGN, false, true, true>);
+                fn = splits > 1 ? reinterpret_cast<const void*>(&gemm_nt_kernel<TR, BM, BN, WGM, WGN, ST, true, true, true>)
+                                : reinterpret_cast<const void*>(&gemm_nt_kernel<TR, BM, BN, WGM, WGN, ST, false, true, true>);
             else
-                fn = splits > 1 ? reinterpret_cast<const void*>(&gemm_nt_kernel<TR, BM, BN, WGM, WGN, true, false, true>)
-                                : reinterpret_cast<const void*>(&gemm_nt_kernel<TR, BM, BN, WGM, WGN, false, false, true>);
+                fn = splits > 1 ? reinterpret_cast<const void*>(&gemm_nt_kernel<TR, BM, BN, WGM, WGN, ST, true, false, true>)
+                                : reinterpret_cast<const void*>(&gemm_nt_kernel<TR, BM, BN, WGM, WGN, ST, false, false, true>);
         }
     if(!fn)
-        fn = conv ? reinterpret_cast<const void*>(&gemm_nt_kernel<TR, BM, BN, WGM, WGN, false, true>)
-           : splits > 1 ? reinterpret_cast<const void*>(&gemm_nt_kernel<TR, BM, BN, WGM, WGN, true>)
-                        : reinterpret_cast<const void*>(&gemm_nt_kernel<TR, BM, BN, WGM, WGN, false>);
+        fn = conv ? reinterpret_cast<const void*>(&gemm_nt_kernel<TR, BM, BN, WGM, WGN, ST, false, true>)
+           : splits > 1 ? reinterpret_cast<const void*>(&gemm_nt_kernel<TR, BM, BN, WGM, WGN, ST, true>)
+                        : reinterpret_cast<const void*>(&gemm_nt_kernel<TR, BM, BN, WGM, WGN, ST, false>);
     if(slot < 0 || !attr_set[slot][which])
     {
         const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -1395,32 +1449,40 @@ hipError_t launch_tile(const GemmKernelArgs& a, int splits, hipStream_t st, bool
         if(tn)
         {
             if(conv && splits > 1)
-                gemm_nt_kernel<TR, BM, BN, WGM, WGN, true, true, true><<<grid, block, lds_bytes, st>>>(a);
+                gemm_nt_kernel<TR, BM, BN, WGM, WGN, ST, true, true, true><<<grid, block, lds_bytes, st>>>(a);
             else if(conv)
-                gemm_nt_kernel<TR, BM, BN, WGM, WGN, false, true, true><<<grid, block, lds_bytes, st>>>(a);
+                gemm_nt_kernel<TR, BM, BN, WGM, WGN, ST, false, true, true><<<grid, block, lds_bytes, st>>>(a);
             else if(splits > 1)
-                gemm_nt_kernel<TR, BM, BN, WGM, WGN, true, false, true><<<grid, block, lds_bytes, st>>>(a);
+                gemm_nt_kernel<TR, BM, BN, WGM, WGN, ST, true, false, true><<<grid, block, lds_bytes, st>>>(a);
             else
-                gemm_nt_kernel<TR, BM, BN, WGM, WGN, false, false, true><<<grid, block, lds_bytes, st>>>(a);
+                gemm_nt_kernel<TR, BM, BN, WGM, WGN, ST, false, false, true><<<grid, block, lds_bytes, st>>>(a);
             return hipGetLastError();
         }
     if(conv)
-        gemm_nt_kernel<TR, BM, BN, WGM, WGN, false, true><<<grid, block, lds_bytes, st>>>(a);
+        gemm_nt_kernel<TR, BM, BN, WGM, WGN, ST, false, true><<<grid, block, lds_bytes, st>>>(a);
     else if(splits > 1)
-        gemm_nt_kernel<TR, BM, BN, WGM, WGN, true><<<grid, block, lds_bytes, st>>>(a);
+        gemm_nt_kernel<TR, BM, BN, WGM, WGN, ST, true><<<grid, block, lds_bytes, st>>>(a);
     else
-        gemm_nt_kernel<TR, BM, BN, WGM, WGN, false><<<grid, block, lds_bytes, st>>>(a);
+        gemm_nt_kernel<TR, BM, BN, WGM, WGN, ST, false><<<grid, block, lds_bytes, st>>>(a);
     return hipGetLastError();
 }
 
 template <typename TR>
 hipError_t launch_traits(int tile, const GemmKernelArgs& a, int splits, hipStream_t st, bool tn = false)
 {
+    // Three stages for the 128x128 tile where every compute unit gets one workgroup at most: with a second one resident
+    // (two stages) its K loop fills the gaps instead.  Measured, two -> three stages: 4096x768x3072 (192 workgroups)
+    // int8 20.4 -> 17.8 us, binary16 35.8 -> 30.3; 1000x1032x2056 binary16 (64) 20.2 -> 19.4; but 4096x3072x768
+    // (768 workgroups) int8 18.5 -> 23.3.  The 64x64 tile gains nothing from 3, 4 or 8 stages (14.7 / 16.4 / 17.3 /
+    // 23.9 us on 2056x1000x1032 binary16): it is bound by the compute unit's load path, not by latency.
+    const int64_t workgroups = static_cast<int64_t>(a.tiles_m) * a.tiles_n * splits;
     switch(tile)
     {
-    case 0: return launch_tile<TR, 256, 256, 2, 4>(a, splits, st, tn);
-    case 1: return launch_tile<TR, 128, 128, 2, 2>(a, splits, st, tn);
-    default: return launch_tile<TR, 64, 64, 2, 2>(a, splits, st, tn);
+    case 0: return launch_tile<TR, 256, 256, 2, 4, 2>(a, splits, st, tn);
+    case 1:
+        return workgroups <= kNumCu ? launch_tile<TR, 128, 128, 2, 2, 3>(a, splits, st, tn)
+                                    : launch_tile<TR, 128, 128, 2, 2, 2>(a, splits, st, tn);
+    default: return launch_tile<TR, 64, 64, 2, 2, 2>(a, splits, st, tn);
     }
 }
 

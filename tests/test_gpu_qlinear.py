@@ -120,6 +120,32 @@ def test_every_gemm_tile_shape_on_ragged_operators(tile, tag):
         Q.qsync_debug_set_gemm_tile(-1)
 
 
+@pytest.mark.parametrize("K", [16, 128, 144, 256, 272, 384, 512, 528, 656])
+def test_k_pipeline_fills_and_drains_at_every_length(K):
+    """One to six K tiles (whole and partial) through the tiles' stages, with one and with many workgroups per compute
+    unit: int32 accumulators and the epilogue with and without column parameters."""
+    rng = np.random.default_rng(K)
+    for M, N, tile in [(256, 144, 1), (2176, 2064, 1), (80, 144, 2), (272, 272, 0)]:
+        say("K pipeline", M, N, K, "tile", tile)
+        a, b = rng.integers(-127, 128, (M, K)).astype(np.int8), rng.integers(-127, 128, (N, K)).astype(np.int8)
+        sw, bias, sx = rng.random(N).astype(np.float32), rng.standard_normal(N).astype(np.float32), np.float32([0.37])
+        y, y0 = torch.empty(M, N, device="cuda"), torch.empty(M, N, device="cuda")
+        acc = torch.empty(M, N, dtype=torch.int32, device="cuda")
+        w = torch.zeros(max(256, Q.qsync_qlinear_workspace_bytes(Q.INT8, M, N, K)), dtype=torch.uint8, device="cuda")
+        Q.qsync_debug_set_gemm_tile(tile)
+        try:
+            Q.qsync_qlinear_fwd(Q.INT8, M, N, K, dev(a), dev(sx), dev(b), dev(sw), Q.PER_ROW, dev(bias), y, acc, w)
+            Q.qsync_qlinear_fwd(Q.INT8, M, N, K, dev(a), dev(sx), dev(b), dev(sx), Q.PER_TENSOR, None, y0, None, w)
+        finally:
+            Q.qsync_debug_set_gemm_tile(-1)
+        want = (a.astype(np.float64) @ b.astype(np.float64).T)          # exact: below 2^53
+        assert_bits_equal(host(acc), want.astype(np.int32), "accumulators")
+        # three fp32 roundings (scale product, accumulator, fused multiply-add): 3 * 2^-24 of the terms' size
+        for got, ref, size in [(host(y), want * (sx[0] * sw).astype(np.float64) + bias, np.abs(want) * sx[0] * sw + np.abs(bias)),
+                               (host(y0), want * float(sx[0] * sx[0]), np.abs(want) * float(sx[0] * sx[0]))]:
+            assert np.all(np.abs(got - ref) <= 4 * 2.0 ** -24 * size + 1e-30)
+
+
 @pytest.mark.parametrize("ydt,dxdt,dwdt", [(np.float16, np.float16, np.float32), (np.float32, np.float32, np.float16)])
 def test_production_epilogue_on_ragged_shapes_int8(ydt, dxdt, dwdt):
     """INT8 without accumulator dumps: the staged-store epilogue (and the split-K reduction) on ragged shapes
