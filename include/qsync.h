@@ -155,19 +155,17 @@ int qsync_quantize(const void* x, int xdt, int64_t rows, int64_t cols, int64_t l
 
 /*
  * qsync_absmax_quantize - qsync_absmax_scale (PER_TENSOR) followed by qsync_quantize (tag INT8, PER_TENSOR) on a
- * packed tensor (ld == cols), with identical results, in one launch where that pays: for a small tensor (up to
- * 4M elements, 1M with stochastic rounding) that meets the vector path's rules (cols % 8 == 0, 16-byte aligned x
- * and outputs, rows % 16 == 0 with a transposed copy) every workgroup finds the maximum of its share, they meet
- * once, and each quantizes the part it has just read; other tensors take the two launches.  Paper: Backend section, "Minimum and Maximum
- * Optimization" (the collection of the maximum is the casting cost the paper trims); Cost Mapper, cvt_cost.
+ * packed tensor (ld == cols), with identical results.  Where the vector rules hold (cols % 8 == 0, 16-byte aligned x
+ * and outputs) a tensor of up to 128 KB takes one launch, every workgroup of which reads all of it for the maximum, and
+ * a larger one two: block maxima, then a quantizing pass that folds them; other tensors take the two calls.  Paper:
+ * Backend section, "Minimum and Maximum Optimization" (the collection of the maximum is the casting cost the paper
+ * trims); Cost Mapper, cvt_cost.
  *
  * scale, inv_scale, amax_opt, q_opt, qT_opt, bits, rnd, philox_seed, philox_offset: as in the two calls.
  * workspace   at least qsync_absmax_quantize_workspace_bytes(rows, cols) bytes, 16-byte aligned; its first 4 bytes
  *             must be zero before the first use and are zero again after every call (the same rule, and the same
  *             buffer if wanted, as qsync_absmax_scale).  Calls that overlap in time need separate workspaces.
- * poll_limit  how many times a workgroup polls for the others before it finds the maximum by reading the whole
- *             tensor itself (same result; this bounds every wait, so the call cannot hang when its workgroups
- *             are not all resident at once, e.g. beside another stream's kernel).  < 0: library default.
+ * poll_limit  accepted and without effect: no workgroup waits for another.
  */
 int qsync_absmax_quantize(const void* x, int xdt, int64_t rows, int64_t cols, int bits, int rnd,
                           uint64_t philox_seed, uint64_t philox_offset,

@@ -167,11 +167,11 @@ int qsync_absmax_quantize(const void* x, int xdt, int64_t rows, int64_t cols, in
     const size_t need = qsync_absmax_quantize_workspace_bytes(rows, cols);
     if(!workspace || workspace_bytes < need) return QSYNC_ERR_WORKSPACE;
     if(!aligned16(workspace)) return QSYNC_ERR_ALIGN;
-    const int          qmax  = (1 << (bits - 1)) - 1;
-    const unsigned int polls = poll_limit < 0 ? (1u << 14) : static_cast<unsigned int>(poll_limit);
+    const int qmax = (1 << (bits - 1)) - 1;
+    (void)poll_limit;       // nothing waits any more
     return hip_status(launch_absmax_quantize(x, xdt, rows, cols, qmax, rnd, philox_seed, philox_offset, scale, inv_scale,
                                              amax_opt, static_cast<int8_t*>(q_opt), static_cast<int8_t*>(qT_opt),
-                                             workspace, polls, static_cast<hipStream_t>(stream)));
+                                             workspace, static_cast<hipStream_t>(stream)));
 }
 
 size_t qsync_qlinear_workspace_bytes(int tag, int64_t M, int64_t N, int64_t K)

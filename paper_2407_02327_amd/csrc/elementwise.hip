@@ -222,18 +222,6 @@ __global__ __launch_bounds__(BLOCK) void absmax_tensor_kernel(const T* __restric
     }
 }
 
-// Second launch of the two-launch form: one block folds the partials.
-__global__ __launch_bounds__(kBlock) void absmax_tensor_finalize_kernel(const float* __restrict__ partial, int n,
-                                                                        float qmax, float* scale, float* inv_scale,
-                                                                        float* amax_opt)
-{
-    __shared__ float lds[16];
-    float            m = 0.0f;
-    for(int i = threadIdx.x; i < n; i += kBlock) m = fmaxf(m, partial[i]);
-    m = block_reduce_max(m, lds);
-    if(threadIdx.x == 0) write_scale(m, qmax, scale, inv_scale, amax_opt, 0);
-}
-
 // Scale and inverse scale from a maximum some other kernel has collected (a GEMM epilogue); `consume` clears the
 // word for the next collection.
 __global__ void scale_from_amax_kernel(float* amax, float qmax, float* scale, float* inv_scale, int consume)
@@ -299,13 +287,13 @@ __global__ __launch_bounds__(kBlock) void absmax_rows_kernel(const T* __restrict
 // Stage 1: block (bx, by) reduces rows by*rpb + tr, + gridDim.y*rpb, ... of a strip of tpr*E
 // columns, four rows in flight per lane.  Lanes own adjacent columns (one 16-byte vector each
 // when VEC); the block's row lanes are folded through LDS, so partial[by][c] holds one value
-// per block row; a second launch folds those.  The tensor-wide maximum of OP_SUMMAX is folded
-// by the last block of the grid to arrive (ctr != nullptr).
+// per block row; a second launch folds those, and with OP_SUMMAX one more block of it folds the block maxima: a launch that is
+// needed anyway, where an arrival counter in the streaming pass cost 7 us of dependent device-scope round trips
+// (4096x3072 binary16 14.9 + 4.0 us with it).
 enum { OP_MAX = 0, OP_SUM = 1, OP_SUMMAX = 2 };
 
 struct TensorFinal          // OP_SUMMAX: where the tensor-wide result goes
 {
-    unsigned int* ctr;      // arrival counter; nullptr: a second launch folds the block maxima
     float         qmax;
     float*        scale;
     float*        inv_scale;
@@ -323,7 +311,6 @@ __global__ __launch_bounds__(BLOCK) void colreduce_kernel(const T* __restrict__ 
     constexpr int U = 4;                                    // rows in flight per lane
     __shared__ float lds[BLOCK * E];
     __shared__ float lds_max[16];
-    __shared__ bool  flag;
     RunMax<T>        rm;                                    // OP_SUMMAX only
     float            sqv     = 0.0f;                        // OP_SUMMAX with fin.sumsq_opt: sum of squares
     const bool       want_sq = OP == OP_SUMMAX && fin.sumsq_opt != nullptr;
@@ -398,12 +385,12 @@ __global__ __launch_bounds__(BLOCK) void colreduce_kernel(const T* __restrict__ 
     if(OP == OP_SUMMAX)
     {   // every thread of the block takes part (threads beyond the last column carry 0)
         const float bm = block_reduce_max(rm.get(), lds_max);
-        if(threadIdx.x == 0) st_partial(partial_max + blockIdx.y * gridDim.x + blockIdx.x, bm);
+        if(threadIdx.x == 0) partial_max[blockIdx.y * gridDim.x + blockIdx.x] = bm;
         if(want_sq)
         {
             __syncthreads();
             const float bs = block_reduce_sum(sqv, lds_max);
-            if(threadIdx.x == 0) st_partial(fin.partial_sq + blockIdx.y * gridDim.x + blockIdx.x, bs);
+            if(threadIdx.x == 0) fin.partial_sq[blockIdx.y * gridDim.x + blockIdx.x] = bs;
         }
     }
     // fold the block's row lanes in order 0, 1, ... through LDS
@@ -426,36 +413,30 @@ __global__ __launch_bounds__(BLOCK) void colreduce_kernel(const T* __restrict__ 
 #pragma unroll
         for(int e = 0; e < E; ++e) partial[static_cast<int64_t>(blockIdx.y) * cols + c0 + e] = acc[e];
     }
-    if(OP != OP_SUMMAX || !fin.ctr) return;
-
-    // ---- tensor-wide maximum: the last block of the whole grid
-    const unsigned int nblocks = gridDim.x * gridDim.y;
-    if(last_arrival(fin.ctr, nblocks, &flag))
-    {
-        if(want_sq)
-        {   // the strip buffer is free by now: borrow it for the fold
-            fold_sumsq(fin.partial_sq, nblocks, fin.sumsq_opt, reinterpret_cast<double*>(lds), BLOCK * E / 2);
-            __syncthreads();
-        }
-        float mm = 0.0f;
-        for(unsigned int i = threadIdx.x; i < nblocks; i += BLOCK) mm = fmaxf(mm, ld_partial(partial_max + i));
-        mm = block_reduce_max(mm, lds_max);
-        if(threadIdx.x == 0)
-        {
-            write_scale(mm, fin.qmax, fin.scale, fin.inv_scale, fin.amax_opt, 0);
-            *fin.ctr = 0u;
-        }
-    }
 }
 
 // Second launch of the two-launch form: 16 columns per block; sixteen threads per column fold a
 // sixteenth of the partials each (fixed assignment, fixed order), then the sixteen are folded in order.
+// OP_SUMMAX: the last block folds the `nmax` block maxima (and sums of squares) of the tensor instead.
 template <int OP>
 __global__ __launch_bounds__(kBlock) void colreduce_finalize_kernel(const float* __restrict__ partial, int S,
                                                                     int64_t cols, float qmax, float* out,
-                                                                    float* inv_scale, float* amax_opt)
+                                                                    float* inv_scale, float* amax_opt,
+                                                                    const float* __restrict__ partial_max, int nmax,
+                                                                    const TensorFinal fin)
 {
     __shared__ float lds[kBlock];
+    if constexpr(OP == OP_SUMMAX)
+        if(blockIdx.x == gridDim.x - 1)
+        {
+            __shared__ double lds_d[kAbsmaxMaxBlocks];
+            float             mm = 0.0f;
+            for(int i = threadIdx.x; i < nmax; i += kBlock) mm = fmaxf(mm, partial_max[i]);
+            mm = block_reduce_max(mm, lds);
+            if(threadIdx.x == 0) write_scale(mm, fin.qmax, fin.scale, fin.inv_scale, fin.amax_opt, 0);
+            if(fin.sumsq_opt) fold_sumsq(fin.partial_sq, static_cast<unsigned int>(nmax), fin.sumsq_opt, lds_d, kAbsmaxMaxBlocks);
+            return;
+        }
     const int     tc = threadIdx.x % 16, q = threadIdx.x / 16;
     const int64_t c  = static_cast<int64_t>(blockIdx.x) * 16 + tc;
     float         acc = 0.0f;
@@ -481,83 +462,337 @@ __global__ __launch_bounds__(kBlock) void colreduce_finalize_kernel(const float*
     }
 }
 
-// ------------------------------------------------------------------ weights: row and column maxima in one pass
-// Block b owns rows b*R .. b*R+R-1 in full: a thread sweeps its 16-byte column vectors with the R
-// row loads of a vector in flight together, keeps the running maximum of every row in registers and
-// writes the column maxima of its row group to partial[b][c] (folded by colreduce_finalize_kernel).
-// Row maxima are complete inside the block: wave shuffles, one LDS exchange, then scale and inverse.
-// Maxima are order independent, so the results equal those of the separate per-row and per-column passes.
-template <typename T, int R, int U>
-__global__ __launch_bounds__(kBlock) void absmax_rowcol_kernel(const T* __restrict__ x, int64_t rows, int64_t cols,
-                                                               int64_t ld, float qmax, float* row_scale, float* row_inv,
-                                                               float* row_amax_opt, float* __restrict__ col_partial)
+// ------------------------------------------------------------------ INT8 quantize, tiled through LDS
+// A workgroup owns a tile of TR rows x 128 columns, a thread four rows x eight columns of it (one Philox block per
+// row, four 16-byte loads in flight for binary16, eight for fp32).  The codes of a row leave as 8-byte stores, 128
+// contiguous bytes per tile row; the transposed copy goes through LDS as dwords of four rows (a 4x4 byte transpose in
+// registers) and leaves as 16-byte stores, TR contiguous bytes per column.  16-byte chunks of a column are
+// XOR-swizzled with (column / 8) % 8: writes are two-way, reads conflict free.
+// What bounds it is memory latency at small sizes: against one 16 x 32-byte patch per lane with strided 8 or 16-byte
+// transposed stores this keeps four times the wavefronts in flight and writes whole lines.
+constexpr int kTileCols = 128;
+
+// Maximum over the whole workgroup, handed to every thread.
+template <int THREADS> __device__ __forceinline__ float block_max_all(float v, float* lds /* THREADS / 64 floats */)
 {
-    constexpr int E = Vec16<T>::N;
-    __shared__ float lds[R][kBlock / kWaveSize];
-    const int64_t r0  = static_cast<int64_t>(blockIdx.x) * R;
-    const int64_t ncv = cols / E;                    // cols % E == 0 on this path
-    float         rowm[R];
+    v = wave_reduce_max(v);
+    if(threadIdx.x % kWaveSize == 0) lds[threadIdx.x / kWaveSize] = v;
+    __syncthreads();
+    float m = lds[0];
 #pragma unroll
-    for(int i = 0; i < R; ++i) rowm[i] = 0.0f;
-    for(int64_t cv0 = threadIdx.x; cv0 < ncv; cv0 += static_cast<int64_t>(kBlock) * U)
+    for(int w = 1; w < THREADS / kWaveSize; ++w) m = fmaxf(m, lds[w]);
+    return m;
+}
+
+// Where a per-tensor quantizer takes its scale from.  kInv: the inverse scale in memory.  kPartials: block maxima of
+// an earlier launch, folded by every workgroup (at most kFoldMax of them: a load or two per thread, hidden behind the
+// tile's own loads), which saves the maximum pass its arrival counter -- 5 us of dependent device-scope round trips --
+// and this pass a launch between them.  kWhole: the workgroup finds the maximum of the whole tensor by itself.
+enum ScaleFrom { kInv = 0, kPartials = 1, kWhole = 2 };
+constexpr int kFoldMax = 256;
+struct TensorScale
+{
+    const float* inv;            // kInv
+    const float* partial;        // kPartials: n block maxima
+    int          n;
+    float*       scale;          // kPartials, kWhole: written by workgroup 0
+    float*       inv_out;
+    float*       amax_opt;
+};
+
+// The inverse scale of the tensor in every thread (contains barriers; lds: THREADS / 64 floats).
+template <typename T, int SRC, int THREADS>
+__device__ __forceinline__ float tensor_inverse_scale(const TensorScale& ts, const T* __restrict__ x, int64_t n, int qmax,
+                                                      float* lds)
+{
+    if constexpr(SRC == kInv) return ts.inv[0];
+    float m = 0.0f;
+    if constexpr(SRC == kPartials)
     {
-        uint4 raw[U][R];                             // R x U loads in flight
-#pragma unroll
-        for(int u = 0; u < U; ++u)
-#pragma unroll
-            for(int i = 0; i < R; ++i)
-            {
-                const int64_t cv = cv0 + u * kBlock;
-                raw[u][i] = (r0 + i < rows && cv < ncv) ? *reinterpret_cast<const uint4*>(x + (r0 + i) * ld + cv * E)
-                                                         : make_uint4(0, 0, 0, 0);
-            }
-#pragma unroll
-        for(int u = 0; u < U; ++u)
+        for(int i = threadIdx.x; i < ts.n; i += THREADS) m = fmaxf(m, ts.partial[i]);
+    }
+    else
+    {   // (contiguous, 16-byte aligned, whole vectors)
+        constexpr int U    = 8;
+        const int64_t nvec = n / Vec16<T>::N;
+        const uint4*  xv   = reinterpret_cast<const uint4*>(x);
+        RunMax<T>     rm;
+        for(int64_t c = threadIdx.x; c < nvec; c += static_cast<int64_t>(THREADS) * U)
         {
-            const int64_t cv = cv0 + u * kBlock;
-            float         cm[E];
+            uint4 v[U];
 #pragma unroll
-            for(int e = 0; e < E; ++e) cm[e] = 0.0f;
+            for(int u = 0; u < U; ++u) v[u] = c + u * THREADS < nvec ? xv[c + u * THREADS] : make_uint4(0, 0, 0, 0);
 #pragma unroll
-            for(int i = 0; i < R; ++i)
-            {
-                float v[E];
-                Vec16<T>::decode(raw[u][i], v);
+            for(int u = 0; u < U; ++u) rm.add(v[u]);
+        }
+        m = rm.get();
+    }
+    m = block_max_all<THREADS>(m, lds);
+    if(blockIdx.x == 0 && threadIdx.x == 0) write_scale(m, static_cast<float>(qmax), ts.scale, ts.inv_out, ts.amax_opt, 0);
+    return m != 0.0f ? __fdiv_rn(static_cast<float>(qmax), m) : 1.0f;
+}
+
+// One thread's share of a tile: rows r0 .. r0 + 3, columns c0 .. c0 + 7 (absent ones are zero).
+template <typename T> struct TileShare
+{
+    static constexpr int VG = 8 / Vec16<T>::N;       // 16-byte loads per row
+    uint4 raw[4][VG];
+    __device__ __forceinline__ void load(const T* __restrict__ x, int64_t r0, int64_t c0, int64_t rows, int64_t cols, int64_t ld)
+    {
 #pragma unroll
-                for(int e = 0; e < E; ++e)
-                {
-                    const float a = fabsf(v[e]);
-                    cm[e]   = fmaxf(cm[e], a);
-                    rowm[i] = fmaxf(rowm[i], a);
-                }
-            }
-            if(cv < ncv)
-            {
-                float* dst = col_partial + static_cast<int64_t>(blockIdx.x) * cols + cv * E;
+        for(int i = 0; i < 4; ++i)
 #pragma unroll
-                for(int e = 0; e < E; e += 4)
-                    *reinterpret_cast<float4*>(dst + e) = make_float4(cm[e], cm[e + 1], cm[e + 2], cm[e + 3]);
-            }
+            for(int l = 0; l < VG; ++l)
+                raw[i][l] = (r0 + i < rows && c0 < cols) ? *reinterpret_cast<const uint4*>(x + (r0 + i) * ld + c0 + l * Vec16<T>::N)
+                                                         : make_uint4(0, 0, 0, 0);
+    }
+    __device__ __forceinline__ void decode(int i, float (&v)[8]) const
+    {
+#pragma unroll
+        for(int l = 0; l < VG; ++l)
+        {
+            float t[Vec16<T>::N];
+            Vec16<T>::decode(raw[i][l], t);
+#pragma unroll
+            for(int e = 0; e < Vec16<T>::N; ++e) v[l * Vec16<T>::N + e] = t[e];
         }
     }
-    const int lane = threadIdx.x % kWaveSize, wave = threadIdx.x / kWaveSize;
+};
+
+// 4 x 8 codes (two dwords per row) -> eight dwords, one per column, row 0 in the low byte
+__device__ __forceinline__ void transpose_codes_4x8(const uint32_t (&code)[4][2], uint32_t (&t)[8])
+{
 #pragma unroll
-    for(int i = 0; i < R; ++i)
-    {
-        const float m = wave_reduce_max(rowm[i]);
-        if(lane == 0) lds[i][wave] = m;
-    }
-    __syncthreads();
-    if(threadIdx.x < R && r0 + threadIdx.x < rows)
-    {
-        float m = lds[threadIdx.x][0];
-#pragma unroll
-        for(int w = 1; w < kBlock / kWaveSize; ++w) m = fmaxf(m, lds[threadIdx.x][w]);
-        write_scale(m, qmax, row_scale, row_inv, row_amax_opt, r0 + threadIdx.x);
+    for(int w = 0; w < 2; ++w)
+    {   // v_perm_b32: selector bytes 0-3 take from the second operand, 4-7 from the first
+        const uint32_t lo01 = __builtin_amdgcn_perm(code[1][w], code[0][w], 0x05010400u);
+        const uint32_t hi01 = __builtin_amdgcn_perm(code[1][w], code[0][w], 0x07030602u);
+        const uint32_t lo23 = __builtin_amdgcn_perm(code[3][w], code[2][w], 0x05010400u);
+        const uint32_t hi23 = __builtin_amdgcn_perm(code[3][w], code[2][w], 0x07030602u);
+        t[4 * w + 0] = __builtin_amdgcn_perm(lo23, lo01, 0x05040100u);
+        t[4 * w + 1] = __builtin_amdgcn_perm(lo23, lo01, 0x07060302u);
+        t[4 * w + 2] = __builtin_amdgcn_perm(hi23, hi01, 0x05040100u);
+        t[4 * w + 3] = __builtin_amdgcn_perm(hi23, hi01, 0x07060302u);
     }
 }
 
-// ------------------------------------------------------------------ INT8 quantize, vector path
+// Transposed codes of a tile through LDS: `trow(c)` is the row of qT that column c lands in.
+template <int TR, typename F>
+__device__ __forceinline__ void store_transposed_tile(const uint32_t (&t)[8], uint8_t* lds_t, int64_t tile_r, int64_t tile_c,
+                                                      int64_t rows, int64_t cols, int8_t* __restrict__ qT, F&& trow)
+{
+    constexpr int THREADS = TR * 4, CH = TR / 16;            // 16-byte chunks per column
+    const int cg = threadIdx.x % 16, quad = threadIdx.x / 16;
+#pragma unroll
+    for(int j = 0; j < 8; ++j)
+        *reinterpret_cast<uint32_t*>(lds_t + (8 * cg + j) * TR + (((quad / 4) ^ (cg % CH)) * 16) + (quad % 4) * 4) = t[j];
+    __syncthreads();
+#pragma unroll
+    for(int k = threadIdx.x; k < kTileCols * CH; k += THREADS)
+    {
+        const int     col = k / CH, ch = k % CH;
+        const uint4   v   = *reinterpret_cast<const uint4*>(lds_t + col * TR + ((ch ^ ((col / 8) % CH)) * 16));
+        const int64_t r   = tile_r + 16 * ch, c = tile_c + col;
+        if(c >= cols || r >= rows) continue;
+        int8_t* dst = qT + trow(c) * rows + r;
+        if(rows % 16 == 0)
+            *reinterpret_cast<uint4*>(dst) = v;
+        else
+        {
+            const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+            for(int b = 0; b < 16; ++b)
+                if(r + b < rows) dst[b] = static_cast<int8_t>((w[b / 4] >> (8 * (b % 4))) & 0xFFu);
+        }
+    }
+}
+
+// Per-tensor scale.  Needs cols % 8 == 0, 16-byte aligned rows of x, 8-byte aligned q; qT 16-byte aligned when
+// rows % 16 == 0 (any alignment and byte stores otherwise).
+template <typename T, int RND, int TR, int SRC>
+__global__ __launch_bounds__(TR * 4) void quantize_tile_kernel(const T* __restrict__ x, int64_t rows, int64_t cols, int64_t ld,
+                                                               int qmax, uint64_t seed, uint64_t offset, const TensorScale ts,
+                                                               int8_t* __restrict__ q, int8_t* __restrict__ qT, int tiles_x)
+{
+    __shared__ __attribute__((aligned(16))) uint8_t lds_t[TR * kTileCols];
+    __shared__ float lds_m[TR * 4 / kWaveSize];
+    const int     by = static_cast<int>(blockIdx.x) / tiles_x, bx = static_cast<int>(blockIdx.x) - by * tiles_x;
+    const int64_t tile_r = static_cast<int64_t>(by) * TR, tile_c = static_cast<int64_t>(bx) * kTileCols;
+    const int64_t r0 = tile_r + (threadIdx.x / 16) * 4, c0 = tile_c + (threadIdx.x % 16) * 8;
+    TileShare<T>  s;
+    s.load(x, r0, c0, rows, cols, ld);
+    const float   inv = tensor_inverse_scale<T, SRC, TR * 4>(ts, x, rows * cols, qmax, lds_m);
+    uint32_t      code[4][2];
+#pragma unroll
+    for(int i = 0; i < 4; ++i)
+    {
+        float v[8];
+        s.decode(i, v);
+        uint4 blk = {0u, 0u, 0u, 0u};
+        if(RND == kStochastic) blk = philox_group(seed, offset, static_cast<uint64_t>((r0 + i) * cols + c0) >> 3);
+        code[i][0] = code[i][1] = 0u;
+#pragma unroll
+        for(int j = 0; j < 8; ++j)
+            code[i][j / 4] |= (static_cast<uint32_t>(quantize_code<RND>(v[j], inv, qmax, philox_draw16(blk, j))) & 0xFFu) << (8 * (j % 4));
+        if(q && r0 + i < rows && c0 < cols) *reinterpret_cast<uint2*>(q + (r0 + i) * cols + c0) = make_uint2(code[i][0], code[i][1]);
+    }
+    if(!qT) return;
+    uint32_t t[8];
+    transpose_codes_4x8(code, t);
+    store_transposed_tile<TR>(t, lds_t, tile_r, tile_c, rows, cols, qT, [](int64_t c) { return c; });
+}
+
+// ------------------------------------------------------------------ weights: two quantizations in two launches
+// The forward wants codes with one scale per row, dX transposed codes with one scale per column.  The first launch
+// leaves, per 64 x 128 tile, the maxima of its rows (row_part[bx][row]) and -- per group of row tiles, at most
+// kWeightGroups of them -- of its columns (col_part[by][col]).  The second folds what its own tile needs of both
+// (a few loads per thread, behind the tile's own loads), so no launch stands between them to fold anything, and
+// converts; the first tile column and tile row write the scales out.  Maxima are order free: the results are those of
+// the separate passes.
+constexpr int kWeightTileRows = 64, kWeightGroups = 64;
+
+template <typename T>
+__global__ __launch_bounds__(256) void weight_maxima_kernel(const T* __restrict__ x, int64_t rows, int64_t cols, int tiles_x,
+                                                            int groups, float* __restrict__ row_part, float* __restrict__ col_part)
+{
+    constexpr int TR = kWeightTileRows;
+    __shared__ float lds[4][kTileCols];
+    const int     by = static_cast<int>(blockIdx.x) / tiles_x, bx = static_cast<int>(blockIdx.x) - by * tiles_x;
+    const int     cg = threadIdx.x % 16, quad = threadIdx.x / 16;
+    const int64_t c0 = static_cast<int64_t>(bx) * kTileCols + cg * 8;
+    float         cm[8];
+#pragma unroll
+    for(int j = 0; j < 8; ++j) cm[j] = 0.0f;
+    for(int64_t tile_r = static_cast<int64_t>(by) * TR; tile_r < rows; tile_r += static_cast<int64_t>(groups) * TR)
+    {
+        const int64_t r0 = tile_r + quad * 4;
+        TileShare<T>  s;
+        s.load(x, r0, c0, rows, cols, cols);
+#pragma unroll
+        for(int i = 0; i < 4; ++i)
+        {
+            float v[8], rm = 0.0f;
+            s.decode(i, v);
+#pragma unroll
+            for(int j = 0; j < 8; ++j)
+            {
+                const float a = fabsf(v[j]);
+                cm[j] = fmaxf(cm[j], a);
+                rm    = fmaxf(rm, a);
+            }
+#pragma unroll
+            for(int off = 8; off > 0; off >>= 1) rm = fmaxf(rm, __shfl_xor(rm, off, kWaveSize));     // the 16 lanes of a row
+            if(cg == 0 && r0 + i < rows) row_part[bx * rows + r0 + i] = rm;
+        }
+    }
+#pragma unroll
+    for(int j = 0; j < 8; ++j)
+    {   // the four row quads of the wavefront, then the four wavefronts
+        cm[j] = fmaxf(cm[j], __shfl_xor(cm[j], 16, kWaveSize));
+        cm[j] = fmaxf(cm[j], __shfl_xor(cm[j], 32, kWaveSize));
+    }
+    if(quad % 4 == 0)
+#pragma unroll
+        for(int j = 0; j < 8; ++j) lds[quad / 4][cg * 8 + j] = cm[j];
+    __syncthreads();
+    const int64_t c = static_cast<int64_t>(bx) * kTileCols + threadIdx.x;
+    if(threadIdx.x < kTileCols && c < cols)
+        col_part[by * cols + c] = fmaxf(fmaxf(lds[0][threadIdx.x], lds[1][threadIdx.x]), fmaxf(lds[2][threadIdx.x], lds[3][threadIdx.x]));
+}
+
+struct WeightOut
+{
+    float*  row_scale; float* row_inv; float* row_amax_opt;
+    float*  col_scale; float* col_inv;
+    int8_t* wq;
+    int8_t* wqT;
+};
+// conv_C > 0 (3x3 convolution weights [N, 9 * C]): the column scale belongs to the input channel c = column % C, i.e. it
+// covers the nine columns (tap, c), and column (tap, c) lands in row c * 9 + (8 - tap) of the transposed copy, the
+// mirrored, channel-exchanged weights.
+template <typename T>
+__global__ __launch_bounds__(256) void weight_quantize_kernel(const T* __restrict__ x, int64_t rows, int64_t cols, int qmax,
+                                                              int tiles_x, int groups, const float* __restrict__ row_part,
+                                                              const float* __restrict__ col_part, const WeightOut o, int conv_C)
+{
+    constexpr int TR = kWeightTileRows;
+    __shared__ __attribute__((aligned(16))) uint8_t lds_t[TR * kTileCols];
+    __shared__ float lds_c[2][kTileCols], lds_r[4][TR], inv_c[kTileCols], inv_r[TR];
+    const int     by = static_cast<int>(blockIdx.x) / tiles_x, bx = static_cast<int>(blockIdx.x) - by * tiles_x;
+    const int64_t tile_r = static_cast<int64_t>(by) * TR, tile_c = static_cast<int64_t>(bx) * kTileCols;
+    const int     cg = threadIdx.x % 16, quad = threadIdx.x / 16;
+    const int64_t r0 = tile_r + quad * 4, c0 = tile_c + cg * 8;
+    TileShare<T>  s;
+    s.load(x, r0, c0, rows, cols, cols);
+    {   // columns: two threads each; rows: four threads each
+        const int     cc = threadIdx.x % kTileCols, half = threadIdx.x / kTileCols;
+        const int64_t c  = tile_c + cc;
+        float         m  = 0.0f;
+        if(c < cols)
+        {
+            const int64_t step = conv_C > 0 ? conv_C : cols;          // conv: [groups][9][C] read as groups * 9 rows of C
+            const int     n    = conv_C > 0 ? groups * 9 : groups;
+            const float*  src  = col_part + (conv_C > 0 ? static_cast<int64_t>(static_cast<uint32_t>(c) % static_cast<uint32_t>(conv_C)) : c);
+#pragma unroll 8
+            for(int g = half; g < n; g += 2) m = fmaxf(m, src[g * step]);
+        }
+        lds_c[half][cc] = m;
+        const int     rr = threadIdx.x % TR, part = threadIdx.x / TR;
+        const int64_t r  = tile_r + rr;
+        m = 0.0f;
+        if(r < rows)
+#pragma unroll 4
+            for(int b = part; b < tiles_x; b += 4) m = fmaxf(m, row_part[b * rows + r]);
+        lds_r[part][rr] = m;
+    }
+    __syncthreads();
+    const float fq = static_cast<float>(qmax);
+    if(threadIdx.x < kTileCols)
+    {
+        const int     t = threadIdx.x;
+        const float   m = fmaxf(lds_c[0][t], lds_c[1][t]);
+        const int64_t c = tile_c + t;
+        inv_c[t] = m != 0.0f ? __fdiv_rn(fq, m) : 1.0f;
+        if(by == 0 && c < (conv_C > 0 ? conv_C : cols)) write_scale(m, fq, o.col_scale, o.col_inv, nullptr, c);
+    }
+    else if(threadIdx.x < kTileCols + TR)
+    {
+        const int     t = threadIdx.x - kTileCols;
+        const float   m = fmaxf(fmaxf(lds_r[0][t], lds_r[1][t]), fmaxf(lds_r[2][t], lds_r[3][t]));
+        inv_r[t] = m != 0.0f ? __fdiv_rn(fq, m) : 1.0f;
+        if(bx == 0 && tile_r + t < rows) write_scale(m, fq, o.row_scale, o.row_inv, o.row_amax_opt, tile_r + t);
+    }
+    __syncthreads();
+    float fc[8];
+#pragma unroll
+    for(int j = 0; j < 8; ++j) fc[j] = inv_c[cg * 8 + j];
+    uint32_t codeT[4][2];
+#pragma unroll
+    for(int i = 0; i < 4; ++i)
+    {
+        float v[8];
+        s.decode(i, v);
+        const float fr = inv_r[quad * 4 + i];
+        uint32_t    code[2] = {0u, 0u};
+        codeT[i][0] = codeT[i][1] = 0u;
+#pragma unroll
+        for(int j = 0; j < 8; ++j)
+        {
+            code[j / 4]     |= (static_cast<uint32_t>(quantize_code<kNearest>(v[j], fr, qmax, 0u)) & 0xFFu) << (8 * (j % 4));
+            codeT[i][j / 4] |= (static_cast<uint32_t>(quantize_code<kNearest>(v[j], fc[j], qmax, 0u)) & 0xFFu) << (8 * (j % 4));
+        }
+        if(r0 + i < rows && c0 < cols) *reinterpret_cast<uint2*>(o.wq + (r0 + i) * cols + c0) = make_uint2(code[0], code[1]);
+    }
+    uint32_t t[8];
+    transpose_codes_4x8(codeT, t);
+    store_transposed_tile<TR>(t, lds_t, tile_r, tile_c, rows, cols, o.wqT, [&](int64_t c) {
+        if(conv_C == 0) return c;
+        const uint32_t tap = static_cast<uint32_t>(c) / static_cast<uint32_t>(conv_C);
+        return (c - static_cast<int64_t>(tap) * conv_C) * 9 + (8 - tap);
+    });
+}
+
+// ------------------------------------------------------------------ INT8 quantize, vector path of per-row and per-column scales
 // Each lane owns a patch of 16 (or 8) rows x 32 input bytes (16 binary16 or 8 fp32 columns) and
 // requests the eight 16-byte loads of four rows together before it converts them.  A wavefront is up
 // to 8 patches wide (fewer for narrow matrices, so that no lane idles) and the rest of its lanes
@@ -570,20 +805,13 @@ __global__ __launch_bounds__(kBlock) void absmax_rowcol_kernel(const T* __restri
 
 __device__ __forceinline__ uint32_t byte_of(uint32_t w, int b) { return (w >> (8 * b)) & 0xFFu; }
 
-// `block` is the workgroup's index in the patch grid; GIVEN: the per-tensor inverse scale arrives as a value
-// (a kernel that has just computed it) instead of through inv_scale.
-template <typename T, int RND, bool PERCOL, int PR, bool DUAL, bool GIVEN>
-__device__ __forceinline__ void quantize_patch_body(int64_t block, float inv_given, const T* __restrict__ x, int64_t rows,
-                                                    int64_t cols, int64_t ld, int qmax, int gran, uint64_t seed,
-                                                    uint64_t offset, const float* __restrict__ inv_scale,
-                                                    int8_t* __restrict__ q, int8_t* __restrict__ qT, int64_t grid_x,
-                                                    int lpr_log2, const float* __restrict__ inv_scale_T, int flip_C)
+template <typename T, int RND, bool PERCOL, int PR>
+__global__ __launch_bounds__(kBlock, 3) void quantize_patch_kernel(const T* __restrict__ x, int64_t rows, int64_t cols,
+                                                                int64_t ld, int qmax, uint64_t seed,
+                                                                uint64_t offset, const float* __restrict__ inv_scale,
+                                                                int8_t* __restrict__ q, int8_t* __restrict__ qT,
+                                                                int64_t grid_x, int lpr_log2)
 {
-    // DUAL (weights): q takes the scales of `gran` (per row), the transposed copy takes one scale per column
-    // from inv_scale_T -- two quantizations of the same values from one read.  flip_C > 0 (3x3 convolution
-    // weights [N, 9*C]): the column scale belongs to the input channel c = column % C and column (tap, c)
-    // lands in row c*9 + (8 - tap) of the transposed copy, i.e. the mirrored, channel-exchanged weights.
-    static_assert(!DUAL || (!PERCOL && RND != kStochastic), "dual scales: nearest/floor, row scales for q");
     // A lane converts a patch of PR rows x PCOLS columns; the 2^lpr_log2 lanes of a wavefront that share
     // rows cover a contiguous row segment, the other lane bits stack patches downwards.  Narrow matrices
     // use fewer lanes per row (no idle lanes), small ones shorter patches (more wavefronts in flight).
@@ -593,24 +821,18 @@ __device__ __forceinline__ void quantize_patch_body(int64_t block, float inv_giv
     constexpr int CW    = PCOLS / 4;              // code dwords per patch row
     const int     wtile_r = (kWaveSize >> lpr_log2) * PR, wtile_c = PCOLS << lpr_log2;
     const int     lane = threadIdx.x % kWaveSize, wave = threadIdx.x / kWaveSize;
-    const int64_t by   = block / grid_x, bx = block - by * grid_x;
+    const int64_t by   = blockIdx.x / grid_x, bx = blockIdx.x - by * grid_x;
     const int64_t r0   = (by * (kBlock / kWaveSize) + wave) * wtile_r + (lane >> lpr_log2) * PR;
     const int64_t c0   = bx * wtile_c + (lane & ((1 << lpr_log2) - 1)) * PCOLS;
     if(r0 >= rows || c0 >= cols) return;
     const bool second_ok = NH == 1 || c0 + 8 < cols;      // binary16: the patch's second 8 columns exist
 
     float fcol[PCOLS];
-    if(PERCOL || DUAL)
-    {
-        const float* cs = DUAL ? inv_scale_T : inv_scale;
+    if(PERCOL)
 #pragma unroll
-        for(int j = 0; j < PCOLS; ++j)
-            fcol[j] = (j < 8 || second_ok) ? cs[(DUAL && flip_C > 0) ? (c0 + j) % flip_C : (c0 + j)] : 1.0f;
-    }
-    const float ftensor = GIVEN ? inv_given : ((!PERCOL && gran == kPerTensor) ? inv_scale[0] : 1.0f);
+        for(int j = 0; j < PCOLS; ++j) fcol[j] = (j < 8 || second_ok) ? inv_scale[c0 + j] : 1.0f;
 
     uint32_t code[PR][CW];   // row i, columns 4w..4w+3 in dword w
-    uint32_t codeT[DUAL ? PR : 1][CW];   // DUAL: the codes of the transposed copy
     constexpr int RB = 4;                // rows per batch
 #pragma unroll
     for(int batch = 0; batch < PR / RB; ++batch)
@@ -632,7 +854,7 @@ __device__ __forceinline__ void quantize_patch_body(int64_t block, float inv_giv
         {
             const int     i    = batch * RB + ii;
             const int64_t r    = r0 + i;
-            const float   frow = PERCOL ? 1.0f : ((gran == kPerRow && r < rows) ? inv_scale[r] : ftensor);
+            const float   frow = (!PERCOL && r < rows) ? inv_scale[r] : 1.0f;
             float         v[PCOLS];
             float         t0[E], t1[E];
             Vec16<T>::decode(raw[ii][0], t0);
@@ -645,17 +867,6 @@ __device__ __forceinline__ void quantize_patch_body(int64_t block, float inv_giv
             }
 #pragma unroll
             for(int w = 0; w < CW; ++w) code[i][w] = 0u;
-            if constexpr(DUAL)
-            {
-#pragma unroll
-                for(int w = 0; w < CW; ++w) codeT[i][w] = 0u;
-#pragma unroll
-                for(int col = 0; col < PCOLS; ++col)
-                {
-                    const int c = quantize_code<RND>(v[col], fcol[col], qmax, 0u);
-                    codeT[i][col / 4] |= (static_cast<uint32_t>(c) & 0xFFu) << (8 * (col % 4));
-                }
-            }
 #pragma unroll
             for(int h = 0; h < NH; ++h)
             {
@@ -709,56 +920,32 @@ __device__ __forceinline__ void quantize_patch_body(int64_t block, float inv_giv
 #pragma unroll
             for(int g = 0; g < PR / 4; ++g)
             {
-                auto pick = [&](int r, int w) -> uint32_t {
-                    if constexpr(DUAL) return codeT[r][w]; else return code[r][w];
-                };
-                t[g] = byte_of(pick(4 * g + 0, col / 4), col % 4) | (byte_of(pick(4 * g + 1, col / 4), col % 4) << 8)
-                     | (byte_of(pick(4 * g + 2, col / 4), col % 4) << 16)
-                     | (byte_of(pick(4 * g + 3, col / 4), col % 4) << 24);
+                t[g] = byte_of(code[4 * g + 0][col / 4], col % 4) | (byte_of(code[4 * g + 1][col / 4], col % 4) << 8)
+                     | (byte_of(code[4 * g + 2][col / 4], col % 4) << 16)
+                     | (byte_of(code[4 * g + 3][col / 4], col % 4) << 24);
             }
-            int64_t trow = c0 + col;
-            if(DUAL && flip_C > 0)
-            {
-                const int64_t tap = trow / flip_C;
-                trow = (trow - tap * flip_C) * 9 + (8 - tap);
-            }
-            int8_t* dst = qT + trow * rows + r0;
+            int8_t* dst = qT + (c0 + col) * rows + r0;
             if constexpr(PR == 16)
                 *reinterpret_cast<uint4*>(dst) = make_uint4(t[0], t[1], t[2], t[3]);
-            else if constexpr(PR == 8)
-                *reinterpret_cast<uint2*>(dst) = make_uint2(t[0], t[1]);
             else
-                *reinterpret_cast<uint32_t*>(dst) = t[0];
+                *reinterpret_cast<uint2*>(dst) = make_uint2(t[0], t[1]);
         }
     }
-}
-
-template <typename T, int RND, bool PERCOL, int PR, bool DUAL = false>
-__global__ __launch_bounds__(kBlock, 3) void quantize_patch_kernel(const T* __restrict__ x, int64_t rows, int64_t cols,
-                                                                int64_t ld, int qmax, int gran, uint64_t seed,
-                                                                uint64_t offset, const float* __restrict__ inv_scale,
-                                                                int8_t* __restrict__ q, int8_t* __restrict__ qT,
-                                                                int64_t grid_x, int lpr_log2,
-                                                                const float* __restrict__ inv_scale_T = nullptr,
-                                                                int flip_C = 0)
-{
-    quantize_patch_body<T, RND, PERCOL, PR, DUAL, false>(blockIdx.x, 1.0f, x, rows, cols, ld, qmax, gran, seed, offset,
-                                                         inv_scale, q, qT, grid_x, lpr_log2, inv_scale_T, flip_C);
 }
 
 // ------------------------------------------------------------------ INT8 quantize, row-major codes only
 // Contiguous tensor, one scale, no transposed copy: nothing ties a lane to a patch, so the lanes of a wavefront take
 // adjacent groups of 8 elements (one Philox block each; a load instruction of a wavefront covers 1 KB of consecutive
 // memory for binary16 input) with U groups in flight per lane, and the 8 codes of a group leave as one 8-byte store.
-template <typename T, int RND>
+template <typename T, int RND, int SRC>
 __global__ __launch_bounds__(kBlock) void quantize_stream_kernel(const T* __restrict__ x, int64_t ngroups, int qmax,
-                                                                 uint64_t seed, uint64_t offset,
-                                                                 const float* __restrict__ inv_scale, int8_t* __restrict__ q)
+                                                                 uint64_t seed, uint64_t offset, const TensorScale ts,
+                                                                 int8_t* __restrict__ q)
 {
+    __shared__ float lds_m[kBlock / kWaveSize];
     constexpr int E  = Vec16<T>::N;       // elements per 16-byte load (8 or 4)
     constexpr int VG = 8 / E;             // loads per group
     constexpr int U  = 4;
-    const float   f  = inv_scale[0];
     const uint4*  xv = reinterpret_cast<const uint4*>(x);
     const int64_t g0 = static_cast<int64_t>(blockIdx.x) * (kBlock * U) + threadIdx.x;
     uint4         raw[U][VG];
@@ -769,6 +956,7 @@ __global__ __launch_bounds__(kBlock) void quantize_stream_kernel(const T* __rest
 #pragma unroll
         for(int l = 0; l < VG; ++l) raw[u][l] = g < ngroups ? xv[g * VG + l] : make_uint4(0, 0, 0, 0);
     }
+    const float f = tensor_inverse_scale<T, SRC, kBlock>(ts, x, ngroups * 8, qmax, lds_m);
 #pragma unroll
     for(int u = 0; u < U; ++u)
     {
@@ -794,99 +982,6 @@ __global__ __launch_bounds__(kBlock) void quantize_stream_kernel(const T* __rest
         }
         *reinterpret_cast<uint2*>(q + g * 8) = make_uint2(w[0], w[1]);
     }
-}
-
-// ------------------------------------------------------------------ maximum and quantize in one launch
-// Per-tensor scale, contiguous tensor.  Every workgroup (1) folds its share of the tensor into a partial
-// maximum and publishes it, (2) takes a ticket; the last one to arrive clears the ticket counter and advances a
-// generation word, the others poll that word, (3) folds all partials (the same maximum in every workgroup),
-// forms the scale with the arithmetic of the separate pass, and (4) quantizes its patches, which it has just
-// read and which therefore mostly still sit in cache.  The wait in (2) is bounded: a workgroup whose polls run
-// out (the grid does not fit the device at once, or shares it with another kernel) finds the maximum by reading
-// the whole tensor itself -- slower, same result, and no workgroup ever depends on one that has not started.
-// `sync`: two 32-bit words, [0] tickets (zero before first use, zero again afterwards), [1] generation (any
-// value); `partial`: one float per workgroup.
-template <typename T, int RND, int PR>
-__global__ __launch_bounds__(kBlock, 3) void absmax_quantize_kernel(const T* __restrict__ x, int64_t rows, int64_t cols,
-                                                                     int qmax, uint64_t seed, uint64_t offset,
-                                                                     unsigned int* sync, float* partial, float* scale,
-                                                                     float* inv_scale,
-                                                                     float* amax_opt, int8_t* __restrict__ q,
-                                                                     int8_t* __restrict__ qT, int64_t grid_x, int lpr_log2,
-                                                                     int64_t patch_blocks, unsigned int poll_limit)
-{
-    __shared__ float lds[16];
-    __shared__ int   timed_out;
-    __shared__ float amax_all;
-    constexpr int E = Vec16<T>::N;
-    constexpr int U = 8;
-    const int64_t nvec = rows * cols / E;                  // cols % 8 == 0: no scalar tail
-    const uint4*  xv   = reinterpret_cast<const uint4*>(x);
-    unsigned int  gen = 0u;
-    if(threadIdx.x == 0) gen = __hip_atomic_load(sync + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // before the ticket
-    auto fold_range = [&](int64_t first, int64_t step) {
-        RunMax<T> rm;
-        for(int64_t c = first + threadIdx.x; c < nvec; c += step)
-        {
-            uint4 v[U];
-#pragma unroll
-            for(int u = 0; u < U; ++u)
-            {
-                const int64_t idx = c + static_cast<int64_t>(u) * kBlock;
-                v[u] = idx < nvec ? xv[idx] : make_uint4(0, 0, 0, 0);
-            }
-#pragma unroll
-            for(int u = 0; u < U; ++u) rm.add(v[u]);
-        }
-        return block_reduce_max(rm.get(), lds);
-    };
-    // (1) this workgroup's share: pieces of kBlock * U vectors, dealt round-robin
-    const float mine = fold_range(static_cast<int64_t>(blockIdx.x) * kBlock * U, static_cast<int64_t>(gridDim.x) * kBlock * U);
-    // (2)
-    if(threadIdx.x == 0)
-    {
-        st_partial(partial + blockIdx.x, mine);
-        __builtin_amdgcn_s_waitcnt(0x0F70);                 // vmcnt(0): the partial has been written
-        const unsigned int t = atomicAdd(sync, 1u);
-        int late = 0;
-        if(t == gridDim.x - 1u)
-        {
-            __hip_atomic_store(sync, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __builtin_amdgcn_s_waitcnt(0x0F70);
-            __hip_atomic_store(sync + 1, gen + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-        else
-        {
-            unsigned int polls = 0u;
-            while(__hip_atomic_load(sync + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gen)
-            {
-                if(++polls > poll_limit) { late = 1; break; }
-                __builtin_amdgcn_s_sleep(4);
-            }
-        }
-        timed_out = late;
-    }
-    __syncthreads();
-    // (3)
-    float folded;                                           // valid in thread 0
-    if(!timed_out)
-    {
-        float m = 0.0f;
-        for(int i = threadIdx.x; i < static_cast<int>(gridDim.x); i += kBlock) m = fmaxf(m, ld_partial(partial + i));
-        folded = block_reduce_max(m, lds);
-    }
-    else
-        folded = fold_range(0, static_cast<int64_t>(kBlock) * U);
-    if(threadIdx.x == 0) amax_all = folded;
-    __syncthreads();
-    const float amax = amax_all;
-    float inv = 1.0f;
-    if(amax != 0.0f) inv = __fdiv_rn(static_cast<float>(qmax), amax);
-    if(blockIdx.x == 0 && threadIdx.x == 0) write_scale(amax, static_cast<float>(qmax), scale, inv_scale, amax_opt, 0);
-    // (4)
-    for(int64_t b = blockIdx.x; b < patch_blocks; b += gridDim.x)
-        quantize_patch_body<T, RND, false, PR, false, true>(b, inv, x, rows, cols, cols, qmax, kPerTensor, seed, offset,
-                                                            nullptr, q, qT, grid_x, lpr_log2, nullptr, 0);
 }
 
 // Any shape, any alignment: one element per thread.
@@ -1384,12 +1479,8 @@ hipError_t colreduce_launch(const T* x, int64_t rows, int64_t cols, int64_t ld, 
         else
             colreduce_kernel<T, false, OP, kBlock><<<grid, dim3(kBlock), 0, st>>>(x, rows, cols, ld, tpr, partial, partial_max, tfin);
     }
-    constexpr int FOP = OP == OP_MAX ? OP_MAX : OP_SUM;
-    colreduce_finalize_kernel<FOP><<<dim3((cols + 15) / 16), dim3(kBlock), 0, st>>>(partial, gy, cols, qmax, out, inv_scale,
-                                                                                amax_opt);
-    if(OP == OP_SUMMAX && !tfin.ctr)
-        absmax_tensor_finalize_kernel<<<dim3(1), dim3(kBlock), 0, st>>>(partial_max, static_cast<int>(gx * gy), tfin.qmax,
-                                                                        tfin.scale, tfin.inv_scale, tfin.amax_opt);
+    colreduce_finalize_kernel<OP><<<dim3((cols + 15) / 16 + (OP == OP_SUMMAX ? 1 : 0)), dim3(kBlock), 0, st>>>(
+        partial, gy, cols, qmax, out, inv_scale, amax_opt, partial_max, static_cast<int>(gx * gy), tfin);
     return hipGetLastError();
 }
 
@@ -1421,7 +1512,7 @@ static hipError_t absmax_typed(const T* x, int64_t rows, int64_t cols, int64_t l
         float*        wsq = ws + kAbsmaxMaxBlocks;          // block sums of squares
         if(colsum_opt)
         {   // per-tensor absmax fused with column sums: one pass over x
-            TensorFinal tfin{ctr, qmax, scale, inv_scale, amax_opt, wsq, sumsq_opt};
+            TensorFinal tfin{qmax, scale, inv_scale, amax_opt, wsq, sumsq_opt};
             return colreduce_launch<T, OP_SUMMAX>(x, rows, cols, ld, 0.0f, colsum_opt, nullptr, nullptr,
                                                   ws + 2 * kAbsmaxMaxBlocks, ws, tfin, st);
         }
@@ -1467,7 +1558,7 @@ static hipError_t absmax_typed(const T* x, int64_t rows, int64_t cols, int64_t l
     }
     else
     {
-        TensorFinal none{nullptr, qmax, nullptr, nullptr, nullptr, nullptr, nullptr};
+        TensorFinal none{qmax, nullptr, nullptr, nullptr, nullptr, nullptr};
         return colreduce_launch<T, OP_MAX>(x, rows, cols, ld, qmax, scale, inv_scale, amax_opt,
                                            reinterpret_cast<float*>(static_cast<uint8_t*>(workspace) + kCtrBytes), nullptr,
                                            none, st);
@@ -1547,12 +1638,59 @@ static void quantize_patch_launch(const T* x, int64_t rows, int64_t cols, int64_
     const dim3       grid(static_cast<unsigned>(ps.gx * ps.gy));
     auto go = [&](auto percol, auto pr) {
         quantize_patch_kernel<T, RND, decltype(percol)::value, decltype(pr)::value><<<grid, dim3(kBlock), 0, st>>>(
-            x, rows, cols, ld, qmax, gran, seed, offset, inv, q, qT, ps.gx, ps.lpr_log2);
+            x, rows, cols, ld, qmax, seed, offset, inv, q, qT, ps.gx, ps.lpr_log2);
     };
     typedef std::integral_constant<int, 16> P16;
     typedef std::integral_constant<int, 8>  P8;
     if(gran == kPerCol) { if(ps.pr == 16) go(std::true_type{}, P16{}); else go(std::true_type{}, P8{}); }
     else                { if(ps.pr == 16) go(std::false_type{}, P16{}); else go(std::false_type{}, P8{}); }
+}
+
+// f(std::integral_constant<int, RND>) for a run-time rounding mode
+template <typename F> static void with_rounding(int rnd, F&& f)
+{
+    if(rnd == kStochastic)  f(std::integral_constant<int, kStochastic>{});
+    else if(rnd == kFloor)  f(std::integral_constant<int, kFloor>{});
+    else                    f(std::integral_constant<int, kNearest>{});
+}
+
+// What the tiled kernel and the streaming one need of a tensor and its outputs.
+static int64_t tiles_of(int64_t rows, int64_t cols, int tr) { return ((rows + tr - 1) / tr) * ((cols + kTileCols - 1) / kTileCols); }
+template <typename T> static bool tile_ok(const T* x, int64_t rows, int64_t cols, int64_t ld, const int8_t* q, const int8_t* qT)
+{
+    return cols % 8 == 0 && aligned16(x) && (ld * sizeof(T)) % 16 == 0 && (reinterpret_cast<uintptr_t>(q) & 7) == 0
+        && (rows % 16 != 0 || aligned16(qT)) && tiles_of(rows, cols, 64) < (int64_t(1) << 31);
+}
+
+// Per-tensor codes of a tensor that meets tile_ok: the streaming kernel when only row-major codes of a contiguous tensor
+// are wanted, tiles otherwise.  Tiles are 128 rows high (whole 128-byte lines of the transposed copy) once that gives
+// every compute unit two workgroups, 64 rows below.
+template <typename T, int SRC>
+static void quantize_tensor_launch(const T* x, int64_t rows, int64_t cols, int64_t ld, int qmax, int rnd, uint64_t seed,
+                                   uint64_t offset, const TensorScale& ts, int8_t* q, int8_t* qT, hipStream_t st)
+{
+    const int64_t ngroups = rows * cols / 8, stream_blocks = (ngroups + kBlock * 4 - 1) / (kBlock * 4);
+    const bool    stream  = SRC != kWhole && q && !qT && ld == cols && stream_blocks < (int64_t(1) << 31);
+    const int     tiles_x = static_cast<int>((cols + kTileCols - 1) / kTileCols);
+    with_rounding(rnd, [&](auto r) {
+        constexpr int RND = decltype(r)::value;
+        if constexpr(SRC != kWhole)
+        {
+            if(stream)
+            {
+                quantize_stream_kernel<T, RND, SRC><<<dim3(static_cast<unsigned>(stream_blocks)), dim3(kBlock), 0, st>>>(x, ngroups, qmax, seed, offset, ts, q);
+                return;
+            }
+            if(tiles_of(rows, cols, 128) < 512)
+            {
+                quantize_tile_kernel<T, RND, 64, SRC><<<dim3(static_cast<unsigned>(tiles_of(rows, cols, 64))), dim3(256), 0, st>>>(
+                    x, rows, cols, ld, qmax, seed, offset, ts, q, qT, tiles_x);
+                return;
+            }
+        }
+        quantize_tile_kernel<T, RND, 128, SRC><<<dim3(static_cast<unsigned>(tiles_of(rows, cols, 128))), dim3(512), 0, st>>>(
+            x, rows, cols, ld, qmax, seed, offset, ts, q, qT, tiles_x);
+    });
 }
 
 template <typename T>
@@ -1561,29 +1699,17 @@ static hipError_t quantize_typed(const T* x, int64_t rows, int64_t cols, int64_t
                                  hipStream_t st)
 {
     const PatchShape ps = patch_shape<T>(rows, cols, qT != nullptr);
-    const int64_t    gx = ps.gx, gy = ps.gy;
-    const bool    fast = cols % 8 == 0 && aligned16(x) && (ld * sizeof(T)) % 16 == 0 && (!q || aligned16(q))
-                      && (!qT || (aligned16(qT) && rows % 16 == 0)) && gx * gy < (int64_t(1) << 31);
-    if(fast && q && !qT && gran == kPerTensor && ld == cols && rows * cols / 8 < (int64_t(1) << 40))
-    {   // row-major codes of a contiguous tensor with one scale: the streaming form
-        const int64_t ngroups = rows * cols / 8;
-        const dim3    grid(static_cast<unsigned>((ngroups + kBlock * 4 - 1) / (kBlock * 4)));
-        if(rnd == kStochastic)
-            quantize_stream_kernel<T, kStochastic><<<grid, dim3(kBlock), 0, st>>>(x, ngroups, qmax, seed, offset, inv, q);
-        else if(rnd == kFloor)
-            quantize_stream_kernel<T, kFloor><<<grid, dim3(kBlock), 0, st>>>(x, ngroups, qmax, seed, offset, inv, q);
-        else
-            quantize_stream_kernel<T, kNearest><<<grid, dim3(kBlock), 0, st>>>(x, ngroups, qmax, seed, offset, inv, q);
-    }
-    else if(fast)
+    const bool       fast = cols % 8 == 0 && aligned16(x) && (ld * sizeof(T)) % 16 == 0 && (!q || aligned16(q))
+                      && (!qT || (aligned16(qT) && rows % 16 == 0)) && ps.gx * ps.gy < (int64_t(1) << 31);
+    if(gran == kPerTensor && tile_ok(x, rows, cols, ld, q, qT))
     {
-        if(rnd == kStochastic)
-            quantize_patch_launch<T, kStochastic>(x, rows, cols, ld, qmax, gran, seed, offset, inv, q, qT, st);
-        else if(rnd == kFloor)
-            quantize_patch_launch<T, kFloor>(x, rows, cols, ld, qmax, gran, seed, offset, inv, q, qT, st);
-        else
-            quantize_patch_launch<T, kNearest>(x, rows, cols, ld, qmax, gran, seed, offset, inv, q, qT, st);
+        const TensorScale ts{inv, nullptr, 0, nullptr, nullptr, nullptr};
+        quantize_tensor_launch<T, kInv>(x, rows, cols, ld, qmax, rnd, seed, offset, ts, q, qT, st);
     }
+    else if(fast && gran != kPerTensor)
+        with_rounding(rnd, [&](auto r) {
+            quantize_patch_launch<T, decltype(r)::value>(x, rows, cols, ld, qmax, gran, seed, offset, inv, q, qT, st);
+        });
     else
     {
         int64_t nb = (rows * cols + kBlock - 1) / kBlock;
@@ -1605,71 +1731,57 @@ hipError_t launch_quantize_int8(const void* x, int xdt, int64_t rows, int64_t co
                           qT, stream);
 }
 
-// Per-tensor maximum, scales and codes with one launch where that pays (a small contiguous tensor: the second
-// read comes from cache and one dependent launch is saved), otherwise the two separate launches.  The single
-// launch runs one workgroup per compute unit at most (few tickets), a third of what the separate quantize kernel
-// keeps in flight, so it stops paying at about 4M elements (measured: 2048x1024 14 vs 17 us, 8192x1024 22 vs 18
-// us) and, with the arithmetic-heavy stochastic rounding, at about 1M (1024x1024 13 vs 17 us, 2048x1024 17 vs 17 us).
-constexpr int64_t kOneLaunchMaxElems = int64_t(1) << 22, kOneLaunchMaxElemsStochastic = int64_t(1) << 20;
+// Per-tensor maximum, scales and codes of a contiguous tensor.  Up to kWholeBytes one launch, every workgroup of which
+// reads the whole tensor for its maximum (no workgroup waits for another); above that a launch that leaves one maximum
+// per block and the quantizing launch, which folds them.
+constexpr int64_t kWholeBytes = 128 << 10;
 
 template <typename T>
 static hipError_t absmax_quantize_typed(const T* x, int64_t rows, int64_t cols, int qmax, int rnd, uint64_t seed,
                                         uint64_t offset, float* scale, float* inv_scale, float* amax_opt, int8_t* q,
-                                        int8_t* qT, void* workspace, unsigned int poll_limit, hipStream_t st)
+                                        int8_t* qT, void* workspace, hipStream_t st)
 {
-    const PatchShape ps = patch_shape<T>(rows, cols, qT != nullptr);
-    const int64_t    patch_blocks = ps.gx * ps.gy;
-    const bool one_launch = cols % 8 == 0 && aligned16(x) && (!q || aligned16(q)) && (!qT || (aligned16(qT) && rows % 16 == 0))
-                         && patch_blocks < (int64_t(1) << 31)
-                         && rows * cols <= (rnd == kStochastic ? kOneLaunchMaxElemsStochastic : kOneLaunchMaxElems);
-    if(!one_launch)
+    if(!tile_ok(x, rows, cols, cols, q, qT))
     {
         hipError_t e = absmax_typed(x, rows, cols, cols, kPerTensor, static_cast<float>(qmax), scale, inv_scale, amax_opt,
                                     nullptr, nullptr, workspace, st);
         if(e != hipSuccess) return e;
         return quantize_typed(x, rows, cols, cols, qmax, kPerTensor, rnd, seed, offset, inv_scale, q, qT, st);
     }
-    // one workgroup per compute unit at most: all of them resident at once on an otherwise idle device, and few
-    // tickets on the counter
-    static int cus = 0;
-    if(cus == 0)
+    float* partial = reinterpret_cast<float*>(static_cast<uint8_t*>(workspace) + kCtrBytes);
+    if(rows * cols * static_cast<int64_t>(sizeof(T)) <= kWholeBytes)
     {
-        int dev = 0, n = 0;
-        if(hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0)
-            n = 64;
-        cus = n;
+        const TensorScale ts{nullptr, nullptr, 0, scale, inv_scale, amax_opt};
+        quantize_tensor_launch<T, kWhole>(x, rows, cols, cols, qmax, rnd, seed, offset, ts, q, qT, st);
+        return hipGetLastError();
     }
-    const int64_t g = patch_blocks < cus ? patch_blocks : cus;
-    unsigned int* sync    = static_cast<unsigned int*>(workspace);
-    float*        partial = reinterpret_cast<float*>(static_cast<uint8_t*>(workspace) + kCtrBytes);
-    auto go = [&](auto rnd_tag, auto pr) {
-        absmax_quantize_kernel<T, decltype(rnd_tag)::value, decltype(pr)::value><<<dim3(static_cast<unsigned>(g)), dim3(kBlock), 0, st>>>(
-            x, rows, cols, qmax, seed, offset, sync, partial, scale, inv_scale, amax_opt, q, qT, ps.gx, ps.lpr_log2,
-            patch_blocks, poll_limit);
-    };
-    typedef std::integral_constant<int, 16> P16;
-    typedef std::integral_constant<int, 8>  P8;
-    auto by_pr = [&](auto rnd_tag) { if(ps.pr == 16) go(rnd_tag, P16{}); else go(rnd_tag, P8{}); };
-    if(rnd == kStochastic) by_pr(std::integral_constant<int, kStochastic>{});
-    else if(rnd == kFloor) by_pr(std::integral_constant<int, kFloor>{});
-    else                   by_pr(std::integral_constant<int, kNearest>{});
+    const int64_t nvec = rows * cols / Vec16<T>::N;
+    const int     blk  = nvec >= (int64_t(1) << 19) ? 1024 : kBlock;
+    int64_t       nb   = (nvec + blk * 8 - 1) / (blk * 8);
+    nb                 = nb > kFoldMax ? kFoldMax : nb;
+    if(blk == 1024)
+        absmax_tensor_kernel<T, true, 1024><<<dim3(nb), dim3(1024), 0, st>>>(x, rows, cols, cols, partial, nullptr, 0.0f, nullptr, nullptr, nullptr, nullptr, nullptr);
+    else
+        absmax_tensor_kernel<T, true, kBlock><<<dim3(nb), dim3(kBlock), 0, st>>>(x, rows, cols, cols, partial, nullptr, 0.0f, nullptr, nullptr, nullptr, nullptr, nullptr);
+    const TensorScale ts{nullptr, partial, static_cast<int>(nb), scale, inv_scale, amax_opt};
+    quantize_tensor_launch<T, kPartials>(x, rows, cols, cols, qmax, rnd, seed, offset, ts, q, qT, st);
     return hipGetLastError();
 }
 
 hipError_t launch_absmax_quantize(const void* x, int xdt, int64_t rows, int64_t cols, int qmax, int rnd, uint64_t seed,
                                   uint64_t offset, float* scale, float* inv_scale, float* amax_opt, int8_t* q, int8_t* qT,
-                                  void* workspace, unsigned int poll_limit, hipStream_t stream)
+                                  void* workspace, hipStream_t stream)
 {
     if(xdt == kF32)
         return absmax_quantize_typed(static_cast<const float*>(x), rows, cols, qmax, rnd, seed, offset, scale, inv_scale,
-                                     amax_opt, q, qT, workspace, poll_limit, stream);
+                                     amax_opt, q, qT, workspace, stream);
     return absmax_quantize_typed(static_cast<const __half*>(x), rows, cols, qmax, rnd, seed, offset, scale, inv_scale,
-                                 amax_opt, q, qT, workspace, poll_limit, stream);
+                                 amax_opt, q, qT, workspace, stream);
 }
 
 // Weights of one linear operator in one go: per-row scales and codes for the forward, per-column scales
-// and transposed codes for dX.  Fused form: row + column maxima in one pass, the column fold, one dual
-// quantize (3 launches, W read twice); otherwise the five separate launches.  Same results either way.
+// and transposed codes for dX.  Two launches that read W twice where the vector rules hold; otherwise the
+// separate passes.  Same results either way.
 template <typename T>
 static hipError_t prepare_weights_typed(const T* w, int64_t N, int64_t K, float qmax, float* sw, float* iw,
                                         float* aw_opt, int8_t* wq, float* swb, float* iwb, int8_t* wqbT,
@@ -1677,10 +1789,11 @@ static hipError_t prepare_weights_typed(const T* w, int64_t N, int64_t K, float 
 {
     // conv_C > 0: w is [N, 9*conv_C]; the second scales are per input channel (conv_C of them) and wqbT is the
     // mirrored, channel-exchanged copy [conv_C, 9*N]; only the fused form serves this case.
-    constexpr int E = Vec16<T>::N;
     float*        partial = reinterpret_cast<float*>(static_cast<uint8_t*>(workspace) + kCtrBytes);
-    const bool    fused = aligned16(w) && K % (2 * E) == 0 && K % 8 == 0 && N % 16 == 0 && N <= 16 * kColParts
-                       && aligned16(wq) && aligned16(wqbT) && aligned16(partial);
+    const int64_t tiles_x = (K + kTileCols - 1) / kTileCols, row_tiles = (N + kWeightTileRows - 1) / kWeightTileRows;
+    const bool    fused = aligned16(w) && K % 8 == 0 && N % 16 == 0 && N <= 16 * kColParts
+                       && aligned16(wq) && aligned16(wqbT) && aligned16(partial)
+                       && kWeightGroups * K + tiles_x * N <= kColParts * K;      // both sets of partials fit the workspace
     if(!fused && conv_C > 0) return hipErrorInvalidValue;      // the caller tests the same conditions before choosing this form
     if(!fused)
     {
@@ -1692,36 +1805,13 @@ static hipError_t prepare_weights_typed(const T* w, int64_t N, int64_t K, float 
         if(e != hipSuccess) return e;
         return quantize_typed(w, N, K, K, static_cast<int>(qmax), kPerCol, kNearest, 0, 0, iwb, nullptr, wqbT, st);
     }
-    int gy;          // row groups = partial rows per column (at most kColParts); 16 loads in flight per thread
-    if(N <= 2 * kColParts)
-    {
-        gy = static_cast<int>((N + 1) / 2);
-        absmax_rowcol_kernel<T, 2, 8><<<dim3(gy), dim3(kBlock), 0, st>>>(w, N, K, K, qmax, sw, iw, aw_opt, partial);
-    }
-    else if(N <= 4 * kColParts)
-    {
-        gy = static_cast<int>((N + 3) / 4);
-        absmax_rowcol_kernel<T, 4, 4><<<dim3(gy), dim3(kBlock), 0, st>>>(w, N, K, K, qmax, sw, iw, aw_opt, partial);
-    }
-    else if(N <= 8 * kColParts)
-    {
-        gy = static_cast<int>((N + 7) / 8);
-        absmax_rowcol_kernel<T, 8, 2><<<dim3(gy), dim3(kBlock), 0, st>>>(w, N, K, K, qmax, sw, iw, aw_opt, partial);
-    }
-    else
-    {
-        gy = static_cast<int>((N + 15) / 16);
-        absmax_rowcol_kernel<T, 16, 1><<<dim3(gy), dim3(kBlock), 0, st>>>(w, N, K, K, qmax, sw, iw, aw_opt, partial);
-    }
-    if(conv_C > 0)      // partial[gy][9][C] read as gy*9 rows of C columns: maxima per input channel
-        colreduce_finalize_kernel<OP_MAX><<<dim3((conv_C + 15) / 16), dim3(kBlock), 0, st>>>(partial, gy * 9, conv_C, qmax, swb, iwb, nullptr);
-    else
-        colreduce_finalize_kernel<OP_MAX><<<dim3((K + 15) / 16), dim3(kBlock), 0, st>>>(partial, gy, K, qmax, swb, iwb, nullptr);
-    // 4-row patches: weights are small, more wavefronts in flight matter more than wide transposed stores
-    PatchShape ps = patch_shape<T>(N, K, false);
-    ps.gy = (N + 4 * (kWaveSize >> ps.lpr_log2) * 4 - 1) / (4 * (kWaveSize >> ps.lpr_log2) * 4);
-    quantize_patch_kernel<T, kNearest, false, 4, true><<<dim3(static_cast<unsigned>(ps.gx * ps.gy)), dim3(kBlock), 0, st>>>(
-        w, N, K, K, static_cast<int>(qmax), kPerRow, 0, 0, iw, wq, wqbT, ps.gx, ps.lpr_log2, iwb, static_cast<int>(conv_C));
+    const int groups = static_cast<int>(row_tiles < kWeightGroups ? row_tiles : kWeightGroups);
+    float*    row_part = partial + kWeightGroups * K;
+    weight_maxima_kernel<T><<<dim3(static_cast<unsigned>(tiles_x * groups)), dim3(256), 0, st>>>(
+        w, N, K, static_cast<int>(tiles_x), groups, row_part, partial);
+    const WeightOut out{sw, iw, aw_opt, swb, iwb, wq, wqbT};
+    weight_quantize_kernel<T><<<dim3(static_cast<unsigned>(tiles_x * row_tiles)), dim3(256), 0, st>>>(
+        w, N, K, static_cast<int>(qmax), static_cast<int>(tiles_x), groups, row_part, partial, out, static_cast<int>(conv_C));
     return hipGetLastError();
 }
 
@@ -2008,7 +2098,7 @@ hipError_t launch_zero_f32(float* p, int64_t n, hipStream_t stream)
 hipError_t launch_colsum(const void* x, int xdt, int64_t rows, int64_t cols, float* out, float* workspace,
                          hipStream_t stream)
 {
-    TensorFinal none{nullptr, 0.0f, nullptr, nullptr, nullptr, nullptr, nullptr};
+    TensorFinal none{0.0f, nullptr, nullptr, nullptr, nullptr, nullptr};
     if(xdt == kF32)
         return colreduce_launch<float, OP_SUM>(static_cast<const float*>(x), rows, cols, cols, 0.0f, out, nullptr, nullptr,
                                                workspace, nullptr, none, stream);

@@ -119,9 +119,9 @@ def test_fp16_stochastic_cast_bit_exact(k):
 @pytest.mark.parametrize("dt", [np.float32, np.float16])
 def test_prepare_weights_equals_the_separate_calls(dt):
     """Fused weight preparation (row and column maxima in one pass, both sets of codes in another) against the
-    oracle's per-row and per-column quantizations; shapes on the fused path (both row-group sizes) and off it."""
+    oracle's per-row and per-column quantizations; shapes on the fused path (tile edges, more row tiles than groups) and off it."""
     rng = np.random.default_rng(42)
-    for (n, k) in [(64, 576), (1024, 4096), (4096, 1024), (3072, 768), (48, 40), (20, 24), (16, 8), (8208, 64)]:
+    for (n, k) in [(64, 576), (1024, 4096), (4096, 1024), (3072, 768), (48, 40), (20, 24), (16, 8), (8208, 64), (4112, 136), (80, 264)]:
         say("prepare weights", dt.__name__, n, k)
         w = (rng.standard_normal((n, k)) * 0.02).astype(dt)
         w[rng.integers(0, n), :] = 0                       # an all-zero row: scale 1
@@ -456,3 +456,31 @@ def test_absmax_quantize_all_zero_and_lower_bits():
     assert_bits_equal(host(s), so, "scale, 5 bits")
     assert_bits_equal(host(q), want, "codes, 5 bits")
     assert_bits_equal(host(qT), want.T, "transposed codes, 5 bits")
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float16])
+@pytest.mark.parametrize("rows,cols", [(1, 8), (63, 120), (65, 136), (45, 1024), (128, 256), (129, 256), (130, 520),
+                                       (8208, 1024)])
+def test_transposed_codes_at_the_edges_of_the_tiles(dtype, rows, cols):
+    """Codes and transposed codes of the tiled quantizer around its 64 and 128-row tiles, with row counts that leave the
+    transposed copy unaligned, on both sides of the one-launch size, and of a strided input: bits of the oracle."""
+    rng = np.random.default_rng(rows * 10007 + cols)
+    x = _data(rng, (rows, cols), dtype, sigma=0.3)
+    so, io = orc.scales_from_amax(orc.absmax(x, "tensor"))
+    want = orc.quantize_int(x, io, "tensor", "stochastic", 5, 99)
+    say("tile edges", dtype.__name__, rows, cols)
+    s, iv, am = empty(1, torch.float32), empty(1, torch.float32), empty(1, torch.float32)
+    q = torch.full((rows, cols), 99, dtype=torch.int8, device="cuda")
+    qT = torch.full((cols, rows), 99, dtype=torch.int8, device="cuda")
+    Q.qsync_absmax_quantize(dev(x), rows, cols, 8, Q.ROUND_STOCHASTIC, 5, 99, s, iv, am, q, qT,
+                            ws(Q.qsync_absmax_quantize_workspace_bytes(rows, cols)))
+    assert_bits_equal(host(s), so, "scale")
+    assert_bits_equal(host(iv), io, "inverse scale")
+    assert_bits_equal(host(q), want, "codes")
+    assert_bits_equal(host(qT), want.T, "transposed codes")
+    wide = torch.zeros(rows, cols + 16, dtype=dev(x).dtype, device="cuda")      # rows 16 elements apart
+    wide[:, :cols] = dev(x)
+    q.fill_(99), qT.fill_(99)
+    Q.qsync_quantize(wide, rows, cols, cols + 16, Q.INT8, 8, Q.PER_TENSOR, Q.ROUND_STOCHASTIC, 5, 99, iv, q, qT)
+    assert_bits_equal(host(q), want, "codes of the strided input")
+    assert_bits_equal(host(qT), want.T, "transposed codes of the strided input")
