@@ -1391,8 +1391,11 @@ __global__ __launch_bounds__(kThreads) void splitk_reduce_kernel(const ACC* __re
 }
 
 struct TileShape { int bm, bn; };
-// 0: 256x256, 8 wavefronts (2x4, 128x64 each)   1: 128x128, 4 wavefronts (2x2, 64x64 each)
+// 0: 256x256, 8 wavefronts (2x4, 128x64 each)   1: 128x128, 8 wavefronts (2x4, 64x32 each)
 // 2: 64x64, 4 wavefronts (2x2, 32x32 each)
+// (128x128 with four wavefronts of 64x64, one per SIMD, reads a third less LDS per operation but has nobody to issue
+//  matrix instructions while it queues direct loads.  Four -> eight wavefronts: 4096x768x3072 int8 18.1 -> 16.2 us,
+//  3072x768x4096 20.4 -> 18.2, 2056x1000x1032 binary16 14.0 -> 12.5, 64x128x128 4.7 -> 3.9.)
 // (256x256 with 4 wavefronts of 128x128 -- a third fewer LDS fragment reads per matrix instruction, 256
 //  accumulator registers per lane -- needs matrix instructions written as inline assembly on accumulator
 //  registers, one loop body without branches around them, and fragment reads and direct loads placed one by one
@@ -1470,18 +1473,18 @@ hipError_t launch_tile(const GemmKernelArgs& a, int splits, hipStream_t st, bool
 template <typename TR>
 hipError_t launch_traits(int tile, const GemmKernelArgs& a, int splits, hipStream_t st, bool tn = false)
 {
-    // Three stages for the 128x128 tile where every compute unit gets one workgroup at most: with a second one resident
-    // (two stages) its K loop fills the gaps instead.  Measured, two -> three stages: 4096x768x3072 (192 workgroups)
-    // int8 20.4 -> 17.8 us, binary16 35.8 -> 30.3; 1000x1032x2056 binary16 (64) 20.2 -> 19.4; but 4096x3072x768
-    // (768 workgroups) int8 18.5 -> 23.3.  The 64x64 tile gains nothing from 3, 4 or 8 stages (14.7 / 16.4 / 17.3 /
-    // 23.9 us on 2056x1000x1032 binary16): it is bound by the compute unit's load path, not by latency.
+    // Three stages for the 128x128 tile where every compute unit gets one workgroup at most; with a second one resident
+    // (two stages) its K loop fills the gaps instead.  Measured with four wavefronts, two -> three stages: 4096x768x3072
+    // (192 workgroups) int8 20.4 -> 17.8 us, binary16 35.8 -> 30.3; but 4096x3072x768 (768 workgroups) int8 18.5 -> 23.3.
+    // The 64x64 tile gains nothing from 3, 4 or 8 stages (14.7 / 16.4 / 17.3 / 23.9 us on 2056x1000x1032 binary16), nor
+    // from fragments read a whole K tile ahead (14.7).
     const int64_t workgroups = static_cast<int64_t>(a.tiles_m) * a.tiles_n * splits;
     switch(tile)
     {
     case 0: return launch_tile<TR, 256, 256, 2, 4, 2>(a, splits, st, tn);
     case 1:
-        return workgroups <= kNumCu ? launch_tile<TR, 128, 128, 2, 2, 3>(a, splits, st, tn)
-                                    : launch_tile<TR, 128, 128, 2, 2, 2>(a, splits, st, tn);
+        return workgroups <= kNumCu ? launch_tile<TR, 128, 128, 2, 4, 3>(a, splits, st, tn)
+                                    : launch_tile<TR, 128, 128, 2, 4, 2>(a, splits, st, tn);
     default: return launch_tile<TR, 64, 64, 2, 2, 2>(a, splits, st, tn);
     }
 }
@@ -1536,17 +1539,17 @@ GemmPlan plan_gemm(int prec, int64_t M, int64_t N, int64_t K, int force_tile, in
     const int64_t ktiles = (kb + kRowBytes - 1) / kRowBytes;
     auto ntiles = [&](int t) { return ((M + kTiles[t].bm - 1) / kTiles[t].bm) * ((N + kTiles[t].bn - 1) / kTiles[t].bn); };
     // Plan = (tile, K splits) with the smallest estimated time.  The estimate is a small model fitted to gfx950
-    // measurements of this kernel (int8, the step's code distribution, 17 shapes x up to 10 plans, launched alone;
-    // rms error 6 %; binary16 scales alike):
+    // measurements of this kernel (int8 and binary16, forward, row-major and transposed weight-gradient forms: 54
+    // operands x 3 tiles, replayed from a graph; rms error 11 %, the choice at most 8 % behind the best tile):
     //   a compute unit retires `r1` Mop/us per resident workgroup of a tile shape, up to `rmax` with `occ` of them
     //   sharing it; the chip as a whole retires at most `cap` Mop/us (the power limit: 256 busy units do not
     //   each reach `rmax`); every round of co-resident workgroups costs `ovh` us of launch, first-load latency
     //   and epilogue; split K adds its reduction pass.
     struct TileModel { double r1, rmax, ovh, cap; int occ; };
-    const TileModel model[kNumTiles] = {{14.9, 15.5, 9.2, 2555.0, 1}, {6.56, 8.42, 4.4, 2000.0, 2}, {2.89, 5.03, 2.5, 2035.0, 4}};
+    const TileModel model[kNumTiles] = {{14.0, 15.8, 6.9, 2280.0, 1}, {8.3, 9.0, 4.2, 1900.0, 2}, {3.55, 5.48, 3.2, 2060.0, 4}};
     // Row-major (TN) operands: a K tile takes twice the LDS fragment reads, and a 64-wide tile of int8 operands
     // loads 64-byte row pieces (binary16: 128 bytes, no penalty); fitted slow-down of the main loop per tile shape.
-    const double    tn_rate[kNumTiles] = {0.89, 0.99, prec == 8 ? 0.66 : 0.95};
+    const double    tn_rate[kNumTiles] = {0.94, 0.89, prec == 8 ? 0.74 : 0.97};
     const double    cus = 256.0;
     auto estimate = [&](int t, int64_t s) {
         const TileModel& m    = model[t];
@@ -1559,7 +1562,7 @@ GemmPlan plan_gemm(int prec, int64_t M, int64_t N, int64_t K, int force_tile, in
         const double     mop  = 2.0 * kTiles[t].bm * kTiles[t].bn * kRowBytes * 1e-6 * kwork;    // per K tile (int8 ops)
         const double     unit = per * kt * mop / rate, chip = wgs * kt * mop / (m.cap * tnf);
         double           us   = (unit > chip ? unit : chip) + m.ovh * std::ceil(wgs / (cus * m.occ));
-        if(s > 1) us += 4.2 + static_cast<double>(s + 1) * static_cast<double>(M) * static_cast<double>(N) * 4.0 / 6.35e6;
+        if(s > 1) us += 4.0 + static_cast<double>(s + 1) * static_cast<double>(M) * static_cast<double>(N) * 4.0 / 6.24e6;
         return us;
     };
     // Candidates: no split, and the split counts that fill the units once, twice or up to their co-residency.  Tiles are
