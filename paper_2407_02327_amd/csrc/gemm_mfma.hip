@@ -225,28 +225,31 @@ __device__ uint4 g_zero_chunk;     // never written: static storage starts at ze
 
 __device__ const float g_one = 1.0f;     // stands in for an absent scale
 
-struct ConvTap { int delta[2]; int dh[2]; int dw[2]; bool valid[2]; };     // per chunk parity of the lane
+// Where a lane's two chunk positions (by parity of the load slot) stand on the K axis: the byte offset, the tap it lies
+// in and the channel offset in that tap.  Requests go over consecutive K tiles, so the position is carried on instead of
+// divided out of the tile index (a division per parity and tile, and border tests per load, made the gather's own
+// arithmetic the bound of the K loop: four loads took about 130 vector instructions, now about 55).
+struct ConvTap { uint32_t koff[2], tap[2], c0[2]; };
 
+// `mask`: bit t says that tap t of the lane's output pixel lies inside the image; taps from 9 on (chunks past the end
+// of K) have no bit.  `delta`: byte distance from the pixel to the chunk's source, plus (W + 1) pixels.
 template <int D, int DPW>
-__device__ __forceinline__ void conv_issue(const uint8_t* a, const uint8_t* zero, uint32_t pix_off, uint32_t hw,
-                                           const ConvTap& t, int H, int W, uint8_t* lds_mid)
+__device__ __forceinline__ void conv_issue(const uint8_t* a, const uint8_t* zero, uint32_t pix_off, uint32_t mask,
+                                           const ConvTap& t, const uint32_t (&delta)[2], uint8_t* lds_mid)
 {
     constexpr int IMM = dma_imm<D, DPW>();
     constexpr int par = D & 1;
-    const int  hh  = static_cast<int>(hw >> 16) + t.dh[par], ww = static_cast<int>(hw & 0xffffu) + t.dw[par];
-    const bool inb = t.valid[par] && static_cast<unsigned>(hh) < static_cast<unsigned>(H)
-                     && static_cast<unsigned>(ww) < static_cast<unsigned>(W);
-    const uint8_t* src = inb ? a + static_cast<int64_t>(static_cast<int32_t>(pix_off) + t.delta[par]) : zero;
+    const uint8_t* src = ((mask >> t.tap[par]) & 1u) ? a + (pix_off + delta[par]) : zero;
     __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src - IMM),
                                      (__attribute__((address_space(3))) void*)(lds_mid + dma_lds_shift<D, DPW>()), 16, IMM, 0);
 }
 
 template <int DPW, int... Ds>
 __device__ __forceinline__ void conv_sequence(std::integer_sequence<int, Ds...>, const uint8_t* a, const uint8_t* zero,
-                                              const uint32_t (&pix_off)[DPW], const uint32_t (&hw)[DPW],
-                                              const ConvTap& t, int H, int W, uint8_t* lds_mid)
+                                              const uint32_t (&pix_off)[DPW], const uint32_t (&mask)[DPW],
+                                              const ConvTap& t, const uint32_t (&delta)[2], uint8_t* lds_mid)
 {
-    (conv_issue<Ds, DPW>(a, zero, pix_off[Ds], hw[Ds], t, H, W, lds_mid), ...);
+    (conv_issue<Ds, DPW>(a, zero, pix_off[Ds], mask[Ds], t, delta, lds_mid), ...);
 }
 
 // TN form with the B operand gathered from an NHWC tensor (weight gradient of the 3x3 convolution): stage row r of
@@ -441,7 +444,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_nt_kernel(const GemmKerne
                                   : (is_a ? p.A + m0 * p.Kb : ((!CONV && p.remap_C > 0) ? p.B : p.B + n0 * p.Kb));
     const int64_t  rows_left = is_a ? p.M - m0 : p.N - n0;           // >= 1
     uint32_t       voff[DPW];                                         // lane offset + kDmaBias - immediate
-    uint32_t       hw[CONV ? DPW : 1];                                // CONV: (h << 16) | w of the lane's pixels
+    uint32_t       hw[CONV ? DPW : 1];       // CONVTN: (h << 16) | w of the lane's pixels; CONVA: their taps inside the image
     int            tnc_delta[CONVTN ? DPW : 1], tnc_code[CONVTN ? DPW : 1];      // CONVTN, B side (see conv_tn_issue)
     int            gchunk[2];                                         // the swizzle term depends on d%2 only
     {
@@ -496,7 +499,9 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_nt_kernel(const GemmKerne
                 {   // A side: voff holds the byte offset of output pixel m in the NHWC tensor instead
                     const uint32_t m = static_cast<uint32_t>(m0 + lrow), q = m / static_cast<uint32_t>(p.conv_W);
                     voff[d] = m * static_cast<uint32_t>(p.conv_Cb);
-                    hw[d]   = ((q % static_cast<uint32_t>(p.conv_H)) << 16) | (m - q * static_cast<uint32_t>(p.conv_W));
+                    const uint32_t h = q % static_cast<uint32_t>(p.conv_H), w = m - q * static_cast<uint32_t>(p.conv_W);
+                    const uint32_t row = (w > 0 ? 1u : 0u) | 2u | (w + 1 < static_cast<uint32_t>(p.conv_W) ? 4u : 0u);
+                    hw[d] = (h > 0 ? row : 0u) | (row << 3) | (h + 1 < static_cast<uint32_t>(p.conv_H) ? row << 6 : 0u);
                 }
             if(d < 2) gchunk[d] = chunk * 16;
         }
@@ -530,6 +535,20 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_nt_kernel(const GemmKerne
     // CONVTN: pixels per K tile, and how far (h, w) of a stage row move from one K tile to the next
     constexpr int tnc_KR = kRowBytes / ESZ;
     const int     tnc_dr = CONVTN ? tnc_KR % p.conv_W : 0, tnc_hq = CONVTN ? (tnc_KR / p.conv_W) % p.conv_H : 0;
+    // CONVA: the K axis position of the lane's two chunks, how it moves from one K tile to the next, and the extra distance
+    // of a step in kh
+    ConvTap        conv_t;
+    const uint32_t conv_cb = CONVA ? static_cast<uint32_t>(p.conv_Cb) : 1u;
+    const uint32_t conv_q = kRowBytes / conv_cb, conv_r = kRowBytes % conv_cb;
+    const uint32_t conv_kh_step = CONVA ? static_cast<uint32_t>((p.conv_W - 3) * p.conv_Cb) : 0u;       // (modulo 2^32 for W < 3)
+    if constexpr(CONVA)
+#pragma unroll
+        for(int par = 0; par < 2; ++par)
+        {
+            conv_t.koff[par] = static_cast<uint32_t>(gchunk[par]);
+            conv_t.tap[par]  = conv_t.koff[par] / conv_cb;
+            conv_t.c0[par]   = conv_t.koff[par] % conv_cb;
+        }
     auto dma = [&](int stage, int kt) {
         const int64_t  kb    = static_cast<int64_t>(kt) * kRowBytes;
         uint8_t*       lbase = lds + stage * STAGE_BYTES + wave * (DPW * 1024) + (dma_group<DPW>() / 2) * 1024;
@@ -544,22 +563,23 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_nt_kernel(const GemmKerne
         if constexpr(CONVA)
             if(is_a)
             {
-                ConvTap t;
+                // (for consecutive K tiles, starting at 0)  Source of a chunk: pixel + (kh - 1) rows + (kw - 1) pixels + c0
+                // = pixel - (W + 1) pixels + koff + kh (W - 3) pixels, since koff = (3 kh + kw) pixels + c0; the constant
+                // part is in the panel's base.
+                uint32_t delta[2];
+#pragma unroll
+                for(int par = 0; par < 2; ++par)
+                    delta[par] = conv_t.koff[par] + (conv_t.tap[par] >= 3 ? conv_kh_step : 0u) + (conv_t.tap[par] >= 6 ? conv_kh_step : 0u);
+                conv_sequence<DPW>(std::make_integer_sequence<int, DPW>{}, p.A - static_cast<int64_t>(p.conv_W + 1) * p.conv_Cb,
+                                   reinterpret_cast<const uint8_t*>(&g_zero_chunk), voff, hw, conv_t, delta, lbase);
 #pragma unroll
                 for(int par = 0; par < 2; ++par)
                 {
-                    const uint32_t koff = static_cast<uint32_t>(kb) + static_cast<uint32_t>(gchunk[par]);
-                    const uint32_t tap  = koff / static_cast<uint32_t>(p.conv_Cb);
-                    const int      c0   = static_cast<int>(koff - tap * static_cast<uint32_t>(p.conv_Cb));
-                    const int      kh   = static_cast<int>((tap * 11u) >> 5);         // tap / 3 for tap < 12
-                    const int      kw   = static_cast<int>(tap) - 3 * kh;
-                    t.dh[par]    = kh - 1;
-                    t.dw[par]    = kw - 1;
-                    t.delta[par] = ((kh - 1) * p.conv_W + (kw - 1)) * p.conv_Cb + c0;
-                    t.valid[par] = static_cast<int64_t>(koff) < p.Kb;
+                    conv_t.koff[par] += kRowBytes;
+                    conv_t.tap[par]  += conv_q;
+                    conv_t.c0[par]   += conv_r;
+                    if(conv_t.c0[par] >= static_cast<uint32_t>(p.conv_Cb)) { conv_t.c0[par] -= static_cast<uint32_t>(p.conv_Cb); ++conv_t.tap[par]; }
                 }
-                conv_sequence<DPW>(std::make_integer_sequence<int, DPW>{}, p.A,
-                                   reinterpret_cast<const uint8_t*>(&g_zero_chunk), voff, hw, t, p.conv_H, p.conv_W, lbase);
                 return;
             }
         const uint8_t* sb    = TN ? sbase0 + kb * (is_a ? p.M : p.N) : sbase0 + kb;      // TN: 128 operand rows further
