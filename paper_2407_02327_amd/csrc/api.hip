@@ -279,6 +279,23 @@ int qsync_scale_from_amax(float* amax, int bits, float* scale, float* inv_scale,
     return hip_status(launch_scale_from_amax(amax, qmax, scale, inv_scale, consume != 0, static_cast<hipStream_t>(stream)));
 }
 
+namespace {
+GemmProblem data_gradient(int tag, int64_t M, int64_t N, int64_t K, const void* dyq, const float* sdy, const void* wqbT,
+                          const float* swb, int wbgran, void* dx, int dxdt, int32_t* acc_dump)
+{
+    GemmProblem p{};
+    p.prec = tag; p.M = M; p.N = K; p.K = N;
+    p.A = dyq; p.B = wqbT; p.C = dx; p.c_dtype = dxdt;
+    if(tag == QSYNC_INT8)
+    {
+        p.s0 = sdy;
+        if(wbgran == QSYNC_PER_TENSOR) p.s1 = swb; else p.col_scale = swb;
+        p.acc_dump = acc_dump;
+    }
+    return p;
+}
+}  // namespace
+
 int qsync_qlinear_bwd(int tag, int64_t M, int64_t N, int64_t K, const void* dyq, const void* dyqT, const float* sdy,
                       const void* xqT, const float* sx, const void* wqbT, const float* swb, int wbgran, void* dx_opt,
                       int dxdt, void* dw_opt, int dwdt, float* db_opt, const void* dy_float_opt, int dydt,
@@ -322,33 +339,26 @@ int qsync_qlinear_bwd(int tag, int64_t M, int64_t N, int64_t K, const void* dyq,
     }
     hipStream_t st  = static_cast<hipStream_t>(stream);
     char*       wsb = static_cast<char*>(workspace);
-    if(dx_opt && M > 0 && K > 0)
+    GemmProblem pdx = data_gradient(tag, M, N, K, dyq, sdy, wqbT, swb, wbgran, dx_opt, dxdt, acc_dx_dump_opt), pdw{};
+    pdw.prec = tag; pdw.M = N; pdw.N = K; pdw.K = M;
+    pdw.A = dyqT; pdw.B = xqT; pdw.C = dw_opt; pdw.c_dtype = dwdt;
+    if(tag == QSYNC_INT8)
     {
-        GemmProblem p{};
-        p.prec = tag; p.M = M; p.N = K; p.K = N;
-        p.A = dyq; p.B = wqbT; p.C = dx_opt; p.c_dtype = dxdt;
-        if(tag == QSYNC_INT8)
-        {
-            p.s0 = sdy;
-            if(wbgran == QSYNC_PER_TENSOR) p.s1 = swb; else p.col_scale = swb;
-            p.acc_dump = acc_dx_dump_opt;
-        }
-        const int rc = hip_status(launch_gemm(p, plan_dx, wsb, st));
-        if(rc != QSYNC_OK) return rc;
+        pdw.s0 = sdy; pdw.s1 = sx;
+        pdw.acc_dump = acc_dw_dump_opt;
     }
-    if(dw_opt && N > 0 && K > 0)
+    const bool want_dx = dx_opt && M > 0 && K > 0, want_dw = dw_opt && N > 0 && K > 0;
+    void*      ws_dw   = wsb ? wsb + off_dw : nullptr;
+    int        rc      = QSYNC_OK;
+    const int  pair    = want_dx && want_dw ? gradient_pair_tile(pdx, plan_dx, pdw, plan_dw) : -1;
+    if(pair >= 0)
+        rc = hip_status(launch_gradient_pair(pdx, pdw, pair, st));
+    else
     {
-        GemmProblem p{};
-        p.prec = tag; p.M = N; p.N = K; p.K = M;
-        p.A = dyqT; p.B = xqT; p.C = dw_opt; p.c_dtype = dwdt;
-        if(tag == QSYNC_INT8)
-        {
-            p.s0 = sdy; p.s1 = sx;
-            p.acc_dump = acc_dw_dump_opt;
-        }
-        const int rc = hip_status(launch_gemm(p, plan_dw, wsb ? wsb + off_dw : nullptr, st));
-        if(rc != QSYNC_OK) return rc;
+        if(want_dx) rc = hip_status(launch_gemm(pdx, plan_dx, wsb, st));
+        if(want_dw && rc == QSYNC_OK) rc = hip_status(launch_gemm(pdw, plan_dw, ws_dw, st));
     }
+    if(rc != QSYNC_OK) return rc;
     if(db_opt && N > 0 && M == 0)
     {   // no rows to sum: the bias gradient is zero (the column-sum kernels need their workspace, which an
         // empty batch does not have to bring)
@@ -398,30 +408,38 @@ int qsync_qlinear_bwd_rm(int tag, int64_t M, int64_t N, int64_t K, const void* d
     if(dx_opt && (N % mult != 0 || !aligned16(dyq) || !aligned16(wqbT))) return QSYNC_ERR_ALIGN;
     // the weight gradient reads both operands row-major: whole K tiles of contraction rows, 16-byte column chunks
     if(dw_opt && (M % 128 != 0 || N % mult != 0 || K % mult != 0 || !aligned16(dyq) || !aligned16(xq))) return QSYNC_ERR_ALIGN;
-    // the data gradient is the NT GEMM of qsync_qlinear_bwd; it also owns the bias gradient
-    if(dx_opt || db_opt)
-    {
-        const int rc = qsync_qlinear_bwd(tag, M, N, K, dyq, nullptr, sdy, nullptr, nullptr, wqbT, swb, wbgran, dx_opt, dxdt,
-                                         nullptr, dwdt, db_opt, dy_float_opt, dydt, acc_dx_dump_opt, nullptr, workspace,
-                                         workspace_bytes, stream);
-        if(rc != QSYNC_OK) return rc;
-    }
-    if(!dw_opt || N == 0 || K == 0) return QSYNC_OK;
-    const GemmPlan plan   = plan_gemm(tag, N, K, M, -1, -1, true, /*tn=*/M > 0);
-    const size_t   off_dw = round256(plan_gemm(tag, M, K, N).workspace);
-    if(plan.workspace > 0)
-    {
-        if(!workspace || workspace_bytes < qsync_qlinear_bwd_rm_workspace_bytes(tag, M, N, K)) return QSYNC_ERR_WORKSPACE;
-        if(!aligned16(workspace)) return QSYNC_ERR_ALIGN;
-    }
+    const GemmPlan plan   = plan_gemm(tag, N, K, M, -1, -1, true, /*tn=*/M > 0), plan_dx = plan_gemm(tag, M, K, N);
+    const size_t   off_dw = round256(plan_dx.workspace);
+    const bool     want_dw = dw_opt && N > 0 && K > 0;
     GemmProblem p{};
     p.prec = tag; p.M = N; p.N = K; p.K = M;
     p.A = dyq; p.B = xq; p.C = dw_opt; p.c_dtype = dwdt;
     p.s0 = i8 ? sdy : nullptr; p.s1 = i8 ? sx : nullptr; p.acc_dump = acc_dw_dump_opt;
-    p.tn = true;
-    if(M == 0)
-    {   // empty contraction: the NT form writes the zeros (no operand is read)
-        p.tn = false;
+    p.tn = M > 0;      // (empty contraction: the NT form writes the zeros, no operand is read)
+    const GemmProblem pdx  = data_gradient(tag, M, N, K, dyq, sdy, wqbT, swb, wbgran, dx_opt, dxdt, acc_dx_dump_opt);
+    const int         pair = dx_opt && want_dw ? gradient_pair_tile(pdx, plan_dx, p, plan) : -1;
+    if(pair >= 0)
+    {   // (a workspace is asked for as if the two ran by their own plans)
+        const bool part = plan_dx.workspace > 0 || (db_opt && M > 0);
+        if(part && (!workspace || workspace_bytes < qsync_qlinear_bwd_workspace_bytes(tag, M, N, K))) return QSYNC_ERR_WORKSPACE;
+        if(plan.workspace > 0 && (!workspace || workspace_bytes < qsync_qlinear_bwd_rm_workspace_bytes(tag, M, N, K))) return QSYNC_ERR_WORKSPACE;
+        if((part || plan.workspace > 0) && !aligned16(workspace)) return QSYNC_ERR_ALIGN;
+        const int rc = hip_status(launch_gradient_pair(pdx, p, pair, static_cast<hipStream_t>(stream)));
+        if(rc != QSYNC_OK) return rc;
+    }
+    // the data gradient by itself is the NT GEMM of qsync_qlinear_bwd, which also owns the bias gradient
+    if((dx_opt && pair < 0) || db_opt)
+    {
+        const int rc = qsync_qlinear_bwd(tag, M, N, K, dyq, nullptr, sdy, nullptr, nullptr, wqbT, swb, wbgran, pair < 0 ? dx_opt : nullptr,
+                                         dxdt, nullptr, dwdt, db_opt, dy_float_opt, dydt, acc_dx_dump_opt, nullptr, workspace,
+                                         workspace_bytes, stream);
+        if(rc != QSYNC_OK) return rc;
+    }
+    if(!want_dw || pair >= 0) return QSYNC_OK;
+    if(plan.workspace > 0)
+    {
+        if(!workspace || workspace_bytes < qsync_qlinear_bwd_rm_workspace_bytes(tag, M, N, K)) return QSYNC_ERR_WORKSPACE;
+        if(!aligned16(workspace)) return QSYNC_ERR_ALIGN;
     }
     return hip_status(launch_gemm(p, plan, workspace ? static_cast<char*>(workspace) + off_dw : nullptr,
                                   static_cast<hipStream_t>(stream)));

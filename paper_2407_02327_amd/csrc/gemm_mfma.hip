@@ -124,6 +124,16 @@ struct GemmKernelArgs
     int            code_qmax;
 };
 
+// A 64-bit value that is the same in every lane, as a pair of scalar registers.
+__device__ __forceinline__ int64_t uniform64(int64_t v)
+{
+    const uint64_t u = static_cast<uint64_t>(v);
+    // (the builtin returns a signed int: widen each half through uint32_t, never by sign extension)
+    const uint32_t lo = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(static_cast<uint32_t>(u))));
+    const uint32_t hi = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(static_cast<uint32_t>(u >> 32))));
+    return static_cast<int64_t>((static_cast<uint64_t>(hi) << 32) | static_cast<uint64_t>(lo));
+}
+
 // Work item (K split, tile) of a workgroup.  Workgroups are dealt round-robin to the eight XCDs
 // in launch order, each with its own L2, so XCD x takes the x-th contiguous eighth of the item
 // list (split-major, tiles in grouped row-major order inside a split): the workgroups that share
@@ -389,8 +399,9 @@ __device__ __forceinline__ void frag_reads(v4i32 (&dst)[F], uint32_t addr, std::
 // matrix instruction wants; two reads make a lane's 16 operand bytes.  16-byte chunks are XOR-swizzled per row so
 // that the lanes of one access pass touch all banks once.  Everything behind the fragments
 // (matrix instructions, epilogue, split K) is shared with the NT form.  Kb is the contraction length P here.
-template <typename TR, int BM, int BN, int WGM, int WGN, int ST, bool SPLIT, bool CONV = false, bool TN = false>
-__global__ __launch_bounds__(64 * WGM * WGN) void gemm_nt_kernel(const GemmKernelArgs p)
+// `lin` is the workgroup's index among the `splits` x tiles workgroups of the problem.
+template <typename TR, int BM, int BN, int WGM, int WGN, int ST, bool SPLIT, bool CONV, bool TN>
+__device__ __forceinline__ void gemm_tile(const GemmKernelArgs& p, int lin, int splits)
 {
     static_assert(!(SPLIT && CONV && !TN), "the implicit patch matrix of the forward is not combined with split K");
     static_assert(!TN || (TR::kElemBytes <= 2 && BM == BN && BM >= 64), "TN: int8 or binary16 operands, square tiles");
@@ -410,8 +421,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_nt_kernel(const GemmKerne
     extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
 
     int split, tm, tn;
-    item_of_block(static_cast<int>(blockIdx.y * gridDim.x + blockIdx.x), p.tiles_m, p.tiles_n, SPLIT ? static_cast<int>(gridDim.y) : 1, p.group_m,
-                  split, tm, tn);
+    item_of_block(lin, p.tiles_m, p.tiles_n, SPLIT ? splits : 1, p.group_m, split, tm, tn);
     const int64_t m0 = static_cast<int64_t>(tm) * BM, n0 = static_cast<int64_t>(tn) * BN;
     const int     tid = threadIdx.x, lane = tid % kWaveSize;
     const int     wave = __builtin_amdgcn_readfirstlane(tid / kWaveSize);     // wavefront index, held in an SGPR
@@ -524,10 +534,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_nt_kernel(const GemmKerne
     }
     // the panel base as two scalar registers (the wavefront index is uniform, so is the choice of panel)
     const uint64_t gbits = reinterpret_cast<uint64_t>(gbase) - kDmaBias;
-    // (the builtin returns a signed int: widen each half through uint32_t, never by sign extension)
-    const uint32_t glo    = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(static_cast<uint32_t>(gbits))));
-    const uint32_t ghi    = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(static_cast<uint32_t>(gbits >> 32))));
-    const uint8_t* sbase0 = reinterpret_cast<const uint8_t*>((static_cast<uint64_t>(ghi) << 32) | static_cast<uint64_t>(glo));
+    const uint8_t* sbase0 = reinterpret_cast<const uint8_t*>(uniform64(static_cast<int64_t>(gbits)));
     // All DPW instructions of a wavefront share one LDS base (M0): instruction d reaches its 1 KB
     // slot through the instruction's immediate offset (d - DPW/2) KB.  Rewriting M0 between direct
     // loads would stall the wavefront until the previous load has left the issue queue
@@ -549,6 +556,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_nt_kernel(const GemmKerne
             conv_t.tap[par]  = conv_t.koff[par] / conv_cb;
             conv_t.c0[par]   = conv_t.koff[par] % conv_cb;
         }
+    const int64_t tn_ld = TN ? uniform64(is_a ? p.M : p.N) : 0;      // operand row length in elements
     auto dma = [&](int stage, int kt) {
         const int64_t  kb    = static_cast<int64_t>(kt) * kRowBytes;
         uint8_t*       lbase = lds + stage * STAGE_BYTES + wave * (DPW * 1024) + (dma_group<DPW>() / 2) * 1024;
@@ -582,7 +590,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_nt_kernel(const GemmKerne
                 }
                 return;
             }
-        const uint8_t* sb    = TN ? sbase0 + kb * (is_a ? p.M : p.N) : sbase0 + kb;      // TN: 128 operand rows further
+        const uint8_t* sb    = TN ? sbase0 + kb * tn_ld : sbase0 + kb;      // TN: 128 operand rows further
         asm volatile("" : "+s"(sb));      // keep base + K offset a scalar pair: the lane offsets stay loop-invariant 32-bit values
         if(!TN && kt == tail_kt)
             dma_sequence_tail<DPW>(std::make_integer_sequence<int, DPW>{}, sb, voff, gchunk, kb, p.Kb, lbase);
@@ -993,6 +1001,33 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_nt_kernel(const GemmKerne
         staged_store(float{}, std::false_type{}, static_cast<uint8_t*>(p.C));
         if(p.amax_bits) publish_amax(abs_bits_as_f32<4>(out_run));
     }
+}
+
+template <typename TR, int BM, int BN, int WGM, int WGN, int ST, bool SPLIT, bool CONV = false, bool TN = false>
+__global__ __launch_bounds__(64 * WGM * WGN) void gemm_nt_kernel(const GemmKernelArgs p)
+{
+    gemm_tile<TR, BM, BN, WGM, WGN, ST, SPLIT, CONV, TN>(p, static_cast<int>(blockIdx.y * gridDim.x + blockIdx.x),
+                                                         static_cast<int>(gridDim.y));
+}
+
+// Two independent GEMMs of one operand type in one launch, the first `na` workgroups on the first: the data and weight gradient
+// of an operator.  Each of them alone leaves compute units idle unless its tiles happen to fill the chip, and pays its own
+// launch, first-load latency and drain.
+struct GemmPairArgs
+{
+    GemmKernelArgs g[2];
+    int            na;
+};
+template <typename TR, int BM, int BN, int WGM, int WGN, int ST, bool TNA>
+__global__ __launch_bounds__(64 * WGM * WGN) void gemm_nt_pair_kernel(const GemmPairArgs p)
+{
+    const int blk = static_cast<int>(blockIdx.x);
+    if constexpr(!TNA)
+        gemm_tile<TR, BM, BN, WGM, WGN, ST, false, false, false>(p.g[blk < p.na ? 0 : 1], blk < p.na ? blk : blk - p.na, 1);
+    else if(blk < p.na)
+        gemm_tile<TR, BM, BN, WGM, WGN, ST, false, false, TNA>(p.g[0], blk, 1);
+    else
+        gemm_tile<TR, BM, BN, WGM, WGN, ST, false, false, false>(p.g[1], blk - p.na, 1);
 }
 
 // ---------------------------------------------------------------------------------------------------------------
@@ -1509,6 +1544,31 @@ hipError_t launch_traits(int tile, const GemmKernelArgs& a, int splits, hipStrea
     }
 }
 
+template <typename TR, int BM, int BN, int WGM, int WGN, int ST, bool TNA>
+hipError_t launch_pair_tile(const GemmPairArgs& p, int workgroups, hipStream_t st)
+{
+    constexpr size_t lds_bytes = ST * static_cast<size_t>(BM + BN) * kRowBytes + 2 * BN * sizeof(float) + 64;
+    static bool      attr_set[kMaxDevices] = {};      // per instantiation and device; benign if set twice
+    const int        slot = current_device_slot();
+    if(slot < 0 || !attr_set[slot])
+    {
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_nt_pair_kernel<TR, BM, BN, WGM, WGN, ST, TNA>),
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds_bytes));
+        if(e != hipSuccess) return e;
+        if(slot >= 0) attr_set[slot] = true;
+    }
+    gemm_nt_pair_kernel<TR, BM, BN, WGM, WGN, ST, TNA><<<dim3(static_cast<unsigned>(workgroups)), dim3(64 * WGM * WGN), lds_bytes, st>>>(p);
+    return hipGetLastError();
+}
+template <typename TR, bool TNA>
+hipError_t launch_pair_traits(int tile, const GemmPairArgs& p, int workgroups, hipStream_t st)
+{
+    if(tile == 1)
+        return workgroups <= kNumCu ? launch_pair_tile<TR, 128, 128, 2, 4, 3, TNA>(p, workgroups, st)
+                                    : launch_pair_tile<TR, 128, 128, 2, 4, 2, TNA>(p, workgroups, st);
+    return launch_pair_tile<TR, 64, 64, 2, 2, 2, TNA>(p, workgroups, st);
+}
+
 // The persistent kernel serves full 256x256 tiles with binary16 output and nothing optional in the epilogue.
 bool persistent_eligible(const GemmKernelArgs& a, int prec, int tile, int splits)
 {
@@ -1543,6 +1603,17 @@ void set_gemm_tile_override(int tile) { g_tile_override = (tile >= 0 && tile < k
 static thread_local int g_persistent_mode = -1;   // 1: whenever eligible; anything else: never (the default, see launch_gemm)
 void set_gemm_persistent_mode(int mode) { g_persistent_mode = (mode == 0 || mode == 1) ? mode : -1; }
 
+// Model of a tile shape's time; the constants are explained in plan_gemm.
+struct TileModel { double r1, rmax, ovh, cap; int occ; };
+static constexpr TileModel kTileModel[kNumTiles] = {{14.0, 15.8, 6.9, 2280.0, 1}, {8.3, 9.0, 4.2, 1900.0, 2}, {3.55, 5.48, 3.2, 2060.0, 4}};
+// Row-major (TN) operands: a K tile takes twice the LDS fragment reads, and a 64-wide tile of int8 operands
+// loads 64-byte row pieces (binary16: 128 bytes, no penalty); fitted slow-down of the main loop per tile shape.
+static double tn_factor(int tile, int prec, bool tn)
+{
+    const double rate[kNumTiles] = {0.94, 0.89, prec == 8 ? 0.74 : 0.97};
+    return tn ? rate[tile] : 1.0;
+}
+
 GemmPlan plan_gemm(int prec, int64_t M, int64_t N, int64_t K, int force_tile, int force_splits, bool allow_split, bool tn)
 {
     if(force_tile < 0 && g_tile_override >= 0)
@@ -1550,7 +1621,7 @@ GemmPlan plan_gemm(int prec, int64_t M, int64_t N, int64_t K, int force_tile, in
         GemmPlan forced = plan_gemm(prec, M, N, K, g_tile_override, force_splits >= 1 ? force_splits : 0, allow_split, tn);
         return forced;
     }
-    GemmPlan plan{1, 1, 0};
+    GemmPlan plan{1, 1, 0, 0.0};
     if(M <= 0 || N <= 0) return plan;
     const int64_t kb     = K * (prec == 8 ? 1 : (prec == 16 ? 2 : 4));
     if(prec == 32 && kb % 16 != 0) return plan;                   // the any-shape fp32 kernel: no tiles to plan
@@ -1565,15 +1636,10 @@ GemmPlan plan_gemm(int prec, int64_t M, int64_t N, int64_t K, int force_tile, in
     //   sharing it; the chip as a whole retires at most `cap` Mop/us (the power limit: 256 busy units do not
     //   each reach `rmax`); every round of co-resident workgroups costs `ovh` us of launch, first-load latency
     //   and epilogue; split K adds its reduction pass.
-    struct TileModel { double r1, rmax, ovh, cap; int occ; };
-    const TileModel model[kNumTiles] = {{14.0, 15.8, 6.9, 2280.0, 1}, {8.3, 9.0, 4.2, 1900.0, 2}, {3.55, 5.48, 3.2, 2060.0, 4}};
-    // Row-major (TN) operands: a K tile takes twice the LDS fragment reads, and a 64-wide tile of int8 operands
-    // loads 64-byte row pieces (binary16: 128 bytes, no penalty); fitted slow-down of the main loop per tile shape.
-    const double    tn_rate[kNumTiles] = {0.94, 0.89, prec == 8 ? 0.74 : 0.97};
     const double    cus = 256.0;
     auto estimate = [&](int t, int64_t s) {
-        const TileModel& m    = model[t];
-        const double     tnf  = tn ? tn_rate[t] : 1.0;
+        const TileModel& m    = kTileModel[t];
+        const double     tnf  = tn_factor(t, prec, tn);
         const double     wgs  = static_cast<double>(ntiles(t)) * static_cast<double>(s);
         const double     per  = std::ceil(wgs / cus);                                    // workgroups of the busiest unit
         const double     share = per < m.occ ? per : m.occ;                              // co-resident ones
@@ -1600,8 +1666,8 @@ GemmPlan plan_gemm(int prec, int64_t M, int64_t N, int64_t K, int force_tile, in
         if(allow_split && !(force_tile >= 0 && force_splits < 0))
             for(int f = 0; f < 3; ++f)
             {
-                const int64_t fill = f == 0 ? 256 : (f == 1 ? 512 : 256 * model[t].occ);
-                if(fill > 256 * model[t].occ) continue;
+                const int64_t fill = f == 0 ? 256 : (f == 1 ? 512 : 256 * kTileModel[t].occ);
+                if(fill > 256 * kTileModel[t].occ) continue;
                 int64_t       s    = fill / ntiles(t);
                 if(s > ktiles / 8) s = ktiles / 8;                // keep at least 8 K tiles per split
                 if(s > 128) s = 128;
@@ -1620,21 +1686,16 @@ GemmPlan plan_gemm(int prec, int64_t M, int64_t N, int64_t K, int force_tile, in
     plan.tile      = tile;
     plan.splits    = splits;
     plan.workspace = splits > 1 ? static_cast<size_t>(splits) * M * N * 4 : 0;
+    plan.us        = estimate(tile, splits);
     return plan;
 }
 
-hipError_t launch_gemm(const GemmProblem& p, const GemmPlan& plan, void* workspace, hipStream_t stream)
+// Kernel arguments of a problem under a plan; hipErrorInvalidValue for operands the kernels cannot address.
+static hipError_t kernel_args(const GemmProblem& p, const GemmPlan& plan, void* workspace, GemmKernelArgs& a)
 {
-    if(p.M <= 0 || p.N <= 0) return hipSuccess;
-    if(p.prec == 32 && (p.conv_H > 0 || p.b_remap_C > 0)) return hipErrorInvalidValue;
-    // fp32 on the matrix cores needs 16-byte aligned, 16-byte multiple operand rows; anything else takes the
-    // any-shape kernel
-    if(p.prec == 32 && ((p.K * 4) % 16 != 0 || ((reinterpret_cast<uintptr_t>(p.A) | reinterpret_cast<uintptr_t>(p.B)) & 15) != 0))
-        return launch_gemm_f32(p, stream);
     const int      esz = p.prec == 8 ? 1 : (p.prec == 16 ? 2 : 4);
     // lane offsets inside an operand panel are 32-bit: 255 rows of K bytes (plus the load immediates) must fit
     if(p.K > kGemmMaxRowBytes / esz) return hipErrorInvalidValue;
-    GemmKernelArgs a;
     a.A = static_cast<const uint8_t*>(p.A);
     a.B = static_cast<const uint8_t*>(p.B);
     a.M = p.M; a.N = p.N; a.Kb = p.K * esz;
@@ -1687,6 +1748,21 @@ hipError_t launch_gemm(const GemmProblem& p, const GemmPlan& plan, void* workspa
     a.tiles_m = static_cast<int>((p.M + ts.bm - 1) / ts.bm);
     a.tiles_n = static_cast<int>((p.N + ts.bn - 1) / ts.bn);
     a.group_m = kGroupM;      // (2, 4, 16 and 32 measured within noise of 8 on config 5's shapes, int8 and binary16)
+    return hipSuccess;
+}
+
+hipError_t launch_gemm(const GemmProblem& p, const GemmPlan& plan, void* workspace, hipStream_t stream)
+{
+    if(p.M <= 0 || p.N <= 0) return hipSuccess;
+    if(p.prec == 32 && (p.conv_H > 0 || p.b_remap_C > 0)) return hipErrorInvalidValue;
+    // fp32 on the matrix cores needs 16-byte aligned, 16-byte multiple operand rows; anything else takes the
+    // any-shape kernel
+    if(p.prec == 32 && ((p.K * 4) % 16 != 0 || ((reinterpret_cast<uintptr_t>(p.A) | reinterpret_cast<uintptr_t>(p.B)) & 15) != 0))
+        return launch_gemm_f32(p, stream);
+    GemmKernelArgs   a;
+    const hipError_t bad = kernel_args(p, plan, workspace, a);
+    if(bad != hipSuccess) return bad;
+    const int splits = plan.splits < 1 ? 1 : plan.splits;
     // The persistent kernel is opt-in.  Launched alone and back to back it beats the per-tile kernel by 7-20 % (the
     // write-back of a tile overlaps the next tile's K loop), but inside an operator sequence its fixed tile
     // assignment loses what it gains: workgroups that start late, behind the tail of the previous kernel, still
@@ -1719,6 +1795,86 @@ hipError_t launch_gemm(const GemmProblem& p, const GemmPlan& plan, void* workspa
         else     reduce(float{}, std::false_type{}, workspace, nullptr);
     }
     return hipGetLastError();
+}
+
+// K tiles of a workgroup per round of 256 workgroups -> time of the compute unit that gets the first workgroup of every
+// round (the hardware deals them out in order): `occ` workgroups share the unit's rate evenly, the next one starts when
+// one ends.
+static double unit_time(const TileModel& m, double mop, const double* rounds, int n)
+{
+    double left[8], us = 0.0;
+    int    active = 0, next = 0;
+    for(;;)
+    {
+        while(active < m.occ && next < n) left[active++] = rounds[next++];
+        if(active == 0) return us;
+        double shortest = left[0];
+        for(int i = 1; i < active; ++i) shortest = left[i] < shortest ? left[i] : shortest;
+        const double rate = m.r1 * active < m.rmax ? m.r1 * active : m.rmax;
+        us += shortest * active * mop / rate;
+        int kept = 0;
+        for(int i = 0; i < active; ++i)
+            if(left[i] > shortest) left[kept++] = left[i] - shortest;
+        active = kept;
+    }
+}
+
+// Tile on which two GEMMs share a launch (`a` first), or -1 when two launches are estimated to be about as fast: with more
+// than sixteen rounds of workgroups each of them fills the chip by itself, and a long contraction unsplit beside short ones
+// would outlast them.  Separate launches -> one, measured: int8 1808x1040x784 21.3 -> 14.2 us, 4096x768x3072 38.0 ->
+// 29.5, 1024^3 11.1 -> 7.1; binary16 2056x1000x1032 36.5 -> 26.9, 4096x3072x768 62.2 -> 54.2; not paired: 4096x768x768
+// binary16 27.5 (one launch 36.6), 3000x768x768 26.4 (31.2).
+static int pair_tile(const GemmProblem& a, const GemmProblem& b, double separate_us)
+{
+    constexpr int kMaxRounds = 16;
+    int    tile = -1;
+    double best = 0.93 * separate_us;
+    for(int t = 1; t < kNumTiles; ++t)
+    {
+        if(g_tile_override >= 0 && t != g_tile_override) continue;
+        TileModel m = kTileModel[t];
+        if(a.prec == 16) m.r1 *= t == 1 ? 0.83 : 0.6;       // a long binary16 contraction left over alone, fitted
+        auto tiles  = [&](const GemmProblem& p) { return ((p.M + kTiles[t].bm - 1) / kTiles[t].bm) * ((p.N + kTiles[t].bn - 1) / kTiles[t].bn); };
+        auto ktiles = [&](const GemmProblem& p) { return std::ceil(static_cast<double>(p.K * (p.prec / 8)) / kRowBytes) / tn_factor(t, p.prec, p.tn); };
+        const int64_t wa = tiles(a), wgs = wa + tiles(b);
+        if(wgs > kMaxRounds * kNumCu) continue;
+        const double ka = ktiles(a), kb = ktiles(b), mop = 2.0 * kTiles[t].bm * kTiles[t].bn * kRowBytes * 1e-6;
+        double rounds[kMaxRounds];
+        int    n = 0;
+        for(int64_t at = 0; at < wgs; at += kNumCu) rounds[n++] = at < wa ? ka : kb;
+        const double unit = unit_time(m, mop, rounds, n), chip = (wa * ka + (wgs - wa) * kb) * mop / m.cap;
+        const double full = std::ceil(static_cast<double>(wgs) / (kNumCu * m.occ));      // rounds of co-resident workgroups
+        const double us   = (unit > chip ? unit : chip) + m.ovh * (full > 1.0 ? full - 0.5 : full);
+        if(us < best) { best = us; tile = t; }
+    }
+    return tile;
+}
+
+int gradient_pair_tile(const GemmProblem& dx, const GemmPlan& plan_dx, const GemmProblem& dw, const GemmPlan& plan_dw)
+{
+    auto plain = [](const GemmProblem& p) {
+        return (p.prec == 8 || p.prec == 16) && p.M > 0 && p.N > 0 && p.K > 0 && p.conv_H == 0 && p.b_remap_C == 0
+            && !p.out_amax_bits && !p.out_codes;
+    };
+    if(dx.prec != dw.prec || !plain(dx) || !plain(dw) || dx.tn || g_persistent_mode == 1) return -1;
+    const double us = plan_dx.us + plan_dw.us;
+    return dw.tn || dw.K >= dx.K ? pair_tile(dw, dx, us) : pair_tile(dx, dw, us);
+}
+
+hipError_t launch_gradient_pair(const GemmProblem& dx, const GemmProblem& dw, int tile, hipStream_t stream)
+{
+    const bool         dw_first = dw.tn || dw.K >= dx.K;      // the longer contraction, or the row-major one
+    const GemmProblem &a = dw_first ? dw : dx, &b = dw_first ? dx : dw;
+    const GemmPlan     plan{tile, 1, 0, 0.0};
+    GemmPairArgs       args;
+    hipError_t         e = kernel_args(a, plan, nullptr, args.g[0]);
+    if(e == hipSuccess) e = kernel_args(b, plan, nullptr, args.g[1]);
+    if(e != hipSuccess) return e;
+    args.na = args.g[0].tiles_m * args.g[0].tiles_n;
+    const int workgroups = args.na + args.g[1].tiles_m * args.g[1].tiles_n;
+    if(a.prec == 8)
+        return a.tn ? launch_pair_traits<I8Traits, true>(tile, args, workgroups, stream) : launch_pair_traits<I8Traits, false>(tile, args, workgroups, stream);
+    return a.tn ? launch_pair_traits<F16Traits, true>(tile, args, workgroups, stream) : launch_pair_traits<F16Traits, false>(tile, args, workgroups, stream);
 }
 
 }  // namespace qsync

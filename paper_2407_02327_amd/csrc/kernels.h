@@ -115,6 +115,7 @@ struct GemmPlan {
     int     tile;          // index into the tile table (see gemm_mfma.hip)
     int     splits;        // split-K factor (1 = epilogue fused in the GEMM kernel)
     size_t  workspace;     // bytes needed for split-K partials
+    double  us;            // estimated time
 };
 // force_tile / force_splits < 0 leave the choice to the heuristic; tn: plan for GemmProblem::tn operands.
 GemmPlan plan_gemm(int prec, int64_t M, int64_t N, int64_t K, int force_tile = -1, int force_splits = -1,
@@ -124,6 +125,10 @@ void set_gemm_tile_override(int tile);
 // 1: launch the persistent 256x256 kernel whenever a problem is eligible; anything else: never (the default)
 void set_gemm_persistent_mode(int mode);
 hipError_t launch_gemm(const GemmProblem& p, const GemmPlan& plan, void* workspace, hipStream_t stream);
+// Data and weight gradient of one operator in one launch: the tile to run both on, or -1 when their own plans are
+// estimated to be about as fast one after the other.
+int gradient_pair_tile(const GemmProblem& dx, const GemmPlan& plan_dx, const GemmProblem& dw, const GemmPlan& plan_dw);
+hipError_t launch_gradient_pair(const GemmProblem& dx, const GemmProblem& dw, int tile, hipStream_t stream);
 
 // ---- measurement probe (probe.hip): matrix instructions on register operands, no memory traffic
 constexpr int kProbeBlocks = 512;       // workgroups of 4 wavefronts, 4 matrix instructions per wavefront and iteration

@@ -42,10 +42,10 @@ class QLinear:
         and the weight-gradient GEMM reads them as they are (qsync_qlinear_bwd_rm; needs M % 128 == 0 and N, K
         multiples of 16 -- 8 for FP16); True: the conversion also writes the transposed copies xqT / dyqT for
         qsync_qlinear_bwd.
-        None picks False when the shape allows it and the copies are large enough to be worth it: the row-major
-        weight-gradient GEMM is 6-8 % slower on 256-wide tiles and loses the 64-wide tile, the quantizer saves one
-        byte written per element (measured on MI355X: 16384x4096x1024 operators 0.803 -> 0.749 ms per step,
-        4096x768x3072 operators 0.129 -> 0.132 ms)."""
+        None picks False when the shape allows it: the row-major weight-gradient GEMM is up to 10 % slower than the one
+        on transposed copies, but the conversions write a byte (FP16: two) less per element (measured on MI355X, whole
+        steps with copies -> row-major: INT8 1024^3 48.5 -> 45.6 us, 4096x3072x768 91.8 -> 88.8, 8192x1024x1024 87.7
+        -> 82.9; FP16 2048x256x256 38.3 -> 23.8, 4096x3072x768 109.3 -> 93.3)."""
         self.tag, self.M, self.N, self.K = tag, M, N, K
         # max |Y| collected by the forward GEMM's epilogue, for a consumer that quantizes Y as it is
         self.y_amax = torch.zeros(1, dtype=torch.float32, device=device) if collect_y_amax else None
@@ -59,7 +59,7 @@ class QLinear:
         if transposed_copies is False and not rm_ok:
             raise ValueError("transposed_copies=False needs tag INT8 or FP16 with the same backward tag, M % 128 == 0, "
                              "N and K multiples of 16 (FP16: 8)")
-        self.rowmajor_bwd = (rm_ok and M * (N + K) >= (32 << 20)) if transposed_copies is None else not transposed_copies
+        self.rowmajor_bwd = rm_ok if transposed_copies is None else not transposed_copies
         dy_dtype = dy_dtype or x_dtype
         dev = device
         e = lambda *s, dt: torch.empty(*s, dtype=dt, device=dev)

@@ -146,6 +146,37 @@ def test_k_pipeline_fills_and_drains_at_every_length(K):
             assert np.all(np.abs(got - ref) <= 4 * 2.0 ** -24 * size + 1e-30)
 
 
+@pytest.mark.parametrize("tag", [Q.INT8, Q.FP16])
+@pytest.mark.parametrize("shape", [(64, 128, 128), (400, 64, 272), (128, 16, 16), (1024, 256, 512), (2304, 768, 512),
+                                   (4096, 3072, 768)])
+def test_both_gradients_of_one_call_equal_the_separate_calls(tag, shape):
+    """dX and dW asked for together may share one launch (one workgroup to several per compute unit, row-major and
+    transposed operands): the same values as when each is asked for alone.  INT8: the same bits.  FP16: the tile or the
+    K splits may differ, so fp32 sums of M (N) products in another order: 2^-24 sqrt(n) of the sum's size, plus dX's
+    binary16 rounding."""
+    M, N, K = shape
+    say("both gradients", tag, shape)
+    g = torch.Generator(device="cuda").manual_seed(M + N + K)
+    x, w = torch.randn(M, K, device="cuda", generator=g).half(), torch.randn(N, K, device="cuda", generator=g) * 0.02
+    dy = (torch.randn(M, N, device="cuda", generator=g) * 1e-3).half()
+    for copies in ((True, False) if M % 128 == 0 else (True,)):
+        op = QLinear(tag, M, N, K, x_dtype=torch.float16, y_dtype=torch.float16, dx_dtype=torch.float32,
+                     transposed_copies=copies)
+        op.forward(x, w)
+        op.convert_dy(dy)
+        op.gemm_bwd(dy)
+        dx, dw = op.dx.clone(), op.dw.clone()
+        op.dx.fill_(float("nan")), op.dw.fill_(float("nan"))
+        op.gemm_bwd_part("dx", dy)
+        op.gemm_bwd_part("dw", dy)
+        if tag == Q.INT8:
+            assert torch.equal(dx, op.dx) and torch.equal(dw, op.dw)
+        else:
+            for got, want, n in [(dx, op.dx, N), (dw, op.dw, M)]:
+                bound = 4 * 2.0 ** -24 * n ** 0.5 * want.abs().max()
+                assert (got - want).abs().max() <= bound
+
+
 @pytest.mark.parametrize("ydt,dxdt,dwdt", [(np.float16, np.float16, np.float32), (np.float32, np.float32, np.float16)])
 def test_production_epilogue_on_ragged_shapes_int8(ydt, dxdt, dwdt):
     """INT8 without accumulator dumps: the staged-store epilogue (and the split-K reduction) on ragged shapes
