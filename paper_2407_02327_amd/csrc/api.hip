@@ -508,12 +508,9 @@ int qsync_qlinear_bwd_fp16_of_int8(int64_t M, int64_t N, int64_t K, const void* 
         e = launch_dequantize(xqT, kI8, M, K, K, nullptr, nullptr, 1.0f, sx, nullptr, xhT, kF16, st);
     else if(dw_opt)      // x_hat^T, straight from the saved transposed codes
         e = launch_dequantize(xqT, kI8, K, M, M, nullptr, nullptr, 1.0f, sx, nullptr, xhT, kF16, st);
-    if(e == hipSuccess && dx_opt)
-    {   // w_hat with the forward's scales (one per output channel, or one), then its transpose for dX
-        e = launch_dequantize(wq, kI8, N, K, K, wgran == QSYNC_PER_ROW ? sw : nullptr, nullptr, 1.0f,
-                              wgran == QSYNC_PER_ROW ? nullptr : sw, nullptr, wh, kF16, st);
-        if(e == hipSuccess) e = launch_convert(wh, kF16, N, K, K, kF16, nullptr, whT, st);
-    }
+    if(e == hipSuccess && dx_opt)      // w_hat with the forward's scales (one per output channel, or one) and its transpose for dX
+        e = launch_dequantize_f16_both(static_cast<const int8_t*>(wq), N, K, wgran == QSYNC_PER_ROW ? sw : nullptr,
+                                       wgran == QSYNC_PER_ROW ? nullptr : sw, wh, whT, st);
     void* const dyh_out  = dydt == QSYNC_F16 ? nullptr : const_cast<void*>(dyh);
     void* const dyhT_out = (dw_opt && !x_rowmajor) ? dyhT : nullptr;
     if(e == hipSuccess && (dyh_out || dyhT_out))      // dY narrowed to binary16 (or used in place) and transposed

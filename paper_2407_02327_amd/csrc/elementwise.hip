@@ -308,8 +308,8 @@ __global__ __launch_bounds__(BLOCK) void colreduce_kernel(const T* __restrict__ 
                                                           const TensorFinal fin)
 {
     constexpr int E = VEC ? Vec16<T>::N : 1;
-    constexpr int U = 4;                                    // rows in flight per lane
-    __shared__ float lds[BLOCK * E];
+    constexpr int U = 4;      // rows in flight per lane (eight: 16384x4096 binary16 28.2 -> 30.3 us)
+    __shared__ __attribute__((aligned(16))) float lds[BLOCK * E];
     __shared__ float lds_max[16];
     RunMax<T>        rm;                                    // OP_SUMMAX only
     float            sqv     = 0.0f;                        // OP_SUMMAX with fin.sumsq_opt: sum of squares
@@ -393,25 +393,29 @@ __global__ __launch_bounds__(BLOCK) void colreduce_kernel(const T* __restrict__ 
             if(threadIdx.x == 0) fin.partial_sq[blockIdx.y * gridDim.x + blockIdx.x] = bs;
         }
     }
-    // fold the block's row lanes in order 0, 1, ... through LDS
-    auto fold_rows = [&]() {
+    // fold the block's row lanes in order 0, 1, ... through LDS, a column per thread (consecutive threads, consecutive
+    // banks; one row lane folding eight columns each met eight-way conflicts with fifteen of sixteen wavefronts idle)
 #pragma unroll
-        for(int e = 0; e < E; ++e) lds[(tr * tpr + tc) * E + e] = acc[e];
-        __syncthreads();
-        if(tr == 0)
-            for(int q = 1; q < rpb; ++q)
-#pragma unroll
-                for(int e = 0; e < E; ++e)
-                {
-                    const float o = lds[(q * tpr + tc) * E + e];
-                    acc[e] = OP == OP_MAX ? fmaxf(acc[e], o) : acc[e] + o;
-                }
-    };
-    fold_rows();
-    if(tr == 0 && c0 < cols)
+    for(int e = 0; e < E; e += (E % 4 == 0 ? 4 : 1))
     {
-#pragma unroll
-        for(int e = 0; e < E; ++e) partial[static_cast<int64_t>(blockIdx.y) * cols + c0 + e] = acc[e];
+        if constexpr(E % 4 == 0)
+            *reinterpret_cast<float4*>(lds + (tr * tpr + tc) * E + e) = make_float4(acc[e], acc[e + 1], acc[e + 2], acc[e + 3]);
+        else
+            lds[(tr * tpr + tc) * E + e] = acc[e];
+    }
+    __syncthreads();
+    const int strip = tpr * E;
+    for(int t = threadIdx.x; t < strip; t += BLOCK)
+    {
+        const int64_t c = static_cast<int64_t>(blockIdx.x) * strip + t;
+        if(c >= cols) break;
+        float v = lds[t];
+        for(int q = 1; q < rpb; ++q)
+        {
+            const float o = lds[q * strip + t];
+            v = OP == OP_MAX ? fmaxf(v, o) : v + o;
+        }
+        partial[static_cast<int64_t>(blockIdx.y) * cols + c] = v;
     }
 }
 
@@ -1239,67 +1243,6 @@ __global__ __launch_bounds__(kBlock) void convert_kernel(const Ti* __restrict__ 
     }
 }
 
-// Vector path of the cast to binary16 (and of the plain binary16 copy/transpose): each lane owns an
-// 8 x 8 patch (8 rows x 16 bytes of binary16 output), a wavefront is 8 x 8 patches, so every load and
-// every store instruction covers 128-byte (binary16) or 256-byte (fp32 input) row segments.  The patch
-// is transposed in registers by pairing 16-bit halves; no LDS, no barrier.  Needs cols % 8 == 0, 16-byte
-// aligned rows, and rows % 8 == 0 when the transposed copy is written.
-template <typename Ti>
-__global__ __launch_bounds__(kBlock) void cast_f16_patch_kernel(const Ti* __restrict__ x, int64_t rows, int64_t cols,
-                                                                int64_t ld, __half* __restrict__ q,
-                                                                __half* __restrict__ qT, int64_t grid_x)
-{
-    const int     lane = threadIdx.x % kWaveSize, wave = threadIdx.x / kWaveSize;
-    const int64_t by = blockIdx.x / grid_x, bx = blockIdx.x - by * grid_x;
-    const int64_t r0 = (by * (kBlock / kWaveSize) + wave) * 64 + (lane / 8) * 8;
-    const int64_t c0 = bx * 64 + (lane % 8) * 8;
-    if(r0 >= rows || c0 >= cols) return;
-    uint32_t w[8][4];                           // row i of the patch as four pairs of binary16
-#pragma unroll
-    for(int i = 0; i < 8; ++i)
-    {
-        const int64_t r  = r0 + i;
-        const bool    ok = r < rows;
-        if constexpr(sizeof(Ti) == 2)
-        {
-            const uint4 v = ok ? *reinterpret_cast<const uint4*>(x + r * ld + c0) : make_uint4(0, 0, 0, 0);
-            w[i][0] = v.x; w[i][1] = v.y; w[i][2] = v.z; w[i][3] = v.w;
-        }
-        else
-        {
-            const uint4 a = ok ? *reinterpret_cast<const uint4*>(x + r * ld + c0) : make_uint4(0, 0, 0, 0);
-            const uint4 b = ok ? *reinterpret_cast<const uint4*>(x + r * ld + c0 + 4) : make_uint4(0, 0, 0, 0);
-            const uint32_t f[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
-#pragma unroll
-            for(int j = 0; j < 4; ++j)
-                w[i][j] = static_cast<uint32_t>(__half_as_ushort(__float2half_rn(__uint_as_float(f[2 * j]))))
-                        | (static_cast<uint32_t>(__half_as_ushort(__float2half_rn(__uint_as_float(f[2 * j + 1])))) << 16);
-        }
-    }
-    if(q)
-    {
-#pragma unroll
-        for(int i = 0; i < 8; ++i)
-            if(r0 + i < rows)
-                *reinterpret_cast<uint4*>(q + (r0 + i) * cols + c0) = make_uint4(w[i][0], w[i][1], w[i][2], w[i][3]);
-    }
-    if(qT)
-    {   // rows % 8 == 0 here: all eight rows exist.  Column c of the patch = halves c%2 of pair c/2 of every row.
-#pragma unroll
-        for(int c = 0; c < 8; ++c)
-        {
-            uint32_t t[4];
-#pragma unroll
-            for(int g = 0; g < 4; ++g)
-            {
-                const uint32_t lo = w[2 * g][c / 2], hi = w[2 * g + 1][c / 2];
-                t[g] = (c % 2 == 0) ? ((lo & 0xFFFFu) | (hi << 16)) : ((lo >> 16) | (hi & 0xFFFF0000u));
-            }
-            *reinterpret_cast<uint4*>(qT + (c0 + c) * rows + r0) = make_uint4(t[0], t[1], t[2], t[3]);
-        }
-    }
-}
-
 // ------------------------------------------------------------------ standalone dequantize
 // code * scale (+ bias) in the output type.  The dequantized scalar is the exact product of a code and a scale
 // (Indicator section: x_hat = round(x_bar) * q_x); for an 8-bit code and one binary32 scale that product has at
@@ -1321,6 +1264,79 @@ template <> __device__ __forceinline__ __half scaled_code<__half>(float a, float
     if(e != 0.0f && (b & 1u) == 0u && (b & 0x7F800000u) != 0u)
         b += ((e > 0.0f) == (p > 0.0f)) ? 1u : 0xFFFFFFFFu;       // the neighbour on the residual's side is the odd one
     return __float2half_rn(__uint_as_float(b));
+}
+
+// Conversion with an optional transposed copy, tiled like the fixed-point quantizer: a workgroup owns 64 rows x 16
+// threads of 16 output bytes, a thread four rows.  Codes (int8) are scaled per row or per tensor.  The transposed copy
+// goes through LDS, four rows of a column per write, and leaves as whole 128-byte (binary16) or 256-byte segments.
+// Latency bound at small sizes: one 8 x 8 patch per lane kept half the wavefronts in flight (2056x1032 fp32 -> binary16
+// with both copies 8.5 -> 7.4 us, 4096x1024 11.5 -> 9.4; fp32 8192x4096 transposed element by element 69.2 -> 54.6).
+constexpr int kConvertRows = 64;
+template <typename Ti, typename To>
+__global__ __launch_bounds__(kBlock) void convert_tile_kernel(const Ti* __restrict__ x, int64_t rows, int64_t cols, int64_t ld,
+                                                              const float* __restrict__ row_scale, const float* __restrict__ scale,
+                                                              To* __restrict__ q, To* __restrict__ qT, int tiles_x)
+{
+    constexpr int TC = 16 / sizeof(To);                      // columns of a thread
+    constexpr int CH = kConvertRows * sizeof(To) / 16;       // 16-byte chunks of a tile column
+    __shared__ __attribute__((aligned(16))) uint8_t lds_t[16 * TC * CH * 16];
+    const int     by = static_cast<int>(blockIdx.x) / tiles_x, bx = static_cast<int>(blockIdx.x) - by * tiles_x;
+    const int     cg = threadIdx.x % 16, quad = threadIdx.x / 16;
+    const int64_t tile_r = static_cast<int64_t>(by) * kConvertRows, tile_c = static_cast<int64_t>(bx) * 16 * TC;
+    const int64_t r0 = tile_r + quad * 4, c0 = tile_c + cg * TC;
+    struct alignas(sizeof(Ti) * TC < 16 ? sizeof(Ti) * TC : 16) In { Ti v[TC]; };
+    union Out { To v[TC]; uint4 w; };
+    In  in[4];
+    Out out[4];
+#pragma unroll
+    for(int i = 0; i < 4; ++i)
+        if(r0 + i < rows && c0 < cols) in[i] = *reinterpret_cast<const In*>(x + (r0 + i) * ld + c0);
+#pragma unroll
+    for(int i = 0; i < 4; ++i)
+    {
+        const bool ok = r0 + i < rows && c0 < cols;
+        float      g  = 1.0f;
+        if constexpr(std::is_same<Ti, int8_t>::value) g = row_scale ? (ok ? row_scale[r0 + i] : 1.0f) : *scale;
+#pragma unroll
+        for(int e = 0; e < TC; ++e)
+        {
+            if constexpr(std::is_same<Ti, int8_t>::value) out[i].v[e] = scaled_code<To>(static_cast<float>(in[i].v[e]), g, 0.0f, false);
+            else out[i].v[e] = convert_elem<To, Ti>(in[i].v[e]);
+        }
+        if(q && ok) *reinterpret_cast<uint4*>(q + (r0 + i) * cols + c0) = out[i].w;
+    }
+    if(!qT) return;
+#pragma unroll
+    for(int e = 0; e < TC; ++e)
+    {
+        const uint32_t* w[4] = {&out[0].w.x, &out[1].w.x, &out[2].w.x, &out[3].w.x};
+        uint8_t*        col  = lds_t + (cg * TC + e) * CH * 16;
+        if constexpr(sizeof(To) == 2)
+        {
+            const uint32_t sel = e % 2 ? 0x07060302u : 0x05040100u;
+            const uint32_t lo = __builtin_amdgcn_perm(w[1][e / 2], w[0][e / 2], sel), hi = __builtin_amdgcn_perm(w[3][e / 2], w[2][e / 2], sel);
+            *reinterpret_cast<uint2*>(col + ((quad / 2) ^ (cg % CH)) * 16 + (quad % 2) * 8) = make_uint2(lo, hi);
+        }
+        else
+            *reinterpret_cast<uint4*>(col + (quad ^ (cg % CH)) * 16) = make_uint4(w[0][e], w[1][e], w[2][e], w[3][e]);
+    }
+    __syncthreads();
+#pragma unroll
+    for(int k = threadIdx.x; k < 16 * TC * CH; k += kBlock)
+    {
+        const int     lc = k / CH, ch = k % CH;
+        const int64_t r = tile_r + ch * TC, c = tile_c + lc;        // a chunk holds TC rows
+        if(c >= cols || r >= rows) continue;
+        Out v;
+        v.w = *reinterpret_cast<const uint4*>(lds_t + lc * CH * 16 + ((ch ^ ((lc / TC) % CH)) * 16));
+        To* dst = qT + c * rows + r;
+        if(rows % TC == 0)
+            *reinterpret_cast<uint4*>(dst) = v.w;
+        else
+#pragma unroll
+            for(int e = 0; e < TC; ++e)
+                if(r + e < rows) dst[e] = v.v[e];
+    }
 }
 
 template <typename Ti, typename To, int V>
@@ -1824,21 +1840,27 @@ hipError_t launch_prepare_weights(const void* w, int wdt, int64_t N, int64_t K, 
     return prepare_weights_typed(static_cast<const __half*>(w), N, K, qmax, sw, iw, aw_opt, wq, swb, iwb, wqbT, workspace, stream);
 }
 
+// The tiled conversion where its vector rules hold; false: nothing was launched.
+template <typename Ti, typename To>
+static bool convert_tiles(const Ti* x, int64_t rows, int64_t cols, int64_t ld, const float* row_scale, const float* scale, To* q,
+                          To* qT, hipStream_t st)
+{
+    constexpr int64_t TC = 16 / sizeof(To), in_bytes = TC * sizeof(Ti) < 16 ? TC * sizeof(Ti) : 16;
+    const int64_t     bx = (cols + 16 * TC - 1) / (16 * TC), by = (rows + kConvertRows - 1) / kConvertRows;
+    if(cols % TC != 0 || (reinterpret_cast<uintptr_t>(x) & (in_bytes - 1)) != 0 || (ld * sizeof(Ti)) % in_bytes != 0 || !aligned16(q)
+       || (rows % TC == 0 && !aligned16(qT)) || bx * by >= (int64_t(1) << 31))
+        return false;
+    convert_tile_kernel<Ti, To><<<dim3(static_cast<unsigned>(bx * by)), dim3(kBlock), 0, st>>>(x, rows, cols, ld, row_scale, scale, q, qT,
+                                                                                             static_cast<int>(bx));
+    return true;
+}
+
 template <typename Ti, typename To>
 static hipError_t convert_typed(const void* x, int64_t rows, int64_t cols, int64_t ld, void* q, void* qT,
                                 hipStream_t st)
 {
-    if constexpr(std::is_same<To, __half>::value)
-    {
-        const int64_t bx = (cols + 63) / 64, by = (rows + 255) / 256;
-        if(cols % 8 == 0 && aligned16(x) && (ld * sizeof(Ti)) % 16 == 0 && (!q || aligned16(q))
-           && (!qT || (aligned16(qT) && rows % 8 == 0)) && bx * by < (int64_t(1) << 31))
-        {
-            cast_f16_patch_kernel<Ti><<<dim3(static_cast<unsigned>(bx * by)), dim3(kBlock), 0, st>>>(
-                static_cast<const Ti*>(x), rows, cols, ld, static_cast<__half*>(q), static_cast<__half*>(qT), bx);
-            return hipGetLastError();
-        }
-    }
+    if(convert_tiles(static_cast<const Ti*>(x), rows, cols, ld, nullptr, nullptr, static_cast<To*>(q), static_cast<To*>(qT), st))
+        return hipGetLastError();
     const int64_t gx = (cols + 63) / 64, gy = (rows + 63) / 64;
     convert_kernel<Ti, To, false><<<dim3(static_cast<unsigned>(gx * gy)), dim3(kBlock), 0, st>>>(
         static_cast<const Ti*>(x), rows, cols, ld, static_cast<To*>(q), static_cast<To*>(qT), gx, 0, 0, 0);
@@ -1900,6 +1922,14 @@ static hipError_t dequantize_typed(const void* a, int64_t rows, int64_t cols, in
         dequantize_kernel<Ti, To, 1><<<dim3(nb), dim3(kBlock), 0, st>>>(static_cast<const Ti*>(a), rows, cols, ld, rs,
                                                                        cs, ts, tsd, cb, static_cast<To*>(y));
     return hipGetLastError();
+}
+
+hipError_t launch_dequantize_f16_both(const int8_t* a, int64_t rows, int64_t cols, const float* row_scale, const float* scale, void* y,
+                                      void* yT, hipStream_t stream)
+{
+    if(convert_tiles(a, rows, cols, cols, row_scale, scale, static_cast<__half*>(y), static_cast<__half*>(yT), stream)) return hipGetLastError();
+    const hipError_t e = launch_dequantize(a, kI8, rows, cols, cols, row_scale, nullptr, 1.0f, row_scale ? nullptr : scale, nullptr, y, kF16, stream);
+    return e != hipSuccess ? e : launch_convert(y, kF16, rows, cols, cols, kF16, nullptr, yT, stream);
 }
 
 hipError_t launch_dequantize(const void* a, int adt, int64_t rows, int64_t cols, int64_t ld, const float* row_scale,
