@@ -564,7 +564,7 @@ WgradLayout wgrad_layout(int tag, int64_t nimg, int64_t H, int64_t W, int64_t C,
 bool wgrad_gathers(int tag, int64_t nimg, int64_t H, int64_t W, int64_t C, int64_t N)
 {
     const int64_t esz = tag == QSYNC_INT8 ? 1 : 2, M = nimg * H * W;
-    return M > 0 && M % 128 == 0 && M * C * esz < (int64_t(1) << 31) && N < (int64_t(1) << 24) && 9 * C < (int64_t(1) << 24)
+    return M > 0 && M * C * esz < (int64_t(1) << 31) && N < (int64_t(1) << 24) && 9 * C < (int64_t(1) << 24)
            && H <= 65535 && W <= 65535;
 }
 bool wgrad_shape_ok(int tag, int64_t nimg, int64_t H, int64_t W, int64_t C, int64_t N)
@@ -584,17 +584,22 @@ size_t qsync_conv3x3_wgrad_workspace_bytes(int tag, int64_t nimg, int64_t H, int
     if((tag != QSYNC_INT8 && tag != QSYNC_FP16) || nimg <= 0 || H <= 0 || W <= 0 || C <= 0 || N <= 0
        || !wgrad_shape_ok(tag, nimg, H, W, C, N))
         return 0;
-    if(wgrad_gathers(tag, nimg, H, W, C, N))
-    {   // split-K partials only (the largest over the tile shapes, so that a pinned tile fits too)
-        size_t need = plan_gemm(tag, N, 9 * C, nimg * H * W, -1, -1, true, true).workspace;
-        for(int t = 0; t < 3; ++t)
-        {
-            const size_t w = plan_gemm(tag, N, 9 * C, nimg * H * W, t, 0, true, true).workspace;
-            need = w > need ? w : need;
-        }
-        return round256(need);
+    if(!wgrad_gathers(tag, nimg, H, W, C, N)) return wgrad_layout(tag, nimg, H, W, C, N).total;
+    // split-K partials only (the largest over the tile shapes, so that a pinned tile fits too)
+    size_t need = plan_gemm(tag, N, 9 * C, nimg * H * W, -1, -1, true, true).workspace;
+    for(int t = 0; t < 3; ++t)
+    {
+        const size_t w = plan_gemm(tag, N, 9 * C, nimg * H * W, t, 0, true, true).workspace;
+        need = w > need ? w : need;
     }
-    return wgrad_layout(tag, nimg, H, W, C, N).total;
+    // a pixel count that is no multiple of 128 used to need the transposed copies: callers bring that much, and a call
+    // with less is refused
+    if(nimg * H * W % 128 != 0)
+    {
+        const size_t copies = wgrad_layout(tag, nimg, H, W, C, N).total;
+        need = need > copies ? need : copies;
+    }
+    return round256(need);
 }
 
 int qsync_conv3x3_wgrad(int tag, int64_t nimg, int64_t H, int64_t W, int64_t C, int64_t N, const void* xq, const float* sx,
@@ -615,9 +620,10 @@ int qsync_conv3x3_wgrad(int tag, int64_t nimg, int64_t H, int64_t W, int64_t C, 
     {
         const int64_t  M    = nimg * H * W;
         const GemmPlan plan = plan_gemm(tag, N, 9 * C, M, -1, -1, true, /*tn=*/true);
-        if(plan.workspace > 0)
+        const size_t   need = M % 128 != 0 ? qsync_conv3x3_wgrad_workspace_bytes(tag, nimg, H, W, C, N) : plan.workspace;
+        if(need > 0)
         {
-            if(!workspace || workspace_bytes < plan.workspace) return QSYNC_ERR_WORKSPACE;
+            if(!workspace || workspace_bytes < need) return QSYNC_ERR_WORKSPACE;
             if((reinterpret_cast<uintptr_t>(workspace) & 255) != 0) return QSYNC_ERR_ALIGN;
         }
         GemmProblem p{};

@@ -295,6 +295,15 @@ __device__ __forceinline__ void conv_tn_sequence(std::integer_sequence<int, Ds..
     (conv_tn_issue<Ds, DPW>(x, zero, pix_base, delta[Ds], code[Ds], hw[Ds], H, W, dr, hq, lds_mid), ...);
 }
 
+// TN, last K tile with fewer contraction rows than a stage holds: rows from `rows` on are fetched from the tile's first
+// row instead (and overwritten with zeros once landed).
+template <int DPW, int RPS, int... Ds>
+__device__ __forceinline__ void dma_sequence_short(std::integer_sequence<int, Ds...>, const uint8_t* sbase,
+                                                   const uint32_t (&voff)[DPW], int row0, int rows, uint32_t row_bytes, uint8_t* lds_mid)
+{
+    (dma_issue<Ds, DPW>(sbase, voff[Ds] - (row0 + Ds * RPS >= rows ? static_cast<uint32_t>(row0 + Ds * RPS) * row_bytes : 0u), lds_mid), ...);
+}
+
 template <int DPW, int... Ds>
 __device__ __forceinline__ void fill_dma_imms(int (&imm)[DPW], std::integer_sequence<int, Ds...>)
 {
@@ -557,12 +566,20 @@ __device__ __forceinline__ void gemm_tile(const GemmKernelArgs& p, int lin, int 
             conv_t.c0[par]   = conv_t.koff[par] % conv_cb;
         }
     const int64_t tn_ld = TN ? uniform64(is_a ? p.M : p.N) : 0;      // operand row length in elements
+    // TN: stage row of the lane in load slot 0, rows from slot to slot, and the contraction rows of a partial last K tile
+    constexpr int tn_rps = TN ? 1024 / (BM * ESZ) : 0;
+    const int     tn_row0 = TN ? ((wave * DPW - (is_a ? 0 : BM / 8)) * 1024 + lane * 16) / (BM * ESZ) : 0;
+    const int     tn_tail_rows = TN ? static_cast<int>(p.Kb % kRowBytes) / ESZ : 0;
     auto dma = [&](int stage, int kt) {
         const int64_t  kb    = static_cast<int64_t>(kt) * kRowBytes;
         uint8_t*       lbase = lds + stage * STAGE_BYTES + wave * (DPW * 1024) + (dma_group<DPW>() / 2) * 1024;
         if constexpr(CONVTN)
             if(!is_a)
             {   // (requested for consecutive K tiles only, starting at kt_begin: hw is advanced by every call)
+                if(kt == tail_kt)      // (the last request) stage rows without a pixel read zeros
+#pragma unroll
+                    for(int d = 0; d < DPW; ++d)
+                        if(tn_row0 + d * tn_rps >= tn_tail_rows) tnc_code[d] = 0;
                 conv_tn_sequence<DPW>(std::make_integer_sequence<int, DPW>{}, p.B, reinterpret_cast<const uint8_t*>(&g_zero_chunk),
                                       static_cast<int64_t>(kt) * tnc_KR * p.conv_Cb, tnc_delta, tnc_code, hw, p.conv_H, p.conv_W,
                                       tnc_dr, tnc_hq, lbase);
@@ -592,7 +609,10 @@ __device__ __forceinline__ void gemm_tile(const GemmKernelArgs& p, int lin, int 
             }
         const uint8_t* sb    = TN ? sbase0 + kb * tn_ld : sbase0 + kb;      // TN: 128 operand rows further
         asm volatile("" : "+s"(sb));      // keep base + K offset a scalar pair: the lane offsets stay loop-invariant 32-bit values
-        if(!TN && kt == tail_kt)
+        if(TN && kt == tail_kt)
+            dma_sequence_short<DPW, tn_rps>(std::make_integer_sequence<int, DPW>{}, sb, voff, tn_row0, tn_tail_rows,
+                                            static_cast<uint32_t>(tn_ld * ESZ), lbase);
+        else if(!TN && kt == tail_kt)
             dma_sequence_tail<DPW>(std::make_integer_sequence<int, DPW>{}, sb, voff, gchunk, kb, p.Kb, lbase);
         else
             dma_sequence<DPW>(std::make_integer_sequence<int, DPW>{}, sb, voff, lbase);
@@ -601,12 +621,12 @@ __device__ __forceinline__ void gemm_tile(const GemmKernelArgs& p, int lin, int 
     // stage they read to the next direct load, and the compiler does not see those reads), zero-fills its
     // out-of-K chunks, then joins the block.
     auto zero_tail = [&](int stage, int kt) {
-        if(!TN && kt == tail_kt)
+        if((!CONVTN || is_a) && kt == tail_kt)
         {
             const int64_t kb = static_cast<int64_t>(kt) * kRowBytes;
 #pragma unroll
             for(int d = 0; d < DPW; ++d)
-                if(kb + gchunk[d & 1] >= p.Kb)
+                if(TN ? tn_row0 + d * tn_rps >= tn_tail_rows : kb + gchunk[d & 1] >= p.Kb)
                     *reinterpret_cast<uint4*>(lds + stage * STAGE_BYTES + (wave * DPW + d) * 1024 + lane * 16)
                         = make_uint4(0, 0, 0, 0);
         }
@@ -1708,7 +1728,7 @@ static hipError_t kernel_args(const GemmProblem& p, const GemmPlan& plan, void* 
     if(p.tn)
     {   // A [K, M], B [K, N] row-major int8 or binary16: rows are contraction indices (128 bytes' worth per K tile),
         // 16-byte column chunks
-        if((p.prec != 8 && p.prec != 16) || p.b_remap_C > 0 || (p.K * esz) % kRowBytes != 0
+        if((p.prec != 8 && p.prec != 16) || p.b_remap_C > 0
            || (p.M * esz) % 16 != 0 || (p.N * esz) % 16 != 0
            || p.M >= (int64_t(1) << 24) || p.N >= (int64_t(1) << 24)
            || ((reinterpret_cast<uintptr_t>(p.A) | reinterpret_cast<uintptr_t>(p.B)) & 15) != 0)

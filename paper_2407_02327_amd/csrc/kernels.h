@@ -98,8 +98,8 @@ struct GemmProblem {
     // [3*b_remap_C, K] matrix, read with the K axis displaced by (tap/3 - 1)*b_remap_shift bytes (a multiple of
     // 16, at most 1024); that many bytes in front of and behind the matrix must be readable.
     int64_t     b_remap_C = 0, b_remap_shift = 0;
-    // tn (int8 only): A is [K, M] and B is [K, N], row-major with the contraction axis as rows (K % 128 == 0,
-    // M % 16 == 0, N % 16 == 0): C[m,n] = sum_k A[k,m] B[k,n] without transposed copies of the operands
+    // tn (int8 and binary16): A is [K, M] and B is [K, N], row-major with the contraction axis as rows (any K; rows
+    // of 16-byte multiples): C[m,n] = sum_k A[k,m] B[k,n] without transposed copies of the operands
     bool        tn = false;
     // optional device word holding a running maximum of |C| as stored (bit pattern of a non-negative fp32);
     // raised by the epilogue (by the reduction pass when K is split)
