@@ -493,7 +493,8 @@ template <int THREADS> __device__ __forceinline__ float block_max_all(float v, f
 // tile's own loads), which saves the maximum pass its arrival counter -- 5 us of dependent device-scope round trips --
 // and this pass a launch between them.  kWhole: the workgroup finds the maximum of the whole tensor by itself.
 enum ScaleFrom { kInv = 0, kPartials = 1, kWhole = 2 };
-constexpr int kFoldMax = 256;
+constexpr int     kFoldMax    = 256;
+constexpr int64_t kWholeBytes = 128 << 10;      // largest tensor of kWhole
 struct TensorScale
 {
     const float* inv;            // kInv
@@ -516,8 +517,8 @@ __device__ __forceinline__ float tensor_inverse_scale(const TensorScale& ts, con
         for(int i = threadIdx.x; i < ts.n; i += THREADS) m = fmaxf(m, ts.partial[i]);
     }
     else
-    {   // (contiguous, 16-byte aligned, whole vectors)
-        constexpr int U    = 8;
+    {   // (contiguous, 16-byte aligned, whole vectors)  all of it in flight at once
+        constexpr int U    = static_cast<int>(kWholeBytes / 16 / THREADS);
         const int64_t nvec = n / Vec16<T>::N;
         const uint4*  xv   = reinterpret_cast<const uint4*>(x);
         RunMax<T>     rm;
@@ -591,6 +592,28 @@ __device__ __forceinline__ void store_transposed_tile(const uint32_t (&t)[8], ui
     for(int j = 0; j < 8; ++j)
         *reinterpret_cast<uint32_t*>(lds_t + (8 * cg + j) * TR + (((quad / 4) ^ (cg % CH)) * 16) + (quad % 4) * 4) = t[j];
     __syncthreads();
+    if(rows <= TR && rows % 16 != 0 && (reinterpret_cast<uintptr_t>(qT) & 3) == 0 && trow(tile_c) == tile_c)
+    {   // the tile holds whole columns of odd length, i.e. one contiguous piece of qT: dwords across column ends
+        const uint32_t len = static_cast<uint32_t>(cols - tile_c < kTileCols ? cols - tile_c : kTileCols) * static_cast<uint32_t>(rows);
+        const uint32_t h   = static_cast<uint32_t>(rows);
+        int8_t*        dst = qT + tile_c * rows;
+        for(uint32_t w = threadIdx.x; 4 * w < len; w += THREADS)
+        {
+            uint32_t col = 4 * w / h, r = 4 * w - col * h, v = 0u;
+#pragma unroll
+            for(int b = 0; b < 4; ++b)
+            {
+                if(4 * w + b < len)
+                    v |= static_cast<uint32_t>(lds_t[col * TR + (((r / 16) ^ ((col / 8) % CH)) * 16) + r % 16]) << (8 * b);
+                if(++r == h) { r = 0u; ++col; }
+            }
+            if(4 * w + 4 <= len)
+                *reinterpret_cast<uint32_t*>(dst + 4 * w) = v;
+            else
+                for(uint32_t b = 0; 4 * w + b < len; ++b) dst[4 * w + b] = static_cast<int8_t>((v >> (8 * b)) & 0xFFu);
+        }
+        return;
+    }
 #pragma unroll
     for(int k = threadIdx.x; k < kTileCols * CH; k += THREADS)
     {
@@ -1750,8 +1773,6 @@ hipError_t launch_quantize_int8(const void* x, int xdt, int64_t rows, int64_t co
 // Per-tensor maximum, scales and codes of a contiguous tensor.  Up to kWholeBytes one launch, every workgroup of which
 // reads the whole tensor for its maximum (no workgroup waits for another); above that a launch that leaves one maximum
 // per block and the quantizing launch, which folds them.
-constexpr int64_t kWholeBytes = 128 << 10;
-
 template <typename T>
 static hipError_t absmax_quantize_typed(const T* x, int64_t rows, int64_t cols, int qmax, int rnd, uint64_t seed,
                                         uint64_t offset, float* scale, float* inv_scale, float* amax_opt, int8_t* q,

@@ -1865,7 +1865,7 @@ static int pair_tile(const GemmProblem& a, const GemmProblem& b, double separate
         const double unit = unit_time(m, mop, rounds, n), chip = (wa * ka + (wgs - wa) * kb) * mop / m.cap;
         const double full = std::ceil(static_cast<double>(wgs) / (kNumCu * m.occ));      // rounds of co-resident workgroups
         const double us   = (unit > chip ? unit : chip) + m.ovh * (full > 1.0 ? full - 0.5 : full);
-        if(us < best) { best = us; tile = t; }
+        if(us < (tile < 0 ? 1.0 : 0.95) * best) { best = us; tile = t; }      // (the smaller tile must win by 5 %)
     }
     return tile;
 }

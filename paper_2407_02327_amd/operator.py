@@ -109,7 +109,7 @@ class QLinear:
             if x_amax is not None:
                 Q.qsync_scale_from_amax(x_amax, self.bits, self.sx, self.ix, True, stream)
             else:
-                # maximum, scale and codes: one launch for small activations, the two separate passes otherwise
+                # maximum, scale and codes in one call
                 Q.qsync_absmax_quantize(x, M, K, self.bits, Q.ROUND_NEAREST, 0, 0, self.sx, self.ix, self.ax, self.xq,
                                         self.xqT, self.ws_absmax, -1, stream)
                 return
@@ -143,10 +143,8 @@ class QLinear:
             Q.qsync_quantize(w, N, K, K, self.tag, 0, 0, 0, 0, 0, None, self.wq, self.wqbT, stream)
             return
         if self.w_gran == Q.PER_TENSOR:       # one quantization serves the forward and dX
-            Q.qsync_absmax_scale(w, N, K, K, Q.PER_TENSOR, self.bits, self.sw, self.iw, self.aw, None, self.ws_absmax_w,
-                                 stream)
-            Q.qsync_quantize(w, N, K, K, Q.INT8, self.bits, Q.PER_TENSOR, Q.ROUND_NEAREST, 0, 0, self.iw, self.wq,
-                             self.wqbT, stream)
+            Q.qsync_absmax_quantize(w, N, K, self.bits, Q.ROUND_NEAREST, 0, 0, self.sw, self.iw, self.aw, self.wq,
+                                    self.wqbT, self.ws_absmax_w, -1, stream)
             self.swb = self.sw
             return
         # per-output-channel codes for the forward; dX contracts over the output channels, so its weight codes
@@ -352,8 +350,8 @@ class QConv3x3:
             Q.qsync_conv3x3_wflip(self.wq, N, C, self.wflip, stream)
             return
         if self.w_gran == Q.PER_TENSOR:
-            Q.qsync_absmax_scale(w, N, K, K, Q.PER_TENSOR, self.bits, self.sw, self.iw, self.aw, None, self.ws_absmax_w, stream)
-            Q.qsync_quantize(w, N, K, K, Q.INT8, self.bits, Q.PER_TENSOR, Q.ROUND_NEAREST, 0, 0, self.iw, self.wq, None, stream)
+            Q.qsync_absmax_quantize(w, N, K, self.bits, Q.ROUND_NEAREST, 0, 0, self.sw, self.iw, self.aw, self.wq, None,
+                                    self.ws_absmax_w, -1, stream)
             self.swb = self.sw
             Q.qsync_conv3x3_wflip(self.wq, N, C, self.wflip, stream)
             return
