@@ -505,11 +505,11 @@ int qsync_qlinear_bwd_fp16_of_int8(int64_t M, int64_t N, int64_t K, const void* 
     const void* dyh = dydt == QSYNC_F16 ? dy : base + l.off_dyh;
     hipError_t e = hipSuccess;
     if(dw_opt && x_rowmajor)      // x_hat = code * q_x narrowed to binary16, [M,K] like the codes (xqT holds xq here)
-        e = launch_dequantize(xqT, kI8, M, K, K, nullptr, nullptr, 1.0f, sx, nullptr, xhT, kF16, st);
+        e = launch_dequantize_f16_tiles(static_cast<const int8_t*>(xqT), M, K, nullptr, sx, xhT, nullptr, st);
     else if(dw_opt)      // x_hat^T, straight from the saved transposed codes
-        e = launch_dequantize(xqT, kI8, K, M, M, nullptr, nullptr, 1.0f, sx, nullptr, xhT, kF16, st);
+        e = launch_dequantize_f16_tiles(static_cast<const int8_t*>(xqT), K, M, nullptr, sx, xhT, nullptr, st);
     if(e == hipSuccess && dx_opt)      // w_hat with the forward's scales (one per output channel, or one) and its transpose for dX
-        e = launch_dequantize_f16_both(static_cast<const int8_t*>(wq), N, K, wgran == QSYNC_PER_ROW ? sw : nullptr,
+        e = launch_dequantize_f16_tiles(static_cast<const int8_t*>(wq), N, K, wgran == QSYNC_PER_ROW ? sw : nullptr,
                                        wgran == QSYNC_PER_ROW ? nullptr : sw, wh, whT, st);
     void* const dyh_out  = dydt == QSYNC_F16 ? nullptr : const_cast<void*>(dyh);
     void* const dyhT_out = (dw_opt && !x_rowmajor) ? dyhT : nullptr;

@@ -1945,12 +1945,12 @@ static hipError_t dequantize_typed(const void* a, int64_t rows, int64_t cols, in
     return hipGetLastError();
 }
 
-hipError_t launch_dequantize_f16_both(const int8_t* a, int64_t rows, int64_t cols, const float* row_scale, const float* scale, void* y,
+hipError_t launch_dequantize_f16_tiles(const int8_t* a, int64_t rows, int64_t cols, const float* row_scale, const float* scale, void* y,
                                       void* yT, hipStream_t stream)
 {
     if(convert_tiles(a, rows, cols, cols, row_scale, scale, static_cast<__half*>(y), static_cast<__half*>(yT), stream)) return hipGetLastError();
     const hipError_t e = launch_dequantize(a, kI8, rows, cols, cols, row_scale, nullptr, 1.0f, row_scale ? nullptr : scale, nullptr, y, kF16, stream);
-    return e != hipSuccess ? e : launch_convert(y, kF16, rows, cols, cols, kF16, nullptr, yT, stream);
+    return e != hipSuccess || !yT ? e : launch_convert(y, kF16, rows, cols, cols, kF16, nullptr, yT, stream);
 }
 
 hipError_t launch_dequantize(const void* a, int adt, int64_t rows, int64_t cols, int64_t ld, const float* row_scale,

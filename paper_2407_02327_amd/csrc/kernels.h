@@ -48,8 +48,9 @@ hipError_t launch_dequantize(const void* a, int adt, int64_t rows, int64_t cols,
                              const float* row_scale, const float* col_scale, float tensor_scale,
                              const float* tensor_scale_dev, const float* col_bias, void* y, int ydt,
                              hipStream_t stream);
-// int8 codes times one scale per row, or one scale, narrowed to binary16 once: y [rows, cols] and yT [cols, rows]
-hipError_t launch_dequantize_f16_both(const int8_t* a, int64_t rows, int64_t cols, const float* row_scale, const float* scale, void* y,
+// int8 codes times one scale per row, or one scale, narrowed to binary16 once: y [rows, cols] and, unless nullptr,
+// yT [cols, rows]
+hipError_t launch_dequantize_f16_tiles(const int8_t* a, int64_t rows, int64_t cols, const float* row_scale, const float* scale, void* y,
                                       void* yT, hipStream_t stream);
 // 3x3 / stride 1 / pad 1 patches of an int8 NHWC tensor: a [M, 9C] and/or aT [9C, M], M = nimg*H*W
 hipError_t launch_prepare_weights(const void* w, int wdt, int64_t N, int64_t K, float qmax, float* sw, float* iw,
