@@ -98,10 +98,21 @@ __device__ __forceinline__ void fold_sumsq(const float* partial_sq, unsigned int
     __syncthreads();
     if(threadIdx.x == 0)
     {
-        double t = 0.0;
-        for(unsigned int i = 0; i < nblocks; ++i)
-            t += i < cap ? lds_d[i]
-                         : static_cast<double>(__hip_atomic_load(partial_sq + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+        // (sixteen LDS reads in flight per batch: one at a time, every addition waited out an LDS round trip)
+        double             t = 0.0;
+        const unsigned int n = nblocks < cap ? nblocks : cap;
+        unsigned int       i = 0;
+        for(; i + 16 <= n; i += 16)
+        {
+            double v[16];
+#pragma unroll
+            for(int k = 0; k < 16; ++k) v[k] = lds_d[i + k];
+#pragma unroll
+            for(int k = 0; k < 16; ++k) t += v[k];
+        }
+        for(; i < n; ++i) t += lds_d[i];
+        for(; i < nblocks; ++i)
+            t += static_cast<double>(__hip_atomic_load(partial_sq + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
         *sumsq = static_cast<float>(t);
     }
 }
