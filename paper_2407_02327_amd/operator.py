@@ -45,7 +45,9 @@ class QLinear:
         None picks False when the shape allows it: the row-major weight-gradient GEMM is up to 10 % slower than the one
         on transposed copies, but the conversions write a byte (FP16: two) less per element (measured on MI355X, whole
         steps with copies -> row-major: INT8 1024^3 48.5 -> 45.6 us, 4096x3072x768 91.8 -> 88.8, 8192x1024x1024 87.7
-        -> 82.9; FP16 2048x256x256 38.3 -> 23.8, 4096x3072x768 109.3 -> 93.3)."""
+        -> 82.9; FP16 from fp32 activations 1024^3 50.4 -> 48.8).  Except a binary16 activation under the FP16 tag below
+        M (N + K) = 32 Mi elements: without copies the activation itself is what backward reads, so ask for that
+        (2048x256x256 38.3 -> 23.8, 4096x3072x768 109.3 -> 93.3) only if its buffer stays untouched until then."""
         self.tag, self.M, self.N, self.K = tag, M, N, K
         # max |Y| collected by the forward GEMM's epilogue, for a consumer that quantizes Y as it is
         self.y_amax = torch.zeros(1, dtype=torch.float32, device=device) if collect_y_amax else None
@@ -59,7 +61,11 @@ class QLinear:
         if transposed_copies is False and not rm_ok:
             raise ValueError("transposed_copies=False needs tag INT8 or FP16 with the same backward tag, M % 128 == 0, "
                              "N and K multiples of 16 (FP16: 8)")
-        self.rowmajor_bwd = rm_ok if transposed_copies is None else not transposed_copies
+        # a binary16 activation under the FP16 tag is its own row-major operand: smaller operators keep their copy, so that
+        # a caller may reuse the activation's buffer between forward and backward as it always could there
+        in_place = tag == Q.FP16 and x_dtype == torch.float16
+        self.rowmajor_bwd = ((rm_ok and (not in_place or M * (N + K) >= (32 << 20))) if transposed_copies is None
+                             else not transposed_copies)
         dy_dtype = dy_dtype or x_dtype
         dev = device
         e = lambda *s, dt: torch.empty(*s, dtype=dt, device=dev)

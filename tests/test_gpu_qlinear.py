@@ -177,6 +177,25 @@ def test_both_gradients_of_one_call_equal_the_separate_calls(tag, shape):
                 assert (got - want).abs().max() <= bound
 
 
+@pytest.mark.parametrize("tag,act", [(Q.INT8, torch.float16), (Q.FP16, torch.float16), (Q.FP16, torch.float32)])
+def test_activation_buffer_may_be_reused_before_backward(tag, act):
+    """The operator's default form holds its own copy of a small activation: overwriting x after forward changes nothing."""
+    say("activation reused", tag, act)
+    M, N, K = 256, 128, 192
+    g = torch.Generator(device="cuda").manual_seed(3)
+    x, w = torch.randn(M, K, device="cuda", generator=g).to(act), torch.randn(N, K, device="cuda", generator=g) * 0.02
+    dy = (torch.randn(M, N, device="cuda", generator=g) * 1e-3).to(act)
+    results = []
+    for overwrite in (False, True):
+        op = QLinear(tag, M, N, K, x_dtype=act, y_dtype=act, dx_dtype=act)
+        mine = x.clone()
+        op.forward(mine, w)
+        if overwrite:
+            mine.fill_(7.0)
+        results.append([t.clone() for t in op.backward(dy)])
+    assert all(torch.equal(a, b) for a, b in zip(*results))
+
+
 @pytest.mark.parametrize("ydt,dxdt,dwdt", [(np.float16, np.float16, np.float32), (np.float32, np.float32, np.float16)])
 def test_production_epilogue_on_ragged_shapes_int8(ydt, dxdt, dwdt):
     """INT8 without accumulator dumps: the staged-store epilogue (and the split-K reduction) on ragged shapes
