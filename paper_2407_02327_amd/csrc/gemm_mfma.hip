@@ -235,14 +235,16 @@ __device__ uint4 g_zero_chunk;     // never written: static storage starts at ze
 
 __device__ const float g_one = 1.0f;     // stands in for an absent scale
 
-// Where a lane's two chunk positions (by parity of the load slot) stand on the K axis: the byte offset, the tap it lies
-// in and the channel offset in that tap.  Requests go over consecutive K tiles, so the position is carried on instead of
+// Where a lane's two chunk positions (by parity of the load slot) stand on the K axis: the byte offset (less W + 1 pixels,
+// modulo 2^32), the tap it lies in and the channel offset in that tap.  Requests go over consecutive K tiles, so the position is carried on instead of
 // divided out of the tile index (a division per parity and tile, and border tests per load, made the gather's own
 // arithmetic the bound of the K loop: four loads took about 130 vector instructions, now about 55).
 struct ConvTap { uint32_t koff[2], tap[2], c0[2]; };
 
 // `mask`: bit t says that tap t of the lane's output pixel lies inside the image; taps from 9 on (chunks past the end
-// of K) have no bit.  `delta`: byte distance from the pixel to the chunk's source, plus (W + 1) pixels.
+// of K) have no bit.  `delta`: byte distance from the pixel to the chunk's source, modulo 2^32: their sum is the source's
+// offset in the tensor, below 2^31 wherever the mask has the bit.  (Without the modulus, on a base W + 1 pixels in front
+// of the tensor, the sum reaches 2 W + 1 pixels and left 32 bits for one row of nearly 2^31 bytes.)
 template <int D, int DPW>
 __device__ __forceinline__ void conv_issue(const uint8_t* a, const uint8_t* zero, uint32_t pix_off, uint32_t mask,
                                            const ConvTap& t, const uint32_t (&delta)[2], uint8_t* lds_mid)
@@ -564,6 +566,7 @@ __device__ __forceinline__ void gemm_tile(const GemmKernelArgs& p, int lin, int 
             conv_t.koff[par] = static_cast<uint32_t>(gchunk[par]);
             conv_t.tap[par]  = conv_t.koff[par] / conv_cb;
             conv_t.c0[par]   = conv_t.koff[par] % conv_cb;
+            conv_t.koff[par] -= (static_cast<uint32_t>(p.conv_W) + 1u) * conv_cb;
         }
     const int64_t tn_ld = TN ? uniform64(is_a ? p.M : p.N) : 0;      // operand row length in elements
     // TN: stage row of the lane in load slot 0, rows from slot to slot, and the contraction rows of a partial last K tile
@@ -589,14 +592,14 @@ __device__ __forceinline__ void gemm_tile(const GemmKernelArgs& p, int lin, int 
             if(is_a)
             {
                 // (for consecutive K tiles, starting at 0)  Source of a chunk: pixel + (kh - 1) rows + (kw - 1) pixels + c0
-                // = pixel - (W + 1) pixels + koff + kh (W - 3) pixels, since koff = (3 kh + kw) pixels + c0; the constant
-                // part is in the panel's base.
+                // = pixel - (W + 1) pixels + K offset + kh (W - 3) pixels, since the K offset = (3 kh + kw) pixels + c0;
+                // koff carries the constant part.
                 uint32_t delta[2];
 #pragma unroll
                 for(int par = 0; par < 2; ++par)
                     delta[par] = conv_t.koff[par] + (conv_t.tap[par] >= 3 ? conv_kh_step : 0u) + (conv_t.tap[par] >= 6 ? conv_kh_step : 0u);
-                conv_sequence<DPW>(std::make_integer_sequence<int, DPW>{}, p.A - static_cast<int64_t>(p.conv_W + 1) * p.conv_Cb,
-                                   reinterpret_cast<const uint8_t*>(&g_zero_chunk), voff, hw, conv_t, delta, lbase);
+                conv_sequence<DPW>(std::make_integer_sequence<int, DPW>{}, p.A, reinterpret_cast<const uint8_t*>(&g_zero_chunk),
+                                   voff, hw, conv_t, delta, lbase);
 #pragma unroll
                 for(int par = 0; par < 2; ++par)
                 {

@@ -117,3 +117,25 @@ def test_cast_and_dequantize_over_more_than_2_to_31_elements():
         want = orc.dequantize(host(acc[r])[None, :], 0.5, None, host(cs), host(cb), out_dtype=np.float64)
         assert_close(host(y[r])[None, :], want, f"dequantized row {r}")
     del x, y
+
+
+@pytest.mark.parametrize("tag", [Q.INT8, Q.FP16])
+def test_convolution_over_one_row_of_nearly_2_to_31_bytes(tag):
+    """One image of one row whose tensor takes nearly 2^31 bytes: the gather's 32-bit source offsets at the last pixel.
+    Whole numbers of at most 3 in magnitude: every sum stays below 2^24 and is exact in any order."""
+    cb, w, n = (1 << 20) - 16, 2048, 16
+    c = cb if tag == Q.INT8 else cb // 2
+    dt = torch.int8 if tag == Q.INT8 else torch.float16
+    say("large index: convolution of one row", tag, w, c)
+    g = torch.Generator(device="cuda").manual_seed(9)
+    x = torch.randint(-3, 4, (w, c), dtype=dt, device="cuda", generator=g)
+    wt = torch.randint(-3, 4, (n, 9, c), dtype=dt, device="cuda", generator=g)
+    y, one = torch.empty(w, n, device="cuda"), torch.ones(1, device="cuda")
+    Q.qsync_conv3x3_fwd(tag, 1, 1, w, c, n, x, one, wt, one, Q.PER_TENSOR, None, y)
+    want = torch.zeros(w, n, device="cuda")
+    for c0 in range(0, c, 1 << 16):
+        for kw in range(3):                                      # the one row meets the middle row of the window only
+            part = x[:, c0:c0 + (1 << 16)].float() @ wt[:, 3 + kw, c0:c0 + (1 << 16)].float().t()
+            lo, hi = max(0, 1 - kw), min(w, w + 1 - kw)          # output pixels whose tap lies inside
+            want[lo:hi] += part[lo + kw - 1:hi + kw - 1]
+    assert torch.equal(y, want)
