@@ -285,6 +285,8 @@ int qsync_scale_from_amax(float* amax, int bits, float* scale, float* inv_scale,
  * db_opt  out N floats or NULL; needs dy_float_opt, the unquantized gradient [M,N] of dydt
  *         (QSYNC_F32 or QSYNC_F16, packed), summed in fp32.
  * acc_dx_dump_opt [M,K], acc_dw_dump_opt [N,K]: raw int32 accumulators (INT8 only), or NULL.
+ * With dx_opt and dw_opt both given the two GEMMs may share one launch.  INT8 results are the same bits as those of two
+ * calls with one of them each; FP16 and FP32 sums may then run in another order (other K splits).
  * workspace  at least qsync_qlinear_bwd_workspace_bytes(tag, M, N, K) bytes.
  * Alignment: INT8 needs N % 16 == 0 (for dX) and M % 16 == 0 (for dW); FP16 needs % 8.
  */
@@ -309,7 +311,7 @@ size_t qsync_qlinear_bwd_workspace_bytes(int tag, int64_t M, int64_t N, int64_t 
  * the casting costs of the forward and backward pass); Appendix, proof of Prop. 1 (the two gradient contractions).
  *
  *   dX[m,k] = sum_n dyq[m,n] wqbT[k,n] * (sdy swb[k or 0])      dW[n,k] = sum_m dyq[m,n] xq[m,k] * (sdy sx)
- *   db[n] = sum_m dY[m,n]                                          same bits as qsync_qlinear_bwd
+ *   db[n] = sum_m dY[m,n]               INT8 and db: same bits as qsync_qlinear_bwd; FP16 up to the order of the sums
  *
  * tag  QSYNC_INT8 or QSYNC_FP16 (QSYNC_ERR_UNSUPPORTED otherwise).
  * dyq [M,N], xq [M,K] int8 / binary16 row-major (the forward's own operand), wqbT [K,N]; scales as in

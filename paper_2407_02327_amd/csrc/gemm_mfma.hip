@@ -159,8 +159,8 @@ __device__ __forceinline__ void item_of_block(int lin, int tiles_m, int tiles_n,
 
 // Output value a*s + b of the fused epilogues.  fp32: the fused multiply-add.  binary16: the same sum rounded ONCE
 // to binary16, by the mixed-precision fused multiply-add (fp32 sources, binary16 result) -- written as an
-// instruction so that every epilogue (per-tile staged and element-wise, persistent) produces the same bits; left to
-// the compiler, fmaf + conversion becomes that instruction in some places and a fp32 result converted afterwards
+// instruction so that every epilogue (per tile, persistent, reduction of K splits) produces the same bits from the same
+// sum; left to the compiler, fmaf + conversion becomes that instruction in some places and a fp32 result converted afterwards
 // (two roundings, different at binary16 ties) in others.
 template <typename T> __device__ __forceinline__ T fma_out(float a, float s, float b);
 template <> __device__ __forceinline__ float fma_out<float>(float a, float s, float b) { return fmaf(a, s, b); }
@@ -1398,13 +1398,9 @@ __global__ __launch_bounds__(kThreads) void splitk_reduce_kernel(const ACC* __re
 #pragma unroll
         for(int e = 0; e < V; ++e)
         {
-            const float f = alpha * (col_scale ? col_scale[col + e] : 1.0f);
-            y[e] = static_cast<float>(acc[e]) * f + (col_bias ? col_bias[col + e] : 0.0f);
-        }
-        if(c_is_f16)
-        {   // what is stored is the rounded value: take the maximum of that
-#pragma unroll
-            for(int e = 0; e < V; ++e) y[e] = __half2float(__float2half_rn(y[e]));
+            const float f = alpha * (col_scale ? col_scale[col + e] : 1.0f), b = col_bias ? col_bias[col + e] : 0.0f;
+            const float a = static_cast<float>(acc[e]);
+            y[e] = c_is_f16 ? __half2float(fma_out<__half>(a, f, b)) : fma_out<float>(a, f, b);      // the value as stored
         }
         if(amax_bits)
         {

@@ -177,6 +177,28 @@ def test_both_gradients_of_one_call_equal_the_separate_calls(tag, shape):
                 assert (got - want).abs().max() <= bound
 
 
+@pytest.mark.parametrize("M,N", [(384, 528), (192, 301)])
+def test_split_k_rounds_a_binary16_output_once(M, N):
+    """The reduction of K splits (vectors, and single elements for an odd N) stores round_f16(acc * scale + bias) like the
+    unsplit epilogue: accumulators below 2^24, so binary64 holds the product exactly.  A product or sum rounded to binary32
+    on the way gives other bits here."""
+    K = 4096
+    say("split K, binary16 output", M, N)
+    rng = np.random.default_rng(M)
+    a, b = rng.integers(-9, 10, (M, K)).astype(np.int8), rng.integers(-9, 10, (N, K)).astype(np.int8)
+    sx, sw, bias = np.float32([0.37]), rng.random(N).astype(np.float32), rng.standard_normal(N).astype(np.float32)
+    w = torch.zeros(max(256, Q.qsync_qlinear_workspace_bytes(Q.INT8, M, N, K)), dtype=torch.uint8, device="cuda")
+    assert w.numel() >= 2 * M * N * 4                              # the plan does split
+    y = torch.empty(M, N, dtype=torch.float16, device="cuda")
+    Q.qsync_qlinear_fwd(Q.INT8, M, N, K, dev(a), dev(sx), dev(b), dev(sw), Q.PER_ROW, dev(bias), y, None, w)
+    acc = a.astype(np.float64) @ b.astype(np.float64).T
+    f = sx[0] * sw
+    want = (acc * f.astype(np.float64) + bias.astype(np.float64)).astype(np.float16)
+    twice = (acc.astype(np.float32) * f + bias).astype(np.float16)
+    assert (want != twice).any()                                   # the data tells the two roundings apart
+    assert_bits_equal(host(y), want, "Y")
+
+
 @pytest.mark.parametrize("tag,act", [(Q.INT8, torch.float16), (Q.FP16, torch.float16), (Q.FP16, torch.float32)])
 def test_activation_buffer_may_be_reused_before_backward(tag, act):
     """The operator's default form holds its own copy of a small activation: overwriting x after forward changes nothing."""
