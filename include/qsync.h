@@ -285,7 +285,9 @@ int qsync_scale_from_amax(float* amax, int bits, float* scale, float* inv_scale,
  * db_opt  out N floats or NULL; needs dy_float_opt, the unquantized gradient [M,N] of dydt
  *         (QSYNC_F32 or QSYNC_F16, packed), summed in fp32.
  * acc_dx_dump_opt [M,K], acc_dw_dump_opt [N,K]: raw int32 accumulators (INT8 only), or NULL.
- * With dx_opt and dw_opt both given the two GEMMs may share one launch.  INT8 results are the same bits as those of two
+ * dw_opt and acc_dw_dump_opt may lie on operands that the data gradient alone reads (dyq, wqbT, swb): it has read them by
+ * the time they are written.
+ * With dx_opt and dw_opt both given the two GEMMs may otherwise share one launch.  INT8 results are the same bits as those of two
  * calls with one of them each; FP16 and FP32 sums may then run in another order (other K splits).
  * workspace  at least qsync_qlinear_bwd_workspace_bytes(tag, M, N, K) bytes.
  * Alignment: INT8 needs N % 16 == 0 (for dX) and M % 16 == 0 (for dW); FP16 needs % 8.

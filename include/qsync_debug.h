@@ -32,8 +32,8 @@ int qsync_probe_mfma(int tag, int random_operands, int iters, void* out, double*
  * (0: 256x256, 1: 128x128, 2: 64x64) for every later call made by the calling thread, -1 (or any other value)
  * returns the choice to the planner.  Workspace sizes reported afterwards follow the pinned tile.
  * The override is per calling thread (a thread sees only its own setting), so it never races with other
- * threads that use the library; it is the only state the library keeps besides a per-process note of which
- * kernels already had their dynamic-LDS limit raised.
+ * threads that use the library; the library keeps no other state but the values below, per thread too, and a
+ * per-process note of which kernels already had their dynamic-LDS limit raised.
  */
 void qsync_debug_set_gemm_tile(int tile);
 
@@ -45,6 +45,13 @@ void qsync_debug_set_gemm_tile(int tile);
  * int8 operands; binary16 operands sum in the same order, too.
  */
 void qsync_debug_set_gemm_persistent(int mode);
+
+/*
+ * qsync_debug_last_gradient_pair - for tests: how the calling thread's last qsync_qlinear_bwd, qsync_qlinear_bwd_rm or
+ * qsync_qlinear_bwd_fp16_of_int8 that passed its argument checks ran its GEMMs: the tile shape (numbered as above) on
+ * which data and weight gradient shared one launch, or -1 when they were launched apart or only one was asked for.
+ */
+int qsync_debug_last_gradient_pair(void);
 
 #ifdef __cplusplus
 }

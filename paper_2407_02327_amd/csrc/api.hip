@@ -12,6 +12,7 @@ using namespace qsync;
 namespace {
 
 thread_local int g_last_hip_error = 0;
+thread_local int g_last_pair_tile = -1;      // see qsync_debug_last_gradient_pair
 
 int hip_status(hipError_t e)
 {
@@ -43,6 +44,21 @@ bool gemm_row_ok(int tag, int64_t k)
 }
 
 size_t round256(size_t v) { return (v + 255) & ~static_cast<size_t>(255); }
+
+GemmProblem data_gradient(int tag, int64_t M, int64_t N, int64_t K, const void* dyq, const float* sdy, const void* wqbT,
+                          const float* swb, int wbgran, void* dx, int dxdt, int32_t* acc_dump)
+{
+    GemmProblem p{};
+    p.prec = tag; p.M = M; p.N = K; p.K = N;
+    p.A = dyq; p.B = wqbT; p.C = dx; p.c_dtype = dxdt;
+    if(tag == QSYNC_INT8)
+    {
+        p.s0 = sdy;
+        if(wbgran == QSYNC_PER_TENSOR) p.s1 = swb; else p.col_scale = swb;
+        p.acc_dump = acc_dump;
+    }
+    return p;
+}
 
 }  // namespace
 
@@ -279,23 +295,6 @@ int qsync_scale_from_amax(float* amax, int bits, float* scale, float* inv_scale,
     return hip_status(launch_scale_from_amax(amax, qmax, scale, inv_scale, consume != 0, static_cast<hipStream_t>(stream)));
 }
 
-namespace {
-GemmProblem data_gradient(int tag, int64_t M, int64_t N, int64_t K, const void* dyq, const float* sdy, const void* wqbT,
-                          const float* swb, int wbgran, void* dx, int dxdt, int32_t* acc_dump)
-{
-    GemmProblem p{};
-    p.prec = tag; p.M = M; p.N = K; p.K = N;
-    p.A = dyq; p.B = wqbT; p.C = dx; p.c_dtype = dxdt;
-    if(tag == QSYNC_INT8)
-    {
-        p.s0 = sdy;
-        if(wbgran == QSYNC_PER_TENSOR) p.s1 = swb; else p.col_scale = swb;
-        p.acc_dump = acc_dump;
-    }
-    return p;
-}
-}  // namespace
-
 int qsync_qlinear_bwd(int tag, int64_t M, int64_t N, int64_t K, const void* dyq, const void* dyqT, const float* sdy,
                       const void* xqT, const float* sx, const void* wqbT, const float* swb, int wbgran, void* dx_opt,
                       int dxdt, void* dw_opt, int dwdt, float* db_opt, const void* dy_float_opt, int dydt,
@@ -351,6 +350,7 @@ int qsync_qlinear_bwd(int tag, int64_t M, int64_t N, int64_t K, const void* dyq,
     void*      ws_dw   = wsb ? wsb + off_dw : nullptr;
     int        rc      = QSYNC_OK;
     const int  pair    = want_dx && want_dw ? gradient_pair_tile(pdx, plan_dx, pdw, plan_dw) : -1;
+    g_last_pair_tile   = pair;
     if(pair >= 0)
         rc = hip_status(launch_gradient_pair(pdx, pdw, pair, st));
     else
@@ -424,6 +424,7 @@ int qsync_qlinear_bwd_rm(int tag, int64_t M, int64_t N, int64_t K, const void* d
         if(part && (!workspace || workspace_bytes < qsync_qlinear_bwd_workspace_bytes(tag, M, N, K))) return QSYNC_ERR_WORKSPACE;
         if(plan.workspace > 0 && (!workspace || workspace_bytes < qsync_qlinear_bwd_rm_workspace_bytes(tag, M, N, K))) return QSYNC_ERR_WORKSPACE;
         if((part || plan.workspace > 0) && !aligned16(workspace)) return QSYNC_ERR_ALIGN;
+        g_last_pair_tile = pair;
         const int rc = hip_status(launch_gradient_pair(pdx, p, pair, static_cast<hipStream_t>(stream)));
         if(rc != QSYNC_OK) return rc;
     }
@@ -435,6 +436,7 @@ int qsync_qlinear_bwd_rm(int tag, int64_t M, int64_t N, int64_t K, const void* d
                                          workspace_bytes, stream);
         if(rc != QSYNC_OK) return rc;
     }
+    g_last_pair_tile = pair;
     if(!want_dw || pair >= 0) return QSYNC_OK;
     if(plan.workspace > 0)
     {
@@ -687,6 +689,7 @@ int qsync_probe_mfma(int tag, int random_operands, int iters, void* out, double*
 
 void qsync_debug_set_gemm_tile(int tile) { set_gemm_tile_override(tile); }
 void qsync_debug_set_gemm_persistent(int mode) { set_gemm_persistent_mode(mode); }
+int qsync_debug_last_gradient_pair(void) { return g_last_pair_tile; }
 
 static int conv3x3_fwd_impl(int tag, int64_t nimg, int64_t H, int64_t W, int64_t C, int64_t N, const void* xq,
                             const float* sx, const void* wq, const float* sw, int wgran, const float* bias_opt, void* y,

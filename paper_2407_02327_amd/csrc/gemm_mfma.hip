@@ -1869,13 +1869,29 @@ static int pair_tile(const GemmProblem& a, const GemmProblem& b, double separate
     return tile;
 }
 
+// The weight gradient lands in memory that the data gradient reads (a caller that stores dW over the transposed weights or
+// over dY, say): fine in two launches, data gradient first, a race in one.
+static bool dw_over_dx_operands(const GemmProblem& dx, const GemmProblem& dw)
+{
+    auto meets = [](const void* a, int64_t a_bytes, const void* b, int64_t b_bytes) {
+        const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+        return a && b && x < y + static_cast<uintptr_t>(b_bytes) && y < x + static_cast<uintptr_t>(a_bytes);
+    };
+    const int64_t esz = dx.prec / 8, out = dw.M * dw.N;
+    auto written = [&](const void* p, int64_t bytes) {
+        return meets(dw.C, out * (dw.c_dtype == kF16 ? 2 : 4), p, bytes) || meets(dw.acc_dump, out * 4, p, bytes);
+    };
+    return written(dx.A, dx.M * dx.K * esz) || written(dx.B, dx.N * dx.K * esz) || written(dx.s0, 4) || written(dx.s1, 4)
+        || written(dx.col_scale, dx.N * 4);
+}
+
 int gradient_pair_tile(const GemmProblem& dx, const GemmPlan& plan_dx, const GemmProblem& dw, const GemmPlan& plan_dw)
 {
     auto plain = [](const GemmProblem& p) {
         return (p.prec == 8 || p.prec == 16) && p.M > 0 && p.N > 0 && p.K > 0 && p.conv_H == 0 && p.b_remap_C == 0
             && !p.out_amax_bits && !p.out_codes;
     };
-    if(dx.prec != dw.prec || !plain(dx) || !plain(dw) || dx.tn || g_persistent_mode == 1) return -1;
+    if(dx.prec != dw.prec || !plain(dx) || !plain(dw) || dx.tn || g_persistent_mode == 1 || dw_over_dx_operands(dx, dw)) return -1;
     const double us = plan_dx.us + plan_dw.us;
     return dw.tn || dw.K >= dx.K ? pair_tile(dw, dx, us) : pair_tile(dx, dw, us);
 }

@@ -130,7 +130,7 @@ void set_gemm_tile_override(int tile);
 void set_gemm_persistent_mode(int mode);
 hipError_t launch_gemm(const GemmProblem& p, const GemmPlan& plan, void* workspace, hipStream_t stream);
 // Data and weight gradient of one operator in one launch: the tile to run both on, or -1 when their own plans are
-// estimated to be about as fast one after the other.
+// estimated to be about as fast one after the other, or when dw writes what dx reads.
 int gradient_pair_tile(const GemmProblem& dx, const GemmPlan& plan_dx, const GemmProblem& dw, const GemmPlan& plan_dw);
 hipError_t launch_gradient_pair(const GemmProblem& dx, const GemmProblem& dw, int tile, hipStream_t stream);
 

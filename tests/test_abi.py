@@ -233,6 +233,36 @@ def test_conv_wgrad_validation():
     assert lib.qsync_conv3x3_wgrad_workspace_bytes(16, 63, 56, 56, 64, 64) > 2 * 3 * 63 * 64 * 57 * 64
 
 
+@pytest.mark.parametrize("rowmajor", [False, True])
+def test_gradients_share_no_launch_when_dw_lands_on_what_dx_reads(rowmajor):
+    """The weight gradient may be stored over an operand of the data gradient (transposed weights, their scales, dY): in
+    two launches the data gradient has read it by then.  Choice only, before any launch: fake addresses."""
+    M, N, K, MB = 1024, 512, 256, 1 << 20
+    at = lambda mb, off=0: (mb << 20) + off
+    base = dict(dyq=at(16), dyqT=at(32), xqT=at(48), wqbT=at(64), swb=at(80), sdy=at(96), sx=at(112), dx=at(128), dw=at(144),
+                acc_dw=None)
+
+    def pair(**kw):
+        b = {k: P(v) if v else None for k, v in {**base, **kw}.items()}
+        if rowmajor:
+            rc = lib.qsync_qlinear_bwd_rm(8, M, N, K, b["dyq"], b["sdy"], b["xqT"], b["sx"], b["wqbT"], b["swb"], qsync.PER_ROW, b["dx"],
+                                          qsync.F32, b["dw"], qsync.F16, None, None, 0, None, b["acc_dw"], P(at(512)), 256 * MB, None)
+        else:
+            rc = lib.qsync_qlinear_bwd(8, M, N, K, b["dyq"], b["dyqT"], b["sdy"], b["xqT"], b["sx"], b["wqbT"], b["swb"], qsync.PER_ROW,
+                                       b["dx"], qsync.F32, b["dw"], qsync.F16, None, None, 0, None, b["acc_dw"], P(at(512)), 256 * MB, None)
+        assert rc == qsync.ERR_HIP                                # (no GPU here; the arguments themselves are fine)
+        return lib.qsync_debug_last_gradient_pair()
+
+    tile, out = pair(), 2 * N * K
+    assert tile >= 0
+    assert pair(wqbT=at(144)) == -1
+    assert pair(wqbT=at(144, out - 16)) == -1 and pair(wqbT=at(144, out)) == tile
+    assert pair(wqbT=at(144, -N * K + 16)) == -1 and pair(wqbT=at(144, -N * K)) == tile
+    assert pair(dyq=at(144, out - 16)) == -1 and pair(dyq=at(144, out)) == tile
+    assert pair(swb=at(144, out - 4)) == -1 and pair(sdy=at(144, 4)) == -1
+    assert pair(acc_dw=at(64, -4 * N * K + 16)) == -1 and pair(acc_dw=at(64, -4 * N * K)) == tile
+
+
 def test_conv_prepare_weights_validation():
     f = lib.qsync_conv3x3_prepare_weights
     ok = [A, qsync.F32, 8, 16, 8, A, A, A, A, A, A, A, 1 << 24, None]

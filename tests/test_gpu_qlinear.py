@@ -177,6 +177,37 @@ def test_both_gradients_of_one_call_equal_the_separate_calls(tag, shape):
                 assert (got - want).abs().max() <= bound
 
 
+@pytest.mark.parametrize("rowmajor,over", [(False, "weights"), (False, "gradient"), (True, "weights")])
+def test_weight_gradient_stored_over_an_operand_of_the_data_gradient(rowmajor, over):
+    """dW written where the transposed weight codes or the gradient codes lay: the data gradient has read them by then."""
+    M, N, K = 1024, 512, 256
+    say("dW over", over, "row-major", rowmajor)
+    rng = np.random.default_rng(5)
+    dyq, xq, wb = (dev(rng.integers(-127, 128, s).astype(np.int8)) for s in [(M, N), (M, K), (K, N)])
+    s = dev(np.float32([0.01]))
+    dyqT, xqT = dyq.t().contiguous(), xq.t().contiguous()
+    w = torch.zeros(max(256, Q.qsync_qlinear_bwd_workspace_bytes(8, M, N, K), Q.qsync_qlinear_bwd_rm_workspace_bytes(8, M, N, K)),
+                    dtype=torch.uint8, device="cuda")
+
+    def backward(a, b, dw):
+        dx = torch.empty(M, K, device="cuda")
+        if rowmajor:
+            Q.qsync_qlinear_bwd_rm(8, M, N, K, a, s, xq, s, b, s, Q.PER_TENSOR, dx, dw, None, None, None, None, w)
+        else:
+            Q.qsync_qlinear_bwd(8, M, N, K, a, dyqT, s, xqT, s, b, s, Q.PER_TENSOR, dx, dw, None, None, None, None, w)
+        return dx, dw.clone(), Q.qsync_debug_last_gradient_pair()
+
+    dx, dw, tile = backward(dyq, wb, torch.empty(N, K, device="cuda"))
+    assert tile >= 0
+    buf = torch.zeros(4 * N * K, dtype=torch.uint8, device="cuda")      # dW fills it; the operand lies at its start
+    operand = wb if over == "weights" else dyq
+    here = buf.view(torch.int8)[:operand.numel()].view_as(operand)
+    here.copy_(operand)
+    dx2, dw2, tile2 = backward(dyq if over == "weights" else here, here if over == "weights" else wb, buf.view(torch.float32).view(N, K))
+    assert tile2 == -1
+    assert torch.equal(dx, dx2) and torch.equal(dw, dw2)
+
+
 @pytest.mark.parametrize("M,N", [(384, 528), (192, 301)])
 def test_split_k_rounds_a_binary16_output_once(M, N):
     """The reduction of K splits (vectors, and single elements for an odd N) stores round_f16(acc * scale + bias) like the
