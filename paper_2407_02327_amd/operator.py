@@ -45,9 +45,10 @@ class QLinear:
         None picks False when the shape allows it: the row-major weight-gradient GEMM is up to 10 % slower than the one
         on transposed copies, but the conversions write a byte (FP16: two) less per element (measured on MI355X, whole
         steps with copies -> row-major: INT8 1024^3 48.5 -> 45.6 us, 4096x3072x768 91.8 -> 88.8, 8192x1024x1024 87.7
-        -> 82.9; FP16 from fp32 activations 1024^3 50.4 -> 48.8).  Except a binary16 activation under the FP16 tag below
-        M (N + K) = 32 Mi elements: without copies the activation itself is what backward reads, so ask for that
-        (2048x256x256 38.3 -> 23.8, 4096x3072x768 109.3 -> 93.3) only if its buffer stays untouched until then."""
+        -> 82.9; FP16 from fp32 activations 1024^3 50.4 -> 48.8).  Except a binary16 activation or gradient under the FP16
+        tag below M (N + K) = 32 Mi elements: without copies the tensor itself is what backward reads, so ask for that
+        (2048x256x256 38.3 -> 23.8, 4096x3072x768 109.3 -> 93.3) only if its buffer stays untouched until then.  An
+        operator of that size declared for other types copies a binary16 tensor that it is handed all the same."""
         self.tag, self.M, self.N, self.K = tag, M, N, K
         # max |Y| collected by the forward GEMM's epilogue, for a consumer that quantizes Y as it is
         self.y_amax = torch.zeros(1, dtype=torch.float32, device=device) if collect_y_amax else None
@@ -61,12 +62,14 @@ class QLinear:
         if transposed_copies is False and not rm_ok:
             raise ValueError("transposed_copies=False needs tag INT8 or FP16 with the same backward tag, M % 128 == 0, "
                              "N and K multiples of 16 (FP16: 8)")
-        # a binary16 activation under the FP16 tag is its own row-major operand: smaller operators keep their copy, so that
-        # a caller may reuse the activation's buffer between forward and backward as it always could there
-        in_place = tag == Q.FP16 and x_dtype == torch.float16
-        self.rowmajor_bwd = ((rm_ok and (not in_place or M * (N + K) >= (32 << 20))) if transposed_copies is None
-                             else not transposed_copies)
+        # a binary16 tensor under the FP16 tag is its own row-major operand: smaller operators keep a copy that the weight
+        # gradient reads, so that a caller may reuse the tensor's buffer before that as it always could there -- by the
+        # declared types a transposed one, else (`own_copies`) a plain one of whatever arrives in binary16 after all
         dy_dtype = dy_dtype or x_dtype
+        small = M * (N + K) < (32 << 20)
+        in_place = tag == Q.FP16 and torch.float16 in (x_dtype, dy_dtype)
+        self.rowmajor_bwd = (rm_ok and not (in_place and small)) if transposed_copies is None else not transposed_copies
+        self.own_copies = self.rowmajor_bwd and transposed_copies is None and small
         dev = device
         e = lambda *s, dt: torch.empty(*s, dtype=dt, device=dev)
         qd = _TORCH_OF_TAG[tag]
@@ -121,7 +124,7 @@ class QLinear:
                 return
             Q.qsync_quantize(x, M, K, K, Q.INT8, self.bits, Q.PER_TENSOR, Q.ROUND_NEAREST, 0, 0, self.ix, self.xq,
                              self.xqT, stream)
-        elif x.dtype == _TORCH_OF_TAG[self.tag] and x.is_contiguous():
+        elif x.dtype == _TORCH_OF_TAG[self.tag] and x.is_contiguous() and not self.own_copies:
             # already in the operand type: the tensor itself is the saved operand, only its transpose (if kept) is written
             self.xq = x
             if self.xqT is not None:
@@ -170,7 +173,7 @@ class QLinear:
                              self.idy, self.dyq, self.dyqT, stream)
             self.last_dy_offset = self.offset
             self.offset += (M * N + 7) // 8
-        elif dy.dtype == _TORCH_OF_TAG[self.tag] and dy.is_contiguous():
+        elif dy.dtype == _TORCH_OF_TAG[self.tag] and dy.is_contiguous() and not self.own_copies:
             self.dyq = dy
             if self.dyqT is not None:
                 Q.qsync_quantize(dy, M, N, N, self.tag, 0, 0, 0, 0, 0, None, None, self.dyqT, stream)

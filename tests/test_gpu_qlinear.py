@@ -249,6 +249,31 @@ def test_activation_buffer_may_be_reused_before_backward(tag, act):
     assert all(torch.equal(a, b) for a, b in zip(*results))
 
 
+@pytest.mark.parametrize("declared", [(torch.float32, None), (torch.float32, torch.float16), (torch.float16, torch.float32)])
+def test_binary16_buffers_may_be_reused_whatever_the_declared_types(declared):
+    """FP16 tag, default form: what decides is the type of the tensors that arrive.  The activation is overwritten after
+    forward, the gradient after the data gradient."""
+    say("binary16 buffers reused", declared)
+    M, N, K = 256, 128, 192
+    g = torch.Generator(device="cuda").manual_seed(3)
+    x, w = torch.randn(M, K, device="cuda", generator=g).half(), torch.randn(N, K, device="cuda", generator=g) * 0.02
+    dy = (torch.randn(M, N, device="cuda", generator=g) * 1e-3).half()
+    results = []
+    for overwrite in (False, True):
+        op = QLinear(Q.FP16, M, N, K, x_dtype=declared[0], dy_dtype=declared[1])
+        mine, grad = x.clone(), dy.clone()
+        op.forward(mine, w)
+        if overwrite:
+            mine.fill_(7.0)
+        op.convert_dy(grad)
+        op.gemm_bwd_part("dx", grad)
+        if overwrite:
+            grad.fill_(7.0)
+        op.gemm_bwd_part("dw", None)
+        results.append([op.y.clone(), op.dx.clone(), op.dw.clone()])
+    assert all(torch.equal(a, b) for a, b in zip(*results))
+
+
 @pytest.mark.parametrize("ydt,dxdt,dwdt", [(np.float16, np.float16, np.float32), (np.float32, np.float32, np.float16)])
 def test_production_epilogue_on_ragged_shapes_int8(ydt, dxdt, dwdt):
     """INT8 without accumulator dumps: the staged-store epilogue (and the split-K reduction) on ragged shapes
