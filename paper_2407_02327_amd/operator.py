@@ -79,6 +79,7 @@ class QLinear:
         self.wq, self.wqbT = e(N, K, dt=qd), e(K, N, dt=qd)
         fp16_bwd = self.bwd_tag != tag           # that backward converts dY itself: no gradient operands are kept here
         self.dyq = e(M, N, dt=qd) if not fp16_bwd else None
+        self._xq, self._dyq = self.xq, self.dyq          # (xq, dyq may come to name a caller's tensor that is used in place)
         self.dyqT = e(N, M, dt=qd) if not (self.rowmajor_bwd or fp16_bwd) else None
         # scales (amax/qmax), inverse scales, and the raw maxima
         self.sx, self.ix, self.ax = e(1, dt=f32), e(1, dt=f32), e(1, dt=f32)
@@ -130,6 +131,7 @@ class QLinear:
             if self.xqT is not None:
                 Q.qsync_quantize(x, M, K, K, self.tag, 0, 0, 0, 0, 0, None, None, self.xqT, stream)
         else:
+            self.xq = self._xq
             Q.qsync_quantize(x, M, K, K, self.tag, 0, 0, 0, 0, 0, None, self.xq, self.xqT, stream)
 
     def convert_x_nhwc(self, act: torch.Tensor, stream=None) -> None:
@@ -178,6 +180,7 @@ class QLinear:
             if self.dyqT is not None:
                 Q.qsync_quantize(dy, M, N, N, self.tag, 0, 0, 0, 0, 0, None, None, self.dyqT, stream)
         else:
+            self.dyq = self._dyq
             Q.qsync_quantize(dy, M, N, N, self.tag, 0, 0, 0, 0, 0, None, self.dyq, self.dyqT, stream)
 
     # ---- GEMMs ---------------------------------------------------------------------------
@@ -314,6 +317,7 @@ class QConv3x3:
         self.xqTp = e(K, M, dt=qd) if (tag == Q.INT8 and wgrad_via_patches) else None   # transposed patch matrix
         self.wq, self.wflip = e(N, K, dt=qd), e(C, 9 * N, dt=qd)
         self.dyq = e(M, N, dt=qd)
+        self._xq, self._dyq = self.xq, self.dyq          # (xq, dyq may come to name a caller's tensor that is used in place)
         self.dyqT = e(N, M, dt=qd) if wgrad_via_patches else None
         self.sx, self.ix, self.ax = e(1, dt=f32), e(1, dt=f32), e(1, dt=f32)
         nsw, nswb = (N, C) if w_gran == Q.PER_ROW else (1, 1)
@@ -350,6 +354,7 @@ class QConv3x3:
         elif act.dtype == _TORCH_OF_TAG[self.tag] and act.is_contiguous():
             self.xq = act.view(M, C)           # already in the operand type: used in place
         else:
+            self.xq = self._xq
             Q.qsync_quantize(act, M, C, C, self.tag, 0, 0, 0, 0, 0, None, self.xq, None, stream)
 
     def convert_w(self, w: torch.Tensor, stream=None) -> None:
@@ -387,6 +392,7 @@ class QConv3x3:
         elif dy.dtype == _TORCH_OF_TAG[self.tag] and dy.is_contiguous():
             self.dyq = dy
         else:
+            self.dyq = self._dyq
             Q.qsync_quantize(dy, M, N, N, self.tag, 0, 0, 0, 0, 0, None, self.dyq, None, stream)
 
     def conv_dgrad(self, stream=None) -> None:

@@ -10,7 +10,7 @@ import torch
 from oracle import qsync_oracle as orc
 from paper_2407_02327_amd import qsync as Q
 from paper_2407_02327_amd import workloads as wl
-from paper_2407_02327_amd.operator import QLinear
+from paper_2407_02327_amd.operator import QConv3x3, QLinear
 from tests.gpu_util import GRAN, RND, assert_bits_equal, assert_close, dev, host, say
 
 pytestmark = pytest.mark.gpu
@@ -272,6 +272,27 @@ def test_binary16_buffers_may_be_reused_whatever_the_declared_types(declared):
         op.gemm_bwd_part("dw", None)
         results.append([op.y.clone(), op.dx.clone(), op.dw.clone()])
     assert all(torch.equal(a, b) for a, b in zip(*results))
+
+
+@pytest.mark.parametrize("kind", ["linear FP16", "linear FP32", "convolution"])
+def test_a_tensor_used_in_place_is_never_written(kind):
+    """A pass on tensors of the operand type (used as they are) followed by one on tensors of the other type (converted):
+    the conversion goes to the operator's own buffers."""
+    say("in-place operands", kind)
+    g = torch.Generator(device="cuda").manual_seed(4)
+    dt, other = (torch.float32, torch.float16) if kind == "linear FP32" else (torch.float16, torch.float32)
+    if kind == "convolution":
+        op, xs, ws_, ds = QConv3x3(Q.FP16, 2, 5, 6, 16, 24), (2, 5, 6, 16), (24, 144), (60, 24)
+    else:
+        op, xs, ws_, ds = QLinear(Q.FP16 if dt == torch.float16 else Q.FP32, 200, 96, 160, x_dtype=dt), (200, 160), (96, 160), (200, 96)
+    x, w, dy = (torch.randn(*s, device="cuda", generator=g) for s in (xs, ws_, ds))
+    x1, dy1 = x.to(dt), dy.to(dt)
+    keep = x1.clone(), dy1.clone()
+    op.forward(x1, w)
+    op.backward(dy1)
+    op.forward((x + 1).to(other), w)
+    op.backward((dy + 1).to(other))
+    assert torch.equal(x1, keep[0]) and torch.equal(dy1, keep[1])
 
 
 @pytest.mark.parametrize("ydt,dxdt,dwdt", [(np.float16, np.float16, np.float32), (np.float32, np.float32, np.float16)])
