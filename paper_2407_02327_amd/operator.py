@@ -75,12 +75,12 @@ class QLinear:
         qd = _TORCH_OF_TAG[tag]
         f32 = torch.float32
         # operands in the layouts the GEMMs consume (contraction axis contiguous)
-        self.xq, self.xqT = e(M, K, dt=qd), (e(K, M, dt=qd) if not self.rowmajor_bwd else None)
+        self.xq, self._xqT = e(M, K, dt=qd), (e(K, M, dt=qd) if not self.rowmajor_bwd else None)
         self.wq, self.wqbT = e(N, K, dt=qd), e(K, N, dt=qd)
         fp16_bwd = self.bwd_tag != tag           # that backward converts dY itself: no gradient operands are kept here
         self.dyq = e(M, N, dt=qd) if not fp16_bwd else None
         self._xq, self._dyq = self.xq, self.dyq          # (xq, dyq may come to name a caller's tensor that is used in place)
-        self.dyqT = e(N, M, dt=qd) if not (self.rowmajor_bwd or fp16_bwd) else None
+        self._dyqT = e(N, M, dt=qd) if not (self.rowmajor_bwd or fp16_bwd) else None
         # scales (amax/qmax), inverse scales, and the raw maxima
         self.sx, self.ix, self.ax = e(1, dt=f32), e(1, dt=f32), e(1, dt=f32)
         nsw = N if w_gran == Q.PER_ROW else 1
@@ -110,6 +110,12 @@ class QLinear:
             nb = Q.qsync_qlinear_bwd_fp16_of_int8_workspace_bytes(M, N, K, Q._DTYPE_OF[dy_dtype])
             self.ws_bwd16 = torch.zeros(max(nb, 256), dtype=torch.uint8, device=dev)
 
+    # Transposed operands: the kept copies, made when read by a small operator that is row-major by default, None otherwise.
+    xqT = property(lambda self: self.xq.t().contiguous() if self.own_copies else self._xqT)
+    dyqT = property(lambda self: self.dyq.t().contiguous() if self.own_copies and self.dyq is not None else self._dyqT)
+    xhT = property(lambda self: self.xh.t().contiguous() if self.own_copies else self._xhT)
+    dyhT = property(lambda self: self.dyh.t().contiguous() if self.own_copies else self._dyhT)
+
     # ---- precision conversion -----------------------------------------------------------
     def convert_x(self, x: torch.Tensor, stream=None, x_amax: Optional[torch.Tensor] = None) -> None:
         """x_amax: device float holding max |x| already (the producer's `y_amax`); it replaces the pass over x
@@ -121,18 +127,18 @@ class QLinear:
             else:
                 # maximum, scale and codes in one call
                 Q.qsync_absmax_quantize(x, M, K, self.bits, Q.ROUND_NEAREST, 0, 0, self.sx, self.ix, self.ax, self.xq,
-                                        self.xqT, self.ws_absmax, -1, stream)
+                                        self._xqT, self.ws_absmax, -1, stream)
                 return
             Q.qsync_quantize(x, M, K, K, Q.INT8, self.bits, Q.PER_TENSOR, Q.ROUND_NEAREST, 0, 0, self.ix, self.xq,
-                             self.xqT, stream)
+                             self._xqT, stream)
         elif x.dtype == _TORCH_OF_TAG[self.tag] and x.is_contiguous() and not self.own_copies:
             # already in the operand type: the tensor itself is the saved operand, only its transpose (if kept) is written
             self.xq = x
-            if self.xqT is not None:
-                Q.qsync_quantize(x, M, K, K, self.tag, 0, 0, 0, 0, 0, None, None, self.xqT, stream)
+            if self._xqT is not None:
+                Q.qsync_quantize(x, M, K, K, self.tag, 0, 0, 0, 0, 0, None, None, self._xqT, stream)
         else:
             self.xq = self._xq
-            Q.qsync_quantize(x, M, K, K, self.tag, 0, 0, 0, 0, 0, None, self.xq, self.xqT, stream)
+            Q.qsync_quantize(x, M, K, K, self.tag, 0, 0, 0, 0, 0, None, self.xq, self._xqT, stream)
 
     def convert_x_nhwc(self, act: torch.Tensor, stream=None) -> None:
         """3x3 / stride 1 / pad 1 convolution lowered to this operator (K = 9*C): the NHWC activation is
@@ -146,7 +152,7 @@ class QLinear:
                              stream)
         Q.qsync_quantize(act, self.M, c, c, Q.INT8, self.bits, Q.PER_TENSOR, Q.ROUND_NEAREST, 0, 0, self.ix, self.xq_nhwc,
                          None, stream)
-        Q.qsync_im2col3x3_i8(self.xq_nhwc, b, h, w, c, self.xq, self.xqT, stream)
+        Q.qsync_im2col3x3_i8(self.xq_nhwc, b, h, w, c, self.xq, self._xqT, stream)
 
     def convert_w(self, w: torch.Tensor, stream=None) -> None:
         N, K = self.N, self.K
@@ -172,16 +178,16 @@ class QLinear:
             Q.qsync_absmax_scale(dy, M, N, N, Q.PER_TENSOR, self.bits, self.sdy, self.idy, self.ady, self.db,
                                  self.ws_absmax, stream)
             Q.qsync_quantize(dy, M, N, N, Q.INT8, self.bits, Q.PER_TENSOR, self.dy_round, self.seed, self.offset,
-                             self.idy, self.dyq, self.dyqT, stream)
+                             self.idy, self.dyq, self._dyqT, stream)
             self.last_dy_offset = self.offset
             self.offset += (M * N + 7) // 8
         elif dy.dtype == _TORCH_OF_TAG[self.tag] and dy.is_contiguous() and not self.own_copies:
             self.dyq = dy
-            if self.dyqT is not None:
-                Q.qsync_quantize(dy, M, N, N, self.tag, 0, 0, 0, 0, 0, None, None, self.dyqT, stream)
+            if self._dyqT is not None:
+                Q.qsync_quantize(dy, M, N, N, self.tag, 0, 0, 0, 0, 0, None, None, self._dyqT, stream)
         else:
             self.dyq = self._dyq
-            Q.qsync_quantize(dy, M, N, N, self.tag, 0, 0, 0, 0, 0, None, self.dyq, self.dyqT, stream)
+            Q.qsync_quantize(dy, M, N, N, self.tag, 0, 0, 0, 0, 0, None, self.dyq, self._dyqT, stream)
 
     # ---- GEMMs ---------------------------------------------------------------------------
     def gemm_fwd(self, stream=None) -> None:
@@ -204,8 +210,8 @@ class QLinear:
         """Forward of an INT8 operator whose activation codes (`xq`, scale `sx`/`ix`) were written by its
         producer's epilogue: only the transposed copy for the weight gradient is still to be made."""
         self.convert_w(w, stream)
-        if self.xqT is not None:
-            Q.qsync_transpose_i8(self.xq, self.M, self.K, self.xqT, stream)
+        if self._xqT is not None:
+            Q.qsync_transpose_i8(self.xq, self.M, self.K, self._xqT, stream)
         self.gemm_fwd(stream)
         return self.y
 
@@ -220,7 +226,7 @@ class QLinear:
                                    self.db if want_db else None, dy if want_db else None,
                                    self.acc_dx, self.acc_dw, self.ws_bwd, stream)
             return
-        Q.qsync_qlinear_bwd(self.tag, self.M, self.N, self.K, self.dyq, self.dyqT, self.sdy, self.xqT, self.sx,
+        Q.qsync_qlinear_bwd(self.tag, self.M, self.N, self.K, self.dyq, self._dyqT, self.sdy, self._xqT, self.sx,
                             self.wqbT, self.swb, self.w_gran if self.w_gran == Q.PER_TENSOR else Q.PER_ROW,
                             self.dx, self.dw, self.db if want_db else None, dy if want_db else None, self.acc_dx,
                             self.acc_dw, self.ws_bwd, stream)
@@ -230,15 +236,15 @@ class QLinear:
         if not dy.is_contiguous():
             dy = dy.contiguous()
         rm = self.rowmajor_bwd
-        offs = Q.qsync_qlinear_bwd_fp16_of_int8(M, N, K, dy, self.xq if rm else self.xqT, rm, self.sx, self.wq, self.sw,
+        offs = Q.qsync_qlinear_bwd_fp16_of_int8(M, N, K, dy, self.xq if rm else self._xqT, rm, self.sx, self.wq, self.sw,
                                                 self.w_gran, dx, dw, db, self.ws_bwd16, stream)
         h = torch.float16
         view = lambda off, r, c: self.ws_bwd16[off:off + 2 * r * c].view(h).view(r, c)
         # the binary16 operands as the call left them in its workspace (for inspection and tests)
-        self.xh, self.xhT = (view(offs[0], M, K), None) if rm else (None, view(offs[0], K, M))
+        self.xh, self._xhT = (view(offs[0], M, K), None) if rm else (None, view(offs[0], K, M))
         self.wh, self.whT = view(offs[1], N, K), view(offs[2], K, N)
         self.dyh = dy if dy.dtype == h else view(offs[3], M, N)
-        self.dyhT = None if rm else view(offs[4], N, M)
+        self._dyhT = None if rm else view(offs[4], N, M)
 
     def gemm_bwd_part(self, which: str, dy: Optional[torch.Tensor], stream=None) -> None:
         """One of the two independent backward GEMMs ("dx" or "dw", the latter with the bias gradient when the tag
@@ -256,7 +262,7 @@ class QLinear:
                                    self.acc_dx if dx is not None else None, self.acc_dw if dw is not None else None,
                                    self.ws_bwd, stream)
             return
-        Q.qsync_qlinear_bwd(self.tag, self.M, self.N, self.K, self.dyq, self.dyqT, self.sdy, self.xqT, self.sx,
+        Q.qsync_qlinear_bwd(self.tag, self.M, self.N, self.K, self.dyq, self._dyqT, self.sdy, self._xqT, self.sx,
                             self.wqbT, self.swb, self.w_gran if self.w_gran == Q.PER_TENSOR else Q.PER_ROW,
                             dx, dw, self.db if want_db else None, dy if want_db else None,
                             self.acc_dx if dx is not None else None, self.acc_dw if dw is not None else None,

@@ -274,6 +274,23 @@ def test_binary16_buffers_may_be_reused_whatever_the_declared_types(declared):
     assert all(torch.equal(a, b) for a, b in zip(*results))
 
 
+@pytest.mark.parametrize("tag,bwd", [(Q.INT8, None), (Q.INT8, Q.FP16), (Q.FP16, None)])
+def test_transposed_operands_of_a_small_operator_can_be_read(tag, bwd):
+    """A small operator that is row-major by default still answers for its transposed operands."""
+    say("transposed operands", tag, bwd)
+    M, N, K = 256, 144, 272
+    case = wl.ragged_case(M, N, K, seed=11, dtype=np.float32)
+    op = QLinear(tag, M, N, K, x_dtype=torch.float32, dx_dtype=torch.float32, bwd_tag=bwd)
+    assert op.rowmajor_bwd
+    op.forward(dev(case.x), dev(case.w))
+    op.backward(dev(case.dy))
+    assert torch.equal(op.xqT, op.xq.t()) and op.xqT.is_contiguous()
+    if bwd is None:
+        assert torch.equal(op.dyqT, op.dyq.t())
+    else:
+        assert op.dyqT is None and torch.equal(op.xhT, op.xh.t()) and torch.equal(op.dyhT, op.dyh.t())
+
+
 @pytest.mark.parametrize("kind", ["linear FP16", "linear FP32", "convolution"])
 def test_a_tensor_used_in_place_is_never_written(kind):
     """A pass on tensors of the operand type (used as they are) followed by one on tensors of the other type (converted):
