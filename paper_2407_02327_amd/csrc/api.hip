@@ -544,8 +544,8 @@ int qsync_prepare_weights(const void* w, int wdt, int64_t N, int64_t K, int bits
                                              static_cast<hipStream_t>(stream)));
 }
 
-// Workspace of qsync_conv3x3_wgrad: [margin][three displaced copies of the activation, C x Mp each][margin]
-// [gradient operand, N x Mp][split-K partials]; every part starts on a 256-byte boundary.
+// Workspace of qsync_conv3x3_wgrad over padded copies: [margin][three displaced copies of the activation, C x Mp each]
+// [margin][gradient operand, N x Mp][split-K partials]; every part starts on a 256-byte boundary.
 namespace {
 struct WgradLayout { ConvPaddedAxis ax; size_t margin, off_x, off_dy, off_part, total; GemmPlan plan; };
 WgradLayout wgrad_layout(int tag, int64_t nimg, int64_t H, int64_t W, int64_t C, int64_t N)
@@ -562,13 +562,10 @@ WgradLayout wgrad_layout(int tag, int64_t nimg, int64_t H, int64_t W, int64_t C,
     return l;
 }
 // The gathering form: the weight-gradient GEMM reads the row-major gradient and the NHWC activation themselves (TN
-// form, patches formed by its loads).  Needs whole K tiles of 128 pixels and 32-bit byte offsets into the activation.
-bool wgrad_gathers(int tag, int64_t nimg, int64_t H, int64_t W, int64_t C, int64_t N)
-{
-    const int64_t esz = tag == QSYNC_INT8 ? 1 : 2, M = nimg * H * W;
-    return M > 0 && M * C * esz < (int64_t(1) << 31) && N < (int64_t(1) << 24) && 9 * C < (int64_t(1) << 24)
-           && H <= 65535 && W <= 65535;
-}
+// form, patches formed by its loads).  It needs rows of at most 2^24 elements for its 32-bit lane offsets, so gradients
+// with more output channels take the padded copies.  Its other bounds (9 C below 2^24, an activation below 2^31 bytes,
+// H and W below 2^16) follow from wgrad_shape_ok, whose three padded copies stay below 2^32 bytes.
+bool wgrad_gathers(int64_t N) { return N < (int64_t(1) << 24); }
 bool wgrad_shape_ok(int tag, int64_t nimg, int64_t H, int64_t W, int64_t C, int64_t N)
 {
     const int64_t esz = tag == QSYNC_INT8 ? 1 : 2;
@@ -586,20 +583,13 @@ size_t qsync_conv3x3_wgrad_workspace_bytes(int tag, int64_t nimg, int64_t H, int
     if((tag != QSYNC_INT8 && tag != QSYNC_FP16) || nimg <= 0 || H <= 0 || W <= 0 || C <= 0 || N <= 0
        || !wgrad_shape_ok(tag, nimg, H, W, C, N))
         return 0;
-    if(!wgrad_gathers(tag, nimg, H, W, C, N)) return wgrad_layout(tag, nimg, H, W, C, N).total;
+    if(!wgrad_gathers(N)) return wgrad_layout(tag, nimg, H, W, C, N).total;
     // split-K partials only (the largest over the tile shapes, so that a pinned tile fits too)
     size_t need = plan_gemm(tag, N, 9 * C, nimg * H * W, -1, -1, true, true).workspace;
     for(int t = 0; t < 3; ++t)
     {
         const size_t w = plan_gemm(tag, N, 9 * C, nimg * H * W, t, 0, true, true).workspace;
         need = w > need ? w : need;
-    }
-    // a pixel count that is no multiple of 128 used to need the transposed copies: callers bring that much, and a call
-    // with less is refused
-    if(nimg * H * W % 128 != 0)
-    {
-        const size_t copies = wgrad_layout(tag, nimg, H, W, C, N).total;
-        need = need > copies ? need : copies;
     }
     return round256(need);
 }
@@ -618,14 +608,13 @@ int qsync_conv3x3_wgrad(int tag, int64_t nimg, int64_t H, int64_t W, int64_t C, 
     const int esz = tag == QSYNC_INT8 ? 1 : 2;
     if((C * esz) % 16 != 0 || (N * esz) % 16 != 0 || !aligned16(xq) || !aligned16(dyq)) return QSYNC_ERR_ALIGN;
     hipStream_t st  = static_cast<hipStream_t>(stream);
-    if(wgrad_gathers(tag, nimg, H, W, C, N))
+    if(wgrad_gathers(N))
     {
         const int64_t  M    = nimg * H * W;
         const GemmPlan plan = plan_gemm(tag, N, 9 * C, M, -1, -1, true, /*tn=*/true);
-        const size_t   need = M % 128 != 0 ? qsync_conv3x3_wgrad_workspace_bytes(tag, nimg, H, W, C, N) : plan.workspace;
-        if(need > 0)
+        if(plan.workspace > 0)
         {
-            if(!workspace || workspace_bytes < need) return QSYNC_ERR_WORKSPACE;
+            if(!workspace || workspace_bytes < plan.workspace) return QSYNC_ERR_WORKSPACE;
             if((reinterpret_cast<uintptr_t>(workspace) & 255) != 0) return QSYNC_ERR_ALIGN;
         }
         GemmProblem p{};

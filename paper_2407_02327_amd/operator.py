@@ -293,12 +293,11 @@ class QLinear:
 
 class QConv3x3:
     """One 3x3 / stride 1 / pad 1 NHWC convolution as quantized operator (paper: Backend section, low-precision
-    convolution on NHWC tensors).  Forward and data gradient run as implicit GEMMs over the codes (the patch
-    matrix is never stored); the weight gradient contracts over the pixels and reads the transposed patch
-    matrix, expanded from the int8 codes.  Buffers are allocated once; nothing here computes.
+    convolution on NHWC tensors).  All three passes run as implicit GEMMs over the codes (the patch matrix is never
+    stored); the weight gradient contracts over the pixels.  Buffers are allocated once; nothing here computes.
 
     INT8 and FP16: all three passes (the patch-matrix form of the weight gradient is INT8 only).
-    The weight gradient reads both operands transposed over a zero-padded pixel axis (qsync_conv3x3_wgrad);
+    The weight gradient reads the gradient and the activation as they lie (qsync_conv3x3_wgrad);
     wgrad_via_patches=True materialises the transposed patch matrix instead (qsync_im2col3x3_i8 + the linear
     operator's dW GEMM).
     """

@@ -219,18 +219,26 @@ def test_conv_wgrad_validation():
     assert f(*a) == qsync.ERR_ALIGN
     a = list(ok); a[0] = 16; a[12] = A
     assert f(*a) == qsync.ERR_UNSUPPORTED                    # accumulator dump: INT8 only
-    a = list(ok); a[14] = 64
-    assert f(*a) == qsync.ERR_WORKSPACE
-    a = list(ok); a[13] = P(4112)                            # 16-byte but not 256-byte aligned
-    assert f(*a) == qsync.ERR_ALIGN
+    for nimg in (64, 63):                                    # (a contraction long enough to be split, see below)
+        a = list(ok); a[1:6] = [nimg, 56, 56, 64, 64]; a[14] = 64
+        assert f(*a) == qsync.ERR_WORKSPACE
+        a = list(ok); a[1:6] = [nimg, 56, 56, 64, 64]; a[13] = P(4112)      # 16-byte but not 256-byte aligned
+        assert f(*a) == qsync.ERR_ALIGN
     a = list(ok); a[1] = 0
     assert f(*a) == qsync.OK
-    # 64 x 56 x 56 pixels are a multiple of 128: the GEMM gathers its operands itself, the workspace holds split-K
-    # partials only; 63 images are not: padded transposed copies (three of the activation, one of the gradient)
-    gather = lib.qsync_conv3x3_wgrad_workspace_bytes(8, 64, 56, 56, 64, 64)
-    assert 0 < gather < 3 * 64 * 64 * 57 * 64 // 2 and gather % (64 * 576 * 4) == 0
-    assert lib.qsync_conv3x3_wgrad_workspace_bytes(8, 63, 56, 56, 64, 64) > 3 * 63 * 64 * 57 * 64
-    assert lib.qsync_conv3x3_wgrad_workspace_bytes(16, 63, 56, 56, 64, 64) > 2 * 3 * 63 * 64 * 57 * 64
+    # the GEMM gathers its operands itself at any pixel count (64 images of 56 x 56 are a multiple of 128 pixels, 63 are
+    # not): the workspace holds split-K partials only
+    for nimg in (64, 63):
+        for tag in (8, 16):
+            gather = lib.qsync_conv3x3_wgrad_workspace_bytes(tag, nimg, 56, 56, 64, 64)
+            assert 0 < gather < 3 * 64 * 64 * 57 * 64 // 2 and gather % (64 * 576 * 4) == 0
+    assert lib.qsync_conv3x3_wgrad_workspace_bytes(8, 1, 1, 1, 16, 1 << 12) == 0          # one K tile: nothing to split
+    a = list(ok); a[1:6] = [1, 1, 1, 16, 1 << 12]; a[13], a[14] = None, 0
+    assert f(*a) == qsync.ERR_HIP                                                         # and none is asked for
+    # from 2^24 output channels on: padded transposed copies (three of the activation, one of the gradient, 48 pixels each)
+    for tag in (8, 16):
+        assert lib.qsync_conv3x3_wgrad_workspace_bytes(tag, 1, 1, 1, 16, 1 << 24) >= tag // 8 * 48 * (48 + (1 << 24))
+        assert lib.qsync_conv3x3_wgrad_workspace_bytes(tag, 1, 1, 1, 16, (1 << 24) - 16) < 1 << 24
 
 
 @pytest.mark.parametrize("rowmajor", [False, True])

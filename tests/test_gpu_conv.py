@@ -112,7 +112,7 @@ def test_weight_gradient_on_codes_bit_exact(tile):
     from tests.gpu_util import ws
     rng = np.random.default_rng(67)
     Q.qsync_debug_set_gemm_tile(tile)
-    # (pixel counts that are multiples of 128 take the gathering TN GEMM, the others the padded transposed copies)
+    # (pixel counts that are multiples of 128, and others: the gather's last K tile is then partial)
     for (b, h, w, c, n) in [(1, 4, 4, 16, 16), (2, 7, 5, 16, 32), (3, 8, 8, 64, 64), (1, 13, 16, 48, 48), (2, 3, 70, 80, 16),
                             (5, 9, 15, 32, 144), (1, 1, 1, 16, 16), (2, 31, 33, 16, 16),
                             (2, 8, 8, 16, 16), (4, 8, 8, 64, 64), (2, 16, 16, 48, 48), (8, 4, 4, 80, 16), (1, 16, 24, 32, 144),
@@ -278,3 +278,26 @@ def test_chained_convolution_takes_its_scale_from_the_producers_epilogue(tile):
         assert_bits_equal(host(cons.acc), want_acc.astype(np.int32), "consumer accumulators")
     finally:
         Q.qsync_debug_set_gemm_tile(-1)
+
+
+@pytest.mark.parametrize("tag", [Q.INT8, Q.FP16])
+def test_weight_gradient_with_more_output_channels_than_the_gather_addresses(tag):
+    """2^24 output channels and more: the weight gradient over padded transposed copies.  Whole numbers of at most 9 in
+    magnitude: the sums are exact in any order and in binary16."""
+    from tests.gpu_util import ws
+    b, h, w, c, n = 2, 2, 3, 16, (1 << 24) + 16
+    dt = torch.int8 if tag == Q.INT8 else torch.float16
+    say("conv wgrad over padded copies", tag, b, h, w, c, n)
+    g = torch.Generator(device="cuda").manual_seed(8)
+    x = torch.randint(-9, 10, (b, h, w, c), dtype=dt, device="cuda", generator=g)
+    dy = torch.randint(-9, 10, (b * h * w, n), dtype=dt, device="cuda", generator=g)
+    one = torch.ones(1, device="cuda")
+    wsp = ws(Q.qsync_conv3x3_wgrad_workspace_bytes(tag, b, h, w, c, n))
+    wsp.fill_(0x7E)                                               # NaN patterns: nothing in it needs initialising
+    dw = torch.empty(n, 9 * c, dtype=torch.float16, device="cuda")
+    Q.qsync_conv3x3_wgrad(tag, b, h, w, c, n, x, one, dy, one, dw, None, wsp)
+    pad = torch.nn.functional.pad(x.float(), (0, 0, 1, 1, 1, 1))
+    patches = torch.cat([pad[:, i:i + h, j:j + w, :].reshape(b * h * w, c) for i in range(3) for j in range(3)], dim=1)
+    for n0 in range(0, n, 1 << 22):
+        want = dy[:, n0:n0 + (1 << 22)].float().t().contiguous() @ patches
+        assert torch.equal(dw[n0:n0 + (1 << 22)].float(), want), n0
