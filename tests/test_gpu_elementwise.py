@@ -398,12 +398,13 @@ def test_empty_tensors_are_noops():
 @pytest.mark.parametrize("rnd", ["nearest", "stochastic", "floor"])
 def test_absmax_quantize_in_one_launch(dtype, rnd):
     """qsync_absmax_quantize: maximum, scales, codes and transposed codes equal the oracle's absmax ->
-    scales_from_amax -> quantize_int bit for bit -- on shapes the single launch serves (one to 128 workgroups, ragged
-    patch tails), on shapes it hands to the two launches (odd columns, large tensors), with the
-    wait for the other workgroups cut to zero polls (every workgroup but the last then finds the maximum by itself),
-    and on repeated calls that share one workspace without clearing it."""
+    scales_from_amax -> quantize_int bit for bit -- on shapes the single launch serves (up to 128 KB: 64x504, for fp32
+    64x512 is the last, for binary16 128x512), on shapes that take block maxima and a quantizing pass, on shapes handed to
+    the two separate passes (odd columns), for any poll_limit, and on repeated calls that share one workspace without
+    clearing it."""
     rng = np.random.default_rng(31)
-    shapes = [(64, 128), (272, 1000), (1008, 72), (4096, 768), (2048, 2048), (48, 8200), (130, 72), (3, 5), (257, 1001)]
+    shapes = [(64, 128), (272, 1000), (1008, 72), (4096, 768), (2048, 2048), (48, 8200), (130, 72), (3, 5), (257, 1001),
+              (64, 504), (64, 512), (64, 520), (128, 512), (128, 520)]
     w = ws(max(Q.qsync_absmax_quantize_workspace_bytes(r, c) for r, c in shapes))       # zero-filled once
     for rows, cols in shapes:
         x = _data(rng, (rows, cols), dtype, sigma=0.3)
@@ -412,23 +413,20 @@ def test_absmax_quantize_in_one_launch(dtype, rnd):
         amax = orc.absmax(x, "tensor")
         so, io = orc.scales_from_amax(amax)
         want = orc.quantize_int(x, io, "tensor", rnd, 77, 1234)
-        for polls in (-1, 0, 3):
-            for with_t in (True, False):
-                if with_t and rows % 16 != 0:
-                    continue
-                say("absmax_quantize", dtype.__name__, rnd, rows, cols, "polls", polls, "transposed", with_t)
-                s, iv, am = empty(1, torch.float32), empty(1, torch.float32), empty(1, torch.float32)
-                q = torch.full((rows, cols), 99, dtype=torch.int8, device="cuda")
-                qT = torch.full((cols, rows), 99, dtype=torch.int8, device="cuda") if with_t else None
-                Q.qsync_absmax_quantize(xd, rows, cols, 8, RND[rnd], 77, 1234, s, iv, am, q, qT, w, polls)
-                torch.cuda.synchronize()
-                assert_bits_equal(host(am), amax, "amax")
-                assert_bits_equal(host(s), so, "scale")
-                assert_bits_equal(host(iv), io, "inverse scale")
-                assert_bits_equal(host(q), want, "codes")
-                if with_t:
-                    assert_bits_equal(host(qT), want.T, "transposed codes")
-    # the workspace's ticket word is back at zero: the separate maximum pass can use the same buffer next
+        for with_t, polls in ((True, -1), (False, 0)):
+            say("absmax_quantize", dtype.__name__, rnd, rows, cols, "polls", polls, "transposed", with_t)
+            s, iv, am = empty(1, torch.float32), empty(1, torch.float32), empty(1, torch.float32)
+            q = torch.full((rows, cols), 99, dtype=torch.int8, device="cuda")
+            qT = torch.full((cols, rows), 99, dtype=torch.int8, device="cuda") if with_t else None
+            Q.qsync_absmax_quantize(xd, rows, cols, 8, RND[rnd], 77, 1234, s, iv, am, q, qT, w, polls)
+            torch.cuda.synchronize()
+            assert_bits_equal(host(am), amax, "amax")
+            assert_bits_equal(host(s), so, "scale")
+            assert_bits_equal(host(iv), io, "inverse scale")
+            assert_bits_equal(host(q), want, "codes")
+            if with_t:
+                assert_bits_equal(host(qT), want.T, "transposed codes")
+    # the workspace's arrival counter is zero: the separate maximum pass can use the same buffer next
     assert int(w[:4].view(torch.int32).item()) == 0
     x = _data(rng, (512, 4096), dtype)
     s, iv, am = empty(1, torch.float32), empty(1, torch.float32), empty(1, torch.float32)
