@@ -65,7 +65,8 @@ typedef enum {
 /*
  * qsync_absmax_scale - absolute maximum and symmetric fixed-point scale.
  * Paper: Backend section, "Minmax Optimization" (two-step reduction: block partials, then a
- * small second step; here the last block to finish performs that step inside the same launch);
+ * small second step; per tensor the last block to finish performs that step inside the same launch, per column and
+ * with colsum_opt a second launch does);
  * scale of the fixed-point quantizer x_bar = (x - z)/q with z = 0.
  *
  *   amax  = max |x| over the tensor (PER_TENSOR), each row (PER_ROW) or each column (PER_COL)
@@ -145,8 +146,9 @@ int qsync_absmax_scale_static(const void* x, int xdt, int64_t rows, int64_t cols
  *           At least one of q_opt, qT_opt is required.  The GEMM entry points take some
  *           operands in transposed form; this is where those copies are made.
  * bits, gran, rnd, seed, offset are ignored for FP16 / FP32 (except the stochastic FP16 case above).
- * Any shape and alignment is accepted; the vectorised path needs cols % 8 == 0, x and ld*sizeof(elem)
- * multiples of 16 bytes, q 16-byte aligned (and rows % 16 == 0 for qT).
+ * Any shape and alignment is accepted; the vectorised path needs cols % 8 == 0 (% 4 for FP32), x and ld*sizeof(elem)
+ * multiples of 16 bytes, q 16-byte aligned (8 for PER_TENSOR codes), and qT 16-byte aligned with rows % 16 == 0
+ * (PER_TENSOR, FP16 and FP32: any other row count as well, at any alignment of qT).
  */
 int qsync_quantize(const void* x, int xdt, int64_t rows, int64_t cols, int64_t ld,
                    int tag, int bits, int gran, int rnd,
@@ -423,8 +425,9 @@ size_t qsync_conv3x3_wgrad_workspace_bytes(int tag, int64_t nimg, int64_t H, int
  *   qsync_absmax_scale(w as [9N,C], PER_COL) -> swb, iwb;     qsync_quantize(PER_COL, nearest) -> codes [N,9C]
  *   qsync_conv3x3_wflip(codes) -> wflip [C,9N]
  * wflip with swb (QSYNC_PER_ROW of wflip) is the weight operand of the data gradient, see qsync_conv3x3_fwd.
- * Three launches and two reads of w when N % 16 == 0 (row and column maxima in one pass, both sets of codes
- * from one read, written straight to their final places), the five separate passes otherwise.
+ * Two launches and two reads of w when N % 16 == 0, N <= 8192 and rows of w are multiples of 32 bytes (row and column
+ * maxima in one pass, both sets of codes from one read, written straight to their final places), the five separate
+ * passes otherwise.
  * w [N, 9*C] packed (k = (kh, kw, c)), wdt QSYNC_F32 or QSYNC_F16; sw, iw: N floats; swb, iwb: C floats.
  * workspace  at least qsync_conv3x3_prepare_weights_workspace_bytes(N, C) bytes, 16-byte aligned, its first
  *            256 bytes zeroed once by the caller (as for qsync_absmax_scale).
@@ -452,8 +455,7 @@ size_t qsync_conv3x3_prepare_weights_workspace_bytes(int64_t N, int64_t C);
  *
  * The data gradient of the convolution is this same entry point with the roles of the channels
  * swapped: dX[m, c] = conv3x3(dyq [nimg,H,W,N], wflip [C, 9*N]) with wflip from qsync_conv3x3_wflip
- * (C and N exchanged in the call).  The weight gradient is qsync_qlinear_bwd (dx_opt = NULL) on the
- * transposed patch matrix of qsync_im2col3x3_i8.
+ * (C and N exchanged in the call).  The weight gradient is qsync_conv3x3_wgrad.
  */
 int qsync_conv3x3_fwd(int tag, int64_t nimg, int64_t H, int64_t W, int64_t C, int64_t N,
                       const void* xq, const float* sx, const void* wq, const float* sw, int wgran,

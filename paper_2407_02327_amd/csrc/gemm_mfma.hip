@@ -14,8 +14,8 @@
 //     one 256-byte bank row per group, so the chunk position is XOR-swizzled with (row/2)%8
 //     (applied on the global-address side of the direct load): the 16 lanes that read one
 //     chunk index of 16 consecutive rows then touch 16 different 16-byte bank groups;
-//   * two LDS stages: the next K step streams in while the current one feeds the matrix
-//     cores; fragments for the next 32-byte K chunk are requested before the current chunk's
+//   * two LDS stages (three for the 128x128 tile while no compute unit gets a second workgroup): the next K
+//     step streams in while the current one feeds the matrix cores; fragments for the next 32-byte K chunk are requested before the current chunk's
 //     matrix instructions; one barrier per K step;
 //   * the dequantizer (scalar scales, per-column scale vector, per-column bias) runs on the
 //     accumulator registers (the paper fuses dequantization at the same point: before the
@@ -1548,8 +1548,11 @@ template <typename TR>
 hipError_t launch_traits(int tile, const GemmKernelArgs& a, int splits, hipStream_t st, bool tn = false)
 {
     // Three stages for the 128x128 tile where every compute unit gets one workgroup at most; with a second one resident
-    // (two stages) its K loop fills the gaps instead.  Measured with four wavefronts, two -> three stages: 4096x768x3072
-    // (192 workgroups) int8 20.4 -> 17.8 us, binary16 35.8 -> 30.3; but 4096x3072x768 (768 workgroups) int8 18.5 -> 23.3.
+    // (two stages) its K loop fills the gaps instead.  Measured, two -> three stages: 4096x768x3072 (192 workgroups) int8
+    // 18.5 -> 15.3 us, binary16 33.5 -> 26.4; 2048x2048x4096 (256) int8 25.8 -> 22.5, binary16 45.4 -> 39.4; a short
+    // contraction gains nothing (4096x768x768 int8 6.8 -> 7.0, binary16 9.3 -> 9.6).  Beyond 256 workgroups it loses:
+    // 2176x2048x1024 (272) int8 10.9 -> 14.2, binary16 17.6 -> 21.8; 4096x2048x3072 (512) int8 29.9 -> 34.2, binary16
+    // 55.2 -> 60.4; 4096x3072x768 (768) int8 15.5 -> 18.9, binary16 25.6 -> 28.5.
     // The 64x64 tile gains nothing from 3, 4 or 8 stages (14.7 / 16.4 / 17.3 / 23.9 us on 2056x1000x1032 binary16), nor
     // from fragments read a whole K tile ahead (14.7).
     const int64_t workgroups = static_cast<int64_t>(a.tiles_m) * a.tiles_n * splits;
@@ -1652,8 +1655,8 @@ GemmPlan plan_gemm(int prec, int64_t M, int64_t N, int64_t K, int force_tile, in
     // measurements of this kernel (int8 and binary16, forward, row-major and transposed weight-gradient forms: 54
     // operands x 3 tiles, replayed from a graph; rms error 11 %, the choice at most 8 % behind the best tile):
     //   a compute unit retires `r1` Mop/us per resident workgroup of a tile shape, up to `rmax` with `occ` of them
-    //   sharing it; the chip as a whole retires at most `cap` Mop/us (the power limit: 256 busy units do not
-    //   each reach `rmax`); every round of co-resident workgroups costs `ovh` us of launch, first-load latency
+    //   sharing it; the chip as a whole retires at most `cap` Mop/us (256 busy units, at a lower clock and on
+    //   shared caches, do not each reach `rmax`); every round of co-resident workgroups costs `ovh` us of launch, first-load latency
     //   and epilogue; split K adds its reduction pass.
     const double    cus = 256.0;
     auto estimate = [&](int t, int64_t s) {
@@ -1840,9 +1843,15 @@ static double unit_time(const TileModel& m, double mop, const double* rounds, in
 
 // Tile on which two GEMMs share a launch (`a` first), or -1 when two launches are estimated to be about as fast: with more
 // than sixteen rounds of workgroups each of them fills the chip by itself, and a long contraction unsplit beside short ones
-// would outlast them.  Separate launches -> one, measured: int8 1808x1040x784 21.3 -> 14.2 us, 4096x768x3072 38.0 ->
-// 29.5, 1024^3 11.1 -> 7.1; binary16 2056x1000x1032 36.5 -> 26.9, 4096x3072x768 62.2 -> 54.2; not paired: 4096x768x768
-// binary16 27.5 (one launch 36.6), 3000x768x768 26.4 (31.2).
+// would outlast them.  Separate launches -> one, measured: int8 1808x1040x784 15.8 -> 11.7 us, 4096x768x3072 35.1 ->
+// 30.2, 1024^3 11.2 -> 7.4; binary16 2056x1000x1032 31.2 -> 25.4, 4096x3072x768 60.9 -> 51.7; not paired: 4096x768x768
+// binary16 28.5 (one launch 32.8), 3000x768x768 25.4 (30.2).
+// How far the estimate reaches, over 146 backward passes (44 operators from 512^3 to 8192 x 1024^2, drawn evenly over the
+// logarithm, both types, transposed copies and row-major, replayed from a graph; two launches against one on either tile):
+// its rms error is 17 % for int8 and 27 % for binary16, where it is 14 % too long on average.  The choice costs 1.9 % on
+// average against the best of the three and more than 10 % in ten cases (binary16 384x1744x1168 left apart, 19.5 us against
+// 14.2, is the worst); it errs towards two launches: the 114 pairs run 1.48 times as fast as apart, the worst of them
+// 2.4 % slower.
 static int pair_tile(const GemmProblem& a, const GemmProblem& b, double separate_us)
 {
     constexpr int kMaxRounds = 16;

@@ -52,7 +52,6 @@ hipError_t launch_dequantize(const void* a, int adt, int64_t rows, int64_t cols,
 // yT [cols, rows]
 hipError_t launch_dequantize_f16_tiles(const int8_t* a, int64_t rows, int64_t cols, const float* row_scale, const float* scale, void* y,
                                       void* yT, hipStream_t stream);
-// 3x3 / stride 1 / pad 1 patches of an int8 NHWC tensor: a [M, 9C] and/or aT [9C, M], M = nimg*H*W
 hipError_t launch_prepare_weights(const void* w, int wdt, int64_t N, int64_t K, float qmax, float* sw, float* iw,
                                   float* aw_opt, int8_t* wq, float* swb, float* iwb, int8_t* wqbT, void* workspace,
                                   hipStream_t stream);
@@ -68,6 +67,7 @@ ConvPaddedAxis conv_padded_axis(int64_t nimg, int H, int W);
 // and behind `out` are cleared as well
 hipError_t launch_conv_padded_transpose(const void* in, int elem_bytes, int64_t nimg, int H, int W, int Ch, int copies,
                                         void* out, int margin_bytes, hipStream_t stream);
+// 3x3 / stride 1 / pad 1 patches of an int8 NHWC tensor: a [M, 9C] and/or aT [9C, M], M = nimg*H*W
 hipError_t launch_im2col3x3_i8(const int8_t* xq, int64_t nimg, int H, int W, int C, int8_t* a, int8_t* aT,
                                hipStream_t stream);
 hipError_t launch_zero_f32(float* p, int64_t n, hipStream_t stream);
