@@ -159,7 +159,8 @@ int qsync_quantize(const void* x, int xdt, int64_t rows, int64_t cols, int64_t l
  * qsync_absmax_quantize - qsync_absmax_scale (PER_TENSOR) followed by qsync_quantize (tag INT8, PER_TENSOR) on a
  * packed tensor (ld == cols), with identical results.  Where the vector rules hold (cols % 8 == 0, 16-byte aligned x
  * and outputs) a tensor of up to 128 KB takes one launch, every workgroup of which reads all of it for the maximum, and
- * a larger one two: block maxima, then a quantizing pass that folds them; other tensors take the two calls.  Paper:
+ * a larger one two: block maxima, then a quantizing pass that folds them; other tensors, and some with a transposed copy
+ * of a row count that is no multiple of 16, take the two calls.  Paper:
  * Backend section, "Minimum and Maximum Optimization" (the collection of the maximum is the casting cost the paper
  * trims); Cost Mapper, cvt_cost.
  *

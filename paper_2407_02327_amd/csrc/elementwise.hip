@@ -1712,6 +1712,16 @@ template <typename T> static bool tile_ok(const T* x, int64_t rows, int64_t cols
         && (rows % 16 != 0 || aligned16(qT)) && tiles_of(rows, cols, 64) < (int64_t(1) << 31);
 }
 
+// A row count that is no multiple of 16 leaves the columns of the transposed copy unaligned, and the tile kernel then
+// gathers or stores them in pieces, with most of a tile's rows absent when there are few: one element per thread
+// (quantize_generic_kernel) is faster for fewer than 16 rows (1 x 65536: 2.4 against 4.4 us, 1 x 1048576: 4.5 against
+// 30; 9 x 65536: 4.0 against 4.1) and up to about 400 000 elements (45 x 1024: 2.5 against 4.7 us, 500 x 128: 2.8 against
+// 4.5, 1000 x 264: 3.8 against 4.7, 1000 x 392: 4.6 against 4.9; 1000 x 528: 5.5 against 5.1, 1000 x 1048: 8.4 against 6.1).
+static bool odd_transpose_generic(int64_t rows, int64_t n, const int8_t* qT)
+{
+    return qT && rows % 16 != 0 && (rows < 16 || n < (int64_t(3) << 17));
+}
+
 // Per-tensor codes of a tensor that meets tile_ok: the streaming kernel when only row-major codes of a contiguous tensor
 // are wanted, tiles otherwise.  Tiles are 128 rows high (whole 128-byte lines of the transposed copy) once that gives
 // every compute unit two workgroups, 64 rows below.
@@ -1751,7 +1761,7 @@ static hipError_t quantize_typed(const T* x, int64_t rows, int64_t cols, int64_t
     const PatchShape ps = patch_shape<T>(rows, cols, qT != nullptr);
     const bool       fast = cols % 8 == 0 && aligned16(x) && (ld * sizeof(T)) % 16 == 0 && (!q || aligned16(q))
                       && (!qT || (aligned16(qT) && rows % 16 == 0)) && ps.gx * ps.gy < (int64_t(1) << 31);
-    if(gran == kPerTensor && tile_ok(x, rows, cols, ld, q, qT))
+    if(gran == kPerTensor && tile_ok(x, rows, cols, ld, q, qT) && !odd_transpose_generic(rows, rows * cols, qT))
     {
         const TensorScale ts{inv, nullptr, 0, nullptr, nullptr, nullptr};
         quantize_tensor_launch<T, kInv>(x, rows, cols, ld, qmax, rnd, seed, offset, ts, q, qT, st);
@@ -1783,13 +1793,20 @@ hipError_t launch_quantize_int8(const void* x, int xdt, int64_t rows, int64_t co
 
 // Per-tensor maximum, scales and codes of a contiguous tensor.  Up to kWholeBytes one launch, every workgroup of which
 // reads the whole tensor for its maximum (no workgroup waits for another); above that a launch that leaves one maximum
-// per block and the quantizing launch, which folds them.
+// per block and the quantizing launch, which folds them.  Where the transposed copy of an odd row count goes one element per
+// thread, the two separate passes -- except for tensors so small that saving a launch outweighs it (nearest 100 x 80:
+// one launch 5.8 us, 6.1 apart; but 100 x 160 6.7 against 6.1, 45 x 1024 6.7 against 6.0; stochastic rounding, whose Philox blocks
+// the tile's absent rows cost as well, 36 x 344: 6.6 against 6.2), and from 192 K elements of 16 rows or more on, where
+// folding the maxima in the quantizer makes up for it (70 x 3744 7.5 against 8.4, 500 x 528 8.1 against 8.5).
 template <typename T>
 static hipError_t absmax_quantize_typed(const T* x, int64_t rows, int64_t cols, int qmax, int rnd, uint64_t seed,
                                         uint64_t offset, float* scale, float* inv_scale, float* amax_opt, int8_t* q,
                                         int8_t* qT, void* workspace, hipStream_t st)
 {
-    if(!tile_ok(x, rows, cols, cols, q, qT))
+    const int64_t n     = rows * cols;
+    const bool    apart = odd_transpose_generic(rows, n, qT) && n >= (int64_t(1) << (rnd == kStochastic ? 13 : 14))
+                       && (rows < 16 || n < (int64_t(3) << 16));
+    if(apart || !tile_ok(x, rows, cols, cols, q, qT))
     {
         hipError_t e = absmax_typed(x, rows, cols, cols, kPerTensor, static_cast<float>(qmax), scale, inv_scale, amax_opt,
                                     nullptr, nullptr, workspace, st);

@@ -456,6 +456,33 @@ def test_absmax_quantize_all_zero_and_lower_bits():
     assert_bits_equal(host(qT), want.T, "transposed codes, 5 bits")
 
 
+@pytest.mark.parametrize("rnd", ["nearest", "stochastic"])
+@pytest.mark.parametrize("rows,cols", [(1, 8), (1, 16384), (3, 65536), (15, 26216), (24, 336), (24, 344), (24, 680), (24, 688),
+                                       (40, 4912), (40, 4920), (17, 23128), (17, 23136)])
+def test_transposed_codes_of_odd_row_counts_by_every_route(rows, cols, rnd):
+    """Row counts that are no multiple of 16, on both sides of each limit between one element per thread and tiles, and
+    between one call's fused forms and the two separate passes: bits of the oracle either way."""
+    rng = np.random.default_rng(rows + cols)
+    x = _data(rng, (rows, cols), np.float16, sigma=0.3)
+    so, io = orc.scales_from_amax(orc.absmax(x, "tensor"))
+    want = orc.quantize_int(x, io, "tensor", rnd, 3, 17)
+    say("odd rows", rows, cols, rnd)
+    w = ws(Q.qsync_absmax_quantize_workspace_bytes(rows, cols))
+    s, iv = empty(1, torch.float32), empty(1, torch.float32)
+    for fused in (True, False):
+        q = torch.full((rows, cols), 99, dtype=torch.int8, device="cuda")
+        qT = torch.full((cols, rows), 99, dtype=torch.int8, device="cuda")
+        if fused:
+            Q.qsync_absmax_quantize(dev(x), rows, cols, 8, RND[rnd], 3, 17, s, iv, None, q, qT, w)
+            assert_bits_equal(host(s), so, "scale")
+            assert_bits_equal(host(iv), io, "inverse scale")
+            assert int(w[:4].view(torch.int32).item()) == 0       # the arrival counter is left at zero
+        else:
+            Q.qsync_quantize(dev(x), rows, cols, cols, Q.INT8, 8, Q.PER_TENSOR, RND[rnd], 3, 17, iv, q, qT)
+        assert_bits_equal(host(q), want, "codes")
+        assert_bits_equal(host(qT), want.T, "transposed codes")
+
+
 @pytest.mark.parametrize("dtype", [np.float32, np.float16])
 @pytest.mark.parametrize("rows,cols", [(1, 8), (63, 120), (65, 136), (45, 1024), (128, 256), (129, 256), (130, 520),
                                        (8208, 1024)])
