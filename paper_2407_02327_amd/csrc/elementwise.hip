@@ -1305,6 +1305,7 @@ template <> __device__ __forceinline__ __half scaled_code<__half>(float a, float
 // goes through LDS, four rows of a column per write, and leaves as whole 128-byte (binary16) or 256-byte segments.
 // Latency bound at small sizes: one 8 x 8 patch per lane kept half the wavefronts in flight (2056x1032 fp32 -> binary16
 // with both copies 8.5 -> 7.4 us, 4096x1024 11.5 -> 9.4; fp32 8192x4096 transposed element by element 69.2 -> 54.6).
+// binary16 sources go by patches all the same (copy_f16_patch_kernel).
 constexpr int kConvertRows = 64;
 template <typename Ti, typename To>
 __global__ __launch_bounds__(kBlock) void convert_tile_kernel(const Ti* __restrict__ x, int64_t rows, int64_t cols, int64_t ld,
@@ -1370,6 +1371,41 @@ __global__ __launch_bounds__(kBlock) void convert_tile_kernel(const Ti* __restri
 #pragma unroll
             for(int e = 0; e < TC; ++e)
                 if(r + e < rows) dst[e] = v.v[e];
+    }
+}
+
+// binary16 copied and transposed without converting anything: a lane owns an 8 x 8 patch, transposed in registers by pairing
+// 16-bit halves, a wavefront 8 x 8 patches, so every load and store instruction covers 128-byte row segments; no LDS,
+// no barrier.  Needs cols % 8 == 0, 16-byte aligned rows, and rows % 8 == 0 when the transposed copy is written.
+// Bound by latency when small and by its two streams when large; the tile kernel's pass through LDS is a second latency that
+// nothing hides here (fp32 sources, whose loads are twice as long, run faster through it).  Tiles -> patches, transposed
+// copy alone: 64x512 3.5 -> 2.4 us, 4096x768 5.1 -> 3.8, 16384x1024 15.8 -> 12.7, 16384x4096 49 -> 43; both copies 4096x768
+// 6.2 -> 5.2, 16384x1024 18.0 -> 16.4, 16384x4096 88 -> 89.
+__global__ __launch_bounds__(kBlock) void copy_f16_patch_kernel(const __half* __restrict__ x, int64_t rows, int64_t cols, int64_t ld,
+                                                                __half* __restrict__ q, __half* __restrict__ qT, int64_t grid_x)
+{
+    const int     lane = threadIdx.x % kWaveSize, wave = threadIdx.x / kWaveSize;
+    const int64_t by = blockIdx.x / grid_x, bx = blockIdx.x - by * grid_x;
+    const int64_t r0 = (by * (kBlock / kWaveSize) + wave) * 64 + (lane / 8) * 8;
+    const int64_t c0 = bx * 64 + (lane % 8) * 8;
+    if(r0 >= rows || c0 >= cols) return;
+    uint4 w[8];
+#pragma unroll
+    for(int i = 0; i < 8; ++i) w[i] = r0 + i < rows ? *reinterpret_cast<const uint4*>(x + (r0 + i) * ld + c0) : make_uint4(0, 0, 0, 0);
+    if(q)
+#pragma unroll
+        for(int i = 0; i < 8; ++i)
+            if(r0 + i < rows) *reinterpret_cast<uint4*>(q + (r0 + i) * cols + c0) = w[i];
+    if(!qT) return;
+    auto pair = [&](int i, int p) { return p == 0 ? w[i].x : p == 1 ? w[i].y : p == 2 ? w[i].z : w[i].w; };
+#pragma unroll
+    for(int c = 0; c < 8; ++c)
+    {   // column c of the patch: halves c % 2 of pair c / 2 of every row
+        uint32_t t[4];
+#pragma unroll
+        for(int g = 0; g < 4; ++g)
+            t[g] = __builtin_amdgcn_perm(pair(2 * g + 1, c / 2), pair(2 * g, c / 2), c % 2 ? 0x07060302u : 0x05040100u);
+        *reinterpret_cast<uint4*>(qT + (c0 + c) * rows + r0) = make_uint4(t[0], t[1], t[2], t[3]);
     }
 }
 
@@ -1904,11 +1940,36 @@ static bool convert_tiles(const Ti* x, int64_t rows, int64_t cols, int64_t ld, c
     return true;
 }
 
+// binary16 to binary16 by patches, where their vector rules hold; false: nothing was launched.  A row-major copy alone gains from
+// them below 2 M elements (1024x1024 3.0 -> 2.7 us) and, while every patch column is whole, below 8 M (4096x768 3.8 -> 3.4,
+// 100000x64 5.5 -> 4.8; but 2256x2640 5.6 -> 6.0, and 16384x1024 from memory 13.8 -> 14.7); not with so few rows that most of
+// a workgroup's are absent (1x2097152 9.9 -> 12.3).
+static bool copy_patches(const __half* x, int64_t rows, int64_t cols, int64_t ld, __half* q, __half* qT, hipStream_t st)
+{
+    const int64_t bx = (cols + 63) / 64, by = (rows + 255) / 256;
+    if(cols % 8 != 0 || !aligned16(x) || ld % 8 != 0 || !aligned16(q) || !aligned16(qT) || (qT && rows % 8 != 0)
+       || (!qT && (rows < 32 || rows * cols >= (int64_t(1) << (cols % 64 == 0 ? 23 : 21)))) || bx * by >= (int64_t(1) << 31))
+        return false;
+    copy_f16_patch_kernel<<<dim3(static_cast<unsigned>(bx * by)), dim3(kBlock), 0, st>>>(x, rows, cols, ld, q, qT, bx);
+    return true;
+}
+
 template <typename Ti, typename To>
 static hipError_t convert_typed(const void* x, int64_t rows, int64_t cols, int64_t ld, void* q, void* qT,
                                 hipStream_t st)
 {
-    if(convert_tiles(static_cast<const Ti*>(x), rows, cols, ld, nullptr, nullptr, static_cast<To*>(q), static_cast<To*>(qT), st))
+    if constexpr(std::is_same<Ti, __half>::value && std::is_same<To, __half>::value)
+        if(copy_patches(static_cast<const __half*>(x), rows, cols, ld, static_cast<__half*>(q), static_cast<__half*>(qT), st))
+            return hipGetLastError();
+    // columns of a binary16 copy that are no multiple of 16 bytes leave a tile of eight-row chunks element by element; the
+    // kernel below, a column per wavefront and store, is faster for large ones of some rows (10002x1032 binary16, transposed
+    // alone, 25.3 -> 17.7 us, fp32 28.6 -> 18.5, with both copies 30.7 -> 21.3; but 1569x320 4.7 -> 5.2, 9x262144 7.8 -> 10.2).
+    // binary16 with both copies gains in between only (30004x256 19.3 -> 15.3; 7001x304 from memory 9.7 -> 11.4, 10002x1032
+    // 28.7 -> 38.6)
+    const int64_t n   = rows * cols;
+    const bool    odd = std::is_same<To, __half>::value && qT && rows % 8 != 0 && rows >= 32
+                     && (std::is_same<Ti, float>::value || !q ? n >= (int64_t(1) << 21) : n >= (int64_t(1) << 22) && n < (int64_t(1) << 23));
+    if(!odd && convert_tiles(static_cast<const Ti*>(x), rows, cols, ld, nullptr, nullptr, static_cast<To*>(q), static_cast<To*>(qT), st))
         return hipGetLastError();
     const int64_t gx = (cols + 63) / 64, gy = (rows + 63) / 64;
     convert_kernel<Ti, To, false><<<dim3(static_cast<unsigned>(gx * gy)), dim3(kBlock), 0, st>>>(

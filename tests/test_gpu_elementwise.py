@@ -456,6 +456,24 @@ def test_absmax_quantize_all_zero_and_lower_bits():
     assert_bits_equal(host(qT), want.T, "transposed codes, 5 bits")
 
 
+@pytest.mark.parametrize("src", [torch.float16, torch.float32])
+@pytest.mark.parametrize("rows,cols,ld", [(8, 8, 8), (72, 64, 64), (248, 72, 88), (264, 136, 136), (4099, 8, 8), (8192, 1024, 1024),
+                                          (8200, 256, 264), (8201, 256, 256), (8191, 264, 264), (31, 67656, 67656), (16401, 256, 256)])
+def test_binary16_copies_by_every_route(src, rows, cols, ld):
+    """Row-major and transposed binary16 copies, alone and together: patches, tiles and single elements on both sides of
+    their limits (2^21 and 2^23 elements, whole and partial patches, row counts off 8), strided sources."""
+    say("binary16 copies", src, rows, cols, ld)
+    g = torch.Generator(device="cuda").manual_seed(rows + cols)
+    x = torch.randn(rows, ld, device="cuda", generator=g).to(src)
+    want = x[:, :cols].half()
+    for want_q, want_t in ((True, False), (False, True), (True, True)):
+        q = torch.full((rows, cols), 9.0, dtype=torch.float16, device="cuda") if want_q else None
+        qT = torch.full((cols, rows), 9.0, dtype=torch.float16, device="cuda") if want_t else None
+        Q.qsync_quantize(x, rows, cols, ld, Q.FP16, 0, 0, 0, 0, 0, None, q, qT)
+        assert q is None or torch.equal(q, want)
+        assert qT is None or torch.equal(qT, want.t())
+
+
 @pytest.mark.parametrize("rnd", ["nearest", "stochastic"])
 @pytest.mark.parametrize("rows,cols", [(1, 8), (1, 16384), (3, 65536), (15, 26216), (24, 336), (24, 344), (24, 680), (24, 688),
                                        (40, 4912), (40, 4920), (17, 23128), (17, 23136)])
