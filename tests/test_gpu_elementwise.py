@@ -121,7 +121,8 @@ def test_prepare_weights_equals_the_separate_calls(dt):
     """Fused weight preparation (row and column maxima in one pass, both sets of codes in another) against the
     oracle's per-row and per-column quantizations; shapes on the fused path (tile edges, more row tiles than groups) and off it."""
     rng = np.random.default_rng(42)
-    for (n, k) in [(64, 576), (1024, 4096), (4096, 1024), (3072, 768), (48, 40), (20, 24), (16, 8), (8208, 64), (4112, 136), (80, 264)]:
+    for (n, k) in [(64, 576), (1024, 4096), (4096, 1024), (3072, 768), (48, 40), (20, 24), (16, 8), (8208, 64), (4112, 136), (80, 264),
+                   (4096, 8), (8192, 8), (8192, 16), (8192, 128)]:
         say("prepare weights", dt.__name__, n, k)
         w = (rng.standard_normal((n, k)) * 0.02).astype(dt)
         w[rng.integers(0, n), :] = 0                       # an all-zero row: scale 1
