@@ -1627,7 +1627,7 @@ void set_gemm_persistent_mode(int mode) { g_persistent_mode = (mode == 0 || mode
 
 // Model of a tile shape's time; the constants are explained in plan_gemm.
 struct TileModel { double r1, rmax, ovh, cap; int occ; };
-static constexpr TileModel kTileModel[kNumTiles] = {{14.0, 15.8, 6.9, 2280.0, 1}, {8.3, 9.0, 4.2, 1900.0, 2}, {3.55, 5.48, 3.2, 2060.0, 4}};
+static constexpr TileModel kTileModel[kNumTiles] = {{14.0, 15.8, 7.5, 2280.0, 1}, {8.3, 9.0, 4.2, 1900.0, 2}, {3.55, 5.48, 3.2, 2060.0, 4}};
 // Row-major (TN) operands: a K tile takes twice the LDS fragment reads, and a 64-wide tile of int8 operands
 // loads 64-byte row pieces (binary16: 128 bytes, no penalty); fitted slow-down of the main loop per tile shape.
 static double tn_factor(int tile, int prec, bool tn)
