@@ -1829,19 +1829,21 @@ hipError_t launch_quantize_int8(const void* x, int xdt, int64_t rows, int64_t co
 
 // Per-tensor maximum, scales and codes of a contiguous tensor.  Up to kWholeBytes one launch, every workgroup of which
 // reads the whole tensor for its maximum (no workgroup waits for another); above that a launch that leaves one maximum
-// per block and the quantizing launch, which folds them.  Where the transposed copy of an odd row count goes one element per
-// thread, the two separate passes -- except for tensors so small that saving a launch outweighs it (nearest 100 x 80:
-// one launch 5.8 us, 6.1 apart; but 100 x 160 6.7 against 6.1, 45 x 1024 6.7 against 6.0; stochastic rounding, whose Philox blocks
-// the tile's absent rows cost as well, 36 x 344: 6.6 against 6.2), and from 192 K elements of 16 rows or more on, where
-// folding the maxima in the quantizer makes up for it (70 x 3744 7.5 against 8.4, 500 x 528 8.1 against 8.5).
+// per block and the quantizing launch, which folds them.  The transposed copy of an odd row count goes one element per
+// thread, in two separate passes, where that is faster: not up to kWholeBytes, where launched one by one a second launch
+// costs the host more (nearest, 45 x 1024 binary16: one launch 6.6 us, apart 8.5; 100 x 512 7.6 against 8.6; replayed from a
+// graph 6.7 against 6.5 and 7.9 against 6.5), except from 128 rows on (129 x 512: 9.1 against 8.7, from a graph 9.0 against
+// 6.6; 250 x 256 8.7 against 8.5), and not from 192 K elements of 16 rows or more on, where folding the maxima in the
+// quantizer makes up for it (70 x 3744 7.5 against 8.4, 500 x 528 8.1 against 8.5).
 template <typename T>
 static hipError_t absmax_quantize_typed(const T* x, int64_t rows, int64_t cols, int qmax, int rnd, uint64_t seed,
                                         uint64_t offset, float* scale, float* inv_scale, float* amax_opt, int8_t* q,
                                         int8_t* qT, void* workspace, hipStream_t st)
 {
     const int64_t n     = rows * cols;
-    const bool    apart = odd_transpose_generic(rows, n, qT) && n >= (int64_t(1) << (rnd == kStochastic ? 13 : 14))
-                       && (rows < 16 || n < (int64_t(3) << 16));
+    const bool    whole = n * static_cast<int64_t>(sizeof(T)) <= kWholeBytes;
+    const bool    apart = odd_transpose_generic(rows, n, qT) && (rows < 16 || n < (int64_t(3) << 16))
+                       && (!whole || (rows >= 128 && n >= (int64_t(1) << 15)));
     if(apart || !tile_ok(x, rows, cols, cols, q, qT))
     {
         hipError_t e = absmax_typed(x, rows, cols, cols, kPerTensor, static_cast<float>(qmax), scale, inv_scale, amax_opt,
@@ -1850,7 +1852,7 @@ static hipError_t absmax_quantize_typed(const T* x, int64_t rows, int64_t cols, 
         return quantize_typed(x, rows, cols, cols, qmax, kPerTensor, rnd, seed, offset, inv_scale, q, qT, st);
     }
     float* partial = reinterpret_cast<float*>(static_cast<uint8_t*>(workspace) + kCtrBytes);
-    if(rows * cols * static_cast<int64_t>(sizeof(T)) <= kWholeBytes)
+    if(whole)
     {
         const TensorScale ts{nullptr, nullptr, 0, scale, inv_scale, amax_opt};
         quantize_tensor_launch<T, kWhole>(x, rows, cols, cols, qmax, rnd, seed, offset, ts, q, qT, st);

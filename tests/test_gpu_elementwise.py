@@ -477,7 +477,8 @@ def test_binary16_copies_by_every_route(src, rows, cols, ld):
 
 @pytest.mark.parametrize("rnd", ["nearest", "stochastic"])
 @pytest.mark.parametrize("rows,cols", [(1, 8), (1, 16384), (3, 65536), (15, 26216), (24, 336), (24, 344), (24, 680), (24, 688),
-                                       (40, 4912), (40, 4920), (17, 23128), (17, 23136)])
+                                       (40, 4912), (40, 4920), (17, 23128), (17, 23136), (129, 248), (129, 256), (127, 264),
+                                       (24, 2728), (24, 2736)])
 def test_transposed_codes_of_odd_row_counts_by_every_route(rows, cols, rnd):
     """Row counts that are no multiple of 16, on both sides of each limit between one element per thread and tiles, and
     between one call's fused forms and the two separate passes: bits of the oracle either way."""
