@@ -148,7 +148,8 @@ int qsync_absmax_scale_static(const void* x, int xdt, int64_t rows, int64_t cols
  * bits, gran, rnd, seed, offset are ignored for FP16 / FP32 (except the stochastic FP16 case above).
  * Any shape and alignment is accepted; the vectorised path needs cols % 8 == 0 (% 4 for FP32), x and ld*sizeof(elem)
  * multiples of 16 bytes, q 16-byte aligned (8 for PER_TENSOR codes), and qT 16-byte aligned with rows % 16 == 0
- * (PER_TENSOR, FP16 and FP32: any other row count as well, at any alignment of qT).
+ * (PER_TENSOR, FP16 and FP32: any other row count as well, at any alignment of qT, except where one element per thread
+ * is faster: codes of fewer than 16 such rows or up to some 400 000 elements, large binary16 outputs).
  */
 int qsync_quantize(const void* x, int xdt, int64_t rows, int64_t cols, int64_t ld,
                    int tag, int bits, int gran, int rnd,
