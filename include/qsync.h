@@ -178,6 +178,21 @@ int qsync_absmax_quantize(const void* x, int xdt, int64_t rows, int64_t cols, in
 size_t qsync_absmax_quantize_workspace_bytes(int64_t rows, int64_t cols);
 
 /*
+ * qsync_gradient_quantize - qsync_absmax_scale (PER_TENSOR, with colsum) followed by qsync_quantize (tag INT8, PER_TENSOR) on a
+ * packed gradient [rows, cols]: scale, inverse scale, maximum, bias gradient and codes, with identical results except that the
+ * column sums of a small tensor (one launch) are added in another order.  Paper: Appendix, proof of Prop. 1 (gradient of a
+ * linear operator); Indicator section (stochastic rounding of the gradient).  The second pass over dy folds what the first one
+ * left per block, so no launch stands between them.
+ *
+ * colsum      out, cols floats, required; cols <= 2^19 (QSYNC_ERR_UNSUPPORTED otherwise).
+ * workspace   at least qsync_absmax_workspace_bytes(rows, cols, QSYNC_PER_TENSOR) bytes, under the rules of qsync_absmax_scale.
+ * Everything else as in the two calls.  Empty tensors: nothing is written.
+ */
+int qsync_gradient_quantize(const void* dy, int dydt, int64_t rows, int64_t cols, int bits, int rnd, uint64_t philox_seed,
+                            uint64_t philox_offset, float* scale, float* inv_scale, float* amax_opt, float* colsum, void* q_opt,
+                            void* qT_opt, void* workspace, size_t workspace_bytes, void* stream);
+
+/*
  * qsync_qlinear_fwd - forward GEMM with the dequantizer and bias fused into the epilogue.
  * Paper: proof of Prop. 2 (y = q_v q_w sum(v_q w_q) + b), Backend section "Dequantization
  * Fusion" (int32 accumulation, INT32 -> FP32 conversion with the scale in the epilogue),

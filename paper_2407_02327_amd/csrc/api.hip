@@ -190,6 +190,22 @@ int qsync_absmax_quantize(const void* x, int xdt, int64_t rows, int64_t cols, in
                                              workspace, static_cast<hipStream_t>(stream)));
 }
 
+int qsync_gradient_quantize(const void* dy, int dydt, int64_t rows, int64_t cols, int bits, int rnd, uint64_t philox_seed,
+                            uint64_t philox_offset, float* scale, float* inv_scale, float* amax_opt, float* colsum, void* q_opt,
+                            void* qT_opt, void* workspace, size_t workspace_bytes, void* stream)
+{
+    if(!dy || !scale || !inv_scale || !colsum || (!q_opt && !qT_opt)) return QSYNC_ERR_NULL;
+    if(!is_float_dtype(dydt) || !is_round(rnd)) return QSYNC_ERR_BAD_ENUM;
+    if(!count_ok(rows, cols)) return QSYNC_ERR_BAD_SHAPE;
+    if(bits < 2 || bits > 8 || cols > (int64_t(1) << 19)) return QSYNC_ERR_UNSUPPORTED;
+    if(rows == 0 || cols == 0) return QSYNC_OK;
+    if(!workspace || workspace_bytes < qsync_absmax_workspace_bytes(rows, cols, QSYNC_PER_TENSOR)) return QSYNC_ERR_WORKSPACE;
+    if(!aligned16(workspace)) return QSYNC_ERR_ALIGN;
+    return hip_status(launch_gradient_quantize(dy, dydt, rows, cols, (1 << (bits - 1)) - 1, rnd, philox_seed, philox_offset, scale,
+                                               inv_scale, amax_opt, colsum, static_cast<int8_t*>(q_opt), static_cast<int8_t*>(qT_opt),
+                                               workspace, static_cast<hipStream_t>(stream)));
+}
+
 size_t qsync_qlinear_workspace_bytes(int tag, int64_t M, int64_t N, int64_t K)
 {
     if(!is_tag(tag) || M < 0 || N < 0 || K < 0) return 0;

@@ -35,6 +35,33 @@ __device__ __forceinline__ void write_scale(float amax, float qmax, float* scale
     if(amax_opt) amax_opt[i] = amax;
 }
 
+// ------------------------------------------------------------------ parts
+// A part is the work of one kernel as a value: its arguments and `run(block, lds)`, for workgroups of kThreads threads and
+// kLds bytes of LDS.  It is launched by itself (part_kernel) or beside an independent one (two_parts_kernel: the first `na`
+// workgroups are a's).  What bounds the small conversions is the launch: a kernel that does nothing takes 2.1 us in a
+// replayed graph and 2.7 us of the host otherwise, and few of them fill the chip, so parts that do not wait for each
+// other share one.
+template <typename P> __global__ __launch_bounds__(P::kThreads) void part_kernel(const P p)
+{
+    __shared__ __attribute__((aligned(16))) uint8_t lds[P::kLds];
+    p.run(blockIdx.x, lds);
+}
+template <typename A, typename B> __global__ __launch_bounds__(A::kThreads) void two_parts_kernel(const A a, const B b, const uint32_t na)
+{
+    static_assert(A::kThreads == B::kThreads, "one workgroup size");
+    __shared__ __attribute__((aligned(16))) uint8_t lds[A::kLds > B::kLds ? A::kLds : B::kLds];
+    if(blockIdx.x < na) a.run(blockIdx.x, lds);
+    else                b.run(blockIdx.x - na, lds);
+}
+template <typename P> void launch_part(const P& p, int64_t blocks, hipStream_t st)
+{
+    part_kernel<P><<<dim3(static_cast<unsigned>(blocks)), dim3(P::kThreads), 0, st>>>(p);
+}
+template <typename A, typename B> void launch_parts(const A& a, int64_t blocks_a, const B& b, int64_t blocks_b, hipStream_t st)
+{
+    two_parts_kernel<A, B><<<dim3(static_cast<unsigned>(blocks_a + blocks_b)), dim3(A::kThreads), 0, st>>>(a, b, static_cast<uint32_t>(blocks_a));
+}
+
 // Running maximum of |x| over 16-byte vectors.  binary16 magnitudes order like their bit
 // patterns with the sign bit cleared, so for binary16 the maximum runs on packed 16-bit
 // integers (two elements per VALU operation) and is widened to fp32 once at the end.
@@ -433,6 +460,25 @@ __global__ __launch_bounds__(BLOCK) void colreduce_kernel(const T* __restrict__ 
 // Second launch of the two-launch form: 16 columns per block; sixteen threads per column fold a
 // sixteenth of the partials each (fixed assignment, fixed order), then the sixteen are folded in order.
 // OP_SUMMAX: the last block folds the `nmax` block maxima (and sums of squares) of the tensor instead.
+template <int OP> __device__ __forceinline__ float fold_column(const float* __restrict__ partial, int S, int64_t cols, int64_t c, int q, float* lds)
+{   // (the first 256 threads; the result is valid in those with q == 0)
+    float acc = 0.0f;
+    if(c < cols && threadIdx.x < kBlock)
+    {
+#pragma unroll 8                              // independent loads in flight; the fold keeps its order
+        for(int s = q; s < S; s += 16)
+        {
+            const float o = partial[static_cast<int64_t>(s) * cols + c];
+            acc = OP == OP_MAX ? fmaxf(acc, o) : acc + o;
+        }
+    }
+    if(threadIdx.x < kBlock) lds[threadIdx.x] = acc;
+    __syncthreads();
+    float t = 0.0f;
+    if(q == 0)
+        for(int i = 0; i < 16; ++i) t = OP == OP_MAX ? fmaxf(t, lds[i * 16 + threadIdx.x % 16]) : t + lds[i * 16 + threadIdx.x % 16];
+    return t;
+}
 template <int OP>
 __global__ __launch_bounds__(kBlock) void colreduce_finalize_kernel(const float* __restrict__ partial, int S,
                                                                     int64_t cols, float qmax, float* out,
@@ -454,28 +500,60 @@ __global__ __launch_bounds__(kBlock) void colreduce_finalize_kernel(const float*
         }
     const int     tc = threadIdx.x % 16, q = threadIdx.x / 16;
     const int64_t c  = static_cast<int64_t>(blockIdx.x) * 16 + tc;
-    float         acc = 0.0f;
-    if(c < cols)
-    {
-#pragma unroll 8                              // independent loads in flight; the fold keeps its order
-        for(int s = q; s < S; s += 16)
-        {
-            const float o = partial[static_cast<int64_t>(s) * cols + c];
-            acc = OP == OP_MAX ? fmaxf(acc, o) : acc + o;
-        }
-    }
-    lds[threadIdx.x] = acc;
-    __syncthreads();
+    const float   t  = fold_column<OP>(partial, S, cols, c, q, lds);
     if(q == 0 && c < cols)
     {
-        float t = 0.0f;
-        for(int i = 0; i < 16; ++i) t = OP == OP_MAX ? fmaxf(t, lds[i * 16 + tc]) : t + lds[i * 16 + tc];
         if(OP == OP_MAX)
             write_scale(t, qmax, out, inv_scale, amax_opt, c);
         else
             out[c] = t;
     }
 }
+
+// The fold of the column sums beside the pass that needs the block maxima.
+template <int THREADS> struct ColumnFold
+{
+    static constexpr int kThreads = THREADS, kLds = kBlock * 4;
+    const float* partial;
+    int          S;
+    int64_t      cols;
+    float*       out;
+    __device__ __forceinline__ void run(uint32_t block, uint8_t* lds) const
+    {
+        const int     q = threadIdx.x / 16;
+        const int64_t c = static_cast<int64_t>(block) * 16 + threadIdx.x % 16;
+        const float   t = fold_column<OP_SUM>(partial, S, cols, c, q, reinterpret_cast<float*>(lds));
+        if(q == 0 && c < cols) out[c] = t;
+    }
+};
+
+// Column sums of a small tensor in one go: 16 columns per workgroup, THREADS / 16 row lanes (at most kColumnSumRows rows: their
+// loads are all in flight at once), folded in order.
+constexpr int64_t kColumnSumRows = 512;
+template <typename T, int THREADS> struct ColumnSum
+{
+    static constexpr int kThreads = THREADS, kLds = THREADS * 4;
+    const T* x;
+    int64_t  rows, cols;
+    float*   out;
+    __device__ __forceinline__ void run(uint32_t block, uint8_t* lds) const
+    {
+        constexpr int LANES = THREADS / 16;
+        float*        part = reinterpret_cast<float*>(lds);
+        const int     tc = threadIdx.x % 16, q = threadIdx.x / 16;
+        const int64_t c   = static_cast<int64_t>(block) * 16 + tc;
+        float         acc = 0.0f;
+        if(c < cols)
+#pragma unroll 8
+            for(int64_t r = q; r < rows; r += LANES) acc += to_f32(x[r * cols + c]);
+        part[threadIdx.x] = acc;
+        __syncthreads();
+        if(q != 0 || c >= cols) return;
+        float t = 0.0f;
+        for(int i = 0; i < LANES; ++i) t += part[i * 16 + tc];
+        out[c] = t;
+    }
+};
 
 // ------------------------------------------------------------------ INT8 quantize, tiled through LDS
 // A workgroup owns a tile of TR rows x 128 columns, a thread four rows x eight columns of it (one Philox block per
@@ -500,9 +578,8 @@ template <int THREADS> __device__ __forceinline__ float block_max_all(float v, f
 }
 
 // Where a per-tensor quantizer takes its scale from.  kInv: the inverse scale in memory.  kPartials: block maxima of
-// an earlier launch, folded by every workgroup (at most kFoldMax of them: a load or two per thread, hidden behind the
-// tile's own loads), which saves the maximum pass its arrival counter -- 5 us of dependent device-scope round trips --
-// and this pass a launch between them.  kWhole: the workgroup finds the maximum of the whole tensor by itself.
+// an earlier launch, folded by every workgroup (a few loads per thread, hidden behind the tile's own loads), which saves the
+// maximum pass its arrival counter -- 5 us of dependent device-scope round trips -- and this pass a launch between them.  kWhole: the workgroup finds the maximum of the whole tensor by itself.
 enum ScaleFrom { kInv = 0, kPartials = 1, kWhole = 2 };
 constexpr int     kFoldMax    = 256;
 constexpr int64_t kWholeBytes = 128 << 10;      // largest tensor of kWhole
@@ -519,12 +596,13 @@ struct TensorScale
 // The inverse scale of the tensor in every thread (contains barriers; lds: THREADS / 64 floats).
 template <typename T, int SRC, int THREADS>
 __device__ __forceinline__ float tensor_inverse_scale(const TensorScale& ts, const T* __restrict__ x, int64_t n, int qmax,
-                                                      float* lds)
+                                                      uint32_t block, float* lds)
 {
     if constexpr(SRC == kInv) return ts.inv[0];
     float m = 0.0f;
     if constexpr(SRC == kPartials)
     {
+#pragma unroll 4
         for(int i = threadIdx.x; i < ts.n; i += THREADS) m = fmaxf(m, ts.partial[i]);
     }
     else
@@ -544,7 +622,7 @@ __device__ __forceinline__ float tensor_inverse_scale(const TensorScale& ts, con
         m = rm.get();
     }
     m = block_max_all<THREADS>(m, lds);
-    if(blockIdx.x == 0 && threadIdx.x == 0) write_scale(m, static_cast<float>(qmax), ts.scale, ts.inv_out, ts.amax_opt, 0);
+    if(block == 0 && threadIdx.x == 0) write_scale(m, static_cast<float>(qmax), ts.scale, ts.inv_out, ts.amax_opt, 0);
     return m != 0.0f ? __fdiv_rn(static_cast<float>(qmax), m) : 1.0f;
 }
 
@@ -647,38 +725,45 @@ __device__ __forceinline__ void store_transposed_tile(const uint32_t (&t)[8], ui
 
 // Per-tensor scale.  Needs cols % 8 == 0, 16-byte aligned rows of x, 8-byte aligned q; qT 16-byte aligned when
 // rows % 16 == 0 (any alignment and byte stores otherwise).
-template <typename T, int RND, int TR, int SRC>
-__global__ __launch_bounds__(TR * 4) void quantize_tile_kernel(const T* __restrict__ x, int64_t rows, int64_t cols, int64_t ld,
-                                                               int qmax, uint64_t seed, uint64_t offset, const TensorScale ts,
-                                                               int8_t* __restrict__ q, int8_t* __restrict__ qT, int tiles_x)
+template <typename T, int RND, int TR, int SRC> struct QuantizeTile
 {
-    __shared__ __attribute__((aligned(16))) uint8_t lds_t[TR * kTileCols];
-    __shared__ float lds_m[TR * 4 / kWaveSize];
-    const int     by = static_cast<int>(blockIdx.x) / tiles_x, bx = static_cast<int>(blockIdx.x) - by * tiles_x;
-    const int64_t tile_r = static_cast<int64_t>(by) * TR, tile_c = static_cast<int64_t>(bx) * kTileCols;
-    const int64_t r0 = tile_r + (threadIdx.x / 16) * 4, c0 = tile_c + (threadIdx.x % 16) * 8;
-    TileShare<T>  s;
-    s.load(x, r0, c0, rows, cols, ld);
-    const float   inv = tensor_inverse_scale<T, SRC, TR * 4>(ts, x, rows * cols, qmax, lds_m);
-    uint32_t      code[4][2];
-#pragma unroll
-    for(int i = 0; i < 4; ++i)
+    static constexpr int kThreads = TR * 4, kLds = TR * kTileCols + kThreads / kWaveSize * 4;
+    const T*    x;
+    int64_t     rows, cols, ld;
+    int         qmax;
+    uint64_t    seed, offset;
+    TensorScale ts;
+    int8_t*     q;
+    int8_t*     qT;
+    int         tiles_x;
+    __device__ __forceinline__ void run(uint32_t block, uint8_t* lds) const
     {
-        float v[8];
-        s.decode(i, v);
-        uint4 blk = {0u, 0u, 0u, 0u};
-        if(RND == kStochastic) blk = philox_group(seed, offset, static_cast<uint64_t>((r0 + i) * cols + c0) >> 3);
-        code[i][0] = code[i][1] = 0u;
+        const int     by = static_cast<int>(block) / tiles_x, bx = static_cast<int>(block) - by * tiles_x;
+        const int64_t tile_r = static_cast<int64_t>(by) * TR, tile_c = static_cast<int64_t>(bx) * kTileCols;
+        const int64_t r0 = tile_r + (threadIdx.x / 16) * 4, c0 = tile_c + (threadIdx.x % 16) * 8;
+        TileShare<T>  s;
+        s.load(x, r0, c0, rows, cols, ld);
+        const float   inv = tensor_inverse_scale<T, SRC, kThreads>(ts, x, rows * cols, qmax, block, reinterpret_cast<float*>(lds + TR * kTileCols));
+        uint32_t      code[4][2];
 #pragma unroll
-        for(int j = 0; j < 8; ++j)
-            code[i][j / 4] |= (static_cast<uint32_t>(quantize_code<RND>(v[j], inv, qmax, philox_draw16(blk, j))) & 0xFFu) << (8 * (j % 4));
-        if(q && r0 + i < rows && c0 < cols) *reinterpret_cast<uint2*>(q + (r0 + i) * cols + c0) = make_uint2(code[i][0], code[i][1]);
+        for(int i = 0; i < 4; ++i)
+        {
+            float v[8];
+            s.decode(i, v);
+            uint4 blk = {0u, 0u, 0u, 0u};
+            if(RND == kStochastic) blk = philox_group(seed, offset, static_cast<uint64_t>((r0 + i) * cols + c0) >> 3);
+            code[i][0] = code[i][1] = 0u;
+#pragma unroll
+            for(int j = 0; j < 8; ++j)
+                code[i][j / 4] |= (static_cast<uint32_t>(quantize_code<RND>(v[j], inv, qmax, philox_draw16(blk, j))) & 0xFFu) << (8 * (j % 4));
+            if(q && r0 + i < rows && c0 < cols) *reinterpret_cast<uint2*>(q + (r0 + i) * cols + c0) = make_uint2(code[i][0], code[i][1]);
+        }
+        if(!qT) return;
+        uint32_t t[8];
+        transpose_codes_4x8(code, t);
+        store_transposed_tile<TR>(t, lds, tile_r, tile_c, rows, cols, qT, [](int64_t c) { return c; });
     }
-    if(!qT) return;
-    uint32_t t[8];
-    transpose_codes_4x8(code, t);
-    store_transposed_tile<TR>(t, lds_t, tile_r, tile_c, rows, cols, qT, [](int64_t c) { return c; });
-}
+};
 
 // ------------------------------------------------------------------ weights: two quantizations in two launches
 // The forward wants codes with one scale per row, dX transposed codes with one scale per column.  The first launch
@@ -975,52 +1060,58 @@ __global__ __launch_bounds__(kBlock, 3) void quantize_patch_kernel(const T* __re
 // Contiguous tensor, one scale, no transposed copy: nothing ties a lane to a patch, so the lanes of a wavefront take
 // adjacent groups of 8 elements (one Philox block each; a load instruction of a wavefront covers 1 KB of consecutive
 // memory for binary16 input) with U groups in flight per lane, and the 8 codes of a group leave as one 8-byte store.
-template <typename T, int RND, int SRC>
-__global__ __launch_bounds__(kBlock) void quantize_stream_kernel(const T* __restrict__ x, int64_t ngroups, int qmax,
-                                                                 uint64_t seed, uint64_t offset, const TensorScale ts,
-                                                                 int8_t* __restrict__ q)
+template <typename T, int RND, int SRC> struct QuantizeStream
 {
-    __shared__ float lds_m[kBlock / kWaveSize];
-    constexpr int E  = Vec16<T>::N;       // elements per 16-byte load (8 or 4)
-    constexpr int VG = 8 / E;             // loads per group
-    constexpr int U  = 4;
-    const uint4*  xv = reinterpret_cast<const uint4*>(x);
-    const int64_t g0 = static_cast<int64_t>(blockIdx.x) * (kBlock * U) + threadIdx.x;
-    uint4         raw[U][VG];
-#pragma unroll
-    for(int u = 0; u < U; ++u)
+    static constexpr int kThreads = kBlock, kLds = kBlock / kWaveSize * 4;
+    const T*    x;
+    int64_t     ngroups;
+    int         qmax;
+    uint64_t    seed, offset;
+    TensorScale ts;
+    int8_t*     q;
+    __device__ __forceinline__ void run(uint32_t block, uint8_t* lds) const
     {
-        const int64_t g = g0 + u * kBlock;
+        constexpr int E  = Vec16<T>::N;       // elements per 16-byte load (8 or 4)
+        constexpr int VG = 8 / E;             // loads per group
+        constexpr int U  = 4;
+        const uint4*  xv = reinterpret_cast<const uint4*>(x);
+        const int64_t g0 = static_cast<int64_t>(block) * (kBlock * U) + threadIdx.x;
+        uint4         raw[U][VG];
 #pragma unroll
-        for(int l = 0; l < VG; ++l) raw[u][l] = g < ngroups ? xv[g * VG + l] : make_uint4(0, 0, 0, 0);
-    }
-    const float f = tensor_inverse_scale<T, SRC, kBlock>(ts, x, ngroups * 8, qmax, lds_m);
-#pragma unroll
-    for(int u = 0; u < U; ++u)
-    {
-        const int64_t g = g0 + u * kBlock;
-        if(g >= ngroups) continue;
-        float v[8];
-#pragma unroll
-        for(int l = 0; l < VG; ++l)
+        for(int u = 0; u < U; ++u)
         {
-            float t[E];
-            Vec16<T>::decode(raw[u][l], t);
+            const int64_t g = g0 + u * kBlock;
 #pragma unroll
-            for(int e = 0; e < E; ++e) v[l * E + e] = t[e];
+            for(int l = 0; l < VG; ++l) raw[u][l] = g < ngroups ? xv[g * VG + l] : make_uint4(0, 0, 0, 0);
         }
-        uint4 blk = {0u, 0u, 0u, 0u};
-        if(RND == kStochastic) blk = philox_group(seed, offset, static_cast<uint64_t>(g));
-        uint32_t w[2] = {0u, 0u};
+        const float f = tensor_inverse_scale<T, SRC, kBlock>(ts, x, ngroups * 8, qmax, block, reinterpret_cast<float*>(lds));
 #pragma unroll
-        for(int j = 0; j < 8; ++j)
+        for(int u = 0; u < U; ++u)
         {
-            const int c = quantize_code<RND>(v[j], f, qmax, philox_draw16(blk, j));
-            w[j / 4] |= (static_cast<uint32_t>(c) & 0xFFu) << (8 * (j % 4));
+            const int64_t g = g0 + u * kBlock;
+            if(g >= ngroups) continue;
+            float v[8];
+#pragma unroll
+            for(int l = 0; l < VG; ++l)
+            {
+                float t[E];
+                Vec16<T>::decode(raw[u][l], t);
+#pragma unroll
+                for(int e = 0; e < E; ++e) v[l * E + e] = t[e];
+            }
+            uint4 blk = {0u, 0u, 0u, 0u};
+            if(RND == kStochastic) blk = philox_group(seed, offset, static_cast<uint64_t>(g));
+            uint32_t w[2] = {0u, 0u};
+#pragma unroll
+            for(int j = 0; j < 8; ++j)
+            {
+                const int c = quantize_code<RND>(v[j], f, qmax, philox_draw16(blk, j));
+                w[j / 4] |= (static_cast<uint32_t>(c) & 0xFFu) << (8 * (j % 4));
+            }
+            *reinterpret_cast<uint2*>(q + g * 8) = make_uint2(w[0], w[1]);
         }
-        *reinterpret_cast<uint2*>(q + g * 8) = make_uint2(w[0], w[1]);
     }
-}
+};
 
 // Any shape, any alignment: one element per thread.
 template <typename T>
@@ -1536,15 +1627,15 @@ void colreduce_shape(int64_t rows, int64_t cols, int E, int block, int& tpr, int
 // Workspace of the per-tensor reductions: the arrival counter first (a 256-byte slot), partials behind it.
 constexpr size_t kCtrBytes = 256;
 
+// The pass over x; `gy` partials per column, `nmax` block maxima.
 template <typename T, int OP>
-hipError_t colreduce_launch(const T* x, int64_t rows, int64_t cols, int64_t ld, float qmax, float* out,
-                            float* inv_scale, float* amax_opt, float* partial, float* partial_max, TensorFinal tfin,
-                            hipStream_t st)
+void colreduce_first(const T* x, int64_t rows, int64_t cols, int64_t ld, float* partial, float* partial_max, const TensorFinal& tfin,
+                     int& gy, int& nmax, hipStream_t st)
 {
     constexpr int E     = Vec16<T>::N;
     const bool    vec   = aligned16(x) && (ld * sizeof(T)) % 16 == 0 && cols % E == 0;
     const int     block = rows * cols >= (int64_t(1) << 20) ? 1024 : kBlock;
-    int           tpr, gy;
+    int           tpr;
     colreduce_shape(rows, cols, vec ? E : 1, block, tpr, gy);
     const int64_t ncv = (cols + (vec ? E : 1) - 1) / (vec ? E : 1);
     const int64_t gx  = (ncv + tpr - 1) / tpr;
@@ -1565,8 +1656,18 @@ hipError_t colreduce_launch(const T* x, int64_t rows, int64_t cols, int64_t ld, 
         else
             colreduce_kernel<T, false, OP, kBlock><<<grid, dim3(kBlock), 0, st>>>(x, rows, cols, ld, tpr, partial, partial_max, tfin);
     }
+    nmax = static_cast<int>(gx * gy);
+}
+
+template <typename T, int OP>
+hipError_t colreduce_launch(const T* x, int64_t rows, int64_t cols, int64_t ld, float qmax, float* out,
+                            float* inv_scale, float* amax_opt, float* partial, float* partial_max, TensorFinal tfin,
+                            hipStream_t st)
+{
+    int gy, nmax;
+    colreduce_first<T, OP>(x, rows, cols, ld, partial, partial_max, tfin, gy, nmax, st);
     colreduce_finalize_kernel<OP><<<dim3((cols + 15) / 16 + (OP == OP_SUMMAX ? 1 : 0)), dim3(kBlock), 0, st>>>(
-        partial, gy, cols, qmax, out, inv_scale, amax_opt, partial_max, static_cast<int>(gx * gy), tfin);
+        partial, gy, cols, qmax, out, inv_scale, amax_opt, partial_max, nmax, tfin);
     return hipGetLastError();
 }
 
@@ -1745,7 +1846,7 @@ static int64_t tiles_of(int64_t rows, int64_t cols, int tr) { return ((rows + tr
 template <typename T> static bool tile_ok(const T* x, int64_t rows, int64_t cols, int64_t ld, const int8_t* q, const int8_t* qT)
 {
     return cols % 8 == 0 && aligned16(x) && (ld * sizeof(T)) % 16 == 0 && (reinterpret_cast<uintptr_t>(q) & 7) == 0
-        && (rows % 16 != 0 || aligned16(qT)) && tiles_of(rows, cols, 64) < (int64_t(1) << 31);
+        && (rows % 16 != 0 || aligned16(qT)) && tiles_of(rows, cols, 64) < (int64_t(1) << 30);
 }
 
 // A row count that is no multiple of 16 leaves the columns of the transposed copy unaligned, and the tile kernel then
@@ -1758,15 +1859,15 @@ static bool odd_transpose_generic(int64_t rows, int64_t n, const int8_t* qT)
     return qT && rows % 16 != 0 && (rows < 16 || n < (int64_t(3) << 17));
 }
 
-// Per-tensor codes of a tensor that meets tile_ok: the streaming kernel when only row-major codes of a contiguous tensor
-// are wanted, tiles otherwise.  Tiles are 128 rows high (whole 128-byte lines of the transposed copy) once that gives
-// every compute unit two workgroups, 64 rows below.
-template <typename T, int SRC>
-static void quantize_tensor_launch(const T* x, int64_t rows, int64_t cols, int64_t ld, int qmax, int rnd, uint64_t seed,
-                                   uint64_t offset, const TensorScale& ts, int8_t* q, int8_t* qT, hipStream_t st)
+// Per-tensor codes of a tensor that meets tile_ok, as parts: f(part, workgroups).  Streaming when only row-major codes of a
+// contiguous tensor are wanted, tiles otherwise.  Tiles are 128 rows high (whole 128-byte lines of the transposed copy)
+// once that gives every compute unit two workgroups, 64 rows below.
+template <typename T, int SRC, typename F>
+static void with_quantize_part(const T* x, int64_t rows, int64_t cols, int64_t ld, int qmax, int rnd, uint64_t seed, uint64_t offset,
+                               const TensorScale& ts, int8_t* q, int8_t* qT, F&& f)
 {
     const int64_t ngroups = rows * cols / 8, stream_blocks = (ngroups + kBlock * 4 - 1) / (kBlock * 4);
-    const bool    stream  = SRC != kWhole && q && !qT && ld == cols && stream_blocks < (int64_t(1) << 31);
+    const bool    stream  = SRC != kWhole && q && !qT && ld == cols && stream_blocks < (int64_t(1) << 30);
     const int     tiles_x = static_cast<int>((cols + kTileCols - 1) / kTileCols);
     with_rounding(rnd, [&](auto r) {
         constexpr int RND = decltype(r)::value;
@@ -1774,19 +1875,23 @@ static void quantize_tensor_launch(const T* x, int64_t rows, int64_t cols, int64
         {
             if(stream)
             {
-                quantize_stream_kernel<T, RND, SRC><<<dim3(static_cast<unsigned>(stream_blocks)), dim3(kBlock), 0, st>>>(x, ngroups, qmax, seed, offset, ts, q);
+                f(QuantizeStream<T, RND, SRC>{x, ngroups, qmax, seed, offset, ts, q}, stream_blocks);
                 return;
             }
             if(tiles_of(rows, cols, 128) < 512)
             {
-                quantize_tile_kernel<T, RND, 64, SRC><<<dim3(static_cast<unsigned>(tiles_of(rows, cols, 64))), dim3(256), 0, st>>>(
-                    x, rows, cols, ld, qmax, seed, offset, ts, q, qT, tiles_x);
+                f(QuantizeTile<T, RND, 64, SRC>{x, rows, cols, ld, qmax, seed, offset, ts, q, qT, tiles_x}, tiles_of(rows, cols, 64));
                 return;
             }
         }
-        quantize_tile_kernel<T, RND, 128, SRC><<<dim3(static_cast<unsigned>(tiles_of(rows, cols, 128))), dim3(512), 0, st>>>(
-            x, rows, cols, ld, qmax, seed, offset, ts, q, qT, tiles_x);
+        f(QuantizeTile<T, RND, 128, SRC>{x, rows, cols, ld, qmax, seed, offset, ts, q, qT, tiles_x}, tiles_of(rows, cols, 128));
     });
+}
+template <typename T, int SRC>
+static void quantize_tensor_launch(const T* x, int64_t rows, int64_t cols, int64_t ld, int qmax, int rnd, uint64_t seed,
+                                   uint64_t offset, const TensorScale& ts, int8_t* q, int8_t* qT, hipStream_t st)
+{
+    with_quantize_part<T, SRC>(x, rows, cols, ld, qmax, rnd, seed, offset, ts, q, qT, [&](const auto& p, int64_t blocks) { launch_part(p, blocks, st); });
 }
 
 template <typename T>
@@ -1880,6 +1985,54 @@ hipError_t launch_absmax_quantize(const void* x, int xdt, int64_t rows, int64_t 
                                      amax_opt, q, qT, workspace, stream);
     return absmax_quantize_typed(static_cast<const __half*>(x), rows, cols, qmax, rnd, seed, offset, scale, inv_scale,
                                  amax_opt, q, qT, workspace, stream);
+}
+
+// Maximum, scales, column sums and codes of a gradient: the pass that leaves block maxima and column partials, then a launch
+// that converts and, in workgroups of its own, folds the partials.  A tensor of at most kWholeBytes takes one launch.
+// Bound by the launches when small.  Three launches -> two, whole steps: 4096x3072x768 92.6 -> 90.6 us, 1808x1040x784 52.7 ->
+// 50.9; -> one: 64x128x128 35.7 -> 28.7.
+template <typename T>
+static hipError_t gradient_quantize_typed(const T* x, int64_t rows, int64_t cols, int qmax, int rnd, uint64_t seed, uint64_t offset,
+                                          float* scale, float* inv_scale, float* amax_opt, float* colsum, int8_t* q, int8_t* qT,
+                                          void* workspace, hipStream_t st)
+{
+    const int64_t n = rows * cols, fold_blocks = (cols + 15) / 16;
+    if(!tile_ok(x, rows, cols, cols, q, qT) || odd_transpose_generic(rows, n, qT))
+    {
+        hipError_t e = absmax_typed(x, rows, cols, cols, kPerTensor, static_cast<float>(qmax), scale, inv_scale, amax_opt, colsum, nullptr,
+                                    workspace, st);
+        if(e != hipSuccess) return e;
+        return quantize_typed(x, rows, cols, cols, qmax, kPerTensor, rnd, seed, offset, inv_scale, q, qT, st);
+    }
+    if(n * static_cast<int64_t>(sizeof(T)) <= kWholeBytes && rows <= kColumnSumRows)
+    {
+        const TensorScale ts{nullptr, nullptr, 0, scale, inv_scale, amax_opt};
+        with_quantize_part<T, kWhole>(x, rows, cols, cols, qmax, rnd, seed, offset, ts, q, qT, [&](const auto& p, int64_t blocks) {
+            launch_parts(p, blocks, ColumnSum<T, std::decay_t<decltype(p)>::kThreads>{x, rows, cols, colsum}, fold_blocks, st);
+        });
+        return hipGetLastError();
+    }
+    float* maxima  = reinterpret_cast<float*>(static_cast<uint8_t*>(workspace) + kCtrBytes);
+    float* partial = maxima + 2 * kAbsmaxMaxBlocks;
+    const TensorFinal none{0.0f, nullptr, nullptr, nullptr, nullptr, nullptr};
+    int gy, nmax;
+    colreduce_first<T, OP_SUMMAX>(x, rows, cols, cols, partial, maxima, none, gy, nmax, st);
+    const TensorScale ts{nullptr, maxima, nmax, scale, inv_scale, amax_opt};
+    with_quantize_part<T, kPartials>(x, rows, cols, cols, qmax, rnd, seed, offset, ts, q, qT, [&](const auto& p, int64_t blocks) {
+        launch_parts(ColumnFold<std::decay_t<decltype(p)>::kThreads>{partial, gy, cols, colsum}, fold_blocks, p, blocks, st);
+    });
+    return hipGetLastError();
+}
+
+hipError_t launch_gradient_quantize(const void* x, int xdt, int64_t rows, int64_t cols, int qmax, int rnd, uint64_t seed, uint64_t offset,
+                                    float* scale, float* inv_scale, float* amax_opt, float* colsum, int8_t* q, int8_t* qT,
+                                    void* workspace, hipStream_t stream)
+{
+    if(xdt == kF32)
+        return gradient_quantize_typed(static_cast<const float*>(x), rows, cols, qmax, rnd, seed, offset, scale, inv_scale, amax_opt,
+                                       colsum, q, qT, workspace, stream);
+    return gradient_quantize_typed(static_cast<const __half*>(x), rows, cols, qmax, rnd, seed, offset, scale, inv_scale, amax_opt, colsum,
+                                   q, qT, workspace, stream);
 }
 
 // Weights of one linear operator in one go: per-row scales and codes for the forward, per-column scales

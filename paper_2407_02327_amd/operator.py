@@ -174,11 +174,9 @@ class QLinear:
         if self.bwd_tag != self.tag:
             return          # the FP16 backward converts its operands inside its own call (gemm_bwd)
         if self.tag == Q.INT8:
-            # the same pass over dY yields its absmax and the bias gradient db (column sums)
-            Q.qsync_absmax_scale(dy, M, N, N, Q.PER_TENSOR, self.bits, self.sdy, self.idy, self.ady, self.db,
-                                 self.ws_absmax, stream)
-            Q.qsync_quantize(dy, M, N, N, Q.INT8, self.bits, Q.PER_TENSOR, self.dy_round, self.seed, self.offset,
-                             self.idy, self.dyq, self._dyqT, stream)
+            # maximum, bias gradient db (column sums) and codes
+            Q.qsync_gradient_quantize(dy, M, N, self.bits, self.dy_round, self.seed, self.offset, self.sdy, self.idy, self.ady,
+                                      self.db, self.dyq, self._dyqT, self.ws_absmax, stream)
             self.last_dy_offset = self.offset
             self.offset += (M * N + 7) // 8
         elif dy.dtype == _TORCH_OF_TAG[self.tag] and dy.is_contiguous() and not self.own_copies:
@@ -390,9 +388,8 @@ class QConv3x3:
     def convert_dy(self, dy: torch.Tensor, stream=None) -> None:
         M, N = self.M, self.N
         if self.tag == Q.INT8:
-            Q.qsync_absmax_scale(dy, M, N, N, Q.PER_TENSOR, self.bits, self.sdy, self.idy, self.ady, self.db, self.ws_absmax, stream)
-            Q.qsync_quantize(dy, M, N, N, Q.INT8, self.bits, Q.PER_TENSOR, self.dy_round, self.seed, self.offset,
-                             self.idy, self.dyq, self.dyqT, stream)
+            Q.qsync_gradient_quantize(dy, M, N, self.bits, self.dy_round, self.seed, self.offset, self.sdy, self.idy, self.ady,
+                                      self.db, self.dyq, self.dyqT, self.ws_absmax, stream)
             self.offset += (M * N + 7) // 8
         elif dy.dtype == _TORCH_OF_TAG[self.tag] and dy.is_contiguous():
             self.dyq = dy

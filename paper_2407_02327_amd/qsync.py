@@ -36,6 +36,7 @@ SIGNATURES = {
     "qsync_qlinear_fwd": (_i, [_i, _i64, _i64, _i64, _vp, _vp, _vp, _vp, _i, _vp, _vp, _i, _vp, _vp, _sz, _vp]),
     "qsync_absmax_quantize": (_i, [_vp, _i, _i64, _i64, _i, _i, ctypes.c_uint64, ctypes.c_uint64, _vp, _vp, _vp, _vp, _vp,
                                    _vp, _sz, _i, _vp]),
+    "qsync_gradient_quantize": (_i, [_vp, _i, _i64, _i64, _i, _i, _u64, _u64, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _sz, _vp]),
     "qsync_absmax_quantize_workspace_bytes": (_sz, [_i64, _i64]),
     "qsync_qlinear_fwd_amax": (_i, [_i, _i64, _i64, _i64, _vp, _vp, _vp, _vp, _i, _vp, _vp, _i, _vp, _vp, _vp, _sz, _vp]),
     "qsync_scale_from_amax": (_i, [_vp, _i, _vp, _vp, _i, _vp]),
@@ -162,6 +163,13 @@ def qsync_absmax_quantize(x, rows, cols, bits, rnd, seed, offset, scale, inv_sca
     _check(lib.qsync_absmax_quantize(_ptr(x), dtype_code(x), rows, cols, bits, rnd, seed, offset, _ptr(scale),
                                      _ptr(inv_scale), _ptr(amax_opt), _ptr(q_opt), _ptr(qT_opt), _ptr(workspace),
                                      _bytes(workspace), poll_limit, _stream(stream)))
+
+
+def qsync_gradient_quantize(dy, rows, cols, bits, rnd, seed, offset, scale, inv_scale, amax_opt, colsum, q_opt, qT_opt, workspace,
+                            stream=None) -> None:
+    _check(lib.qsync_gradient_quantize(_ptr(dy), dtype_code(dy), rows, cols, bits, rnd, seed, offset, _ptr(scale), _ptr(inv_scale),
+                                       _ptr(amax_opt), _ptr(colsum), _ptr(q_opt), _ptr(qT_opt), _ptr(workspace), _bytes(workspace),
+                                       _stream(stream)))
 
 
 def qsync_qlinear_fwd_amax(tag, M, N, K, xq, sx, wq, sw, wgran, bias_opt, y, acc_dump_opt, y_amax, workspace,

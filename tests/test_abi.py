@@ -365,6 +365,23 @@ def test_absmax_quantize_validation():
     assert f(A, 0, 64, 128, 8, 0, 0, 0, A, A, None, A, None, U, need, -1, None) == qsync.ERR_ALIGN
 
 
+def test_gradient_quantize_validation():
+    f = lib.qsync_gradient_quantize
+    #        dy dt rows cols bits rnd seed off scale inv amax colsum q qT ws wsb stream
+    need = lib.qsync_absmax_workspace_bytes(64, 128, qsync.PER_TENSOR)
+    assert f(None, 0, 64, 128, 8, 0, 0, 0, A, A, None, A, A, None, A, need, None) == qsync.ERR_NULL
+    assert f(A, 0, 64, 128, 8, 0, 0, 0, A, A, None, None, A, None, A, need, None) == qsync.ERR_NULL       # no column sums
+    assert f(A, 0, 64, 128, 8, 0, 0, 0, A, A, None, A, None, None, A, need, None) == qsync.ERR_NULL       # no codes
+    assert f(A, 7, 64, 128, 8, 0, 0, 0, A, A, None, A, A, None, A, need, None) == qsync.ERR_BAD_ENUM
+    assert f(A, 0, 64, 128, 8, 5, 0, 0, A, A, None, A, A, None, A, need, None) == qsync.ERR_BAD_ENUM
+    assert f(A, 0, 64, -1, 8, 0, 0, 0, A, A, None, A, A, None, A, need, None) == qsync.ERR_BAD_SHAPE
+    assert f(A, 0, 64, 128, 1, 0, 0, 0, A, A, None, A, A, None, A, need, None) == qsync.ERR_UNSUPPORTED
+    assert f(A, 0, 64, (1 << 19) + 8, 8, 0, 0, 0, A, A, None, A, A, None, A, need, None) == qsync.ERR_UNSUPPORTED
+    assert f(A, 0, 0, 128, 8, 0, 0, 0, A, A, None, A, A, None, None, 0, None) == qsync.OK
+    assert f(A, 0, 64, 128, 8, 0, 0, 0, A, A, None, A, A, None, A, need - 1, None) == qsync.ERR_WORKSPACE
+    assert f(A, 0, 64, 128, 8, 0, 0, 0, A, A, None, A, A, None, U, need, None) == qsync.ERR_ALIGN
+
+
 # ---- qsync_variance_increment: a host function, so it is exercised in full here (no GPU needed) ----
 class _Stats:
     def __init__(self, sumsq, amax, D):

@@ -436,6 +436,40 @@ def test_absmax_quantize_in_one_launch(dtype, rnd):
     assert_bits_equal(host(am), orc.absmax(x, "tensor"), "amax by the separate pass on the shared workspace")
 
 
+@pytest.mark.parametrize("dtype", [np.float32, np.float16])
+def test_gradient_quantize(dtype):
+    """qsync_gradient_quantize: maximum, scales and codes bit for bit those of the oracle, column sums within the bound of a
+    recursive fp32 sum, (rows - 1) 2^-24 sum |x| per column: at the last sizes of the single launch (128 KB; 512 rows), on
+    both tile heights and the streaming form, around the fold's sixteen columns, and on shapes handed to the two calls."""
+    rng = np.random.default_rng(47)
+    per = 16 // np.dtype(dtype).itemsize                            # 64 x (128 per) elements are 128 KB
+    shapes = [(64, 128 * per), (64, 128 * per + 8), (512, 16), (513, 16), (128, 72), (16, 24), (1808, 1040), (272, 1000),
+              (4096, 2056), (45, 1024), (500, 800), (3, 5), (257, 1001)]
+    w = ws(max(Q.qsync_absmax_workspace_bytes(r, c, Q.PER_TENSOR) for r, c in shapes))
+    for rows, cols in shapes:
+        x = _data(rng, (rows, cols), dtype, sigma=0.3)
+        x[rows // 2, cols // 3] = dtype(-7.5)
+        amax = orc.absmax(x, "tensor")
+        so, io = orc.scales_from_amax(amax)
+        xd, x64 = dev(x), x.astype(np.float64)
+        bound = (rows - 1) * 2.0 ** -24 * np.abs(x64).sum(0) + 1e-30
+        for rnd, with_t in (("stochastic", True), ("nearest", False)):
+            say("gradient_quantize", dtype.__name__, rnd, rows, cols, "transposed", with_t)
+            want = orc.quantize_int(x, io, "tensor", rnd, 77, 1234)
+            s, iv, am = (torch.full((1,), -3.0, dtype=torch.float32, device="cuda") for _ in range(3))
+            cs = torch.full((cols,), -3.0, dtype=torch.float32, device="cuda")
+            q = torch.full((rows, cols), 99, dtype=torch.int8, device="cuda")
+            qT = torch.full((cols, rows), 99, dtype=torch.int8, device="cuda") if with_t else None
+            Q.qsync_gradient_quantize(xd, rows, cols, 8, RND[rnd], 77, 1234, s, iv, am, cs, q, qT, w)
+            assert_bits_equal(host(am), amax, "amax")
+            assert_bits_equal(host(s), so, "scale")
+            assert_bits_equal(host(iv), io, "inverse scale")
+            assert_bits_equal(host(q), want, "codes")
+            if with_t:
+                assert_bits_equal(host(qT), want.T, "transposed codes")
+            assert np.all(np.abs(host(cs).astype(np.float64) - x64.sum(0)) <= bound), "column sums"
+
+
 def test_absmax_quantize_all_zero_and_lower_bits():
     w = ws(Q.qsync_absmax_quantize_workspace_bytes(128, 256))
     z = torch.zeros(64, 128, dtype=torch.float16, device="cuda")
