@@ -752,10 +752,7 @@ template <typename T, int RND, int TR, int SRC> struct QuantizeTile
             s.decode(i, v);
             uint4 blk = {0u, 0u, 0u, 0u};
             if(RND == kStochastic) blk = philox_group(seed, offset, static_cast<uint64_t>((r0 + i) * cols + c0) >> 3);
-            code[i][0] = code[i][1] = 0u;
-#pragma unroll
-            for(int j = 0; j < 8; ++j)
-                code[i][j / 4] |= (static_cast<uint32_t>(quantize_code<RND>(v[j], inv, qmax, philox_draw16(blk, j))) & 0xFFu) << (8 * (j % 4));
+            quantize_group<T, RND>(v, inv, qmax, blk, code[i]);
             if(q && r0 + i < rows && c0 < cols) *reinterpret_cast<uint2*>(q + (r0 + i) * cols + c0) = make_uint2(code[i][0], code[i][1]);
         }
         if(!qT) return;
@@ -1101,13 +1098,8 @@ template <typename T, int RND, int SRC> struct QuantizeStream
             }
             uint4 blk = {0u, 0u, 0u, 0u};
             if(RND == kStochastic) blk = philox_group(seed, offset, static_cast<uint64_t>(g));
-            uint32_t w[2] = {0u, 0u};
-#pragma unroll
-            for(int j = 0; j < 8; ++j)
-            {
-                const int c = quantize_code<RND>(v[j], f, qmax, philox_draw16(blk, j));
-                w[j / 4] |= (static_cast<uint32_t>(c) & 0xFFu) << (8 * (j % 4));
-            }
+            uint32_t w[2];
+            quantize_group<T, RND>(v, f, qmax, blk, w);
             *reinterpret_cast<uint2*>(q + g * 8) = make_uint2(w[0], w[1]);
         }
     }

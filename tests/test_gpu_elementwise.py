@@ -470,6 +470,26 @@ def test_gradient_quantize(dtype):
             assert np.all(np.abs(host(cs).astype(np.float64) - x64.sum(0)) <= bound), "column sums"
 
 
+@pytest.mark.parametrize("power", [-140, -120, -101, -100, -20, 3, 15, 99, 100, 101])
+def test_stochastic_codes_for_any_inverse_scale(power):
+    """Binary16 values times 2^16 times the inverse scale in one multiplication inside 2^-100 .. 2^100, in two outside:
+    the oracle's codes either way, clamped, subnormal and zero products among them, streaming and tiled.  (These draws hold
+    no 65535, the one draw for which a negative product below 2^-24 is floor(x inv) here and 0 in the oracle, whose
+    residual rounds to 1.)"""
+    say("stochastic codes, inverse scale 1.37 * 2^", power)
+    rng = np.random.default_rng(12)
+    x = _data(rng, (96, 264), np.float16, sigma=0.4)
+    x.reshape(-1)[:6] = np.array([65504.0, -65504.0, 2.0 ** -24, -2.0 ** -24, 0.0, -0.0], np.float16)
+    inv = np.array([1.37 * 2.0 ** power], np.float32)
+    want = orc.quantize_int(x, inv, "tensor", "stochastic", 5, 99)
+    for with_t in (False, True):
+        q, qT = empty((96, 264), torch.int8), empty((264, 96), torch.int8) if with_t else None
+        Q.qsync_quantize(dev(x), 96, 264, 264, Q.INT8, 8, Q.PER_TENSOR, Q.ROUND_STOCHASTIC, 5, 99, dev(inv), q, qT)
+        assert_bits_equal(host(q), want, "codes")
+        if with_t:
+            assert_bits_equal(host(qT), want.T, "transposed codes")
+
+
 def test_absmax_quantize_all_zero_and_lower_bits():
     w = ws(Q.qsync_absmax_quantize_workspace_bytes(128, 256))
     z = torch.zeros(64, 128, dtype=torch.float16, device="cuda")
