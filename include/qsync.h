@@ -193,6 +193,26 @@ int qsync_gradient_quantize(const void* dy, int dydt, int64_t rows, int64_t cols
                             void* qT_opt, void* workspace, size_t workspace_bytes, void* stream);
 
 /*
+ * qsync_convert_operands - the operands of a forward pass and of the data gradient in one call: the activation x [M, C] and the
+ * weights w [N, taps * C], taps 1 (linear operator) or 9 (3x3 convolution, NHWC activation of M pixels).  Paper: Cost Mapper
+ * paragraph (casting cost of inputs and weights).  Same results as, in this order,
+ *   activation, INT8:  qsync_absmax_quantize (nearest) -> sx, ix, ax_opt, xq, xqT_opt; with x_amax_opt (a maximum some other
+ *                      call has collected) qsync_scale_from_amax, which leaves it at zero, and qsync_quantize
+ *   activation, FP16 / FP32: qsync_quantize -> xq, xqT_opt; nothing when both are NULL (the tensor is used as it is)
+ *   weights, INT8:     w_gran PER_ROW: qsync_prepare_weights -> sw, iw, aw_opt, wq, swb, iwb, wqbT (taps 9:
+ *                      qsync_conv3x3_prepare_weights, aw_opt not written); PER_TENSOR: qsync_absmax_quantize -> sw, iw, aw_opt, wq, wqbT
+ *   weights, FP16 / FP32: qsync_quantize -> wq, wqbT
+ *   taps 9 with PER_TENSOR or FP16: wqbT by qsync_conv3x3_wflip
+ * whose arguments, workspaces (ws_x: activation, ws_w: weights) and errors it shares; fp32 weights whose vector rules hold and
+ * buffers that do not overlap across the two operands are converted side by side in shared launches.
+ * taps 9 takes INT8 and FP16 and no xqT_opt (QSYNC_ERR_UNSUPPORTED).
+ */
+int qsync_convert_operands(int tag, const void* x, int xdt, int64_t M, int64_t C, float* x_amax_opt, const void* w, int wdt, int64_t N,
+                           int taps, int bits, int w_gran, float* sx, float* ix, float* ax_opt, void* xq, void* xqT_opt, float* sw,
+                           float* iw, float* aw_opt, void* wq, float* swb, float* iwb, void* wqbT, void* ws_x, size_t ws_x_bytes,
+                           void* ws_w, size_t ws_w_bytes, void* stream);
+
+/*
  * qsync_qlinear_fwd - forward GEMM with the dequantizer and bias fused into the epilogue.
  * Paper: proof of Prop. 2 (y = q_v q_w sum(v_q w_q) + b), Backend section "Dequantization
  * Fusion" (int32 accumulation, INT32 -> FP32 conversion with the scale in the epilogue),

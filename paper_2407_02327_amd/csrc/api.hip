@@ -750,6 +750,91 @@ int qsync_conv3x3_fwd_amax(int tag, int64_t nimg, int64_t H, int64_t W, int64_t 
     return conv3x3_fwd_impl(tag, nimg, H, W, C, N, xq, sx, wq, sw, wgran, bias_opt, y, ydt, acc_dump_opt, y_amax, stream);
 }
 
+// The operands of a forward pass one after the other, activation first.
+static int convert_operands_apart(int tag, const void* x, int xdt, int64_t M, int64_t C, float* x_amax_opt, const void* w, int wdt,
+                                  int64_t N, int taps, int bits, int w_gran, float* sx, float* ix, float* ax_opt, void* xq, void* xqT_opt,
+                                  float* sw, float* iw, float* aw_opt, void* wq, float* swb, float* iwb, void* wqbT, void* ws_x,
+                                  size_t ws_x_bytes, void* ws_w, size_t ws_w_bytes, void* stream)
+{
+    const int64_t K  = taps * C;
+    int           rc = QSYNC_OK;
+    if(tag == QSYNC_INT8 && !x_amax_opt)
+        rc = qsync_absmax_quantize(x, xdt, M, C, bits, QSYNC_ROUND_NEAREST, 0, 0, sx, ix, ax_opt, xq, xqT_opt, ws_x, ws_x_bytes, -1, stream);
+    else
+    {
+        if(tag == QSYNC_INT8) rc = qsync_scale_from_amax(x_amax_opt, bits, sx, ix, 1, stream);
+        if(rc == QSYNC_OK && (tag == QSYNC_INT8 || xq || xqT_opt))
+            rc = qsync_quantize(x, xdt, M, C, C, tag, tag == QSYNC_INT8 ? bits : 0, QSYNC_PER_TENSOR, QSYNC_ROUND_NEAREST, 0, 0,
+                                tag == QSYNC_INT8 ? ix : nullptr, xq, xqT_opt, stream);
+    }
+    if(rc != QSYNC_OK) return rc;
+    if(tag == QSYNC_INT8 && w_gran == QSYNC_PER_ROW)
+        return taps == 9 ? qsync_conv3x3_prepare_weights(w, wdt, N, C, bits, sw, iw, wq, swb, iwb, wqbT, ws_w, ws_w_bytes, stream)
+                         : qsync_prepare_weights(w, wdt, N, K, bits, sw, iw, aw_opt, wq, swb, iwb, wqbT, ws_w, ws_w_bytes, stream);
+    void* const wT = taps == 9 ? nullptr : wqbT;
+    rc = tag == QSYNC_INT8 ? qsync_absmax_quantize(w, wdt, N, K, bits, QSYNC_ROUND_NEAREST, 0, 0, sw, iw, aw_opt, wq, wT, ws_w, ws_w_bytes, -1, stream)
+                           : qsync_quantize(w, wdt, N, K, K, tag, 0, QSYNC_PER_TENSOR, QSYNC_ROUND_NEAREST, 0, 0, nullptr, wq, wT, stream);
+    if(rc != QSYNC_OK || taps == 1) return rc;
+    return qsync_conv3x3_wflip(wq, tag == QSYNC_INT8 ? QSYNC_I8 : QSYNC_F16, N, C, wqbT, stream);
+}
+
+int qsync_convert_operands(int tag, const void* x, int xdt, int64_t M, int64_t C, float* x_amax_opt, const void* w, int wdt, int64_t N,
+                           int taps, int bits, int w_gran, float* sx, float* ix, float* ax_opt, void* xq, void* xqT_opt, float* sw,
+                           float* iw, float* aw_opt, void* wq, float* swb, float* iwb, void* wqbT, void* ws_x, size_t ws_x_bytes,
+                           void* ws_w, size_t ws_w_bytes, void* stream)
+{
+    if(!is_tag(tag)) return QSYNC_ERR_BAD_ENUM;
+    if(tag == QSYNC_INT8 && w_gran != QSYNC_PER_TENSOR && w_gran != QSYNC_PER_ROW) return QSYNC_ERR_BAD_ENUM;
+    if((taps != 1 && taps != 9) || (taps == 9 && (tag == QSYNC_FP32 || xqT_opt))) return QSYNC_ERR_UNSUPPORTED;
+    // shared launches where each conversion by itself would pass its checks and neither writes what the other reads or writes
+    const bool   i8 = tag == QSYNC_INT8, rows = w_gran == QSYNC_PER_ROW;
+    bool         ok = x && w && wq && wqbT && is_float_dtype(xdt) && wdt == QSYNC_F32 && M > 0 && C > 0 && N > 0 && C <= (1 << 28)
+              && count_ok(M, C) && count_ok(N, taps * C) && (taps == 1 || C <= (1 << 20));
+    size_t need_x = 0, need_w = 0;
+    if(ok && i8)
+    {
+        need_x = x_amax_opt ? 0 : qsync_absmax_workspace_bytes(M, C, QSYNC_PER_TENSOR);
+        need_w = !rows ? qsync_absmax_workspace_bytes(N, taps * C, QSYNC_PER_TENSOR)
+                 : taps == 9 ? qsync_conv3x3_prepare_weights_workspace_bytes(N, C) : absmax_workspace_bytes(N, C, kPerCol);
+        ok = bits >= 2 && bits <= 8 && sx && ix && sw && iw && (!rows || (swb && iwb)) && (xq || xqT_opt)
+          && (x_amax_opt || (ws_x && ws_x_bytes >= need_x && aligned16(ws_x))) && ws_w && ws_w_bytes >= need_w && aligned16(ws_w);
+    }
+    if(ok)
+    {
+        struct Span { const void* p; int64_t n; };
+        const int64_t xe = xdt == QSYNC_F16 ? 2 : 4, oe = i8 ? 1 : (tag == QSYNC_FP16 ? 2 : 4), nx = M * C, nw = N * taps * C;
+        const int64_t nsw = rows ? N : 1, nsb = rows ? C : 1;
+        const Span x_in[] = {{x, nx * xe}, {x_amax_opt, 4}};
+        const Span x_out[] = {{xq, nx * oe}, {xqT_opt, nx * oe}, {i8 ? sx : nullptr, 4}, {i8 ? ix : nullptr, 4}, {i8 ? ax_opt : nullptr, 4},
+                              {i8 ? ws_x : nullptr, static_cast<int64_t>(need_x)}, {x_amax_opt, 4}};
+        const Span w_in[] = {{w, nw * 4}};
+        const Span w_out[] = {{wq, nw * oe}, {wqbT, nw * oe}, {i8 ? sw : nullptr, nsw * 4}, {i8 ? iw : nullptr, nsw * 4},
+                              {i8 ? aw_opt : nullptr, nsw * 4}, {i8 && rows ? swb : nullptr, nsb * 4}, {i8 && rows ? iwb : nullptr, nsb * 4},
+                              {i8 ? ws_w : nullptr, static_cast<int64_t>(need_w)}};
+        auto apart = [](const Span& a, const Span& b) {
+            const uintptr_t p = reinterpret_cast<uintptr_t>(a.p), q = reinterpret_cast<uintptr_t>(b.p);
+            return !a.p || !b.p || p >= q + static_cast<uintptr_t>(b.n) || q >= p + static_cast<uintptr_t>(a.n);
+        };
+        for(const Span& o : x_out)
+        {
+            for(const Span& i : w_in) ok = ok && apart(o, i);
+            for(const Span& i : w_out) ok = ok && apart(o, i);
+        }
+        for(const Span& o : w_out)
+            for(const Span& i : x_in) ok = ok && apart(o, i);
+    }
+    if(ok)
+    {
+        const OperandConversion c{x, M, C, i8 ? x_amax_opt : nullptr, w, N, taps, i8 ? (1 << (bits - 1)) - 1 : 0, w_gran, sx, ix, ax_opt,
+                                  xq, xqT_opt, sw, iw, taps == 9 && rows ? nullptr : aw_opt, wq, swb, iwb, wqbT, ws_x, ws_w};
+        bool      taken = false;
+        const int rc    = hip_status(launch_convert_operands(c, tag, xdt, &taken, static_cast<hipStream_t>(stream)));
+        if(taken || rc != QSYNC_OK) return rc;
+    }
+    return convert_operands_apart(tag, x, xdt, M, C, x_amax_opt, w, wdt, N, taps, bits, w_gran, sx, ix, ax_opt, xq, xqT_opt, sw, iw,
+                                  aw_opt, wq, swb, iwb, wqbT, ws_x, ws_x_bytes, ws_w, ws_w_bytes, stream);
+}
+
 int qsync_conv3x3_wflip(const void* w, int wdt, int64_t N, int64_t C, void* wflip, void* stream)
 {
     if(!w || !wflip) return QSYNC_ERR_NULL;

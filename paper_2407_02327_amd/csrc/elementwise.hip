@@ -260,15 +260,50 @@ __global__ __launch_bounds__(BLOCK) void absmax_tensor_kernel(const T* __restric
     }
 }
 
+// One maximum per workgroup of a contiguous, 16-byte aligned tensor of whole vectors, for a pass that folds them.
+template <typename T> struct BlockMaxima
+{
+    static constexpr int kThreads = kBlock, kLds = 64, kVectors = kBlock * 8;      // vectors a workgroup has in flight
+    const T* x;
+    int64_t  n;
+    int64_t  blocks;
+    float*   partial;
+    __device__ __forceinline__ void run(uint32_t block, uint8_t* lds) const
+    {
+        const int64_t nvec = n / Vec16<T>::N;
+        const uint4*  xv   = reinterpret_cast<const uint4*>(x);
+        RunMax<T>     rm;
+        for(int64_t c = static_cast<int64_t>(block) * kVectors + threadIdx.x; c < nvec; c += blocks * kVectors)
+        {
+            uint4 v[8];
+#pragma unroll
+            for(int u = 0; u < 8; ++u) v[u] = c + u * kBlock < nvec ? xv[c + u * kBlock] : make_uint4(0, 0, 0, 0);
+#pragma unroll
+            for(int u = 0; u < 8; ++u) rm.add(v[u]);
+        }
+        const float m = block_reduce_max(rm.get(), reinterpret_cast<float*>(lds));
+        if(threadIdx.x == 0) partial[block] = m;
+    }
+};
+
 // Scale and inverse scale from a maximum some other kernel has collected (a GEMM epilogue); `consume` clears the
 // word for the next collection.
-__global__ void scale_from_amax_kernel(float* amax, float qmax, float* scale, float* inv_scale, int consume)
+struct ScaleFromAmax
 {
-    if(threadIdx.x != 0 || blockIdx.x != 0) return;
-    const float m = __hip_atomic_load(amax, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    write_scale(m, qmax, scale, inv_scale, nullptr, 0);
-    if(consume) *amax = 0.0f;
-}
+    static constexpr int kThreads = kBlock, kLds = 16;
+    float* amax;
+    float  qmax;
+    float* scale;
+    float* inv_scale;
+    int    consume;
+    __device__ __forceinline__ void run(uint32_t, uint8_t*) const
+    {
+        if(threadIdx.x != 0) return;
+        const float m = __hip_atomic_load(amax, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        write_scale(m, qmax, scale, inv_scale, nullptr, 0);
+        if(consume) *amax = 0.0f;
+    }
+};
 
 // ------------------------------------------------------------------ absmax, per row
 // WPR wavefronts per row (1 when there are many rows, 4 = the whole block when there are few),
@@ -771,54 +806,61 @@ template <typename T, int RND, int TR, int SRC> struct QuantizeTile
 // the separate passes.
 constexpr int kWeightTileRows = 64, kWeightGroups = 64;
 
-template <typename T>
-__global__ __launch_bounds__(256) void weight_maxima_kernel(const T* __restrict__ x, int64_t rows, int64_t cols, int tiles_x,
-                                                            int groups, float* __restrict__ row_part, float* __restrict__ col_part)
+template <typename T> struct WeightMaxima
 {
-    constexpr int TR = kWeightTileRows;
-    __shared__ float lds[4][kTileCols];
-    const int     by = static_cast<int>(blockIdx.x) / tiles_x, bx = static_cast<int>(blockIdx.x) - by * tiles_x;
-    const int     cg = threadIdx.x % 16, quad = threadIdx.x / 16;
-    const int64_t c0 = static_cast<int64_t>(bx) * kTileCols + cg * 8;
-    float         cm[8];
-#pragma unroll
-    for(int j = 0; j < 8; ++j) cm[j] = 0.0f;
-    for(int64_t tile_r = static_cast<int64_t>(by) * TR; tile_r < rows; tile_r += static_cast<int64_t>(groups) * TR)
+    static constexpr int kThreads = 256, kLds = 4 * kTileCols * 4;
+    const T* x;
+    int64_t  rows, cols;
+    int      tiles_x, groups;
+    float*   row_part;
+    float*   col_part;
+    __device__ __forceinline__ void run(uint32_t block, uint8_t* lds_bytes) const
     {
-        const int64_t r0 = tile_r + quad * 4;
-        TileShare<T>  s;
-        s.load(x, r0, c0, rows, cols, cols);
+        constexpr int TR = kWeightTileRows;
+        float (*lds)[kTileCols] = reinterpret_cast<float (*)[kTileCols]>(lds_bytes);
+        const int     by = static_cast<int>(block) / tiles_x, bx = static_cast<int>(block) - by * tiles_x;
+        const int     cg = threadIdx.x % 16, quad = threadIdx.x / 16;
+        const int64_t c0 = static_cast<int64_t>(bx) * kTileCols + cg * 8;
+        float         cm[8];
 #pragma unroll
-        for(int i = 0; i < 4; ++i)
+        for(int j = 0; j < 8; ++j) cm[j] = 0.0f;
+        for(int64_t tile_r = static_cast<int64_t>(by) * TR; tile_r < rows; tile_r += static_cast<int64_t>(groups) * TR)
         {
-            float v[8], rm = 0.0f;
-            s.decode(i, v);
+            const int64_t r0 = tile_r + quad * 4;
+            TileShare<T>  s;
+            s.load(x, r0, c0, rows, cols, cols);
 #pragma unroll
-            for(int j = 0; j < 8; ++j)
+            for(int i = 0; i < 4; ++i)
             {
-                const float a = fabsf(v[j]);
-                cm[j] = fmaxf(cm[j], a);
-                rm    = fmaxf(rm, a);
+                float v[8], rm = 0.0f;
+                s.decode(i, v);
+#pragma unroll
+                for(int j = 0; j < 8; ++j)
+                {
+                    const float a = fabsf(v[j]);
+                    cm[j] = fmaxf(cm[j], a);
+                    rm    = fmaxf(rm, a);
+                }
+#pragma unroll
+                for(int off = 8; off > 0; off >>= 1) rm = fmaxf(rm, __shfl_xor(rm, off, kWaveSize));     // the 16 lanes of a row
+                if(cg == 0 && r0 + i < rows) row_part[bx * rows + r0 + i] = rm;
             }
-#pragma unroll
-            for(int off = 8; off > 0; off >>= 1) rm = fmaxf(rm, __shfl_xor(rm, off, kWaveSize));     // the 16 lanes of a row
-            if(cg == 0 && r0 + i < rows) row_part[bx * rows + r0 + i] = rm;
         }
-    }
 #pragma unroll
-    for(int j = 0; j < 8; ++j)
-    {   // the four row quads of the wavefront, then the four wavefronts
-        cm[j] = fmaxf(cm[j], __shfl_xor(cm[j], 16, kWaveSize));
-        cm[j] = fmaxf(cm[j], __shfl_xor(cm[j], 32, kWaveSize));
-    }
-    if(quad % 4 == 0)
+        for(int j = 0; j < 8; ++j)
+        {   // the four row quads of the wavefront, then the four wavefronts
+            cm[j] = fmaxf(cm[j], __shfl_xor(cm[j], 16, kWaveSize));
+            cm[j] = fmaxf(cm[j], __shfl_xor(cm[j], 32, kWaveSize));
+        }
+        if(quad % 4 == 0)
 #pragma unroll
-        for(int j = 0; j < 8; ++j) lds[quad / 4][cg * 8 + j] = cm[j];
-    __syncthreads();
-    const int64_t c = static_cast<int64_t>(bx) * kTileCols + threadIdx.x;
-    if(threadIdx.x < kTileCols && c < cols)
-        col_part[by * cols + c] = fmaxf(fmaxf(lds[0][threadIdx.x], lds[1][threadIdx.x]), fmaxf(lds[2][threadIdx.x], lds[3][threadIdx.x]));
-}
+            for(int j = 0; j < 8; ++j) lds[quad / 4][cg * 8 + j] = cm[j];
+        __syncthreads();
+        const int64_t c = static_cast<int64_t>(bx) * kTileCols + threadIdx.x;
+        if(threadIdx.x < kTileCols && c < cols)
+            col_part[by * cols + c] = fmaxf(fmaxf(lds[0][threadIdx.x], lds[1][threadIdx.x]), fmaxf(lds[2][threadIdx.x], lds[3][threadIdx.x]));
+    }
+};
 
 struct WeightOut
 {
@@ -830,87 +872,95 @@ struct WeightOut
 // conv_C > 0 (3x3 convolution weights [N, 9 * C]): the column scale belongs to the input channel c = column % C, i.e. it
 // covers the nine columns (tap, c), and column (tap, c) lands in row c * 9 + (8 - tap) of the transposed copy, the
 // mirrored, channel-exchanged weights.
-template <typename T>
-__global__ __launch_bounds__(256) void weight_quantize_kernel(const T* __restrict__ x, int64_t rows, int64_t cols, int qmax,
-                                                              int tiles_x, int groups, const float* row_part /* may be o.row_scale */,
-                                                              const float* __restrict__ col_part, const WeightOut o, int conv_C)
+template <typename T> struct WeightQuantize
 {
-    constexpr int TR = kWeightTileRows;
-    __shared__ __attribute__((aligned(16))) uint8_t lds_t[TR * kTileCols];
-    __shared__ float lds_c[2][kTileCols], lds_r[4][TR], inv_c[kTileCols], inv_r[TR];
-    const int     by = static_cast<int>(blockIdx.x) / tiles_x, bx = static_cast<int>(blockIdx.x) - by * tiles_x;
-    const int64_t tile_r = static_cast<int64_t>(by) * TR, tile_c = static_cast<int64_t>(bx) * kTileCols;
-    const int     cg = threadIdx.x % 16, quad = threadIdx.x / 16;
-    const int64_t r0 = tile_r + quad * 4, c0 = tile_c + cg * 8;
-    TileShare<T>  s;
-    s.load(x, r0, c0, rows, cols, cols);
-    {   // columns: two threads each; rows: four threads each
-        const int     cc = threadIdx.x % kTileCols, half = threadIdx.x / kTileCols;
-        const int64_t c  = tile_c + cc;
-        float         m  = 0.0f;
-        if(c < cols)
-        {
-            const int64_t step = conv_C > 0 ? conv_C : cols;          // conv: [groups][9][C] read as groups * 9 rows of C
-            const int     n    = conv_C > 0 ? groups * 9 : groups;
-            const float*  src  = col_part + (conv_C > 0 ? static_cast<int64_t>(static_cast<uint32_t>(c) % static_cast<uint32_t>(conv_C)) : c);
+    static constexpr int TR = kWeightTileRows, kThreads = 256, kLds = TR * kTileCols + (3 * kTileCols + 5 * TR) * 4;
+    const T*     x;
+    int64_t      rows, cols;
+    int          qmax, tiles_x, groups;
+    const float* row_part;       // may be o.row_scale
+    const float* col_part;
+    WeightOut    o;
+    int          conv_C;
+    __device__ __forceinline__ void run(uint32_t block, uint8_t* lds_t) const
+    {
+        float (*lds_c)[kTileCols] = reinterpret_cast<float (*)[kTileCols]>(lds_t + TR * kTileCols);
+        float (*lds_r)[TR]        = reinterpret_cast<float (*)[TR]>(lds_c + 2);
+        float *inv_c = reinterpret_cast<float*>(lds_r + 4), *inv_r = inv_c + kTileCols;
+        const int     by = static_cast<int>(block) / tiles_x, bx = static_cast<int>(block) - by * tiles_x;
+        const int64_t tile_r = static_cast<int64_t>(by) * TR, tile_c = static_cast<int64_t>(bx) * kTileCols;
+        const int     cg = threadIdx.x % 16, quad = threadIdx.x / 16;
+        const int64_t r0 = tile_r + quad * 4, c0 = tile_c + cg * 8;
+        TileShare<T>  s;
+        s.load(x, r0, c0, rows, cols, cols);
+        {   // columns: two threads each; rows: four threads each
+            const int     cc = threadIdx.x % kTileCols, half = threadIdx.x / kTileCols;
+            const int64_t c  = tile_c + cc;
+            float         m  = 0.0f;
+            if(c < cols)
+            {
+                const int64_t step = conv_C > 0 ? conv_C : cols;          // conv: [groups][9][C] read as groups * 9 rows of C
+                const int     n    = conv_C > 0 ? groups * 9 : groups;
+                const float*  src  = col_part + (conv_C > 0 ? static_cast<int64_t>(static_cast<uint32_t>(c) % static_cast<uint32_t>(conv_C)) : c);
 #pragma unroll 8
-            for(int g = half; g < n; g += 2) m = fmaxf(m, src[g * step]);
-        }
-        lds_c[half][cc] = m;
-        const int     rr = threadIdx.x % TR, part = threadIdx.x / TR;
-        const int64_t r  = tile_r + rr;
-        m = 0.0f;
-        if(r < rows)
+                for(int g = half; g < n; g += 2) m = fmaxf(m, src[g * step]);
+            }
+            lds_c[half][cc] = m;
+            const int     rr = threadIdx.x % TR, part = threadIdx.x / TR;
+            const int64_t r  = tile_r + rr;
+            m = 0.0f;
+            if(r < rows)
 #pragma unroll 4
-            for(int b = part; b < tiles_x; b += 4) m = fmaxf(m, row_part[b * rows + r]);
-        lds_r[part][rr] = m;
-    }
-    __syncthreads();
-    const float fq = static_cast<float>(qmax);
-    if(threadIdx.x < kTileCols)
-    {
-        const int     t = threadIdx.x;
-        const float   m = fmaxf(lds_c[0][t], lds_c[1][t]);
-        const int64_t c = tile_c + t;
-        inv_c[t] = m != 0.0f ? __fdiv_rn(fq, m) : 1.0f;
-        if(by == 0 && c < (conv_C > 0 ? conv_C : cols)) write_scale(m, fq, o.col_scale, o.col_inv, nullptr, c);
-    }
-    else if(threadIdx.x < kTileCols + TR)
-    {
-        const int     t = threadIdx.x - kTileCols;
-        const float   m = fmaxf(fmaxf(lds_r[0][t], lds_r[1][t]), fmaxf(lds_r[2][t], lds_r[3][t]));
-        inv_r[t] = m != 0.0f ? __fdiv_rn(fq, m) : 1.0f;
-        if(bx == 0 && tile_r + t < rows) write_scale(m, fq, o.row_scale, o.row_inv, o.row_amax_opt, tile_r + t);
-    }
-    __syncthreads();
-    float fc[8];
-#pragma unroll
-    for(int j = 0; j < 8; ++j) fc[j] = inv_c[cg * 8 + j];
-    uint32_t codeT[4][2];
-#pragma unroll
-    for(int i = 0; i < 4; ++i)
-    {
-        float v[8];
-        s.decode(i, v);
-        const float fr = inv_r[quad * 4 + i];
-        uint32_t    code[2] = {0u, 0u};
-        codeT[i][0] = codeT[i][1] = 0u;
-#pragma unroll
-        for(int j = 0; j < 8; ++j)
-        {
-            code[j / 4]     |= (static_cast<uint32_t>(quantize_code<kNearest>(v[j], fr, qmax, 0u)) & 0xFFu) << (8 * (j % 4));
-            codeT[i][j / 4] |= (static_cast<uint32_t>(quantize_code<kNearest>(v[j], fc[j], qmax, 0u)) & 0xFFu) << (8 * (j % 4));
+                for(int b = part; b < tiles_x; b += 4) m = fmaxf(m, row_part[b * rows + r]);
+            lds_r[part][rr] = m;
         }
-        if(r0 + i < rows && c0 < cols) *reinterpret_cast<uint2*>(o.wq + (r0 + i) * cols + c0) = make_uint2(code[0], code[1]);
+        __syncthreads();
+        const float fq = static_cast<float>(qmax);
+        if(threadIdx.x < kTileCols)
+        {
+            const int     t = threadIdx.x;
+            const float   m = fmaxf(lds_c[0][t], lds_c[1][t]);
+            const int64_t c = tile_c + t;
+            inv_c[t] = m != 0.0f ? __fdiv_rn(fq, m) : 1.0f;
+            if(by == 0 && c < (conv_C > 0 ? conv_C : cols)) write_scale(m, fq, o.col_scale, o.col_inv, nullptr, c);
+        }
+        else if(threadIdx.x < kTileCols + TR)
+        {
+            const int     t = threadIdx.x - kTileCols;
+            const float   m = fmaxf(fmaxf(lds_r[0][t], lds_r[1][t]), fmaxf(lds_r[2][t], lds_r[3][t]));
+            inv_r[t] = m != 0.0f ? __fdiv_rn(fq, m) : 1.0f;
+            if(bx == 0 && tile_r + t < rows) write_scale(m, fq, o.row_scale, o.row_inv, o.row_amax_opt, tile_r + t);
+        }
+        __syncthreads();
+        float fc[8];
+#pragma unroll
+        for(int j = 0; j < 8; ++j) fc[j] = inv_c[cg * 8 + j];
+        uint32_t codeT[4][2];
+#pragma unroll
+        for(int i = 0; i < 4; ++i)
+        {
+            float v[8];
+            s.decode(i, v);
+            const float fr = inv_r[quad * 4 + i];
+            uint32_t    code[2] = {0u, 0u};
+            codeT[i][0] = codeT[i][1] = 0u;
+#pragma unroll
+            for(int j = 0; j < 8; ++j)
+            {
+                code[j / 4]     |= (static_cast<uint32_t>(quantize_code<kNearest>(v[j], fr, qmax, 0u)) & 0xFFu) << (8 * (j % 4));
+                codeT[i][j / 4] |= (static_cast<uint32_t>(quantize_code<kNearest>(v[j], fc[j], qmax, 0u)) & 0xFFu) << (8 * (j % 4));
+            }
+            if(r0 + i < rows && c0 < cols) *reinterpret_cast<uint2*>(o.wq + (r0 + i) * cols + c0) = make_uint2(code[0], code[1]);
+        }
+        uint32_t t[8];
+        transpose_codes_4x8(codeT, t);
+        store_transposed_tile<TR>(t, lds_t, tile_r, tile_c, rows, cols, o.wqT, [&](int64_t c) {
+            if(conv_C == 0) return c;
+            const uint32_t tap = static_cast<uint32_t>(c) / static_cast<uint32_t>(conv_C);
+            return (c - static_cast<int64_t>(tap) * conv_C) * 9 + (8 - tap);
+        });
     }
-    uint32_t t[8];
-    transpose_codes_4x8(codeT, t);
-    store_transposed_tile<TR>(t, lds_t, tile_r, tile_c, rows, cols, o.wqT, [&](int64_t c) {
-        if(conv_C == 0) return c;
-        const uint32_t tap = static_cast<uint32_t>(c) / static_cast<uint32_t>(conv_C);
-        return (c - static_cast<int64_t>(tap) * conv_C) * 9 + (8 - tap);
-    });
-}
+};
 
 // ------------------------------------------------------------------ INT8 quantize, vector path of per-row and per-column scales
 // Each lane owns a patch of 16 (or 8) rows x 32 input bytes (16 binary16 or 8 fp32 columns) and
@@ -1390,72 +1440,83 @@ template <> __device__ __forceinline__ __half scaled_code<__half>(float a, float
 // with both copies 8.5 -> 7.4 us, 4096x1024 11.5 -> 9.4; fp32 8192x4096 transposed element by element 69.2 -> 54.6).
 // binary16 sources go by patches all the same (copy_f16_patch_kernel).
 constexpr int kConvertRows = 64;
-template <typename Ti, typename To>
-__global__ __launch_bounds__(kBlock) void convert_tile_kernel(const Ti* __restrict__ x, int64_t rows, int64_t cols, int64_t ld,
-                                                              const float* __restrict__ row_scale, const float* __restrict__ scale,
-                                                              To* __restrict__ q, To* __restrict__ qT, int tiles_x)
+// conv_C > 0 (3x3 convolution weights [N, 9 * C]): column (tap, c) lands in row c * 9 + (8 - tap) of the transposed copy, as
+// for WeightQuantize.
+template <typename Ti, typename To> struct ConvertTile
 {
-    constexpr int TC = 16 / sizeof(To);                      // columns of a thread
-    constexpr int CH = kConvertRows * sizeof(To) / 16;       // 16-byte chunks of a tile column
-    __shared__ __attribute__((aligned(16))) uint8_t lds_t[16 * TC * CH * 16];
-    const int     by = static_cast<int>(blockIdx.x) / tiles_x, bx = static_cast<int>(blockIdx.x) - by * tiles_x;
-    const int     cg = threadIdx.x % 16, quad = threadIdx.x / 16;
-    const int64_t tile_r = static_cast<int64_t>(by) * kConvertRows, tile_c = static_cast<int64_t>(bx) * 16 * TC;
-    const int64_t r0 = tile_r + quad * 4, c0 = tile_c + cg * TC;
-    struct alignas(sizeof(Ti) * TC < 16 ? sizeof(Ti) * TC : 16) In { Ti v[TC]; };
-    union Out { To v[TC]; uint4 w; };
-    In  in[4];
-    Out out[4];
-#pragma unroll
-    for(int i = 0; i < 4; ++i)
-        if(r0 + i < rows && c0 < cols) in[i] = *reinterpret_cast<const In*>(x + (r0 + i) * ld + c0);
-#pragma unroll
-    for(int i = 0; i < 4; ++i)
+    static constexpr int TC = 16 / sizeof(To);                      // columns of a thread
+    static constexpr int CH = kConvertRows * sizeof(To) / 16;       // 16-byte chunks of a tile column
+    static constexpr int kThreads = kBlock, kLds = 16 * TC * CH * 16;
+    const Ti*    x;
+    int64_t      rows, cols, ld;
+    const float* row_scale;
+    const float* scale;
+    To*          q;
+    To*          qT;
+    int          tiles_x;
+    int          conv_C;
+    __device__ __forceinline__ void run(uint32_t block, uint8_t* lds_t) const
     {
-        const bool ok = r0 + i < rows && c0 < cols;
-        float      g  = 1.0f;
-        if constexpr(std::is_same<Ti, int8_t>::value) g = row_scale ? (ok ? row_scale[r0 + i] : 1.0f) : *scale;
+        const int     by = static_cast<int>(block) / tiles_x, bx = static_cast<int>(block) - by * tiles_x;
+        const int     cg = threadIdx.x % 16, quad = threadIdx.x / 16;
+        const int64_t tile_r = static_cast<int64_t>(by) * kConvertRows, tile_c = static_cast<int64_t>(bx) * 16 * TC;
+        const int64_t r0 = tile_r + quad * 4, c0 = tile_c + cg * TC;
+        struct alignas(sizeof(Ti) * TC < 16 ? sizeof(Ti) * TC : 16) In { Ti v[TC]; };
+        union Out { To v[TC]; uint4 w; };
+        In  in[4];
+        Out out[4];
+#pragma unroll
+        for(int i = 0; i < 4; ++i)
+            if(r0 + i < rows && c0 < cols) in[i] = *reinterpret_cast<const In*>(x + (r0 + i) * ld + c0);
+#pragma unroll
+        for(int i = 0; i < 4; ++i)
+        {
+            const bool ok = r0 + i < rows && c0 < cols;
+            float      g  = 1.0f;
+            if constexpr(std::is_same<Ti, int8_t>::value) g = row_scale ? (ok ? row_scale[r0 + i] : 1.0f) : *scale;
+#pragma unroll
+            for(int e = 0; e < TC; ++e)
+            {
+                if constexpr(std::is_same<Ti, int8_t>::value) out[i].v[e] = scaled_code<To>(static_cast<float>(in[i].v[e]), g, 0.0f, false);
+                else out[i].v[e] = convert_elem<To, Ti>(in[i].v[e]);
+            }
+            if(q && ok) *reinterpret_cast<uint4*>(q + (r0 + i) * cols + c0) = out[i].w;
+        }
+        if(!qT) return;
 #pragma unroll
         for(int e = 0; e < TC; ++e)
         {
-            if constexpr(std::is_same<Ti, int8_t>::value) out[i].v[e] = scaled_code<To>(static_cast<float>(in[i].v[e]), g, 0.0f, false);
-            else out[i].v[e] = convert_elem<To, Ti>(in[i].v[e]);
+            const uint32_t* w[4] = {&out[0].w.x, &out[1].w.x, &out[2].w.x, &out[3].w.x};
+            uint8_t*        col  = lds_t + (cg * TC + e) * CH * 16;
+            if constexpr(sizeof(To) == 2)
+            {
+                const uint32_t sel = e % 2 ? 0x07060302u : 0x05040100u;
+                const uint32_t lo = __builtin_amdgcn_perm(w[1][e / 2], w[0][e / 2], sel), hi = __builtin_amdgcn_perm(w[3][e / 2], w[2][e / 2], sel);
+                *reinterpret_cast<uint2*>(col + ((quad / 2) ^ (cg % CH)) * 16 + (quad % 2) * 8) = make_uint2(lo, hi);
+            }
+            else
+                *reinterpret_cast<uint4*>(col + (quad ^ (cg % CH)) * 16) = make_uint4(w[0][e], w[1][e], w[2][e], w[3][e]);
         }
-        if(q && ok) *reinterpret_cast<uint4*>(q + (r0 + i) * cols + c0) = out[i].w;
-    }
-    if(!qT) return;
+        __syncthreads();
 #pragma unroll
-    for(int e = 0; e < TC; ++e)
-    {
-        const uint32_t* w[4] = {&out[0].w.x, &out[1].w.x, &out[2].w.x, &out[3].w.x};
-        uint8_t*        col  = lds_t + (cg * TC + e) * CH * 16;
-        if constexpr(sizeof(To) == 2)
+        for(int k = threadIdx.x; k < 16 * TC * CH; k += kBlock)
         {
-            const uint32_t sel = e % 2 ? 0x07060302u : 0x05040100u;
-            const uint32_t lo = __builtin_amdgcn_perm(w[1][e / 2], w[0][e / 2], sel), hi = __builtin_amdgcn_perm(w[3][e / 2], w[2][e / 2], sel);
-            *reinterpret_cast<uint2*>(col + ((quad / 2) ^ (cg % CH)) * 16 + (quad % 2) * 8) = make_uint2(lo, hi);
+            const int     lc = k / CH, ch = k % CH;
+            const int64_t r = tile_r + ch * TC, c = tile_c + lc;        // a chunk holds TC rows
+            if(c >= cols || r >= rows) continue;
+            Out v;
+            v.w = *reinterpret_cast<const uint4*>(lds_t + lc * CH * 16 + ((ch ^ ((lc / TC) % CH)) * 16));
+            const int64_t tr  = conv_C == 0 ? c : (c % conv_C) * 9 + (8 - c / conv_C);
+            To*           dst = qT + tr * rows + r;
+            if(rows % TC == 0)
+                *reinterpret_cast<uint4*>(dst) = v.w;
+            else
+#pragma unroll
+                for(int e = 0; e < TC; ++e)
+                    if(r + e < rows) dst[e] = v.v[e];
         }
-        else
-            *reinterpret_cast<uint4*>(col + (quad ^ (cg % CH)) * 16) = make_uint4(w[0][e], w[1][e], w[2][e], w[3][e]);
     }
-    __syncthreads();
-#pragma unroll
-    for(int k = threadIdx.x; k < 16 * TC * CH; k += kBlock)
-    {
-        const int     lc = k / CH, ch = k % CH;
-        const int64_t r = tile_r + ch * TC, c = tile_c + lc;        // a chunk holds TC rows
-        if(c >= cols || r >= rows) continue;
-        Out v;
-        v.w = *reinterpret_cast<const uint4*>(lds_t + lc * CH * 16 + ((ch ^ ((lc / TC) % CH)) * 16));
-        To* dst = qT + c * rows + r;
-        if(rows % TC == 0)
-            *reinterpret_cast<uint4*>(dst) = v.w;
-        else
-#pragma unroll
-            for(int e = 0; e < TC; ++e)
-                if(r + e < rows) dst[e] = v.v[e];
-    }
-}
+};
 
 // binary16 copied and transposed without converting anything: a lane owns an 8 x 8 patch, transposed in registers by pairing
 // 16-bit halves, a wavefront 8 x 8 patches, so every load and store instruction covers 128-byte row segments; no LDS,
@@ -1464,33 +1525,41 @@ __global__ __launch_bounds__(kBlock) void convert_tile_kernel(const Ti* __restri
 // nothing hides here (fp32 sources, whose loads are twice as long, run faster through it).  Tiles -> patches, transposed
 // copy alone: 64x512 3.5 -> 2.4 us, 4096x768 5.1 -> 3.8, 16384x1024 15.8 -> 12.7, 16384x4096 49 -> 43; both copies 4096x768
 // 6.2 -> 5.2, 16384x1024 18.0 -> 16.4, 16384x4096 88 -> 89.
-__global__ __launch_bounds__(kBlock) void copy_f16_patch_kernel(const __half* __restrict__ x, int64_t rows, int64_t cols, int64_t ld,
-                                                                __half* __restrict__ q, __half* __restrict__ qT, int64_t grid_x)
+struct CopyF16Patch
 {
-    const int     lane = threadIdx.x % kWaveSize, wave = threadIdx.x / kWaveSize;
-    const int64_t by = blockIdx.x / grid_x, bx = blockIdx.x - by * grid_x;
-    const int64_t r0 = (by * (kBlock / kWaveSize) + wave) * 64 + (lane / 8) * 8;
-    const int64_t c0 = bx * 64 + (lane % 8) * 8;
-    if(r0 >= rows || c0 >= cols) return;
-    uint4 w[8];
+    static constexpr int kThreads = kBlock, kLds = 16;
+    const __half* x;
+    int64_t       rows, cols, ld;
+    __half*       q;
+    __half*       qT;
+    int64_t       grid_x;
+    __device__ __forceinline__ void run(uint32_t block, uint8_t*) const
+    {
+        const int     lane = threadIdx.x % kWaveSize, wave = threadIdx.x / kWaveSize;
+        const int64_t by = block / grid_x, bx = block - by * grid_x;
+        const int64_t r0 = (by * (kBlock / kWaveSize) + wave) * 64 + (lane / 8) * 8;
+        const int64_t c0 = bx * 64 + (lane % 8) * 8;
+        if(r0 >= rows || c0 >= cols) return;
+        uint4 w[8];
 #pragma unroll
-    for(int i = 0; i < 8; ++i) w[i] = r0 + i < rows ? *reinterpret_cast<const uint4*>(x + (r0 + i) * ld + c0) : make_uint4(0, 0, 0, 0);
-    if(q)
+        for(int i = 0; i < 8; ++i) w[i] = r0 + i < rows ? *reinterpret_cast<const uint4*>(x + (r0 + i) * ld + c0) : make_uint4(0, 0, 0, 0);
+        if(q)
 #pragma unroll
-        for(int i = 0; i < 8; ++i)
-            if(r0 + i < rows) *reinterpret_cast<uint4*>(q + (r0 + i) * cols + c0) = w[i];
-    if(!qT) return;
-    auto pair = [&](int i, int p) { return p == 0 ? w[i].x : p == 1 ? w[i].y : p == 2 ? w[i].z : w[i].w; };
+            for(int i = 0; i < 8; ++i)
+                if(r0 + i < rows) *reinterpret_cast<uint4*>(q + (r0 + i) * cols + c0) = w[i];
+        if(!qT) return;
+        auto pair = [&](int i, int p) { return p == 0 ? w[i].x : p == 1 ? w[i].y : p == 2 ? w[i].z : w[i].w; };
 #pragma unroll
-    for(int c = 0; c < 8; ++c)
-    {   // column c of the patch: halves c % 2 of pair c / 2 of every row
-        uint32_t t[4];
+        for(int c = 0; c < 8; ++c)
+        {   // column c of the patch: halves c % 2 of pair c / 2 of every row
+            uint32_t t[4];
 #pragma unroll
-        for(int g = 0; g < 4; ++g)
-            t[g] = __builtin_amdgcn_perm(pair(2 * g + 1, c / 2), pair(2 * g, c / 2), c % 2 ? 0x07060302u : 0x05040100u);
-        *reinterpret_cast<uint4*>(qT + (c0 + c) * rows + r0) = make_uint4(t[0], t[1], t[2], t[3]);
+            for(int g = 0; g < 4; ++g)
+                t[g] = __builtin_amdgcn_perm(pair(2 * g + 1, c / 2), pair(2 * g, c / 2), c % 2 ? 0x07060302u : 0x05040100u);
+            *reinterpret_cast<uint4*>(qT + (c0 + c) * rows + r0) = make_uint4(t[0], t[1], t[2], t[3]);
+        }
     }
-}
+};
 
 template <typename Ti, typename To, int V>
 __global__ __launch_bounds__(kBlock) void dequantize_kernel(const Ti* __restrict__ a, int64_t rows, int64_t cols,
@@ -1747,7 +1816,7 @@ static hipError_t absmax_typed(const T* x, int64_t rows, int64_t cols, int64_t l
 
 hipError_t launch_scale_from_amax(float* amax, float qmax, float* scale, float* inv_scale, int consume, hipStream_t st)
 {
-    scale_from_amax_kernel<<<dim3(1), dim3(64), 0, st>>>(amax, qmax, scale, inv_scale, consume);
+    launch_part(ScaleFromAmax{amax, qmax, scale, inv_scale, consume}, 1, st);
     return hipGetLastError();
 }
 
@@ -2030,39 +2099,50 @@ hipError_t launch_gradient_quantize(const void* x, int xdt, int64_t rows, int64_
 // Weights of one linear operator in one go: per-row scales and codes for the forward, per-column scales
 // and transposed codes for dX.  Two launches that read W twice where the vector rules hold; otherwise the
 // separate passes.  Same results either way.
+// conv_C > 0: w is [N, 9*conv_C]; the second scales are per input channel (conv_C of them) and wqbT is the
+// mirrored, channel-exchanged copy [conv_C, 9*N]; only the two launches serve this case.
 template <typename T>
-static hipError_t prepare_weights_typed(const T* w, int64_t N, int64_t K, float qmax, float* sw, float* iw,
-                                        float* aw_opt, int8_t* wq, float* swb, float* iwb, int8_t* wqbT,
-                                        void* workspace, hipStream_t st, int64_t conv_C = 0)
+static bool weights_in_two_passes(const T* w, int64_t N, int64_t K, const int8_t* wq, const int8_t* wqbT, const void* workspace)
 {
-    // conv_C > 0: w is [N, 9*conv_C]; the second scales are per input channel (conv_C of them) and wqbT is the
-    // mirrored, channel-exchanged copy [conv_C, 9*N]; only the fused form serves this case.
+    return aligned16(w) && K % 8 == 0 && N % 16 == 0 && N <= 16 * kColParts && aligned16(wq) && aligned16(wqbT) && aligned16(workspace);
+}
+template <typename T> struct WeightParts { WeightMaxima<T> maxima; int64_t maxima_blocks; WeightQuantize<T> quantize; int64_t quantize_blocks; };
+template <typename T>
+static WeightParts<T> weight_parts(const T* w, int64_t N, int64_t K, float qmax, float* sw, float* iw, float* aw_opt, int8_t* wq,
+                                   float* swb, float* iwb, int8_t* wqbT, void* workspace, int64_t conv_C)
+{
     float*        partial = reinterpret_cast<float*>(static_cast<uint8_t*>(workspace) + kCtrBytes);
     const int64_t tiles_x = (K + kTileCols - 1) / kTileCols, row_tiles = (N + kWeightTileRows - 1) / kWeightTileRows;
-    const bool    fused = aligned16(w) && K % 8 == 0 && N % 16 == 0 && N <= 16 * kColParts
-                       && aligned16(wq) && aligned16(wqbT) && aligned16(partial);
-    if(!fused && conv_C > 0) return hipErrorInvalidValue;      // the caller tests the same conditions before choosing this form
-    if(!fused)
-    {
-        hipError_t e = absmax_typed(w, N, K, K, kPerRow, qmax, sw, iw, aw_opt, nullptr, nullptr, workspace, st);
-        if(e != hipSuccess) return e;
-        e = quantize_typed(w, N, K, K, static_cast<int>(qmax), kPerRow, kNearest, 0, 0, iw, wq, nullptr, st);
-        if(e != hipSuccess) return e;
-        e = absmax_typed(w, N, K, K, kPerCol, qmax, swb, iwb, nullptr, nullptr, nullptr, workspace, st);
-        if(e != hipSuccess) return e;
-        return quantize_typed(w, N, K, K, static_cast<int>(qmax), kPerCol, kNearest, 0, 0, iwb, nullptr, wqbT, st);
-    }
     const int groups = static_cast<int>(row_tiles < kWeightGroups ? row_tiles : kWeightGroups);
     // Row maxima lie behind the 64 K column maxima in a workspace of 512 K floats: ceil(K / 128) N of them fit while K > 128
     // (N <= 8192 here).  Of a single tile column they are final and wait in sw, where the tile that owns the rows replaces
     // them by their scales (they need not fit then: 4096x8 fp32 in separate passes 17.2 us, so 9.5).
     float*    row_part = tiles_x == 1 ? sw : partial + kWeightGroups * K;
-    weight_maxima_kernel<T><<<dim3(static_cast<unsigned>(tiles_x * groups)), dim3(256), 0, st>>>(
-        w, N, K, static_cast<int>(tiles_x), groups, row_part, partial);
-    const WeightOut out{sw, iw, aw_opt, swb, iwb, wq, wqbT};
-    weight_quantize_kernel<T><<<dim3(static_cast<unsigned>(tiles_x * row_tiles)), dim3(256), 0, st>>>(
-        w, N, K, static_cast<int>(qmax), static_cast<int>(tiles_x), groups, row_part, partial, out, static_cast<int>(conv_C));
-    return hipGetLastError();
+    return WeightParts<T>{WeightMaxima<T>{w, N, K, static_cast<int>(tiles_x), groups, row_part, partial}, tiles_x * groups,
+                          WeightQuantize<T>{w, N, K, static_cast<int>(qmax), static_cast<int>(tiles_x), groups, row_part, partial,
+                                            WeightOut{sw, iw, aw_opt, swb, iwb, wq, wqbT}, static_cast<int>(conv_C)}, tiles_x * row_tiles};
+}
+
+template <typename T>
+static hipError_t prepare_weights_typed(const T* w, int64_t N, int64_t K, float qmax, float* sw, float* iw,
+                                        float* aw_opt, int8_t* wq, float* swb, float* iwb, int8_t* wqbT,
+                                        void* workspace, hipStream_t st, int64_t conv_C = 0)
+{
+    if(weights_in_two_passes(w, N, K, wq, wqbT, workspace))
+    {
+        const WeightParts<T> p = weight_parts(w, N, K, qmax, sw, iw, aw_opt, wq, swb, iwb, wqbT, workspace, conv_C);
+        launch_part(p.maxima, p.maxima_blocks, st);
+        launch_part(p.quantize, p.quantize_blocks, st);
+        return hipGetLastError();
+    }
+    if(conv_C > 0) return hipErrorInvalidValue;      // the caller tests the same conditions before choosing this form
+    hipError_t e = absmax_typed(w, N, K, K, kPerRow, qmax, sw, iw, aw_opt, nullptr, nullptr, workspace, st);
+    if(e != hipSuccess) return e;
+    e = quantize_typed(w, N, K, K, static_cast<int>(qmax), kPerRow, kNearest, 0, 0, iw, wq, nullptr, st);
+    if(e != hipSuccess) return e;
+    e = absmax_typed(w, N, K, K, kPerCol, qmax, swb, iwb, nullptr, nullptr, nullptr, workspace, st);
+    if(e != hipSuccess) return e;
+    return quantize_typed(w, N, K, K, static_cast<int>(qmax), kPerCol, kNearest, 0, 0, iwb, nullptr, wqbT, st);
 }
 
 hipError_t launch_prepare_weights(const void* w, int wdt, int64_t N, int64_t K, float qmax, float* sw, float* iw,
@@ -2074,42 +2154,47 @@ hipError_t launch_prepare_weights(const void* w, int wdt, int64_t N, int64_t K, 
     return prepare_weights_typed(static_cast<const __half*>(w), N, K, qmax, sw, iw, aw_opt, wq, swb, iwb, wqbT, workspace, stream);
 }
 
-// The tiled conversion where its vector rules hold; false: nothing was launched.
+// The tiled conversion as a part, f(part, workgroups), where its vector rules hold; false: f was not called.
+template <typename Ti, typename To, typename F>
+static bool with_convert_tiles(const Ti* x, int64_t rows, int64_t cols, int64_t ld, const float* row_scale, const float* scale, To* q,
+                               To* qT, int conv_C, F&& f)
+{
+    constexpr int64_t TC = 16 / sizeof(To), in_bytes = TC * sizeof(Ti) < 16 ? TC * sizeof(Ti) : 16;
+    const int64_t     bx = (cols + 16 * TC - 1) / (16 * TC), by = (rows + kConvertRows - 1) / kConvertRows;
+    if(conv_C > 0 && cols != 9 * conv_C) return false;
+    if(cols % TC != 0 || (reinterpret_cast<uintptr_t>(x) & (in_bytes - 1)) != 0 || (ld * sizeof(Ti)) % in_bytes != 0 || !aligned16(q)
+       || (rows % TC == 0 && !aligned16(qT)) || bx * by >= (int64_t(1) << 30))
+        return false;
+    f(ConvertTile<Ti, To>{x, rows, cols, ld, row_scale, scale, q, qT, static_cast<int>(bx), conv_C}, bx * by);
+    return true;
+}
 template <typename Ti, typename To>
 static bool convert_tiles(const Ti* x, int64_t rows, int64_t cols, int64_t ld, const float* row_scale, const float* scale, To* q,
                           To* qT, hipStream_t st)
 {
-    constexpr int64_t TC = 16 / sizeof(To), in_bytes = TC * sizeof(Ti) < 16 ? TC * sizeof(Ti) : 16;
-    const int64_t     bx = (cols + 16 * TC - 1) / (16 * TC), by = (rows + kConvertRows - 1) / kConvertRows;
-    if(cols % TC != 0 || (reinterpret_cast<uintptr_t>(x) & (in_bytes - 1)) != 0 || (ld * sizeof(Ti)) % in_bytes != 0 || !aligned16(q)
-       || (rows % TC == 0 && !aligned16(qT)) || bx * by >= (int64_t(1) << 31))
-        return false;
-    convert_tile_kernel<Ti, To><<<dim3(static_cast<unsigned>(bx * by)), dim3(kBlock), 0, st>>>(x, rows, cols, ld, row_scale, scale, q, qT,
-                                                                                             static_cast<int>(bx));
-    return true;
+    return with_convert_tiles(x, rows, cols, ld, row_scale, scale, q, qT, 0, [&](const auto& p, int64_t blocks) { launch_part(p, blocks, st); });
 }
 
-// binary16 to binary16 by patches, where their vector rules hold; false: nothing was launched.  A row-major copy alone gains from
+// binary16 to binary16 by patches, as a part, where their vector rules hold; false: f was not called.  A row-major copy alone gains from
 // them below 2 M elements (1024x1024 3.0 -> 2.7 us) and, while every patch column is whole, below 8 M (4096x768 3.8 -> 3.4,
 // 100000x64 5.5 -> 4.8; but 2256x2640 5.6 -> 6.0, and 16384x1024 from memory 13.8 -> 14.7); not with so few rows that most of
 // a workgroup's are absent (1x2097152 9.9 -> 12.3).
-static bool copy_patches(const __half* x, int64_t rows, int64_t cols, int64_t ld, __half* q, __half* qT, hipStream_t st)
+template <typename F> static bool with_copy_patches(const __half* x, int64_t rows, int64_t cols, int64_t ld, __half* q, __half* qT, F&& f)
 {
     const int64_t bx = (cols + 63) / 64, by = (rows + 255) / 256;
     if(cols % 8 != 0 || !aligned16(x) || ld % 8 != 0 || !aligned16(q) || !aligned16(qT) || (qT && rows % 8 != 0)
-       || (!qT && (rows < 32 || rows * cols >= (int64_t(1) << (cols % 64 == 0 ? 23 : 21)))) || bx * by >= (int64_t(1) << 31))
+       || (!qT && (rows < 32 || rows * cols >= (int64_t(1) << (cols % 64 == 0 ? 23 : 21)))) || bx * by >= (int64_t(1) << 30))
         return false;
-    copy_f16_patch_kernel<<<dim3(static_cast<unsigned>(bx * by)), dim3(kBlock), 0, st>>>(x, rows, cols, ld, q, qT, bx);
+    f(CopyF16Patch{x, rows, cols, ld, q, qT, bx}, bx * by);
     return true;
 }
 
-template <typename Ti, typename To>
-static hipError_t convert_typed(const void* x, int64_t rows, int64_t cols, int64_t ld, void* q, void* qT,
-                                hipStream_t st)
+// The conversion as a part, f(part, workgroups), unless convert_kernel is to do it (false).
+template <typename Ti, typename To, typename F>
+static bool with_convert_part(const Ti* x, int64_t rows, int64_t cols, int64_t ld, To* q, To* qT, F&& f)
 {
     if constexpr(std::is_same<Ti, __half>::value && std::is_same<To, __half>::value)
-        if(copy_patches(static_cast<const __half*>(x), rows, cols, ld, static_cast<__half*>(q), static_cast<__half*>(qT), st))
-            return hipGetLastError();
+        if(with_copy_patches(x, rows, cols, ld, q, qT, f)) return true;
     // columns of a binary16 copy that are no multiple of 16 bytes leave a tile of eight-row chunks element by element; the
     // kernel below, a column per wavefront and store, is faster for large ones of some rows (10002x1032 binary16, transposed
     // alone, 25.3 -> 17.7 us, fp32 28.6 -> 18.5, with both copies 30.7 -> 21.3; but 1569x320 4.7 -> 5.2, 9x262144 7.8 -> 10.2).
@@ -2118,12 +2203,124 @@ static hipError_t convert_typed(const void* x, int64_t rows, int64_t cols, int64
     const int64_t n   = rows * cols;
     const bool    odd = std::is_same<To, __half>::value && qT && rows % 8 != 0 && rows >= 32
                      && (std::is_same<Ti, float>::value || !q ? n >= (int64_t(1) << 21) : n >= (int64_t(1) << 22) && n < (int64_t(1) << 23));
-    if(!odd && convert_tiles(static_cast<const Ti*>(x), rows, cols, ld, nullptr, nullptr, static_cast<To*>(q), static_cast<To*>(qT), st))
+    return !odd && with_convert_tiles(x, rows, cols, ld, nullptr, nullptr, q, qT, 0, f);
+}
+
+template <typename Ti, typename To>
+static hipError_t convert_typed(const void* x, int64_t rows, int64_t cols, int64_t ld, void* q, void* qT,
+                                hipStream_t st)
+{
+    if(with_convert_part(static_cast<const Ti*>(x), rows, cols, ld, static_cast<To*>(q), static_cast<To*>(qT),
+                         [&](const auto& p, int64_t blocks) { launch_part(p, blocks, st); }))
         return hipGetLastError();
     const int64_t gx = (cols + 63) / 64, gy = (rows + 63) / 64;
     convert_kernel<Ti, To, false><<<dim3(static_cast<unsigned>(gx * gy)), dim3(kBlock), 0, st>>>(
         static_cast<const Ti*>(x), rows, cols, ld, static_cast<To*>(q), static_cast<To*>(qT), gx, 0, 0, 0);
     return hipGetLastError();
+}
+
+// ---- both operands of a forward pass, activation and weights, in shared launches
+// What the two conversions do one after the other, stage by stage beside each other: the passes that leave maxima, then the
+// passes that fold them and convert.  The weights of an ordinary operator fill a fraction of the chip and each pass over
+// them is one memory latency long, so beside the activation they cost next to nothing; a small operator is bound by the
+// number of launches.  Whole steps, apart -> beside each other: 64x128x128 28.7 -> 22.9 us, 1808x1040x784 50.9 -> 43.5, INT8
+// 4096x3072x768 87.8 -> 80.0, FP16 2056x1000x1032 64.9 -> 61.7, convolution 64x56x56x64 126.4 -> 115.8.  Merged where every part is one of 256 threads: weights fp32 and, for codes, in two passes or small;
+// an activation whose transposed copy is large enough for 128-row tiles keeps its own launches.
+template <typename T> static bool small_tiles(int64_t rows, int64_t cols, const int8_t* qT, int64_t n)
+{
+    return tiles_of(rows, cols, 128) < 512 && !(odd_transpose_generic(rows, n, qT) && (rows < 16 || n < (int64_t(3) << 16))
+                                                && (n * static_cast<int64_t>(sizeof(T)) > kWholeBytes || (rows >= 128 && n >= (int64_t(1) << 15))));
+}
+template <typename T> static int64_t maxima_blocks(int64_t n)
+{
+    const int64_t nb = (n / Vec16<T>::N + BlockMaxima<T>::kVectors - 1) / BlockMaxima<T>::kVectors;
+    return nb > 1024 ? 1024 : nb;
+}
+
+template <typename TX> static bool convert_int8_operands(const OperandConversion& c, hipStream_t st)
+{
+    const TX*     x = static_cast<const TX*>(c.x);
+    const float*  w = static_cast<const float*>(c.w);
+    const int64_t nx = c.M * c.C, K = c.taps * c.C, nw = c.N * K;
+    int8_t *const xq = static_cast<int8_t*>(c.xq), *const xqT = static_cast<int8_t*>(c.xqT);
+    int8_t *const wq = static_cast<int8_t*>(c.wq), *const wqbT = static_cast<int8_t*>(c.wqbT);
+    const bool    stream = xq && !xqT;
+    if(!tile_ok(x, c.M, c.C, c.C, xq, xqT) || !(stream || small_tiles<TX>(c.M, c.C, xqT, nx))) return false;
+    const bool w_rows = c.w_gran == kPerRow;
+    if(w_rows ? !weights_in_two_passes(w, c.N, K, wq, wqbT, c.ws_w)
+              : c.taps != 1 || !tile_ok(w, c.N, K, K, wq, wqbT) || !small_tiles<float>(c.N, K, wqbT, nw)) return false;
+    const bool    x_whole = !c.x_amax && nx * static_cast<int64_t>(sizeof(TX)) <= kWholeBytes;
+    const bool    w_whole = !w_rows && nw * 4 <= kWholeBytes;
+    const float   qm = static_cast<float>(c.qmax);
+    float* const  px = reinterpret_cast<float*>(static_cast<uint8_t*>(c.ws_x) + kCtrBytes);
+    float* const  pw = reinterpret_cast<float*>(static_cast<uint8_t*>(c.ws_w) + kCtrBytes);
+    const int64_t bx = maxima_blocks<TX>(nx), bw = maxima_blocks<float>(nw);
+    const int     tx = static_cast<int>((c.C + kTileCols - 1) / kTileCols), tw = static_cast<int>((K + kTileCols - 1) / kTileCols);
+    const TensorScale sx{c.ix, px, static_cast<int>(bx), c.sx, c.ix, c.ax}, sw{nullptr, pw, static_cast<int>(bw), c.sw, c.iw, c.aw};
+    const int64_t tiles_x = tiles_of(c.M, c.C, 64), tiles_w = tiles_of(c.N, K, 64);
+    const int64_t groups = nx / 8, stream_blocks = (groups + kBlock * 4 - 1) / (kBlock * 4);
+    if(stream_blocks + tiles_x + tiles_w >= (int64_t(1) << 31)) return false;
+    const WeightParts<float> wp = w_rows ? weight_parts(w, c.N, K, qm, c.sw, c.iw, c.aw, wq, c.swb, c.iwb, wqbT, c.ws_w, c.taps == 9 ? c.C : 0)
+                                         : WeightParts<float>{};
+    auto x1 = [&](auto&& f) {
+        if(c.x_amax)     f(ScaleFromAmax{c.x_amax, qm, c.sx, c.ix, 1}, 1);
+        else if(x_whole) f(QuantizeTile<TX, kNearest, 64, kWhole>{x, c.M, c.C, c.C, c.qmax, 0, 0, sx, xq, xqT, tx}, tiles_x);
+        else             f(BlockMaxima<TX>{x, nx, bx, px}, bx);
+    };
+    auto x2 = [&](auto&& f) {
+        if(c.x_amax && stream) f(QuantizeStream<TX, kNearest, kInv>{x, groups, c.qmax, 0, 0, sx, xq}, stream_blocks);
+        else if(c.x_amax)      f(QuantizeTile<TX, kNearest, 64, kInv>{x, c.M, c.C, c.C, c.qmax, 0, 0, sx, xq, xqT, tx}, tiles_x);
+        else if(stream)        f(QuantizeStream<TX, kNearest, kPartials>{x, groups, c.qmax, 0, 0, sx, xq}, stream_blocks);
+        else                   f(QuantizeTile<TX, kNearest, 64, kPartials>{x, c.M, c.C, c.C, c.qmax, 0, 0, sx, xq, xqT, tx}, tiles_x);
+    };
+    auto w1 = [&](auto&& f) {
+        if(w_rows)       f(wp.maxima, wp.maxima_blocks);
+        else if(w_whole) f(QuantizeTile<float, kNearest, 64, kWhole>{w, c.N, K, K, c.qmax, 0, 0, sw, wq, wqbT, tw}, tiles_w);
+        else             f(BlockMaxima<float>{w, nw, bw, pw}, bw);
+    };
+    auto w2 = [&](auto&& f) {
+        if(w_rows) f(wp.quantize, wp.quantize_blocks);
+        else       f(QuantizeTile<float, kNearest, 64, kPartials>{w, c.N, K, K, c.qmax, 0, 0, sw, wq, wqbT, tw}, tiles_w);
+    };
+    // (weights first: theirs are the longer chains of dependent accesses)
+    auto together = [&](auto&& a, auto&& b) {
+        a([&](const auto& pa, int64_t na) { b([&](const auto& pb, int64_t nb) { launch_parts(pa, na, pb, nb, st); }); });
+    };
+    auto alone = [&](const auto& p, int64_t blocks) { launch_part(p, blocks, st); };
+    together(w1, x1);
+    if(!x_whole && !w_whole) together(w2, x2);
+    else if(!x_whole)        x2(alone);
+    else if(!w_whole)        w2(alone);
+    return true;
+}
+
+// Casts and copies: activation (unless it is used as it is) and weights in one launch.
+template <typename TX, typename To> static bool convert_float_operands(const OperandConversion& c, hipStream_t st)
+{
+    const int64_t K = c.taps * c.C;
+    const float*  w = static_cast<const float*>(c.w);
+    To *const     wq = static_cast<To*>(c.wq), *const wqbT = static_cast<To*>(c.wqbT);
+    bool          done = false;
+    auto weights = [&](auto&& f) {
+        return c.taps == 9 ? with_convert_tiles(w, c.N, K, K, nullptr, nullptr, wq, wqbT, static_cast<int>(c.C), f)
+                           : with_convert_part(w, c.N, K, K, wq, wqbT, f);
+    };
+    if(!c.xq && !c.xqT)
+        return weights([&](const auto& p, int64_t blocks) { launch_part(p, blocks, st); });
+    weights([&](const auto& pw, int64_t bw) {
+        done = with_convert_part(static_cast<const TX*>(c.x), c.M, c.C, c.C, static_cast<To*>(c.xq), static_cast<To*>(c.xqT),
+                                 [&](const auto& px, int64_t bx) { launch_parts(pw, bw, px, bx, st); });
+    });
+    return done;
+}
+
+hipError_t launch_convert_operands(const OperandConversion& c, int tag, int xdt, bool* taken, hipStream_t st)
+{
+    const bool half = xdt == kF16;
+    *taken = tag == 8    ? (half ? convert_int8_operands<__half>(c, st) : convert_int8_operands<float>(c, st))
+             : tag == 16 ? (half ? convert_float_operands<__half, __half>(c, st) : convert_float_operands<float, __half>(c, st))
+                         : (half ? convert_float_operands<__half, float>(c, st) : convert_float_operands<float, float>(c, st));
+    return *taken ? hipGetLastError() : hipSuccess;
 }
 
 hipError_t launch_convert(const void* x, int xdt, int64_t rows, int64_t cols, int64_t ld, int outdt, void* q, void* qT,
@@ -2237,10 +2434,7 @@ hipError_t launch_conv3x3_prepare_weights(const void* w, int wdt, int64_t N, int
 {
     const int64_t K = 9 * C;
     const int64_t e2 = wdt == kF32 ? 8 : 16;
-    float*        partial = reinterpret_cast<float*>(static_cast<uint8_t*>(workspace) + kCtrBytes);
-    const bool    fused = aligned16(w) && K % e2 == 0 && N % 16 == 0 && N <= 16 * kColParts && C <= (1 << 20)
-                       && aligned16(wq) && aligned16(wflip) && aligned16(partial);
-    if(fused)
+    if(K % e2 == 0 && weights_in_two_passes(w, N, K, wq, wflip, workspace))
     {
         if(wdt == kF32)
             return prepare_weights_typed(static_cast<const float*>(w), N, K, qmax, sw, iw, nullptr, wq, swb, iwb, wflip, workspace, st, C);

@@ -62,6 +62,25 @@ hipError_t launch_prepare_weights(const void* w, int wdt, int64_t N, int64_t K, 
 hipError_t launch_conv3x3_prepare_weights(const void* w, int wdt, int64_t N, int64_t C, float qmax, float* sw, float* iw,
                                           float* swb, float* iwb, int8_t* wq, int8_t* wflip, void* workspace,
                                           hipStream_t stream);
+// Activation [M, C] and fp32 weights [N, taps * C] (taps 9: a 3x3 convolution) of a forward pass, for both GEMM directions, in
+// shared launches; *taken is false, and nothing launched, where the operands have to be converted one after the other.
+struct OperandConversion
+{
+    const void* x;
+    int64_t     M, C;
+    float*      x_amax;      // int8: max |x| already collected (consumed), or nullptr
+    const void* w;
+    int64_t     N;
+    int         taps, qmax, w_gran;
+    float *sx, *ix, *ax;
+    void *xq, *xqT;
+    float *sw, *iw, *aw;
+    void*  wq;
+    float *swb, *iwb;
+    void*  wqbT;
+    void *ws_x, *ws_w;
+};
+hipError_t launch_convert_operands(const OperandConversion& c, int tag, int xdt, bool* taken, hipStream_t st);
 hipError_t launch_conv3x3_wflip(const void* w, int elem_bytes, int64_t N, int64_t C, void* wflip, hipStream_t stream);
 // padded pixel axis of the convolution's weight-gradient operands (see conv_padded_transpose_kernel)
 struct ConvPaddedAxis { int Wp; int64_t Mp; };

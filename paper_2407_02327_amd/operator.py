@@ -169,6 +169,17 @@ class QLinear:
         Q.qsync_prepare_weights(w, N, K, self.bits, self.sw, self.iw, self.aw, self.wq, self.swb, self.iwb, self.wqbT,
                                 self.ws_absmax_w, stream)
 
+    def convert_operands(self, x: torch.Tensor, w: torch.Tensor, stream=None, x_amax: Optional[torch.Tensor] = None) -> None:
+        """`convert_x` and `convert_w` in one call, the two beside each other."""
+        in_place = (self.tag != Q.INT8 and x.dtype == _TORCH_OF_TAG[self.tag] and x.is_contiguous() and not self.own_copies)
+        if self.tag != Q.INT8:
+            self.xq = x if in_place else self._xq
+        Q.qsync_convert_operands(self.tag, x, self.M, self.K, x_amax if self.tag == Q.INT8 else None, w, self.N, 1, self.bits, self.w_gran,
+                                 self.sx, self.ix, self.ax, None if in_place else self.xq, self._xqT, self.sw, self.iw, self.aw, self.wq,
+                                 self.swb, self.iwb, self.wqbT, self.ws_absmax, self.ws_absmax_w, stream)
+        if self.tag == Q.INT8 and self.w_gran == Q.PER_TENSOR:
+            self.swb = self.sw
+
     def convert_dy(self, dy: torch.Tensor, stream=None) -> None:
         M, N, K = self.M, self.N, self.K
         if self.bwd_tag != self.tag:
@@ -272,8 +283,7 @@ class QLinear:
         """With `side_stream` (a torch stream of default priority) the small, latency-bound weight
         conversion kernels run beside the HBM-bound activation conversion and join before the GEMM."""
         if side_stream is None:
-            self.convert_x(x, stream, x_amax)
-            self.convert_w(w, stream)
+            self.convert_operands(x, w, stream, x_amax)
         else:
             main = stream if stream is not None else torch.cuda.current_stream()
             side_stream.wait_stream(main)
@@ -377,6 +387,18 @@ class QConv3x3:
         Q.qsync_conv3x3_prepare_weights(w, N, C, self.bits, self.sw, self.iw, self.wq, self.swb, self.iwb, self.wflip,
                                         self.ws_absmax_w, stream)
 
+    def convert_operands(self, act: torch.Tensor, w: torch.Tensor, stream=None, x_amax: Optional[torch.Tensor] = None) -> None:
+        """`convert_x` and `convert_w` in one call, the two beside each other."""
+        in_place = self.tag != Q.INT8 and act.dtype == _TORCH_OF_TAG[self.tag] and act.is_contiguous()
+        if self.tag != Q.INT8:
+            self.xq = act.view(self.M, self.C) if in_place else self._xq
+        Q.qsync_convert_operands(self.tag, act, self.M, self.C, x_amax if self.tag == Q.INT8 else None, w, self.N, 9, self.bits,
+                                 self.w_gran, self.sx, self.ix, self.ax, None if in_place else self.xq, None, self.sw, self.iw,
+                                 self.aw if self.w_gran == Q.PER_TENSOR else None, self.wq, self.swb, self.iwb, self.wflip,
+                                 self.ws_absmax, self.ws_absmax_w, stream)
+        if self.tag == Q.INT8 and self.w_gran == Q.PER_TENSOR:
+            self.swb = self.sw
+
     def conv_fwd(self, stream=None) -> None:
         if self.y_amax is not None:
             Q.qsync_conv3x3_fwd_amax(self.tag, self.nimg, self.H, self.W, self.C, self.N, self.xq, self.sx, self.wq, self.sw,
@@ -412,8 +434,7 @@ class QConv3x3:
                             Q.PER_TENSOR, None, self.dw, None, None, None, self.acc_dw, self.ws_bwd, stream)
 
     def forward(self, act: torch.Tensor, w: torch.Tensor, stream=None, x_amax: Optional[torch.Tensor] = None) -> torch.Tensor:
-        self.convert_w(w, stream)
-        self.convert_x(act, stream, x_amax)
+        self.convert_operands(act, w, stream, x_amax)
         self.conv_fwd(stream)
         return self.y
 

@@ -37,6 +37,8 @@ SIGNATURES = {
     "qsync_absmax_quantize": (_i, [_vp, _i, _i64, _i64, _i, _i, ctypes.c_uint64, ctypes.c_uint64, _vp, _vp, _vp, _vp, _vp,
                                    _vp, _sz, _i, _vp]),
     "qsync_gradient_quantize": (_i, [_vp, _i, _i64, _i64, _i, _i, _u64, _u64, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _sz, _vp]),
+    "qsync_convert_operands": (_i, [_i, _vp, _i, _i64, _i64, _vp, _vp, _i, _i64, _i, _i, _i, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp,
+                                    _vp, _vp, _vp, _vp, _vp, _sz, _vp, _sz, _vp]),
     "qsync_absmax_quantize_workspace_bytes": (_sz, [_i64, _i64]),
     "qsync_qlinear_fwd_amax": (_i, [_i, _i64, _i64, _i64, _vp, _vp, _vp, _vp, _i, _vp, _vp, _i, _vp, _vp, _vp, _sz, _vp]),
     "qsync_scale_from_amax": (_i, [_vp, _i, _vp, _vp, _i, _vp]),
@@ -170,6 +172,14 @@ def qsync_gradient_quantize(dy, rows, cols, bits, rnd, seed, offset, scale, inv_
     _check(lib.qsync_gradient_quantize(_ptr(dy), dtype_code(dy), rows, cols, bits, rnd, seed, offset, _ptr(scale), _ptr(inv_scale),
                                        _ptr(amax_opt), _ptr(colsum), _ptr(q_opt), _ptr(qT_opt), _ptr(workspace), _bytes(workspace),
                                        _stream(stream)))
+
+
+def qsync_convert_operands(tag, x, M, C, x_amax_opt, w, N, taps, bits, w_gran, sx, ix, ax_opt, xq, xqT_opt, sw, iw, aw_opt, wq, swb,
+                           iwb, wqbT, ws_x, ws_w, stream=None) -> None:
+    _check(lib.qsync_convert_operands(tag, _ptr(x), dtype_code(x), M, C, _ptr(x_amax_opt), _ptr(w), dtype_code(w), N, taps, bits, w_gran,
+                                      _ptr(sx), _ptr(ix), _ptr(ax_opt), _ptr(xq), _ptr(xqT_opt), _ptr(sw), _ptr(iw), _ptr(aw_opt),
+                                      _ptr(wq), _ptr(swb), _ptr(iwb), _ptr(wqbT), _ptr(ws_x), _bytes(ws_x), _ptr(ws_w), _bytes(ws_w),
+                                      _stream(stream)))
 
 
 def qsync_qlinear_fwd_amax(tag, M, N, K, xq, sx, wq, sw, wgran, bias_opt, y, acc_dump_opt, y_amax, workspace,

@@ -382,6 +382,24 @@ def test_gradient_quantize_validation():
     assert f(A, 0, 64, 128, 8, 0, 0, 0, A, A, None, A, A, None, U, need, None) == qsync.ERR_ALIGN
 
 
+def test_convert_operands_validation():
+    f = lib.qsync_convert_operands
+    need = lib.qsync_absmax_workspace_bytes(64, 128, qsync.PER_TENSOR)
+
+    def call(tag=8, x=A, xdt=0, M=64, C=128, w=A, wdt=0, N=64, taps=1, bits=8, gran=qsync.PER_ROW, sx=A, xq=A, xqT=None, wq=A, ws=A,
+             wsb=need, amax=None):
+        return f(tag, x, xdt, M, C, amax, w, wdt, N, taps, bits, gran, sx, A, A, xq, xqT, A, A, A, wq, A, A, A, ws, wsb, ws, wsb, None)
+
+    assert call(tag=9) == qsync.ERR_BAD_ENUM and call(gran=qsync.PER_COL) == qsync.ERR_BAD_ENUM and call(xdt=5) == qsync.ERR_BAD_ENUM
+    assert call(taps=3) == qsync.ERR_UNSUPPORTED and call(taps=9, tag=32) == qsync.ERR_UNSUPPORTED
+    assert call(taps=9, xqT=A) == qsync.ERR_UNSUPPORTED and call(bits=9) == qsync.ERR_UNSUPPORTED
+    assert call(x=None) == qsync.ERR_NULL and call(sx=None) == qsync.ERR_NULL and call(xq=None) == qsync.ERR_NULL
+    assert call(M=-1) == qsync.ERR_BAD_SHAPE
+    assert call(ws=None) == qsync.ERR_WORKSPACE and call(wsb=need - 256) == qsync.ERR_WORKSPACE and call(ws=U) == qsync.ERR_ALIGN
+    assert call(M=0, w=None) == qsync.ERR_NULL            # an empty activation is no work; its weights are checked next
+    assert call(M=0, N=0) == qsync.OK and call(tag=16, xq=None, N=0) == qsync.OK
+
+
 # ---- qsync_variance_increment: a host function, so it is exercised in full here (no GPU needed) ----
 class _Stats:
     def __init__(self, sumsq, amax, D):

@@ -490,6 +490,79 @@ def test_stochastic_codes_for_any_inverse_scale(power):
             assert_bits_equal(host(qT), want.T, "transposed codes")
 
 
+OPERANDS = [
+    # tag, weight granularity, taps, M, C, N, transposed activation copy: whole tensors (128 KB) on either side, around 16 rows, tiles
+    # and streaming, odd row counts, shapes that no shared launch takes (odd columns; N % 16)
+    ("int8", "tensor", 1, 64, 128, 128, True), ("int8", "tensor", 1, 512, 1024, 64, False), ("int8", "tensor", 1, 64, 256, 1024, True),
+    ("int8", "tensor", 1, 272, 1000, 304, True), ("int8", "row", 1, 64, 128, 128, True), ("int8", "row", 1, 1808, 784, 1040, True),
+    ("int8", "row", 1, 2048, 768, 768, False), ("int8", "row", 1, 45, 1024, 256, True), ("int8", "row", 1, 130, 72, 48, True),
+    ("int8", "row", 1, 16, 8, 8192, False), ("int8", "row", 1, 64, 33, 16, True), ("int8", "row", 1, 64, 64, 24, True),
+    ("int8", "row", 9, 3 * 7 * 9, 16, 32, False), ("int8", "row", 9, 4 * 14 * 14, 64, 48, False), ("int8", "tensor", 9, 99, 16, 16, False),
+    ("fp16", "row", 1, 2056, 1032, 1000, True), ("fp16", "row", 1, 65, 72, 8, True), ("fp16", "row", 1, 64, 33, 7, True),
+    ("fp16", "row", 9, 4704, 64, 40, False), ("fp16", "row", 9, 99, 8, 8, False), ("fp32", "row", 1, 260, 132, 64, True),
+    ("fp32", "row", 1, 33, 7, 5, True)]
+
+
+@pytest.mark.parametrize("case", OPERANDS, ids=lambda c: "-".join(map(str, c)))
+@pytest.mark.parametrize("x_from", ["float32", "float16", "amax", "in place"])
+def test_convert_operands_equals_the_separate_calls(case, x_from):
+    """qsync_convert_operands against its definition, the separate calls, bit for bit in every output; once more with one
+    workspace for both operands, which has to fall back to one conversion after the other."""
+    tag, gran, taps, M, C, N, with_t = case
+    if (x_from == "amax" and tag != "int8") or (x_from == "in place" and tag == "int8"):
+        pytest.skip("INT8 only" if x_from == "amax" else "casts only")
+    say("convert_operands", *case, x_from)
+    i8, K = tag == "int8", taps * C
+    code, qd = {"int8": (Q.INT8, torch.int8), "fp16": (Q.FP16, torch.float16), "fp32": (Q.FP32, torch.float32)}[tag]
+    rng = np.random.default_rng(M + 7 * C + N)
+    x = dev(_data(rng, (M, C), np.float32 if x_from == "float32" else np.float16, sigma=0.5))
+    w = dev(_data(rng, (N, K), np.float32, sigma=0.02))
+    ns, nsb = (N, C) if gran == "row" else (1, 1)
+    need = max(Q.qsync_absmax_workspace_bytes(M, C, Q.PER_TENSOR), Q.qsync_absmax_workspace_bytes(N, K, Q.PER_TENSOR),
+               Q.qsync_conv3x3_prepare_weights_workspace_bytes(N, C) if taps == 9 else 0)
+    g = Q.PER_ROW if gran == "row" else Q.PER_TENSOR
+
+    def buffers():
+        f = lambda n: torch.full((n,), -3.0, dtype=torch.float32, device="cuda")
+        e = lambda r, c: torch.full((r, c), 77, dtype=qd, device="cuda")
+        inp = x_from == "in place"
+        return dict(sx=f(1), ix=f(1), ax=f(1), sw=f(ns), iw=f(ns), aw=f(ns), swb=f(nsb), iwb=f(nsb), xq=None if inp else e(M, C),
+                    xqT=e(C, M) if with_t else None, wq=e(N, K), wqbT=e(C, taps * N),
+                    amax=x.float().abs().max().reshape(1).clone() if x_from == "amax" else None)
+
+    def separate(b, wx, ww):
+        if i8 and b["amax"] is None:
+            Q.qsync_absmax_quantize(x, M, C, 8, Q.ROUND_NEAREST, 0, 0, b["sx"], b["ix"], b["ax"], b["xq"], b["xqT"], wx)
+        elif i8:
+            Q.qsync_scale_from_amax(b["amax"], 8, b["sx"], b["ix"], True)
+            Q.qsync_quantize(x, M, C, C, Q.INT8, 8, Q.PER_TENSOR, Q.ROUND_NEAREST, 0, 0, b["ix"], b["xq"], b["xqT"])
+        elif b["xq"] is not None or b["xqT"] is not None:
+            Q.qsync_quantize(x, M, C, C, code, 0, 0, 0, 0, 0, None, b["xq"], b["xqT"])
+        if i8 and gran == "row" and taps == 9:
+            Q.qsync_conv3x3_prepare_weights(w, N, C, 8, b["sw"], b["iw"], b["wq"], b["swb"], b["iwb"], b["wqbT"], ww)
+        elif i8 and gran == "row":
+            Q.qsync_prepare_weights(w, N, C, 8, b["sw"], b["iw"], b["aw"], b["wq"], b["swb"], b["iwb"], b["wqbT"], ww)
+        else:
+            wT = b["wqbT"] if taps == 1 else None
+            if i8:
+                Q.qsync_absmax_quantize(w, N, K, 8, Q.ROUND_NEAREST, 0, 0, b["sw"], b["iw"], b["aw"], b["wq"], wT, ww)
+            else:
+                Q.qsync_quantize(w, N, K, K, code, 0, 0, 0, 0, 0, None, b["wq"], wT)
+            if taps == 9:
+                Q.qsync_conv3x3_wflip(b["wq"], N, C, b["wqbT"])
+
+    want = buffers()
+    separate(want, ws(need), ws(need))
+    wx, ww = ws(need), ws(need)
+    for second in (ww, wx):
+        b = buffers()
+        Q.qsync_convert_operands(code, x, M, C, b["amax"], w, N, taps, 8, g, b["sx"], b["ix"], b["ax"], b["xq"], b["xqT"], b["sw"],
+                                 b["iw"], b["aw"], b["wq"], b["swb"], b["iwb"], b["wqbT"], wx, second)
+        for name, t in want.items():
+            if t is not None:
+                assert_bits_equal(host(b[name]), host(t), name)
+
+
 def test_absmax_quantize_all_zero_and_lower_bits():
     w = ws(Q.qsync_absmax_quantize_workspace_bytes(128, 256))
     z = torch.zeros(64, 128, dtype=torch.float16, device="cuda")
