@@ -1438,7 +1438,7 @@ template <> __device__ __forceinline__ __half scaled_code<__half>(float a, float
 // goes through LDS, four rows of a column per write, and leaves as whole 128-byte (binary16) or 256-byte segments.
 // Latency bound at small sizes: one 8 x 8 patch per lane kept half the wavefronts in flight (2056x1032 fp32 -> binary16
 // with both copies 8.5 -> 7.4 us, 4096x1024 11.5 -> 9.4; fp32 8192x4096 transposed element by element 69.2 -> 54.6).
-// binary16 sources go by patches all the same (copy_f16_patch_kernel).
+// binary16 sources go by patches all the same (CopyF16Patch).
 constexpr int kConvertRows = 64;
 // conv_C > 0 (3x3 convolution weights [N, 9 * C]): column (tap, c) lands in row c * 9 + (8 - tap) of the transposed copy, as
 // for WeightQuantize.

@@ -151,6 +151,9 @@ GemmPlan plan_gemm(int prec, int64_t M, int64_t N, int64_t K, int force_tile = -
 void set_gemm_tile_override(int tile);
 // 1: launch the persistent 256x256 kernel whenever a problem is eligible; anything else: never (the default)
 void set_gemm_persistent_mode(int mode);
+// GemmProblem with conv_H > 0, not tn, checked by launch_gemm: input tile kept in LDS (conv3x3.hip); *taken is false, and nothing
+// launched, where that does not fit.  force_tile >= 0: pixels of a workgroup, 256 >> force_tile.
+hipError_t launch_conv3x3(const GemmProblem& p, int force_tile, bool* taken, hipStream_t stream);
 hipError_t launch_gemm(const GemmProblem& p, const GemmPlan& plan, void* workspace, hipStream_t stream);
 // Data and weight gradient of one operator in one launch: the tile to run both on, or -1 when their own plans are
 // estimated to be about as fast one after the other, or when dw writes what dx reads.

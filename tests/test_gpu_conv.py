@@ -67,6 +67,30 @@ def test_implicit_gemm_fp16(tile):
         assert_close(host(y), want, "Y fp16 tag")
 
 
+# one shape per route and edge: two wavefront sets on 128-byte rows with a partial last chunk; one-pixel-wide and one-row images over
+# several chunks; narrow outputs small and large; a row too wide for LDS and a wide output, which the implicit GEMM takes; 32-byte rows
+ROUTES = [(1, 40, 48, 80, 520), (2, 3, 1, 144, 40), (1, 1, 131, 272, 33), (5, 31, 29, 16, 20), (1, 5, 6, 336, 16),
+          (42, 56, 56, 16, 16), (1, 2, 3000, 16, 40), (1, 67, 64, 80, 512), (3, 104, 112, 16, 64)]
+
+
+@pytest.mark.parametrize("shape", ROUTES, ids=lambda s: "x".join(map(str, s)))
+def test_convolution_routes(shape):
+    b, h, w, c, n = shape
+    say("conv routes", *shape)
+    rng = np.random.default_rng(c + n)
+    xq, wq = rng.integers(-127, 128, (b, h, w, c)).astype(np.int8), rng.integers(-127, 128, (n, 9 * c)).astype(np.int8)
+    acc, y = empty((b * h * w, n), torch.int32), empty((b * h * w, n), torch.float32)
+    one = dev(np.ones(1, np.float32))
+    Q.qsync_conv3x3_fwd(Q.INT8, b, h, w, c, n, dev(xq), one, dev(wq), one, Q.PER_TENSOR, None, y, acc)
+    want = orc.conv3x3_fwd_f64(xq, wq.reshape(n, 3, 3, c)).reshape(-1, n)
+    assert_bits_equal(host(acc), want.astype(np.int32), "accumulators")
+    # binary16 of small integers: products and sums below 2^24 are exact in fp32, whatever their order
+    xh, wh = (xq // 16).astype(np.float16), (wq // 16).astype(np.float16)
+    Q.qsync_conv3x3_fwd(Q.FP16, b, h, w, c, n, dev(xh), None, dev(wh), None, Q.PER_TENSOR, None, y)
+    want = orc.conv3x3_fwd_f64(xh, wh.reshape(n, 3, 3, c)).reshape(-1, n)
+    assert_bits_equal(host(y), want.astype(np.float32), "Y fp16 tag")
+
+
 def test_weight_flip_bit_exact():
     rng = np.random.default_rng(62)
     for (n, c) in [(8, 16), (64, 64), (5, 3), (136, 32)]:
