@@ -13,6 +13,7 @@ from concurrent.futures import ThreadPoolExecutor
 PKG_DIR = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(PKG_DIR, "csrc")
 LIB_PATH = os.path.join(PKG_DIR, "libqsync.so")
+BINDING_PATH = os.path.join(PKG_DIR, "_native.so")      # CPython module over the library's C ABI and torch's tensors
 SOURCES = ["api.hip", "elementwise.hip", "gemm_mfma.hip", "conv3x3.hip", "gemm_f32.hip", "probe.hip", "indicator.hip"]
 
 # -ffp-contract=off: the quantizer's multiply and subtract must stay separately rounded.
@@ -85,15 +86,33 @@ def build(force: bool = True, verbose: bool = False) -> str:
                          capture_output=True, text=True)
     if res.returncode != 0:
         raise RuntimeError(f"link failed:\n{res.stderr}")
+    _build_binding()
     return LIB_PATH
 
 
+def _build_binding() -> None:
+    """Compile csrc/binding.cpp (host code only) against this interpreter and torch, linked to libqsync.so beside it."""
+    import sysconfig
+
+    import torch
+    tdir = os.path.dirname(torch.__file__)
+    rocm = os.path.dirname(os.path.dirname(os.path.realpath(_hipcc())))
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", f"-I{tdir}/include",
+           f"-I{tdir}/include/torch/csrc/api/include", f"-I{sysconfig.get_paths()['include']}", f"-I{rocm}/include",
+           "-I/opt/rocm/include", os.path.join(CSRC, "binding.cpp"), "-o", BINDING_PATH, f"-L{tdir}/lib", "-ltorch_python",
+           "-ltorch_cpu", "-lc10", "-lc10_hip", f"-L{PKG_DIR}", "-l:libqsync.so", "-Wl,-rpath,$ORIGIN"]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError(f"binding failed:\n{res.stderr}")
+
+
 def library_is_stale() -> bool:
-    """True when any kernel source or header is newer than the built library."""
-    if not os.path.exists(LIB_PATH):
+    """True when any source or header is newer than the built library or the binding."""
+    if not (os.path.exists(LIB_PATH) and os.path.exists(BINDING_PATH)):
         return True
-    built = os.path.getmtime(LIB_PATH)
-    deps = [os.path.join(CSRC, f) for f in os.listdir(CSRC) if f.endswith((".hip", ".h"))]
+    built = min(os.path.getmtime(LIB_PATH), os.path.getmtime(BINDING_PATH))
+    deps = [os.path.join(CSRC, f) for f in os.listdir(CSRC) if f.endswith((".hip", ".h", ".cpp"))]
     inc = os.path.join(os.path.dirname(PKG_DIR), "include")
     deps += [os.path.join(inc, f) for f in os.listdir(inc) if f.endswith(".h")]
     return any(os.path.getmtime(d) > built for d in deps)
@@ -104,7 +123,7 @@ def ensure_built(rebuild_if_stale: bool = False) -> str:
     check load what is built; with `rebuild_if_stale` (the benchmark) a library older than any of its
     sources is rebuilt as well, and if that is impossible (no compiler) the call fails instead of timing
     stale code."""
-    if not os.path.exists(LIB_PATH) or (rebuild_if_stale and library_is_stale()):
+    if not (os.path.exists(LIB_PATH) and os.path.exists(BINDING_PATH)) or (rebuild_if_stale and library_is_stale()):
         return build(force=True)
     return LIB_PATH
 
