@@ -369,6 +369,20 @@ int qsync_qlinear_bwd_rm(int tag, int64_t M, int64_t N, int64_t K, const void* d
 size_t qsync_qlinear_bwd_rm_workspace_bytes(int tag, int64_t M, int64_t N, int64_t K);
 
 /*
+ * qsync_qlinear_backward - the whole FP16 or FP32 backward of one linear operator from the gradient as it arrives: qsync_quantize of
+ * dy (tag FP16 or FP32) into dyq_opt [M,N] and dyqT_opt [N,M], then qsync_qlinear_bwd_rm (x_rowmajor 1: x is [M,K]) or
+ * qsync_qlinear_bwd (0: x is [K,M], dyqT_opt is read) with dy_float = dy, whose arguments, workspaces and errors it shares.
+ * Paper: proof of Prop. 1 (dX = dY W, dW = dY^T X, db); Cost Mapper paragraph (casting cost of the gradient).
+ * One pass over an fp32 dy casts it and sums its columns; the sums are finished beside the last GEMM where that launch can
+ * take them.
+ * dyq_opt   NULL: dy, of the operand type (QSYNC_ERR_UNSUPPORTED otherwise), is used as it is.
+ * Outputs equal those of the separate calls, except that db may be added up in another order.
+ */
+int qsync_qlinear_backward(int tag, int64_t M, int64_t N, int64_t K, const void* dy, int dydt, void* dyq_opt, void* dyqT_opt, const void* x,
+                           int x_rowmajor, const void* wqbT, void* dx_opt, int dxdt, void* dw_opt, int dwdt, float* db_opt,
+                           void* workspace, size_t workspace_bytes, void* stream);
+
+/*
  * qsync_qlinear_bwd_fp16_of_int8 - backward of an INT8 operator the way the paper runs it: in FP16, on the
  * dequantized codes the forward saved.  Paper: footnote of the Cost Mapper paragraph (integer backward is
  * inefficient, the backward of fixed-point kernels is executed in FP16 and incurs additional casting);

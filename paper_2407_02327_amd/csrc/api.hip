@@ -60,6 +60,44 @@ GemmProblem data_gradient(int tag, int64_t M, int64_t N, int64_t K, const void* 
     return p;
 }
 
+bool overlap(const void* a, int64_t a_bytes, const void* b, int64_t b_bytes)
+{
+    const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+    return a && b && x < y + static_cast<uintptr_t>(b_bytes) && y < x + static_cast<uintptr_t>(a_bytes);
+}
+
+// (Beside the last launch and with the cast of dY summing its columns, whole steps: FP16 2056x1000x1032 from fp32 gradients 61.7
+// -> 56.1 us, INT8 forward with FP16 backward 4096x768x3072 123.5 -> 121.4 -- with the two dequantizations in one launch --,
+// fp32 8192x4096x1024 1611 -> 1580.)
+// The gradient GEMMs that are wanted, in one launch where that is estimated faster, and the fold of the column sums: in
+// workgroups of the last launch that can take it, unless the sums go where the GEMMs read or write.
+int run_gradients(const GemmProblem* dx, const GemmPlan& plan_dx, void* ws_dx, const GemmProblem* dw, const GemmPlan& plan_dw, void* ws_dw,
+                  ColumnFoldArgs fold, hipStream_t st)
+{
+    auto touches = [&](const GemmProblem* p) {
+        const int64_t esz = p ? p->prec / 8 : 0, n = fold.cols * 4;
+        return p && (overlap(fold.out, n, p->A, p->M * p->K * esz) || overlap(fold.out, n, p->B, p->N * p->K * esz)
+                     || overlap(fold.out, n, p->C, p->M * p->N * (p->c_dtype == kF16 ? 2 : 4)) || overlap(fold.out, n, p->acc_dump, p->M * p->N * 4)
+                     || overlap(fold.out, n, p->s0, 4) || overlap(fold.out, n, p->s1, 4) || overlap(fold.out, n, p->col_scale, p->N * 4));
+    };
+    const bool beside = fold.out && !touches(dx) && !touches(dw);
+    const int  pair   = dx && dw ? gradient_pair_tile(*dx, plan_dx, *dw, plan_dw) : -1;
+    g_last_pair_tile  = pair;
+    int rc = QSYNC_OK;
+    if(pair >= 0)
+    {
+        rc = hip_status(launch_gradient_pair(*dx, *dw, pair, beside ? fold : ColumnFoldArgs{}, st));
+        if(beside) fold = ColumnFoldArgs{};
+    }
+    else
+    {
+        if(dx) rc = hip_status(launch_gemm(*dx, plan_dx, ws_dx, st, beside && !dw ? &fold : nullptr));
+        if(dw && rc == QSYNC_OK) rc = hip_status(launch_gemm(*dw, plan_dw, ws_dw, st, beside ? &fold : nullptr));
+    }
+    if(rc == QSYNC_OK && fold.out) rc = hip_status(launch_column_fold(fold, st));
+    return rc;
+}
+
 }  // namespace
 
 extern "C" {
@@ -311,11 +349,12 @@ int qsync_scale_from_amax(float* amax, int bits, float* scale, float* inv_scale,
     return hip_status(launch_scale_from_amax(amax, qmax, scale, inv_scale, consume != 0, static_cast<hipStream_t>(stream)));
 }
 
-int qsync_qlinear_bwd(int tag, int64_t M, int64_t N, int64_t K, const void* dyq, const void* dyqT, const float* sdy,
-                      const void* xqT, const float* sx, const void* wqbT, const float* swb, int wbgran, void* dx_opt,
-                      int dxdt, void* dw_opt, int dwdt, float* db_opt, const void* dy_float_opt, int dydt,
-                      int32_t* acc_dx_dump_opt, int32_t* acc_dw_dump_opt, void* workspace, size_t workspace_bytes,
-                      void* stream)
+// sums: partial column sums that lie in the workspace already (their number), or 0
+static int qlinear_bwd_impl(int tag, int64_t M, int64_t N, int64_t K, const void* dyq, const void* dyqT, const float* sdy,
+                            const void* xqT, const float* sx, const void* wqbT, const float* swb, int wbgran, void* dx_opt,
+                            int dxdt, void* dw_opt, int dwdt, float* db_opt, const void* dy_float_opt, int dydt,
+                            int32_t* acc_dx_dump_opt, int32_t* acc_dw_dump_opt, void* workspace, size_t workspace_bytes,
+                            void* stream, int sums)
 {
     if(dx_opt && (!dyq || !wqbT)) return QSYNC_ERR_NULL;
     if(dw_opt && (!dyqT || !xqT)) return QSYNC_ERR_NULL;
@@ -363,31 +402,45 @@ int qsync_qlinear_bwd(int tag, int64_t M, int64_t N, int64_t K, const void* dyq,
         pdw.acc_dump = acc_dw_dump_opt;
     }
     const bool want_dx = dx_opt && M > 0 && K > 0, want_dw = dw_opt && N > 0 && K > 0;
-    void*      ws_dw   = wsb ? wsb + off_dw : nullptr;
-    int        rc      = QSYNC_OK;
-    const int  pair    = want_dx && want_dw ? gradient_pair_tile(pdx, plan_dx, pdw, plan_dw) : -1;
-    g_last_pair_tile   = pair;
-    if(pair >= 0)
-        rc = hip_status(launch_gradient_pair(pdx, pdw, pair, st));
-    else
+    ColumnFoldArgs fold;
+    if(db_opt && N > 0 && M > 0)
     {
-        if(want_dx) rc = hip_status(launch_gemm(pdx, plan_dx, wsb, st));
-        if(want_dw && rc == QSYNC_OK) rc = hip_status(launch_gemm(pdw, plan_dw, ws_dw, st));
+        float* part = reinterpret_cast<float*>(wsb + off_db);
+        if(sums > 0) fold = ColumnFoldArgs{part, sums, N, db_opt};
+        else
+        {
+            const int rc = hip_status(launch_colsum_partials(dy_float_opt, dydt, M, N, db_opt, part, &fold, st));
+            if(rc != QSYNC_OK) return rc;
+        }
     }
-    if(rc != QSYNC_OK) return rc;
-    if(db_opt && N > 0 && M == 0)
-    {   // no rows to sum: the bias gradient is zero (the column-sum kernels need their workspace, which an
-        // empty batch does not have to bring)
-        const int rc = hip_status(launch_zero_f32(db_opt, N, st));
-        if(rc != QSYNC_OK) return rc;
-    }
-    else if(db_opt && N > 0)
-    {
-        const int rc = hip_status(launch_colsum(dy_float_opt, dydt, M, N, db_opt,
-                                                reinterpret_cast<float*>(wsb + off_db), st));
-        if(rc != QSYNC_OK) return rc;
-    }
-    return QSYNC_OK;
+    const int rc = run_gradients(want_dx ? &pdx : nullptr, plan_dx, wsb, want_dw ? &pdw : nullptr, plan_dw, wsb ? wsb + off_dw : nullptr, fold, st);
+    // no rows to sum: the bias gradient is zero (the column-sum kernels need their workspace, which an empty batch does not
+    // have to bring)
+    if(rc == QSYNC_OK && db_opt && N > 0 && M == 0) return hip_status(launch_zero_f32(db_opt, N, st));
+    return rc;
+}
+
+int qsync_qlinear_bwd(int tag, int64_t M, int64_t N, int64_t K, const void* dyq, const void* dyqT, const float* sdy,
+                      const void* xqT, const float* sx, const void* wqbT, const float* swb, int wbgran, void* dx_opt,
+                      int dxdt, void* dw_opt, int dwdt, float* db_opt, const void* dy_float_opt, int dydt,
+                      int32_t* acc_dx_dump_opt, int32_t* acc_dw_dump_opt, void* workspace, size_t workspace_bytes,
+                      void* stream)
+{
+    return qlinear_bwd_impl(tag, M, N, K, dyq, dyqT, sdy, xqT, sx, wqbT, swb, wbgran, dx_opt, dxdt, dw_opt, dwdt, db_opt, dy_float_opt,
+                            dydt, acc_dx_dump_opt, acc_dw_dump_opt, workspace, workspace_bytes, stream, 0);
+}
+
+// Row-major backward: data gradient's and weight gradient's partial products, then the column sums, behind both so that they can be
+// folded last.  A workspace without room for the column sums there keeps them behind the transposed form's parts, folded first.
+static size_t rm_products_bytes(int tag, int64_t M, int64_t N, int64_t K)
+{
+    return round256(plan_gemm(tag, M, K, N).workspace) + round256(plan_gemm(tag, N, K, M, -1, -1, true, /*tn=*/M > 0).workspace);
+}
+static size_t rm_sums_offset(int tag, int64_t M, int64_t N, int64_t K)
+{
+    const size_t nt = round256(plan_gemm(tag, M, K, N).workspace) + round256(plan_gemm(tag, N, K, M).workspace);
+    const size_t rm = rm_products_bytes(tag, M, N, K);
+    return nt > rm ? nt : rm;
 }
 
 size_t qsync_qlinear_bwd_rm_workspace_bytes(int tag, int64_t M, int64_t N, int64_t K)
@@ -395,15 +448,14 @@ size_t qsync_qlinear_bwd_rm_workspace_bytes(int tag, int64_t M, int64_t N, int64
     if((tag != QSYNC_INT8 && tag != QSYNC_FP16) || M < 0 || N < 0 || K < 0) return 0;
     // the data gradient (and bias gradient) go through qsync_qlinear_bwd, which asks for its own full size
     const size_t nt = qsync_qlinear_bwd_workspace_bytes(tag, M, N, K);
-    const size_t rm = round256(plan_gemm(tag, M, K, N).workspace)
-                    + round256(plan_gemm(tag, N, K, M, -1, -1, true, /*tn=*/true).workspace);
+    const size_t rm = rm_sums_offset(tag, M, N, K) + round256(colsum_workspace_bytes(M, N));
     return nt > rm ? nt : rm;
 }
 
-int qsync_qlinear_bwd_rm(int tag, int64_t M, int64_t N, int64_t K, const void* dyq, const float* sdy, const void* xq, const float* sx,
-                         const void* wqbT, const float* swb, int wbgran, void* dx_opt, int dxdt, void* dw_opt, int dwdt,
-                         float* db_opt, const void* dy_float_opt, int dydt, int32_t* acc_dx_dump_opt,
-                         int32_t* acc_dw_dump_opt, void* workspace, size_t workspace_bytes, void* stream)
+static int qlinear_bwd_rm_impl(int tag, int64_t M, int64_t N, int64_t K, const void* dyq, const float* sdy, const void* xq, const float* sx,
+                               const void* wqbT, const float* swb, int wbgran, void* dx_opt, int dxdt, void* dw_opt, int dwdt,
+                               float* db_opt, const void* dy_float_opt, int dydt, int32_t* acc_dx_dump_opt,
+                               int32_t* acc_dw_dump_opt, void* workspace, size_t workspace_bytes, void* stream, int sums)
 {
     if(!is_tag(tag)) return QSYNC_ERR_BAD_ENUM;
     if(tag != QSYNC_INT8 && tag != QSYNC_FP16) return QSYNC_ERR_UNSUPPORTED;
@@ -433,34 +485,82 @@ int qsync_qlinear_bwd_rm(int tag, int64_t M, int64_t N, int64_t K, const void* d
     p.s0 = i8 ? sdy : nullptr; p.s1 = i8 ? sx : nullptr; p.acc_dump = acc_dw_dump_opt;
     p.tn = M > 0;      // (empty contraction: the NT form writes the zeros, no operand is read)
     const GemmProblem pdx  = data_gradient(tag, M, N, K, dyq, sdy, wqbT, swb, wbgran, dx_opt, dxdt, acc_dx_dump_opt);
-    const int         pair = dx_opt && want_dw ? gradient_pair_tile(pdx, plan_dx, p, plan) : -1;
-    if(pair >= 0)
-    {   // (a workspace is asked for as if the two ran by their own plans)
-        const bool part = plan_dx.workspace > 0 || (db_opt && M > 0);
-        if(part && (!workspace || workspace_bytes < qsync_qlinear_bwd_workspace_bytes(tag, M, N, K))) return QSYNC_ERR_WORKSPACE;
-        if(plan.workspace > 0 && (!workspace || workspace_bytes < qsync_qlinear_bwd_rm_workspace_bytes(tag, M, N, K))) return QSYNC_ERR_WORKSPACE;
-        if((part || plan.workspace > 0) && !aligned16(workspace)) return QSYNC_ERR_ALIGN;
-        g_last_pair_tile = pair;
-        const int rc = hip_status(launch_gradient_pair(pdx, p, pair, static_cast<hipStream_t>(stream)));
+    const bool want_dx = dx_opt && M > 0 && K > 0, want_db = db_opt && M > 0 && N > 0;
+    const size_t nt = qsync_qlinear_bwd_workspace_bytes(tag, M, N, K), products = rm_products_bytes(tag, M, N, K);
+    const bool   need_nt = (dx_opt && plan_dx.workspace > 0) || want_db, need_rm = want_dw && plan.workspace > 0;
+    if((need_nt && (!workspace || workspace_bytes < nt)) || (need_rm && (!workspace || workspace_bytes < (nt > products ? nt : products))))
+        return QSYNC_ERR_WORKSPACE;
+    if((need_nt || need_rm) && !aligned16(workspace)) return QSYNC_ERR_ALIGN;
+    hipStream_t st  = static_cast<hipStream_t>(stream);
+    char*       wsb = static_cast<char*>(workspace);
+    int         rc  = QSYNC_OK;
+    ColumnFoldArgs fold;
+    if(want_db)
+    {
+        const bool   last = workspace_bytes >= rm_sums_offset(tag, M, N, K) + colsum_workspace_bytes(M, N);
+        float* const part = reinterpret_cast<float*>(wsb + (last ? rm_sums_offset(tag, M, N, K)
+                                                                 : round256(plan_dx.workspace) + round256(plan_gemm(tag, N, K, M).workspace)));
+        if(sums > 0) fold = ColumnFoldArgs{part, sums, N, db_opt};
+        else rc = hip_status(launch_colsum_partials(dy_float_opt, dydt, M, N, db_opt, part, &fold, st));
+        if(rc == QSYNC_OK && !last)
+        {
+            rc   = hip_status(launch_column_fold(fold, st));
+            fold = ColumnFoldArgs{};
+        }
         if(rc != QSYNC_OK) return rc;
     }
-    // the data gradient by itself is the NT GEMM of qsync_qlinear_bwd, which also owns the bias gradient
-    if((dx_opt && pair < 0) || db_opt)
+    rc = run_gradients(want_dx ? &pdx : nullptr, plan_dx, wsb, want_dw ? &p : nullptr, plan, wsb ? wsb + off_dw : nullptr, fold, st);
+    if(rc == QSYNC_OK && db_opt && N > 0 && M == 0) return hip_status(launch_zero_f32(db_opt, N, st));
+    return rc;
+}
+
+int qsync_qlinear_bwd_rm(int tag, int64_t M, int64_t N, int64_t K, const void* dyq, const float* sdy, const void* xq, const float* sx,
+                         const void* wqbT, const float* swb, int wbgran, void* dx_opt, int dxdt, void* dw_opt, int dwdt,
+                         float* db_opt, const void* dy_float_opt, int dydt, int32_t* acc_dx_dump_opt,
+                         int32_t* acc_dw_dump_opt, void* workspace, size_t workspace_bytes, void* stream)
+{
+    return qlinear_bwd_rm_impl(tag, M, N, K, dyq, sdy, xq, sx, wqbT, swb, wbgran, dx_opt, dxdt, dw_opt, dwdt, db_opt, dy_float_opt, dydt,
+                               acc_dx_dump_opt, acc_dw_dump_opt, workspace, workspace_bytes, stream, 0);
+}
+
+int qsync_qlinear_backward(int tag, int64_t M, int64_t N, int64_t K, const void* dy, int dydt, void* dyq_opt, void* dyqT_opt, const void* x,
+                           int x_rowmajor, const void* wqbT, void* dx_opt, int dxdt, void* dw_opt, int dwdt, float* db_opt,
+                           void* workspace, size_t workspace_bytes, void* stream)
+{
+    if(!is_tag(tag) || !is_float_dtype(dydt) || (x_rowmajor != 0 && x_rowmajor != 1)) return QSYNC_ERR_BAD_ENUM;
+    if(tag == QSYNC_INT8) return QSYNC_ERR_UNSUPPORTED;
+    if(!dy) return QSYNC_ERR_NULL;
+    const void* dyq = dyq_opt ? dyq_opt : dy;
+    if(!dyq_opt && (dydt == QSYNC_F16) != (tag == QSYNC_FP16)) return QSYNC_ERR_UNSUPPORTED;      // used as it is: of the operand type
+    int sums = 0;
+    if(dyq_opt || dyqT_opt)
     {
-        const int rc = qsync_qlinear_bwd(tag, M, N, K, dyq, nullptr, sdy, nullptr, nullptr, wqbT, swb, wbgran, pair < 0 ? dx_opt : nullptr,
-                                         dxdt, nullptr, dwdt, db_opt, dy_float_opt, dydt, acc_dx_dump_opt, nullptr, workspace,
-                                         workspace_bytes, stream);
-        if(rc != QSYNC_OK) return rc;
+        const bool   shape = count_ok(M, N) && count_ok(M, K) && count_ok(N, K) && M > 0 && N > 0 && K > 0;
+        const size_t need  = !shape ? 0 : x_rowmajor ? qsync_qlinear_bwd_rm_workspace_bytes(tag, M, N, K) : qsync_qlinear_bwd_workspace_bytes(tag, M, N, K);
+        bool         taken = false;
+        if(shape && db_opt && dydt == QSYNC_F32 && workspace && workspace_bytes >= need && aligned16(workspace)
+           && (!x_rowmajor || tag == QSYNC_FP16))
+        {   // the cast reads dY once for both
+            const size_t off = x_rowmajor ? rm_sums_offset(tag, M, N, K)
+                                          : round256(plan_gemm(tag, M, K, N).workspace) + round256(plan_gemm(tag, N, K, M).workspace);
+            ColumnFoldArgs fold;
+            const int rc = hip_status(launch_convert_sums(static_cast<const float*>(dy), M, N, tag == QSYNC_FP16 ? kF16 : kF32, dyq_opt, dyqT_opt,
+                                                          db_opt, reinterpret_cast<float*>(static_cast<char*>(workspace) + off), &fold, &taken,
+                                                          static_cast<hipStream_t>(stream)));
+            if(rc != QSYNC_OK) return rc;
+            sums = taken ? fold.S : 0;
+        }
+        if(!taken)
+        {
+            const int rc = qsync_quantize(dy, dydt, M, N, N, tag, 0, QSYNC_PER_TENSOR, QSYNC_ROUND_NEAREST, 0, 0, nullptr, dyq_opt, dyqT_opt, stream);
+            if(rc != QSYNC_OK) return rc;
+        }
     }
-    g_last_pair_tile = pair;
-    if(!want_dw || pair >= 0) return QSYNC_OK;
-    if(plan.workspace > 0)
-    {
-        if(!workspace || workspace_bytes < qsync_qlinear_bwd_rm_workspace_bytes(tag, M, N, K)) return QSYNC_ERR_WORKSPACE;
-        if(!aligned16(workspace)) return QSYNC_ERR_ALIGN;
-    }
-    return hip_status(launch_gemm(p, plan, workspace ? static_cast<char*>(workspace) + off_dw : nullptr,
-                                  static_cast<hipStream_t>(stream)));
+    if(x_rowmajor)
+        return qlinear_bwd_rm_impl(tag, M, N, K, dyq, nullptr, x, nullptr, wqbT, nullptr, QSYNC_PER_TENSOR, dx_opt, dxdt, dw_opt, dwdt, db_opt,
+                                   dy, dydt, nullptr, nullptr, workspace, workspace_bytes, stream, sums);
+    return qlinear_bwd_impl(tag, M, N, K, dyq, dyqT_opt, nullptr, x, nullptr, wqbT, nullptr, QSYNC_PER_TENSOR, dx_opt, dxdt, dw_opt, dwdt,
+                            db_opt, dy, dydt, nullptr, nullptr, workspace, workspace_bytes, stream, sums);
 }
 
 // Workspace of qsync_qlinear_bwd_fp16_of_int8: binary16 operands of the FP16 backward, then the GEMMs' own scratch;
@@ -522,25 +622,22 @@ int qsync_qlinear_bwd_fp16_of_int8(int64_t M, int64_t N, int64_t K, const void* 
     void *xhT = base + l.off_xhT, *wh = base + l.off_wh, *whT = base + l.off_whT, *dyhT = base + l.off_dyhT;
     const void* dyh = dydt == QSYNC_F16 ? dy : base + l.off_dyh;
     hipError_t e = hipSuccess;
-    if(dw_opt && x_rowmajor)      // x_hat = code * q_x narrowed to binary16, [M,K] like the codes (xqT holds xq here)
-        e = launch_dequantize_f16_tiles(static_cast<const int8_t*>(xqT), M, K, nullptr, sx, xhT, nullptr, st);
-    else if(dw_opt)      // x_hat^T, straight from the saved transposed codes
-        e = launch_dequantize_f16_tiles(static_cast<const int8_t*>(xqT), K, M, nullptr, sx, xhT, nullptr, st);
-    if(e == hipSuccess && dx_opt)      // w_hat with the forward's scales (one per output channel, or one) and its transpose for dX
-        e = launch_dequantize_f16_tiles(static_cast<const int8_t*>(wq), N, K, wgran == QSYNC_PER_ROW ? sw : nullptr,
-                                       wgran == QSYNC_PER_ROW ? nullptr : sw, wh, whT, st);
+    // x_hat = code * q_x narrowed to binary16, [M,K] or [K,M] like the codes; w_hat with the forward's scales (one per output
+    // channel, or one) and its transpose for dX: side by side when both are wanted
+    const int64_t xr = x_rowmajor ? M : K, xc = x_rowmajor ? K : M;
+    const float *w_rows = wgran == QSYNC_PER_ROW ? sw : nullptr, *w_one = wgran == QSYNC_PER_ROW ? nullptr : sw;
+    if(dw_opt && dx_opt)
+        e = launch_dequantize_f16_both(static_cast<const int8_t*>(xqT), xr, xc, sx, xhT, static_cast<const int8_t*>(wq), N, K, w_rows, w_one, wh, whT, st);
+    else if(dw_opt)
+        e = launch_dequantize_f16_tiles(static_cast<const int8_t*>(xqT), xr, xc, nullptr, sx, xhT, nullptr, st);
+    else if(dx_opt)
+        e = launch_dequantize_f16_tiles(static_cast<const int8_t*>(wq), N, K, w_rows, w_one, wh, whT, st);
+    if(e != hipSuccess) return hip_status(e);
+    // dY narrowed to binary16 (or used in place) and transposed, then the FP16 gradients
     void* const dyh_out  = dydt == QSYNC_F16 ? nullptr : const_cast<void*>(dyh);
     void* const dyhT_out = (dw_opt && !x_rowmajor) ? dyhT : nullptr;
-    if(e == hipSuccess && (dyh_out || dyhT_out))      // dY narrowed to binary16 (or used in place) and transposed
-        e = launch_convert(dy, dydt == QSYNC_F16 ? kF16 : kF32, M, N, N, kF16, dyh_out, dyhT_out, st);
-    if(e != hipSuccess) return hip_status(e);
-    if(x_rowmajor)
-        return qsync_qlinear_bwd_rm(QSYNC_FP16, M, N, K, dyh, nullptr, xhT, nullptr, whT, nullptr, QSYNC_PER_TENSOR, dx_opt, dxdt,
-                                    dw_opt, dwdt, db_opt, dy, dydt, nullptr, nullptr, base + l.off_gemm,
-                                    workspace_bytes - l.off_gemm, stream);
-    return qsync_qlinear_bwd(QSYNC_FP16, M, N, K, dyh, dyhT, nullptr, xhT, nullptr, whT, nullptr, QSYNC_PER_TENSOR, dx_opt, dxdt,
-                             dw_opt, dwdt, db_opt, dy, dydt, nullptr, nullptr, base + l.off_gemm, workspace_bytes - l.off_gemm,
-                             stream);
+    return qsync_qlinear_backward(QSYNC_FP16, M, N, K, dy, dydt, dyh_out, dyhT_out, xhT, x_rowmajor, whT, dx_opt, dxdt, dw_opt, dwdt, db_opt,
+                                  base + l.off_gemm, workspace_bytes - l.off_gemm, stream);
 }
 
 int qsync_prepare_weights(const void* w, int wdt, int64_t N, int64_t K, int bits, float* sw, float* iw, float* aw_opt,

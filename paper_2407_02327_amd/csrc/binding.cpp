@@ -177,7 +177,7 @@ PyMethodDef methods[] = {
     ENTRY(qsync_absmax_scale), ENTRY(qsync_absmax_scale_static), ENTRY(qsync_quantize), ENTRY(qsync_absmax_quantize),
     ENTRY(qsync_gradient_quantize), ENTRY(qsync_convert_operands), ENTRY(qsync_qlinear_fwd), ENTRY(qsync_qlinear_fwd_amax),
     ENTRY(qsync_qlinear_fwd_codes), ENTRY(qsync_transpose_i8), ENTRY(qsync_scale_from_amax), ENTRY(qsync_qlinear_bwd),
-    ENTRY(qsync_qlinear_bwd_rm), ENTRY(qsync_qlinear_bwd_fp16_of_int8), ENTRY(qsync_conv3x3_fwd), ENTRY(qsync_conv3x3_fwd_amax),
+    ENTRY(qsync_qlinear_bwd_rm), ENTRY(qsync_qlinear_backward), ENTRY(qsync_qlinear_bwd_fp16_of_int8), ENTRY(qsync_conv3x3_fwd), ENTRY(qsync_conv3x3_fwd_amax),
     ENTRY(qsync_conv3x3_wgrad), ENTRY(qsync_conv3x3_prepare_weights), ENTRY(qsync_conv3x3_wflip), ENTRY(qsync_im2col3x3_i8),
     ENTRY(qsync_prepare_weights), ENTRY(qsync_dequantize), {nullptr, nullptr, 0, nullptr}};
 

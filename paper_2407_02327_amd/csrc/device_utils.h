@@ -5,6 +5,8 @@
 #include <hip/hip_fp16.h>
 #include <stdint.h>
 
+#include "kernels.h"
+
 namespace qsync {
 
 constexpr int kWaveSize = 64;
@@ -51,6 +53,35 @@ __device__ __forceinline__ float block_reduce_sum(float v, float* lds /* >= 16 f
         for(int i = 1; i < nw; ++i) v += lds[i];
     }
     return v;
+}
+
+// One column of S partials [S][cols]: thread q < 16 of the column folds every sixteenth partial, then the sixteen are folded in
+// order (fixed assignment, fixed order).  The first 256 threads of the workgroup take part; the result is valid for q == 0.
+template <bool MAX> __device__ __forceinline__ float fold_column(const float* __restrict__ partial, int S, int64_t cols, int64_t c, int q, float* lds)
+{
+    float acc = 0.0f;
+    if(c < cols && threadIdx.x < 256)
+    {
+#pragma unroll 8                              // independent loads in flight; the fold keeps its order
+        for(int s = q; s < S; s += 16)
+        {
+            const float o = partial[static_cast<int64_t>(s) * cols + c];
+            acc = MAX ? fmaxf(acc, o) : acc + o;
+        }
+    }
+    if(threadIdx.x < 256) lds[threadIdx.x] = acc;
+    __syncthreads();
+    float t = 0.0f;
+    if(q == 0)
+        for(int i = 0; i < 16; ++i) t = MAX ? fmaxf(t, lds[i * 16 + threadIdx.x % 16]) : t + lds[i * 16 + threadIdx.x % 16];
+    return t;
+}
+__device__ __forceinline__ void fold_columns(const ColumnFoldArgs& f, uint32_t block, float* lds /* 256 floats */)
+{
+    const int     q = threadIdx.x / 16;
+    const int64_t c = static_cast<int64_t>(block) * 16 + threadIdx.x % 16;
+    const float   t = fold_column<false>(f.partial, f.S, f.cols, c, q, lds);
+    if(q == 0 && c < f.cols) f.out[c] = t;
 }
 
 // Element access that widens to fp32 (binary16 -> fp32 is exact).

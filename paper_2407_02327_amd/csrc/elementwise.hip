@@ -495,25 +495,6 @@ __global__ __launch_bounds__(BLOCK) void colreduce_kernel(const T* __restrict__ 
 // Second launch of the two-launch form: 16 columns per block; sixteen threads per column fold a
 // sixteenth of the partials each (fixed assignment, fixed order), then the sixteen are folded in order.
 // OP_SUMMAX: the last block folds the `nmax` block maxima (and sums of squares) of the tensor instead.
-template <int OP> __device__ __forceinline__ float fold_column(const float* __restrict__ partial, int S, int64_t cols, int64_t c, int q, float* lds)
-{   // (the first 256 threads; the result is valid in those with q == 0)
-    float acc = 0.0f;
-    if(c < cols && threadIdx.x < kBlock)
-    {
-#pragma unroll 8                              // independent loads in flight; the fold keeps its order
-        for(int s = q; s < S; s += 16)
-        {
-            const float o = partial[static_cast<int64_t>(s) * cols + c];
-            acc = OP == OP_MAX ? fmaxf(acc, o) : acc + o;
-        }
-    }
-    if(threadIdx.x < kBlock) lds[threadIdx.x] = acc;
-    __syncthreads();
-    float t = 0.0f;
-    if(q == 0)
-        for(int i = 0; i < 16; ++i) t = OP == OP_MAX ? fmaxf(t, lds[i * 16 + threadIdx.x % 16]) : t + lds[i * 16 + threadIdx.x % 16];
-    return t;
-}
 template <int OP>
 __global__ __launch_bounds__(kBlock) void colreduce_finalize_kernel(const float* __restrict__ partial, int S,
                                                                     int64_t cols, float qmax, float* out,
@@ -535,7 +516,7 @@ __global__ __launch_bounds__(kBlock) void colreduce_finalize_kernel(const float*
         }
     const int     tc = threadIdx.x % 16, q = threadIdx.x / 16;
     const int64_t c  = static_cast<int64_t>(blockIdx.x) * 16 + tc;
-    const float   t  = fold_column<OP>(partial, S, cols, c, q, lds);
+    const float   t  = fold_column<OP == OP_MAX>(partial, S, cols, c, q, lds);
     if(q == 0 && c < cols)
     {
         if(OP == OP_MAX)
@@ -549,17 +530,8 @@ __global__ __launch_bounds__(kBlock) void colreduce_finalize_kernel(const float*
 template <int THREADS> struct ColumnFold
 {
     static constexpr int kThreads = THREADS, kLds = kBlock * 4;
-    const float* partial;
-    int          S;
-    int64_t      cols;
-    float*       out;
-    __device__ __forceinline__ void run(uint32_t block, uint8_t* lds) const
-    {
-        const int     q = threadIdx.x / 16;
-        const int64_t c = static_cast<int64_t>(block) * 16 + threadIdx.x % 16;
-        const float   t = fold_column<OP_SUM>(partial, S, cols, c, q, reinterpret_cast<float*>(lds));
-        if(q == 0 && c < cols) out[c] = t;
-    }
+    ColumnFoldArgs f;
+    __device__ __forceinline__ void run(uint32_t block, uint8_t* lds) const { fold_columns(f, block, reinterpret_cast<float*>(lds)); }
 };
 
 // Column sums of a small tensor in one go: 16 columns per workgroup, THREADS / 16 row lanes (at most kColumnSumRows rows: their
@@ -1442,7 +1414,8 @@ template <> __device__ __forceinline__ __half scaled_code<__half>(float a, float
 constexpr int kConvertRows = 64;
 // conv_C > 0 (3x3 convolution weights [N, 9 * C]): column (tap, c) lands in row c * 9 + (8 - tap) of the transposed copy, as
 // for WeightQuantize.
-template <typename Ti, typename To> struct ConvertTile
+// SUMS: also the sums of the tile's columns of x, one partial per tile row.
+template <typename Ti, typename To, bool SUMS = false> struct ConvertTile
 {
     static constexpr int TC = 16 / sizeof(To);                      // columns of a thread
     static constexpr int CH = kConvertRows * sizeof(To) / 16;       // 16-byte chunks of a tile column
@@ -1455,6 +1428,7 @@ template <typename Ti, typename To> struct ConvertTile
     To*          qT;
     int          tiles_x;
     int          conv_C;
+    float*       sums;
     __device__ __forceinline__ void run(uint32_t block, uint8_t* lds_t) const
     {
         const int     by = static_cast<int>(block) / tiles_x, bx = static_cast<int>(block) - by * tiles_x;
@@ -1481,6 +1455,28 @@ template <typename Ti, typename To> struct ConvertTile
                 else out[i].v[e] = convert_elem<To, Ti>(in[i].v[e]);
             }
             if(q && ok) *reinterpret_cast<uint4*>(q + (r0 + i) * cols + c0) = out[i].w;
+        }
+        if constexpr(SUMS)
+        {
+            float* part = reinterpret_cast<float*>(lds_t);          // [16 row quads][columns of the tile]
+#pragma unroll
+            for(int e = 0; e < TC; ++e)
+            {
+                float t = 0.0f;
+#pragma unroll
+                for(int i = 0; i < 4; ++i)
+                    if(r0 + i < rows && c0 < cols) t += to_f32(in[i].v[e]);
+                part[(quad * 16 + cg) * TC + e] = t;
+            }
+            __syncthreads();
+            if(threadIdx.x < 16 * TC && tile_c + threadIdx.x < cols)
+            {
+                float t = 0.0f;
+#pragma unroll
+                for(int k = 0; k < 16; ++k) t += part[k * 16 * TC + threadIdx.x];
+                sums[by * cols + tile_c + threadIdx.x] = t;
+            }
+            __syncthreads();
         }
         if(!qT) return;
 #pragma unroll
@@ -2080,7 +2076,7 @@ static hipError_t gradient_quantize_typed(const T* x, int64_t rows, int64_t cols
     colreduce_first<T, OP_SUMMAX>(x, rows, cols, cols, partial, maxima, none, gy, nmax, st);
     const TensorScale ts{nullptr, maxima, nmax, scale, inv_scale, amax_opt};
     with_quantize_part<T, kPartials>(x, rows, cols, cols, qmax, rnd, seed, offset, ts, q, qT, [&](const auto& p, int64_t blocks) {
-        launch_parts(ColumnFold<std::decay_t<decltype(p)>::kThreads>{partial, gy, cols, colsum}, fold_blocks, p, blocks, st);
+        launch_parts(ColumnFold<std::decay_t<decltype(p)>::kThreads>{{partial, gy, cols, colsum}}, fold_blocks, p, blocks, st);
     });
     return hipGetLastError();
 }
@@ -2155,9 +2151,9 @@ hipError_t launch_prepare_weights(const void* w, int wdt, int64_t N, int64_t K, 
 }
 
 // The tiled conversion as a part, f(part, workgroups), where its vector rules hold; false: f was not called.
-template <typename Ti, typename To, typename F>
+template <typename Ti, typename To, bool SUMS = false, typename F>
 static bool with_convert_tiles(const Ti* x, int64_t rows, int64_t cols, int64_t ld, const float* row_scale, const float* scale, To* q,
-                               To* qT, int conv_C, F&& f)
+                               To* qT, int conv_C, F&& f, float* sums = nullptr)
 {
     constexpr int64_t TC = 16 / sizeof(To), in_bytes = TC * sizeof(Ti) < 16 ? TC * sizeof(Ti) : 16;
     const int64_t     bx = (cols + 16 * TC - 1) / (16 * TC), by = (rows + kConvertRows - 1) / kConvertRows;
@@ -2165,7 +2161,7 @@ static bool with_convert_tiles(const Ti* x, int64_t rows, int64_t cols, int64_t 
     if(cols % TC != 0 || (reinterpret_cast<uintptr_t>(x) & (in_bytes - 1)) != 0 || (ld * sizeof(Ti)) % in_bytes != 0 || !aligned16(q)
        || (rows % TC == 0 && !aligned16(qT)) || bx * by >= (int64_t(1) << 30))
         return false;
-    f(ConvertTile<Ti, To>{x, rows, cols, ld, row_scale, scale, q, qT, static_cast<int>(bx), conv_C}, bx * by);
+    f(ConvertTile<Ti, To, SUMS>{x, rows, cols, ld, row_scale, scale, q, qT, static_cast<int>(bx), conv_C, sums}, bx * by);
     return true;
 }
 template <typename Ti, typename To>
@@ -2190,8 +2186,8 @@ template <typename F> static bool with_copy_patches(const __half* x, int64_t row
 }
 
 // The conversion as a part, f(part, workgroups), unless convert_kernel is to do it (false).
-template <typename Ti, typename To, typename F>
-static bool with_convert_part(const Ti* x, int64_t rows, int64_t cols, int64_t ld, To* q, To* qT, F&& f)
+template <typename Ti, typename To, bool SUMS = false, typename F>
+static bool with_convert_part(const Ti* x, int64_t rows, int64_t cols, int64_t ld, To* q, To* qT, F&& f, float* sums = nullptr)
 {
     if constexpr(std::is_same<Ti, __half>::value && std::is_same<To, __half>::value)
         if(with_copy_patches(x, rows, cols, ld, q, qT, f)) return true;
@@ -2203,7 +2199,7 @@ static bool with_convert_part(const Ti* x, int64_t rows, int64_t cols, int64_t l
     const int64_t n   = rows * cols;
     const bool    odd = std::is_same<To, __half>::value && qT && rows % 8 != 0 && rows >= 32
                      && (std::is_same<Ti, float>::value || !q ? n >= (int64_t(1) << 21) : n >= (int64_t(1) << 22) && n < (int64_t(1) << 23));
-    return !odd && with_convert_tiles(x, rows, cols, ld, nullptr, nullptr, q, qT, 0, f);
+    return !odd && with_convert_tiles<Ti, To, SUMS>(x, rows, cols, ld, nullptr, nullptr, q, qT, 0, f, sums);
 }
 
 template <typename Ti, typename To>
@@ -2386,6 +2382,19 @@ hipError_t launch_dequantize_f16_tiles(const int8_t* a, int64_t rows, int64_t co
     if(convert_tiles(a, rows, cols, cols, row_scale, scale, static_cast<__half*>(y), static_cast<__half*>(yT), stream)) return hipGetLastError();
     const hipError_t e = launch_dequantize(a, kI8, rows, cols, cols, row_scale, nullptr, 1.0f, row_scale ? nullptr : scale, nullptr, y, kF16, stream);
     return e != hipSuccess || !yT ? e : launch_convert(y, kF16, rows, cols, cols, kF16, nullptr, yT, stream);
+}
+
+hipError_t launch_dequantize_f16_both(const int8_t* x, int64_t xr, int64_t xc, const float* x_scale, void* xh, const int8_t* w, int64_t N,
+                                      int64_t K, const float* w_row_scale, const float* w_scale, void* wh, void* whT, hipStream_t st)
+{
+    bool done = false;
+    with_convert_tiles(w, N, K, K, w_row_scale, w_scale, static_cast<__half*>(wh), static_cast<__half*>(whT), 0, [&](const auto& pw, int64_t bw) {
+        done = with_convert_tiles(x, xr, xc, xc, nullptr, x_scale, static_cast<__half*>(xh), static_cast<__half*>(nullptr), 0,
+                                  [&](const auto& px, int64_t bx) { launch_parts(pw, bw, px, bx, st); });
+    });
+    if(done) return hipGetLastError();
+    const hipError_t e = launch_dequantize_f16_tiles(x, xr, xc, nullptr, x_scale, xh, nullptr, st);
+    return e != hipSuccess ? e : launch_dequantize_f16_tiles(w, N, K, w_row_scale, w_scale, wh, whT, st);
 }
 
 hipError_t launch_dequantize(const void* a, int adt, int64_t rows, int64_t cols, int64_t ld, const float* row_scale,
@@ -2578,15 +2587,44 @@ hipError_t launch_zero_f32(float* p, int64_t n, hipStream_t stream)
     return hipGetLastError();
 }
 
-hipError_t launch_colsum(const void* x, int xdt, int64_t rows, int64_t cols, float* out, float* workspace,
-                         hipStream_t stream)
+template <typename T>
+static void colsum_partials(const T* x, int64_t rows, int64_t cols, float* workspace, int& S, hipStream_t st)
 {
-    TensorFinal none{0.0f, nullptr, nullptr, nullptr, nullptr, nullptr};
-    if(xdt == kF32)
-        return colreduce_launch<float, OP_SUM>(static_cast<const float*>(x), rows, cols, cols, 0.0f, out, nullptr, nullptr,
-                                               workspace, nullptr, none, stream);
-    return colreduce_launch<__half, OP_SUM>(static_cast<const __half*>(x), rows, cols, cols, 0.0f, out, nullptr, nullptr,
-                                            workspace, nullptr, none, stream);
+    const TensorFinal none{0.0f, nullptr, nullptr, nullptr, nullptr, nullptr};
+    int               nmax;
+    colreduce_first<T, OP_SUM>(x, rows, cols, cols, workspace, nullptr, none, S, nmax, st);
+}
+hipError_t launch_colsum_partials(const void* x, int xdt, int64_t rows, int64_t cols, float* out, float* workspace, ColumnFoldArgs* fold,
+                                  hipStream_t stream)
+{
+    int S;
+    if(xdt == kF32) colsum_partials(static_cast<const float*>(x), rows, cols, workspace, S, stream);
+    else            colsum_partials(static_cast<const __half*>(x), rows, cols, workspace, S, stream);
+    *fold = ColumnFoldArgs{workspace, S, cols, out};
+    return hipGetLastError();
+}
+
+hipError_t launch_column_fold(const ColumnFoldArgs& fold, hipStream_t stream)
+{
+    launch_part(ColumnFold<kBlock>{fold}, fold.blocks(), stream);
+    return hipGetLastError();
+}
+
+template <typename To>
+static bool convert_sums(const float* x, int64_t rows, int64_t cols, void* q, void* qT, float* workspace, hipStream_t st)
+{
+    return with_convert_part<float, To, true>(x, rows, cols, cols, static_cast<To*>(q), static_cast<To*>(qT),
+                                              [&](const auto& p, int64_t blocks) { launch_part(p, blocks, st); }, workspace);
+}
+hipError_t launch_convert_sums(const float* x, int64_t rows, int64_t cols, int outdt, void* q, void* qT, float* out, float* workspace,
+                               ColumnFoldArgs* fold, bool* taken, hipStream_t stream)
+{
+    const int64_t S = (rows + kConvertRows - 1) / kConvertRows;
+    *taken = S <= kColParts && (outdt == kF16 ? convert_sums<__half>(x, rows, cols, q, qT, workspace, stream)
+                                              : convert_sums<float>(x, rows, cols, q, qT, workspace, stream));
+    if(!*taken) return hipSuccess;
+    *fold = ColumnFoldArgs{workspace, static_cast<int>(S), cols, out};
+    return hipGetLastError();
 }
 
 }  // namespace qsync

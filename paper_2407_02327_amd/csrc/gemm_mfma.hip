@@ -550,12 +550,19 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_nt_kernel(const GemmKerne
 struct GemmPairArgs
 {
     GemmKernelArgs g[2];
-    int            na;
+    int            na, total;      // workgroups of the first, of both; behind them those of the fold
+    ColumnFoldArgs fold;
 };
 template <typename TR, int BM, int BN, int WGM, int WGN, int ST, bool TNA>
 __global__ __launch_bounds__(64 * WGM * WGN) void gemm_nt_pair_kernel(const GemmPairArgs p)
 {
     const int blk = static_cast<int>(blockIdx.x);
+    if(blk >= p.total)
+    {
+        extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
+        fold_columns(p.fold, static_cast<uint32_t>(blk - p.total), reinterpret_cast<float*>(lds));
+        return;
+    }
     if constexpr(!TNA)
         gemm_tile<TR, BM, BN, WGM, WGN, ST, false, false, false>(p.g[blk < p.na ? 0 : 1], blk < p.na ? blk : blk - p.na, 1);
     else if(blk < p.na)
@@ -877,14 +884,21 @@ __global__ __launch_bounds__(kThreads) void splitk_reduce_kernel(const ACC* __re
                                                                  const float* __restrict__ col_scale,
                                                                  const float* __restrict__ col_bias, int32_t* acc_dump,
                                                                  unsigned int* amax_bits, int8_t* codes,
-                                                                 const float* code_inv_p, int code_qmax)
+                                                                 const float* code_inv_p, int code_qmax, const int blocks,
+                                                                 const ColumnFoldArgs fold)
 {
+    if(static_cast<int>(blockIdx.x) >= blocks)      // workgroups behind the reduction's own: column sums of some other tensor
+    {
+        __shared__ float lds_f[kThreads];
+        fold_columns(fold, blockIdx.x - blocks, lds_f);
+        return;
+    }
     const float code_inv = codes ? *code_inv_p : 0.0f;
     constexpr int V      = VEC4 ? 4 : 1;       // VEC4: N % 4 == 0 and 16-byte aligned buffers
     uint32_t      run    = 0u;                 // maximum of |C| as stored (fp32 bits), when amax_bits is given
     const uint32_t seen  = amax_bits ? __hip_atomic_load(amax_bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
     const int64_t n      = M * N;
-    const int64_t stride = static_cast<int64_t>(gridDim.x) * kThreads * V;
+    const int64_t stride = static_cast<int64_t>(blocks) * kThreads * V;
     float         alpha  = 1.0f;
     if(s0) alpha *= *s0;
     if(s1) alpha *= *s1;
@@ -1090,7 +1104,7 @@ hipError_t launch_pair_tile(const GemmPairArgs& p, int workgroups, hipStream_t s
         if(e != hipSuccess) return e;
         if(slot >= 0) attr_set[slot] = true;
     }
-    gemm_nt_pair_kernel<TR, BM, BN, WGM, WGN, ST, TNA><<<dim3(static_cast<unsigned>(workgroups)), dim3(64 * WGM * WGN), lds_bytes, st>>>(p);
+    gemm_nt_pair_kernel<TR, BM, BN, WGM, WGN, ST, TNA><<<dim3(static_cast<unsigned>(workgroups + p.fold.blocks())), dim3(64 * WGM * WGN), lds_bytes, st>>>(p);
     return hipGetLastError();
 }
 template <typename TR, bool TNA>
@@ -1287,7 +1301,7 @@ static hipError_t kernel_args(const GemmProblem& p, const GemmPlan& plan, void* 
     return hipSuccess;
 }
 
-hipError_t launch_gemm(const GemmProblem& p, const GemmPlan& plan, void* workspace, hipStream_t stream)
+hipError_t launch_gemm(const GemmProblem& p, const GemmPlan& plan, void* workspace, hipStream_t stream, ColumnFoldArgs* fold)
 {
     if(p.M <= 0 || p.N <= 0) return hipSuccess;
     if(p.prec == 32 && (p.conv_H > 0 || p.b_remap_C > 0)) return hipErrorInvalidValue;
@@ -1320,11 +1334,13 @@ hipError_t launch_gemm(const GemmProblem& p, const GemmPlan& plan, void* workspa
     int64_t    nb   = (p.M * p.N / (vec4 ? 4 : 1) + kThreads - 1) / kThreads;
     nb              = nb > 65536 ? 65536 : nb;
     if(p.out_amax_bits && nb > 1024) nb = 1024;    // at most one atomic per workgroup on one word: keep them few
+    const ColumnFoldArgs beside = fold ? *fold : ColumnFoldArgs{};
+    if(fold) *fold = ColumnFoldArgs{};
     auto reduce = [&](auto acc_tag, auto vec_tag, const void* ws, int32_t* dump) {
         typedef decltype(acc_tag) acc_t;
-        splitk_reduce_kernel<acc_t, decltype(vec_tag)::value><<<dim3(nb), dim3(kThreads), 0, stream>>>(
+        splitk_reduce_kernel<acc_t, decltype(vec_tag)::value><<<dim3(nb + beside.blocks()), dim3(kThreads), 0, stream>>>(
             static_cast<const acc_t*>(ws), splits, p.M, p.N, p.C, a.c_is_f16, p.s0, p.s1, p.col_scale, p.col_bias, dump,
-            p.out_amax_bits, static_cast<int8_t*>(p.out_codes), p.out_code_inv, p.out_code_qmax);
+            p.out_amax_bits, static_cast<int8_t*>(p.out_codes), p.out_code_inv, p.out_code_qmax, static_cast<int>(nb), beside);
     };
     if(p.prec == 8)
     {
@@ -1425,7 +1441,7 @@ int gradient_pair_tile(const GemmProblem& dx, const GemmPlan& plan_dx, const Gem
     return dw.tn || dw.K >= dx.K ? pair_tile(dw, dx, us) : pair_tile(dx, dw, us);
 }
 
-hipError_t launch_gradient_pair(const GemmProblem& dx, const GemmProblem& dw, int tile, hipStream_t stream)
+hipError_t launch_gradient_pair(const GemmProblem& dx, const GemmProblem& dw, int tile, const ColumnFoldArgs& fold, hipStream_t stream)
 {
     const bool         dw_first = dw.tn || dw.K >= dx.K;      // the longer contraction, or the row-major one
     const GemmProblem &a = dw_first ? dw : dx, &b = dw_first ? dx : dw;
@@ -1435,7 +1451,9 @@ hipError_t launch_gradient_pair(const GemmProblem& dx, const GemmProblem& dw, in
     if(e == hipSuccess) e = kernel_args(b, plan, nullptr, args.g[1]);
     if(e != hipSuccess) return e;
     args.na = args.g[0].tiles_m * args.g[0].tiles_n;
-    const int workgroups = args.na + args.g[1].tiles_m * args.g[1].tiles_n;
+    args.total = args.na + args.g[1].tiles_m * args.g[1].tiles_n;
+    args.fold  = fold;
+    const int workgroups = args.total;
     if(a.prec == 8)
         return a.tn ? launch_pair_traits<I8Traits, true>(tile, args, workgroups, stream) : launch_pair_traits<I8Traits, false>(tile, args, workgroups, stream);
     return a.tn ? launch_pair_traits<F16Traits, true>(tile, args, workgroups, stream) : launch_pair_traits<F16Traits, false>(tile, args, workgroups, stream);

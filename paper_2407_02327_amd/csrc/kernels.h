@@ -12,6 +12,16 @@ enum Dtype { kF32 = 0, kF16 = 1, kI8 = 2, kI32 = 3 };
 enum Gran { kPerTensor = 0, kPerRow = 1, kPerCol = 2 };
 enum Round { kNearest = 0, kStochastic = 1, kFloor = 2 };
 
+// S partial sums per column, [S][cols], still to be added up into out[cols] (16 columns per workgroup); out nullptr: nothing.
+struct ColumnFoldArgs
+{
+    const float* partial = nullptr;
+    int          S = 0;
+    int64_t      cols = 0;
+    float*       out = nullptr;
+    int64_t blocks() const { return out ? (cols + 15) / 16 : 0; }
+};
+
 // ---- absmax / scale -------------------------------------------------------------------
 constexpr int kAbsmaxMaxBlocks = 2048;  // per-tensor stage-1 partials
 constexpr int kColParts = 512;          // most stage-1 partials per column of a per-column reduction
@@ -56,6 +66,9 @@ hipError_t launch_dequantize(const void* a, int adt, int64_t rows, int64_t cols,
 // yT [cols, rows]
 hipError_t launch_dequantize_f16_tiles(const int8_t* a, int64_t rows, int64_t cols, const float* row_scale, const float* scale, void* y,
                                       void* yT, hipStream_t stream);
+// ... of the activation's codes (one scale) and of the weights' with their transpose, side by side
+hipError_t launch_dequantize_f16_both(const int8_t* x, int64_t xr, int64_t xc, const float* x_scale, void* xh, const int8_t* w, int64_t N,
+                                      int64_t K, const float* w_row_scale, const float* w_scale, void* wh, void* whT, hipStream_t st);
 hipError_t launch_prepare_weights(const void* w, int wdt, int64_t N, int64_t K, float qmax, float* sw, float* iw,
                                   float* aw_opt, int8_t* wq, float* swb, float* iwb, int8_t* wqbT, void* workspace,
                                   hipStream_t stream);
@@ -97,8 +110,14 @@ hipError_t launch_zero_f32(float* p, int64_t n, hipStream_t stream);
 // out[c, r] = in[r, c] for int8 codes, any shape (16-byte patches when rows and cols are multiples of 16)
 hipError_t launch_transpose_i8(const int8_t* in, int64_t rows, int64_t cols, int8_t* out, hipStream_t stream);
 size_t colsum_workspace_bytes(int64_t rows, int64_t cols);
-hipError_t launch_colsum(const void* x, int xdt, int64_t rows, int64_t cols, float* out, float* workspace,
-                         hipStream_t stream);
+// the partial sums of x's columns (workspace: colsum_workspace_bytes), and the fold by itself
+hipError_t launch_colsum_partials(const void* x, int xdt, int64_t rows, int64_t cols, float* out, float* workspace, ColumnFoldArgs* fold,
+                                  hipStream_t stream);
+hipError_t launch_column_fold(const ColumnFoldArgs& fold, hipStream_t stream);
+// launch_convert of a contiguous fp32 tensor that also leaves those partial sums; *taken is false, and nothing launched, where
+// the tiled conversion does not serve the tensor
+hipError_t launch_convert_sums(const float* x, int64_t rows, int64_t cols, int outdt, void* q, void* qT, float* out, float* workspace,
+                               ColumnFoldArgs* fold, bool* taken, hipStream_t stream);
 
 // ---- GEMM  C[M,N] = epilogue( sum_k A[M,k] B[N,k] ) ------------------------------------
 // epilogue(acc) = float(acc) * (s0 * s1 * col_scale[n]) + col_bias[n]; absent factors are 1 / 0.
@@ -154,11 +173,13 @@ void set_gemm_persistent_mode(int mode);
 // GemmProblem with conv_H > 0, not tn, checked by launch_gemm: input tile kept in LDS (conv3x3.hip); *taken is false, and nothing
 // launched, where that does not fit.  force_tile >= 0: pixels of a workgroup, 256 >> force_tile.
 hipError_t launch_conv3x3(const GemmProblem& p, int force_tile, bool* taken, hipStream_t stream);
-hipError_t launch_gemm(const GemmProblem& p, const GemmPlan& plan, void* workspace, hipStream_t stream);
+// fold (optional): column sums to be finished beside the reduction of K splits; cleared when that was done.
+hipError_t launch_gemm(const GemmProblem& p, const GemmPlan& plan, void* workspace, hipStream_t stream, ColumnFoldArgs* fold = nullptr);
 // Data and weight gradient of one operator in one launch: the tile to run both on, or -1 when their own plans are
 // estimated to be about as fast one after the other, or when dw writes what dx reads.
 int gradient_pair_tile(const GemmProblem& dx, const GemmPlan& plan_dx, const GemmProblem& dw, const GemmPlan& plan_dw);
-hipError_t launch_gradient_pair(const GemmProblem& dx, const GemmProblem& dw, int tile, hipStream_t stream);
+// (in workgroups behind theirs: the fold of column sums)
+hipError_t launch_gradient_pair(const GemmProblem& dx, const GemmProblem& dw, int tile, const ColumnFoldArgs& fold, hipStream_t stream);
 
 // ---- measurement probe (probe.hip): matrix instructions on register operands, no memory traffic
 constexpr int kProbeBlocks = 512;       // workgroups of 4 wavefronts, 4 matrix instructions per wavefront and iteration

@@ -32,6 +32,11 @@ def _ws(nbytes: int, device) -> Optional[torch.Tensor]:
     return torch.zeros(max(nbytes, 256), dtype=torch.uint8, device=device)
 
 
+def _scratch(nbytes: int, device) -> torch.Tensor:
+    # the GEMM calls' workspaces need no contents (clearing those of a large operator took as long as its buffers)
+    return torch.empty(max(nbytes, 256), dtype=torch.uint8, device=device)
+
+
 class QLinear:
     def __init__(self, tag: int, M: int, N: int, K: int, x_dtype=torch.float16, w_dtype=torch.float32,
                  dy_dtype=None, y_dtype=torch.float32, dx_dtype=torch.float16, dw_dtype=torch.float32,
@@ -100,15 +105,15 @@ class QLinear:
         # the weight conversion may run on a second stream beside the activation conversion: own scratch
         self.ws_absmax_w = _ws(max(Q.qsync_absmax_workspace_bytes(N, K, Q.PER_COL),
                                    Q.qsync_absmax_workspace_bytes(N, K, Q.PER_TENSOR)), dev)
-        self.ws_fwd = _ws(Q.qsync_qlinear_workspace_bytes(tag, M, N, K), dev)
-        self.ws_bwd = _ws(max(Q.qsync_qlinear_bwd_workspace_bytes(self.bwd_tag, M, N, K),
-                              Q.qsync_qlinear_bwd_rm_workspace_bytes(tag, M, N, K) if self.rowmajor_bwd else 0), dev)
+        self.ws_fwd = _scratch(Q.qsync_qlinear_workspace_bytes(tag, M, N, K), dev)
+        self.ws_bwd = _scratch(max(Q.qsync_qlinear_bwd_workspace_bytes(self.bwd_tag, M, N, K),
+                                   Q.qsync_qlinear_bwd_rm_workspace_bytes(tag, M, N, K) if self.rowmajor_bwd else 0), dev)
         if self.bwd_tag != tag:
             # FP16 backward of the INT8 forward: one C-ABI call; its workspace receives the binary16 operands
             # (dequantized X^T, dequantized W and its transpose, cast dY and its transpose)
             self.dy_dtype = dy_dtype
             nb = Q.qsync_qlinear_bwd_fp16_of_int8_workspace_bytes(M, N, K, Q._DTYPE_OF[dy_dtype])
-            self.ws_bwd16 = torch.zeros(max(nb, 256), dtype=torch.uint8, device=dev)
+            self.ws_bwd16 = _scratch(nb, dev)
 
     # Transposed operands: the kept copies, made when read by a small operator that is row-major by default, None otherwise.
     xqT = property(lambda self: self.xq.t().contiguous() if self.own_copies else self._xqT)
@@ -294,8 +299,15 @@ class QLinear:
         return self.y
 
     def backward(self, dy: torch.Tensor, stream=None):
-        self.convert_dy(dy, stream)
-        self.gemm_bwd(dy, stream)
+        if self.tag == Q.INT8:
+            self.convert_dy(dy, stream)
+            self.gemm_bwd(dy, stream)
+            return self.dx, self.dw, self.db
+        in_place = dy.dtype == _TORCH_OF_TAG[self.tag] and dy.is_contiguous() and not self.own_copies
+        self.dyq = dy if in_place else self._dyq
+        Q.qsync_qlinear_backward(self.tag, self.M, self.N, self.K, dy, None if in_place else self.dyq, self._dyqT,
+                                 self.xq if self.rowmajor_bwd else self._xqT, self.rowmajor_bwd, self.wqbT, self.dx, self.dw, self.db,
+                                 self.ws_bwd, stream)
         return self.dx, self.dw, self.db
 
 
@@ -350,8 +362,8 @@ class QConv3x3:
                                    Q.qsync_absmax_workspace_bytes(N, K, Q.PER_TENSOR)), device)
         if wgrad_via_patches and tag != Q.INT8:
             raise ValueError("QConv3x3: the patch-matrix weight gradient exists for INT8 only")
-        self.ws_bwd = _ws(Q.qsync_qlinear_bwd_workspace_bytes(tag, M, N, K) if wgrad_via_patches
-                          else Q.qsync_conv3x3_wgrad_workspace_bytes(tag, nimg, H, W, C, N), device)
+        self.ws_bwd = _scratch(Q.qsync_qlinear_bwd_workspace_bytes(tag, M, N, K) if wgrad_via_patches
+                               else Q.qsync_conv3x3_wgrad_workspace_bytes(tag, nimg, H, W, C, N), device)
 
     def convert_x(self, act: torch.Tensor, stream=None, x_amax: Optional[torch.Tensor] = None) -> None:
         """x_amax: device float holding max |act| already (the producer's `y_amax`); it replaces the pass over the

@@ -53,6 +53,7 @@ SIGNATURES = {
     "qsync_qlinear_bwd_rm": (_i, [_i, _i64, _i64, _i64, _vp, _vp, _vp, _vp, _vp, _vp, _i, _vp, _i, _vp, _i, _vp, _vp, _i, _vp, _vp,
                                  _vp, _sz, _vp]),
     "qsync_qlinear_bwd_rm_workspace_bytes": (_sz, [_i, _i64, _i64, _i64]),
+    "qsync_qlinear_backward": (_i, [_i, _i64, _i64, _i64, _vp, _i, _vp, _vp, _vp, _i, _vp, _vp, _i, _vp, _i, _vp, _vp, _sz, _vp]),
     "qsync_qlinear_bwd_fp16_of_int8": (_i, [_i64, _i64, _i64, _vp, _i, _vp, _i, _vp, _vp, _vp, _i, _vp, _i, _vp, _i, _vp, _vp, _sz,
                                            ctypes.POINTER(ctypes.c_size_t), _vp]),
     "qsync_qlinear_bwd_fp16_of_int8_workspace_bytes": (_sz, [_i64, _i64, _i64, _i]),
@@ -210,6 +211,11 @@ def qsync_qlinear_bwd_rm(tag, M, N, K, dyq, sdy, xq, sx, wqbT, swb, wbgran, dx_o
     _native.qsync_qlinear_bwd_rm(tag, M, N, K, dyq, sdy, xq, sx, wqbT, swb, wbgran, dx_opt, _or_f32(dx_opt), dw_opt,
                                  _or_f32(dw_opt), db_opt, dy_float_opt, _or_f32(dy_float_opt), acc_dx_dump_opt,
                                  acc_dw_dump_opt, workspace, workspace, stream)
+
+
+def qsync_qlinear_backward(tag, M, N, K, dy, dyq_opt, dyqT_opt, x, x_rowmajor, wqbT, dx_opt, dw_opt, db_opt, workspace, stream=None) -> None:
+    _native.qsync_qlinear_backward(tag, M, N, K, dy, dy, dyq_opt, dyqT_opt, x, int(bool(x_rowmajor)), wqbT, dx_opt, _or_f32(dx_opt),
+                                   dw_opt, _or_f32(dw_opt), db_opt, workspace, workspace, stream)
 
 
 def qsync_qlinear_bwd_fp16_of_int8_workspace_bytes(M: int, N: int, K: int, dy_dtype_code: int) -> int:

@@ -400,6 +400,22 @@ def test_convert_operands_validation():
     assert call(M=0, N=0) == qsync.OK and call(tag=16, xq=None, N=0) == qsync.OK
 
 
+def test_qlinear_backward_validation():
+    f = lib.qsync_qlinear_backward
+    need = lib.qsync_qlinear_bwd_workspace_bytes(16, 64, 64, 64)
+
+    def call(tag=16, dy=A, dydt=1, dyq=None, dyqT=A, x=A, rm=0, wT=A, dx=A, dxdt=0, dw=A, db=A, ws=A, wsb=need, M=64):
+        return f(tag, M, 64, 64, dy, dydt, dyq, dyqT, x, rm, wT, dx, dxdt, dw, 0, db, ws, wsb, None)
+
+    assert call(tag=8) == qsync.ERR_UNSUPPORTED and call(tag=9) == qsync.ERR_BAD_ENUM and call(rm=2) == qsync.ERR_BAD_ENUM
+    assert call(dydt=2) == qsync.ERR_BAD_ENUM and call(dxdt=2, dyqT=None, dw=None) == qsync.ERR_BAD_ENUM
+    assert call(dydt=0) == qsync.ERR_UNSUPPORTED                            # fp32 is no FP16 operand as it is
+    assert call(dy=None) == qsync.ERR_NULL and call(wT=None, dyqT=None, dw=None) == qsync.ERR_NULL
+    assert call(dyqT=None) == qsync.ERR_NULL                                # dW reads the transposed gradient
+    assert call(dyqT=None, dw=None, wsb=need - 256 if need else 0, ws=None) == qsync.ERR_WORKSPACE
+    assert call(M=0, dy=A, dyqT=None, dw=None, dx=None, db=None, ws=None, wsb=0) == qsync.OK
+
+
 # ---- qsync_variance_increment: a host function, so it is exercised in full here (no GPU needed) ----
 class _Stats:
     def __init__(self, sumsq, amax, D):

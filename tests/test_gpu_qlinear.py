@@ -356,6 +356,59 @@ def test_per_tensor_weights_share_codes_between_forward_and_backward():
     assert op.swb is op.sw
 
 
+# both gradients in one launch, K splits, neither; more rows than one pass of cast and column sums leaves partials for (512 x 64);
+# rows that fit no vector
+BACKWARD = [(Q.FP16, 256, 64, 128), (Q.FP16, 2056, 1000, 1032), (Q.FP16, 65, 72, 40), (Q.FP16, 4096, 768, 768), (Q.FP16, 16384, 256, 512),
+            (Q.FP16, 32832, 64, 64), (Q.FP32, 260, 36, 132), (Q.FP32, 2048, 256, 512), (Q.FP32, 65, 7, 5)]
+
+
+@pytest.mark.parametrize("case", BACKWARD, ids=lambda c: "-".join(map(str, c)))
+@pytest.mark.parametrize("act", [torch.float32, torch.float16])
+def test_whole_backward_equals_the_separate_calls(case, act):
+    """qsync_qlinear_backward through QLinear.backward against convert_dy + gemm_bwd: dX and dW bit for bit, db within the bound
+    of a recursive fp32 sum, (M - 1) 2^-24 sum |dY| per column, of the exact sums."""
+    tag, M, N, K = case
+    say("whole backward", *case, act)
+    if tag == Q.FP16 and M % 8:
+        M += 8 - M % 8                                  # (binary16 rows of dY^T are 16-byte multiples)
+    g = torch.Generator(device="cuda").manual_seed(M + N)
+    x = torch.randn(M, K, generator=g, device="cuda").to(act)
+    w = torch.randn(N, K, generator=g, device="cuda") * 0.05
+    dy = (torch.randn(M, N, generator=g, device="cuda") * 0.1).to(act)
+    op = QLinear(tag, M, N, K, x_dtype=act, y_dtype=torch.float32, dx_dtype=torch.float32)
+    op.forward(x, w)
+    op.convert_dy(dy)
+    op.gemm_bwd(dy)
+    want = [t.clone() for t in (op.dx, op.dw)]
+    dbs = [op.db.clone()]
+    for t in (op.dx, op.dw, op.db):
+        t.fill_(float("nan"))
+    dx, dw, db = op.backward(dy)
+    for got, ref, name in ((dx, want[0], "dX"), (dw, want[1], "dW")):
+        assert_bits_equal(host(got), host(ref), name)
+    exact, bound = dy.double().sum(0), (M - 1) * 2.0 ** -24 * dy.double().abs().sum(0) + 1e-30
+    for got in (db, dbs[0]):
+        assert bool(((got.double() - exact).abs() <= bound).all()), "db"
+
+
+def test_row_major_backward_takes_a_workspace_without_room_behind_the_products():
+    """The workspace that held the column sums in front of the weight gradient's partial products still does."""
+    M, N, K = 16384, 256, 512
+    say("row-major backward, smaller workspace", M, N, K)
+    g = torch.Generator(device="cuda").manual_seed(3)
+    dy, x = (torch.randn(M, n, generator=g, device="cuda").half() for n in (N, K))
+    wT = torch.randn(K, N, generator=g, device="cuda").half()
+    out = []
+    full = Q.qsync_qlinear_bwd_rm_workspace_bytes(Q.FP16, M, N, K)
+    for nbytes in (full, max(Q.qsync_qlinear_bwd_workspace_bytes(Q.FP16, M, N, K), full - 4 * 512 * N)):
+        wsp = torch.zeros(nbytes, dtype=torch.uint8, device="cuda")
+        dx, dw, db = (torch.full(s, float("nan"), device="cuda") for s in ((M, K), (N, K), (N,)))
+        Q.qsync_qlinear_bwd_rm(Q.FP16, M, N, K, dy, None, x, None, wT, None, 0, dx, dw, db, dy, None, None, wsp)
+        out.append([host(t) for t in (dx, dw, db)])
+    for a, b, name in zip(out[0], out[1], ("dX", "dW", "db")):
+        assert_bits_equal(a, b, name)
+
+
 def test_bias_gradient_from_the_backward_call():
     """db requested from qsync_qlinear_bwd itself (not from the fused absmax pass)."""
     case = wl.ragged_case(208, 144, 80, seed=31, dtype=np.float16)
