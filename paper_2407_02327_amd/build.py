@@ -14,7 +14,7 @@ PKG_DIR = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(PKG_DIR, "csrc")
 LIB_PATH = os.path.join(PKG_DIR, "libqsync.so")
 BINDING_PATH = os.path.join(PKG_DIR, "_native.so")      # CPython module over the library's C ABI and torch's tensors
-SOURCES = ["api.hip", "elementwise.hip", "gemm_mfma.hip", "conv3x3.hip", "gemm_f32.hip", "probe.hip", "indicator.hip"]
+SOURCES = ["api.hip", "elementwise.hip", "gemm_mfma.hip", "conv3x3.hip", "gemm_rows.hip", "gemm_f32.hip", "probe.hip", "indicator.hip"]
 
 # -ffp-contract=off: the quantizer's multiply and subtract must stay separately rounded.
 # packed fp32 VALU ops are disabled for the device pass (hipcc's host pass warns that it
@@ -29,7 +29,7 @@ HIPCC_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-cont
 # result before it has arrived (the compiler does not know the instruction is a memory read), so these must
 # build without any scratch memory.  Checked from the compiler's resource-usage remarks at every build.
 NO_SPILL = {"gemm_mfma.hip": ("gemm_nt_kernel", "gemm_nt_pair_kernel", "gemm_nt_persistent_kernel"),
-            "conv3x3.hip": ("conv3x3_kernel",)}
+            "conv3x3.hip": ("conv3x3_kernel",), "gemm_rows.hip": ("gemm_rows_kernel",)}
 
 
 def _check_no_spill(src: str, remarks: str) -> None:

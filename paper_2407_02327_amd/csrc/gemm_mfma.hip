@@ -1312,6 +1312,12 @@ hipError_t launch_gemm(const GemmProblem& p, const GemmPlan& plan, void* workspa
     GemmKernelArgs   a;
     const hipError_t bad = kernel_args(p, plan, workspace, a);
     if(bad != hipSuccess) return bad;
+    if(p.M <= 64 && g_tile_override < 0)
+    {
+        bool             taken = false;
+        const hipError_t e     = launch_gemm_rows(p, &taken, stream);
+        if(taken || e != hipSuccess) return e;
+    }
     if(p.conv_H > 0 && !p.tn)
     {
         bool             taken = false;

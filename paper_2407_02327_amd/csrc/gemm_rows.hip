@@ -1,0 +1,185 @@
+// C[M,N] = epilogue( sum_k A[m,k] B[n,k] ) for at most 64 rows of A (a handful of tokens), int8 and binary16.
+//
+// Such a product reads B once for little arithmetic, and on tiles of 64 columns a few dozen workgroups walk K one LDS stage
+// and barrier after the other (0.26 us per 128 bytes).  Here a
+// workgroup owns 16 columns and its eight wavefronts take K in turns of 64 bytes, each through stages of its own with three
+// turns in flight and no barrier, into the 16x16 matrix instructions; the eight sums meet in LDS once at the end.
+#include "gemm_device.h"
+
+namespace qsync {
+
+namespace {
+
+constexpr int kRowsWaves = 8, kRowsCols = 16;
+
+typedef int   v4i __attribute__((ext_vector_type(4)));
+typedef float v4f __attribute__((ext_vector_type(4)));
+template <typename TR> struct Mfma16;
+template <> struct Mfma16<I8Traits>
+{
+    typedef v4i vec;
+    __device__ static __forceinline__ vec mfma(const v4i32& a, const v4i32& b, const vec& c) { return __builtin_amdgcn_mfma_i32_16x16x64_i8(a, b, c, 0, 0, 0); }
+};
+template <> struct Mfma16<F16Traits>
+{
+    typedef v4f vec;
+    __device__ static __forceinline__ vec mfma(const v4i32& a, const v4i32& b, const vec& c)
+    {
+        return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(v8f16, a), __builtin_bit_cast(v8f16, b), c, 0, 0, 0);
+    }
+};
+
+template <int OFF> __device__ __forceinline__ void operand_read(v4i32& d, uint32_t addr)
+{
+    asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(d) : "v"(addr), "n"(OFF) : "memory");
+}
+
+// MF: fragments of 16 rows.  The B fragment is the instruction's first operand, so a lane holds four consecutive columns
+// (4 (lane / 16) ..) of output row lane % 16.
+constexpr int rows_stages(int mf) { return mf == 4 ? 3 : 4; }             // turns in LDS: 120 KB of them at most
+template <typename TR, int MF>
+__global__ __launch_bounds__(64 * kRowsWaves) void gemm_rows_kernel(const GemmKernelArgs p)
+{
+    typedef typename Mfma16<TR>::vec vec;
+    constexpr int kStages = rows_stages(MF), kLoads = MF + 1, kTurn = kLoads * 1024;
+    extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
+    const int     lane = threadIdx.x % kWaveSize, wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x / kWaveSize));
+    const int64_t n0 = static_cast<int64_t>(blockIdx.x) * kRowsCols;
+    uint8_t* const mine = lds + wave * (kStages * kTurn);
+
+    // loads: four lanes read 64 consecutive bytes of a row (lanes on sixteen rows, as the operands want them, took four times as
+    // long); the 16-byte chunks land XOR-swizzled so that sixteen rows of one chunk meet all banks
+    const int      lrow = lane / 4, lchunk = ((lane % 4) ^ ((lane >> 4) & 3)) * 16;
+    const uint8_t* src[kLoads];
+#pragma unroll
+    for(int f = 0; f < MF; ++f) src[f] = p.A + (f * 16 + lrow < p.M ? f * 16 + lrow : p.M - 1) * p.Kb;      // (rows and columns past the end:
+    src[MF] = p.B + (n0 + lrow < p.N ? n0 + lrow : p.N - 1) * p.Kb;                                          //  any valid one, never stored)
+    const int all = static_cast<int>((p.Kb + 63) / 64), turns = all > wave ? (all - wave + kRowsWaves - 1) / kRowsWaves : 0;
+    auto issue = [&](int t) {
+        const int64_t k   = (static_cast<int64_t>(t) * kRowsWaves + wave) * 64 + lchunk;
+        const bool    in  = k < p.Kb;                                        // (16-byte pieces: Kb is a multiple of 16)
+        uint8_t*      dst = mine + t % kStages * kTurn;
+        static_for<kLoads>([&](auto f) {
+            constexpr int i = decltype(f)::value, IMM = i % 4 * 1024;
+            const uint8_t* at = in ? src[i] + k : reinterpret_cast<const uint8_t*>(&g_zero_chunk);
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(at - IMM),
+                                             (__attribute__((address_space(3))) void*)(dst + i / 4 * 4096), 16, IMM, 0);
+        });
+    };
+    vec acc[MF];
+#pragma unroll
+    for(int f = 0; f < MF; ++f) acc[f] = vec{0, 0, 0, 0};
+    const int      row = lane % 16, quad = lane / 16;
+    const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) uint8_t*)mine));
+    const uint32_t frag = static_cast<uint32_t>(row * 64 + ((quad ^ ((row >> 2) & 3)) * 16));
+#pragma unroll
+    for(int t = 0; t < kStages - 1; ++t)
+        if(t < turns) issue(t);
+    for(int t = 0; t < turns; ++t)
+    {   // (every wavefront by itself: its loads, its slice of LDS)
+        if(t + kStages - 1 < turns) issue(t + kStages - 1);
+        wait_tiles<kLoads, kStages - 1>(turns - 1 - t);
+        v4i32          op[kLoads];
+        const uint32_t at = lds0 + static_cast<uint32_t>(t % kStages * kTurn) + frag;
+        static_for<kLoads>([&](auto f) { operand_read<decltype(f)::value * 1024>(op[decltype(f)::value], at); });
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for(int f = 0; f < MF; ++f) acc[f] = Mfma16<TR>::mfma(op[MF], op[f], acc[f]);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    __syncthreads();                                                        // (the sums take the place of the stages)
+#pragma unroll
+    for(int f = 0; f < MF; ++f) *reinterpret_cast<vec*>(lds + ((wave * MF + f) * 64 + lane) * 16) = acc[f];
+    __syncthreads();
+    if(wave >= MF) return;
+    vec sum = *reinterpret_cast<const vec*>(lds + (wave * 64 + lane) * 16);
+#pragma unroll
+    for(int w = 1; w < kRowsWaves; ++w) sum += *reinterpret_cast<const vec*>(lds + ((w * MF + wave) * 64 + lane) * 16);
+
+    const int64_t m = wave * 16 + row, n = n0 + quad * 4;
+    if(m >= p.M || n >= p.N) return;
+    const float alpha = *(p.s0 ? p.s0 : &g_one) * *(p.s1 ? p.s1 : &g_one);
+    float       fs[4], bs[4];
+#pragma unroll
+    for(int e = 0; e < 4; ++e)
+    {
+        const int64_t c = n + e < p.N ? n + e : p.N - 1;
+        fs[e] = p.col_scale ? alpha * p.col_scale[c] : alpha;
+        bs[e] = p.col_bias ? p.col_bias[c] : 0.0f;
+    }
+    const int64_t at = m * p.N + n;
+    const int     os = p.c_is_f16 ? 2 : 4;
+    uint8_t* const dst = static_cast<uint8_t*>(p.C) + at * os;
+    const bool    vector = p.N % 4 == 0 && (reinterpret_cast<uintptr_t>(p.C) & (4 * os - 1)) == 0;
+    float v[4];
+#pragma unroll
+    for(int e = 0; e < 4; ++e) v[e] = static_cast<float>(sum[e]);
+    if(p.c_is_f16)
+    {
+        const uint2 h = make_uint2(fma_out_half2(v[0], fs[0], bs[0], v[1], fs[1], bs[1]), fma_out_half2(v[2], fs[2], bs[2], v[3], fs[3], bs[3]));
+        if(vector) *reinterpret_cast<uint2*>(dst) = h;
+        else
+            for(int e = 0; e < 4 && n + e < p.N; ++e)
+                reinterpret_cast<uint16_t*>(dst)[e] = static_cast<uint16_t>((e < 2 ? h.x : h.y) >> (16 * (e % 2)));
+    }
+    else
+    {
+        const float4 y = make_float4(fmaf(v[0], fs[0], bs[0]), fmaf(v[1], fs[1], bs[1]), fmaf(v[2], fs[2], bs[2]), fmaf(v[3], fs[3], bs[3]));
+        const float  o[4] = {y.x, y.y, y.z, y.w};
+        if(vector) *reinterpret_cast<float4*>(dst) = y;
+        else
+            for(int e = 0; e < 4 && n + e < p.N; ++e) reinterpret_cast<float*>(dst)[e] = o[e];
+    }
+}
+
+template <typename TR, int MF> hipError_t launch_fragments(const GemmKernelArgs& a, hipStream_t st)
+{
+    constexpr int kLds = kRowsWaves * rows_stages(MF) * (MF + 1) * 1024;
+    static bool   attr_set[16] = {};      // per instantiation and device; benign if set twice
+    int           dev = 0;
+    const bool    known = hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < 16;
+    if(!known || !attr_set[dev])
+    {
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_rows_kernel<TR, MF>), hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
+        if(e != hipSuccess) return e;
+        if(known) attr_set[dev] = true;
+    }
+    gemm_rows_kernel<TR, MF><<<dim3(static_cast<unsigned>((a.N + kRowsCols - 1) / kRowsCols)), dim3(64 * kRowsWaves), kLds, st>>>(a);
+    return hipGetLastError();
+}
+template <typename TR> hipError_t launch_rows(const GemmKernelArgs& a, hipStream_t st)
+{
+    switch((a.M + 15) / 16)
+    {
+    case 1: return launch_fragments<TR, 1>(a, st);
+    case 2: return launch_fragments<TR, 2>(a, st);
+    case 3: return launch_fragments<TR, 3>(a, st);
+    default: return launch_fragments<TR, 4>(a, st);
+    }
+}
+
+}  // namespace
+
+// At most 64 rows and contractions of up to 6 KB (8 KB up to 32 rows); beyond, K splits over workgroups are faster.  Tiles -> here,
+// weights rotated through three matrices, binary16 outputs: int8 1x4096x1024 5.2 -> 3.2 us, 17x1024x2048 7.3 -> 3.8, 45x4096x1024
+// 5.3 -> 3.9, 64x4096x4096 12.6 -> 9.0; binary16 17x4096x4096 11.7 -> 9.4; 64x4096x64 3.5 -> 3.5 is the least, and
+// 45x1024x4096 binary16 (8 KB) would lose, 8.4 -> 10.0.
+hipError_t launch_gemm_rows(const GemmProblem& p, bool* taken, hipStream_t st)
+{
+    *taken = false;
+    if(p.K * (p.prec / 8) > (p.M <= 32 ? 8192 : 6144)) return hipSuccess;
+    if((p.prec != 8 && p.prec != 16) || p.M > 64 || p.tn || p.conv_H > 0 || p.b_remap_C > 0 || p.acc_dump || p.out_amax_bits || p.out_codes
+       || (p.N + kRowsCols - 1) / kRowsCols >= (int64_t(1) << 31))
+        return hipSuccess;
+    GemmKernelArgs a{};
+    a.A = static_cast<const uint8_t*>(p.A);
+    a.B = static_cast<const uint8_t*>(p.B);
+    a.M = p.M; a.N = p.N; a.Kb = p.K * (p.prec / 8);
+    a.C = p.C; a.c_is_f16 = p.c_dtype == kF16;
+    a.s0 = p.s0; a.s1 = p.s1; a.col_scale = p.col_scale; a.col_bias = p.col_bias;
+    *taken = true;
+    return p.prec == 8 ? launch_rows<I8Traits>(a, st) : launch_rows<F16Traits>(a, st);
+}
+
+}  // namespace qsync

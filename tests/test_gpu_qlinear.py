@@ -409,6 +409,32 @@ def test_row_major_backward_takes_a_workspace_without_room_behind_the_products()
         assert_bits_equal(a, b, name)
 
 
+@pytest.mark.parametrize("tag", [Q.INT8, Q.FP16])
+@pytest.mark.parametrize("M", [1, 16, 17, 45, 64])
+def test_few_rows_equal_the_tiled_product(tag, M):
+    """Products of at most 64 rows against the 64x64 tile, bit for bit (integer sums; binary16 operands are small integers,
+    whose sums below 2^24 are exact in any order): a last, partial column group, odd N, one to many turns of the wavefronts
+    with a partial last one, the longest contractions taken, both outputs, both scale granularities, with and without bias."""
+    rng = np.random.default_rng(M)
+    for N, K in ((1, 16), (33, 48), (130, 528), (1040, 1040), (7, 4096), (256, 64)):
+        lim = 127 if tag == Q.INT8 else 8
+        a, b = (dev(rng.integers(-lim, lim + 1, s).astype(np.int8 if tag == Q.INT8 else np.float16)) for s in ((M, K), (N, K)))
+        sx, sw, bias = (dev((rng.random(n) * 1e-3 + 1e-4).astype(np.float32)) for n in (1, N, N))
+        for ydt, gran, with_bias in ((torch.float32, Q.PER_ROW, True), (torch.float16, Q.PER_TENSOR, True), (torch.float16, Q.PER_ROW, False)):
+            say("few rows", tag, M, N, K, ydt, gran)
+            ys = []
+            for tile in (2, -1):
+                Q.qsync_debug_set_gemm_tile(tile)
+                try:
+                    y = torch.full((M, N), float("nan"), dtype=ydt, device="cuda")
+                    w = torch.empty(max(256, Q.qsync_qlinear_workspace_bytes(tag, M, N, K)), dtype=torch.uint8, device="cuda")
+                    Q.qsync_qlinear_fwd(tag, M, N, K, a, sx, b, sw, gran, bias if with_bias else None, y, None, w)
+                    ys.append(host(y))
+                finally:
+                    Q.qsync_debug_set_gemm_tile(-1)
+            assert_bits_equal(ys[1], ys[0], "Y")
+
+
 def test_bias_gradient_from_the_backward_call():
     """db requested from qsync_qlinear_bwd itself (not from the fused absmax pass)."""
     case = wl.ragged_case(208, 144, 80, seed=31, dtype=np.float16)
