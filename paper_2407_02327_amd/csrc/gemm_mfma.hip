@@ -1312,7 +1312,7 @@ hipError_t launch_gemm(const GemmProblem& p, const GemmPlan& plan, void* workspa
     GemmKernelArgs   a;
     const hipError_t bad = kernel_args(p, plan, workspace, a);
     if(bad != hipSuccess) return bad;
-    if(p.M <= 64 && g_tile_override < 0)
+    if(g_tile_override < 0 && g_persistent_mode != 1)
     {
         bool             taken = false;
         const hipError_t e     = launch_gemm_rows(p, &taken, stream);

@@ -1,16 +1,17 @@
-// C[M,N] = epilogue( sum_k A[m,k] B[n,k] ) for at most 64 rows of A (a handful of tokens), int8 and binary16.
+// C[M,N] = epilogue( sum_k A[m,k] B[n,k] ), int8 and binary16, where 64 rows and 16 or 32 columns a workgroup are few enough
+// workgroups for one on each unit: a handful of tokens, small operators.
 //
-// Such a product reads B once for little arithmetic, and on tiles of 64 columns a few dozen workgroups walk K one LDS stage
-// and barrier after the other (0.26 us per 128 bytes).  Here a
-// workgroup owns 16 columns and its eight wavefronts take K in turns of 64 bytes, each through stages of its own with three
-// turns in flight and no barrier, into the 16x16 matrix instructions; the eight sums meet in LDS once at the end.
+// On the tiles of 64 columns and more such a product is a few dozen workgroups (or one K split each of them) that walk K one LDS
+// stage and barrier after the other, 0.26 us per 128 bytes.  Here a workgroup's eight wavefronts take K in turns of 64 bytes,
+// each through stages of its own with two or three turns in flight and no barrier, into the 16x16 matrix instructions; the
+// eight sums meet in LDS once at the end.
 #include "gemm_device.h"
 
 namespace qsync {
 
 namespace {
 
-constexpr int kRowsWaves = 8, kRowsCols = 16;
+constexpr int kRowsWaves = 8;
 
 typedef int   v4i __attribute__((ext_vector_type(4)));
 typedef float v4f __attribute__((ext_vector_type(4)));
@@ -34,17 +35,23 @@ template <int OFF> __device__ __forceinline__ void operand_read(v4i32& d, uint32
     asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(d) : "v"(addr), "n"(OFF) : "memory");
 }
 
-// MF: fragments of 16 rows.  The B fragment is the instruction's first operand, so a lane holds four consecutive columns
+// MF, NF: fragments of 16 rows, of 16 columns.  The B fragment is the instruction's first operand, so a lane holds four consecutive columns
 // (4 (lane / 16) ..) of output row lane % 16.
-constexpr int rows_stages(int mf) { return mf == 4 ? 3 : 4; }             // turns in LDS: 120 KB of them at most
-template <typename TR, int MF>
+constexpr int64_t kRowsGroups = 256;                                        // one for each unit
+// The dimension of more groups runs fastest and is padded to a multiple of the eight XCDs where that stays within one group for
+// each unit: the workgroups that read one piece of the longer operand then share an L2.  4096x128 by 3072, int8: 11.5 -> 7.5 us.
+template <int NF> __host__ __device__ constexpr bool rows_first(int64_t M, int64_t N) { return M > N * (4 / NF); }
+constexpr int rows_stages(int loads) { return loads > 4 ? 3 : 4; }             // turns in LDS: 144 KB of them at most
+template <typename TR, int MF, int NF>
 __global__ __launch_bounds__(64 * kRowsWaves) void gemm_rows_kernel(const GemmKernelArgs p)
 {
     typedef typename Mfma16<TR>::vec vec;
-    constexpr int kStages = rows_stages(MF), kLoads = MF + 1, kTurn = kLoads * 1024;
+    constexpr int kLoads = MF + NF, kStages = rows_stages(kLoads), kTurn = kLoads * 1024;
     extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
     const int     lane = threadIdx.x % kWaveSize, wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x / kWaveSize));
-    const int64_t n0 = static_cast<int64_t>(blockIdx.x) * kRowsCols;
+    const bool    tall = rows_first<NF>(p.M, p.N);
+    const int64_t n0 = static_cast<int64_t>(tall ? blockIdx.y : blockIdx.x) * (16 * NF), m0 = static_cast<int64_t>(tall ? blockIdx.x : blockIdx.y) * 64;
+    if(m0 >= p.M || n0 >= p.N) return;                                      // (padded to a multiple of the XCDs)
     uint8_t* const mine = lds + wave * (kStages * kTurn);
 
     // loads: four lanes read 64 consecutive bytes of a row (lanes on sixteen rows, as the operands want them, took four times as
@@ -52,8 +59,10 @@ __global__ __launch_bounds__(64 * kRowsWaves) void gemm_rows_kernel(const GemmKe
     const int      lrow = lane / 4, lchunk = ((lane % 4) ^ ((lane >> 4) & 3)) * 16;
     const uint8_t* src[kLoads];
 #pragma unroll
-    for(int f = 0; f < MF; ++f) src[f] = p.A + (f * 16 + lrow < p.M ? f * 16 + lrow : p.M - 1) * p.Kb;      // (rows and columns past the end:
-    src[MF] = p.B + (n0 + lrow < p.N ? n0 + lrow : p.N - 1) * p.Kb;                                          //  any valid one, never stored)
+    for(int f = 0; f < MF; ++f) src[f] = p.A + (m0 + f * 16 + lrow < p.M ? m0 + f * 16 + lrow : p.M - 1) * p.Kb;
+#pragma unroll
+    for(int j = 0; j < NF; ++j) src[MF + j] = p.B + (n0 + j * 16 + lrow < p.N ? n0 + j * 16 + lrow : p.N - 1) * p.Kb;
+    // (rows and columns past the end: any valid one, never stored)
     const int all = static_cast<int>((p.Kb + 63) / 64), turns = all > wave ? (all - wave + kRowsWaves - 1) / kRowsWaves : 0;
     auto issue = [&](int t) {
         const int64_t k   = (static_cast<int64_t>(t) * kRowsWaves + wave) * 64 + lchunk;
@@ -66,9 +75,9 @@ __global__ __launch_bounds__(64 * kRowsWaves) void gemm_rows_kernel(const GemmKe
                                              (__attribute__((address_space(3))) void*)(dst + i / 4 * 4096), 16, IMM, 0);
         });
     };
-    vec acc[MF];
+    vec acc[MF * NF];
 #pragma unroll
-    for(int f = 0; f < MF; ++f) acc[f] = vec{0, 0, 0, 0};
+    for(int f = 0; f < MF * NF; ++f) acc[f] = vec{0, 0, 0, 0};
     const int      row = lane % 16, quad = lane / 16;
     const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) uint8_t*)mine));
     const uint32_t frag = static_cast<uint32_t>(row * 64 + ((quad ^ ((row >> 2) & 3)) * 16));
@@ -85,19 +94,21 @@ __global__ __launch_bounds__(64 * kRowsWaves) void gemm_rows_kernel(const GemmKe
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for(int f = 0; f < MF; ++f) acc[f] = Mfma16<TR>::mfma(op[MF], op[f], acc[f]);
+        for(int f = 0; f < MF; ++f)
+#pragma unroll
+            for(int j = 0; j < NF; ++j) acc[j * MF + f] = Mfma16<TR>::mfma(op[MF + j], op[f], acc[j * MF + f]);
         __builtin_amdgcn_sched_barrier(0);
     }
     __syncthreads();                                                        // (the sums take the place of the stages)
 #pragma unroll
-    for(int f = 0; f < MF; ++f) *reinterpret_cast<vec*>(lds + ((wave * MF + f) * 64 + lane) * 16) = acc[f];
+    for(int f = 0; f < MF * NF; ++f) *reinterpret_cast<vec*>(lds + ((wave * MF * NF + f) * 64 + lane) * 16) = acc[f];
     __syncthreads();
-    if(wave >= MF) return;
+    if(wave >= MF * NF) return;
     vec sum = *reinterpret_cast<const vec*>(lds + (wave * 64 + lane) * 16);
 #pragma unroll
-    for(int w = 1; w < kRowsWaves; ++w) sum += *reinterpret_cast<const vec*>(lds + ((w * MF + wave) * 64 + lane) * 16);
+    for(int w = 1; w < kRowsWaves; ++w) sum += *reinterpret_cast<const vec*>(lds + ((w * MF * NF + wave) * 64 + lane) * 16);
 
-    const int64_t m = wave * 16 + row, n = n0 + quad * 4;
+    const int64_t m = m0 + wave % MF * 16 + row, n = n0 + wave / MF * 16 + quad * 4;
     if(m >= p.M || n >= p.N) return;
     const float alpha = *(p.s0 ? p.s0 : &g_one) * *(p.s1 ? p.s1 : &g_one);
     float       fs[4], bs[4];
@@ -133,45 +144,61 @@ __global__ __launch_bounds__(64 * kRowsWaves) void gemm_rows_kernel(const GemmKe
     }
 }
 
-template <typename TR, int MF> hipError_t launch_fragments(const GemmKernelArgs& a, hipStream_t st)
+template <typename TR, int MF, int NF> hipError_t launch_fragments(const GemmKernelArgs& a, hipStream_t st)
 {
-    constexpr int kLds = kRowsWaves * rows_stages(MF) * (MF + 1) * 1024;
+    static_assert(MF * NF <= kRowsWaves, "a wavefront per fragment in the epilogue");
+    constexpr int kLds = kRowsWaves * rows_stages(MF + NF) * (MF + NF) * 1024;
     static bool   attr_set[16] = {};      // per instantiation and device; benign if set twice
     int           dev = 0;
     const bool    known = hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < 16;
     if(!known || !attr_set[dev])
     {
-        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_rows_kernel<TR, MF>), hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_rows_kernel<TR, MF, NF>), hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
         if(e != hipSuccess) return e;
         if(known) attr_set[dev] = true;
     }
-    gemm_rows_kernel<TR, MF><<<dim3(static_cast<unsigned>((a.N + kRowsCols - 1) / kRowsCols)), dim3(64 * kRowsWaves), kLds, st>>>(a);
+    const int64_t m = (a.M + 63) / 64, n = (a.N + 16 * NF - 1) / (16 * NF), few = rows_first<NF>(a.M, a.N) ? n : m;
+    int64_t       many = rows_first<NF>(a.M, a.N) ? m : n;
+    if((many + 7) / 8 * 8 * few <= kRowsGroups) many = (many + 7) / 8 * 8;
+    gemm_rows_kernel<TR, MF, NF><<<dim3(static_cast<unsigned>(many), static_cast<unsigned>(few)), dim3(64 * kRowsWaves), kLds, st>>>(a);
     return hipGetLastError();
 }
-template <typename TR> hipError_t launch_rows(const GemmKernelArgs& a, hipStream_t st)
+template <typename TR> hipError_t launch_rows(const GemmKernelArgs& a, int columns, hipStream_t st)
 {
-    switch((a.M + 15) / 16)
+    if(columns == 2) return launch_fragments<TR, 4, 2>(a, st);
+    switch(a.M > 64 ? 4 : (a.M + 15) / 16)
     {
-    case 1: return launch_fragments<TR, 1>(a, st);
-    case 2: return launch_fragments<TR, 2>(a, st);
-    case 3: return launch_fragments<TR, 3>(a, st);
-    default: return launch_fragments<TR, 4>(a, st);
+    case 1: return launch_fragments<TR, 1, 1>(a, st);
+    case 2: return launch_fragments<TR, 2, 1>(a, st);
+    case 3: return launch_fragments<TR, 3, 1>(a, st);
+    default: return launch_fragments<TR, 4, 1>(a, st);
     }
+}
+// Fragments of columns a workgroup, 0: other tiles are faster.  A second workgroup on a unit waits for the first (its stages fill
+// the LDS; at most 16 rows two fit), which loses at once: 64x16384x64 3.8 us on the tiles, 9.0 here.  Beyond 6 KB of contraction
+// (8 KB up to 32 rows) K splits over workgroups win.  Tiles -> here, operands warm, binary16 outputs, us:
+//   int8, 16 columns:  1x4096x1024 5.2 -> 3.2, 64x4096x4096 13.2 -> 7.7, 128x1024x2048 7.3 -> 4.7, 256x1024x4096 10.2 -> 7.0,
+//                      512x512x4096 10.4 -> 8.0, 4096x64x3072 9.5 -> 6.2; 100x768x6144 9.4 -> 7.4 and 4096x64x64 3.7 -> 3.5 gain
+//                      least, 100x768x8192 8.9 -> 8.7 and 65x1000x8192 8.7 -> 11.8 lie beyond
+//   int8, 32 columns:  512x1024x2048 7.5 -> 5.7, 200x2000x4096 12.7 -> 9.9, 4096x128x3072 9.8 -> 7.5, 64x8192x6144 16.3 -> 14.0;
+//                      512x1024x128 3.6 -> 3.9 is the loss at the short end (one K tile of the 64 tile: from 256 bytes on)
+//   binary16, the same bytes: within 2 % of the int8 times.
+int rows_columns(const GemmProblem& p)
+{
+    const int64_t bytes = p.K * (p.prec / 8), rows = (p.M + 63) / 64;
+    if(bytes > (p.M <= 32 ? 8192 : 6144)) return 0;
+    if(rows * ((p.N + 15) / 16) <= (p.M <= 16 ? 2 * kRowsGroups : kRowsGroups)) return 1;
+    return bytes > 256 && rows * ((p.N + 31) / 32) <= kRowsGroups ? 2 : 0;
 }
 
 }  // namespace
 
-// At most 64 rows and contractions of up to 6 KB (8 KB up to 32 rows); beyond, K splits over workgroups are faster.  Tiles -> here,
-// weights rotated through three matrices, binary16 outputs: int8 1x4096x1024 5.2 -> 3.2 us, 17x1024x2048 7.3 -> 3.8, 45x4096x1024
-// 5.3 -> 3.9, 64x4096x4096 12.6 -> 9.0; binary16 17x4096x4096 11.7 -> 9.4; 64x4096x64 3.5 -> 3.5 is the least, and
-// 45x1024x4096 binary16 (8 KB) would lose, 8.4 -> 10.0.
 hipError_t launch_gemm_rows(const GemmProblem& p, bool* taken, hipStream_t st)
 {
     *taken = false;
-    if(p.K * (p.prec / 8) > (p.M <= 32 ? 8192 : 6144)) return hipSuccess;
-    if((p.prec != 8 && p.prec != 16) || p.M > 64 || p.tn || p.conv_H > 0 || p.b_remap_C > 0 || p.acc_dump || p.out_amax_bits || p.out_codes
-       || (p.N + kRowsCols - 1) / kRowsCols >= (int64_t(1) << 31))
-        return hipSuccess;
+    if((p.prec != 8 && p.prec != 16) || p.tn || p.conv_H > 0 || p.b_remap_C > 0 || p.acc_dump || p.out_amax_bits || p.out_codes) return hipSuccess;
+    const int columns = rows_columns(p);
+    if(columns == 0) return hipSuccess;
     GemmKernelArgs a{};
     a.A = static_cast<const uint8_t*>(p.A);
     a.B = static_cast<const uint8_t*>(p.B);
@@ -179,7 +206,7 @@ hipError_t launch_gemm_rows(const GemmProblem& p, bool* taken, hipStream_t st)
     a.C = p.C; a.c_is_f16 = p.c_dtype == kF16;
     a.s0 = p.s0; a.s1 = p.s1; a.col_scale = p.col_scale; a.col_bias = p.col_bias;
     *taken = true;
-    return p.prec == 8 ? launch_rows<I8Traits>(a, st) : launch_rows<F16Traits>(a, st);
+    return p.prec == 8 ? launch_rows<I8Traits>(a, columns, st) : launch_rows<F16Traits>(a, columns, st);
 }
 
 }  // namespace qsync

@@ -173,7 +173,7 @@ void set_gemm_persistent_mode(int mode);
 // GemmProblem with conv_H > 0, not tn, checked by launch_gemm: input tile kept in LDS (conv3x3.hip); *taken is false, and nothing
 // launched, where that does not fit.  force_tile >= 0: pixels of a workgroup, 256 >> force_tile.
 hipError_t launch_conv3x3(const GemmProblem& p, int force_tile, bool* taken, hipStream_t stream);
-// At most 64 rows of A, plain epilogue (gemm_rows.hip); *taken is false, and nothing launched, for any other problem.
+// Few rows or a small product, plain epilogue (gemm_rows.hip); *taken is false, and nothing launched, for any other problem.
 hipError_t launch_gemm_rows(const GemmProblem& p, bool* taken, hipStream_t stream);
 // fold (optional): column sums to be finished beside the reduction of K splits; cleared when that was done.
 hipError_t launch_gemm(const GemmProblem& p, const GemmPlan& plan, void* workspace, hipStream_t stream, ColumnFoldArgs* fold = nullptr);

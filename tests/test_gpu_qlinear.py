@@ -410,10 +410,11 @@ def test_row_major_backward_takes_a_workspace_without_room_behind_the_products()
 
 
 @pytest.mark.parametrize("tag", [Q.INT8, Q.FP16])
-@pytest.mark.parametrize("M", [1, 16, 17, 45, 64])
+@pytest.mark.parametrize("M", [1, 16, 17, 45, 64, 65, 300, 2000])
 def test_few_rows_equal_the_tiled_product(tag, M):
-    """Products of at most 64 rows against the 64x64 tile, bit for bit (integer sums; binary16 operands are small integers,
-    whose sums below 2^24 are exact in any order): a last, partial column group, odd N, one to many turns of the wavefronts
+    """Few rows and small products against the 64x64 tile, bit for bit (integer sums; binary16 operands are small integers,
+    whose sums below 2^24 are exact in any order): last, partial groups of rows and columns, odd N, more groups of columns than
+    of rows and the reverse, 16 columns a workgroup and 32 (300x1040, 2000x130), one to many turns of the wavefronts
     with a partial last one, the longest contractions taken, both outputs, both scale granularities, with and without bias."""
     rng = np.random.default_rng(M)
     for N, K in ((1, 16), (33, 48), (130, 528), (1040, 1040), (7, 4096), (256, 64)):
