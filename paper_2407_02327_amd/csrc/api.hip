@@ -244,6 +244,11 @@ int qsync_gradient_quantize(const void* dy, int dydt, int64_t rows, int64_t cols
                                                workspace, static_cast<hipStream_t>(stream)));
 }
 
+// fp32 products whose contraction is no multiple of 16 bytes split it only where the workspace has room for the parts: it used to
+// be none, and a caller that brings that still gets the result.
+static bool splits_optional(int tag, int64_t contraction) { return tag == QSYNC_FP32 && contraction % 4 != 0; }
+static void unsplit(GemmPlan& plan) { plan.splits = 1; plan.workspace = 0; }
+
 size_t qsync_qlinear_workspace_bytes(int tag, int64_t M, int64_t N, int64_t K)
 {
     if(!is_tag(tag) || M < 0 || N < 0 || K < 0) return 0;
@@ -279,7 +284,8 @@ static int qlinear_fwd_impl(int tag, int64_t M, int64_t N, int64_t K, const void
         if(!aligned16(xq) || !aligned16(wq)) return QSYNC_ERR_ALIGN;
     }
     if(M == 0 || N == 0) return QSYNC_OK;
-    const GemmPlan plan = plan_gemm(tag, M, N, K);
+    GemmPlan plan = plan_gemm(tag, M, N, K);
+    if(splits_optional(tag, K) && !(workspace && aligned16(workspace) && workspace_bytes >= plan.workspace)) unsplit(plan);
     if(plan.workspace > 0)
     {
         if(!workspace || workspace_bytes < plan.workspace) return QSYNC_ERR_WORKSPACE;
@@ -380,15 +386,18 @@ static int qlinear_bwd_impl(int tag, int64_t M, int64_t N, int64_t K, const void
         if(dx_opt && (N % mult != 0 || !aligned16(dyq) || !aligned16(wqbT))) return QSYNC_ERR_ALIGN;
         if(dw_opt && (M % mult != 0 || !aligned16(dyqT) || !aligned16(xqT))) return QSYNC_ERR_ALIGN;
     }
-    const GemmPlan plan_dx = plan_gemm(tag, M, K, N);
-    const GemmPlan plan_dw = plan_gemm(tag, N, K, M);
+    GemmPlan plan_dx = plan_gemm(tag, M, K, N);
+    GemmPlan plan_dw = plan_gemm(tag, N, K, M);
+    const bool full = workspace && aligned16(workspace) && workspace_bytes >= qsync_qlinear_bwd_workspace_bytes(tag, M, N, K);
+    if(!full && splits_optional(tag, N)) unsplit(plan_dx);
+    if(!full && splits_optional(tag, M)) unsplit(plan_dw);
     const size_t   off_dw  = round256(plan_dx.workspace);
     const size_t   off_db  = off_dw + round256(plan_dw.workspace);
     const size_t   need    = (dx_opt ? plan_dx.workspace : 0) + (dw_opt ? plan_dw.workspace : 0)
                         + ((db_opt && M > 0 && N > 0) ? colsum_workspace_bytes(M, N) : 0);
     if(need > 0)
     {
-        if(!workspace || workspace_bytes < qsync_qlinear_bwd_workspace_bytes(tag, M, N, K)) return QSYNC_ERR_WORKSPACE;
+        if(!workspace || workspace_bytes < off_db + round256(colsum_workspace_bytes(M, N))) return QSYNC_ERR_WORKSPACE;
         if(!aligned16(workspace)) return QSYNC_ERR_ALIGN;
     }
     hipStream_t st  = static_cast<hipStream_t>(stream);

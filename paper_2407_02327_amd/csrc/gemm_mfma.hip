@@ -1143,7 +1143,7 @@ template <typename TR> hipError_t launch_persistent(const GemmKernelArgs& a, hip
 
 }  // namespace
 
-hipError_t launch_gemm_f32(const GemmProblem& p, hipStream_t stream);   // gemm_f32.hip
+hipError_t launch_gemm_f32(const GemmProblem& p, const GemmPlan& plan, void* workspace, hipStream_t stream);   // gemm_f32.hip
 
 static thread_local int g_tile_override = -1;     // set by tests and tuning runs only; per calling thread
 void set_gemm_tile_override(int tile) { g_tile_override = (tile >= 0 && tile < kNumTiles) ? tile : -1; }
@@ -1171,7 +1171,6 @@ GemmPlan plan_gemm(int prec, int64_t M, int64_t N, int64_t K, int force_tile, in
     GemmPlan plan{1, 1, 0, 0.0};
     if(M <= 0 || N <= 0) return plan;
     const int64_t kb     = K * (prec == 8 ? 1 : (prec == 16 ? 2 : 4));
-    if(prec == 32 && kb % 16 != 0) return plan;                   // the any-shape fp32 kernel: no tiles to plan
     // a K tile of fp32 operands takes the matrix cores eight times as long as one of int8 or binary16 operands
     const double  kwork  = prec == 32 ? 8.0 : 1.0;
     const int64_t ktiles = (kb + kRowBytes - 1) / kRowBytes;
@@ -1301,14 +1300,45 @@ static hipError_t kernel_args(const GemmProblem& p, const GemmPlan& plan, void* 
     return hipSuccess;
 }
 
+// Second launch of a product in K splits: their sum and the epilogue.
+static hipError_t reduce_splits(const GemmProblem& p, int splits, void* workspace, hipStream_t stream, ColumnFoldArgs* fold)
+{
+    const bool vec4 = p.N % 4 == 0 && ((reinterpret_cast<uintptr_t>(workspace) | reinterpret_cast<uintptr_t>(p.C)) & 15) == 0;
+    int64_t    nb   = (p.M * p.N / (vec4 ? 4 : 1) + kThreads - 1) / kThreads;
+    nb              = nb > 65536 ? 65536 : nb;
+    if(p.out_amax_bits && nb > 1024) nb = 1024;    // at most one atomic per workgroup on one word: keep them few
+    const ColumnFoldArgs beside = fold ? *fold : ColumnFoldArgs{};
+    if(fold) *fold = ColumnFoldArgs{};
+    auto reduce = [&](auto acc_tag, auto vec_tag, const void* ws, int32_t* dump) {
+        typedef decltype(acc_tag) acc_t;
+        splitk_reduce_kernel<acc_t, decltype(vec_tag)::value><<<dim3(nb + beside.blocks()), dim3(kThreads), 0, stream>>>(
+            static_cast<const acc_t*>(ws), splits, p.M, p.N, p.C, p.c_dtype == kF16, p.s0, p.s1, p.col_scale, p.col_bias, dump,
+            p.out_amax_bits, static_cast<int8_t*>(p.out_codes), p.out_code_inv, p.out_code_qmax, static_cast<int>(nb), beside);
+    };
+    if(p.prec == 8)
+    {
+        if(vec4) reduce(int32_t{}, std::true_type{}, workspace, p.acc_dump);
+        else     reduce(int32_t{}, std::false_type{}, workspace, p.acc_dump);
+    }
+    else
+    {
+        if(vec4) reduce(float{}, std::true_type{}, workspace, nullptr);
+        else     reduce(float{}, std::false_type{}, workspace, nullptr);
+    }
+    return hipGetLastError();
+}
+
 hipError_t launch_gemm(const GemmProblem& p, const GemmPlan& plan, void* workspace, hipStream_t stream, ColumnFoldArgs* fold)
 {
     if(p.M <= 0 || p.N <= 0) return hipSuccess;
     if(p.prec == 32 && (p.conv_H > 0 || p.b_remap_C > 0)) return hipErrorInvalidValue;
-    // fp32 on the matrix cores needs 16-byte aligned, 16-byte multiple operand rows; anything else takes the
-    // any-shape kernel
+    const int splits = plan.splits < 1 ? 1 : plan.splits;
+    // 16-byte pieces to LDS need 16-byte aligned, 16-byte multiple operand rows; any other fp32 operands go through registers
     if(p.prec == 32 && ((p.K * 4) % 16 != 0 || ((reinterpret_cast<uintptr_t>(p.A) | reinterpret_cast<uintptr_t>(p.B)) & 15) != 0))
-        return launch_gemm_f32(p, stream);
+    {
+        const hipError_t e = launch_gemm_f32(p, plan, workspace, stream);
+        return e != hipSuccess || splits == 1 ? e : reduce_splits(p, splits, workspace, stream, fold);
+    }
     GemmKernelArgs   a;
     const hipError_t bad = kernel_args(p, plan, workspace, a);
     if(bad != hipSuccess) return bad;
@@ -1324,7 +1354,6 @@ hipError_t launch_gemm(const GemmProblem& p, const GemmPlan& plan, void* workspa
         const hipError_t e     = launch_conv3x3(p, g_tile_override, &taken, stream);
         if(taken || e != hipSuccess) return e;
     }
-    const int splits = plan.splits < 1 ? 1 : plan.splits;
     // The persistent kernel is opt-in.  Launched alone and back to back it beats the per-tile kernel by 7-20 % (the
     // write-back of a tile overlaps the next tile's K loop), but inside an operator sequence its fixed tile
     // assignment loses what it gains: workgroups that start late, behind the tail of the previous kernel, still
@@ -1335,30 +1364,7 @@ hipError_t launch_gemm(const GemmProblem& p, const GemmPlan& plan, void* workspa
     hipError_t e = p.prec == 8    ? launch_traits<I8Traits>(plan.tile, a, splits, stream, p.tn)
                    : p.prec == 16 ? launch_traits<F16Traits>(plan.tile, a, splits, stream, p.tn)
                                   : launch_traits<F32Traits>(plan.tile, a, splits, stream);
-    if(e != hipSuccess || splits == 1) return e;
-    const bool vec4 = p.N % 4 == 0 && ((reinterpret_cast<uintptr_t>(workspace) | reinterpret_cast<uintptr_t>(p.C)) & 15) == 0;
-    int64_t    nb   = (p.M * p.N / (vec4 ? 4 : 1) + kThreads - 1) / kThreads;
-    nb              = nb > 65536 ? 65536 : nb;
-    if(p.out_amax_bits && nb > 1024) nb = 1024;    // at most one atomic per workgroup on one word: keep them few
-    const ColumnFoldArgs beside = fold ? *fold : ColumnFoldArgs{};
-    if(fold) *fold = ColumnFoldArgs{};
-    auto reduce = [&](auto acc_tag, auto vec_tag, const void* ws, int32_t* dump) {
-        typedef decltype(acc_tag) acc_t;
-        splitk_reduce_kernel<acc_t, decltype(vec_tag)::value><<<dim3(nb + beside.blocks()), dim3(kThreads), 0, stream>>>(
-            static_cast<const acc_t*>(ws), splits, p.M, p.N, p.C, a.c_is_f16, p.s0, p.s1, p.col_scale, p.col_bias, dump,
-            p.out_amax_bits, static_cast<int8_t*>(p.out_codes), p.out_code_inv, p.out_code_qmax, static_cast<int>(nb), beside);
-    };
-    if(p.prec == 8)
-    {
-        if(vec4) reduce(int32_t{}, std::true_type{}, workspace, a.acc_dump);
-        else     reduce(int32_t{}, std::false_type{}, workspace, a.acc_dump);
-    }
-    else
-    {
-        if(vec4) reduce(float{}, std::true_type{}, workspace, nullptr);
-        else     reduce(float{}, std::false_type{}, workspace, nullptr);
-    }
-    return hipGetLastError();
+    return e != hipSuccess || splits == 1 ? e : reduce_splits(p, splits, workspace, stream, fold);
 }
 
 // K tiles of a workgroup per round of 256 workgroups -> time of the compute unit that gets the first workgroup of every

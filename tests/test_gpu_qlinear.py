@@ -436,6 +436,36 @@ def test_few_rows_equal_the_tiled_product(tag, M):
             assert_bits_equal(ys[1], ys[0], "Y")
 
 
+@pytest.mark.parametrize("M, N, K", [(1, 1, 1), (3, 130, 31), (65, 63, 33), (130, 70, 97), (64, 64, 64), (257, 129, 1023), (70, 6, 4099), (1, 300, 20001)])
+def test_fp32_operands_that_are_no_16_byte_rows(M, N, K):
+    """Odd contractions and operands off 16 bytes, on both tiles, in K splits and, without a workspace, in one; against the
+    product in double.  A dot product of K fp32 terms in any order is off by at most (K + 1) 2^-24 sum |a b| (the products are
+    fused; scale and bias add two roundings), a binary16 output by another 2^-11 of itself."""
+    rng = np.random.default_rng(K)
+    a, b, bias = rng.standard_normal((M, K)).astype(np.float32), rng.standard_normal((N, K)).astype(np.float32), rng.standard_normal(N).astype(np.float32)
+    want = a.astype(np.float64) @ b.astype(np.float64).T + bias
+    bound = (K + 3) * 2.0 ** -24 * (np.abs(a).astype(np.float64) @ np.abs(b).astype(np.float64).T + np.abs(bias))
+    at = lambda v: torch.cat([torch.zeros(1, device="cuda"), dev(v.reshape(-1))])[1:]      # four bytes past an allocation's start
+    da, db = at(a), at(b)
+    for tile in (-1, 0, 2):
+        Q.qsync_debug_set_gemm_tile(tile)
+        try:
+            need = Q.qsync_qlinear_workspace_bytes(Q.FP32, M, N, K)
+            rooms = [need] + ([0] if K % 4 else [])
+            for dt, room in [(d, r) for d in (torch.float32, torch.float16) for r in rooms]:
+                say("odd fp32", M, N, K, tile, dt, room)
+                y = torch.full((M, N), float("nan"), dtype=dt, device="cuda")
+                amax = torch.zeros(1, device="cuda")
+                w = torch.full((room,), 255, dtype=torch.uint8, device="cuda") if room else None
+                Q.qsync_qlinear_fwd_amax(Q.FP32, M, N, K, da, None, db, None, Q.PER_TENSOR, dev(bias), y, None, amax, w)
+                got = host(y).astype(np.float64)
+                limit = bound + (np.abs(want) * 2.0 ** -11 + 2.0 ** -25 if dt == torch.float16 else 0.0)
+                assert (np.abs(got - want) <= limit).all()
+                assert float(amax) == np.abs(got).max()
+        finally:
+            Q.qsync_debug_set_gemm_tile(-1)
+
+
 def test_bias_gradient_from_the_backward_call():
     """db requested from qsync_qlinear_bwd itself (not from the fused absmax pass)."""
     case = wl.ragged_case(208, 144, 80, seed=31, dtype=np.float16)
