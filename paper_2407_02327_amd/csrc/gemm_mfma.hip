@@ -1153,6 +1153,11 @@ void set_gemm_persistent_mode(int mode) { g_persistent_mode = (mode == 0 || mode
 // Model of a tile shape's time; the constants are explained in plan_gemm.
 struct TileModel { double r1, rmax, ovh, cap; int occ; };
 static constexpr TileModel kTileModel[kNumTiles] = {{14.0, 15.8, 7.5, 2280.0, 1}, {8.3, 9.0, 4.2, 1900.0, 2}, {3.55, 5.48, 3.2, 2060.0, 4}};
+// fp32: the matrix instructions bound every tile alike (19.7 in these units), so rates lie close together and the smaller tile's finer
+// grain decides; fitted to 70 shapes of 64..16384 by 64..4096, timed on the three tiles: 2.5 % behind the best on average, before,
+// with the constants above, 10-13 %; 2652x440x1912 84 -> 57 us, 968x1288x2140 89 -> 63, 14828x552x380 108 -> 72.  On 70 others
+// 1.9 % (7 %).
+static constexpr TileModel kTileModelF32[kNumTiles] = {{14.5, 16.3, 7.5, 4300.0, 1}, {14.3, 16.2, 4.2, 4300.0, 2}, {11.5, 15.3, 3.2, 4300.0, 4}};
 // Row-major (TN) operands: a K tile takes twice the LDS fragment reads, and a 64-wide tile of int8 operands
 // loads 64-byte row pieces (binary16: 128 bytes, no penalty); fitted slow-down of the main loop per tile shape.
 static double tn_factor(int tile, int prec, bool tn)
@@ -1178,8 +1183,8 @@ GemmPlan plan_gemm(int prec, int64_t M, int64_t N, int64_t K, int force_tile, in
     // Plan = (tile, K splits) with the smallest estimated time.  The estimate is a small model fitted to gfx950
     // measurements of this kernel (int8 and binary16, forward, row-major and transposed weight-gradient forms: 54
     // operands x 3 tiles, replayed from a graph; rms error 11 %, the choice at most 8 % behind the best tile of those.  65
-    // other shapes a type: 1.0 % behind on average with int8, 1.6 % with binary16, 22 % at most, 3120 x 3504 x 64.  fp32
-    // operands were not fitted: 7.5 % on average, 55 % at most):
+    // other shapes a type: 1.0 % behind on average with int8, 1.6 % with binary16, 22 % at most, 3120 x 3504 x 64; fp32 operands have
+    // constants of their own):
     //   a compute unit retires `r1` Mop/us per resident workgroup of a tile shape, up to `rmax` with `occ` of them
     //   sharing it; the chip as a whole retires at most `cap` Mop/us (256 busy units, at a lower clock and on
     //   shared caches, do not each reach `rmax`); every round of co-resident workgroups costs `ovh` us of launch, first-load latency
@@ -1187,7 +1192,7 @@ GemmPlan plan_gemm(int prec, int64_t M, int64_t N, int64_t K, int force_tile, in
     //   tile 28.5 us, 128 tile 21.5; 49 of 6000 shapes drawn over the same range change, 18 % faster on average); split K adds its reduction pass.
     const double    cus = 256.0;
     auto estimate = [&](int t, int64_t s) {
-        const TileModel& m    = kTileModel[t];
+        const TileModel& m    = (prec == 32 ? kTileModelF32 : kTileModel)[t];
         const double     tnf  = tn_factor(t, prec, tn);
         const double     wgs  = static_cast<double>(ntiles(t)) * static_cast<double>(s);
         const double     per  = std::ceil(wgs / cus);                                    // workgroups of the busiest unit
