@@ -2,7 +2,7 @@
 //
 // A call through ctypes cost the host 1.3 to 2.9 us for its arguments beside the 2.7 us of a kernel launch, which is what
 // bounds operators of a few thousand elements; here it is 0.2 to 0.4 us.  Arguments: a pointer parameter takes a tensor (its data
-// pointer), None or an address; an integer parameter an int.  A dtype takes the tensor passed just in front of it once more,
+// pointer), None or an address; an integer parameter whatever has an index.  A dtype takes the tensor passed just in front of it once more,
 // a workspace size the tensor or None likewise.  The last parameter, the stream, takes a torch stream, a handle, or None for
 // torch's current stream.  A status other than QSYNC_OK raises what
 // `set_error` was given.  The GIL is released around the call.
@@ -31,16 +31,16 @@ struct PythonError : std::exception {};      // a Python error is set
 
 const at::Tensor* as_tensor(PyObject* o) { return THPVariable_Check(o) ? &THPVariable_Unpack(o) : nullptr; }
 
-uint64_t integer(PyObject* o)
+uint64_t integer(PyObject* o)      // modulo 2^64, as ctypes takes them: of an int, or of what answers as one (numpy's integers)
 {
-    if(PyLong_Check(o))
+    if(!PyIndex_Check(o))
     {
-        const uint64_t v = PyLong_AsUnsignedLongLongMask(o);
-        if(v == static_cast<uint64_t>(-1) && PyErr_Occurred()) throw PythonError();
-        return v;
+        PyErr_Format(PyExc_TypeError, "an integer is required (got type %s)", Py_TYPE(o)->tp_name);
+        throw PythonError();
     }
-    PyErr_Format(PyExc_TypeError, "an integer is required (got type %s)", Py_TYPE(o)->tp_name);
-    throw PythonError();
+    const uint64_t v = PyLong_AsUnsignedLongLongMask(o);
+    if(v == static_cast<uint64_t>(-1) && PyErr_Occurred()) throw PythonError();
+    return v;
 }
 
 void* pointer(PyObject* o)

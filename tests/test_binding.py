@@ -1,0 +1,26 @@
+"""What the compiled binding takes and refuses, through the public functions of `qsync` (CPU only: every call here returns before
+anything is launched -- an empty tensor, or an argument that is refused)."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2407_02327_amd import qsync as Q
+
+
+@pytest.mark.parametrize("integer", [np.int64, np.int32, np.uint8, torch.tensor], ids=lambda f: f.__name__)
+def test_integers_are_whatever_has_an_index(integer):
+    """Sizes, enumerators, seeds: Python's integers and everything that answers as one (a product of shapes in numpy is no `int`)."""
+    i, x, s = integer, torch.empty(4), torch.empty(1)
+    Q.qsync_absmax_scale(x, i(0), i(4), i(4), i(Q.PER_TENSOR), i(8), s, s, None, None, None, 0)
+    Q.qsync_quantize(x, i(0), i(4), i(4), i(Q.FP16), i(0), i(0), i(Q.ROUND_NEAREST), i(7), i(0), None, x, None, 0)
+    rows = i(4)      # one object for sizes that follow each other
+    with pytest.raises(Q.QsyncError) as e:
+        Q.qsync_quantize(x, rows, rows, i(2), i(Q.FP16), i(0), i(0), i(Q.ROUND_NEAREST), i(7), i(0), None, x, None, 0)
+    assert e.value.status == Q.ERR_BAD_SHAPE
+
+
+@pytest.mark.parametrize("bad", [4.0, "4", None])
+def test_other_integers_are_refused(bad):
+    x = torch.empty(4)
+    with pytest.raises(TypeError):
+        Q.qsync_quantize(x, 0, bad, 4, Q.FP16, 0, 0, 0, 0, 0, None, x, None, 0)
