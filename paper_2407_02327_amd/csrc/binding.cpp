@@ -2,9 +2,9 @@
 //
 // A call through ctypes cost the host 1.3 to 2.9 us for its arguments beside the 2.7 us of a kernel launch, which is what
 // bounds operators of a few thousand elements; here it is 0.2 to 0.4 us.  Arguments: a pointer parameter takes a tensor (its data
-// pointer), None or an address; an integer parameter whatever has an index.  A dtype takes the tensor passed just in front of it once more,
-// a workspace size the tensor or None likewise.  The last parameter, the stream, takes a torch stream, a handle, or None for
-// torch's current stream.  A status other than QSYNC_OK raises what
+// pointer) or None -- a pointer to host sizes an address or None --, an integer parameter whatever has an index.  A dtype takes
+// the tensor passed just in front of it once more, a workspace size the tensor or None likewise.  The last parameter, the
+// stream, takes a torch stream, a handle, or None for torch's current stream.  A status other than QSYNC_OK raises what
 // `set_error` was given.  The GIL is released around the call.
 #include <Python.h>
 
@@ -47,8 +47,7 @@ void* pointer(PyObject* o)
 {
     if(o == Py_None) return nullptr;
     if(THPVariable_CheckExact(o)) return THPVariable_Unpack(o).data_ptr();
-    if(PyLong_Check(o)) return reinterpret_cast<void*>(integer(o));
-    PyObject* p = PyObject_CallMethod(o, "data_ptr", nullptr);      // (subclasses answer for themselves)
+    PyObject* p = PyObject_CallMethod(o, "data_ptr", nullptr);      // (subclasses answer for themselves; a number has none)
     if(!p) throw PythonError();
     const uint64_t v = PyLong_AsUnsignedLongLongMask(p);
     Py_DECREF(p);
@@ -110,7 +109,9 @@ template <typename T> T argument(PyObject* const* args, size_t i, bool last)
 {
     PyObject* const o        = args[i];
     const bool      repeated = i > 0 && args[i - 1] == o;
-    if constexpr(std::is_pointer<T>::value)
+    if constexpr(std::is_same<T, size_t*>::value)      // (an array of the host's)
+        return o == Py_None ? nullptr : reinterpret_cast<T>(integer(o));
+    else if constexpr(std::is_pointer<T>::value)
         return reinterpret_cast<T>(last ? stream_handle(o) : pointer(o));
     else if constexpr(std::is_floating_point<T>::value)
     {

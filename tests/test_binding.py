@@ -24,3 +24,14 @@ def test_other_integers_are_refused(bad):
     x = torch.empty(4)
     with pytest.raises(TypeError):
         Q.qsync_quantize(x, 0, bad, 4, Q.FP16, 0, 0, 0, 0, 0, None, x, None, 0)
+
+
+def test_an_address_is_no_tensor():
+    """A pointer argument is a tensor or None: a number there would be an address that nothing has checked."""
+    x, s = torch.empty(4), torch.empty(1)
+    for args in ((4096, 0, 4, 4, Q.FP16, 0, 0, 0, 0, 0, None, x, None, 0), (x, 0, 4, 4, Q.FP16, 0, 0, 0, 0, 0, None, 4096, None, 0),
+                 (x, 0, 4, 4, Q.INT8, 8, 0, 0, 0, 0, True, x, None, 0)):
+        with pytest.raises(AttributeError):
+            Q.qsync_quantize(*args)
+    with pytest.raises(AttributeError):
+        Q.qsync_absmax_scale(x, 0, 4, 4, Q.PER_TENSOR, 8, s, s, None, None, 4096, 0)      # (nor is it a workspace and its size)
