@@ -1,14 +1,15 @@
 // Python binding of the C ABI's launching calls: every function takes the arguments of its C counterpart in order.
 //
 // A call through ctypes cost the host 1.3 to 2.9 us for its arguments beside the 2.7 us of a kernel launch, which is what
-// bounds operators of a few thousand elements; here it is 0.2 to 0.4 us.  Arguments: a pointer parameter takes a tensor (its data
-// pointer) or None -- a pointer to host sizes an address or None --, an integer parameter whatever has an index.  A dtype takes
+// bounds operators of a few thousand elements; here it is 0.2 to 0.4 us.  Arguments: a pointer parameter takes a tensor (or what
+// else has a data_ptr()) or None -- a pointer to host sizes an address or None --, an integer parameter whatever has an index.  A dtype takes
 // the tensor passed just in front of it once more, a workspace size the tensor or None likewise.  The last parameter, the
 // stream, takes a torch stream, a handle, or None for torch's current stream.  A status other than QSYNC_OK raises what
 // `set_error` was given.  The GIL is released around the call.
 #include <Python.h>
 
 #include <c10/hip/HIPStream.h>
+#include <torch/csrc/Dtype.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <cstdint>
@@ -43,21 +44,26 @@ uint64_t integer(PyObject* o)      // modulo 2^64, as ctypes takes them: of an i
     return v;
 }
 
+uint64_t answer(PyObject* o, const char* method)
+{
+    PyObject* r = PyObject_CallMethod(o, method, nullptr);
+    if(!r) throw PythonError();
+    const uint64_t v = PyLong_AsUnsignedLongLongMask(r);
+    Py_DECREF(r);
+    if(PyErr_Occurred()) throw PythonError();
+    return v;
+}
+
 void* pointer(PyObject* o)
 {
     if(o == Py_None) return nullptr;
     if(THPVariable_CheckExact(o)) return THPVariable_Unpack(o).data_ptr();
-    PyObject* p = PyObject_CallMethod(o, "data_ptr", nullptr);      // (subclasses answer for themselves; a number has none)
-    if(!p) throw PythonError();
-    const uint64_t v = PyLong_AsUnsignedLongLongMask(p);
-    Py_DECREF(p);
-    if(PyErr_Occurred()) throw PythonError();
-    return reinterpret_cast<void*>(v);
+    return reinterpret_cast<void*>(answer(o, "data_ptr"));      // (subclasses answer for themselves; a number has none)
 }
 
-int dtype_code(PyObject* o, const at::Tensor& t)
+int dtype_code(PyObject* o, at::ScalarType type)
 {
-    switch(t.scalar_type())
+    switch(type)
     {
     case at::kFloat: return QSYNC_F32;
     case at::kHalf: return QSYNC_F16;
@@ -68,6 +74,19 @@ int dtype_code(PyObject* o, const at::Tensor& t)
     PyObject* dt = PyObject_GetAttrString(o, "dtype");
     if(dt) { PyErr_SetObject(PyExc_KeyError, dt); Py_DECREF(dt); }
     throw PythonError();
+}
+
+// ... of what is no tensor but has a dtype
+int dtype_code(PyObject* o)
+{
+    PyObject* dt = PyObject_GetAttrString(o, "dtype");
+    if(!dt) throw PythonError();
+    const bool known = THPDtype_Check(dt);
+    if(!known) PyErr_SetObject(PyExc_KeyError, dt);
+    const at::ScalarType type = known ? reinterpret_cast<THPDtype*>(dt)->scalar_type : at::ScalarType::Undefined;
+    Py_DECREF(dt);
+    if(!known) throw PythonError();
+    return dtype_code(o, type);
 }
 
 void* stream_handle(PyObject* o)
@@ -121,14 +140,14 @@ template <typename T> T argument(PyObject* const* args, size_t i, bool last)
     }
     else if constexpr(std::is_same<T, int>::value)
     {
-        if(const at::Tensor* t = repeated ? as_tensor(o) : nullptr) return dtype_code(o, *t);
-        return static_cast<int>(integer(o));
+        if(const at::Tensor* t = repeated ? as_tensor(o) : nullptr) return dtype_code(o, t->scalar_type());
+        return repeated && o != Py_None && !PyIndex_Check(o) ? dtype_code(o) : static_cast<int>(integer(o));
     }
     else if constexpr(std::is_same<T, size_t>::value)
     {
         if(repeated && o == Py_None) return 0;
         if(const at::Tensor* t = repeated ? as_tensor(o) : nullptr) return t->nbytes();
-        return integer(o);
+        return repeated && !PyIndex_Check(o) ? answer(o, "numel") * answer(o, "element_size") : integer(o);
     }
     else
         return static_cast<T>(integer(o));

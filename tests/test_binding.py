@@ -35,3 +35,26 @@ def test_an_address_is_no_tensor():
             Q.qsync_quantize(*args)
     with pytest.raises(AttributeError):
         Q.qsync_absmax_scale(x, 0, 4, 4, Q.PER_TENSOR, 8, s, s, None, None, 4096, 0)      # (nor is it a workspace and its size)
+
+
+class _Holder:
+    """Answers for a tensor's memory without being one."""
+
+    def __init__(self, t):
+        self.t, self.dtype = t, t.dtype
+        self.data_ptr, self.numel, self.element_size = t.data_ptr, t.numel, t.element_size
+
+
+def test_objects_that_hold_memory():
+    """data_ptr() and dtype are what a pointer and its type are read from, numel() and element_size() a workspace's size."""
+    h = lambda n, dt=torch.float32: _Holder(torch.empty(n, dtype=dt))
+    Q.qsync_quantize(h(4), 0, 4, 4, Q.FP16, 0, 0, 0, 0, 0, None, h(4, torch.float16), None, 0)
+    with pytest.raises(Q.QsyncError) as e:                        # an integer tensor is no source: its type was read
+        Q.qsync_quantize(h(4, torch.int32), 0, 4, 4, Q.FP16, 0, 0, 0, 0, 0, None, h(4), None, 0)
+    assert e.value.status == Q.ERR_BAD_ENUM
+    with pytest.raises(KeyError):
+        Q.qsync_quantize(h(4, torch.int64), 0, 4, 4, Q.FP16, 0, 0, 0, 0, 0, None, h(4), None, 0)
+    need, s = Q.qsync_absmax_quantize_workspace_bytes(4, 8), h(1)
+    with pytest.raises(Q.QsyncError) as e:
+        Q.qsync_absmax_quantize(h(32), 4, 8, 8, 0, 0, 0, s, s, None, h(32, torch.int8), None, h(need // 4 - 1), -1, 0)
+    assert e.value.status == Q.ERR_WORKSPACE
