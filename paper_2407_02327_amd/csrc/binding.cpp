@@ -8,6 +8,8 @@
 // `set_error` was given.  The GIL is released around the call.
 #include <Python.h>
 
+#include <pthread.h>
+
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/Dtype.h>
 #include <torch/csrc/autograd/python_variable.h>
@@ -27,6 +29,9 @@ namespace {
 PyObject* g_error          = nullptr;      // called with the status, returns the exception
 PyObject* g_is_initialized = nullptr;      // torch.cuda.is_initialized
 PyObject* g_current_stream = nullptr;      // torch.cuda.current_stream
+// torch has initialised the device, which stays so (read and written under the GIL) -- but not in a process forked from this one,
+// where torch refuses the device's use
+bool g_device_ready = false;
 
 struct PythonError : std::exception {};      // a Python error is set
 
@@ -91,10 +96,9 @@ int dtype_code(PyObject* o)
 
 void* stream_handle(PyObject* o)
 {
-    static bool ready = false;      // (under the GIL; once torch has initialised the device it stays so)
     if(o == Py_None)
     {
-        if(!ready)
+        if(!g_device_ready)
         {
             PyObject* r = PyObject_CallNoArgs(g_is_initialized);
             if(!r) throw PythonError();
@@ -106,7 +110,7 @@ void* stream_handle(PyObject* o)
                 if(!s) throw PythonError();
                 Py_DECREF(s);
             }
-            ready = true;
+            g_device_ready = true;
         }
         return c10::hip::getCurrentHIPStream().stream();
     }
@@ -215,5 +219,6 @@ PyMODINIT_FUNC PyInit__native(void)
     if(!g_is_initialized || !g_current_stream) return nullptr;
     g_error = reinterpret_cast<PyObject*>(PyExc_RuntimeError);
     Py_INCREF(g_error);
+    if(pthread_atfork(nullptr, nullptr, [] { g_device_ready = false; }) != 0) return PyErr_NoMemory();
     return PyModule_Create(&module_def);
 }

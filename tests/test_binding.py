@@ -1,5 +1,9 @@
 """What the compiled binding takes and refuses, through the public functions of `qsync` (CPU only: every call here returns before
 anything is launched -- an empty tensor, or an argument that is refused)."""
+import os
+import subprocess
+import sys
+
 import numpy as np
 import pytest
 import torch
@@ -58,3 +62,38 @@ def test_objects_that_hold_memory():
     with pytest.raises(Q.QsyncError) as e:
         Q.qsync_absmax_quantize(h(32), 4, 8, 8, 0, 0, 0, s, s, None, h(32, torch.int8), None, h(need // 4 - 1), -1, 0)
     assert e.value.status == Q.ERR_WORKSPACE
+
+
+FORK = """
+import os, sys
+import torch
+state = {"up": True}                      # stands for torch's own: initialised, and not in a process forked after that
+torch.cuda.is_initialized = lambda: state["up"]
+def current_stream():
+    raise RuntimeError("cannot re-initialize in a forked process")
+torch.cuda.current_stream = current_stream
+from paper_2407_02327_amd import qsync as Q
+x = torch.empty(4)
+def call():
+    try:
+        Q.qsync_quantize(x, 0, 4, 4, Q.FP16, 0, 0, 0, 0, 0, None, x, None)
+    except RuntimeError as e:
+        return str(e)
+    return ""
+first = call()
+assert "forked" not in first, first       # (no device here: whatever the lookup of its stream says)
+pid = os.fork()
+if pid == 0:
+    state["up"] = False
+    os._exit(0 if "forked" in call() else 1)
+sys.exit(os.waitstatus_to_exitcode(os.waitpid(pid, 0)[1]))
+"""
+
+
+@pytest.mark.skipif(torch.cuda.is_available(), reason="forks after a stand-in for the device's initialisation")
+def test_a_forked_process_is_told_so():
+    """torch says, at the first use of the device in a process that was forked from one that had used it, that this cannot work;
+    the look-up of the current stream has to ask again there."""
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    r = subprocess.run([sys.executable, "-c", FORK], cwd=root, capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stderr
