@@ -249,7 +249,8 @@ def qsync_prepare_weights(w, N, K, bits, sw, iw, aw_opt, wq, swb, iwb, wqbT, wor
 def qsync_probe_mfma(tag: int, random_operands: int, iters: int, out, stream=None) -> float:
     """Launches the probe on `stream` and returns the operation count of the launch (the caller times it)."""
     ops = ctypes.c_double(0.0)
-    _check(lib.qsync_probe_mfma(tag, int(random_operands), iters, out.data_ptr(), ctypes.byref(ops), _stream(stream)))
+    _check(lib.qsync_probe_mfma(tag, int(random_operands), iters, None if out is None else out.data_ptr(), ctypes.byref(ops),
+                                _stream(stream)))
     return ops.value
 
 

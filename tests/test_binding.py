@@ -64,6 +64,12 @@ def test_objects_that_hold_memory():
     assert e.value.status == Q.ERR_WORKSPACE
 
 
+def test_probe_without_an_output():
+    with pytest.raises(Q.QsyncError) as e:
+        Q.qsync_probe_mfma(Q.INT8, 0, 4, None, 0)
+    assert e.value.status == Q.ERR_NULL
+
+
 FORK = """
 import os, sys
 import torch
