@@ -37,6 +37,17 @@ def _scratch(nbytes: int, device) -> torch.Tensor:
     return torch.empty(max(nbytes, 256), dtype=torch.uint8, device=device)
 
 
+def _own_steps(op, steps) -> bool:
+    """Whether the `steps`, (name, function), of an operator are those of its class here.  A whole pass joins them in calls that do
+    several at once only then: a step replaced in a subclass, on the class or on the object (weights that are kept, a wrapper
+    that times) is called as it is."""
+    for name, function in steps:
+        step = getattr(op, name)
+        if getattr(step, "__func__", None) is not function or step.__self__ is not op:
+            return False
+    return True
+
+
 class QLinear:
     def __init__(self, tag: int, M: int, N: int, K: int, x_dtype=torch.float16, w_dtype=torch.float32,
                  dy_dtype=None, y_dtype=torch.float32, dx_dtype=torch.float16, dw_dtype=torch.float32,
@@ -121,6 +132,10 @@ class QLinear:
     xhT = property(lambda self: self.xh.t().contiguous() if self.own_copies else self._xhT)
     dyhT = property(lambda self: self.dyh.t().contiguous() if self.own_copies else self._dyhT)
 
+    def _in_place(self, t: torch.Tensor) -> bool:
+        """Whether an activation or gradient is the row-major operand itself (FP16 and FP32 tags)."""
+        return t.dtype == _TORCH_OF_TAG[self.tag] and t.is_contiguous() and not self.own_copies
+
     # ---- precision conversion -----------------------------------------------------------
     def convert_x(self, x: torch.Tensor, stream=None, x_amax: Optional[torch.Tensor] = None) -> None:
         """x_amax: device float holding max |x| already (the producer's `y_amax`); it replaces the pass over x
@@ -136,7 +151,7 @@ class QLinear:
                 return
             Q.qsync_quantize(x, M, K, K, Q.INT8, self.bits, Q.PER_TENSOR, Q.ROUND_NEAREST, 0, 0, self.ix, self.xq,
                              self._xqT, stream)
-        elif x.dtype == _TORCH_OF_TAG[self.tag] and x.is_contiguous() and not self.own_copies:
+        elif self._in_place(x):
             # already in the operand type: the tensor itself is the saved operand, only its transpose (if kept) is written
             self.xq = x
             if self._xqT is not None:
@@ -176,7 +191,7 @@ class QLinear:
 
     def convert_operands(self, x: torch.Tensor, w: torch.Tensor, stream=None, x_amax: Optional[torch.Tensor] = None) -> None:
         """`convert_x` and `convert_w` in one call, the two beside each other."""
-        in_place = (self.tag != Q.INT8 and x.dtype == _TORCH_OF_TAG[self.tag] and x.is_contiguous() and not self.own_copies)
+        in_place = self.tag != Q.INT8 and self._in_place(x)
         if self.tag != Q.INT8:
             self.xq = x if in_place else self._xq
         Q.qsync_convert_operands(self.tag, x, self.M, self.K, x_amax if self.tag == Q.INT8 else None, w, self.N, 1, self.bits, self.w_gran,
@@ -195,7 +210,7 @@ class QLinear:
                                       self.db, self.dyq, self._dyqT, self.ws_absmax, stream)
             self.last_dy_offset = self.offset
             self.offset += (M * N + 7) // 8
-        elif dy.dtype == _TORCH_OF_TAG[self.tag] and dy.is_contiguous() and not self.own_copies:
+        elif self._in_place(dy):
             self.dyq = dy
             if self._dyqT is not None:
                 Q.qsync_quantize(dy, M, N, N, self.tag, 0, 0, 0, 0, 0, None, None, self._dyqT, stream)
@@ -287,8 +302,11 @@ class QLinear:
                 x_amax: Optional[torch.Tensor] = None) -> torch.Tensor:
         """With `side_stream` (a torch stream of default priority) the small, latency-bound weight
         conversion kernels run beside the HBM-bound activation conversion and join before the GEMM."""
-        if side_stream is None:
+        if side_stream is None and _own_steps(self, _LINEAR_CONVERSIONS):
             self.convert_operands(x, w, stream, x_amax)
+        elif side_stream is None:
+            self.convert_x(x, stream, x_amax)
+            self.convert_w(w, stream)
         else:
             main = stream if stream is not None else torch.cuda.current_stream()
             side_stream.wait_stream(main)
@@ -299,16 +317,20 @@ class QLinear:
         return self.y
 
     def backward(self, dy: torch.Tensor, stream=None):
-        if self.tag == Q.INT8:
+        if self.tag == Q.INT8 or not _own_steps(self, _LINEAR_BACKWARD):
             self.convert_dy(dy, stream)
             self.gemm_bwd(dy, stream)
             return self.dx, self.dw, self.db
-        in_place = dy.dtype == _TORCH_OF_TAG[self.tag] and dy.is_contiguous() and not self.own_copies
+        in_place = self._in_place(dy)
         self.dyq = dy if in_place else self._dyq
         Q.qsync_qlinear_backward(self.tag, self.M, self.N, self.K, dy, None if in_place else self.dyq, self._dyqT,
                                  self.xq if self.rowmajor_bwd else self._xqT, self.rowmajor_bwd, self.wqbT, self.dx, self.dw, self.db,
                                  self.ws_bwd, stream)
         return self.dx, self.dw, self.db
+
+
+_LINEAR_CONVERSIONS = (("convert_x", QLinear.convert_x), ("convert_w", QLinear.convert_w))
+_LINEAR_BACKWARD = (("convert_dy", QLinear.convert_dy), ("gemm_bwd", QLinear.gemm_bwd))
 
 
 class QConv3x3:
@@ -365,6 +387,10 @@ class QConv3x3:
         self.ws_bwd = _scratch(Q.qsync_qlinear_bwd_workspace_bytes(tag, M, N, K) if wgrad_via_patches
                                else Q.qsync_conv3x3_wgrad_workspace_bytes(tag, nimg, H, W, C, N), device)
 
+    def _in_place(self, t: torch.Tensor) -> bool:
+        """Whether an activation or gradient is the operand itself (FP16 tag)."""
+        return t.dtype == _TORCH_OF_TAG[self.tag] and t.is_contiguous()
+
     def convert_x(self, act: torch.Tensor, stream=None, x_amax: Optional[torch.Tensor] = None) -> None:
         """x_amax: device float holding max |act| already (the producer's `y_amax`); it replaces the pass over the
         activation that finds the maximum and is left at zero for the producer's next step."""
@@ -376,7 +402,7 @@ class QConv3x3:
         elif self.tag == Q.INT8:
             Q.qsync_absmax_quantize(act, M, C, self.bits, Q.ROUND_NEAREST, 0, 0, self.sx, self.ix, self.ax, self.xq, None,
                                     self.ws_absmax, -1, stream)
-        elif act.dtype == _TORCH_OF_TAG[self.tag] and act.is_contiguous():
+        elif self._in_place(act):
             self.xq = act.view(M, C)           # already in the operand type: used in place
         else:
             self.xq = self._xq
@@ -401,7 +427,7 @@ class QConv3x3:
 
     def convert_operands(self, act: torch.Tensor, w: torch.Tensor, stream=None, x_amax: Optional[torch.Tensor] = None) -> None:
         """`convert_x` and `convert_w` in one call, the two beside each other."""
-        in_place = self.tag != Q.INT8 and act.dtype == _TORCH_OF_TAG[self.tag] and act.is_contiguous()
+        in_place = self.tag != Q.INT8 and self._in_place(act)
         if self.tag != Q.INT8:
             self.xq = act.view(self.M, self.C) if in_place else self._xq
         Q.qsync_convert_operands(self.tag, act, self.M, self.C, x_amax if self.tag == Q.INT8 else None, w, self.N, 9, self.bits,
@@ -425,7 +451,7 @@ class QConv3x3:
             Q.qsync_gradient_quantize(dy, M, N, self.bits, self.dy_round, self.seed, self.offset, self.sdy, self.idy, self.ady,
                                       self.db, self.dyq, self.dyqT, self.ws_absmax, stream)
             self.offset += (M * N + 7) // 8
-        elif dy.dtype == _TORCH_OF_TAG[self.tag] and dy.is_contiguous():
+        elif self._in_place(dy):
             self.dyq = dy
         else:
             self.dyq = self._dyq
@@ -446,7 +472,11 @@ class QConv3x3:
                             Q.PER_TENSOR, None, self.dw, None, None, None, self.acc_dw, self.ws_bwd, stream)
 
     def forward(self, act: torch.Tensor, w: torch.Tensor, stream=None, x_amax: Optional[torch.Tensor] = None) -> torch.Tensor:
-        self.convert_operands(act, w, stream, x_amax)
+        if _own_steps(self, _CONV_CONVERSIONS):
+            self.convert_operands(act, w, stream, x_amax)
+        else:
+            self.convert_w(w, stream)
+            self.convert_x(act, stream, x_amax)
         self.conv_fwd(stream)
         return self.y
 
@@ -455,3 +485,6 @@ class QConv3x3:
         self.conv_dgrad(stream)
         self.conv_wgrad(stream)
         return self.dx, self.dw, (self.db if self.tag == Q.INT8 else None)     # db comes out of the INT8 absmax pass
+
+
+_CONV_CONVERSIONS = (("convert_x", QConv3x3.convert_x), ("convert_w", QConv3x3.convert_w))
