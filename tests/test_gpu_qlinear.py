@@ -391,22 +391,28 @@ def test_whole_backward_equals_the_separate_calls(case, act):
         assert bool(((got.double() - exact).abs() <= bound).all()), "db"
 
 
-def test_row_major_backward_takes_a_workspace_without_room_behind_the_products():
-    """The workspace that held the column sums in front of the weight gradient's partial products still does."""
-    M, N, K = 16384, 256, 512
+@pytest.mark.parametrize("M, N, K", [(6144, 192, 768), (6144, 1152, 128)])
+def test_row_major_backward_takes_a_workspace_without_room_behind_the_products(M, N, K):
+    """The workspace that held the column sums in front of the weight gradient's partial products still does: shapes whose row-major
+    products, in K splits, reach over the place behind the transposed form's, where the sums then lie until they are folded."""
     say("row-major backward, smaller workspace", M, N, K)
     g = torch.Generator(device="cuda").manual_seed(3)
     dy, x = (torch.randn(M, n, generator=g, device="cuda").half() for n in (N, K))
     wT = torch.randn(K, N, generator=g, device="cuda").half()
     out = []
-    full = Q.qsync_qlinear_bwd_rm_workspace_bytes(Q.FP16, M, N, K)
-    for nbytes in (full, max(Q.qsync_qlinear_bwd_workspace_bytes(Q.FP16, M, N, K), full - 4 * 512 * N)):
-        wsp = torch.zeros(nbytes, dtype=torch.uint8, device="cuda")
+    full, sums = Q.qsync_qlinear_bwd_rm_workspace_bytes(Q.FP16, M, N, K), 4 * 512 * N
+    small = max(Q.qsync_qlinear_bwd_workspace_bytes(Q.FP16, M, N, K), full - sums)
+    assert small == full - sums            # the products alone: they end where the larger workspace has the sums
+    for nbytes in (full, small):
+        wsp = torch.full((nbytes,), 0x7E, dtype=torch.uint8, device="cuda")                       # NaN patterns
         dx, dw, db = (torch.full(s, float("nan"), device="cuda") for s in ((M, K), (N, K), (N,)))
         Q.qsync_qlinear_bwd_rm(Q.FP16, M, N, K, dy, None, x, None, wT, None, 0, dx, dw, db, dy, None, None, wsp)
+        assert Q.qsync_debug_last_gradient_pair() == -1                                           # (a pair has no K splits)
         out.append([host(t) for t in (dx, dw, db)])
     for a, b, name in zip(out[0], out[1], ("dX", "dW", "db")):
         assert_bits_equal(a, b, name)
+    dy64 = host(dy).astype(np.float64)     # a recursive fp32 sum of M terms is off by at most (M - 1) 2^-24 sum |dY|
+    assert np.all(np.abs(out[1][2] - dy64.sum(0)) <= (M - 1) * 2.0 ** -24 * np.abs(dy64).sum(0))
 
 
 @pytest.mark.parametrize("tag", [Q.INT8, Q.FP16])
@@ -415,9 +421,13 @@ def test_few_rows_equal_the_tiled_product(tag, M):
     """Few rows and small products against the 64x64 tile, bit for bit (integer sums; binary16 operands are small integers,
     whose sums below 2^24 are exact in any order): last, partial groups of rows and columns, odd N, more groups of columns than
     of rows and the reverse, 16 columns a workgroup and 32 (300x1040, 2000x130), one to many turns of the wavefronts
-    with a partial last one, the longest contractions taken, both outputs, both scale granularities, with and without bias."""
+    with a partial last one, the longest contractions taken (8 KB up to 32 rows, 6 KB above: in 16 columns with N 7, in 32 with
+    N 1040 from 300 rows and with N 130 from 2000) and 16 bytes more, which the tiles do, both outputs, both scale
+    granularities, with and without bias."""
     rng = np.random.default_rng(M)
-    for N, K in ((1, 16), (33, 48), (130, 528), (1040, 1040), (7, 4096), (256, 64)):
+    per, longest = (16, 8192 if M <= 32 else 6144) if tag == Q.INT8 else (8, 4096 if M <= 32 else 3072)
+    for N, K in ((1, 16), (33, 48), (130, 528), (1040, 1040), (256, 64), (7, longest), (7, longest + per), (130, longest),
+                 (1040, longest), (1040, longest + per)):
         lim = 127 if tag == Q.INT8 else 8
         a, b = (dev(rng.integers(-lim, lim + 1, s).astype(np.int8 if tag == Q.INT8 else np.float16)) for s in ((M, K), (N, K)))
         sx, sw, bias = (dev((rng.random(n) * 1e-3 + 1e-4).astype(np.float32)) for n in (1, N, N))
