@@ -1989,14 +1989,22 @@ hipError_t launch_quantize_int8(const void* x, int xdt, int64_t rows, int64_t co
                           qT, stream);
 }
 
+// The transposed copy of an odd row count goes one element per thread, in a pass behind the maximum's, where that is faster:
+// not up to kWholeBytes, where launched one by one a second launch costs the host more (nearest, 45 x 1024 binary16: one
+// launch 6.6 us, apart 8.5; 100 x 512 7.6 against 8.6; replayed from a graph 6.7 against 6.5 and 7.9 against 6.5), except from
+// 128 rows on (129 x 512: 9.1 against 8.7, from a graph 9.0 against 6.6; 250 x 256 8.7 against 8.5), and not from 192 K
+// elements of 16 rows or more on, where folding the maxima in the quantizer makes up for it (70 x 3744 7.5 against 8.4,
+// 500 x 528 8.1 against 8.5).
+template <typename T> static bool odd_transpose_apart(int64_t rows, int64_t n, const int8_t* qT)
+{
+    const bool whole = n * static_cast<int64_t>(sizeof(T)) <= kWholeBytes;
+    return odd_transpose_generic(rows, n, qT) && (rows < 16 || n < (int64_t(3) << 16))
+        && (!whole || (rows >= 128 && n >= (int64_t(1) << 15)));
+}
+
 // Per-tensor maximum, scales and codes of a contiguous tensor.  Up to kWholeBytes one launch, every workgroup of which
 // reads the whole tensor for its maximum (no workgroup waits for another); above that a launch that leaves one maximum
-// per block and the quantizing launch, which folds them.  The transposed copy of an odd row count goes one element per
-// thread, in two separate passes, where that is faster: not up to kWholeBytes, where launched one by one a second launch
-// costs the host more (nearest, 45 x 1024 binary16: one launch 6.6 us, apart 8.5; 100 x 512 7.6 against 8.6; replayed from a
-// graph 6.7 against 6.5 and 7.9 against 6.5), except from 128 rows on (129 x 512: 9.1 against 8.7, from a graph 9.0 against
-// 6.6; 250 x 256 8.7 against 8.5), and not from 192 K elements of 16 rows or more on, where folding the maxima in the
-// quantizer makes up for it (70 x 3744 7.5 against 8.4, 500 x 528 8.1 against 8.5).
+// per block and the quantizing launch, which folds them.
 template <typename T>
 static hipError_t absmax_quantize_typed(const T* x, int64_t rows, int64_t cols, int qmax, int rnd, uint64_t seed,
                                         uint64_t offset, float* scale, float* inv_scale, float* amax_opt, int8_t* q,
@@ -2004,9 +2012,7 @@ static hipError_t absmax_quantize_typed(const T* x, int64_t rows, int64_t cols, 
 {
     const int64_t n     = rows * cols;
     const bool    whole = n * static_cast<int64_t>(sizeof(T)) <= kWholeBytes;
-    const bool    apart = odd_transpose_generic(rows, n, qT) && (rows < 16 || n < (int64_t(3) << 16))
-                       && (!whole || (rows >= 128 && n >= (int64_t(1) << 15)));
-    if(apart || !tile_ok(x, rows, cols, cols, q, qT))
+    if(odd_transpose_apart<T>(rows, n, qT) || !tile_ok(x, rows, cols, cols, q, qT))
     {
         hipError_t e = absmax_typed(x, rows, cols, cols, kPerTensor, static_cast<float>(qmax), scale, inv_scale, amax_opt,
                                     nullptr, nullptr, workspace, st);
@@ -2224,8 +2230,7 @@ static hipError_t convert_typed(const void* x, int64_t rows, int64_t cols, int64
 // an activation whose transposed copy is large enough for 128-row tiles keeps its own launches.
 template <typename T> static bool small_tiles(int64_t rows, int64_t cols, const int8_t* qT, int64_t n)
 {
-    return tiles_of(rows, cols, 128) < 512 && !(odd_transpose_generic(rows, n, qT) && (rows < 16 || n < (int64_t(3) << 16))
-                                                && (n * static_cast<int64_t>(sizeof(T)) > kWholeBytes || (rows >= 128 && n >= (int64_t(1) << 15))));
+    return tiles_of(rows, cols, 128) < 512 && !odd_transpose_apart<T>(rows, n, qT);
 }
 template <typename T> static int64_t maxima_blocks(int64_t n)
 {
