@@ -202,6 +202,15 @@ def run(args):
     op_streams = [main] + [torch.cuda.Stream() for _ in range(len(ops_objs) - 1)]
     side_streams = [torch.cuda.Stream() for _ in ops_objs]
 
+    def convert(op, x, w, st):
+        """Both operands of a forward pass, as the operator's own forward converts them (the patch expansion has a
+        conversion of its own)."""
+        if op.convert_act == op.convert_x:
+            op.convert_operands(x, w, st)
+        else:
+            op.convert_w(w, st)
+            op.convert_act(x, st)
+
     def step(record: str, nstreams=nstreams, base=None):
         """record: "none", "gemm_fwd" (events around the forward GEMM only: the timed region) or "all".
         base: the stream of the first operator (default: the current stream at start-up)."""
@@ -222,10 +231,13 @@ def run(args):
                 run("convert_x", lambda: op.convert_act(x, st), st)
                 st.wait_stream(side)
             else:
-                run("convert_x", lambda: (op.convert_w(w, st), op.convert_act(x, st)), st)
+                run("convert_x", lambda: convert(op, x, w, st), st)
             run("gemm_fwd", lambda: op.gemm_fwd(st), st)
-            run("convert_dy", lambda: op.convert_dy(dy, st), st)
-            run("gemm_bwd", lambda: op.gemm_bwd(dy, st), st)
+            if record == "all":      # (the phases of a pass that the operator runs in one call)
+                run("convert_dy", lambda: op.convert_dy(dy, st), st)
+                run("gemm_bwd", lambda: op.gemm_bwd(dy, st), st)
+            else:
+                op.backward(dy, st)
         for st in streams[1:nstreams]:
             first.wait_stream(st)
 
@@ -235,8 +247,7 @@ def run(args):
         conversion and data-gradient GEMM on the main stream."""
         side = side_streams[0]
         for op, (x, w, dy) in zip(ops_objs, dev_in):
-            op.convert_w(w, main)
-            op.convert_act(x, main)
+            convert(op, x, w, main)
             op.gemm_fwd(main)
         for op, (x, w, dy) in reversed(list(zip(ops_objs, dev_in))):
             op.convert_dy(dy, main)
@@ -251,8 +262,7 @@ def run(args):
         gradient, then the next operator's conversions."""
         side = side_streams[0]
         for op, (x, w, dy) in zip(ops_objs, dev_in):
-            op.convert_w(w, main)
-            op.convert_act(x, main)
+            convert(op, x, w, main)
             op.gemm_fwd(main)
             op.convert_dy(dy, main)
             side.wait_stream(main)
@@ -268,8 +278,7 @@ def run(args):
         pairs = list(zip(ops_objs, dev_in))
         for i, (op, (x, w, dy)) in enumerate(pairs):
             if i == 0:
-                op.convert_w(w, main)
-                op.convert_act(x, main)
+                convert(op, x, w, main)
                 side.wait_stream(main)
                 for op2, (_, w2, _) in pairs[1:]:
                     op2.convert_w(w2, side)
