@@ -489,10 +489,11 @@ int qsync_conv3x3_prepare_weights(const void* w, int wdt, int64_t N, int64_t C, 
 size_t qsync_conv3x3_prepare_weights_workspace_bytes(int64_t N, int64_t C);
 
 /*
- * qsync_conv3x3_fwd - 3x3 / stride 1 / pad 1 convolution over an NHWC tensor as an implicit GEMM.
+ * qsync_conv3x3_fwd - 3x3 / stride 1 / pad 1 convolution over an NHWC tensor.
  * Paper: Backend section (low-precision convolution kernels run on NHWC tensors; dequantization is
  * fused into the kernel's epilogue); Appendix, proof of Prop. 2 (forward flow of a fixed-point
- * kernel).  The patch matrix is never stored: the GEMM's loads gather it from the NHWC codes.
+ * kernel).  The patch matrix is never stored: a workgroup keeps the pixels that its taps reach in LDS, or (rows too wide for
+ * that, some wide outputs) a GEMM's loads gather it from the NHWC codes.
  *
  *   y[m, n] = sx * sw[n] * sum_{kh,kw,c} xq[b, h+kh-1, w+kw-1, c] * wq[n, (kh*3+kw)*C + c] + bias[n]
  *   m = (b*H + h)*W + w; terms outside the image are zero.  FP16: the same sum over binary16 operands

@@ -332,7 +332,7 @@ int qsync_qlinear_fwd_codes(int tag, int64_t M, int64_t N, int64_t K, const void
     if(!yq || !next_inv_scale) return QSYNC_ERR_NULL;
     if(bits < 2 || bits > 8) return QSYNC_ERR_UNSUPPORTED;
     if(y_amax_opt && (reinterpret_cast<uintptr_t>(y_amax_opt) & 3u) != 0) return QSYNC_ERR_ALIGN;
-    // fp32 operands whose rows are not 16-byte multiples run the any-shape kernel, which has no code output
+    // fp32 operands whose rows are not 16-byte multiples are refused: launch_gemm_f32, which takes them, hands its epilogue no codes
     if(tag == QSYNC_FP32 && ((K * 4) % 16 != 0 || !aligned16(xq) || !aligned16(wq))) return QSYNC_ERR_UNSUPPORTED;
     return qlinear_fwd_impl(tag, M, N, K, xq, sx, wq, sw, wgran, bias_opt, y, ydt, nullptr, y_amax_opt, workspace,
                             workspace_bytes, stream, yq, next_inv_scale, (1 << (bits - 1)) - 1);

@@ -534,8 +534,8 @@ template <int THREADS> struct ColumnFold
     __device__ __forceinline__ void run(uint32_t block, uint8_t* lds) const { fold_columns(f, block, reinterpret_cast<float*>(lds)); }
 };
 
-// Column sums of a small tensor in one go: 16 columns per workgroup, THREADS / 16 row lanes (at most kColumnSumRows rows: their
-// loads are all in flight at once), folded in order.
+// Column sums of a small tensor in one go: 16 columns per workgroup, THREADS / 16 row lanes, folded in order.  At most
+// kColumnSumRows rows: of 512 threads that is two batches of eight loads in flight per lane.
 constexpr int64_t kColumnSumRows = 512;
 template <typename T, int THREADS> struct ColumnSum
 {

@@ -335,8 +335,9 @@ _LINEAR_BACKWARD = (("convert_dy", QLinear.convert_dy), ("gemm_bwd", QLinear.gem
 
 class QConv3x3:
     """One 3x3 / stride 1 / pad 1 NHWC convolution as quantized operator (paper: Backend section, low-precision
-    convolution on NHWC tensors).  All three passes run as implicit GEMMs over the codes (the patch matrix is never
-    stored); the weight gradient contracts over the pixels.  Buffers are allocated once; nothing here computes.
+    convolution on NHWC tensors).  No pass stores the patch matrix: forward and data gradient keep the pixels that their
+    taps reach in LDS or gather them in a GEMM's loads, the weight gradient, which contracts over the pixels, gathers them.
+    Buffers are allocated once; nothing here computes.
 
     INT8 and FP16: all three passes (the patch-matrix form of the weight gradient is INT8 only).
     The weight gradient reads the gradient and the activation as they lie (qsync_conv3x3_wgrad);
