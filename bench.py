@@ -114,7 +114,7 @@ def parse_args():
     ap.add_argument("--conv-input", default="nhwc", choices=["nhwc", "patches", "implicit"],
                     help="workload c3 with tag int8: start each step from the NHWC activation (quantize it once, "
                          "expand int8 codes into the patch matrix), from the fp16 patch matrix, or run the convolution "
-                         "itself (implicit: forward and data gradient gather patches inside the GEMM, dX is the NHWC "
+                         "itself (implicit: no patch matrix is stored, dX is the NHWC "
                          "gradient [M,C] instead of the patch gradient [M,9C])")
     ap.add_argument("--tag", default="int8", choices=["int8", "fp16"])
     ap.add_argument("--bwd-tag", default=None, choices=[None, "fp16"],
@@ -613,7 +613,8 @@ def run(args):
                    "activation_and_gradient_codes": "row-major only" if min(ncopies) == 1 else "row-major + transposed copy",
                    **({"conv_input": args.conv_input if (tag == Q.INT8 or args.conv_input == "implicit") else "patches"}
                       if any(c.nhwc is not None for c in cases) else {})},
-        "roofline": {"bound": "mfma", "kernel": "gemm_nt_kernel (forward GEMM launches; HIP events on every 4th timed step)",
+        "roofline": {"bound": "mfma", "kernel": ("conv3x3_kernel (forward launches" if any(hasattr(o, "conv_fwd") for o in ops_objs)
+                                              else "gemm_nt_kernel (forward GEMM launches") + "; HIP events on every 4th timed step)",
                      "achieved": round(achieved, 2), "peak": peak, "unit": "TOP/s" if args.tag == "int8" else "TFLOP/s",
                      "frac": round(achieved / peak, 4),
                      "traffic": measured_traffic(args.workload, args.tag, args.ydtype),
