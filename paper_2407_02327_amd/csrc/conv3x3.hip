@@ -331,7 +331,7 @@ hipError_t launch_conv3x3(const GemmProblem& p, int force_tile, bool* taken, hip
         typedef decltype(tr) TR;
         return kc == 32 ? launch_shape<TR, 32>(a, shape, taken, st) : kc == 64 ? launch_shape<TR, 64>(a, shape, taken, st) : launch_shape<TR, 128>(a, shape, taken, st);
     };
-    return p.prec == 8 ? go(I8Traits{}) : go(F16Traits{});
+    return p.prec == 8 ? go(I8Rows32{}) : go(F16Rows32{});
 }
 
 }  // namespace qsync

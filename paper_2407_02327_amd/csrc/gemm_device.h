@@ -14,6 +14,7 @@ namespace {
 typedef int      v4i32 __attribute__((ext_vector_type(4)));
 typedef int      v16i32 __attribute__((ext_vector_type(16)));
 typedef float    v16f32 __attribute__((ext_vector_type(16)));
+typedef float    v4f32 __attribute__((ext_vector_type(4)));
 typedef _Float16 v8f16 __attribute__((ext_vector_type(8)));
 typedef unsigned v4u32 __attribute__((ext_vector_type(4)));
 
@@ -23,45 +24,72 @@ constexpr int kNumXcd     = 8;
 constexpr int kNumCu      = 256;  // compute units of the target: one persistent workgroup each
 constexpr int kGroupM     = 8;    // tile rows walked together (default; GemmKernelArgs::group_m)
 
+// A fragment is kRows operand rows of 16 bytes a lane, 64 / kRows lanes side by side along K.  The products run on the instructions of
+// 16 rows and columns: with operand values that vary, the chip lowers its clock for either shape, but less for these (nothing but
+// matrix instructions, N(0,1) values, 32x32 -> 16x16: int8 3.5 -> 4.2 POP/s, binary16 1.67 -> 1.95 PFLOP/s; the same 4.9 and
+// 2.45 on zeros), although they read twice the operand registers per operation.
 struct I8Traits
 {
     typedef int32_t acc_t;
-    typedef v16i32  accv_t;
-    static constexpr int kElemBytes = 1;
-    __device__ static __forceinline__ accv_t mfma(const v4i32& a, const v4i32& b, const accv_t& c)
+    typedef v4i32   accv_t;
+    static constexpr int kElemBytes = 1, kRows = 16, kSteps = 1;
+    __device__ static __forceinline__ accv_t mfma(const v4i32& a, const v4i32& b, const accv_t& c, int = 0)
     {
-        return __builtin_amdgcn_mfma_i32_32x32x32_i8(a, b, c, 0, 0, 0);
+        return __builtin_amdgcn_mfma_i32_16x16x64_i8(a, b, c, 0, 0, 0);
     }
 };
 struct F16Traits
 {
     typedef float  acc_t;
-    typedef v16f32 accv_t;
-    static constexpr int kElemBytes = 2;
-    __device__ static __forceinline__ accv_t mfma(const v4i32& a, const v4i32& b, const accv_t& c)
+    typedef v4f32  accv_t;
+    static constexpr int kElemBytes = 2, kRows = 16, kSteps = 1;
+    __device__ static __forceinline__ accv_t mfma(const v4i32& a, const v4i32& b, const accv_t& c, int = 0)
     {
-        return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(v8f16, a), __builtin_bit_cast(v8f16, b), c, 0,
-                                                      0, 0);
+        return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(v8f16, a), __builtin_bit_cast(v8f16, b), c, 0, 0, 0);
     }
 };
-
-// fp32 operands: a lane's 16 K-bytes are four floats of one row; the 32x32x2 instruction takes one float per
-// lane (rows lane%32, K index lane/32), so the four components feed four instructions.  Every instruction pairs
-// the same components of A and B, i.e. the same K indices: the K axis is merely visited in a different order.
-struct F32Traits
+// 32 rows and columns
+struct I8Rows32
+{
+    typedef int32_t acc_t;
+    typedef v16i32  accv_t;
+    static constexpr int kElemBytes = 1, kRows = 32;
+    __device__ static __forceinline__ accv_t mfma(const v4i32& a, const v4i32& b, const accv_t& c)
+    {
+        return __builtin_amdgcn_mfma_i32_32x32x32_i8(a, b, c, 0, 0, 0);
+    }
+};
+struct F16Rows32
 {
     typedef float  acc_t;
     typedef v16f32 accv_t;
-    static constexpr int kElemBytes = 4;
+    static constexpr int kElemBytes = 2, kRows = 32;
     __device__ static __forceinline__ accv_t mfma(const v4i32& a, const v4i32& b, const accv_t& c)
     {
-        typedef float v4f32 __attribute__((ext_vector_type(4)));
-        const v4f32 fa = __builtin_bit_cast(v4f32, a), fb = __builtin_bit_cast(v4f32, b);
-        accv_t      r  = __builtin_amdgcn_mfma_f32_32x32x2f32(fa.x, fb.x, c, 0, 0, 0);
-        r              = __builtin_amdgcn_mfma_f32_32x32x2f32(fa.y, fb.y, r, 0, 0, 0);
-        r              = __builtin_amdgcn_mfma_f32_32x32x2f32(fa.z, fb.z, r, 0, 0, 0);
-        return __builtin_amdgcn_mfma_f32_32x32x2f32(fa.w, fb.w, r, 0, 0, 0);
+        return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(v8f16, a), __builtin_bit_cast(v8f16, b), c, 0, 0,
+                                                      0);
     }
+};
+
+// fp32 operands: a lane's 16 K-bytes are four floats of one row; the 16x16x4 instruction takes one float per
+// lane (rows lane%16, K index lane/16), so the four components feed four instructions (steps).  Every instruction pairs
+// the same components of A and B, i.e. the same K indices: the K axis is merely visited in a different order.
+struct F32Traits
+{
+    typedef float acc_t;
+    typedef v4f32 accv_t;
+    static constexpr int kElemBytes = 4, kRows = 16, kSteps = 4;
+    __device__ static __forceinline__ accv_t mfma(const v4i32& a, const v4i32& b, const accv_t& c, int step)
+    {
+        return __builtin_amdgcn_mfma_f32_16x16x4f32(__builtin_bit_cast(v4f32, a)[step], __builtin_bit_cast(v4f32, b)[step], c, 0, 0, 0);
+    }
+};
+// 32 rows and columns, sums only (gemm_f32_any_kernel forms its operands itself)
+struct F32Rows32
+{
+    typedef float  acc_t;
+    typedef v16f32 accv_t;
+    static constexpr int kElemBytes = 4, kRows = 32;
 };
 
 struct GemmKernelArgs
@@ -102,6 +130,15 @@ __device__ __forceinline__ int64_t uniform64(int64_t v)
     const uint32_t lo = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(static_cast<uint32_t>(u))));
     const uint32_t hi = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(static_cast<uint32_t>(u >> 32))));
     return static_cast<int64_t>((static_cast<uint64_t>(hi) << 32) | static_cast<uint64_t>(lo));
+}
+
+// The lane's index, formed anew where it is asked for: behind a K loop that needs every register, what hangs on it does not have to
+// be kept through the loop.
+__device__ __forceinline__ int lane_again()
+{
+    int l;
+    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
+    return l;
 }
 
 // Work item (K split, tile) of a workgroup.  Workgroups are dealt round-robin to the eight XCDs
@@ -235,12 +272,19 @@ template <int OS> __device__ __forceinline__ uint32_t abs_bits_as_f32(uint32_t r
     return __float_as_uint(__half2float(__ushort_as_half(static_cast<unsigned short>(h))));
 }
 
-// One 16-byte LDS read per fragment of a set, as explicit instructions (the waits are placed by hand in the
-// K loop): fragment I lies I * 32 rows further, which fits the instruction's immediate offset.
-template <int I>
+// One 16-byte LDS read per fragment, as explicit instructions (the waits are placed by hand in the K loop); OFF is the
+// instruction's immediate byte offset (16 bits).
+template <int OFF>
 __device__ __forceinline__ void frag_read(v4i32& dst, uint32_t addr)
 {
-    asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(dst) : "v"(addr), "n"(I * 32 * kRowBytes) : "memory");
+    static_assert(OFF >= 0 && OFF < 65536, "immediate offset");
+    asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(dst) : "v"(addr), "n"(OFF) : "memory");
+}
+// at most N of this wavefront's LDS operations still in flight (other counters untouched).  The counter holds 15, so a wait for more
+// than 14 is one for 14, which also tells a full counter from one that is not.
+template <int N> __device__ __forceinline__ void wait_lds()
+{
+    __builtin_amdgcn_s_waitcnt(0xC07F | ((N < 14 ? N : 14) << 8));
 }
 typedef unsigned v2u32 __attribute__((ext_vector_type(2)));
 // compile-time loop: f(std::integral_constant<int, 0>), ..., f(std::integral_constant<int, N - 1>)
@@ -263,14 +307,25 @@ template <int ESZ, int OFF> __device__ __forceinline__ void frag_read_tr(v2u32& 
     else
         asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(dst) : "v"(addr), "n"(OFF) : "memory");
 }
-// XOR term (in 16-byte chunks) of stage row `row` of a TN operand region whose rows are RB bytes long: the rows that
-// one pass of a transposing read touches (8 rows x 32 bytes for ESZ 1, 4 rows x 64 bytes for ESZ 2) land in
-// different bank groups.  Unchanged by the row steps between the reads of one lane (multiples of 8, resp. 4).
+// XOR term (in 16-byte chunks) of stage row `row` of a TN operand region whose rows are RB bytes long: the rows that one pass of a
+// transposing read touches (32 lanes: 8 rows and the 8 rows 16 further down x 16 bytes for ESZ 1; 4 rows and the 4 rows 8
+// further down x 32 bytes for ESZ 2) land in different bank groups.  Unchanged by the row steps between the reads of one lane
+// (8 and multiples of 64 rows, resp. 4 and multiples of 32).
 template <int ESZ, int RB> __device__ __forceinline__ int tn_swizzle(int row)
 {
     constexpr int CPR = RB / 16;                                    // chunks per row
-    if constexpr(ESZ == 1) return 2 * ((row / (16 / CPR)) % (CPR / 2));
-    else                   return RB >= 256 ? 4 * (row % 4) : 4 * ((row / 2) % 2);
+    if constexpr(ESZ == 1)
+    {
+        constexpr int L = CPR == 16 ? 0 : CPR == 8 ? 1 : 2;         // rows that share 256 bytes, as a power of two
+        static_assert(CPR == 16 || CPR == 8 || CPR == 4, "rows of 64 to 256 bytes");
+        return ((row & 7) >> L) | (((row >> 4) & 1) << (3 - L));
+    }
+    else
+    {
+        constexpr int L = CPR >= 16 ? 0 : 1;
+        static_assert(CPR == 32 || CPR == 16 || CPR == 8, "rows of 128 to 512 bytes");
+        return 2 * (((row & 3) >> L) | (((row >> 3) & 1) << (2 - L)));
+    }
 }
 // Workgroup barrier behind a wait for this wavefront's LDS operations only (the compiler's __syncthreads would also
 // wait for every vector-memory operation in flight, i.e. drain the queue of direct loads).
@@ -289,25 +344,20 @@ template <int DPW, int N> __device__ __forceinline__ void wait_tiles(int n)
     else                 wait_tiles<DPW, N - 1>(n);
 }
 __device__ __forceinline__ void lds_write_b32(uint32_t addr, uint32_t v) { asm volatile("ds_write_b32 %0, %1" ::"v"(addr), "v"(v) : "memory"); }
-template <int F, int... Is>
-__device__ __forceinline__ void frag_reads(v4i32 (&dst)[F], uint32_t addr, std::integer_sequence<int, Is...>)
-{
-    (frag_read<Is>(dst[Is], addr), ...);
-}
 
 // Epilogue: a workgroup's accumulators to memory.  The B fragment is the matrix instruction's first operand, so a lane holds
-// C^T fragments: lane -> output row m = lane%32 of the fragment; register v -> output column n = 8*(v/4) + 4*(lane/32) +
-// v%4, i.e. four consecutive columns per register quad.  `lds`: STG_BYTES per wavefront that nobody reads any more behind the
+// C^T fragments: lane -> output row m = lane%R of the fragment (R = 16 or 32 rows); register v -> output column n = 8*(v/4) +
+// 4*(lane/R) + v%4, i.e. four consecutive columns per register quad (one quad for 16 rows).  `lds`: STG_BYTES per wavefront that nobody reads any more behind the
 // first barrier here; `colp`: column scales and biases [2][BN], maximum slots behind them.
 template <typename TR, int BM, int BN, int WGM, int WGN, int STG_BYTES, bool SPLIT>
-__device__ __forceinline__ void store_tile(const GemmKernelArgs& p, typename TR::accv_t (&acc)[BM / WGM / 32][BN / WGN / 32], uint8_t* lds,
+__device__ __forceinline__ void store_tile(const GemmKernelArgs& p, typename TR::accv_t (&acc)[BM / WGM / TR::kRows][BN / WGN / TR::kRows], uint8_t* lds,
                                            float* colp, int64_t m0, int64_t n0, int split, float alpha, float code_inv, uint32_t amax_seen)
 {
     typedef typename TR::accv_t accv_t;
     typedef typename TR::acc_t  acc_t;
-    constexpr int WTM = BM / WGM, WTN = BN / WGN, FM = WTM / 32, FN = WTN / 32;
-    const int tid = threadIdx.x, lane = tid % kWaveSize, wave = __builtin_amdgcn_readfirstlane(tid / kWaveSize);
-    const int wm = wave / WGN, wn = wave % WGN, frag_row = lane & 31, khalf = lane >> 5;
+    constexpr int R = TR::kRows, WTM = BM / WGM, WTN = BN / WGN, FM = WTM / R, FN = WTN / R, QUADS = R == 32 ? 4 : 1;
+    const int lane = lane_again(), wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / kWaveSize);
+    const int wm = wave / WGN, wn = wave % WGN, frag_row = lane % R, cquad = lane / R;
     const int64_t wrow0 = m0 + wm * WTM, wcol0 = n0 + wn * WTN;
     // Staged stores: pass the wavefront's sub-tile through its private slice of LDS (the K
     // pipeline is drained, so the stages are free) and leave with 16-byte stores whose lanes run
@@ -329,7 +379,7 @@ __device__ __forceinline__ void store_tile(const GemmKernelArgs& p, typename TR:
         uint32_t* slots = reinterpret_cast<uint32_t*>(colp + 2 * BN);
         if(lane == 0) slots[wave] = bits_f32;
         __syncthreads();
-        if(tid == 0)
+        if(wave == 0 && lane == 0)
         {
             uint32_t m = slots[0];
 #pragma unroll
@@ -350,13 +400,13 @@ __device__ __forceinline__ void store_tile(const GemmKernelArgs& p, typename TR:
         constexpr bool RAW   = decltype(raw_tag)::value;
         constexpr int  OS    = sizeof(out_t);
         constexpr int  PITCH = WTN * OS + 16;                    // padded row pitch in the staging slice
-        constexpr int  FITS  = STG_BYTES / (32 * PITCH);
-        constexpr int  FPP   = FITS >= FM ? FM : (FITS >= 2 && FM % 2 == 0 ? 2 : 1);      // row fragments per pass
-        static_assert(32 * PITCH <= STG_BYTES && FM % FPP == 0, "staging slice too small");
+        constexpr int  FITS  = STG_BYTES / (R * PITCH);
+        constexpr int  FPP   = FITS >= FM ? FM : FITS >= 4 && FM % 4 == 0 ? 4 : FITS >= 2 && FM % 2 == 0 ? 2 : 1;      // row fragments per pass
+        static_assert(R * PITCH <= STG_BYTES && FM % FPP == 0, "staging slice too small");
         constexpr int EPV = 16 / OS;                             // elements per 16-byte vector
         constexpr int LPR = WTN / EPV;                           // lanes per output row in the store phase
         constexpr int RPI = 64 / LPR;                            // rows per store instruction
-        static_assert(64 % LPR == 0 && (FPP * 32) % RPI == 0, "store instructions cover whole rows");
+        static_assert(64 % LPR == 0 && (FPP * R) % RPI == 0, "store instructions cover whole rows");
         const bool    vec = (p.N * OS) % 16 == 0 && (reinterpret_cast<uintptr_t>(dst_base) & 15) == 0;
         const int     seg = lane % LPR, lr0 = lane / LPR;
         const int64_t col = wcol0 + seg * EPV;
@@ -367,12 +417,12 @@ __device__ __forceinline__ void store_tile(const GemmKernelArgs& p, typename TR:
 #pragma unroll
             for(int j = 0; j < FN; ++j)
             {
-                float4 fs[4], bs[4];                      // scale and bias of the lane's columns (alpha * column scale, as one product)
+                float4 fs[QUADS], bs[QUADS];                      // scale and bias of the lane's columns (alpha * column scale, as one product)
                 if constexpr(!RAW)
 #pragma unroll
-                    for(int vq = 0; vq < 4; ++vq)
+                    for(int vq = 0; vq < QUADS; ++vq)
                     {
-                        const int c = wn * WTN + j * 32 + 8 * vq + 4 * khalf;          // column inside the tile
+                        const int c = wn * WTN + j * R + 8 * vq + 4 * cquad;          // column inside the tile
                         const float4 cs = *reinterpret_cast<const float4*>(colp + c);
                         const float4 cb = *reinterpret_cast<const float4*>(colp + BN + c);
                         fs[vq] = p.col_scale ? make_float4(alpha * cs.x, alpha * cs.y, alpha * cs.z, alpha * cs.w)
@@ -382,10 +432,10 @@ __device__ __forceinline__ void store_tile(const GemmKernelArgs& p, typename TR:
 #pragma unroll
                 for(int ii = 0; ii < FPP; ++ii)
 #pragma unroll
-                    for(int vq = 0; vq < 4; ++vq)
+                    for(int vq = 0; vq < QUADS; ++vq)
                     {
                         const accv_t& a   = acc[pass * FPP + ii][j];
-                        uint8_t*      dst = stg + (ii * 32 + frag_row) * PITCH + (j * 32 + 8 * vq + 4 * khalf) * OS;
+                        uint8_t*      dst = stg + (ii * R + frag_row) * PITCH + (j * R + 8 * vq + 4 * cquad) * OS;
                         if constexpr(RAW)
                         {
                             const out_t o[4] = {a[vq * 4], a[vq * 4 + 1], a[vq * 4 + 2], a[vq * 4 + 3]};
@@ -409,12 +459,12 @@ __device__ __forceinline__ void store_tile(const GemmKernelArgs& p, typename TR:
             // wavefront's LDS operations in order, and the wavefront-scope fence tells the compiler
             // that these loads may not be satisfied from values a lane has seen before.
             __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-            const int64_t row0 = wrow0 + pass * FPP * 32 + lr0;
+            const int64_t row0 = wrow0 + pass * FPP * R + lr0;
             if constexpr(!RAW)
                 if(vec && p.codes && (reinterpret_cast<uintptr_t>(p.codes) & (EPV - 1)) == 0)
                 {   // C and its codes as vectors (with the quantizer's arithmetic: one fp32 multiply, ties to even, clamp)
 #pragma unroll 2
-                    for(int r = 0; r < FPP * 32; r += RPI)
+                    for(int r = 0; r < FPP * R; r += RPI)
                     {
                         const v4u32 val = *reinterpret_cast<const v4u32*>(stg + (r + lr0) * PITCH + seg * 16);
                         uint32_t    cw[EPV / 4];
@@ -444,7 +494,7 @@ __device__ __forceinline__ void store_tile(const GemmKernelArgs& p, typename TR:
                 uint8_t* dst = dst_base + (row0 * p.N + col) * OS;
                 const int64_t step = RPI * p.N * OS;
 #pragma unroll
-                for(int r = 0; r < FPP * 32; r += RPI, dst += step)
+                for(int r = 0; r < FPP * R; r += RPI, dst += step)
                 {
                     const v4u32 val = *reinterpret_cast<const v4u32*>(stg + (r + lr0) * PITCH + seg * 16);
                     if(row0 + r < p.M && col < p.N)
@@ -460,7 +510,7 @@ __device__ __forceinline__ void store_tile(const GemmKernelArgs& p, typename TR:
                 continue;
             }
 #pragma unroll 1
-            for(int r = 0; r < FPP * 32; r += RPI)
+            for(int r = 0; r < FPP * R; r += RPI)
             {
                 const v4u32   val = *reinterpret_cast<const v4u32*>(stg + (r + lr0) * PITCH + seg * 16);
                 const int64_t row = row0 + r, left = row < p.M ? p.N - col : 0;      // valid elements from here on (may be <= 0)

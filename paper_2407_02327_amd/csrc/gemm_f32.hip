@@ -110,7 +110,7 @@ __global__ __launch_bounds__(256) void gemm_f32_any_kernel(const GemmKernelArgs 
         if(t + 1 < tiles) put(t + 1);      // (read last before the barrier that ended the turn before this one)
         __syncthreads();
     }
-    store_tile<F32Traits, T, T, 2, 2, T * kPitch * 4, SPLIT>(p, acc, lds, colp, m0, n0, split, alpha, 0.0f, seen);
+    store_tile<F32Rows32, T, T, 2, 2, T * kPitch * 4, SPLIT>(p, acc, lds, colp, m0, n0, split, alpha, 0.0f, seen);
 }
 
 template <int T> hipError_t launch_any(const GemmKernelArgs& a, int64_t K, int splits, hipStream_t st)

@@ -1,12 +1,12 @@
 // LDS-tiled MFMA GEMM for gfx950 (CDNA4):  C[M,N] = epilogue( sum_k A[m,k] * B[n,k] ).
 //
 // Both operands are K-contiguous ("NT"), which is exactly the operand shape of the gfx950
-// 32x32 matrix instructions: every lane feeds 16 contiguous K-bytes of one row of A and of
-// one row of B (v_mfma_i32_32x32x32_i8: 16 int8; v_mfma_f32_32x32x16_f16: 8 binary16).  The
+// 16x16 matrix instructions: every lane feeds 16 contiguous K-bytes of one row of A and of
+// one row of B (v_mfma_i32_16x16x64_i8: 16 int8; v_mfma_f32_16x16x32_f16: 8 binary16).  The
 // INT8 and FP16 kernels therefore move identical bytes and share one tiling:
 //
 //   * block tile BM x BN, K step of 128 bytes per row; WGM x WGN wavefronts, each owning a
-//     (BM/WGM) x (BN/WGN) sub-tile as 32x32 accumulator fragments.  The large tile is
+//     (BM/WGM) x (BN/WGN) sub-tile as 16x16 accumulator fragments.  The large tile is
 //     256x256 with 8 wavefronts (2 per SIMD, 128 accumulator registers each), so that one
 //     wavefront's LDS reads and barrier waits hide behind the other's matrix instructions;
 //   * global -> LDS with direct 16-byte loads (global_load_lds_dwordx4), bypassing the VGPRs;
@@ -15,8 +15,8 @@
 //     (applied on the global-address side of the direct load): the 16 lanes that read one
 //     chunk index of 16 consecutive rows then touch 16 different 16-byte bank groups;
 //   * two LDS stages (three for the 128x128 tile while no compute unit gets a second workgroup): the next K
-//     step streams in while the current one feeds the matrix cores; fragments for the next 32-byte K chunk are requested before the current chunk's
-//     matrix instructions; one barrier per K step;
+//     step streams in while the current one feeds the matrix cores; a fragment of the next 64-byte K chunk is requested
+//     behind the last matrix instruction that reads its registers; one barrier per K step;
 //   * the dequantizer (scalar scales, per-column scale vector, per-column bias) runs on the
 //     accumulator registers (the paper fuses dequantization at the same point: before the
 //     accumulators are copied to shared memory); the B fragment is fed as the instruction's
@@ -76,7 +76,7 @@ __device__ __forceinline__ void conv_sequence(std::integer_sequence<int, Ds...>,
 // TN form with the B operand gathered from an NHWC tensor (weight gradient of the 3x3 convolution): stage row r of
 // K tile kt is pixel m = kt * KR + r, and a lane's 16-byte chunk lies in one tap (dh, dw) at channel offset c0, both
 // fixed per load slot; what changes from K tile to K tile is the pixel, i.e. (h, w).  `delta` holds the slot's whole
-// constant part ((dh W + dw) Cb + c0 + r Cb); `code` = (dh + 1) | (dw + 1) << 2 | valid << 4; `hw` = h << 16 | w of the
+// constant part ((dh W + dw) Cb + c0 + r Cb); `code`, low byte: (dh + 1) | (dw + 1) << 2 | valid << 4; `hw` = h << 16 | w of the
 // pixel of the NEXT K tile to be requested and is advanced by KR pixels here (dr = KR % W, hq = (KR / W) % H).
 template <int D, int DPW>
 __device__ __forceinline__ void conv_tn_issue(const uint8_t* x, const uint8_t* zero, int64_t pix_base, int delta, int code,
@@ -85,7 +85,7 @@ __device__ __forceinline__ void conv_tn_issue(const uint8_t* x, const uint8_t* z
     constexpr int IMM = dma_imm<D, DPW>();
     int        h = static_cast<int>(hw >> 16), w = static_cast<int>(hw & 0xffffu);
     const int  hh = h + (code & 3) - 1, ww = w + ((code >> 2) & 3) - 1;
-    const bool inb = (code >> 4) != 0 && static_cast<unsigned>(hh) < static_cast<unsigned>(H)
+    const bool inb = ((code >> 4) & 1) != 0 && static_cast<unsigned>(hh) < static_cast<unsigned>(H)
                      && static_cast<unsigned>(ww) < static_cast<unsigned>(W);
     const uint8_t* src = inb ? x + (pix_base + delta) : zero;
     __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src - IMM),
@@ -100,10 +100,10 @@ __device__ __forceinline__ void conv_tn_issue(const uint8_t* x, const uint8_t* z
 
 template <int DPW, int... Ds>
 __device__ __forceinline__ void conv_tn_sequence(std::integer_sequence<int, Ds...>, const uint8_t* x, const uint8_t* zero,
-                                                 int64_t pix_base, const int (&delta)[DPW], const int (&code)[DPW],
+                                                 int64_t pix_base, const uint32_t (&delta)[DPW], const uint32_t (&codes)[(DPW + 3) / 4],
                                                  uint32_t (&hw)[DPW], int H, int W, int dr, int hq, uint8_t* lds_mid)
 {
-    (conv_tn_issue<Ds, DPW>(x, zero, pix_base, delta[Ds], code[Ds], hw[Ds], H, W, dr, hq, lds_mid), ...);
+    (conv_tn_issue<Ds, DPW>(x, zero, pix_base, static_cast<int>(delta[Ds]), static_cast<int>(codes[Ds / 4] >> (8 * (Ds % 4))), hw[Ds], H, W, dr, hq, lds_mid), ...);
 }
 
 // TN, last K tile with fewer contraction rows than a stage holds: rows from `rows` on are fetched from the tile's first
@@ -137,10 +137,11 @@ __device__ __forceinline__ void gemm_tile(const GemmKernelArgs& p, int lin, int 
     typedef typename TR::acc_t  acc_t;
     constexpr int kThreads = 64 * WGM * WGN;
     constexpr int WTM = BM / WGM, WTN = BN / WGN;   // wavefront sub-tile
-    constexpr int FM = WTM / 32, FN = WTN / 32;     // 32x32 fragments per wavefront
+    constexpr int R = TR::kRows, FM = WTM / R, FN = WTN / R;         // fragments per wavefront
+    constexpr int CH = kRowBytes / (16 * (64 / R));                 // K chunks (16 bytes of each of 64 / R lanes) per K tile
     constexpr int STAGE_BYTES = (BM + BN) * kRowBytes;
     constexpr int DPW = (BM + BN) / 8 / (WGM * WGN);    // direct-load instructions per wavefront per K tile
-    static_assert(WTM % 32 == 0 && WTN % 32 == 0, "wavefront sub-tiles are made of 32x32 fragments");
+    static_assert(R == 16 && CH == 2 && WTM % R == 0 && WTN % R == 0 && FM >= FN && (FN == 2 || FN == 4), "fragments of a wavefront");
     static_assert((BM + BN) % (8 * WGM * WGN) == 0 && BM % 16 == 0, "stage rows must split evenly over the wavefronts");
 
     extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
@@ -180,7 +181,7 @@ __device__ __forceinline__ void gemm_tile(const GemmKernelArgs& p, int lin, int 
     const int64_t  rows_left = is_a ? p.M - m0 : p.N - n0;           // >= 1
     uint32_t       voff[DPW];                                         // lane offset + kDmaBias - immediate
     uint32_t       hw[CONV ? DPW : 1];       // CONVTN: (h << 16) | w of the lane's pixels; CONVA: their taps inside the image
-    int            tnc_delta[CONVTN ? DPW : 1], tnc_code[CONVTN ? DPW : 1];      // CONVTN, B side (see conv_tn_issue)
+    uint32_t       tnc_code[CONVTN ? (DPW + 3) / 4 : 1] = {};      // CONVTN, B side (see conv_tn_issue), a byte per load; voff holds the deltas there
     int            gchunk[2];                                         // the swizzle term depends on d%2 only
     {
         int imm[DPW];
@@ -202,17 +203,16 @@ __device__ __forceinline__ void gemm_tile(const GemmKernelArgs& p, int lin, int 
                     if(!is_a)
                     {   // B side: column byte (n0 * ESZ + 16 chunk) of the implicit [pixels, 9 C] matrix = tap, channel offset
                         constexpr int KR = kRowBytes / ESZ;                       // pixels per K tile
-                        const int64_t colb  = n0 * ESZ + static_cast<int64_t>(chunk) * 16;
-                        const bool    valid = colb < static_cast<int64_t>(9) * p.conv_Cb;      // tile columns past 9 C: zeros, never stored
-                        const int     tap   = valid ? static_cast<int>(colb / p.conv_Cb) : 0;
-                        const int     c0    = valid ? static_cast<int>(colb - static_cast<int64_t>(tap) * p.conv_Cb) : 0;
+                        const uint32_t colb  = static_cast<uint32_t>(n0) * ESZ + static_cast<uint32_t>(chunk) * 16u;      // (9 C < 2^24)
+                        const bool     valid = colb < 9u * static_cast<uint32_t>(p.conv_Cb);      // tile columns past 9 C: zeros, never stored
+                        const int      tap   = valid ? static_cast<int>(colb / static_cast<uint32_t>(p.conv_Cb)) : 0;
+                        const int      c0    = valid ? static_cast<int>(colb) - tap * p.conv_Cb : 0;
                         const int     kh = (tap * 11) >> 5, kw = tap - 3 * kh;          // tap / 3 for tap < 12
-                        tnc_delta[d] = ((kh - 1) * p.conv_W + (kw - 1)) * p.conv_Cb + c0 + row * p.conv_Cb;
-                        tnc_code[d]  = kh | (kw << 2) | (valid ? 16 : 0);
+                        voff[d]      = static_cast<uint32_t>(((kh - 1) * p.conv_W + (kw - 1)) * p.conv_Cb + c0 + row * p.conv_Cb);
+                        tnc_code[d / 4] |= static_cast<uint32_t>(kh | (kw << 2) | (valid ? 16 : 0)) << (8 * (d % 4));
                         const uint32_t m  = static_cast<uint32_t>(kt_begin) * KR + static_cast<uint32_t>(row);
                         const uint32_t qq = m / static_cast<uint32_t>(p.conv_W);
                         hw[d]   = ((qq % static_cast<uint32_t>(p.conv_H)) << 16) | (m - qq * static_cast<uint32_t>(p.conv_W));
-                        voff[d] = 0u;
                         continue;
                     }
                 if(static_cast<int64_t>(chunk) * 16 >= width) chunk = 0;    // columns past the matrix: any valid chunk, never stored
@@ -285,7 +285,7 @@ __device__ __forceinline__ void gemm_tile(const GemmKernelArgs& p, int lin, int 
     const int64_t tn_ld = TN ? uniform64(is_a ? p.M : p.N) : 0;      // operand row length in elements
     // TN: stage row of the lane in load slot 0, rows from slot to slot, and the contraction rows of a partial last K tile
     constexpr int tn_rps = TN ? 1024 / (BM * ESZ) : 0;
-    const int     tn_row0 = TN ? ((wave * DPW - (is_a ? 0 : BM / 8)) * 1024 + lane * 16) / (BM * ESZ) : 0;
+    auto          tn_first_row = [&]() { return ((wave * DPW - (is_a ? 0 : BM / 8)) * 1024 + lane_again() * 16) / (BM * ESZ); };
     const int     tn_tail_rows = TN ? static_cast<int>(p.Kb % kRowBytes) / ESZ : 0;
     auto dma = [&](int stage, int kt) {
         const int64_t  kb    = static_cast<int64_t>(kt) * kRowBytes;
@@ -294,11 +294,14 @@ __device__ __forceinline__ void gemm_tile(const GemmKernelArgs& p, int lin, int 
             if(!is_a)
             {   // (requested for consecutive K tiles only, starting at kt_begin: hw is advanced by every call)
                 if(kt == tail_kt)      // (the last request) stage rows without a pixel read zeros
+                {
+                    const int row0 = tn_first_row();
 #pragma unroll
                     for(int d = 0; d < DPW; ++d)
-                        if(tn_row0 + d * tn_rps >= tn_tail_rows) tnc_code[d] = 0;
+                        if(row0 + d * tn_rps >= tn_tail_rows) tnc_code[d / 4] &= ~(0xFFu << (8 * (d % 4)));
+                }
                 conv_tn_sequence<DPW>(std::make_integer_sequence<int, DPW>{}, p.B, reinterpret_cast<const uint8_t*>(&g_zero_chunk),
-                                      static_cast<int64_t>(kt) * tnc_KR * p.conv_Cb, tnc_delta, tnc_code, hw, p.conv_H, p.conv_W,
+                                      static_cast<int64_t>(kt) * tnc_KR * p.conv_Cb, voff, tnc_code, hw, p.conv_H, p.conv_W,
                                       tnc_dr, tnc_hq, lbase);
                 return;
             }
@@ -327,7 +330,7 @@ __device__ __forceinline__ void gemm_tile(const GemmKernelArgs& p, int lin, int 
         const uint8_t* sb    = TN ? sbase0 + kb * tn_ld : sbase0 + kb;      // TN: 128 operand rows further
         asm volatile("" : "+s"(sb));      // keep base + K offset a scalar pair: the lane offsets stay loop-invariant 32-bit values
         if(TN && kt == tail_kt)
-            dma_sequence_short<DPW, tn_rps>(std::make_integer_sequence<int, DPW>{}, sb, voff, tn_row0, tn_tail_rows,
+            dma_sequence_short<DPW, tn_rps>(std::make_integer_sequence<int, DPW>{}, sb, voff, tn_first_row(), tn_tail_rows,
                                             static_cast<uint32_t>(tn_ld * ESZ), lbase);
         else if(!TN && kt == tail_kt)
             dma_sequence_tail<DPW>(std::make_integer_sequence<int, DPW>{}, sb, voff, gchunk, kb, p.Kb, lbase);
@@ -340,11 +343,12 @@ __device__ __forceinline__ void gemm_tile(const GemmKernelArgs& p, int lin, int 
     auto zero_tail = [&](int stage, int kt) {
         if((!CONVTN || is_a) && kt == tail_kt)
         {
-            const int64_t kb = static_cast<int64_t>(kt) * kRowBytes;
+            const int64_t kb   = static_cast<int64_t>(kt) * kRowBytes;
+            const int     l    = lane_again(), row0 = TN ? ((wave * DPW - (is_a ? 0 : BM / 8)) * 1024 + l * 16) / (BM * ESZ) : 0;
 #pragma unroll
             for(int d = 0; d < DPW; ++d)
-                if(TN ? tn_row0 + d * tn_rps >= tn_tail_rows : kb + gchunk[d & 1] >= p.Kb)
-                    *reinterpret_cast<uint4*>(lds + stage * STAGE_BYTES + (wave * DPW + d) * 1024 + lane * 16)
+                if(TN ? row0 + d * tn_rps >= tn_tail_rows : kb + gchunk[d & 1] >= p.Kb)
+                    *reinterpret_cast<uint4*>(lds + stage * STAGE_BYTES + (wave * DPW + d) * 1024 + l * 16)
                         = make_uint4(0, 0, 0, 0);
         }
     };
@@ -362,108 +366,104 @@ __device__ __forceinline__ void gemm_tile(const GemmKernelArgs& p, int lin, int 
 #pragma unroll
         for(int j = 0; j < FN; ++j)
 #pragma unroll
-            for(int v = 0; v < 16; ++v) acc[i][j][v] = 0;
+            for(int v = 0; v < 4; ++v) acc[i][j][v] = 0;
 
-    // Fragment reads: lane -> row lane%32 of a fragment, K chunk 2*ks + lane/32.  The swizzle term
-    // (row/2)%8 is the same for every fragment of a lane because fragments start at multiples of 32.
-    const int frag_row = lane & 31, khalf = lane >> 5;
-    int       roff[4];
+    // Fragment reads: lane -> row lane%16 of a fragment, 16-byte chunk 4*c + lane/16 of the stage row.  The swizzle term
+    // (row/2)%8 is the same for every fragment of a lane because fragments start at multiples of 16.
+    const int frag_row = lane % R, kq = lane / R;
+    int       roff[CH];
 #pragma unroll
-    for(int ks = 0; ks < 4; ++ks) roff[ks] = frag_row * kRowBytes + swizzle(frag_row, ks * 2 + khalf);
+    for(int c = 0; c < CH; ++c) roff[c] = frag_row * kRowBytes + swizzle(frag_row, c * (8 / CH) + kq);
     const int a_base = (wm * WTM) * kRowBytes, b_base = BM * kRowBytes + (wn * WTN) * kRowBytes;
 
     // The fragment reads are written as instructions with hand-placed waits.  The compiler's own wait
     // insertion treats a direct global->LDS load as an access that may return through either counter, and
     // while one is in flight (always, here) every wait it places on an LDS read becomes "all LDS reads
     // done", including the reads just issued for a later chunk: the wavefront would then sit out a full LDS
-    // latency twice per K tile.  LDS reads of a wavefront return in order, so "at most FM + FN outstanding"
-    // is exactly "the older of two fragment sets has arrived".
-    v4i32          af[2][FM], bf[2][FN];
+    // latency twice per K tile.  LDS reads of a wavefront return in order, so "at most n outstanding" says which have arrived.
+    constexpr bool ROLL = FM > 4;                    // one set of registers for the rows' fragments (below)
+    v4i32          af[ROLL ? 1 : 2][FM], bf[2][FN];
     const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) uint8_t*)lds));
-    // TN: lane (kb = lane/32, g = (lane%32)/16, s = lane%16) receives row 16 g + s of a fragment.
-    // int8: it supplies the 8-byte half s%2 of chunk (first chunk of the sub-tile + 2f + g) of contraction row
-    // 32 ks + 16 kb + 8 r + s/2 (r = 0, 1: the two reads of a fragment) and receives contraction indices
-    // 32 ks + 16 kb + 8 r + 0..7.  binary16: the 8-byte half s%2 of chunk (first chunk + 4f + 2g + (s%4)/2) of
-    // contraction row 16 ks + 8 kb + 4 r + s/4; it receives contraction indices 16 ks + 8 kb + 4 r + 0..3.
-    uint32_t tn_a[TN ? FM : 1], tn_b[TN ? FN : 1];
+    // TN: lane (q = lane/16, s = lane%16) receives row s of a fragment.
+    // int8: it supplies the 8-byte half s%2 of chunk (first chunk of the sub-tile + f) of contraction row
+    // 64 c + 16 q + 8 r + s/2 (r = 0, 1: the two reads of a fragment) and receives contraction indices
+    // 64 c + 16 q + 8 r + 0..7.  binary16: the 8-byte half s%2 of chunk (first chunk + 2f + (s%4)/2) of
+    // contraction row 32 c + 8 q + 4 r + s/4; it receives contraction indices 32 c + 8 q + 4 r + 0..3.
+    // A sub-tile's first chunk is a multiple of its fragments' chunks, so every fragment lies at one lane's address with a
+    // wavefront-uniform chunk XORed in, which leaves stage bases (multiples of 1024) alone: one register for all of them.
+    uint32_t       tn_lane = 0u;
+    const uint32_t tn_a = static_cast<uint32_t>(wm * WTM * ESZ), tn_b = static_cast<uint32_t>(wn * WTN * ESZ);
     if constexpr(TN)
     {
         constexpr int RB = BM * ESZ;
-        const int s16 = lane & 15, g = (lane >> 4) & 1, kb16 = lane >> 5;
-        const int prow = ESZ == 1 ? 16 * kb16 + s16 / 2 : 8 * kb16 + s16 / 4;   // + ks and r steps through the immediate
-        const int swz  = tn_swizzle<ESZ, RB>(prow);
-        const int lch  = ESZ == 1 ? g : 2 * g + (s16 & 3) / 2;                   // chunk inside the fragment's columns
-        constexpr int CPF = 2 * ESZ;                                            // chunks per 32-column fragment
-#pragma unroll
-        for(int f = 0; f < FM; ++f)
-            tn_a[f] = static_cast<uint32_t>(prow * RB + ((((wm * WTM * ESZ) / 16 + CPF * f + lch) ^ swz) * 16) + 8 * (s16 & 1));
-#pragma unroll
-        for(int f = 0; f < FN; ++f)
-            tn_b[f] = static_cast<uint32_t>(128 * BM + prow * RB + ((((wn * WTN * ESZ) / 16 + CPF * f + lch) ^ swz) * 16) + 8 * (s16 & 1));
+        static_assert((WTM / 16) % FM == 0 && (WTN / 16) % FN == 0 && RB <= 1024, "fragments by XOR");
+        const int s16 = lane & 15;
+        const int prow = ESZ == 1 ? 16 * kq + s16 / 2 : 8 * kq + s16 / 4;       // + c and r steps through the immediate
+        const int lch  = ESZ == 1 ? 0 : (s16 & 3) / 2;                           // chunk inside the fragment's columns
+        tn_lane = static_cast<uint32_t>(prow * RB + ((lch ^ tn_swizzle<ESZ, RB>(prow)) * 16) + 8 * (s16 & 1));
     }
-    auto           load_frags = [&](auto buf_tag, int stage, int ks) {
-        constexpr int  buf = decltype(buf_tag)::value;
-        if constexpr(TN)
-        {
-            const uint32_t sb = lds0 + static_cast<uint32_t>(stage * STAGE_BYTES + ks * 32 * BM);
-            static_for<FM>([&](auto ft) {
-                constexpr int f = decltype(ft)::value;
-                v2u32 lo, hi;
-                frag_read_tr<ESZ, 0>(lo, sb + tn_a[f]);
-                frag_read_tr<ESZ, 8 * BM>(hi, sb + tn_a[f]);
-                af[buf][f] = v4i32{static_cast<int>(lo.x), static_cast<int>(lo.y), static_cast<int>(hi.x), static_cast<int>(hi.y)};
-            });
-            static_for<FN>([&](auto ft) {
-                constexpr int f = decltype(ft)::value;
-                v2u32 lo, hi;
-                frag_read_tr<ESZ, 0>(lo, sb + tn_b[f]);
-                frag_read_tr<ESZ, 8 * BN>(hi, sb + tn_b[f]);
-                bf[buf][f] = v4i32{static_cast<int>(lo.x), static_cast<int>(lo.y), static_cast<int>(hi.x), static_cast<int>(hi.y)};
-            });
-            return;
-        }
-        const uint32_t fa  = lds0 + static_cast<uint32_t>(stage * STAGE_BYTES + a_base + roff[ks]);
-        const uint32_t fb  = lds0 + static_cast<uint32_t>(stage * STAGE_BYTES + b_base + roff[ks]);
-        frag_reads<FM>(af[buf], fa, std::make_integer_sequence<int, FM>{});
-        frag_reads<FN>(bf[buf], fb, std::make_integer_sequence<int, FN>{});
+    // fragment f of chunk c of the stage at LDS address sb
+    auto read_tn = [&](v4i32& d, uint32_t addr, auto ct) {
+        constexpr int c = decltype(ct)::value;
+        v2u32 lo, hi;
+        frag_read_tr<ESZ, c * 64 * BM>(lo, addr);
+        frag_read_tr<ESZ, c * 64 * BM + 8 * BM>(hi, addr);
+        d = v4i32{static_cast<int>(lo.x), static_cast<int>(lo.y), static_cast<int>(hi.x), static_cast<int>(hi.y)};
     };
-    // lgkmcnt(reads of one fragment set), other counters untouched.  TN issues two reads per fragment (at most 12
-    // per set; the counter holds 15 and a wavefront's further LDS instructions wait while it is full).
-    constexpr int kReadsPerSet  = TN ? 2 * (FM + FN) : FM + FN;
-    static_assert(kReadsPerSet <= 15, "the LDS counter holds 15");
-    constexpr int kWaitOlderSet = 0xC07F | (kReadsPerSet << 8);
-    static_assert(FM + FN <= 15, "the LDS counter holds 15");
-    auto mma = [&](auto buf_tag) {
-        constexpr int buf = decltype(buf_tag)::value;
+    auto read_a = [&](auto ft, auto ct, uint32_t sb) {
+        constexpr int f = decltype(ft)::value, c = decltype(ct)::value;
+        if constexpr(TN) read_tn(af[ROLL ? 0 : c][f], (sb + tn_lane) ^ (tn_a + static_cast<uint32_t>(f * ESZ * 16)), ct);
+        else             frag_read<f * R * kRowBytes>(af[ROLL ? 0 : c][f], sb + static_cast<uint32_t>(a_base + roff[c]));
+    };
+    auto read_b = [&](auto ft, auto ct, uint32_t sb) {
+        constexpr int f = decltype(ft)::value, c = decltype(ct)::value;
+        if constexpr(TN) read_tn(bf[c][f], (sb + 128 * BM + tn_lane) ^ (tn_b + static_cast<uint32_t>(f * ESZ * 16)), ct);
+        else             frag_read<f * R * kRowBytes>(bf[c][f], sb + static_cast<uint32_t>(b_base + roff[c]));
+    };
+    constexpr int kPer = TN ? 2 : 1;                 // LDS instructions per fragment
+    // row fragment f of chunk c: FN matrix instructions; every other row walks its columns backwards, so that the B operand
+    // stays from one row to the next (instructions on the same operands draw less power: +2 % of the rate above)
+    auto mma = [&](auto ft, auto ct) {
+        constexpr int f = decltype(ft)::value, c = decltype(ct)::value;
         __builtin_amdgcn_sched_barrier(0);           // fences: the matrix instructions stay behind the wait in front of them
 #pragma unroll
-        for(int i = 0; i < FM; ++i)
+        for(int k = 0; k < TR::kSteps; ++k)
 #pragma unroll
-            for(int j = 0; j < FN; ++j) acc[i][j] = TR::mfma(bf[buf][j], af[buf][i], acc[i][j]);
+            for(int jj = 0; jj < FN; ++jj)
+            {
+                const int j = f % 2 ? FN - 1 - jj : jj;
+                acc[f][j]   = TR::mfma(bf[c][j], af[ROLL ? 0 : c][f], acc[f][j], k);
+            }
         __builtin_amdgcn_sched_barrier(0);
     };
-    const std::integral_constant<int, 0> set0{};
-    const std::integral_constant<int, 1> set1{};
 
-    // K pipeline.  A tile has four 32-byte K chunks whose fragments alternate between two
-    // register sets: the reads for chunk ks+2 are issued right behind the matrix instructions of
-    // chunk ks (into the set those instructions have just consumed), so they complete while
-    // chunk ks+1 keeps the matrix cores busy, and every wait in front of a chunk leaves the
-    // younger set's reads in flight.  At the tile boundary the wavefront (1) joins the barrier
-    // that publishes the next stage (every wavefront's reads of the current stage have returned
-    // by then: the barrier's fence waits for them), (2) requests the direct load of the tile
-    // after next into the stage just drained (half of the wavefronts: behind step 4 instead, see
-    // below), (3) reads chunk 0 of the next tile, (4) issues chunk 3, whose operands are already
-    // in registers, and (5) reads chunk 1 of the next tile: barrier release, LDS latency and a
-    // whole K tile of memory latency hide behind matrix work.
+    // K pipeline.  A tile has two 64-byte K chunks.
+    // Wavefronts of few fragments hold those of both chunks: behind the matrix instructions of chunk 0 the wavefront joins the
+    // barrier that publishes the next stage (every wavefront's reads of the current one have returned by then), requests the
+    // direct load of the tile after next into the stage just drained (half of the wavefronts: at the end of the tile
+    // instead, see below), reads chunk 0 of the next tile, issues chunk 1, whose operands are already in registers, and reads
+    // chunk 1 of the next tile: barrier release, LDS latency and a whole K tile of memory latency hide behind matrix work.
+    // With four rows (128 tile) the reads go out between the rows' instructions, and the load behind row 0: 4096x768x3072
+    // int8 16.4 -> 15.7 us, binary16 28.0 -> 26.4, against all of them at the chunk's end; the 64 tile, of which a unit holds
+    // several, gains nothing from that (its convolution's weight gradient 32.2 -> 33.2).
+    // The 256 tile's wavefronts have no registers for both chunks.  A row's fragment is used by FN instructions in a row and
+    // never again, so its registers are requested anew, for the next chunk, right behind them; the columns'
+    // fragments, which every row uses, have two sets, and those of the next chunk are requested behind the first rows.  In chunk 1 no
+    // row in front of the middle requests anything: there the barrier and the load's request follow, then the next tile's columns
+    // and first rows, and the other rows go on as before.
+    // 32x32 instructions with four 32-byte chunks and two sets of fragments -> this, values N(0,1), us: 16384x1024x4096 int8
+    // 60.7 -> 54.8, binary16 115 -> 105, 16384x4096x1024 int8 89.4 -> 83.2; 8192^3 2.44 -> 2.92 POP/s and 1.22 -> 1.46 PFLOP/s;
+    // on zeros, i.e. at the full clock, within 2 % of the same times.  128 tile: 4096x3072x768 int8 16.4 -> 15.2, binary16
+    // 25.6 -> 24.3; row-major 4096x768x3072, one workgroup a unit, binary16 35.8 -> 35.0, int8 20.5 -> 21.7.  64 tile:
+    // 2048x2048x1024 binary16 15.2 -> 14.3, 1808x1040x784 int8 8.1 -> 7.7, a single workgroup walking 48 K tiles 17.6 -> 18.2.
     // The column scales and biases of this tile are fetched by direct loads as well, in front of the first K tile, and
     // wait in LDS behind the stages for the epilogue.
     // The direct loads of a K tile are not requested by all wavefronts at once.  A compute unit takes such an
     // instruction (1 KB) at about 64 bytes per clock, and a wavefront issues nothing else while its loads
     // queue up: with every wavefront requesting right behind the barrier, both wavefronts of every SIMD sit
     // in that queue together and the matrix pipeline idles until the unit has taken all (BM + BN) / 8 of them.
-    // The upper half of the wavefronts (the second wavefront of each SIMD) therefore requests behind its chunk
-    // 3 instead: while one wavefront of a SIMD queues loads, its sibling issues matrix instructions
+    // The upper half of the wavefronts (the second wavefront of each SIMD) therefore requests behind its last
+    // chunk instead: while one wavefront of a SIMD queues loads, its sibling issues matrix instructions
     // (launched alone: 4-10 % fewer cycles per launch on every tile shape, int8 and binary16).
     const bool late_loader = wave >= WGM * WGN / 2;
     float* colp = reinterpret_cast<float*>(lds + ST * STAGE_BYTES);       // [2][BN]: scale, bias
@@ -488,31 +488,95 @@ __device__ __forceinline__ void gemm_tile(const GemmKernelArgs& p, int lin, int 
         wait_tiles<DPW, ST - 1>(kt_end - 1 - kt_begin);      // tile 0; up to ST - 1 tiles are requested behind it
         zero_tail(0, kt_begin);
         wg_barrier();
-        load_frags(set0, 0, 0);
-        load_frags(set1, 0, 1);
+        constexpr int H = FM / 2;
+        const std::integral_constant<int, 0> c0{};
+        const std::integral_constant<int, 1> c1{};
+        auto read_chunk = [&](auto ct, uint32_t sb) {
+            static_for<FN>([&](auto j) { read_b(j, ct, sb); });
+            static_for<FM>([&](auto i) { read_a(i, ct, sb); });
+        };
+        // Both chunks held, four rows: the other chunk's columns and first row go out behind row 0, its other rows behind row 1.
+        auto requested   = [](int i) constexpr { return i == 0 ? 0 : i == 1 ? FN + 1 : FN + FM; };      // in front of row i
+        auto read_behind = [&](auto it, auto ct, uint32_t sb) {
+            constexpr int i = decltype(it)::value;
+            if constexpr(i == 0)
+            {
+                static_for<FN>([&](auto j) { read_b(j, ct, sb); });
+                read_a(std::integral_constant<int, 0>{}, ct, sb);
+            }
+            if constexpr(i == 1)
+                static_for<FM - 1>([&](auto r) { read_a(std::integral_constant<int, decltype(r)::value + 1>{}, ct, sb); });
+        };
+        read_chunk(c0, lds0);
+        if constexpr(FM == 2) read_chunk(c1, lds0);
         int stage = 0;
         for(int kt = kt_begin; kt < kt_end; ++kt)
         {
-            const bool more  = kt + 1 < kt_end;
-            const int  next  = stage + 1 < ST ? stage + 1 : 0;
-            __builtin_amdgcn_s_waitcnt(kWaitOlderSet);
-            mma(set0);
-            load_frags(set0, stage, 2);
-            __builtin_amdgcn_s_waitcnt(kWaitOlderSet);
-            mma(set1);
-            load_frags(set1, stage, 3);
-            __builtin_amdgcn_s_waitcnt(kWaitOlderSet);
-            mma(set0);
+            const bool     more = kt + 1 < kt_end;
+            const int      next = stage + 1 < ST ? stage + 1 : 0;
+            const uint32_t sb   = lds0 + static_cast<uint32_t>(stage * STAGE_BYTES);
+            // without a next tile the reads behind the barrier fetch the current stage again: in bounds, unused
+            const uint32_t nb      = lds0 + static_cast<uint32_t>((more ? next : stage) * STAGE_BYTES);
+            const bool     request = kt + ST < kt_end;
+            if constexpr(ROLL)
+            {
+                static_for<FM>([&](auto it) {
+                    // Younger than this row's fragment: those of the FM - 1 other rows and of min(2 i, FN) columns (and younger
+                    // than the last column's, at row 0: FM - 1 rows)
+                    constexpr int i = decltype(it)::value;
+                    wait_lds<kPer * (FM - 1 + (2 * i < FN ? 2 * i : FN))>();
+                    mma(it, c0);
+                    if constexpr(2 * i < FN)
+                    {
+                        read_b(std::integral_constant<int, 2 * i>{}, c1, sb);
+                        read_b(std::integral_constant<int, 2 * i + 1>{}, c1, sb);
+                    }
+                    read_a(it, c1, sb);
+                });
+                static_for<H>([&](auto it) {
+                    wait_lds<kPer * (FM - 1 - decltype(it)::value)>();
+                    mma(it, c1);
+                });
+            }
+            else if constexpr(FM == 2)
+            {
+                wait_lds<kPer * (FM + FN)>();
+                static_for<FM>([&](auto it) { mma(it, c0); });
+            }
+            else
+                static_for<FM>([&](auto it) {
+                    constexpr int i = decltype(it)::value;
+                    wait_lds<kPer * (FM - 1 - i + requested(i))>();
+                    mma(it, c0);
+                    read_behind(it, c1, sb);
+                });
+            wait_lds<0>();
             if(more) land(next, kt + 1);
-            // without a next tile the reads below fetch chunks 0 and 1 of the current stage again: in bounds, unused
-            const int  nstage  = more ? next : stage;
-            const bool request = kt + ST < kt_end;
-            if(request && !late_loader) dma(stage, kt + ST);
-            load_frags(set0, nstage, 0);
-            __builtin_amdgcn_s_waitcnt(kWaitOlderSet);
-            mma(set1);
+            if((ROLL || FM == 2) && request && !late_loader) dma(stage, kt + ST);
+            if constexpr(ROLL)
+            {
+                static_for<FN>([&](auto j) { read_b(j, c0, nb); });
+                static_for<H>([&](auto i) { read_a(i, c0, nb); });
+                static_for<FM - H>([&](auto it) {
+                    const std::integral_constant<int, H + decltype(it)::value> row{};
+                    mma(row, c1);
+                    read_a(row, c0, nb);
+                });
+            }
+            else if constexpr(FM == 2)
+            {
+                read_chunk(c0, nb);
+                static_for<FM>([&](auto it) { mma(it, c1); });
+                read_chunk(c1, nb);
+            }
+            else
+                static_for<FM>([&](auto it) {
+                    mma(it, c1);
+                    read_behind(it, c0, nb);
+                    if constexpr(decltype(it)::value == 0)
+                        if(request && !late_loader) dma(stage, kt + ST);
+                });
             if(request && late_loader) dma(stage, kt + ST);
-            load_frags(set1, nstage, 1);
             stage = next;
         }
     }
@@ -520,15 +584,12 @@ __device__ __forceinline__ void gemm_tile(const GemmKernelArgs& p, int lin, int 
     // keeps the compiler from handing them out in front of it.
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     if(any_k)
+    {
 #pragma unroll
-        for(int b = 0; b < 2; ++b)
-        {
+        for(int f = 0; f < FM; ++f) asm volatile("" : "+v"(af[0][f]), "+v"(af[ROLL ? 0 : 1][f]));
 #pragma unroll
-            for(int f = 0; f < FM; ++f) asm volatile("" : "+v"(af[b][f]));
-#pragma unroll
-            for(int f = 0; f < FN; ++f) asm volatile("" : "+v"(bf[b][f]));
-        }
-
+        for(int f = 0; f < FN; ++f) asm volatile("" : "+v"(bf[0][f]), "+v"(bf[1][f]));
+    }
     else
         wait_direct_loads<0>();                  // the column parameters
     const float    alpha     = scale0 * scale1;
@@ -537,8 +598,10 @@ __device__ __forceinline__ void gemm_tile(const GemmKernelArgs& p, int lin, int 
     store_tile<TR, BM, BN, WGM, WGN, 2 * STAGE_BYTES / (WGM * WGN), SPLIT>(p, acc, lds, colp, m0, n0, split, alpha, code_inv, amax_seen);
 }
 
+// (Two wavefronts a SIMD at least, i.e. at most 256 registers each: with more allowed the compiler keeps the accumulators in the other
+// half of the register file, and moves the 64 tile's from there and back on every K tile.)
 template <typename TR, int BM, int BN, int WGM, int WGN, int ST, bool SPLIT, bool CONV = false, bool TN = false>
-__global__ __launch_bounds__(64 * WGM * WGN) void gemm_nt_kernel(const GemmKernelArgs p)
+__global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm_nt_kernel(const GemmKernelArgs p)
 {
     gemm_tile<TR, BM, BN, WGM, WGN, ST, SPLIT, CONV, TN>(p, static_cast<int>(blockIdx.y * gridDim.x + blockIdx.x),
                                                          static_cast<int>(gridDim.y));
@@ -554,7 +617,7 @@ struct GemmPairArgs
     ColumnFoldArgs fold;
 };
 template <typename TR, int BM, int BN, int WGM, int WGN, int ST, bool TNA>
-__global__ __launch_bounds__(64 * WGM * WGN) void gemm_nt_pair_kernel(const GemmPairArgs p)
+__global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm_nt_pair_kernel(const GemmPairArgs p)
 {
     const int blk = static_cast<int>(blockIdx.x);
     if(blk >= p.total)
@@ -610,7 +673,8 @@ template <typename TR>
 __global__ __launch_bounds__(512) void gemm_nt_persistent_kernel(const GemmKernelArgs p, const int total_tiles)
 {
     typedef typename TR::accv_t accv_t;
-    constexpr int BM = 256, BN = 256, WGN = 4, WTM = 128, WTN = 64, FM = 4, FN = 2;
+    constexpr int BM = 256, BN = 256, WGN = 4, WTM = 128, WTN = 64, R = TR::kRows, FM = WTM / R, FN = WTN / R;
+    static_assert(R == 16, "fragments of a wavefront");
     constexpr int STAGE_BYTES = (BM + BN) * kRowBytes;        // 64 KB
     constexpr int DPW         = 16;                           // direct loads per loader wavefront and K tile
     constexpr int PITCH       = WTN * 2 + 16;                 // padded row of 64 binary16 outputs in the hand-over area
@@ -670,30 +734,33 @@ __global__ __launch_bounds__(512) void gemm_nt_persistent_kernel(const GemmKerne
         lds_write_b32(lds0 + COLP_BASE + (BN + tid) * 4, __float_as_uint(bi));
     };
 
-    // ---- fragment reads (as in gemm_nt_kernel)
-    const int frag_row = lane & 31, khalf = lane >> 5;
-    int       roff[4];
+    // ---- fragment reads (as in gemm_nt_kernel, but one set of registers for the columns too: there are none left for two)
+    const int frag_row = lane % R, kq = lane / R;
+    int       roff[2];
 #pragma unroll
-    for(int ks = 0; ks < 4; ++ks) roff[ks] = frag_row * kRowBytes + swizzle(frag_row, ks * 2 + khalf);
+    for(int c = 0; c < 2; ++c) roff[c] = frag_row * kRowBytes + swizzle(frag_row, c * 4 + kq);
     const int a_base = (wm * WTM) * kRowBytes, b_base = BM * kRowBytes + (wn * WTN) * kRowBytes;
-    v4i32     af[2][FM], bf[2][FN];
-    auto      load_frags = [&](auto buf_tag, int stage, int ks) {
-        constexpr int  buf = decltype(buf_tag)::value;
-        const uint32_t fa  = lds0 + static_cast<uint32_t>(stage * STAGE_BYTES + a_base + roff[ks]);
-        const uint32_t fb  = lds0 + static_cast<uint32_t>(stage * STAGE_BYTES + b_base + roff[ks]);
-        frag_reads<FM>(af[buf], fa, std::make_integer_sequence<int, FM>{});
-        frag_reads<FN>(bf[buf], fb, std::make_integer_sequence<int, FN>{});
+    v4i32     af[FM], bf[FN];
+    auto      read_a = [&](auto ft, int stage, int c) {
+        frag_read<decltype(ft)::value * R * kRowBytes>(af[decltype(ft)::value], lds0 + static_cast<uint32_t>(stage * STAGE_BYTES + a_base + roff[c]));
     };
-    constexpr int kWaitOlderSet = 0xC07F | ((FM + FN) << 8);
-    accv_t        acc[FM][FN];
-    auto          mma = [&](auto buf_tag) {
-        constexpr int buf = decltype(buf_tag)::value;
+    auto read_b = [&](auto ft, int stage, int c) {
+        frag_read<decltype(ft)::value * R * kRowBytes>(bf[decltype(ft)::value], lds0 + static_cast<uint32_t>(stage * STAGE_BYTES + b_base + roff[c]));
+    };
+    accv_t acc[FM][FN];
+    auto   mma = [&](auto ft) {
+        constexpr int f = decltype(ft)::value;
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for(int i = 0; i < FM; ++i)
-#pragma unroll
-            for(int j = 0; j < FN; ++j) acc[i][j] = TR::mfma(bf[buf][j], af[buf][i], acc[i][j]);
+        for(int j = 0; j < FN; ++j) acc[f][j] = TR::mfma(bf[j], af[f], acc[f][j]);
         __builtin_amdgcn_sched_barrier(0);
+    };
+    // the last row of a chunk, and the next chunk's columns behind it
+    const std::integral_constant<int, FM - 1> last_row{};
+    auto turn = [&](int stage, int c) {
+        mma(last_row);
+        static_for<FN>([&](auto j) { read_b(j, stage, c); });
+        read_a(last_row, stage, c);
     };
     auto clear_acc = [&]() {
 #pragma unroll
@@ -701,10 +768,8 @@ __global__ __launch_bounds__(512) void gemm_nt_persistent_kernel(const GemmKerne
 #pragma unroll
             for(int j = 0; j < FN; ++j)
 #pragma unroll
-                for(int v = 0; v < 16; ++v) acc[i][j][v] = 0;
+                for(int v = 0; v < 4; ++v) acc[i][j][v] = 0;
     };
-    const std::integral_constant<int, 0> set0{};
-    const std::integral_constant<int, 1> set1{};
 
     // ---- first tile: both stages requested, column parameters parked, first K tile awaited
     int lin = static_cast<int>(blockIdx.x);
@@ -731,19 +796,26 @@ __global__ __launch_bounds__(512) void gemm_nt_persistent_kernel(const GemmKerne
         const uint8_t* nxt = has_next ? panel_base(ntm, ntn) : cur;
 
         // ---- K loop.  On entry K tile 0 is in stage 0 and published, K tile 1 is in flight towards stage 1.
-        load_frags(set0, 0, 0);
-        load_frags(set1, 0, 1);
+        static_for<FN>([&](auto j) { read_b(j, 0, 0); });
+        static_for<FM>([&](auto i) { read_a(i, 0, 0); });
         for(int kt = 0; kt < KT; ++kt)
         {
             const int stage = kt & 1;
-            __builtin_amdgcn_s_waitcnt(kWaitOlderSet);
-            mma(set0);
-            load_frags(set0, stage, 2);
-            __builtin_amdgcn_s_waitcnt(kWaitOlderSet);
-            mma(set1);
-            load_frags(set1, stage, 3);
-            __builtin_amdgcn_s_waitcnt(kWaitOlderSet);
-            mma(set0);
+            // chunk 0: younger than the fragment of row i are those of the FM - 1 other rows, less than the rows requested last
+            // behind the columns
+            static_for<FM - 1>([&](auto it) {
+                if constexpr(decltype(it)::value == 0) wait_lds<1>();
+                else                                   wait_lds<FM - 1>();
+                mma(it);
+                read_a(it, stage, 1);
+            });
+            wait_lds<FM - 1>();
+            turn(stage, 1);
+            static_for<FM / 2>([&](auto it) {
+                wait_lds<1>();
+                mma(it);
+            });
+            wait_lds<0>();
             const bool more = kt + 1 < KT;
             if(more)
             {
@@ -756,13 +828,21 @@ __global__ __launch_bounds__(512) void gemm_nt_persistent_kernel(const GemmKerne
                     else if(has_next) dma(stage, nxt, 0);        // kt + 2 == KT: stage 0, first K tile of the next tile
                 }
             }
-            // on the last K tile the reads below fetch chunks 0 and 1 of the current stage again: in bounds, unused
+            // on the last K tile the reads below fetch chunk 0 of the current stage again: in bounds, unused
             const int nstage = more ? (stage ^ 1) : stage;
-            load_frags(set0, nstage, 0);
-            __builtin_amdgcn_s_waitcnt(kWaitOlderSet);
-            mma(set1);
-            load_frags(set1, nstage, 1);
+            static_for<FM / 2>([&](auto it) { read_a(it, nstage, 0); });
+            static_for<FM / 2 - 1>([&](auto it) {
+                const std::integral_constant<int, FM / 2 + decltype(it)::value> row{};
+                mma(row);
+                read_a(row, nstage, 0);
+            });
+            turn(nstage, 0);
         }
+        wait_lds<0>();
+#pragma unroll
+        for(int f = 0; f < FM; ++f) asm volatile("" : "+v"(af[f]));
+#pragma unroll
+        for(int f = 0; f < FN; ++f) asm volatile("" : "+v"(bf[f]));
 
         // ---- epilogue.  Stage 1 (last K tile) is drained once everybody passes this barrier.
         wg_barrier();
@@ -771,39 +851,35 @@ __global__ __launch_bounds__(512) void gemm_nt_persistent_kernel(const GemmKerne
         // private 32-row slice, pass by pass (the storer's base steps back by one pass per pass, so that both
         // use the same immediates)
         const uint32_t my_stg  = lds0 + (loader ? STG_BASE + wave * L_STG : S_BASE + (wave - 4) * S_STG);
-        const uint32_t wr_lane = my_stg + static_cast<uint32_t>(frag_row * PITCH + 8 * khalf);
-        const uint32_t cp_lane = lds0 + COLP_BASE + static_cast<uint32_t>((wn * WTN + 4 * khalf) * 4);
+        const uint32_t wr_lane = my_stg + static_cast<uint32_t>(frag_row * PITCH + 8 * kq);
+        const uint32_t cp_lane = lds0 + COLP_BASE + static_cast<uint32_t>((wn * WTN + 4 * kq) * 4);
         const int      lr8 = lane / 8, seg = lane % 8;
         const uint32_t rd_lane = static_cast<uint32_t>(lr8 * PITCH + seg * 16);
         const int64_t  wcol0 = n0 + wn * WTN;
         __half* const  cbase = static_cast<__half*>(p.C) + wcol0 + seg * 8;
-        // alpha * column scale and bias of this lane's 2 x 16 columns, read once per tile
-        v4u32 rs[FN][4], rb[FN][4];
-        static_for<FN>([&](auto jt) {                         // (a batch of 8 reads per fragment column: the LDS counter holds 15)
+        // alpha * column scale and bias of this lane's 4 x 4 columns, read once per tile
+        v4u32 rs[FN], rb[FN];
+        static_for<FN>([&](auto jt) {
             constexpr int j = decltype(jt)::value;
-            static_for<4>([&](auto vt) {
-                constexpr int vq = decltype(vt)::value;
-                lds_read_b128<(j * 32 + 8 * vq) * 4>(rs[j][vq], cp_lane);
-                lds_read_b128<(BN + j * 32 + 8 * vq) * 4>(rb[j][vq], cp_lane);
-            });
-            wait_lds_all();
+            lds_read_b128<j * R * 4>(rs[j], cp_lane);
+            lds_read_b128<(BN + j * R) * 4>(rb[j], cp_lane);
         });
-        static_for<FM>([&](auto it) {
+        wait_lds_all();
+        static_for<WTM / 32>([&](auto it) {                     // 32 rows a pass
             constexpr int  i       = decltype(it)::value;
             const uint32_t wr_base = loader ? wr_lane : wr_lane - static_cast<uint32_t>(i * 32 * PITCH);
-            static_for<FN>([&](auto jt) {
-                constexpr int j = decltype(jt)::value;
-                static_for<4>([&](auto vt) {
-                    constexpr int vq = decltype(vt)::value;
+            static_for<32 / R>([&](auto ht) {
+                constexpr int f = i * (32 / R) + decltype(ht)::value;
+                static_for<FN>([&](auto jt) {
+                    constexpr int j = decltype(jt)::value;
                     // the per-tile kernel's arithmetic: each value one fused multiply-add rounded once to binary16
                     auto pair = [&](int e) {
-                        return fma_out_half2(static_cast<float>(acc[i][j][vq * 4 + e]), __uint_as_float(rs[j][vq][e]),
-                                             __uint_as_float(rb[j][vq][e]),
-                                             static_cast<float>(acc[i][j][vq * 4 + e + 1]), __uint_as_float(rs[j][vq][e + 1]),
-                                             __uint_as_float(rb[j][vq][e + 1]));
+                        return fma_out_half2(static_cast<float>(acc[f][j][e]), __uint_as_float(rs[j][e]), __uint_as_float(rb[j][e]),
+                                             static_cast<float>(acc[f][j][e + 1]), __uint_as_float(rs[j][e + 1]),
+                                             __uint_as_float(rb[j][e + 1]));
                     };
                     const v2u32 packed = {pair(0), pair(2)};
-                    lds_write_b64<i * 32 * PITCH + (j * 32 + 8 * vq) * 2>(wr_base, packed);
+                    lds_write_b64<f * R * PITCH + j * R * 2>(wr_base, packed);
                 });
             });
             if(!loader)
@@ -840,7 +916,7 @@ __global__ __launch_bounds__(512) void gemm_nt_persistent_kernel(const GemmKerne
                     for(int e = 0; e < 4; ++e)
                         {
                         const uint32_t word = t[decltype(rt)::value][e];
-                        acc[r / 4][0][4 * (r % 4) + e] = word_as<typename TR::acc_t>(word);
+                        acc[r / 4][r % 4][e] = word_as<typename TR::acc_t>(word);
                     }
                 });
             });
@@ -862,7 +938,7 @@ __global__ __launch_bounds__(512) void gemm_nt_persistent_kernel(const GemmKerne
 #pragma unroll
                 for(int e = 0; e < 4; ++e)
                 {
-                    const typename TR::acc_t a = acc[r / 4][0][4 * (r % 4) + e];
+                    const typename TR::acc_t a = acc[r / 4][r % 4][e];
                     val[e] = as_word(a);
                 }
                 __builtin_nontemporal_store(val, reinterpret_cast<v4u32*>(cbase + row * p.N));

@@ -13,28 +13,6 @@ namespace {
 
 constexpr int kRowsWaves = 8;
 
-typedef int   v4i __attribute__((ext_vector_type(4)));
-typedef float v4f __attribute__((ext_vector_type(4)));
-template <typename TR> struct Mfma16;
-template <> struct Mfma16<I8Traits>
-{
-    typedef v4i vec;
-    __device__ static __forceinline__ vec mfma(const v4i32& a, const v4i32& b, const vec& c) { return __builtin_amdgcn_mfma_i32_16x16x64_i8(a, b, c, 0, 0, 0); }
-};
-template <> struct Mfma16<F16Traits>
-{
-    typedef v4f vec;
-    __device__ static __forceinline__ vec mfma(const v4i32& a, const v4i32& b, const vec& c)
-    {
-        return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(v8f16, a), __builtin_bit_cast(v8f16, b), c, 0, 0, 0);
-    }
-};
-
-template <int OFF> __device__ __forceinline__ void operand_read(v4i32& d, uint32_t addr)
-{
-    asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(d) : "v"(addr), "n"(OFF) : "memory");
-}
-
 // MF, NF: fragments of 16 rows, of 16 columns.  The B fragment is the instruction's first operand, so a lane holds four consecutive columns
 // (4 (lane / 16) ..) of output row lane % 16.
 constexpr int64_t kRowsGroups = 256;                                        // one for each unit
@@ -45,7 +23,7 @@ constexpr int rows_stages(int loads) { return loads > 4 ? 3 : 4; }             /
 template <typename TR, int MF, int NF>
 __global__ __launch_bounds__(64 * kRowsWaves) void gemm_rows_kernel(const GemmKernelArgs p)
 {
-    typedef typename Mfma16<TR>::vec vec;
+    typedef typename TR::accv_t vec;
     constexpr int kLoads = MF + NF, kStages = rows_stages(kLoads), kTurn = kLoads * 1024;
     extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
     const int     lane = threadIdx.x % kWaveSize, wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x / kWaveSize));
@@ -90,13 +68,13 @@ __global__ __launch_bounds__(64 * kRowsWaves) void gemm_rows_kernel(const GemmKe
         wait_tiles<kLoads, kStages - 1>(turns - 1 - t);
         v4i32          op[kLoads];
         const uint32_t at = lds0 + static_cast<uint32_t>(t % kStages * kTurn) + frag;
-        static_for<kLoads>([&](auto f) { operand_read<decltype(f)::value * 1024>(op[decltype(f)::value], at); });
+        static_for<kLoads>([&](auto f) { frag_read<decltype(f)::value * 1024>(op[decltype(f)::value], at); });
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for(int f = 0; f < MF; ++f)
 #pragma unroll
-            for(int j = 0; j < NF; ++j) acc[j * MF + f] = Mfma16<TR>::mfma(op[MF + j], op[f], acc[j * MF + f]);
+            for(int j = 0; j < NF; ++j) acc[j * MF + f] = TR::mfma(op[MF + j], op[f], acc[j * MF + f]);
         __builtin_amdgcn_sched_barrier(0);
     }
     __syncthreads();                                                        // (the sums take the place of the stages)
