@@ -76,10 +76,10 @@ __device__ __forceinline__ void conv_sequence(std::integer_sequence<int, Ds...>,
 // TN form with the B operand gathered from an NHWC tensor (weight gradient of the 3x3 convolution): stage row r of
 // K tile kt is pixel m = kt * KR + r, and a lane's 16-byte chunk lies in one tap (dh, dw) at channel offset c0, both
 // fixed per load slot; what changes from K tile to K tile is the pixel, i.e. (h, w).  `delta` holds the slot's whole
-// constant part ((dh W + dw) Cb + c0 + r Cb); `code`, low byte: (dh + 1) | (dw + 1) << 2 | valid << 4; `hw` = h << 16 | w of the
+// constant part ((dh W + dw) Cb + c0 + r Cb), modulo 2^32; `code`, low byte: (dh + 1) | (dw + 1) << 2 | valid << 4; `hw` = h << 16 | w of the
 // pixel of the NEXT K tile to be requested and is advanced by KR pixels here (dr = KR % W, hq = (KR / W) % H).
 template <int D, int DPW>
-__device__ __forceinline__ void conv_tn_issue(const uint8_t* x, const uint8_t* zero, int64_t pix_base, int delta, int code,
+__device__ __forceinline__ void conv_tn_issue(const uint8_t* x, const uint8_t* zero, uint32_t pix_base, uint32_t delta, int code,
                                               uint32_t& hw, int H, int W, int dr, int hq, uint8_t* lds_mid)
 {
     constexpr int IMM = dma_imm<D, DPW>();
@@ -87,7 +87,7 @@ __device__ __forceinline__ void conv_tn_issue(const uint8_t* x, const uint8_t* z
     const int  hh = h + (code & 3) - 1, ww = w + ((code >> 2) & 3) - 1;
     const bool inb = ((code >> 4) & 1) != 0 && static_cast<unsigned>(hh) < static_cast<unsigned>(H)
                      && static_cast<unsigned>(ww) < static_cast<unsigned>(W);
-    const uint8_t* src = inb ? x + (pix_base + delta) : zero;
+    const uint8_t* src = inb ? x + (pix_base + delta) : zero;       // (an offset in the tensor, below 2^31, wherever it is read)
     __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src - IMM),
                                      (__attribute__((address_space(3))) void*)(lds_mid + dma_lds_shift<D, DPW>()), 16, IMM, 0);
     w += dr;
@@ -100,10 +100,10 @@ __device__ __forceinline__ void conv_tn_issue(const uint8_t* x, const uint8_t* z
 
 template <int DPW, int... Ds>
 __device__ __forceinline__ void conv_tn_sequence(std::integer_sequence<int, Ds...>, const uint8_t* x, const uint8_t* zero,
-                                                 int64_t pix_base, const uint32_t (&delta)[DPW], const uint32_t (&codes)[(DPW + 3) / 4],
+                                                 uint32_t pix_base, const uint32_t (&delta)[DPW], const uint32_t (&codes)[(DPW + 3) / 4],
                                                  uint32_t (&hw)[DPW], int H, int W, int dr, int hq, uint8_t* lds_mid)
 {
-    (conv_tn_issue<Ds, DPW>(x, zero, pix_base, static_cast<int>(delta[Ds]), static_cast<int>(codes[Ds / 4] >> (8 * (Ds % 4))), hw[Ds], H, W, dr, hq, lds_mid), ...);
+    (conv_tn_issue<Ds, DPW>(x, zero, pix_base, delta[Ds], static_cast<int>(codes[Ds / 4] >> (8 * (Ds % 4))), hw[Ds], H, W, dr, hq, lds_mid), ...);
 }
 
 // TN, last K tile with fewer contraction rows than a stage holds: rows from `rows` on are fetched from the tile's first
@@ -125,7 +125,7 @@ __device__ __forceinline__ void dma_sequence_short(std::integer_sequence<int, Ds
 // that the lanes of one access pass touch all banks once.  Everything behind the fragments
 // (matrix instructions, epilogue, split K) is shared with the NT form.  Kb is the contraction length P here.
 // `lin` is the workgroup's index among the `splits` x tiles workgroups of the problem.
-template <typename TR, int BM, int BN, int WGM, int WGN, int ST, bool SPLIT, bool CONV, bool TN>
+template <typename TR, int BM, int BN, int WGM, int WGN, int ST, int NL, bool SPLIT, bool CONV, bool TN>
 __device__ __forceinline__ void gemm_tile(const GemmKernelArgs& p, int lin, int splits)
 {
     static_assert(!(SPLIT && CONV && !TN), "the implicit patch matrix of the forward is not combined with split K");
@@ -140,9 +140,10 @@ __device__ __forceinline__ void gemm_tile(const GemmKernelArgs& p, int lin, int 
     constexpr int R = TR::kRows, FM = WTM / R, FN = WTN / R;         // fragments per wavefront
     constexpr int CH = kRowBytes / (16 * (64 / R));                 // K chunks (16 bytes of each of 64 / R lanes) per K tile
     constexpr int STAGE_BYTES = (BM + BN) * kRowBytes;
-    constexpr int DPW = (BM + BN) / 8 / (WGM * WGN);    // direct-load instructions per wavefront per K tile
+    constexpr int WC = WGM * WGN, WL = NL > 0 ? NL : WC;            // wavefronts that compute, that load
+    constexpr int DPW = (BM + BN) / 8 / WL;                         // direct-load instructions per loading wavefront per K tile
     static_assert(R == 16 && CH == 2 && WTM % R == 0 && WTN % R == 0 && FM >= FN && (FN == 2 || FN == 4), "fragments of a wavefront");
-    static_assert((BM + BN) % (8 * WGM * WGN) == 0 && BM % 16 == 0, "stage rows must split evenly over the wavefronts");
+    static_assert((BM + BN) % (8 * WL) == 0 && BM % 16 == 0, "stage rows must split evenly over the wavefronts");
 
     extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
 
@@ -152,6 +153,7 @@ __device__ __forceinline__ void gemm_tile(const GemmKernelArgs& p, int lin, int 
     const int     tid = threadIdx.x, lane = tid % kWaveSize;
     const int     wave = __builtin_amdgcn_readfirstlane(tid / kWaveSize);     // wavefront index, held in an SGPR
     const int     wm = wave / WGN, wn = wave % WGN;
+    const int     lwave = NL == 0 ? wave : wave >= WC ? wave - WC : 0;          // index among the loading wavefronts
 
     // K-tile indices are 32-bit so that the loop control stays on the scalar unit
     const int ktiles_all = static_cast<int>((p.Kb + kRowBytes - 1) / kRowBytes);
@@ -174,7 +176,7 @@ __device__ __forceinline__ void gemm_tile(const GemmKernelArgs& p, int lin, int 
     // its source is one uniform base pointer plus a 32-bit lane offset per instruction.
     constexpr bool kUniformSide = (BM / 8) % DPW == 0;
     static_assert(kUniformSide, "a wavefront must not straddle the A/B boundary of a stage");
-    const bool     is_a      = wave * DPW < BM / 8;
+    const bool     is_a      = lwave * DPW < BM / 8;
     // TN: the panel starts at the tile's first column of the operand (its rows are contraction indices)
     const uint8_t* gbase     = TN ? (is_a ? p.A + m0 * ESZ : (CONVTN ? p.B : p.B + n0 * ESZ))
                                   : (is_a ? p.A + m0 * p.Kb : ((!CONV && p.remap_C > 0) ? p.B : p.B + n0 * p.Kb));
@@ -195,7 +197,7 @@ __device__ __forceinline__ void gemm_tile(const GemmKernelArgs& p, int lin, int 
 #pragma unroll
             for(int d = 0; d < DPW; ++d)
             {
-                const int q     = wave * DPW + d - (is_a ? 0 : BM / 8);
+                const int q     = lwave * DPW + d - (is_a ? 0 : BM / 8);
                 const int o     = q * 1024 + lane * 16;
                 const int row   = o / RB, pos = (o % RB) / 16;
                 int       chunk = pos ^ tn_swizzle<ESZ, RB>(row);
@@ -224,7 +226,7 @@ __device__ __forceinline__ void gemm_tile(const GemmKernelArgs& p, int lin, int 
 #pragma unroll
         for(int d = 0; d < DPW; ++d)
         {
-            const int srow  = (wave * DPW + d) * 8 + lane / 8;            // row inside the stage
+            const int srow  = (lwave * DPW + d) * 8 + lane / 8;           // row inside the stage
             const int chunk = (lane % 8) ^ ((srow >> 1) & 7);             // BM % 16 == 0: same term for A and B rows
             int64_t   lrow  = srow - (is_a ? 0 : BM);
             if(lrow >= rows_left) lrow = rows_left - 1;
@@ -247,7 +249,7 @@ __device__ __forceinline__ void gemm_tile(const GemmKernelArgs& p, int lin, int 
 #pragma unroll
                 for(int d = 0; d < DPW; ++d)
                 {
-                    const int      lrow = (wave * DPW + d) * 8 + lane / 8 - BM;
+                    const int      lrow = (lwave * DPW + d) * 8 + lane / 8 - BM;
                     const uint32_t row  = static_cast<uint32_t>(n0 + (lrow < rows_left ? lrow : rows_left - 1));
                     const int      tap  = static_cast<int>(row / static_cast<uint32_t>(p.remap_C));
                     const int      c    = static_cast<int>(row) - tap * p.remap_C;
@@ -285,11 +287,11 @@ __device__ __forceinline__ void gemm_tile(const GemmKernelArgs& p, int lin, int 
     const int64_t tn_ld = TN ? uniform64(is_a ? p.M : p.N) : 0;      // operand row length in elements
     // TN: stage row of the lane in load slot 0, rows from slot to slot, and the contraction rows of a partial last K tile
     constexpr int tn_rps = TN ? 1024 / (BM * ESZ) : 0;
-    auto          tn_first_row = [&]() { return ((wave * DPW - (is_a ? 0 : BM / 8)) * 1024 + lane_again() * 16) / (BM * ESZ); };
+    auto          tn_first_row = [&]() { return ((lwave * DPW - (is_a ? 0 : BM / 8)) * 1024 + lane_again() * 16) / (BM * ESZ); };
     const int     tn_tail_rows = TN ? static_cast<int>(p.Kb % kRowBytes) / ESZ : 0;
     auto dma = [&](int stage, int kt) {
         const int64_t  kb    = static_cast<int64_t>(kt) * kRowBytes;
-        uint8_t*       lbase = lds + stage * STAGE_BYTES + wave * (DPW * 1024) + (dma_group<DPW>() / 2) * 1024;
+        uint8_t*       lbase = lds + stage * STAGE_BYTES + lwave * (DPW * 1024) + (dma_group<DPW>() / 2) * 1024;
         if constexpr(CONVTN)
             if(!is_a)
             {   // (requested for consecutive K tiles only, starting at kt_begin: hw is advanced by every call)
@@ -301,7 +303,7 @@ __device__ __forceinline__ void gemm_tile(const GemmKernelArgs& p, int lin, int 
                         if(row0 + d * tn_rps >= tn_tail_rows) tnc_code[d / 4] &= ~(0xFFu << (8 * (d % 4)));
                 }
                 conv_tn_sequence<DPW>(std::make_integer_sequence<int, DPW>{}, p.B, reinterpret_cast<const uint8_t*>(&g_zero_chunk),
-                                      static_cast<int64_t>(kt) * tnc_KR * p.conv_Cb, voff, tnc_code, hw, p.conv_H, p.conv_W,
+                                      static_cast<uint32_t>(kt) * static_cast<uint32_t>(tnc_KR) * static_cast<uint32_t>(p.conv_Cb), voff, tnc_code, hw, p.conv_H, p.conv_W,
                                       tnc_dr, tnc_hq, lbase);
                 return;
             }
@@ -344,11 +346,11 @@ __device__ __forceinline__ void gemm_tile(const GemmKernelArgs& p, int lin, int 
         if((!CONVTN || is_a) && kt == tail_kt)
         {
             const int64_t kb   = static_cast<int64_t>(kt) * kRowBytes;
-            const int     l    = lane_again(), row0 = TN ? ((wave * DPW - (is_a ? 0 : BM / 8)) * 1024 + l * 16) / (BM * ESZ) : 0;
+            const int     l    = lane_again(), row0 = TN ? ((lwave * DPW - (is_a ? 0 : BM / 8)) * 1024 + l * 16) / (BM * ESZ) : 0;
 #pragma unroll
             for(int d = 0; d < DPW; ++d)
                 if(TN ? row0 + d * tn_rps >= tn_tail_rows : kb + gchunk[d & 1] >= p.Kb)
-                    *reinterpret_cast<uint4*>(lds + stage * STAGE_BYTES + (wave * DPW + d) * 1024 + l * 16)
+                    *reinterpret_cast<uint4*>(lds + stage * STAGE_BYTES + (lwave * DPW + d) * 1024 + l * 16)
                         = make_uint4(0, 0, 0, 0);
         }
     };
@@ -359,6 +361,51 @@ __device__ __forceinline__ void gemm_tile(const GemmKernelArgs& p, int lin, int 
         zero_tail(stage, kt);
         wg_barrier();
     };
+    float*     colp  = reinterpret_cast<float*>(lds + ST * STAGE_BYTES);       // [2][BN]: scale, bias
+    const bool any_k = kt_begin < kt_end;
+    // Column parameters and as many K tiles as there are stages; the wait for tile 0 (up to ST - 1 tiles are requested behind it).
+    // Nothing in front of the K loop waits for global memory except that wait (a load into a register here would make the
+    // compiler drain the queue before its use).
+    auto request_first = [&]() {
+        if(!SPLIT && lwave < BN / 64)
+        {
+            const int64_t c = n0 + lwave * 64 + lane, col = c < p.N ? c : p.N - 1;       // columns past N: any valid one, never stored
+            if(p.col_scale) column_param_issue(p.col_scale + col, lds + ST * STAGE_BYTES + lwave * 256);
+            if(p.col_bias) column_param_issue(p.col_bias + col, lds + ST * STAGE_BYTES + BN * 4 + lwave * 256);
+        }
+#pragma unroll
+        for(int t = 0; t < ST; ++t)
+            if(kt_begin + t < kt_end) dma(t, kt_begin + t);
+    };
+    auto await_first = [&]() {
+        wait_tiles<DPW, ST - 1>(kt_end - 1 - kt_begin);
+        zero_tail(0, kt_begin);
+        wg_barrier();
+    };
+    // Loading wavefronts of their own (NL): they meet the others at every K tile's barrier and do nothing but request, wait and
+    // clear.  A direct load occupies the compute unit's vector-memory path for 16 clocks, the 32 of a 128 tile's K tile for
+    // 512, and a wavefront whose loads queue there issues nothing else; with two computing wavefronts a SIMD that was twice
+    // what their instructions and LDS reads took.
+    if constexpr(NL > 0)
+        if(wave >= WC)
+        {
+            request_first();
+            if(!any_k)
+            {
+                wait_direct_loads<0>();              // the column parameters
+                return;
+            }
+            await_first();
+            int stage = 0;
+            for(int kt = kt_begin; kt + 1 < kt_end; ++kt)
+            {
+                const int next = stage + 1 < ST ? stage + 1 : 0;
+                land(next, kt + 1);
+                if(kt + ST < kt_end) dma(stage, kt + ST);
+                stage = next;
+            }
+            return;
+        }
 
     accv_t acc[FM][FN];
 #pragma unroll
@@ -465,29 +512,26 @@ __device__ __forceinline__ void gemm_tile(const GemmKernelArgs& p, int lin, int 
     // The upper half of the wavefronts (the second wavefront of each SIMD) therefore requests behind its last
     // chunk instead: while one wavefront of a SIMD queues loads, its sibling issues matrix instructions
     // (launched alone: 4-10 % fewer cycles per launch on every tile shape, int8 and binary16).
-    const bool late_loader = wave >= WGM * WGN / 2;
-    float* colp = reinterpret_cast<float*>(lds + ST * STAGE_BYTES);       // [2][BN]: scale, bias
-    const bool any_k = kt_begin < kt_end;
+    const bool late_loader = wave >= WC / 2;
     // (scalar loads: in front of the first direct load, used by the epilogue)
     const float scale0 = *(!SPLIT && p.s0 ? p.s0 : &g_one), scale1 = *(!SPLIT && p.s1 ? p.s1 : &g_one);
     const float code_inv = *(!SPLIT && p.codes ? p.code_inv : &g_one);
-    // Nothing in front of the K loop waits for global memory except the K loop's own wait for tile 0: column parameters
-    // and as many K tiles as there are stages are requested back to back (a load into a register here would make the
-    // compiler drain the queue before its use).
-    if(!SPLIT && wave < BN / 64)
+    if constexpr(NL == 0) request_first();
+    // (What the K loop starts from is formed while the first loads are in flight, not behind the wait for them: 4096x3072x768 on the
+    // 128 tile int8 15.3 -> 14.8 us)
+    if constexpr(FM > 2 && ESZ <= 2)
     {
-        const int64_t col = n0 + tid < p.N ? n0 + tid : p.N - 1;       // columns past N: any valid one, never stored
-        if(p.col_scale) column_param_issue(p.col_scale + col, lds + ST * STAGE_BYTES + wave * 256);
-        if(p.col_bias) column_param_issue(p.col_bias + col, lds + ST * STAGE_BYTES + BN * 4 + wave * 256);
-    }
 #pragma unroll
-    for(int t = 0; t < ST; ++t)
-        if(kt_begin + t < kt_end) dma(t, kt_begin + t);
+        for(int i = 0; i < FM; ++i)
+#pragma unroll
+            for(int j = 0; j < FN; ++j) asm volatile("" : "+v"(acc[i][j]));
+        if constexpr(TN) asm volatile("" : "+v"(tn_lane));
+        else             asm volatile("" : "+v"(roff[0]), "+v"(roff[1]));
+    }
     if(any_k)
     {
-        wait_tiles<DPW, ST - 1>(kt_end - 1 - kt_begin);      // tile 0; up to ST - 1 tiles are requested behind it
-        zero_tail(0, kt_begin);
-        wg_barrier();
+        if constexpr(NL == 0) await_first();
+        else                  wg_barrier();
         constexpr int H = FM / 2;
         const std::integral_constant<int, 0> c0{};
         const std::integral_constant<int, 1> c1{};
@@ -517,7 +561,7 @@ __device__ __forceinline__ void gemm_tile(const GemmKernelArgs& p, int lin, int 
             const uint32_t sb   = lds0 + static_cast<uint32_t>(stage * STAGE_BYTES);
             // without a next tile the reads behind the barrier fetch the current stage again: in bounds, unused
             const uint32_t nb      = lds0 + static_cast<uint32_t>((more ? next : stage) * STAGE_BYTES);
-            const bool     request = kt + ST < kt_end;
+            const bool     request = NL == 0 && kt + ST < kt_end;
             if constexpr(ROLL)
             {
                 static_for<FM>([&](auto it) {
@@ -551,7 +595,11 @@ __device__ __forceinline__ void gemm_tile(const GemmKernelArgs& p, int lin, int 
                     read_behind(it, c1, sb);
                 });
             wait_lds<0>();
-            if(more) land(next, kt + 1);
+            if(more)
+            {
+                if constexpr(NL > 0) wg_barrier();
+                else                 land(next, kt + 1);
+            }
             if((ROLL || FM == 2) && request && !late_loader) dma(stage, kt + ST);
             if constexpr(ROLL)
             {
@@ -590,7 +638,7 @@ __device__ __forceinline__ void gemm_tile(const GemmKernelArgs& p, int lin, int 
 #pragma unroll
         for(int f = 0; f < FN; ++f) asm volatile("" : "+v"(bf[0][f]), "+v"(bf[1][f]));
     }
-    else
+    else if(NL == 0)
         wait_direct_loads<0>();                  // the column parameters
     const float    alpha     = scale0 * scale1;
     const uint32_t amax_seen = (!SPLIT && p.amax_bits) ? __hip_atomic_load(p.amax_bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
@@ -600,10 +648,10 @@ __device__ __forceinline__ void gemm_tile(const GemmKernelArgs& p, int lin, int 
 
 // (Two wavefronts a SIMD at least, i.e. at most 256 registers each: with more allowed the compiler keeps the accumulators in the other
 // half of the register file, and moves the 64 tile's from there and back on every K tile.)
-template <typename TR, int BM, int BN, int WGM, int WGN, int ST, bool SPLIT, bool CONV = false, bool TN = false>
-__global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm_nt_kernel(const GemmKernelArgs p)
+template <typename TR, int BM, int BN, int WGM, int WGN, int ST, int NL, bool SPLIT, bool CONV = false, bool TN = false>
+__global__ __launch_bounds__(64 * (WGM * WGN + NL), 2) void gemm_nt_kernel(const GemmKernelArgs p)
 {
-    gemm_tile<TR, BM, BN, WGM, WGN, ST, SPLIT, CONV, TN>(p, static_cast<int>(blockIdx.y * gridDim.x + blockIdx.x),
+    gemm_tile<TR, BM, BN, WGM, WGN, ST, NL, SPLIT, CONV, TN>(p, static_cast<int>(blockIdx.y * gridDim.x + blockIdx.x),
                                                          static_cast<int>(gridDim.y));
 }
 
@@ -616,6 +664,7 @@ struct GemmPairArgs
     int            na, total;      // workgroups of the first, of both; behind them those of the fold
     ColumnFoldArgs fold;
 };
+// (No loading wavefronts of their own here: with them 2048x1024x1024 int8 10.1 -> 10.4 us, 2056x1000x1032 binary16 24.8 -> 25.5.)
 template <typename TR, int BM, int BN, int WGM, int WGN, int ST, bool TNA>
 __global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm_nt_pair_kernel(const GemmPairArgs p)
 {
@@ -627,11 +676,11 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm_nt_pair_kernel(const G
         return;
     }
     if constexpr(!TNA)
-        gemm_tile<TR, BM, BN, WGM, WGN, ST, false, false, false>(p.g[blk < p.na ? 0 : 1], blk < p.na ? blk : blk - p.na, 1);
+        gemm_tile<TR, BM, BN, WGM, WGN, ST, 0, false, false, false>(p.g[blk < p.na ? 0 : 1], blk < p.na ? blk : blk - p.na, 1);
     else if(blk < p.na)
-        gemm_tile<TR, BM, BN, WGM, WGN, ST, false, false, TNA>(p.g[0], blk, 1);
+        gemm_tile<TR, BM, BN, WGM, WGN, ST, 0, false, false, TNA>(p.g[0], blk, 1);
     else
-        gemm_tile<TR, BM, BN, WGM, WGN, ST, false, false, false>(p.g[1], blk - p.na, 1);
+        gemm_tile<TR, BM, BN, WGM, WGN, ST, 0, false, false, false>(p.g[1], blk - p.na, 1);
 }
 
 // ---------------------------------------------------------------------------------------------------------------
@@ -1089,81 +1138,64 @@ inline int current_device_slot()
     return (hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < kMaxDevices) ? dev : -1;
 }
 
-template <typename TR, int BM, int BN, int WGM, int WGN, int ST>
+template <typename TR, int BM, int BN, int WGM, int WGN, int ST, int NL>
 hipError_t launch_tile(const GemmKernelArgs& a, int splits, hipStream_t st, bool tn = false)
 {
     constexpr size_t lds_bytes = ST * static_cast<size_t>(BM + BN) * kRowBytes + 2 * BN * sizeof(float) + 64;   // + amax slots
-    const dim3       grid(static_cast<unsigned>(a.tiles_m * a.tiles_n), static_cast<unsigned>(splits));
-    const dim3       block(64 * WGM * WGN);
-    static bool      attr_set[kMaxDevices][7] = {};   // per instantiation and device; benign if set twice
-    const int        slot = current_device_slot();
-    const bool       conv  = a.conv_H > 0;
-    const int        which = tn ? (conv ? (splits > 1 ? 6 : 5) : (splits > 1 ? 4 : 3)) : (conv ? 2 : (splits > 1 ? 1 : 0));
-    if(conv && !tn && splits > 1) return hipErrorInvalidValue;
-    if(tn && TR::kElemBytes > 2) return hipErrorInvalidValue;
-    const void* fn = nullptr;
-    if constexpr(TR::kElemBytes <= 2)
-        if(tn)
+    auto go = [&](auto split, auto conv, auto rowmajor) {
+        const auto  kernel = &gemm_nt_kernel<TR, BM, BN, WGM, WGN, ST, NL, decltype(split)::value, decltype(conv)::value, decltype(rowmajor)::value>;
+        static bool attr_set[kMaxDevices] = {};   // per instantiation and device; benign if set twice
+        const int   slot = current_device_slot();
+        if(slot < 0 || !attr_set[slot])
         {
-            if(conv)
-                fn = splits > 1 ? reinterpret_cast<const void*>(&gemm_nt_kernel<TR, BM, BN, WGM, WGN, ST, true, true, true>)
-                                : reinterpret_cast<const void*>(&gemm_nt_kernel<TR, BM, BN, WGM, WGN, ST, false, true, true>);
-            else
-                fn = splits > 1 ? reinterpret_cast<const void*>(&gemm_nt_kernel<TR, BM, BN, WGM, WGN, ST, true, false, true>)
-                                : reinterpret_cast<const void*>(&gemm_nt_kernel<TR, BM, BN, WGM, WGN, ST, false, false, true>);
+            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                     static_cast<int>(lds_bytes));
+            if(e != hipSuccess) return e;
+            if(slot >= 0) attr_set[slot] = true;
         }
-    if(!fn)
-        fn = conv ? reinterpret_cast<const void*>(&gemm_nt_kernel<TR, BM, BN, WGM, WGN, ST, false, true>)
-           : splits > 1 ? reinterpret_cast<const void*>(&gemm_nt_kernel<TR, BM, BN, WGM, WGN, ST, true>)
-                        : reinterpret_cast<const void*>(&gemm_nt_kernel<TR, BM, BN, WGM, WGN, ST, false>);
-    if(slot < 0 || !attr_set[slot][which])
+        kernel<<<dim3(static_cast<unsigned>(a.tiles_m * a.tiles_n), static_cast<unsigned>(splits)), dim3(64 * (WGM * WGN + NL)), lds_bytes, st>>>(a);
+        return hipGetLastError();
+    };
+    constexpr std::true_type  yes{};
+    constexpr std::false_type no{};
+    if constexpr(TR::kElemBytes <= 2 && NL == 0)
     {
-        const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                 static_cast<int>(lds_bytes));
-        if(e != hipSuccess) return e;
-        if(slot >= 0) attr_set[slot][which] = true;
+        if(a.conv_H > 0 && tn) return splits > 1 ? go(yes, yes, yes) : go(no, yes, yes);
+        if(a.conv_H > 0 && splits == 1) return go(no, yes, no);
     }
+    if(a.conv_H > 0) return hipErrorInvalidValue;
     if constexpr(TR::kElemBytes <= 2)
-        if(tn)
-        {
-            if(conv && splits > 1)
-                gemm_nt_kernel<TR, BM, BN, WGM, WGN, ST, true, true, true><<<grid, block, lds_bytes, st>>>(a);
-            else if(conv)
-                gemm_nt_kernel<TR, BM, BN, WGM, WGN, ST, false, true, true><<<grid, block, lds_bytes, st>>>(a);
-            else if(splits > 1)
-                gemm_nt_kernel<TR, BM, BN, WGM, WGN, ST, true, false, true><<<grid, block, lds_bytes, st>>>(a);
-            else
-                gemm_nt_kernel<TR, BM, BN, WGM, WGN, ST, false, false, true><<<grid, block, lds_bytes, st>>>(a);
-            return hipGetLastError();
-        }
-    if(conv)
-        gemm_nt_kernel<TR, BM, BN, WGM, WGN, ST, false, true><<<grid, block, lds_bytes, st>>>(a);
-    else if(splits > 1)
-        gemm_nt_kernel<TR, BM, BN, WGM, WGN, ST, true><<<grid, block, lds_bytes, st>>>(a);
-    else
-        gemm_nt_kernel<TR, BM, BN, WGM, WGN, ST, false><<<grid, block, lds_bytes, st>>>(a);
-    return hipGetLastError();
+        if(tn) return splits > 1 ? go(yes, no, yes) : go(no, no, yes);
+    if(tn) return hipErrorInvalidValue;
+    return splits > 1 ? go(yes, no, no) : go(no, no, no);
 }
 
 template <typename TR>
 hipError_t launch_traits(int tile, const GemmKernelArgs& a, int splits, hipStream_t st, bool tn = false)
 {
-    // Three stages for the 128x128 tile where every compute unit gets one workgroup at most; with a second one resident
-    // (two stages) its K loop fills the gaps instead.  Measured, two -> three stages: 4096x768x3072 (192 workgroups) int8
-    // 18.5 -> 15.3 us, binary16 33.5 -> 26.4; 2048x2048x4096 (256) int8 25.8 -> 22.5, binary16 45.4 -> 39.4; a short
-    // contraction gains nothing (4096x768x768 int8 6.8 -> 7.0, binary16 9.3 -> 9.6).  Beyond 256 workgroups it loses:
-    // 2176x2048x1024 (272) int8 10.9 -> 14.2, binary16 17.6 -> 21.8; 4096x2048x3072 (512) int8 29.9 -> 34.2, binary16
-    // 55.2 -> 60.4; 4096x3072x768 (768) int8 15.5 -> 18.9, binary16 25.6 -> 28.5.
+    // The 128x128 tile where every compute unit gets one workgroup at most (with a second one resident, two stages,
+    // its K loop fills the gaps):
+    //   four stages and four loading wavefronts, three stages -> this, us: 4096x768x3072 (192 workgroups) int8 15.9 -> 13.9,
+    //   binary16 26.3 -> 22.7; 2048x2048x1536 int8 11.1 -> 10.3, 1024x512x2048 10.6 -> 9.5; row-major 2048x1024x1024 12.9 -> 11.7.
+    //   Their start costs 0.3 us, a K tile less gains 0.05 to 0.12: 8 K tiles int8 8.07 -> 7.99, 6 lose (7.6 -> 7.8), 2 lose 5 %.
+    //   Rows that straddle the 128-byte lines (two lines a piece) keep the loaders the bound: 4096x768x3088 int8 18.4 ->
+    //   18.9; the gathering loads of a convolution have too much arithmetic for four wavefronts (24.9 -> 28.2).
+    //   three stages otherwise.  Two -> three: 4096x768x3072 int8 18.5 -> 15.3 us, binary16 33.5 -> 26.4; 2048x2048x4096
+    //   (256) int8 25.8 -> 22.5; a short contraction gains nothing (4096x768x768 int8 6.8 -> 7.0).
+    // Beyond 256 workgroups a third stage loses: 2176x2048x1024 (272) int8 10.9 -> 14.2, binary16 17.6 -> 21.8; 4096x2048x3072
+    // (512) int8 29.9 -> 34.2, 4096x3072x768 (768) 15.5 -> 18.9.
     // The 64x64 tile gains nothing from 3, 4 or 8 stages (14.7 / 16.4 / 17.3 / 23.9 us on 2056x1000x1032 binary16), nor
     // from fragments read a whole K tile ahead (14.7).
     const int64_t workgroups = static_cast<int64_t>(a.tiles_m) * a.tiles_n * splits;
     switch(tile)
     {
-    case 0: return launch_tile<TR, 256, 256, 2, 4, 2>(a, splits, st, tn);
+    case 0: return launch_tile<TR, 256, 256, 2, 4, 2, 0>(a, splits, st, tn);
     case 1:
-        return workgroups <= kNumCu ? launch_tile<TR, 128, 128, 2, 4, 3>(a, splits, st, tn)
-                                    : launch_tile<TR, 128, 128, 2, 4, 2>(a, splits, st, tn);
-    default: return launch_tile<TR, 64, 64, 2, 2, 2>(a, splits, st, tn);
+        if(workgroups > kNumCu) return launch_tile<TR, 128, 128, 2, 4, 2, 0>(a, splits, st, tn);
+        return a.conv_H == 0 && a.remap_C == 0 && a.ktiles_per_split >= 8 && (tn || a.Kb % kRowBytes == 0)
+                 ? launch_tile<TR, 128, 128, 2, 4, 4, 4>(a, splits, st, tn)
+                 : launch_tile<TR, 128, 128, 2, 4, 3, 0>(a, splits, st, tn);
+    default: return launch_tile<TR, 64, 64, 2, 2, 2, 0>(a, splits, st, tn);
     }
 }
 
