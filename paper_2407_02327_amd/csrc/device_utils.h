@@ -62,11 +62,17 @@ template <bool MAX> __device__ __forceinline__ float fold_column(const float* __
     float acc = 0.0f;
     if(c < cols && threadIdx.x < 256)
     {
-#pragma unroll 8                              // independent loads in flight; the fold keeps its order
-        for(int s = q; s < S; s += 16)
+        for(int s0 = q; s0 < S; s0 += 128)      // eight loads in flight, past the end the last one again; the fold keeps its order
         {
-            const float o = partial[static_cast<int64_t>(s) * cols + c];
-            acc = MAX ? fmaxf(acc, o) : acc + o;
+            float o[8];
+#pragma unroll
+            for(int u = 0; u < 8; ++u) o[u] = partial[static_cast<int64_t>(s0 + 16 * u < S ? s0 + 16 * u : S - 1) * cols + c];
+#pragma unroll
+            for(int u = 0; u < 8; ++u)
+            {
+                const float v = s0 + 16 * u < S ? o[u] : 0.0f;
+                acc = MAX ? fmaxf(acc, v) : acc + v;
+            }
         }
     }
     if(threadIdx.x < 256) lds[threadIdx.x] = acc;

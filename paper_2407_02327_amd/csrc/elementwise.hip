@@ -710,6 +710,7 @@ __device__ __forceinline__ void store_transposed_tile(const uint32_t (&t)[8], ui
         }
         return;
     }
+    const bool dwords = rows % 4 == 0 && (reinterpret_cast<uintptr_t>(qT) & 3) == 0;      // (300x2048: 6.3 us by bytes, 4.9)
 #pragma unroll
     for(int k = threadIdx.x; k < kTileCols * CH; k += THREADS)
     {
@@ -723,9 +724,16 @@ __device__ __forceinline__ void store_transposed_tile(const uint32_t (&t)[8], ui
         else
         {
             const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+            if(dwords)
 #pragma unroll
-            for(int b = 0; b < 16; ++b)
-                if(r + b < rows) dst[b] = static_cast<int8_t>((w[b / 4] >> (8 * (b % 4))) & 0xFFu);
+                for(int b = 0; b < 4; ++b)
+                {
+                    if(r + 4 * b < rows) reinterpret_cast<uint32_t*>(dst)[b] = w[b];
+                }
+            else
+#pragma unroll
+                for(int b = 0; b < 16; ++b)
+                    if(r + b < rows) dst[b] = static_cast<int8_t>((w[b / 4] >> (8 * (b % 4))) & 0xFFu);
         }
     }
 }
@@ -868,23 +876,32 @@ template <typename T> struct WeightQuantize
         {   // columns: two threads each; rows: four threads each
             const int     cc = threadIdx.x % kTileCols, half = threadIdx.x / kTileCols;
             const int64_t c  = tile_c + cc;
-            float         m  = 0.0f;
-            if(c < cols)
-            {
-                const int64_t step = conv_C > 0 ? conv_C : cols;          // conv: [groups][9][C] read as groups * 9 rows of C
-                const int     n    = conv_C > 0 ? groups * 9 : groups;
-                const float*  src  = col_part + (conv_C > 0 ? static_cast<int64_t>(static_cast<uint32_t>(c) % static_cast<uint32_t>(conv_C)) : c);
-#pragma unroll 8
-                for(int g = half; g < n; g += 2) m = fmaxf(m, src[g * step]);
-            }
-            lds_c[half][cc] = m;
             const int     rr = threadIdx.x % TR, part = threadIdx.x / TR;
             const int64_t r  = tile_r + rr;
-            m = 0.0f;
-            if(r < rows)
+            const int64_t step = conv_C > 0 ? conv_C : cols;              // conv: [groups][9][C] read as groups * 9 rows of C
+            const int     n    = conv_C > 0 ? groups * 9 : groups;
+            const int64_t ca   = c < cols ? c : cols - 1, ra = r < rows ? r : rows - 1;      // (absent ones: any, not used)
+            const float*  src  = col_part + (conv_C > 0 ? static_cast<int64_t>(static_cast<uint32_t>(ca) % static_cast<uint32_t>(conv_C)) : ca);
+            // Rows and the first batch of columns are requested together, in front of the first wait, past the end the last one
+            // again (a maximum does not mind): in loops of four and eight with remainders they were up to four more memory
+            // latencies in a row.  Whole INT8 steps, us: 384x1920x736 39.8 -> 38.1, 1120x624x512 35.0 -> 33.9.  (Requested under
+            // conditions of their own, i.e. a branch a load, they were slower than the loops: convolution 48->416 60.5 -> 64.4.)
+            float pr[4], pc[8], mr = 0.0f, mc = 0.0f;
+#pragma unroll
+            for(int i = 0; i < 4; ++i) pr[i] = row_part[(part + 4 * i < tiles_x ? part + 4 * i : tiles_x - 1) * rows + ra];
+            for(int g = half; g < n; g += 16)
+            {
+#pragma unroll
+                for(int i = 0; i < 8; ++i) pc[i] = src[(g + 2 * i < n ? g + 2 * i : n - 1) * step];
+#pragma unroll
+                for(int i = 0; i < 8; ++i) mc = fmaxf(mc, pc[i]);
+            }
+#pragma unroll
+            for(int i = 0; i < 4; ++i) mr = fmaxf(mr, pr[i]);
 #pragma unroll 4
-                for(int b = part; b < tiles_x; b += 4) m = fmaxf(m, row_part[b * rows + r]);
-            lds_r[part][rr] = m;
+            for(int b = part + 16; b < tiles_x; b += 4) mr = fmaxf(mr, row_part[b * rows + ra]);
+            lds_c[half][cc]  = mc;
+            lds_r[part][rr] = mr;
         }
         __syncthreads();
         const float fq = static_cast<float>(qmax);

@@ -654,3 +654,42 @@ def test_transposed_codes_at_the_edges_of_the_tiles(dtype, rows, cols):
     Q.qsync_quantize(wide, rows, cols, cols + 16, Q.INT8, 8, Q.PER_TENSOR, Q.ROUND_STOCHASTIC, 5, 99, iv, q, qT)
     assert_bits_equal(host(q), want, "codes of the strided input")
     assert_bits_equal(host(qT), want.T, "transposed codes of the strided input")
+
+
+@pytest.mark.parametrize("offset", [0, 4, 1])
+@pytest.mark.parametrize("rows,cols", [(132, 136), (300, 256), (190, 128)])
+def test_transposed_codes_of_rows_off_sixteen(rows, cols, offset):
+    """Transposed copies whose columns are no multiple of 16 bytes leave as dwords (rows a multiple of four, aligned copy) or
+    bytes (neither): bits of the oracle, and nothing written around them."""
+    rng = np.random.default_rng(rows + cols + offset)
+    x = _data(rng, (rows, cols), np.float16, sigma=0.3)
+    so, io = orc.scales_from_amax(orc.absmax(x, "tensor"))
+    want = orc.quantize_int(x, io, "tensor", "nearest")
+    say("rows off sixteen", rows, cols, offset)
+    room = torch.full((rows * cols + 64,), 99, dtype=torch.int8, device="cuda")
+    qT = room[16 + offset:16 + offset + rows * cols].view(cols, rows)
+    q = torch.full((rows, cols), 99, dtype=torch.int8, device="cuda")
+    Q.qsync_quantize(dev(x), rows, cols, cols, Q.INT8, 8, Q.PER_TENSOR, Q.ROUND_NEAREST, 0, 0, dev(io), q, qT)
+    assert_bits_equal(host(q), want, "codes")
+    assert_bits_equal(host(qT), want.T, "transposed codes")
+    around = host(room)
+    assert (around[:16 + offset] == 99).all() and (around[16 + offset + rows * cols:] == 99).all()
+
+
+@pytest.mark.parametrize("N,K", [(16, 8), (48, 136), (1040, 72), (2064, 16), (64, 2184)])
+def test_weight_scales_over_every_batch_of_partial_maxima(N, K):
+    """Both sets of scales and codes of the two-launch weight conversion where the folds run over one partial maximum, part of a
+    batch, and several batches (over 16 row tiles, over 16 tile columns): bits of the oracle."""
+    rng = np.random.default_rng(N * 31 + K)
+    w = (rng.standard_normal((N, K)) * 0.02).astype(np.float32)
+    say("partial maxima", N, K)
+    f = lambda n: torch.zeros(n, dtype=torch.float32, device="cuda")
+    sw, iw, aw, swb, iwb = f(N), f(N), f(N), f(K), f(K)
+    wq = torch.empty((N, K), dtype=torch.int8, device="cuda")
+    wqbT = torch.empty((K, N), dtype=torch.int8, device="cuda")
+    Q.qsync_prepare_weights(dev(w), N, K, 8, sw, iw, aw, wq, swb, iwb, wqbT, ws(Q.qsync_absmax_workspace_bytes(N, K, Q.PER_COL)))
+    for gran, s, iv, got in (("row", sw, iw, host(wq)), ("col", swb, iwb, host(wqbT).T)):
+        so, io = orc.scales_from_amax(orc.absmax(w, gran))
+        assert_bits_equal(host(s), so, gran + " scales")
+        assert_bits_equal(host(iv), io, gran + " inverse scales")
+        assert_bits_equal(got, orc.quantize_int(w, io, gran, "nearest"), gran + " codes")

@@ -1045,3 +1045,34 @@ def test_weight_gradient_from_row_major_binary16_operands(tile):
             assert_close(host(dw16), want_dw, "dW binary16 output")
     finally:
         Q.qsync_debug_set_gemm_tile(-1)
+
+
+@pytest.mark.parametrize("tag", [Q.INT8, Q.FP16])
+@pytest.mark.parametrize("ktiles", [7, 8, 9, 12, 13])
+def test_tile_with_loading_wavefronts_at_its_shortest_contractions(tag, ktiles):
+    """The 128x128 tile around the eight K tiles from which it has wavefronts of their own for its loads, with four stages, on whole
+    and overhanging tiles, forward and row-major weight gradient: int32 accumulators bit
+    for bit, binary16 products of small integers exactly."""
+    rng = np.random.default_rng(ktiles)
+    per = 128 if tag == Q.INT8 else 64
+    ints = lambda *s: rng.integers(-8, 9, s).astype(np.int8 if tag == Q.INT8 else np.float16)
+    one = dev(np.ones(1, np.float32))
+    s = one if tag == Q.INT8 else None
+    Q.qsync_debug_set_gemm_tile(1)
+    try:
+        for M, N in ((256, 384), (200, 144)):
+            K = ktiles * per
+            say("loading wavefronts", tag, M, N, K)
+            a, b, bias = ints(M, K), ints(N, K), rng.integers(-50, 50, N).astype(np.float32)
+            y = torch.full((M, N), 7.0, dtype=torch.float32, device="cuda")
+            room = torch.empty(max(256, Q.qsync_qlinear_workspace_bytes(tag, M, N, K)), dtype=torch.uint8, device="cuda")
+            Q.qsync_qlinear_fwd(tag, M, N, K, dev(a), s, dev(b), s, Q.PER_TENSOR, dev(bias), y, None, room)
+            assert_bits_equal(host(y), (a.astype(np.float64) @ b.astype(np.float64).T + bias).astype(np.float32), "Y")
+        for rows, N, K in ((128 * ((ktiles * per + 127) // 128), 256, 128), (128 * ((ktiles * per + 127) // 128), 144, 208)):
+            dy, x = ints(rows, N), ints(rows, K)
+            dw = torch.full((N, K), 7.0, dtype=torch.float32, device="cuda")
+            room = torch.empty(max(256, Q.qsync_qlinear_bwd_rm_workspace_bytes(tag, rows, N, K)), dtype=torch.uint8, device="cuda")
+            Q.qsync_qlinear_bwd_rm(tag, rows, N, K, dev(dy), s, dev(x), s, None, None, Q.PER_TENSOR, None, dw, None, None, None, None, room)
+            assert_bits_equal(host(dw), (dy.astype(np.float64).T @ x.astype(np.float64)).astype(np.float32), "dW")
+    finally:
+        Q.qsync_debug_set_gemm_tile(-1)
