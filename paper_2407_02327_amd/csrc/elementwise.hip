@@ -277,7 +277,7 @@ template <typename T> struct BlockMaxima
         {
             uint4 v[8];
 #pragma unroll
-            for(int u = 0; u < 8; ++u) v[u] = c + u * kBlock < nvec ? xv[c + u * kBlock] : make_uint4(0, 0, 0, 0);
+            for(int u = 0; u < 8; ++u) v[u] = xv[c + u * kBlock < nvec ? c + u * kBlock : nvec - 1];      // (past the end the last one again)
 #pragma unroll
             for(int u = 0; u < 8; ++u) rm.add(v[u]);
         }
@@ -622,7 +622,7 @@ __device__ __forceinline__ float tensor_inverse_scale(const TensorScale& ts, con
         {
             uint4 v[U];
 #pragma unroll
-            for(int u = 0; u < U; ++u) v[u] = c + u * THREADS < nvec ? xv[c + u * THREADS] : make_uint4(0, 0, 0, 0);
+            for(int u = 0; u < U; ++u) v[u] = xv[c + u * THREADS < nvec ? c + u * THREADS : nvec - 1];      // (past the end the last one again)
 #pragma unroll
             for(int u = 0; u < U; ++u) rm.add(v[u]);
         }
@@ -633,19 +633,22 @@ __device__ __forceinline__ float tensor_inverse_scale(const TensorScale& ts, con
     return m != 0.0f ? __fdiv_rn(static_cast<float>(qmax), m) : 1.0f;
 }
 
-// One thread's share of a tile: rows r0 .. r0 + 3, columns c0 .. c0 + 7 (absent ones are zero).
+// One thread's share of a tile: rows r0 .. r0 + 3, columns c0 .. c0 + 7 of at least one row and eight columns.  Absent ones repeat the
+// last: they raise no maximum and their codes are not stored; under a condition each load would be a branch of its own.
 template <typename T> struct TileShare
 {
     static constexpr int VG = 8 / Vec16<T>::N;       // 16-byte loads per row
     uint4 raw[4][VG];
     __device__ __forceinline__ void load(const T* __restrict__ x, int64_t r0, int64_t c0, int64_t rows, int64_t cols, int64_t ld)
     {
+        const int64_t c = c0 < cols ? c0 : cols - 8;
 #pragma unroll
         for(int i = 0; i < 4; ++i)
+        {
+            const T* row = x + (r0 + i < rows ? r0 + i : rows - 1) * ld + c;
 #pragma unroll
-            for(int l = 0; l < VG; ++l)
-                raw[i][l] = (r0 + i < rows && c0 < cols) ? *reinterpret_cast<const uint4*>(x + (r0 + i) * ld + c0 + l * Vec16<T>::N)
-                                                         : make_uint4(0, 0, 0, 0);
+            for(int l = 0; l < VG; ++l) raw[i][l] = *reinterpret_cast<const uint4*>(row + l * Vec16<T>::N);
+        }
     }
     __device__ __forceinline__ void decode(int i, float (&v)[8]) const
     {
@@ -1116,9 +1119,9 @@ template <typename T, int RND, int SRC> struct QuantizeStream
 #pragma unroll
         for(int u = 0; u < U; ++u)
         {
-            const int64_t g = g0 + u * kBlock;
+            const int64_t g = g0 + u * kBlock < ngroups ? g0 + u * kBlock : ngroups - 1;      // (past the end the last one again, not stored)
 #pragma unroll
-            for(int l = 0; l < VG; ++l) raw[u][l] = g < ngroups ? xv[g * VG + l] : make_uint4(0, 0, 0, 0);
+            for(int l = 0; l < VG; ++l) raw[u][l] = xv[g * VG + l];
         }
         const float f = tensor_inverse_scale<T, SRC, kBlock>(ts, x, ngroups * 8, qmax, block, reinterpret_cast<float*>(lds));
 #pragma unroll
