@@ -615,18 +615,25 @@ __device__ __forceinline__ float tensor_inverse_scale(const TensorScale& ts, con
     }
     else
     {   // (contiguous, 16-byte aligned, whole vectors)  all of it in flight at once
-        constexpr int U    = static_cast<int>(kWholeBytes / 16 / THREADS);
-        const int64_t nvec = n / Vec16<T>::N;
-        const uint4*  xv   = reinterpret_cast<const uint4*>(x);
+        constexpr int kMost = static_cast<int>(kWholeBytes / 16 / THREADS), kFew = kMost / 4;
+        const int64_t nvec  = n / Vec16<T>::N;
+        const uint4*  xv    = reinterpret_cast<const uint4*>(x);
         RunMax<T>     rm;
-        for(int64_t c = threadIdx.x; c < nvec; c += static_cast<int64_t>(THREADS) * U)
-        {
-            uint4 v[U];
+        auto fold = [&](auto ut) {
+            constexpr int U = decltype(ut)::value;
+            for(int64_t c = threadIdx.x; c < nvec; c += static_cast<int64_t>(THREADS) * U)
+            {
+                uint4 v[U];
 #pragma unroll
-            for(int u = 0; u < U; ++u) v[u] = xv[c + u * THREADS < nvec ? c + u * THREADS : nvec - 1];      // (past the end the last one again)
+                for(int u = 0; u < U; ++u) v[u] = xv[c + u * THREADS < nvec ? c + u * THREADS : nvec - 1];      // (past the end the last one again)
 #pragma unroll
-            for(int u = 0; u < U; ++u) rm.add(v[u]);
-        }
+                for(int u = 0; u < U; ++u) rm.add(v[u]);
+            }
+        };
+        // A quarter of the requests where that is the whole tensor: all of them, most on the last vector again, 64x128 fp32 with its
+        // column sums 4.7 us, this 3.8.
+        if(nvec <= kFew * THREADS) fold(std::integral_constant<int, kFew>{});
+        else                       fold(std::integral_constant<int, kMost>{});
         m = rm.get();
     }
     m = block_max_all<THREADS>(m, lds);

@@ -561,6 +561,28 @@ def test_convert_operands_equals_the_separate_calls(case, x_from):
                 assert_bits_equal(host(b[name]), host(t), name)
 
 
+@pytest.mark.parametrize("dtype", [np.float32, np.float16])
+@pytest.mark.parametrize("vectors", [2040, 2048, 2056, 4096, 8192])
+@pytest.mark.parametrize("last", [False, True])
+def test_maximum_of_a_whole_tensor_in_every_workgroup(dtype, vectors, last):
+    """Around the 2048 16-byte vectors up to which a workgroup that finds the maximum by itself requests a quarter as many: the
+    maximum in the first or in the last element, codes and scale the oracle's bit for bit."""
+    rows = 8 if vectors % 16 else 64
+    cols = vectors * (16 // np.dtype(dtype).itemsize) // rows
+    x = _data(np.random.default_rng(vectors), (rows, cols), dtype, sigma=0.3)
+    x[(-1, -1) if last else (0, 0)] = dtype(-7.5)
+    say("whole tensor", dtype.__name__, rows, cols, "last", last)
+    so, io = orc.scales_from_amax(orc.absmax(x, "tensor"))
+    s, iv, am = empty(1, torch.float32), empty(1, torch.float32), empty(1, torch.float32)
+    q = torch.full((rows, cols), 99, dtype=torch.int8, device="cuda")
+    qT = torch.full((cols, rows), 99, dtype=torch.int8, device="cuda")
+    Q.qsync_absmax_quantize(dev(x), rows, cols, 8, Q.ROUND_NEAREST, 0, 0, s, iv, am, q, qT, ws(Q.qsync_absmax_quantize_workspace_bytes(rows, cols)))
+    assert_bits_equal(host(s), so, "scale")
+    want = orc.quantize_int(x, io, "tensor", "nearest")
+    assert_bits_equal(host(q), want, "codes")
+    assert_bits_equal(host(qT), want.T, "transposed codes")
+
+
 def test_absmax_quantize_all_zero_and_lower_bits():
     w = ws(Q.qsync_absmax_quantize_workspace_bytes(128, 256))
     z = torch.zeros(64, 128, dtype=torch.float16, device="cuda")
