@@ -562,11 +562,10 @@ def test_convert_operands_equals_the_separate_calls(case, x_from):
 
 
 @pytest.mark.parametrize("dtype", [np.float32, np.float16])
-@pytest.mark.parametrize("vectors", [2040, 2048, 2056, 4096, 8192])
+@pytest.mark.parametrize("vectors", [2040, 2048, 2056, 4096, 4104, 6144, 6152, 8192])
 @pytest.mark.parametrize("last", [False, True])
 def test_maximum_of_a_whole_tensor_in_every_workgroup(dtype, vectors, last):
-    """Around the 2048 16-byte vectors up to which a workgroup that finds the maximum by itself requests a quarter as many: the
-    maximum in the first or in the last element, codes and scale the oracle's bit for bit."""
+    """Around the multiples of 2048 16-byte vectors at which a workgroup that finds the maximum by itself requests more: the maximum in the first or in the last element, codes and scale the oracle's bit for bit."""
     rows = 8 if vectors % 16 else 64
     cols = vectors * (16 // np.dtype(dtype).itemsize) // rows
     x = _data(np.random.default_rng(vectors), (rows, cols), dtype, sigma=0.3)
