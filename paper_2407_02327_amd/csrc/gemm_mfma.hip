@@ -487,9 +487,8 @@ __device__ __forceinline__ void gemm_tile(const GemmKernelArgs& p, int lin, int 
     // K pipeline.  A tile has two 64-byte K chunks.
     // Wavefronts of few fragments hold those of both chunks: behind the matrix instructions of chunk 0 the wavefront joins the
     // barrier that publishes the next stage (every wavefront's reads of the current one have returned by then), requests the
-    // direct load of the tile after next into the stage just drained (half of the wavefronts: at the end of the tile
-    // instead, see below), reads chunk 0 of the next tile, issues chunk 1, whose operands are already in registers, and reads
-    // chunk 1 of the next tile: barrier release, LDS latency and a whole K tile of memory latency hide behind matrix work.
+    // direct load of the tile after next into the stage just drained (some wavefronts: later in the tile, see below), reads
+    // chunk 0 of the next tile, issues chunk 1, whose operands are already in registers, and reads chunk 1 of the next tile: barrier release, LDS latency and a whole K tile of memory latency hide behind matrix work.
     // With four rows (128 tile) the reads go out between the rows' instructions, and the load behind row 0: 4096x768x3072
     // int8 16.4 -> 15.7 us, binary16 28.0 -> 26.4, against all of them at the chunk's end; the 64 tile, of which a unit holds
     // several, gains nothing from that (its convolution's weight gradient 32.2 -> 33.2).
@@ -509,10 +508,17 @@ __device__ __forceinline__ void gemm_tile(const GemmKernelArgs& p, int lin, int 
     // instruction (1 KB) at about 64 bytes per clock, and a wavefront issues nothing else while its loads
     // queue up: with every wavefront requesting right behind the barrier, both wavefronts of every SIMD sit
     // in that queue together and the matrix pipeline idles until the unit has taken all (BM + BN) / 8 of them.
-    // The upper half of the wavefronts (the second wavefront of each SIMD) therefore requests behind its last
-    // chunk instead: while one wavefront of a SIMD queues loads, its sibling issues matrix instructions
-    // (launched alone: 4-10 % fewer cycles per launch on every tile shape, int8 and binary16).
-    const bool late_loader = wave >= WC / 2;
+    // The upper half of the wavefronts (the second wavefront of each SIMD) therefore requests later, among the instructions of
+    // chunk 1: while one wavefront of a SIMD queues loads, its sibling issues matrix instructions (launched alone: 4-10 % fewer
+    // cycles per launch on the 256 and 128 tiles, int8 and binary16).  256 tile: behind the last row.  128 tile: behind the third of
+    // four rows; behind the last, binary16 256x1408x768 backward 14.1 -> 14.5 us, weight gradient of a convolution 200->168 over
+    // 18x47x53 83.3 -> 85.0.
+    // The 64 tile has no second wavefront on a SIMD, and a K tile of its own is over in less than a load takes: a request that goes
+    // out at the chunk's end holds up the next barrier.  All of its wavefronts request right behind the barrier, at the end of
+    // the tile -> this, us: row-major binary16 10368x168x1568 27.4 -> 23.5, 12416x3240x192 47.1 -> 41.1, int8 2560x96x1296 9.78 ->
+    // 8.60.  Operand rows that straddle the 128-byte lines double the queue (binary16 960x1024x1808 16.6 -> 17.8 with all of them
+    // at once), and a convolution's gather adds its arithmetic: there the upper half requests behind the first of two rows.
+    const bool late_loader = wave >= WC / 2 && (FM > 2 || (!TN && (CONV || p.Kb % kRowBytes != 0)));
     // (scalar loads: in front of the first direct load, used by the epilogue)
     const float scale0 = *(!SPLIT && p.s0 ? p.s0 : &g_one), scale1 = *(!SPLIT && p.s1 ? p.s1 : &g_one);
     const float code_inv = *(!SPLIT && p.codes ? p.code_inv : &g_one);
@@ -614,7 +620,9 @@ __device__ __forceinline__ void gemm_tile(const GemmKernelArgs& p, int lin, int 
             else if constexpr(FM == 2)
             {
                 read_chunk(c0, nb);
-                static_for<FM>([&](auto it) { mma(it, c1); });
+                mma(c0, c1);
+                if(request && late_loader) dma(stage, kt + ST);
+                mma(c1, c1);
                 read_chunk(c1, nb);
             }
             else
@@ -623,8 +631,10 @@ __device__ __forceinline__ void gemm_tile(const GemmKernelArgs& p, int lin, int 
                     read_behind(it, c0, nb);
                     if constexpr(decltype(it)::value == 0)
                         if(request && !late_loader) dma(stage, kt + ST);
+                    if constexpr(decltype(it)::value == 2)
+                        if(request && late_loader) dma(stage, kt + ST);
                 });
-            if(request && late_loader) dma(stage, kt + ST);
+            if(ROLL && request && late_loader) dma(stage, kt + ST);
             stage = next;
         }
     }

@@ -1076,3 +1076,33 @@ def test_tile_with_loading_wavefronts_at_its_shortest_contractions(tag, ktiles):
             assert_bits_equal(host(dw), (dy.astype(np.float64).T @ x.astype(np.float64)).astype(np.float32), "dW")
     finally:
         Q.qsync_debug_set_gemm_tile(-1)
+
+
+@pytest.mark.parametrize("tag", [Q.INT8, Q.FP16, Q.FP32])
+@pytest.mark.parametrize("ktiles", [1, 2, 3, 5])
+def test_small_tile_on_whole_and_straddling_rows(tag, ktiles):
+    """The 64x64 tile around its first K tiles, where operand rows are whole 128-byte lines (every wavefront requests behind the
+    barrier), where they are not (half of them later), and row-major: integer sums bit for bit, products of small integers
+    exactly."""
+    rng = np.random.default_rng(100 + ktiles)
+    esz = {Q.INT8: 1, Q.FP16: 2, Q.FP32: 4}[tag]
+    ints = lambda *s: rng.integers(-8, 9, s).astype({Q.INT8: np.int8, Q.FP16: np.float16, Q.FP32: np.float32}[tag])
+    s = dev(np.ones(1, np.float32)) if tag == Q.INT8 else None
+    Q.qsync_debug_set_gemm_tile(2)
+    try:
+        for M, N, K in ((64, 64, ktiles * 128 // esz), (200, 144, ktiles * 128 // esz), (200, 144, (ktiles * 128 - 16) // esz)):
+            say("small tile", tag, M, N, K)
+            a, b, bias = ints(M, K), ints(N, K), rng.integers(-50, 50, N).astype(np.float32)
+            y = torch.full((M, N), 7.0, dtype=torch.float32, device="cuda")
+            room = torch.empty(max(256, Q.qsync_qlinear_workspace_bytes(tag, M, N, K)), dtype=torch.uint8, device="cuda")
+            Q.qsync_qlinear_fwd(tag, M, N, K, dev(a), s, dev(b), s, Q.PER_TENSOR, dev(bias), y, None, room)
+            assert_bits_equal(host(y), (a.astype(np.float64) @ b.astype(np.float64).T + bias).astype(np.float32), "Y")
+        for rows, N, K in ((128 * ktiles, 64, 64), (128 * ktiles, 144, 208)) if tag != Q.FP32 else ():
+            say("small tile row-major", tag, rows, N, K)
+            dy, x = ints(rows, N), ints(rows, K)
+            dw = torch.full((N, K), 7.0, dtype=torch.float32, device="cuda")
+            room = torch.empty(max(256, Q.qsync_qlinear_bwd_rm_workspace_bytes(tag, rows, N, K)), dtype=torch.uint8, device="cuda")
+            Q.qsync_qlinear_bwd_rm(tag, rows, N, K, dev(dy), s, dev(x), s, None, None, Q.PER_TENSOR, None, dw, None, None, None, None, room)
+            assert_bits_equal(host(dw), (dy.astype(np.float64).T @ x.astype(np.float64)).astype(np.float32), "dW")
+    finally:
+        Q.qsync_debug_set_gemm_tile(-1)
