@@ -307,7 +307,7 @@ struct ScaleFromAmax
 
 // ------------------------------------------------------------------ absmax, per row
 // WPR wavefronts per row (1 when there are many rows, 4 = the whole block when there are few),
-// four 16-byte loads in flight per lane; no second stage.
+// up to four 16-byte loads in flight per lane; no second stage.
 template <typename T, bool VEC, int WPR>
 __global__ __launch_bounds__(kBlock) void absmax_rows_kernel(const T* __restrict__ x, int64_t rows, int64_t cols,
                                                              int64_t ld, float qmax, float* scale, float* inv_scale,
@@ -328,14 +328,22 @@ __global__ __launch_bounds__(kBlock) void absmax_rows_kernel(const T* __restrict
             constexpr int E    = Vec16<T>::N;
             const int64_t nvec = cols / E;
             const uint4*  rv   = reinterpret_cast<const uint4*>(row);
-            for(int64_t i = t; i < nvec; i += 4 * TPR)
-            {
-                uint4 v[4];
+            auto         fold = [&](auto ut) {
+                constexpr int U = decltype(ut)::value;
+                for(int64_t i = t; i < nvec; i += U * TPR)
+                {
+                    uint4 v[U];
 #pragma unroll
-                for(int u = 0; u < 4; ++u) v[u] = rv[i + u * TPR < nvec ? i + u * TPR : nvec - 1];      // (past the end the last one again)
+                    for(int u = 0; u < U; ++u) v[u] = rv[i + u * TPR < nvec ? i + u * TPR : nvec - 1];      // (past the end the last one again)
 #pragma unroll
-                for(int u = 0; u < 4; ++u) rm.add(v[u]);
-            }
+                    for(int u = 0; u < U; ++u) rm.add(v[u]);
+                }
+            };
+            // As many loads as a lane has vectors, up to four: all four for any row, fp32 14872x120 5.4 us, one 4.6; 8744x408
+            // binary16 4.2, one 3.7; 2288x1320 4.1, two 3.9.
+            if(nvec <= TPR)          fold(std::integral_constant<int, 1>{});
+            else if(nvec <= 2 * TPR) fold(std::integral_constant<int, 2>{});
+            else                     fold(std::integral_constant<int, 4>{});
             done = nvec * E;
         }
         for(int64_t c = done + t; c < cols; c += TPR) rm.add_scalar(row[c]);

@@ -714,3 +714,21 @@ def test_weight_scales_over_every_batch_of_partial_maxima(N, K):
         assert_bits_equal(host(s), so, gran + " scales")
         assert_bits_equal(host(iv), io, gran + " inverse scales")
         assert_bits_equal(got, orc.quantize_int(w, io, gran, "nearest"), gran + " codes")
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float16])
+@pytest.mark.parametrize("rows", [3, 4097])
+def test_row_maxima_around_the_loads_of_a_lane(dtype, rows):
+    """Rows of one, two and more vectors a lane (64 lanes a row, 256 below 4096 rows), whole and with a remainder, the maximum in
+    the first, the last vector's or the very last element: scales of the oracle bit for bit."""
+    lanes, e = (64 if rows >= 4096 else 256), 16 // np.dtype(dtype).itemsize
+    for nvec in (1, lanes - 1, lanes, lanes + 1, 2 * lanes, 2 * lanes + 1, 4 * lanes, 4 * lanes + 1):
+        cols = nvec * e
+        x = _data(np.random.default_rng(rows + nvec), (rows, cols), dtype, sigma=0.1)
+        x[0, 0], x[rows // 2, cols - e], x[rows - 1, cols - 1] = dtype(-5), dtype(6), dtype(-7)
+        say("row maxima", dtype.__name__, rows, cols)
+        so, io = orc.scales_from_amax(orc.absmax(x, "row"))
+        s, iv, am = (empty(rows, torch.float32) for _ in range(3))
+        Q.qsync_absmax_scale(dev(x), rows, cols, cols, Q.PER_ROW, 8, s, iv, am, None, ws(Q.qsync_absmax_workspace_bytes(rows, cols, Q.PER_ROW)))
+        assert_bits_equal(host(s), so, "scale")
+        assert_bits_equal(host(iv), io, "inverse scale")
