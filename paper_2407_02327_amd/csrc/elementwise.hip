@@ -1667,8 +1667,9 @@ __global__ __launch_bounds__(kBlock) void dequantize_cols_kernel(const Ti* __res
 #pragma unroll
         for(int u = 0; u < U; ++u)
         {
-            const int64_t r = base + u * TY + ty;
-            raw[u] = *reinterpret_cast<const uint4*>(a + (r < rows ? r : rows - 1) * ld + c);      // (absent rows are not stored)
+            const int64_t r = base + u * TY + ty;      // (the last row again for absent ones, without a branch: 107 registers in place of 88,
+            // int8 6320x3616 to fp32 34.0 -> 35.1 us, 383x592 4.13 -> 4.25, and faster nowhere)
+            raw[u] = r < rows ? *reinterpret_cast<const uint4*>(a + r * ld + c) : make_uint4(0, 0, 0, 0);
         }
 #pragma unroll
         for(int u = 0; u < U; ++u)
