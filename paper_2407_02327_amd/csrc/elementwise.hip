@@ -651,21 +651,26 @@ __device__ __forceinline__ float tensor_inverse_scale(const TensorScale& ts, con
     return m != 0.0f ? __fdiv_rn(static_cast<float>(qmax), m) : 1.0f;
 }
 
-// One thread's share of a tile: rows r0 .. r0 + 3, columns c0 .. c0 + 7 of at least one row and eight columns.  Absent ones repeat the
-// last: they raise no maximum and their codes are not stored; under a condition each load would be a branch of its own.
-template <typename T> struct TileShare
+// One thread's share of a tile: rows r0 .. r0 + 3, columns c0 .. c0 + 7 of at least one row and eight columns.  Absent ones raise no
+// maximum and their codes are not stored.  Weights (REPEAT) repeat the last row and columns: with each load under a condition, i.e. in
+// a branch of its own, converting 192x72 weights took 7.7 us in place of 7.1, 2 % more over 64..4096 by 64..4096.  Elsewhere the
+// conditions are the faster: fp32 2096x80 with its transposed copy 3.28 us without them, 3.15 with; maximum and codes of 16x808, where the
+// search for the maximum needs the registers, 4.4 and 3.7; both int8 operands of a 32->32 convolution over 16 pixels 9.3 and 8.6.
+template <typename T, bool REPEAT> struct TileShare
 {
     static constexpr int VG = 8 / Vec16<T>::N;       // 16-byte loads per row
     uint4 raw[4][VG];
     __device__ __forceinline__ void load(const T* __restrict__ x, int64_t r0, int64_t c0, int64_t rows, int64_t cols, int64_t ld)
     {
-        const int64_t c = c0 < cols ? c0 : cols - 8;
+        const int64_t c = !REPEAT || c0 < cols ? c0 : cols - 8;
 #pragma unroll
         for(int i = 0; i < 4; ++i)
         {
-            const T* row = x + (r0 + i < rows ? r0 + i : rows - 1) * ld + c;
+            const bool absent = r0 + i >= rows;
+            const T*   row    = x + (REPEAT && absent ? rows - 1 : r0 + i) * ld + c;
 #pragma unroll
-            for(int l = 0; l < VG; ++l) raw[i][l] = *reinterpret_cast<const uint4*>(row + l * Vec16<T>::N);
+            for(int l = 0; l < VG; ++l)
+                raw[i][l] = REPEAT || (!absent && c0 < cols) ? *reinterpret_cast<const uint4*>(row + l * Vec16<T>::N) : make_uint4(0, 0, 0, 0);
         }
     }
     __device__ __forceinline__ void decode(int i, float (&v)[8]) const
@@ -777,7 +782,7 @@ template <typename T, int RND, int TR, int SRC> struct QuantizeTile
         const int     by = static_cast<int>(block) / tiles_x, bx = static_cast<int>(block) - by * tiles_x;
         const int64_t tile_r = static_cast<int64_t>(by) * TR, tile_c = static_cast<int64_t>(bx) * kTileCols;
         const int64_t r0 = tile_r + (threadIdx.x / 16) * 4, c0 = tile_c + (threadIdx.x % 16) * 8;
-        TileShare<T>  s;
+        TileShare<T, false> s;
         s.load(x, r0, c0, rows, cols, ld);
         const float   inv = tensor_inverse_scale<T, SRC, kThreads>(ts, x, rows * cols, qmax, block, reinterpret_cast<float*>(lds + TR * kTileCols));
         uint32_t      code[4][2];
@@ -828,7 +833,7 @@ template <typename T> struct WeightMaxima
         for(int64_t tile_r = static_cast<int64_t>(by) * TR; tile_r < rows; tile_r += static_cast<int64_t>(groups) * TR)
         {
             const int64_t r0 = tile_r + quad * 4;
-            TileShare<T>  s;
+            TileShare<T, true> s;
             s.load(x, r0, c0, rows, cols, cols);
 #pragma unroll
             for(int i = 0; i < 4; ++i)
@@ -892,7 +897,7 @@ template <typename T> struct WeightQuantize
         const int64_t tile_r = static_cast<int64_t>(by) * TR, tile_c = static_cast<int64_t>(bx) * kTileCols;
         const int     cg = threadIdx.x % 16, quad = threadIdx.x / 16;
         const int64_t r0 = tile_r + quad * 4, c0 = tile_c + cg * 8;
-        TileShare<T>  s;
+        TileShare<T, true> s;
         s.load(x, r0, c0, rows, cols, cols);
         {   // columns: two threads each; rows: four threads each
             const int     cc = threadIdx.x % kTileCols, half = threadIdx.x / kTileCols;
