@@ -62,11 +62,16 @@ template <bool MAX> __device__ __forceinline__ float fold_column(const float* __
     float acc = 0.0f;
     if(c < cols && threadIdx.x < 256)
     {
-        for(int s0 = q; s0 < S; s0 += 128)      // eight loads in flight, past the end the last one again; the fold keeps its order
+        // (the addresses advance: a 64-bit product for each load took as long as the loads; gradient statistics of 2184x65 4.7 us a
+        // fold, 4.1)
+        const float*  at   = partial + static_cast<int64_t>(q) * cols + c;
+        const float*  last = partial + static_cast<int64_t>(S - 1) * cols + c;
+        const int64_t step = 16 * cols;
+        for(int s0 = q; s0 < S; s0 += 128, at += 8 * step)      // eight loads in flight, past the end the last one again; the fold keeps its order
         {
             float o[8];
 #pragma unroll
-            for(int u = 0; u < 8; ++u) o[u] = partial[static_cast<int64_t>(s0 + 16 * u < S ? s0 + 16 * u : S - 1) * cols + c];
+            for(int u = 0; u < 8; ++u) o[u] = *(s0 + 16 * u < S ? at + u * step : last);
 #pragma unroll
             for(int u = 0; u < 8; ++u)
             {
