@@ -517,8 +517,8 @@ __device__ __forceinline__ void gemm_tile(const GemmKernelArgs& p, int lin, int 
     // out at the chunk's end holds up the next barrier.  All of its wavefronts request right behind the barrier, at the end of
     // the tile -> this, us: row-major binary16 10368x168x1568 27.4 -> 23.5, 12416x3240x192 47.1 -> 41.1, int8 2560x96x1296 9.78 ->
     // 8.60.  Operand rows that straddle the 128-byte lines double the queue (binary16 960x1024x1808 16.6 -> 17.8 with all of them
-    // at once), and a convolution's gather adds its arithmetic: there the upper half requests behind the first of two rows.
-    const bool late_loader = wave >= WC / 2 && (FM > 2 || (!TN && (CONV || p.Kb % kRowBytes != 0)));
+    // at once): there the upper half requests behind the first of two rows.
+    const bool late_loader = wave >= WC / 2 && (FM > 2 || (!TN && p.Kb % kRowBytes != 0));
     // (scalar loads: in front of the first direct load, used by the epilogue)
     const float scale0 = *(!SPLIT && p.s0 ? p.s0 : &g_one), scale1 = *(!SPLIT && p.s1 ? p.s1 : &g_one);
     const float code_inv = *(!SPLIT && p.codes ? p.code_inv : &g_one);
