@@ -565,21 +565,37 @@ def test_convert_operands_equals_the_separate_calls(case, x_from):
 @pytest.mark.parametrize("vectors", [2040, 2048, 2056, 4096, 4104, 6144, 6152, 8192])
 @pytest.mark.parametrize("last", [False, True])
 def test_maximum_of_a_whole_tensor_in_every_workgroup(dtype, vectors, last):
-    """Around the multiples of 2048 16-byte vectors at which a workgroup that finds the maximum by itself requests more: the maximum in the first or in the last element, codes and scale the oracle's bit for bit."""
-    rows = 8 if vectors % 16 else 64
-    cols = vectors * (16 // np.dtype(dtype).itemsize) // rows
-    x = _data(np.random.default_rng(vectors), (rows, cols), dtype, sigma=0.3)
+    """Around the multiples of 2048 16-byte vectors at which a workgroup that finds the maximum by itself requests more, by 512 threads (the
+    tensor alone) and by 256 (beside weights with a scale per row): the maximum in the first or in the last element, codes and scale the
+    oracle's bit for bit."""
+    e = 16 // np.dtype(dtype).itemsize
+    rows = e if vectors % 16 else 64
+    cols = vectors * e // rows
+    assert cols % 8 == 0 and rows * cols == vectors * e      # what the vector tiles take
+    rng = np.random.default_rng(vectors)
+    x = _data(rng, (rows, cols), dtype, sigma=0.3)
     x[(-1, -1) if last else (0, 0)] = dtype(-7.5)
     say("whole tensor", dtype.__name__, rows, cols, "last", last)
     so, io = orc.scales_from_amax(orc.absmax(x, "tensor"))
-    s, iv, am = empty(1, torch.float32), empty(1, torch.float32), empty(1, torch.float32)
-    q = torch.full((rows, cols), 99, dtype=torch.int8, device="cuda")
-    qT = torch.full((cols, rows), 99, dtype=torch.int8, device="cuda")
-    Q.qsync_absmax_quantize(dev(x), rows, cols, 8, Q.ROUND_NEAREST, 0, 0, s, iv, am, q, qT, ws(Q.qsync_absmax_quantize_workspace_bytes(rows, cols)))
-    assert_bits_equal(host(s), so, "scale")
     want = orc.quantize_int(x, io, "tensor", "nearest")
-    assert_bits_equal(host(q), want, "codes")
-    assert_bits_equal(host(qT), want.T, "transposed codes")
+    f = lambda n: torch.zeros(n, dtype=torch.float32, device="cuda")
+    codes = lambda r, c: torch.full((r, c), 99, dtype=torch.int8, device="cuda")
+    s, iv, am, q, qT = f(1), f(1), f(1), codes(rows, cols), codes(cols, rows)
+    Q.qsync_absmax_quantize(dev(x), rows, cols, 8, Q.ROUND_NEAREST, 0, 0, s, iv, am, q, qT, ws(Q.qsync_absmax_quantize_workspace_bytes(rows, cols)))
+    N = 48
+    w = _data(rng, (N, cols), np.float32, sigma=0.02)
+    s2, q2, q2T, wq, wqT = f(1), codes(rows, cols), codes(cols, rows), codes(N, cols), codes(cols, N)
+    need = max(Q.qsync_absmax_workspace_bytes(rows, cols, Q.PER_TENSOR), Q.qsync_absmax_workspace_bytes(N, cols, Q.PER_COL))
+    sw = f(N)
+    Q.qsync_convert_operands(Q.INT8, dev(x), rows, cols, None, dev(w), N, 1, 8, Q.PER_ROW, s2, f(1), f(1), q2, q2T, sw, f(N), f(N), wq, f(cols),
+                             f(cols), wqT, ws(need), ws(need))
+    for what, gs, gq, gqT in (("alone", s, q, qT), ("beside weights", s2, q2, q2T)):
+        assert_bits_equal(host(gs), so, "scale " + what)
+        assert_bits_equal(host(gq), want, "codes " + what)
+        assert_bits_equal(host(gqT), want.T, "transposed codes " + what)
+    wo, wi = orc.scales_from_amax(orc.absmax(w, "row"))
+    assert_bits_equal(host(sw), wo, "weight scales")
+    assert_bits_equal(host(wq), orc.quantize_int(w, wi, "row", "nearest"), "weight codes")
 
 
 def test_absmax_quantize_all_zero_and_lower_bits():
