@@ -1106,3 +1106,40 @@ def test_small_tile_on_whole_and_straddling_rows(tag, ktiles):
             assert_bits_equal(host(dw), (dy.astype(np.float64).T @ x.astype(np.float64)).astype(np.float32), "dW")
     finally:
         Q.qsync_debug_set_gemm_tile(-1)
+
+
+@pytest.mark.parametrize("tag", [Q.INT8, Q.FP16, Q.FP32])
+@pytest.mark.parametrize("ktiles,last", [(90, 9), (83, 2), (82, 1), (81, 0)])
+def test_tile_with_loading_wavefronts_in_uneven_splits(tag, ktiles, last):
+    """The 128x128 tile with loading wavefronts in ten K splits of nine K tiles, the last with fewer of them than there are stages,
+    or with none (its loading wavefronts leave at once): sums of products of small integers exactly, contiguous and row-major operands."""
+    rng = np.random.default_rng(200 + ktiles)
+    esz = {Q.INT8: 1, Q.FP16: 2, Q.FP32: 4}[tag]
+    ints = lambda *s: rng.integers(-8, 9, s).astype({Q.INT8: np.int8, Q.FP16: np.float16, Q.FP32: np.float32}[tag])
+    s = dev(np.ones(1, np.float32)) if tag == Q.INT8 else None
+    M, N, K = 640, 528, ktiles * 128 // esz      # 25 tiles: 10 splits keep 250 workgroups
+    splits = 10
+    per = -(-ktiles // splits)
+    assert per == 9 and ktiles - per * (splits - 1) == last
+    Q.qsync_debug_set_gemm_tile(1)
+    try:
+        say("uneven splits", tag, ktiles, last)
+        a, b = ints(M, K), ints(N, K)
+        want = (a.astype(np.float64) @ b.astype(np.float64).T).astype(np.float32)
+        y = torch.full((M, N), 7.0, dtype=torch.float32, device="cuda")
+        bytes_ = Q.qsync_qlinear_workspace_bytes(tag, M, N, K)
+        assert bytes_ == splits * M * N * 4
+        room = torch.full((bytes_,), 255, dtype=torch.uint8, device="cuda")
+        Q.qsync_qlinear_fwd(tag, M, N, K, dev(a), s, dev(b), s, Q.PER_TENSOR, None, y, None, room)
+        assert_bits_equal(host(y), want, "Y")
+        if tag != Q.FP32 and K % 128 == 0:      # the same sum as a weight gradient: K rows
+            say("uneven splits row-major", tag, ktiles, last)
+            dy, x = np.ascontiguousarray(a.T), np.ascontiguousarray(b.T)
+            dw = torch.full((M, N), 7.0, dtype=torch.float32, device="cuda")
+            bytes_ = Q.qsync_qlinear_bwd_rm_workspace_bytes(tag, K, M, N)
+            assert bytes_ >= splits * M * N * 4
+            room = torch.full((bytes_,), 255, dtype=torch.uint8, device="cuda")
+            Q.qsync_qlinear_bwd_rm(tag, K, M, N, dev(dy), s, dev(x), s, None, None, Q.PER_TENSOR, None, dw, None, None, None, None, room)
+            assert_bits_equal(host(dw), want, "dW")
+    finally:
+        Q.qsync_debug_set_gemm_tile(-1)
