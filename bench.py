@@ -400,7 +400,7 @@ def run(args):
     if not args.no_extra_passes:
         scratch = torch.empty(512 * 256, dtype=torch.int32, device="cuda")
         mfma_probe = {"unit": "TOPS" if tag == Q.INT8 else "TFLOP/s", "kernel": "qsync_probe_mfma (512 x 4 wavefronts, "
-                      "back-to-back 32x32 matrix instructions on register operands)"}
+                      "back-to-back 16x16 matrix instructions on register operands)"}
         modes = [("constant_operands", 0), ("random_operands", 1)]
         if tag == Q.FP16:
             modes.append(("random_operands_second_subnormal", 2))

@@ -14,12 +14,12 @@ extern "C" {
 
 /*
  * qsync_probe_mfma - measurement probe, not part of the operator path: launches a kernel that issues
- * `iters` x 4 back-to-back 32x32 matrix instructions per wavefront on register operands (512 workgroups
+ * `iters` x 8 back-to-back 16x16 matrix instructions per wavefront on register operands (512 workgroups
  * of 4 wavefronts, no memory traffic), so that a caller can time the matrix-instruction rate this GPU
  * sustains: with constant operands (random_operands = 0) and with pseudo-random operand values
  * (random_operands = 1; power management lowers the clock when operand bits toggle); random_operands = 2
  * is mode 1 with the second binary16 operand drawn from the subnormal range (same as 1 for QSYNC_INT8).
- * tag QSYNC_INT8 (v_mfma_i32_32x32x32_i8) or QSYNC_FP16 (v_mfma_f32_32x32x16_f16); 1 <= iters <= 2^24,
+ * tag QSYNC_INT8 (v_mfma_i32_16x16x64_i8) or QSYNC_FP16 (v_mfma_f32_16x16x32_f16); 1 <= iters <= 2^24,
  * rounded up to a multiple of 4.
  * out      device scratch, at least 512 KiB (one 4-byte word per thread).
  * ops_out  host pointer or NULL: receives the number of arithmetic operations the launch performs.

@@ -793,8 +793,8 @@ int qsync_probe_mfma(int tag, int random_operands, int iters, void* out, double*
     if(iters < 1 || iters > (1 << 24)) return QSYNC_ERR_BAD_SHAPE;
     iters = (iters + 3) / 4 * 4;               // the kernel runs whole groups of four iterations
     if(random_operands < 0 || random_operands > 2) return QSYNC_ERR_BAD_ENUM;
-    if(ops_out)   // a 32x32x32 int8 instruction is 2*32*32*32 operations, the 32x32x16 binary16 one half of that
-        *ops_out = static_cast<double>(kProbeBlocks) * 4.0 * 4.0 * iters * (tag == QSYNC_INT8 ? 65536.0 : 32768.0);
+    if(ops_out)   // a 16x16x64 int8 instruction is 2*16*16*64 operations, the 16x16x32 binary16 one half of that
+        *ops_out = static_cast<double>(kProbeBlocks) * 4.0 * 8.0 * iters * (tag == QSYNC_INT8 ? 32768.0 : 16384.0);
     return hip_status(launch_probe_mfma(tag, random_operands, iters, out, static_cast<hipStream_t>(stream)));
 }
 

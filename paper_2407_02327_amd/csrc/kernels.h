@@ -184,7 +184,7 @@ int gradient_pair_tile(const GemmProblem& dx, const GemmPlan& plan_dx, const Gem
 hipError_t launch_gradient_pair(const GemmProblem& dx, const GemmProblem& dw, int tile, const ColumnFoldArgs& fold, hipStream_t stream);
 
 // ---- measurement probe (probe.hip): matrix instructions on register operands, no memory traffic
-constexpr int kProbeBlocks = 512;       // workgroups of 4 wavefronts, 4 matrix instructions per wavefront and iteration
+constexpr int kProbeBlocks = 512;       // workgroups of 4 wavefronts, 8 matrix instructions per wavefront and iteration
 hipError_t launch_probe_mfma(int prec, int operand_mode, int iters, void* out, hipStream_t stream);
 
 }  // namespace qsync

@@ -1,6 +1,6 @@
 // Measurement probe: the matrix-instruction rate this GPU sustains with no memory traffic at all.
-// 512 workgroups of 4 wavefronts issue back-to-back 32x32 matrix instructions on register operands
-// (four independent accumulators per wavefront).  The sustained rate depends on the operand values:
+// 512 workgroups of 4 wavefronts issue back-to-back 16x16 matrix instructions, those of the GEMM tiles, on register operands
+// (eight independent accumulators per wavefront).  The sustained rate depends on the operand values:
 // with constant operands the instruction stream runs at the clock the published peak assumes, with
 // varying operands (random codes, as in a quantized GEMM) power management lowers the clock.  The
 // benchmark reports both beside the GEMM's own rate.
@@ -11,8 +11,7 @@ namespace qsync {
 namespace {
 
 typedef int      v4i32 __attribute__((ext_vector_type(4)));
-typedef int      v16i32 __attribute__((ext_vector_type(16)));
-typedef float    v16f32 __attribute__((ext_vector_type(16)));
+typedef float    v4f32 __attribute__((ext_vector_type(4)));
 typedef _Float16 v8f16 __attribute__((ext_vector_type(8)));
 
 __device__ __forceinline__ unsigned mix(unsigned h)
@@ -24,13 +23,10 @@ __device__ __forceinline__ unsigned mix(unsigned h)
 template <bool RANDOM>
 __global__ __launch_bounds__(256) void probe_i8_kernel(int iters, int* out)
 {
-    v16i32 acc[4];
-    v4i32  a[4], b[4];
+    v4i32 acc[8] = {}, a[4], b[4];
 #pragma unroll
     for(int i = 0; i < 4; ++i)
     {
-#pragma unroll
-        for(int v = 0; v < 16; ++v) acc[i][v] = 0;
 #pragma unroll
         for(int j = 0; j < 4; ++j)
         {
@@ -42,25 +38,23 @@ __global__ __launch_bounds__(256) void probe_i8_kernel(int iters, int* out)
 #pragma unroll
         for(int r = 0; r < 4; ++r)
 #pragma unroll
-            for(int i = 0; i < 4; ++i) acc[i] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[i], b[(i + r) & 3], acc[i], 0, 0, 0);
+            for(int i = 0; i < 8; ++i) acc[i] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[i & 3], b[(i + r + i / 4) & 3], acc[i], 0, 0, 0);
     int s = 0;
 #pragma unroll
-    for(int i = 0; i < 4; ++i)
+    for(int i = 0; i < 8; ++i)
 #pragma unroll
-        for(int v = 0; v < 16; ++v) s += acc[i][v];
+        for(int v = 0; v < 4; ++v) s += acc[i][v];
     out[blockIdx.x * 256 + threadIdx.x] = s;
 }
 
 template <bool RANDOM>
 __global__ __launch_bounds__(256) void probe_f16_kernel(int iters, float* out, float b_step)
 {
-    v16f32 acc[4];
-    v8f16  a[4], b[4];
+    v4f32 acc[8] = {};
+    v8f16 a[4], b[4];
 #pragma unroll
     for(int i = 0; i < 4; ++i)
     {
-#pragma unroll
-        for(int v = 0; v < 16; ++v) acc[i][v] = 0.0f;
 #pragma unroll
         for(int j = 0; j < 8; ++j)
         {
@@ -74,12 +68,12 @@ __global__ __launch_bounds__(256) void probe_f16_kernel(int iters, float* out, f
 #pragma unroll
         for(int r = 0; r < 4; ++r)
 #pragma unroll
-            for(int i = 0; i < 4; ++i) acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[i], b[(i + r) & 3], acc[i], 0, 0, 0);
+            for(int i = 0; i < 8; ++i) acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[i & 3], b[(i + r + i / 4) & 3], acc[i], 0, 0, 0);
     float s = 0.0f;
 #pragma unroll
-    for(int i = 0; i < 4; ++i)
+    for(int i = 0; i < 8; ++i)
 #pragma unroll
-        for(int v = 0; v < 16; ++v) s += acc[i][v];
+        for(int v = 0; v < 4; ++v) s += acc[i][v];
     out[blockIdx.x * 256 + threadIdx.x] = s;
 }
 
