@@ -14,9 +14,10 @@
 //     one 256-byte bank row per group, so the chunk position is XOR-swizzled with (row/2)%8
 //     (applied on the global-address side of the direct load): the 16 lanes that read one
 //     chunk index of 16 consecutive rows then touch 16 different 16-byte bank groups;
-//   * two LDS stages (three for the 128x128 tile while no compute unit gets a second workgroup): the next K
-//     step streams in while the current one feeds the matrix cores; a fragment of the next 64-byte K chunk is requested
-//     behind the last matrix instruction that reads its registers; one barrier per K step;
+//   * two LDS stages: the next K step streams in while the current one feeds the matrix cores; a fragment of the next
+//     64-byte K chunk is requested behind the last matrix instruction that reads its registers; one barrier per K step.
+//     The 128x128 tile, while no compute unit gets a second workgroup, has three stages, or four and wavefronts of their
+//     own for the loads (launch_traits);
 //   * the dequantizer (scalar scales, per-column scale vector, per-column bias) runs on the
 //     accumulator registers (the paper fuses dequantization at the same point: before the
 //     accumulators are copied to shared memory); the B fragment is fed as the instruction's
@@ -489,19 +490,21 @@ __device__ __forceinline__ void gemm_tile(const GemmKernelArgs& p, int lin, int 
     // barrier that publishes the next stage (every wavefront's reads of the current one have returned by then), requests the
     // direct load of the tile after next into the stage just drained (some wavefronts: later in the tile, see below), reads
     // chunk 0 of the next tile, issues chunk 1, whose operands are already in registers, and reads chunk 1 of the next tile: barrier release, LDS latency and a whole K tile of memory latency hide behind matrix work.
-    // With four rows (128 tile) the reads go out between the rows' instructions, and the load behind row 0: 4096x768x3072
-    // int8 16.4 -> 15.7 us, binary16 28.0 -> 26.4, against all of them at the chunk's end; the 64 tile, of which a unit holds
+    // With four rows (128 tile) the reads go out between the rows' instructions, and the load behind row 0: 4096x768x3072 in three
+    // stages int8 16.4 -> 15.7 us, binary16 28.0 -> 26.4, against all of them at the chunk's end; the 64 tile, of which a unit holds
     // several, gains nothing from that (its convolution's weight gradient 32.2 -> 33.2).
     // The 256 tile's wavefronts have no registers for both chunks.  A row's fragment is used by FN instructions in a row and
     // never again, so its registers are requested anew, for the next chunk, right behind them; the columns'
     // fragments, which every row uses, have two sets, and those of the next chunk are requested behind the first rows.  In chunk 1 no
     // row in front of the middle requests anything: there the barrier and the load's request follow, then the next tile's columns
     // and first rows, and the other rows go on as before.
-    // 32x32 instructions with four 32-byte chunks and two sets of fragments -> this, values N(0,1), us: 16384x1024x4096 int8
-    // 60.7 -> 54.8, binary16 115 -> 105, 16384x4096x1024 int8 89.4 -> 83.2; 8192^3 2.44 -> 2.92 POP/s and 1.22 -> 1.46 PFLOP/s;
-    // on zeros, i.e. at the full clock, within 2 % of the same times.  128 tile: 4096x3072x768 int8 16.4 -> 15.2, binary16
-    // 25.6 -> 24.3; row-major 4096x768x3072, one workgroup a unit, binary16 35.8 -> 35.0, int8 20.5 -> 21.7.  64 tile:
-    // 2048x2048x1024 binary16 15.2 -> 14.3, 1808x1040x784 int8 8.1 -> 7.7, a single workgroup walking 48 K tiles 17.6 -> 18.2.
+    // 32x32 instructions with four 32-byte chunks and two sets of fragments -> this, values N(0,1), side by side, us: 16384x1024x4096
+    // int8 59.1 -> 53.0, binary16 112 -> 101, 16384x4096x1024 79.4 -> 75.1 and 132 -> 124; 8192^3 2.55 -> 2.84 POP/s and 1.28 -> 1.42
+    // PFLOP/s; on zeros, i.e. at the full clock, within 2 % of the same times.  The smaller tiles are not bound by power, and gain
+    // little: 128 tile, 4096x3072x768 int8 14.9 -> 15.3, binary16 24.5 -> 24.8 (256 tile 15.8 -> 15.6, 23.0 -> 22.1); 64 tile, 2048x2048x1024
+    // binary16 14.4 -> 14.1, 1808x1040x784 int8 7.42 -> 7.37, 64x64x6144 in splits 8.69 -> 8.67.  fp32 8192x4096x1024, whose
+    // instructions are 16x16x4 in place of 32x32x2: 256 tile 493.6 -> 489.4, 128 tile 496.6 -> 492.1, 64 tile 524.9 -> 530.6; over 160
+    // products and backward passes of 64..16384 by 64..4096 as planned 0.4 % faster.
     // The column scales and biases of this tile are fetched by direct loads as well, in front of the first K tile, and
     // wait in LDS behind the stages for the epilogue.
     // The direct loads of a K tile are not requested by all wavefronts at once.  A compute unit takes such an
@@ -738,7 +741,7 @@ __global__ __launch_bounds__(512) void gemm_nt_persistent_kernel(const GemmKerne
     constexpr int DPW         = 16;                           // direct loads per loader wavefront and K tile
     constexpr int PITCH       = WTN * 2 + 16;                 // padded row of 64 binary16 outputs in the hand-over area
     constexpr int L_STG       = WTM * PITCH;                  // a loader's whole sub-tile
-    constexpr int S_STG       = 32 * PITCH;                   // a storer's private slice: one row of fragments
+    constexpr int S_STG       = 32 * PITCH;                   // a storer's private slice: 32 rows, two of fragments
     constexpr int STG_BASE    = STAGE_BYTES;                  // the hand-over area starts where stage 1 starts
     constexpr int S_BASE      = STG_BASE + 4 * L_STG;
     constexpr int COLP_BASE   = S_BASE + 4 * S_STG;           // [2][BN] floats: alpha * column scale, column bias
@@ -1127,6 +1130,7 @@ __global__ __launch_bounds__(kThreads) void splitk_reduce_kernel(const ACC* __re
 struct TileShape { int bm, bn; };
 // 0: 256x256, 8 wavefronts (2x4, 128x64 each)   1: 128x128, 8 wavefronts (2x4, 64x32 each)
 // 2: 64x64, 4 wavefronts (2x2, 32x32 each)
+// (What follows was measured on 32x32 instructions.)
 // (128x128 with four wavefronts of 64x64, one per SIMD, reads a third less LDS per operation but has nobody to issue
 //  matrix instructions while it queues direct loads.  Four -> eight wavefronts: 4096x768x3072 int8 18.1 -> 16.2 us,
 //  3072x768x4096 20.4 -> 18.2, 2056x1000x1032 binary16 14.0 -> 12.5, 64x128x128 4.7 -> 3.9.)
@@ -1185,13 +1189,17 @@ hipError_t launch_traits(int tile, const GemmKernelArgs& a, int splits, hipStrea
 {
     // The 128x128 tile where every compute unit gets one workgroup at most (with a second one resident, two stages,
     // its K loop fills the gaps):
-    //   four stages and four loading wavefronts, three stages -> this, us: 4096x768x3072 (192 workgroups) int8 15.9 -> 13.9,
-    //   binary16 26.3 -> 22.7; 2048x2048x1536 int8 11.1 -> 10.3, 1024x512x2048 10.6 -> 9.5; row-major 2048x1024x1024 12.9 -> 11.7.
-    //   Their start costs 0.3 us, a K tile less gains 0.05 to 0.12: 8 K tiles int8 8.07 -> 7.99, 6 lose (7.6 -> 7.8), 2 lose 5 %.
-    //   Rows that straddle the 128-byte lines (two lines a piece) keep the loaders the bound: 4096x768x3088 int8 18.4 ->
-    //   18.9; the gathering loads of a convolution have too much arithmetic for four wavefronts (24.9 -> 28.2).
-    //   three stages otherwise.  Two -> three: 4096x768x3072 int8 18.5 -> 15.3 us, binary16 33.5 -> 26.4; 2048x2048x4096
-    //   (256) int8 25.8 -> 22.5; a short contraction gains nothing (4096x768x768 int8 6.8 -> 7.0).
+    //   four stages and four loading wavefronts, three stages -> this, us: 4096x768x3072 (192 workgroups) int8 16.4 -> 14.6,
+    //   binary16 25.1 -> 22.6; 2048x2048x1536 int8 9.9 -> 9.3, 1024x512x2048 10.5 -> 9.6; fp32, bound by its instructions, stays as
+    //   it is (33 products: 0.98 to 1.015).
+    //   Their start costs 0.3 us, a K tile less gains 0.05 to 0.12: 8 K tiles int8 7.33 -> 7.30, 6 lose (7.6 -> 7.8), 2 lose 5 %.
+    //   Contiguous rows that straddle the 128-byte lines (two lines a piece) keep the loaders the bound: 4096x768x3088 int8 18.4 ->
+    //   18.9.  A row-major stage row is 128 or 256 bytes of a longer operand row, for which that matters less: they take any row length.
+    //   Whole lines 2048x1024x1024 12.8 -> 11.7, 4096x768x3072 int8 21.7 -> 18.8; others 1536x1344x1792 int8 11.1 -> 10.6, binary16
+    //   1408x576x3640 17.1 -> 15.7, 1792x480x816 14.2 -> 13.8 (over 179 row-major products 0.83 to 1.04 of three stages, on average 0.96).
+    //   The gathering loads of a convolution have too much arithmetic for four wavefronts (24.9 -> 28.2).
+    //   three stages otherwise.  The rest was measured on 32x32 instructions.  Two -> three: 4096x768x3072 int8 18.5 -> 15.3 us,
+    //   binary16 33.5 -> 26.4; 2048x2048x4096 (256) int8 25.8 -> 22.5; a short contraction gains nothing (4096x768x768 int8 6.8 -> 7.0).
     // Beyond 256 workgroups a third stage loses: 2176x2048x1024 (272) int8 10.9 -> 14.2, binary16 17.6 -> 21.8; 4096x2048x3072
     // (512) int8 29.9 -> 34.2, 4096x3072x768 (768) 15.5 -> 18.9.
     // The 64x64 tile gains nothing from 3, 4 or 8 stages (14.7 / 16.4 / 17.3 / 23.9 us on 2056x1000x1032 binary16), nor
@@ -1272,9 +1280,9 @@ void set_gemm_persistent_mode(int mode) { g_persistent_mode = (mode == 0 || mode
 struct TileModel { double r1, rmax, ovh, cap; int occ; };
 static constexpr TileModel kTileModel[kNumTiles] = {{14.0, 15.8, 7.5, 2280.0, 1}, {8.3, 9.0, 4.2, 1900.0, 2}, {3.55, 5.48, 3.2, 2060.0, 4}};
 // fp32: the matrix instructions bound every tile alike (19.7 in these units), so rates lie close together and the smaller tile's finer
-// grain decides; fitted to 70 shapes of 64..16384 by 64..4096, timed on the three tiles: 2.5 % behind the best on average, before,
-// with the constants above, 10-13 %; 2652x440x1912 84 -> 57 us, 968x1288x2140 89 -> 63, 14828x552x380 108 -> 72.  On 70 others
-// 1.9 % (7 %).
+// grain decides; fitted to 70 shapes of 64..16384 by 64..4096, timed on the three tiles of 32x32x2 instructions: 2.5 % behind the best
+// on average, before, with the constants above, 10-13 %; 2652x440x1912 84 -> 57 us, 968x1288x2140 89 -> 63, 14828x552x380 108 -> 72.  On 70
+// others 1.9 % (7 %).  On the present tiles 0.7 % over 100 shapes, 13 % at most (7132x1876x72).
 static constexpr TileModel kTileModelF32[kNumTiles] = {{14.5, 16.3, 7.5, 4300.0, 1}, {14.3, 16.2, 4.2, 4300.0, 2}, {11.5, 15.3, 3.2, 4300.0, 4}};
 // Row-major (TN) operands: a K tile takes twice the LDS fragment reads, and a 64-wide tile of int8 operands
 // loads 64-byte row pieces (binary16: 128 bytes, no penalty); fitted slow-down of the main loop per tile shape.
@@ -1299,10 +1307,12 @@ GemmPlan plan_gemm(int prec, int64_t M, int64_t N, int64_t K, int force_tile, in
     const int64_t ktiles = (kb + kRowBytes - 1) / kRowBytes;
     auto ntiles = [&](int t) { return ((M + kTiles[t].bm - 1) / kTiles[t].bm) * ((N + kTiles[t].bn - 1) / kTiles[t].bn); };
     // Plan = (tile, K splits) with the smallest estimated time.  The estimate is a small model fitted to gfx950
-    // measurements of this kernel (int8 and binary16, forward, row-major and transposed weight-gradient forms: 54
-    // operands x 3 tiles, replayed from a graph; rms error 11 %, the choice at most 8 % behind the best tile of those.  65
-    // other shapes a type: 1.0 % behind on average with int8, 1.6 % with binary16, 22 % at most, 3120 x 3504 x 64; fp32 operands have
-    // constants of their own):
+    // measurements of these tiles on 32x32 instructions (int8 and binary16, forward, row-major and transposed weight-gradient
+    // forms: 54 operands x 3 tiles, replayed from a graph; rms error 11 %; fp32 operands have constants of their own).  It knows
+    // nothing of the 128 tile's loading wavefronts.  The choice against the best of the three present tiles, over 465 shapes of 64..16384
+    // by 64..4096 that are the tiles': forward 1.1 % behind on average with int8 and 1.7 % with binary16, row-major 0.6 % and 1.6 %,
+    // as before (1.0 % and 1.6 %); more than 10 % in 18 of them, 35 % at most (row-major binary16 3328x528x2384, split on the 64 tile
+    // where the 128 tile takes 22.9 us):
     //   a compute unit retires `r1` Mop/us per resident workgroup of a tile shape, up to `rmax` with `occ` of them
     //   sharing it; the chip as a whole retires at most `cap` Mop/us (256 busy units, at a lower clock and on
     //   shared caches, do not each reach `rmax`); every round of co-resident workgroups costs `ovh` us of launch, first-load latency
@@ -1477,10 +1487,11 @@ hipError_t launch_gemm(const GemmProblem& p, const GemmPlan& plan, void* workspa
         const hipError_t e     = launch_conv3x3(p, g_tile_override, &taken, stream);
         if(taken || e != hipSuccess) return e;
     }
-    // The persistent kernel is opt-in.  Launched alone and back to back it beats the per-tile kernel by 7-20 % (the
-    // write-back of a tile overlaps the next tile's K loop), but inside an operator sequence its fixed tile
-    // assignment loses what it gains: workgroups that start late, behind the tail of the previous kernel, still
-    // walk their full share of tiles, while the per-tile grid is balanced by the hardware dispatcher.
+    // The persistent kernel is opt-in.  Its write-back of a tile overlaps the next tile's K loop, which on 32x32 instructions gained
+    // 7-20 % launched alone and back to back; the present K loop leaves its wavefronts no registers for a second set of the columns'
+    // fragments, and it loses there too: 16384x4096x1024 int8 75.1 us per tile, 80.5 persistent, binary16 124.4 and 127.1, 16384x1024x4096 53.0
+    // and 53.5.  Inside an operator sequence its fixed tile assignment costs more: workgroups that start late, behind the tail of the
+    // previous kernel, still walk their full share of tiles, while the per-tile grid is balanced by the hardware dispatcher.
     if(!p.tn && persistent_eligible(a, p.prec, plan.tile, splits)
        && g_persistent_mode == 1)
         return p.prec == 8 ? launch_persistent<I8Traits>(a, stream) : launch_persistent<F16Traits>(a, stream);
@@ -1514,12 +1525,13 @@ static double unit_time(const TileModel& m, double mop, const double* rounds, in
 
 // Tile on which two GEMMs share a launch (`a` first), or -1 when two launches are estimated to be about as fast: with more
 // than sixteen rounds of workgroups each of them fills the chip by itself, and a long contraction unsplit beside short ones
-// would outlast them.  Separate launches -> one, measured: int8 1808x1040x784 15.8 -> 11.7 us, 4096x768x3072 35.1 ->
-// 30.2, 1024^3 11.2 -> 7.4; binary16 2056x1000x1032 31.2 -> 25.4, 4096x3072x768 60.9 -> 51.7; not paired: 4096x768x768
-// binary16 28.5 (one launch 32.8), 3000x768x768 25.4 (30.2).
+// would outlast them.  Separate launches -> one, measured: int8 1808x1040x784 15.6 -> 12.2 us, 1024^3 10.7 -> 6.9, 512^3 6.8 -> 4.8,
+// 4096x768x3072 31.5 -> 30.5; binary16 2056x1000x1032 31.0 -> 25.3, 4096x3072x768 50.3 -> 50.8 (4096x768x3072 and 4096x3072x768
+// gained 5 and 9 us before the separate launches had loading wavefronts); not paired: 4096x768x768 binary16 26.1 (one launch
+// 26.5), 3000x768x768 24.9 (25.1).
 // How far the estimate reaches, over 146 backward passes (44 operators from 512^3 to 8192 x 1024^2, drawn evenly over the
-// logarithm, both types, transposed copies and row-major, replayed from a graph; two launches against one on either tile):
-// its rms error is 17 % for int8 and 27 % for binary16, where it is 14 % too long on average.  The choice costs 1.9 % on
+// logarithm, both types, transposed copies and row-major, replayed from a graph; two launches against one on either tile), all on the
+// tiles' form of 32x32 instructions: its rms error is 17 % for int8 and 27 % for binary16, where it is 14 % too long on average.  The choice costs 1.9 % on
 // average against the best of the three and more than 10 % in ten cases (binary16 384x1744x1168 left apart, 19.5 us against
 // 14.2, is the worst); it errs towards two launches: the 114 pairs run 1.48 times as fast as apart, the worst of them
 // 2.4 % slower.

@@ -154,15 +154,15 @@ template <typename TR> hipError_t launch_rows(const GemmKernelArgs& a, int colum
 }
 // Fragments of columns a workgroup, 0: other tiles are faster.  A second workgroup on a unit waits for the first (its stages fill
 // the LDS; at most 16 rows two fit), which loses at once: 64x16384x64 3.8 us on the tiles, 9.0 here.  Beyond 6 KB of contraction
-// (8 KB up to 32 rows) K splits over workgroups win.  Tiles -> here, operands warm, binary16 outputs, us:
-//   int8, 16 columns:  1x4096x1024 5.2 -> 3.2, 64x4096x4096 13.2 -> 7.7, 128x1024x2048 7.3 -> 4.7, 256x1024x4096 10.2 -> 7.0,
-//                      512x512x4096 10.4 -> 8.0, 4096x64x3072 9.5 -> 6.2; 100x768x6144 9.4 -> 7.4 and 4096x64x64 3.7 -> 3.5 gain
-//                      least, 100x768x8192 8.9 -> 8.7 and 65x1000x8192 8.7 -> 11.8 lie beyond
-//   int8, 32 columns:  512x1024x2048 7.5 -> 5.7, 200x2000x4096 12.7 -> 9.9, 4096x128x3072 9.8 -> 7.5, 64x8192x6144 16.3 -> 14.0;
-//                      512x1024x128 3.6 -> 3.9 is the loss at the short end (one K tile of the 64 tile: from 256 bytes on)
+// (8 KB up to 32 rows) K splits over workgroups win.  The better of the 128 and 64 tiles -> here, operands warm, binary16 outputs, us:
+//   int8, 16 columns:  1x4096x1024 5.0 -> 3.3, 64x4096x4096 10.7 -> 8.5, 128x1024x2048 7.2 -> 4.7, 256x1024x4096 10.7 -> 6.9,
+//                      512x512x4096 10.7 -> 7.1, 4096x64x3072 9.3 -> 6.0; 100x768x6144 9.7 -> 7.1 and 4096x64x64 3.6 -> 3.4 gain
+//                      least, 100x768x8192 9.3 -> 8.7 and 65x1000x8192 9.0 -> 11.8 lie beyond
+//   int8, 32 columns:  512x1024x2048 7.6 -> 5.7, 200x2000x4096 12.8 -> 7.9, 4096x128x3072 9.6 -> 7.2, 64x8192x6144 16.3 -> 13.9;
+//                      512x1024x128 3.5 -> 3.9 is the loss at the short end (one K tile of the 64 tile: from 256 bytes on)
 //   binary16, the same bytes: within 2 % of the int8 times.
 // A product whose maximum, codes or accumulators are wanted too stays on the tiles, whose epilogue has them: with the maximum
-// 64x128x128 int8 3.8 us (here, without it, 3.6), 45x4096x1024 5.8 (4.2), 512x1024x2048 8.2 (6.1); binary16 1.2 to 2.1 times.
+// 64x128x128 int8 3.7 us (here, without it, 3.3), 45x4096x1024 5.6 (3.9), 512x1024x2048 7.9 (5.7); binary16 1.2 to 2.1 times.
 int rows_columns(const GemmProblem& p)
 {
     const int64_t bytes = p.K * (p.prec / 8), rows = (p.M + 63) / 64;
