@@ -654,7 +654,9 @@ __device__ __forceinline__ void gemm_tile(const GemmKernelArgs& p, int lin, int 
     else if(NL == 0)
         wait_direct_loads<0>();                  // the column parameters
     const float    alpha     = scale0 * scale1;
-    const uint32_t amax_seen = (!SPLIT && p.amax_bits) ? __hip_atomic_load(p.amax_bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+    // (by the wavefront that publishes: loads of the word stand in line with the atomics on it, and with some hundred workgroups that end
+    // together the line is what they wait for.  Every wavefront -> one, int8 912x3008x752 28.5 -> 20.4 us, 12896x576x368 24.4 -> 17.3)
+    const uint32_t amax_seen = (!SPLIT && p.amax_bits && wave == 0) ? __hip_atomic_load(p.amax_bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
 
     store_tile<TR, BM, BN, WGM, WGN, 2 * STAGE_BYTES / (WGM * WGN), SPLIT>(p, acc, lds, colp, m0, n0, split, alpha, code_inv, amax_seen);
 }
