@@ -1672,9 +1672,11 @@ __global__ __launch_bounds__(kBlock) void dequantize_cols_kernel(const Ti* __res
 #pragma unroll
         for(int u = 0; u < U; ++u)
         {
-            const int64_t r = base + u * TY + ty;      // (the last row again for absent ones, without a branch: 107 registers in place of 88,
-            // int8 6320x3616 to fp32 34.0 -> 35.1 us, 383x592 4.13 -> 4.25, and faster nowhere)
-            raw[u] = r < rows ? *reinterpret_cast<const uint4*>(a + r * ld + c) : make_uint4(0, 0, 0, 0);
+            // Four-byte inputs load the last row again for absent ones instead of branching around each load (int32 6320x3616 to fp32
+            // 40.8 -> 37.0 us, 1000x1032 to binary16 4.15 -> 3.81).  Bytes, sixteen of them a load, keep the branch: without it int8
+            // to fp32 takes 107 registers in place of 88, 383x592 4.15 -> 4.27 us, and no size gains by more than 2 %.
+            const int64_t r = base + u * TY + ty;
+            raw[u] = sizeof(Ti) == 4 || r < rows ? *reinterpret_cast<const uint4*>(a + (r < rows ? r : rows - 1) * ld + c) : make_uint4(0, 0, 0, 0);
         }
 #pragma unroll
         for(int u = 0; u < U; ++u)
