@@ -900,32 +900,35 @@ template <typename T> struct WeightQuantize
         TileShare<T, true> s;
         s.load(x, r0, c0, rows, cols, cols);
         {   // columns: two threads each; rows: four threads each
-            const int     cc = threadIdx.x % kTileCols, half = threadIdx.x / kTileCols;
+            // (half and part are whole wavefronts': which partials a lane folds is decided, and multiplied out, on the scalar unit; by the
+            // lanes, with a 64-bit product for each load, 4096x2376 26.9 us for both launches, so 26.3, before the joint requests 25.7)
+            static_assert(kTileCols % kWaveSize == 0 && TR % kWaveSize == 0, "wavefronts of one half, of one part");
+            const int     cc = threadIdx.x % kTileCols, half = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / kTileCols);
             const int64_t c  = tile_c + cc;
-            const int     rr = threadIdx.x % TR, part = threadIdx.x / TR;
+            const int     rr = threadIdx.x % TR, part = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / TR);
             const int64_t r  = tile_r + rr;
             const int64_t step = conv_C > 0 ? conv_C : cols;              // conv: [groups][9][C] read as groups * 9 rows of C
             const int     n    = conv_C > 0 ? groups * 9 : groups;
             const int64_t ca   = c < cols ? c : cols - 1, ra = r < rows ? r : rows - 1;      // (absent ones: any, not used)
-            const float*  src  = col_part + (conv_C > 0 ? static_cast<int64_t>(static_cast<uint32_t>(ca) % static_cast<uint32_t>(conv_C)) : ca);
+            const int64_t cs   = conv_C > 0 ? static_cast<int64_t>(static_cast<uint32_t>(ca) % static_cast<uint32_t>(conv_C)) : ca;
             // Rows and the first batch of columns are requested together, in front of the first wait, past the end the last one
             // again (a maximum does not mind): in loops of four and eight with remainders they were up to four more memory
             // latencies in a row.  Whole INT8 steps, us: 384x1920x736 39.8 -> 38.1, 1120x624x512 35.0 -> 33.9.  (Requested under
             // conditions of their own, i.e. a branch a load, they were slower than the loops: convolution 48->416 60.5 -> 64.4.)
             float pr[4], pc[8], mr = 0.0f, mc = 0.0f;
 #pragma unroll
-            for(int i = 0; i < 4; ++i) pr[i] = row_part[(part + 4 * i < tiles_x ? part + 4 * i : tiles_x - 1) * rows + ra];
+            for(int i = 0; i < 4; ++i) pr[i] = (row_part + (part + 4 * i < tiles_x ? part + 4 * i : tiles_x - 1) * rows)[ra];
             for(int g = half; g < n; g += 16)
             {
 #pragma unroll
-                for(int i = 0; i < 8; ++i) pc[i] = src[(g + 2 * i < n ? g + 2 * i : n - 1) * step];
+                for(int i = 0; i < 8; ++i) pc[i] = (col_part + (g + 2 * i < n ? g + 2 * i : n - 1) * step)[cs];
 #pragma unroll
                 for(int i = 0; i < 8; ++i) mc = fmaxf(mc, pc[i]);
             }
 #pragma unroll
             for(int i = 0; i < 4; ++i) mr = fmaxf(mr, pr[i]);
 #pragma unroll 4
-            for(int b = part + 16; b < tiles_x; b += 4) mr = fmaxf(mr, row_part[b * rows + ra]);
+            for(int b = part + 16; b < tiles_x; b += 4) mr = fmaxf(mr, (row_part + b * rows)[ra]);
             lds_c[half][cc]  = mc;
             lds_r[part][rr] = mr;
         }
