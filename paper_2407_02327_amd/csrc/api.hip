@@ -244,9 +244,9 @@ int qsync_gradient_quantize(const void* dy, int dydt, int64_t rows, int64_t cols
                                                workspace, static_cast<hipStream_t>(stream)));
 }
 
-// fp32 products whose contraction is no multiple of 16 bytes split it only where the workspace has room for the parts: it used to
-// be none, and a caller that brings that still gets the result.
-static bool splits_optional(int tag, int64_t contraction) { return tag == QSYNC_FP32 && contraction % 4 != 0; }
+// fp32 products split their contraction only where the workspace has room for the parts: many of them once asked for none, and a
+// caller that brings that still gets the result.
+static bool splits_optional(int tag) { return tag == QSYNC_FP32; }
 static void unsplit(GemmPlan& plan) { plan.splits = 1; plan.workspace = 0; }
 
 size_t qsync_qlinear_workspace_bytes(int tag, int64_t M, int64_t N, int64_t K)
@@ -285,7 +285,7 @@ static int qlinear_fwd_impl(int tag, int64_t M, int64_t N, int64_t K, const void
     }
     if(M == 0 || N == 0) return QSYNC_OK;
     GemmPlan plan = plan_gemm(tag, M, N, K);
-    if(splits_optional(tag, K) && !(workspace && aligned16(workspace) && workspace_bytes >= plan.workspace)) unsplit(plan);
+    if(splits_optional(tag) && !(workspace && aligned16(workspace) && workspace_bytes >= plan.workspace)) unsplit(plan);
     if(plan.workspace > 0)
     {
         if(!workspace || workspace_bytes < plan.workspace) return QSYNC_ERR_WORKSPACE;
@@ -332,7 +332,7 @@ int qsync_qlinear_fwd_codes(int tag, int64_t M, int64_t N, int64_t K, const void
     if(!yq || !next_inv_scale) return QSYNC_ERR_NULL;
     if(bits < 2 || bits > 8) return QSYNC_ERR_UNSUPPORTED;
     if(y_amax_opt && (reinterpret_cast<uintptr_t>(y_amax_opt) & 3u) != 0) return QSYNC_ERR_ALIGN;
-    // fp32 operands whose rows are not 16-byte multiples are refused: launch_gemm_f32, which takes them, hands its epilogue no codes
+    // fp32 operands whose rows are not 16-byte multiples are refused, as the header says
     if(tag == QSYNC_FP32 && ((K * 4) % 16 != 0 || !aligned16(xq) || !aligned16(wq))) return QSYNC_ERR_UNSUPPORTED;
     return qlinear_fwd_impl(tag, M, N, K, xq, sx, wq, sw, wgran, bias_opt, y, ydt, nullptr, y_amax_opt, workspace,
                             workspace_bytes, stream, yq, next_inv_scale, (1 << (bits - 1)) - 1);
@@ -389,8 +389,11 @@ static int qlinear_bwd_impl(int tag, int64_t M, int64_t N, int64_t K, const void
     GemmPlan plan_dx = plan_gemm(tag, M, K, N);
     GemmPlan plan_dw = plan_gemm(tag, N, K, M);
     const bool full = workspace && aligned16(workspace) && workspace_bytes >= qsync_qlinear_bwd_workspace_bytes(tag, M, N, K);
-    if(!full && splits_optional(tag, N)) unsplit(plan_dx);
-    if(!full && splits_optional(tag, M)) unsplit(plan_dw);
+    if(!full && splits_optional(tag))
+    {
+        unsplit(plan_dx);
+        unsplit(plan_dw);
+    }
     const size_t   off_dw  = round256(plan_dx.workspace);
     const size_t   off_db  = off_dw + round256(plan_dw.workspace);
     const size_t   need    = (dx_opt ? plan_dx.workspace : 0) + (dw_opt ? plan_dw.workspace : 0)

@@ -32,8 +32,8 @@ struct I8Traits
 {
     typedef int32_t acc_t;
     typedef v4i32   accv_t;
-    static constexpr int kElemBytes = 1, kRows = 16, kSteps = 1;
-    __device__ static __forceinline__ accv_t mfma(const v4i32& a, const v4i32& b, const accv_t& c, int = 0)
+    static constexpr int kElemBytes = 1, kRows = 16;
+    __device__ static __forceinline__ accv_t mfma(const v4i32& a, const v4i32& b, const accv_t& c)
     {
         return __builtin_amdgcn_mfma_i32_16x16x64_i8(a, b, c, 0, 0, 0);
     }
@@ -42,8 +42,8 @@ struct F16Traits
 {
     typedef float  acc_t;
     typedef v4f32  accv_t;
-    static constexpr int kElemBytes = 2, kRows = 16, kSteps = 1;
-    __device__ static __forceinline__ accv_t mfma(const v4i32& a, const v4i32& b, const accv_t& c, int = 0)
+    static constexpr int kElemBytes = 2, kRows = 16;
+    __device__ static __forceinline__ accv_t mfma(const v4i32& a, const v4i32& b, const accv_t& c)
     {
         return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(v8f16, a), __builtin_bit_cast(v8f16, b), c, 0, 0, 0);
     }
@@ -69,27 +69,6 @@ struct F16Rows32
         return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(v8f16, a), __builtin_bit_cast(v8f16, b), c, 0, 0,
                                                       0);
     }
-};
-
-// fp32 operands: a lane's 16 K-bytes are four floats of one row; the 16x16x4 instruction takes one float per
-// lane (rows lane%16, K index lane/16), so the four components feed four instructions (steps).  Every instruction pairs
-// the same components of A and B, i.e. the same K indices: the K axis is merely visited in a different order.
-struct F32Traits
-{
-    typedef float acc_t;
-    typedef v4f32 accv_t;
-    static constexpr int kElemBytes = 4, kRows = 16, kSteps = 4;
-    __device__ static __forceinline__ accv_t mfma(const v4i32& a, const v4i32& b, const accv_t& c, int step)
-    {
-        return __builtin_amdgcn_mfma_f32_16x16x4f32(__builtin_bit_cast(v4f32, a)[step], __builtin_bit_cast(v4f32, b)[step], c, 0, 0, 0);
-    }
-};
-// 32 rows and columns, sums only (gemm_f32_any_kernel forms its operands itself)
-struct F32Rows32
-{
-    typedef float  acc_t;
-    typedef v16f32 accv_t;
-    static constexpr int kElemBytes = 4, kRows = 32;
 };
 
 struct GemmKernelArgs

@@ -1,128 +1,370 @@
-// FP32 GEMM for operands whose rows are not 16-byte multiples, or that do not start on 16 bytes:
-// C[M,N] = epilogue( sum_k A[m,k] B[n,k] ).
+// FP32 GEMM:  C[M,N] = epilogue( sum_k A[m,k] B[n,k] ), fp32 operands of any row length, on the bf16 matrix instructions.
 //
-// Such rows cannot go to LDS in 16-byte pieces, so they pass through registers, four bytes a lane (a wavefront reads two rows of
-// 128 bytes) and one K tile ahead; the 32x32x2 matrix instruction takes 64 clocks, under which the four-byte loads, their
-// addresses and the LDS writes all fit.  Bound by the matrix instructions, as the 16-byte form is; small products by the K tiles one
-// behind the other (1024 clocks of instructions each on the 64 tile), which the K splits of the plan shorten.
-// Fused multiply-adds
-// on the vector units, 64x64 and no splits -> here, us: 128x175x73 15.4 -> 7.1, 500x300x201 32 -> 11, 1000x1000x1001 193 -> 41,
-// 200x300x8001 1662 -> 27, 4097x175x1023 174 -> 46, 2049x2047x255 67 -> 51; the 16-byte form takes 0.75 of these times.
+// An fp32 value is the exact sum of three bf16 values: its upper eight significant bits (cut off), the next eight (to nearest), the
+// rest.  Of the nine products of two such sums the six largest are added up in fp32, smallest first; what is left out is below 2^-24
+// of a product, of random sign.  Six bf16 instructions of 16x16x32 take 96 clocks where the eight fp32 ones of 16x16x4 take 256, and
+// fewer roundings fall on the sum: an instruction adds 32 products to it, not four.  Error against 64 bits in the 2-norm, values
+// N(0,1), fp32 instructions -> this: K 32 1.0e-7 -> 0.4e-7, 64 1.4e-7 -> 0.9e-7, 256 2.9e-7 -> 2.3e-7, 1024 5.7e-7 -> 4.8e-7, 4096
+// 1.14e-6 -> 1.00e-6, without the sums in parts of the smaller tiles, which halve it (2.4e-7 at 1024 and 2048); over 120 drawn products 1.5
+// times smaller on average, at most 1.05 times larger (832x2696x2096, once on the small tile in splits, now on the large).
+//
+// Bound by the matrix instructions, power and the splitting's share of the issue slots: a K tile of 32 takes the 256x128 tile 1.75 us where
+// its instructions take 1.28 at 2.4 GHz (1.60 without the splitting, 1.68 without its LDS writes).  Operands go through registers, split
+// once a workgroup: each wavefront splitting its own fragments would repeat that two to four times.  fp32 instructions (16-byte rows
+// direct to LDS; others through registers) -> this, us: 8192x4096x1024 490 -> 306, 8192x1024x4096 479 -> 286, 4096x1024x8192 490 -> 300,
+// 2048^3 132 -> 87, 1000x1000x1001 36 -> 23, 1024^3 23.2 -> 23.4, 512^3 12.1 -> 10.5; over 60 shapes of 64..16384 by 64..4096 by 64..16384
+// 1.17 times faster on average, up to 15 % slower with K < 200 and a remainder (121x1232x112 6.5 -> 7.4); 40 operator steps 1.12 times
+// faster (0.97 to 1.49).
 #include "gemm_device.h"
 
 namespace qsync {
 
 namespace {
 
-constexpr int kStepK = kRowBytes / 4;      // floats a K tile
-constexpr int kPitch = kStepK + 4;         // floats an LDS row: 16-byte reads of sixteen rows meet all banks
-
-template <int T> constexpr int f32_lds_bytes() { return 2 * 2 * T * kPitch * 4 + (2 * T + 4) * 4; }
-
-template <int T, bool SPLIT>
-__global__ __launch_bounds__(256) void gemm_f32_any_kernel(const GemmKernelArgs p, int64_t K, int splits)
+struct F32Split
 {
-    constexpr int F = T / 64, R = T / 8;      // fragments of a wavefront each way; rows of an operand a lane loads
-    extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
-    float* const stages = reinterpret_cast<float*>(lds);                       // [stage][A, B][row][kPitch]
-    float* const colp   = stages + 2 * 2 * T * kPitch;
-    const int    tid = threadIdx.x, lane = tid % kWaveSize, wave = __builtin_amdgcn_readfirstlane(tid / kWaveSize);
-    const int    row = lane % 32, half = lane / 32, wm = wave / 2, wn = wave % 2;
-    int          split, tm, tn;
-    item_of_block(static_cast<int>(blockIdx.x), p.tiles_m, p.tiles_n, SPLIT ? splits : 1, p.group_m, split, tm, tn);
-    const int64_t m0 = static_cast<int64_t>(tm) * T, n0 = static_cast<int64_t>(tn) * T;
-    const int64_t first = static_cast<int64_t>(split) * p.ktiles_per_split * kStepK;
-    const int64_t end   = SPLIT && first + static_cast<int64_t>(p.ktiles_per_split) * kStepK < K ? first + static_cast<int64_t>(p.ktiles_per_split) * kStepK : K;
-    const int     tiles = end > first ? static_cast<int>((end - first + kStepK - 1) / kStepK) : 0;
-    const float   alpha = *(p.s0 ? p.s0 : &g_one) * *(p.s1 ? p.s1 : &g_one);
-    const uint32_t seen = p.amax_bits ? __hip_atomic_load(p.amax_bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
-    if constexpr(!SPLIT)
-        for(int c = tid; c < T; c += 256)
-        {
-            const int64_t n = n0 + c < p.N ? n0 + c : p.N - 1;
-            colp[c]     = p.col_scale ? p.col_scale[n] : 1.0f;
-            colp[T + c] = p.col_bias ? p.col_bias[n] : 0.0f;
-        }
+    typedef float acc_t;
+    typedef v4f32 accv_t;
+    static constexpr int kElemBytes = 4, kRows = 16;
+};
+typedef __bf16 v8bf16 __attribute__((ext_vector_type(8)));
+typedef __bf16 v2bf16 __attribute__((ext_vector_type(2)));
+typedef float  v2f32 __attribute__((ext_vector_type(2)));
+typedef float  v4f32_any __attribute__((ext_vector_type(4), aligned(4)));     // 16 bytes of a row that starts on any float
 
-    // rows past the last one load that row again (their outputs are never stored); K indices past the end give zeros
-    const float*  A = reinterpret_cast<const float*>(p.A) + m0 * K;
-    const float*  B = reinterpret_cast<const float*>(p.B) + n0 * K;
-    const int     last_a = static_cast<int>(p.M - m0 < T ? p.M - m0 : T) - 1, last_b = static_cast<int>(p.N - n0 < T ? p.N - n0 : T) - 1;
-    const int     lk = tid % kStepK, lr = tid / kStepK;
-    float         a[R], b[R];
-    auto load = [&](int t) {
-        const int64_t k  = first + static_cast<int64_t>(t) * kStepK + lk;
-        const int64_t at = k < end ? k : 0;
-#pragma unroll
-        for(int i = 0; i < R; ++i)
-        {
-            const int     ra = lr + 8 * i < last_a ? lr + 8 * i : last_a, rb = lr + 8 * i < last_b ? lr + 8 * i : last_b;
-            a[i] = A[ra * K + at];
-            b[i] = B[rb * K + at];
-        }
-    };
-    auto put = [&](int t) {      // (the values are first looked at here: the loads are in flight under a K tile's instructions)
-        const bool in  = first + static_cast<int64_t>(t) * kStepK + lk < end;
-        float*     dst = stages + t % 2 * (2 * T * kPitch) + lr * kPitch + lk;
-#pragma unroll
-        for(int i = 0; i < R; ++i)
-        {
-            dst[8 * i * kPitch]              = in ? a[i] : 0.0f;
-            dst[T * kPitch + 8 * i * kPitch] = in ? b[i] : 0.0f;
-        }
-    };
-    v16f32 acc[F][F];
-#pragma unroll
-    for(int i = 0; i < F; ++i)
-#pragma unroll
-        for(int j = 0; j < F; ++j)
-#pragma unroll
-            for(int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
-    if(tiles > 0)
-    {
-        load(0);
-        put(0);
-    }
-    __syncthreads();
-    for(int t = 0; t < tiles; ++t)
-    {
-        if(t + 1 < tiles) load(t + 1);
-        const float* sa = stages + (t % 2) * (2 * T * kPitch) + (wm * (T / 2) + row) * kPitch;
-        const float* sb = stages + (t % 2) * (2 * T * kPitch) + T * kPitch + (wn * (T / 2) + row) * kPitch;
-#pragma unroll
-        for(int c = 0; c < kStepK; c += 4)
-        {   // K ascending: an instruction takes K index c + e of the lower half's lanes, then c + e + 1 of the upper's
-            float fa[F][2], fb[F][2];
-#pragma unroll
-            for(int i = 0; i < F; ++i)
-            {
-                const float4 va = *reinterpret_cast<const float4*>(sa + i * 32 * kPitch + c), vb = *reinterpret_cast<const float4*>(sb + i * 32 * kPitch + c);
-                fa[i][0] = half ? va.y : va.x; fa[i][1] = half ? va.w : va.z;
-                fb[i][0] = half ? vb.y : vb.x; fb[i][1] = half ? vb.w : vb.z;
-            }
-#pragma unroll
-            for(int e = 0; e < 2; ++e)
-#pragma unroll
-                for(int i = 0; i < F; ++i)
-#pragma unroll
-                    for(int j = 0; j < F; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fb[j][e], fa[i][e], acc[i][j], 0, 0, 0);
-        }
-        if(t + 1 < tiles) put(t + 1);      // (read last before the barrier that ended the turn before this one)
-        __syncthreads();
-    }
-    store_tile<F32Rows32, T, T, 2, 2, T * kPitch * 4, SPLIT>(p, acc, lds, colp, m0, n0, split, alpha, 0.0f, seen);
+constexpr int kStepK    = kRowBytes / 4;     // floats a K tile: one matrix instruction deep
+// LDS bytes of one part of 16 rows, in the order of the instruction's operand: row r, K indices 8 q to 8 q + 7 at 16 bytes times
+// (r ^ 2 q) + 16 q.  Reads and writes are free of bank conflicts (with r ^ 4 q half of the LDS cycles were conflicts, 8192x1024x4096 303 -> 300 us).
+constexpr int kPlane    = 1024;
+constexpr int kFragment = 3 * kPlane;
+
+template <int BM, int BN> constexpr int f32_lds_bytes() { return 2 * (BM + BN) / 16 * kFragment + 2 * BN * 4 + 128; }
+
+// Two values as three pairs of bf16 parts.  `rest` collects the bits behind the third part's: none, down to 2^-110 (the parts of
+// anything smaller would have bits below those of a bf16 number).
+__device__ __forceinline__ void split2(float x0, float x1, uint32_t mask, uint32_t& hi, uint32_t& mid, uint32_t& lo, uint32_t& rest)
+{
+    hi             = __builtin_amdgcn_perm(__float_as_uint(x1), __float_as_uint(x0), 0x07060302u);
+    const float r0 = x0 - __uint_as_float(__float_as_uint(x0) & mask), r1 = x1 - __uint_as_float(__float_as_uint(x1) & mask);
+    mid            = __builtin_bit_cast(uint32_t, __builtin_convertvector((v2f32){r0, r1}, v2bf16));
+    const float    s0 = r0 - __uint_as_float(mid << 16), s1 = r1 - __uint_as_float(mid & mask);
+    const uint32_t u0 = __float_as_uint(s0), u1 = __float_as_uint(s1);
+    lo   = __builtin_amdgcn_perm(u1, u0, 0x07060302u);
+    asm volatile("v_or3_b32 %0, %0, %1, %2" : "+v"(rest) : "v"(u0), "v"(u1));      // (here: gathered up later, both would stay in registers)
 }
 
-template <int T> hipError_t launch_any(const GemmKernelArgs& a, int64_t K, int splits, hipStream_t st)
+template <int BM, int BN, int WGM, int WGN, int D, bool SPLIT>
+__global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm_f32_kernel(const GemmKernelArgs p, int64_t K, int splits)
 {
-    const dim3 grid(static_cast<unsigned>(a.tiles_m) * static_cast<unsigned>(a.tiles_n) * static_cast<unsigned>(splits));
-    constexpr int kLds = f32_lds_bytes<T>();
+    constexpr int kThreads = 64 * WGM * WGN, FM = BM / WGM / 16, FN = BN / WGN / 16;
+    constexpr int kStage = (BM + BN) / 16 * kFragment;
+    // sums of so many K tiles are added up apart where there are registers for both (fewer roundings fall on a long sum)
+    constexpr bool kFold = D > 1;
+    constexpr int  kFoldSteps = 8;
+    constexpr int U = (BM + BN) * 4 / kThreads, kUnitRows = kThreads / 4;      // pieces of eight floats that a thread brings to a stage
+    static_assert((BM + BN) * 4 % kThreads == 0 && BM % kUnitRows == 0 && BN % kUnitRows == 0, "a thread's piece is of A or of B in every thread");
+    extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
+    float* const    colp  = reinterpret_cast<float*>(lds + 2 * kStage);        // [2][BN], eight slots of the maximum, eight flags
+    uint32_t* const flags = reinterpret_cast<uint32_t*>(colp + 2 * BN) + 16;
+    const int       tid = threadIdx.x, lane = tid % kWaveSize, wave = __builtin_amdgcn_readfirstlane(tid / kWaveSize);
+    const int       wm = wave / WGN, wn = wave % WGN, q = lane / 16, fr = lane % 16;
+    int             which, tm, tn;
+    item_of_block(static_cast<int>(blockIdx.x), p.tiles_m, p.tiles_n, SPLIT ? splits : 1, p.group_m, which, tm, tn);
+    const int64_t  m0 = static_cast<int64_t>(tm) * BM, n0 = static_cast<int64_t>(tn) * BN;
+    const int64_t  first = static_cast<int64_t>(which) * p.ktiles_per_split * kStepK;
+    const int64_t  end   = SPLIT && first + static_cast<int64_t>(p.ktiles_per_split) * kStepK < K ? first + static_cast<int64_t>(p.ktiles_per_split) * kStepK : K;
+    const int      tiles = end > first ? static_cast<int>((end - first + kStepK - 1) / kStepK) : 0;
+    const float    alpha = *(p.s0 ? p.s0 : &g_one) * *(p.s1 ? p.s1 : &g_one);
+    const float    code_inv = *(!SPLIT && p.codes ? p.code_inv : &g_one);
+    static_assert(BN <= kThreads, "a column's parameters to a thread");
+    float scale = 1.0f, bias = 0.0f;      // of column n0 + tid
+    if constexpr(!SPLIT)
+    {
+        const int64_t n = n0 + tid < p.N ? n0 + tid : p.N - 1;
+        if(p.col_scale) scale = p.col_scale[n];
+        if(p.col_bias) bias = p.col_bias[n];
+    }
+
+    // rows past the last one load that row again (their outputs are never stored); K indices past the end give zeros
+    const float* const A = reinterpret_cast<const float*>(p.A);
+    const float* const B = reinterpret_cast<const float*>(p.B);
+    const float *      row[U], *src[U];
+    uint32_t           put_at[U];
+#pragma unroll
+    for(int i = 0; i < U; ++i)
+    {
+        const int     line = tid / 4 + i * kUnitRows, g = tid % 4;
+        const bool    is_a = i * kUnitRows < BM;
+        const int64_t at = is_a ? m0 + line : n0 + line - BM, last = (is_a ? p.M : p.N) - 1;
+        row[i]    = (is_a ? A : B) + (at < last ? at : last) * K;
+        src[i]    = row[i] + first + 8 * g;
+        put_at[i] = static_cast<uint32_t>(line / 16 * kFragment + ((line % 16 ^ 2 * g) + 16 * g) * 16);
+    }
+    // whole K tiles, D of them on their way in registers; behind the last one it is loaded again (and not looked at)
+    const int whole = tiles > 0 ? static_cast<int>((end - first) / kStepK) : 0;
+    float     raw[D][U][8];
+    uint32_t  rest = 0u, mask = 0xFFFF0000u;
+    asm volatile("" : "+s"(mask));      // (a scalar register: the instructions that use it are half as long)
+    auto load = [&](auto set, int i, int t) {
+        const v4f32_any lo = *reinterpret_cast<const v4f32_any*>(src[i]), hi = *reinterpret_cast<const v4f32_any*>(src[i] + 4);
+#pragma unroll
+        for(int e = 0; e < 4; ++e) { raw[decltype(set)::value][i][e] = lo[e]; raw[decltype(set)::value][i][4 + e] = hi[e]; }
+        src[i] += t + 1 < whole ? kStepK : 0;
+    };
+    // The partial K tile that ends the row: every float by itself, behind the row's end the last one of it.  (Requested in front of the
+    // other tiles it is no faster, 60 shapes 1.170 instead of 1.174 times the fp32 instructions' rate.)
+    auto load_tail = [&]() {
+        const int64_t at   = first + static_cast<int64_t>(whole) * kStepK + 8 * (tid % 4);
+        const int64_t mine = end - at;
+#pragma unroll
+        for(int i = 0; i < U; ++i)
+#pragma unroll
+            for(int e = 0; e < 8; ++e)
+            {
+                const float v = row[i][at + e < K ? at + e : K - 1];
+                raw[0][i][e]  = e < mine ? v : 0.0f;
+            }
+    };
+    v4u32 part[3];
+    auto split = [&](auto set, int i, int e) {
+        uint32_t hi, mid, lo;
+        split2(raw[decltype(set)::value][i][2 * e], raw[decltype(set)::value][i][2 * e + 1], mask, hi, mid, lo, rest);
+        part[0][e] = hi; part[1][e] = mid; part[2][e] = lo;
+    };
+    auto put = [&](int i, int t) {
+        uint8_t* dst = lds + (t & 1) * kStage + put_at[i];
+#pragma unroll
+        for(int s = 0; s < 3; ++s) *reinterpret_cast<v4u32*>(dst + s * kPlane) = part[s];
+    };
+    v4f32 acc[FM][FN];
+#pragma unroll
+    for(int i = 0; i < FM; ++i)
+#pragma unroll
+        for(int j = 0; j < FN; ++j) acc[i][j] = v4f32{0.0f, 0.0f, 0.0f, 0.0f};
+    v4f32 total[kFold ? FM : 1][kFold ? FN : 1];
+    if constexpr(kFold)
+#pragma unroll
+        for(int i = 0; i < FM; ++i)
+#pragma unroll
+            for(int j = 0; j < FN; ++j) total[i][j] = v4f32{0.0f, 0.0f, 0.0f, 0.0f};
+    const uint32_t read_at = static_cast<uint32_t>(((fr ^ 2 * q) + 16 * q) * 16);
+    // The products of a row of fragments, smallest parts first; a column part's registers are free again for the next K tile behind
+    // the last row's 1st, 3rd and 6th.
+    constexpr int kA[6] = {0, 1, 0, 2, 1, 0}, kB[6] = {2, 1, 1, 0, 0, 0};
+    constexpr int kSlots = 6 * FM, kMeet = kSlots - 6, kPer = (kMeet - 2) / U;
+    v8bf16        b[FN][3], a[2][3];
+    auto read_b = [&](auto s, const uint8_t* stage) {
+#pragma unroll
+        for(int j = 0; j < FN; ++j) b[j][decltype(s)::value] = *reinterpret_cast<const v8bf16*>(stage + read_at + (BM / 16 + wn * FN + j) * kFragment + decltype(s)::value * kPlane);
+    };
+    auto read_a = [&](auto i, auto s, const uint8_t* stage) {
+        a[decltype(i)::value % 2][decltype(s)::value] = *reinterpret_cast<const v8bf16*>(stage + read_at + (wm * FM + decltype(i)::value) * kFragment + decltype(s)::value * kPlane);
+    };
+    constexpr std::integral_constant<int, 0> c0{};
+    constexpr std::integral_constant<int, 1> c1{};
+    constexpr std::integral_constant<int, 2> c2{};
+    // One K tile's products.  Between those of all rows but the last: the next tile's parts into the other stage, the loads of a later one,
+    // of a piece as soon as its registers are free, and the next row's fragments.  Then the workgroup meets, and between the last
+    // row's products the next tile's first fragments are read.
+    enum { kAll, kNoLoads, kLast };
+    auto step = [&](auto mode, auto set, int t) {
+        constexpr int        MODE = decltype(mode)::value;
+        const uint8_t* const cur = lds + (t & 1) * kStage;
+        const uint8_t* const nxt = lds + (~t & 1) * kStage;
+        read_b(c0, cur);
+        static_for<kSlots>([&](auto slot) {
+            constexpr int sl = decltype(slot)::value, i = sl / 6, s = sl % 6, u = sl / kPer, at = sl % kPer;
+            if constexpr(sl == kMeet && MODE != kLast) wg_barrier();
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for(int j = 0; j < FN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[j][kB[s]], a[i % 2][kA[s]], acc[i][j], 0, 0, 0);
+            if constexpr(i + 1 < FM && s < 3) read_a(std::integral_constant<int, i + 1>{}, std::integral_constant<int, s>{}, cur);
+            if constexpr(u < U && MODE != kLast)
+            {
+                static_for<4>([&](auto e) {
+                    if constexpr(decltype(e)::value * kPer / 4 == at) split(set, u, decltype(e)::value);
+                });
+                if constexpr(at == kPer - 1)
+                {
+                    put(u, t + 1);
+                    if constexpr(MODE == kAll) load(set, u, t + 1 + D);
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            if constexpr(MODE != kLast)
+            {
+                if constexpr(sl == kMeet) { read_a(c0, c0, nxt); read_b(c2, nxt); }
+                if constexpr(sl == kMeet + 1) read_a(c0, c1, nxt);
+                if constexpr(sl == kMeet + 2) { read_b(c1, nxt); read_a(c0, c2, nxt); }
+            }
+        });
+    };
+    auto put_first = [&]() {
+#pragma unroll
+        for(int i = 0; i < U; ++i)
+        {
+#pragma unroll
+            for(int e = 0; e < 4; ++e) split(c0, i, e);
+            put(i, 0);
+            if(whole > 0) load(c0, i, D);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        wg_barrier();
+        read_a(c0, c0, lds);
+        read_b(c2, lds);
+        read_a(c0, c1, lds);
+        read_b(c1, lds);
+        read_a(c0, c2, lds);
+    };
+    constexpr std::integral_constant<int, kAll>     all{};
+    constexpr std::integral_constant<int, kNoLoads> no_loads{};
+    constexpr std::integral_constant<int, kLast>    last_one{};
+    if(whole > 0)
+    {
+        static_for<D>([&](auto c) {
+#pragma unroll
+            for(int i = 0; i < U; ++i) load(c, i, decltype(c)::value);
+            __builtin_amdgcn_sched_barrier(0);
+        });
+        put_first();
+        // (straight-line, no way from one of the D steps to another's place: the compiler then knows which load each of its waits is for)
+        int t = 0, since = 0;
+        for(; t + D < whole; t += D)
+        {
+            static_for<D>([&](auto c) { step(all, std::integral_constant<int, (decltype(c)::value + 1) % D>{}, t + decltype(c)::value); });
+            if constexpr(kFold)
+                if((since += D) >= kFoldSteps)
+                {
+                    since = 0;
+#pragma unroll
+                    for(int i = 0; i < FM; ++i)
+#pragma unroll
+                        for(int j = 0; j < FN; ++j)
+                        {
+                            total[i][j] += acc[i][j];
+                            acc[i][j] = v4f32{0.0f, 0.0f, 0.0f, 0.0f};
+                        }
+                }
+        }
+        static_for<D - 1>([&](auto c) {
+            if(t + 1 < whole)
+            {
+                step(all, std::integral_constant<int, (decltype(c)::value + 1) % D>{}, t);
+                ++t;
+            }
+        });
+        if(whole < tiles)
+        {
+            load_tail();
+            step(no_loads, c0, t);
+            ++t;
+        }
+        step(last_one, c0, t);
+        if constexpr(kFold)
+#pragma unroll
+            for(int i = 0; i < FM; ++i)
+#pragma unroll
+                for(int j = 0; j < FN; ++j) acc[i][j] += total[i][j];
+    }
+    else if(tiles > 0)
+    {
+        load_tail();
+        put_first();
+        step(last_one, c0, 0);
+    }
+    if constexpr(!SPLIT)
+        if(tid < BN)
+        {
+            colp[tid]      = scale;
+            colp[BN + tid] = bias;
+        }
+
+    // Sums that are not finite, and those with operands that three bf16 numbers do not hold, are formed again by the fp32 instructions.  An
+    // infinite value is a NaN in its lower parts, so it shows in every sum that it is part of.
+    bool again = (rest & 0xFFFFu) != 0u;
+#pragma unroll
+    for(int i = 0; i < FM; ++i)
+#pragma unroll
+        for(int j = 0; j < FN; ++j)
+#pragma unroll
+            for(int e = 0; e < 4; ++e) again |= !(fabsf(acc[i][j][e]) < __builtin_inff());
+    const bool any = __any(again);
+    if(lane == 0) flags[wave] = any ? 1u : 0u;
+    __syncthreads();
+    uint32_t redo = 0u;
+#pragma unroll
+    for(int w = 0; w < WGM * WGN; ++w) redo |= flags[w];
+    if(__builtin_amdgcn_readfirstlane(static_cast<int>(redo)))
+    {
+#pragma unroll
+        for(int i = 0; i < FM; ++i)
+#pragma unroll
+            for(int j = 0; j < FN; ++j) acc[i][j] = v4f32{0.0f, 0.0f, 0.0f, 0.0f};
+        // (a lane's four K indices of sixteen, of both operands in the same order)
+        const float *ra[FM], *rb[FN];
+#pragma unroll
+        for(int i = 0; i < FM; ++i)
+        {
+            const int64_t at = m0 + wm * (BM / WGM) + 16 * i + fr;
+            ra[i] = A + (at < p.M ? at : p.M - 1) * K;
+        }
+#pragma unroll
+        for(int j = 0; j < FN; ++j)
+        {
+            const int64_t at = n0 + wn * (BN / WGN) + 16 * j + fr;
+            rb[j] = B + (at < p.N ? at : p.N - 1) * K;
+        }
+        auto fetch = [&](v4f32 (&fa)[FM], v4f32 (&fb)[FN], int64_t k) {
+            if(k + 16 <= end)
+            {
+#pragma unroll
+                for(int i = 0; i < FM; ++i) fa[i] = *reinterpret_cast<const v4f32_any*>(ra[i] + k + 4 * q);
+#pragma unroll
+                for(int j = 0; j < FN; ++j) fb[j] = *reinterpret_cast<const v4f32_any*>(rb[j] + k + 4 * q);
+            }
+            else
+#pragma unroll
+                for(int e = 0; e < 4; ++e)
+                {
+                    const bool in = k + 4 * q + e < end;
+#pragma unroll
+                    for(int i = 0; i < FM; ++i) fa[i][e] = in ? ra[i][k + 4 * q + e] : 0.0f;
+#pragma unroll
+                    for(int j = 0; j < FN; ++j) fb[j][e] = in ? rb[j][k + 4 * q + e] : 0.0f;
+                }
+        };
+        v4f32 fa[FM], fb[FN], ga[FM], gb[FN];
+        fetch(fa, fb, first);
+#pragma unroll 1
+        for(int64_t k = first; k < end; k += 16)
+        {
+            fetch(ga, gb, k + 16);
+#pragma unroll
+            for(int e = 0; e < 4; ++e)
+#pragma unroll
+                for(int i = 0; i < FM; ++i)
+#pragma unroll
+                    for(int j = 0; j < FN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[j][e], fa[i][e], acc[i][j], 0, 0, 0);
+#pragma unroll
+            for(int i = 0; i < FM; ++i) fa[i] = ga[i];
+#pragma unroll
+            for(int j = 0; j < FN; ++j) fb[j] = gb[j];
+        }
+    }
+    const uint32_t seen = (!SPLIT && p.amax_bits && wave == 0) ? __hip_atomic_load(p.amax_bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+    store_tile<F32Split, BM, BN, WGM, WGN, 2 * kStage / (WGM * WGN) / 16 * 16, SPLIT>(p, acc, lds, colp, m0, n0, which, alpha, code_inv, seen);
+}
+
+template <int BM, int BN, int WGM, int WGN, int D> hipError_t launch_tile_f32(const GemmKernelArgs& a, int64_t K, int splits, hipStream_t st)
+{
+    const dim3 grid(static_cast<unsigned>(a.tiles_m) * static_cast<unsigned>(a.tiles_n) * static_cast<unsigned>(splits)), block(64 * WGM * WGN);
+    constexpr int kLds = f32_lds_bytes<BM, BN>();
     static bool   attr_set[16] = {};      // per instantiation and device; benign if set twice
     int           dev = 0;
     const bool    known = hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < 16;
     if(!known || !attr_set[dev])
     {
-        const void* const kernels[] = {reinterpret_cast<const void*>(&gemm_f32_any_kernel<T, false>), reinterpret_cast<const void*>(&gemm_f32_any_kernel<T, true>)};
+        const void* const kernels[] = {reinterpret_cast<const void*>(&gemm_f32_kernel<BM, BN, WGM, WGN, D, false>), reinterpret_cast<const void*>(&gemm_f32_kernel<BM, BN, WGM, WGN, D, true>)};
         for(const void* k : kernels)
         {
             const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
@@ -130,31 +372,40 @@ template <int T> hipError_t launch_any(const GemmKernelArgs& a, int64_t K, int s
         }
         if(known) attr_set[dev] = true;
     }
-    if(splits > 1) gemm_f32_any_kernel<T, true><<<grid, dim3(256), kLds, st>>>(a, K, splits);
-    else           gemm_f32_any_kernel<T, false><<<grid, dim3(256), kLds, st>>>(a, K, 1);
+    if(splits > 1) gemm_f32_kernel<BM, BN, WGM, WGN, D, true><<<grid, block, kLds, st>>>(a, K, splits);
+    else           gemm_f32_kernel<BM, BN, WGM, WGN, D, false><<<grid, block, kLds, st>>>(a, K, 1);
     return hipGetLastError();
 }
 
 }  // namespace
 
-// The plan's tile (256: on 128) and K splits; the partial products of more than one are left to the caller.
+// The plan's tile and K splits; the partial products of more than one are left to the caller.
 hipError_t launch_gemm_f32(const GemmProblem& p, const GemmPlan& plan, void* workspace, hipStream_t stream)
 {
-    const int     T = plan.tile == 2 ? 64 : 128, splits = plan.splits < 1 ? 1 : plan.splits;
-    const int64_t ktiles = (p.K + kStepK - 1) / kStepK, per = (ktiles + splits - 1) / splits;
-    GemmKernelArgs a{};
+    const TileShape ts = gemm_tile_shape(32, plan.tile);
+    const int       splits = plan.splits < 1 ? 1 : plan.splits;
+    const int64_t   ktiles = (p.K + kStepK - 1) / kStepK, per = (ktiles + splits - 1) / splits;
+    GemmKernelArgs  a{};
     a.A = static_cast<const uint8_t*>(p.A);
     a.B = static_cast<const uint8_t*>(p.B);
     a.M = p.M; a.N = p.N;
     a.C = p.C; a.c_is_f16 = p.c_dtype == kF16;
     a.s0 = p.s0; a.s1 = p.s1; a.col_scale = p.col_scale; a.col_bias = p.col_bias;
     a.partial   = workspace;
-    a.amax_bits = splits > 1 ? nullptr : p.out_amax_bits;
+    a.amax_bits = splits > 1 ? nullptr : p.out_amax_bits;      // with K splits the reduction pass takes the maximum and writes the codes
+    a.codes     = splits > 1 ? nullptr : static_cast<int8_t*>(p.out_codes);
+    a.code_inv  = p.out_code_inv;
+    a.code_qmax = p.out_code_qmax;
     a.ktiles_per_split = static_cast<int>(per < 1 ? 1 : per);
-    a.tiles_m = static_cast<int>((p.M + T - 1) / T);
-    a.tiles_n = static_cast<int>((p.N + T - 1) / T);
+    a.tiles_m = static_cast<int>((p.M + ts.bm - 1) / ts.bm);
+    a.tiles_n = static_cast<int>((p.N + ts.bn - 1) / ts.bn);
     a.group_m = kGroupM;
-    return T == 64 ? launch_any<64>(a, p.K, splits, stream) : launch_any<128>(a, p.K, splits, stream);
+    switch(plan.tile)
+    {
+    case 0: return launch_tile_f32<256, 128, 4, 2, 1>(a, p.K, splits, stream);
+    case 1: return launch_tile_f32<128, 128, 2, 4, 2>(a, p.K, splits, stream);
+    default: return launch_tile_f32<64, 64, 2, 2, 2>(a, p.K, splits, stream);
+    }
 }
 
 }  // namespace qsync

@@ -475,13 +475,11 @@ __device__ __forceinline__ void gemm_tile(const GemmKernelArgs& p, int lin, int 
         constexpr int f = decltype(ft)::value, c = decltype(ct)::value;
         __builtin_amdgcn_sched_barrier(0);           // fences: the matrix instructions stay behind the wait in front of them
 #pragma unroll
-        for(int k = 0; k < TR::kSteps; ++k)
-#pragma unroll
-            for(int jj = 0; jj < FN; ++jj)
-            {
-                const int j = f % 2 ? FN - 1 - jj : jj;
-                acc[f][j]   = TR::mfma(bf[c][j], af[ROLL ? 0 : c][f], acc[f][j], k);
-            }
+        for(int jj = 0; jj < FN; ++jj)
+        {
+            const int j = f % 2 ? FN - 1 - jj : jj;
+            acc[f][j]   = TR::mfma(bf[c][j], af[ROLL ? 0 : c][f], acc[f][j]);
+        }
         __builtin_amdgcn_sched_barrier(0);
     };
 
@@ -502,9 +500,7 @@ __device__ __forceinline__ void gemm_tile(const GemmKernelArgs& p, int lin, int 
     // int8 59.1 -> 53.0, binary16 112 -> 101, 16384x4096x1024 79.4 -> 75.1 and 132 -> 124; 8192^3 2.55 -> 2.84 POP/s and 1.28 -> 1.42
     // PFLOP/s; on zeros, i.e. at the full clock, within 2 % of the same times.  The smaller tiles are not bound by power, and gain
     // little: 128 tile, 4096x3072x768 int8 14.9 -> 15.3, binary16 24.5 -> 24.8 (256 tile 15.8 -> 15.6, 23.0 -> 22.1); 64 tile, 2048x2048x1024
-    // binary16 14.4 -> 14.1, 1808x1040x784 int8 7.42 -> 7.37, 64x64x6144 in splits 8.69 -> 8.67.  fp32 8192x4096x1024, whose
-    // instructions are 16x16x4 in place of 32x32x2: 256 tile 493.6 -> 489.4, 128 tile 496.6 -> 492.1, 64 tile 524.9 -> 530.6; over 160
-    // products and backward passes of 64..16384 by 64..4096 as planned 0.4 % faster.
+    // binary16 14.4 -> 14.1, 1808x1040x784 int8 7.42 -> 7.37, 64x64x6144 in splits 8.69 -> 8.67.
     // The column scales and biases of this tile are fetched by direct loads as well, in front of the first K tile, and
     // wait in LDS behind the stages for the epilogue.
     // The direct loads of a K tile are not requested by all wavefronts at once.  A compute unit takes such an
@@ -1129,7 +1125,6 @@ __global__ __launch_bounds__(kThreads) void splitk_reduce_kernel(const ACC* __re
     }
 }
 
-struct TileShape { int bm, bn; };
 // 0: 256x256, 8 wavefronts (2x4, 128x64 each)   1: 128x128, 8 wavefronts (2x4, 64x32 each)
 // 2: 64x64, 4 wavefronts (2x2, 32x32 each)
 // (What follows was measured on 32x32 instructions.)
@@ -1192,8 +1187,7 @@ hipError_t launch_traits(int tile, const GemmKernelArgs& a, int splits, hipStrea
     // The 128x128 tile where every compute unit gets one workgroup at most (with a second one resident, two stages,
     // its K loop fills the gaps):
     //   four stages and four loading wavefronts, three stages -> this, us: 4096x768x3072 (192 workgroups) int8 16.4 -> 14.6,
-    //   binary16 25.1 -> 22.6; 2048x2048x1536 int8 9.9 -> 9.3, 1024x512x2048 10.5 -> 9.6; fp32, bound by its instructions, stays as
-    //   it is (33 products: 0.98 to 1.015).
+    //   binary16 25.1 -> 22.6; 2048x2048x1536 int8 9.9 -> 9.3, 1024x512x2048 10.5 -> 9.6.
     //   Their start costs 0.3 us, a K tile less gains 0.05 to 0.12: 8 K tiles int8 7.33 -> 7.30, 6 lose (7.6 -> 7.8), 2 lose 5 %.
     //   Contiguous rows that straddle the 128-byte lines (two lines a piece) keep the loaders the bound: 4096x768x3088 int8 18.4 ->
     //   18.9.  A row-major stage row is 128 or 256 bytes of a longer operand row, for which that matters less: they take any row length.
@@ -1278,14 +1272,16 @@ void set_gemm_tile_override(int tile) { g_tile_override = (tile >= 0 && tile < k
 static thread_local int g_persistent_mode = -1;   // 1: whenever eligible; anything else: never (the default, see launch_gemm)
 void set_gemm_persistent_mode(int mode) { g_persistent_mode = (mode == 0 || mode == 1) ? mode : -1; }
 
+// fp32 operands: 0 is 256x128 (gemm_f32.hip)
+TileShape gemm_tile_shape(int prec, int tile) { return prec == 32 && tile == 0 ? TileShape{256, 128} : kTiles[tile]; }
+
 // Model of a tile shape's time; the constants are explained in plan_gemm.
 struct TileModel { double r1, rmax, ovh, cap; int occ; };
 static constexpr TileModel kTileModel[kNumTiles] = {{14.0, 15.8, 7.5, 2280.0, 1}, {8.3, 9.0, 4.2, 1900.0, 2}, {3.55, 5.48, 3.2, 2060.0, 4}};
-// fp32: the matrix instructions bound every tile alike (19.7 in these units), so rates lie close together and the smaller tile's finer
-// grain decides; fitted to 70 shapes of 64..16384 by 64..4096, timed on the three tiles of 32x32x2 instructions: 2.5 % behind the best
-// on average, before, with the constants above, 10-13 %; 2652x440x1912 84 -> 57 us, 968x1288x2140 89 -> 63, 14828x552x380 108 -> 72.  On 70
-// others 1.9 % (7 %).  On the present tiles 0.7 % over 100 shapes, 13 % at most (7132x1876x72).
-static constexpr TileModel kTileModelF32[kNumTiles] = {{14.5, 16.3, 7.5, 4300.0, 1}, {14.3, 16.2, 4.2, 4300.0, 2}, {11.5, 15.3, 3.2, 4300.0, 4}};
+// fp32: an LDS stage of three bf16 parts leaves room for one workgroup of the larger tiles on a unit, three of the small one.  Fitted to
+// 146 shapes of 64..16384 by 64..4096 by 64..8192, each tile with one and more K splits, replayed from a graph: the choice is 0.5 % behind
+// the best on average, 18 % at most (3120x3508x72).
+static constexpr TileModel kTileModelF32[kNumTiles] = {{37.3, 37.3, 8.4, 7520.0, 1}, {29.5, 29.5, 6.4, 6410.0, 1}, {14.9, 19.5, 5.1, 5400.0, 3}};
 // Row-major (TN) operands: a K tile takes twice the LDS fragment reads, and a 64-wide tile of int8 operands
 // loads 64-byte row pieces (binary16: 128 bytes, no penalty); fitted slow-down of the main loop per tile shape.
 static double tn_factor(int tile, int prec, bool tn)
@@ -1304,10 +1300,11 @@ GemmPlan plan_gemm(int prec, int64_t M, int64_t N, int64_t K, int force_tile, in
     GemmPlan plan{1, 1, 0, 0.0};
     if(M <= 0 || N <= 0) return plan;
     const int64_t kb     = K * (prec == 8 ? 1 : (prec == 16 ? 2 : 4));
-    // a K tile of fp32 operands takes the matrix cores eight times as long as one of int8 or binary16 operands
+    // (the unit of fp32's constants: what a K tile of fp32 operands took on the fp32 instructions)
     const double  kwork  = prec == 32 ? 8.0 : 1.0;
     const int64_t ktiles = (kb + kRowBytes - 1) / kRowBytes;
-    auto ntiles = [&](int t) { return ((M + kTiles[t].bm - 1) / kTiles[t].bm) * ((N + kTiles[t].bn - 1) / kTiles[t].bn); };
+    auto shape  = [&](int t) { return gemm_tile_shape(prec, t); };
+    auto ntiles = [&](int t) { return ((M + shape(t).bm - 1) / shape(t).bm) * ((N + shape(t).bn - 1) / shape(t).bn); };
     // Plan = (tile, K splits) with the smallest estimated time.  The estimate is a small model fitted to gfx950
     // measurements of these tiles on 32x32 instructions (int8 and binary16, forward, row-major and transposed weight-gradient
     // forms: 54 operands x 3 tiles, replayed from a graph; rms error 11 %; fp32 operands have constants of their own).  It knows
@@ -1320,19 +1317,22 @@ GemmPlan plan_gemm(int prec, int64_t M, int64_t N, int64_t K, int force_tile, in
     //   shared caches, do not each reach `rmax`); every round of co-resident workgroups costs `ovh` us of launch, first-load latency
     //   and epilogue (the 256 tile's: fitted 6.9, raised to 7.5 for few K tiles: int8 9856 x 1920 x 176, fp32 output, 256
     //   tile 28.5 us, 128 tile 21.5; 49 of 6000 shapes drawn over the same range change, 18 % faster on average); split K adds its reduction pass.
-    const double    cus = 256.0;
+    const double     cus = 256.0;
+    const TileModel* models = prec == 32 ? kTileModelF32 : kTileModel;
+    const int64_t    least = prec == 32 ? 4 : 8;      // K tiles of a split: one of fp32 operands is 0.5 us and more
     auto estimate = [&](int t, int64_t s) {
-        const TileModel& m    = (prec == 32 ? kTileModelF32 : kTileModel)[t];
+        const TileModel& m    = models[t];
         const double     tnf  = tn_factor(t, prec, tn);
         const double     wgs  = static_cast<double>(ntiles(t)) * static_cast<double>(s);
         const double     per  = std::ceil(wgs / cus);                                    // workgroups of the busiest unit
         const double     share = per < m.occ ? per : m.occ;                              // co-resident ones
         const double     rate = (m.r1 * share < m.rmax ? m.r1 * share : m.rmax) * tnf;
         const double     kt   = std::ceil(static_cast<double>(ktiles) / static_cast<double>(s));
-        const double     mop  = 2.0 * kTiles[t].bm * kTiles[t].bn * kRowBytes * 1e-6 * kwork;    // per K tile (int8 ops)
+        const double     mop  = 2.0 * shape(t).bm * shape(t).bn * kRowBytes * 1e-6 * kwork;    // per K tile (int8 ops)
         const double     unit = per * kt * mop / rate, chip = wgs * kt * mop / (m.cap * tnf);
         double           us   = (unit > chip ? unit : chip) + m.ovh * std::ceil(wgs / (cus * m.occ));
-        if(s > 1) us += 4.0 + static_cast<double>(s + 1) * static_cast<double>(M) * static_cast<double>(N) * 4.0 / 6.24e6;
+        // (the parts' way to memory and back; fp32's was fitted together with its other constants)
+        if(s > 1) us += (prec == 32 ? 1.9 : 4.0) + (prec == 32 ? 2.7 : 1.0) * static_cast<double>(s + 1) * static_cast<double>(M) * static_cast<double>(N) * 4.0 / 6.24e6;
         return us;
     };
     // Candidates: no split, and the split counts that fill the units once, twice or up to their co-residency.  Tiles are
@@ -1350,14 +1350,14 @@ GemmPlan plan_gemm(int prec, int64_t M, int64_t N, int64_t K, int force_tile, in
         if(allow_split && !(force_tile >= 0 && force_splits < 0))
             for(int f = 0; f < 3; ++f)
             {
-                const int64_t fill = f == 0 ? 256 : (f == 1 ? 512 : 256 * kTileModel[t].occ);
-                if(fill > 256 * kTileModel[t].occ) continue;
+                const int64_t fill = f == 0 ? 256 : (f == 1 ? 512 : 256 * models[t].occ);
+                if(fill > 256 * models[t].occ) continue;
                 int64_t       s    = fill / ntiles(t);
-                if(s > ktiles / 8) s = ktiles / 8;                // keep at least 8 K tiles per split
+                if(s > ktiles / least) s = ktiles / least;
                 if(s > 128) s = 128;
                 if(s >= 2 && s != cand[ncand - 1]) cand[ncand++] = s;
             }
-        const double area = static_cast<double>(ntiles(t)) * kTiles[t].bm * kTiles[t].bn;
+        const double area = static_cast<double>(ntiles(t)) * shape(t).bm * shape(t).bn;
         for(int c = 0; c < ncand; ++c)
         {
             const double us     = estimate(t, cand[c]);
@@ -1468,8 +1468,7 @@ hipError_t launch_gemm(const GemmProblem& p, const GemmPlan& plan, void* workspa
     if(p.M <= 0 || p.N <= 0) return hipSuccess;
     if(p.prec == 32 && (p.conv_H > 0 || p.b_remap_C > 0)) return hipErrorInvalidValue;
     const int splits = plan.splits < 1 ? 1 : plan.splits;
-    // 16-byte pieces to LDS need 16-byte aligned, 16-byte multiple operand rows; any other fp32 operands go through registers
-    if(p.prec == 32 && ((p.K * 4) % 16 != 0 || ((reinterpret_cast<uintptr_t>(p.A) | reinterpret_cast<uintptr_t>(p.B)) & 15) != 0))
+    if(p.prec == 32)
     {
         const hipError_t e = launch_gemm_f32(p, plan, workspace, stream);
         return e != hipSuccess || splits == 1 ? e : reduce_splits(p, splits, workspace, stream, fold);
@@ -1497,9 +1496,8 @@ hipError_t launch_gemm(const GemmProblem& p, const GemmPlan& plan, void* workspa
     if(!p.tn && persistent_eligible(a, p.prec, plan.tile, splits)
        && g_persistent_mode == 1)
         return p.prec == 8 ? launch_persistent<I8Traits>(a, stream) : launch_persistent<F16Traits>(a, stream);
-    hipError_t e = p.prec == 8    ? launch_traits<I8Traits>(plan.tile, a, splits, stream, p.tn)
-                   : p.prec == 16 ? launch_traits<F16Traits>(plan.tile, a, splits, stream, p.tn)
-                                  : launch_traits<F32Traits>(plan.tile, a, splits, stream);
+    hipError_t e = p.prec == 8 ? launch_traits<I8Traits>(plan.tile, a, splits, stream, p.tn)
+                               : launch_traits<F16Traits>(plan.tile, a, splits, stream, p.tn);
     return e != hipSuccess || splits == 1 ? e : reduce_splits(p, splits, workspace, stream, fold);
 }
 

@@ -163,6 +163,8 @@ struct GemmPlan {
     size_t  workspace;     // bytes needed for split-K partials
     double  us;            // estimated time
 };
+struct TileShape { int bm, bn; };
+TileShape gemm_tile_shape(int prec, int tile);
 // force_tile / force_splits < 0 leave the choice to the heuristic; tn: plan for GemmProblem::tn operands.
 GemmPlan plan_gemm(int prec, int64_t M, int64_t N, int64_t K, int force_tile = -1, int force_splits = -1,
                    bool allow_split = true, bool tn = false);

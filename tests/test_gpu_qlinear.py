@@ -476,6 +476,63 @@ def test_fp32_operands_that_are_no_16_byte_rows(M, N, K):
             Q.qsync_debug_set_gemm_tile(-1)
 
 
+@pytest.mark.parametrize("tile", [0, 1, 2])
+@pytest.mark.parametrize("K", [0, 1, 8, 31, 32, 33, 64, 65, 96, 127, 128, 161, 300])
+def test_fp32_products_around_the_k_tiles(tile, K):
+    """The fp32 tiles with one K tile, a remainder alone or behind whole ones, and as many K tiles as are on their way at once, at the
+    edges of 256x128, 128x128 and 64x64 outputs; products of integers below 2^11, whose parts and sums are exact, bit for bit."""
+    rng = np.random.default_rng(K)
+    Q.qsync_debug_set_gemm_tile(tile)
+    try:
+        for M, N in ((1, 1), (63, 129), (64, 64), (257, 128), (130, 200)):
+            say("fp32 K tiles", tile, M, N, K)
+            a, b = rng.integers(-2047, 2048, (M, K)).astype(np.float32), rng.integers(-15, 16, (N, K)).astype(np.float32)
+            bias = rng.integers(-99, 99, N).astype(np.float32)
+            y = torch.full((M, N), float("nan"), device="cuda")
+            w = torch.empty(max(256, Q.qsync_qlinear_workspace_bytes(Q.FP32, M, N, K)), dtype=torch.uint8, device="cuda")
+            at = lambda v: dev(v) if K else torch.ones(1, device="cuda")      # (an empty tensor has no address)
+            Q.qsync_qlinear_fwd(Q.FP32, M, N, K, at(a), None, at(b), None, Q.PER_TENSOR, dev(bias), y, None, w)
+            assert_bits_equal(host(y), (a.astype(np.float64) @ b.astype(np.float64).T + bias).astype(np.float32), "Y")
+    finally:
+        Q.qsync_debug_set_gemm_tile(-1)
+
+
+@pytest.mark.parametrize("tile", [0, 1, 2])
+@pytest.mark.parametrize("K", [40, 64, 128])
+def test_fp32_products_of_values_that_have_no_three_parts(tile, K):
+    """Infinities, NaN, sums that overflow and operands down to the smallest denormal: as the fp32 instructions give them.  One nonzero
+    a row makes every finite product exact."""
+    M, N = 130, 70
+    a, b = np.zeros((M, K), np.float32), np.zeros((N, K), np.float32)
+    a[np.arange(M), np.arange(M) % K] = 1.0 + np.arange(M) * np.float32(2.0 ** -23) * 3
+    b[:, :] = np.float32(2.0) ** (np.arange(N) % 5)[:, None]
+    a[3, 5] = np.inf
+    a[70, 6] = -np.inf
+    a[7, 9] = np.nan
+    a[11] = 0.0
+    a[11, 2] = a[11, 3] = np.float32(3.0e38)
+    a[12] = 0.0
+    a[12, K - 1] = np.finfo(np.float32).max
+    for m, e in ((20, -112), (21, -126), (22, -130), (23, -149)):
+        a[m] = 0.0
+        a[m, K - 2] = np.ldexp(np.float64(0xABCDEF if e > -127 else 3), e - (23 if e > -127 else 0)).astype(np.float32)
+    b[1] *= np.float32(2.0 ** 100)
+    b[2] *= np.float32(0.25)
+    with np.errstate(over="ignore", invalid="ignore"):
+        want = np.stack([(a.astype(np.float64) * b[n].astype(np.float64)).sum(1) for n in range(N)], 1)      # (inf * 0 is none here)
+        want = want.astype(np.float32)
+    assert np.isinf(want).any() and np.isnan(want).any() and ((want != 0) & (np.abs(want) < 1e-38)).any()
+    Q.qsync_debug_set_gemm_tile(tile)
+    try:
+        say("fp32 values without parts", tile, K)
+        y = torch.full((M, N), 7.0, device="cuda")
+        w = torch.empty(max(256, Q.qsync_qlinear_workspace_bytes(Q.FP32, M, N, K)), dtype=torch.uint8, device="cuda")
+        Q.qsync_qlinear_fwd(Q.FP32, M, N, K, dev(a), None, dev(b), None, Q.PER_TENSOR, None, y, None, w)
+        np.testing.assert_array_equal(host(y), want)
+    finally:
+        Q.qsync_debug_set_gemm_tile(-1)
+
+
 def test_bias_gradient_from_the_backward_call():
     """db requested from qsync_qlinear_bwd itself (not from the fused absmax pass)."""
     case = wl.ragged_case(208, 144, 80, seed=31, dtype=np.float16)
