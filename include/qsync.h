@@ -81,7 +81,7 @@ typedef enum {
  *           this is the bias gradient db (paper: Appendix, proof of Prop. 1, gradient of a linear
  *           operator), obtained without reading dY a third time.
  * sumsq_opt out, one float or NULL; PER_TENSOR only.  When given, the same pass also yields the squared
- *           Euclidean norm sum x[r,c]^2 (fp32 per lane and block, block results folded in double in block
+ *           Euclidean norm sum x[r,c]^2 (fp32 per lane and block, block results folded in double in a fixed
  *           order): with amax it is what the variance indicator needs from a tensor (paper: Indicator
  *           section, Prop. 3: norms, scaling factors and effective bits "collected through profiling").
  * workspace scratch of at least qsync_absmax_workspace_bytes(rows, cols, gran) bytes, 16-byte aligned.

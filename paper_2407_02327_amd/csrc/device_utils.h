@@ -18,7 +18,7 @@ __device__ __forceinline__ float wave_reduce_max(float v)
     return v;
 }
 
-__device__ __forceinline__ float wave_reduce_sum(float v)
+template <typename F> __device__ __forceinline__ F wave_reduce_sum(F v)
 {
 #pragma unroll
     for(int off = kWaveSize / 2; off > 0; off >>= 1) v += __shfl_xor(v, off, kWaveSize);
@@ -41,7 +41,7 @@ __device__ __forceinline__ float block_reduce_max(float v, float* lds /* >= 16 f
 }
 
 // Block-wide sum in a fixed order (wave shuffles, then the wave sums in order); valid in thread 0.
-__device__ __forceinline__ float block_reduce_sum(float v, float* lds /* >= 16 floats */)
+template <typename F> __device__ __forceinline__ F block_reduce_sum(F v, F* lds /* >= 16 */)
 {
     v = wave_reduce_sum(v);
     const int lane = threadIdx.x % kWaveSize, wave = threadIdx.x / kWaveSize;

@@ -115,35 +115,6 @@ template <typename T> struct RunSq
     __device__ __forceinline__ void add_scalar(T x) { const float v = to_f32(x); s = fmaf(v, v, s); }
 };
 
-// The last block folds the per-block sums of squares in block order, in double.  The first `cap`
-// partials are fetched by the whole block into LDS, any further ones straight from memory.
-__device__ __forceinline__ void fold_sumsq(const float* partial_sq, unsigned int nblocks, float* sumsq, double* lds_d,
-                                           unsigned int cap)
-{
-    for(unsigned int i = threadIdx.x; i < nblocks && i < cap; i += blockDim.x)
-        lds_d[i] = static_cast<double>(__hip_atomic_load(partial_sq + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-    __syncthreads();
-    if(threadIdx.x == 0)
-    {
-        // (sixteen LDS reads in flight per batch: one at a time, every addition waited out an LDS round trip)
-        double             t = 0.0;
-        const unsigned int n = nblocks < cap ? nblocks : cap;
-        unsigned int       i = 0;
-        for(; i + 16 <= n; i += 16)
-        {
-            double v[16];
-#pragma unroll
-            for(int k = 0; k < 16; ++k) v[k] = lds_d[i + k];
-#pragma unroll
-            for(int k = 0; k < 16; ++k) t += v[k];
-        }
-        for(; i < n; ++i) t += lds_d[i];
-        for(; i < nblocks; ++i)
-            t += static_cast<double>(__hip_atomic_load(partial_sq + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-        *sumsq = static_cast<float>(t);
-    }
-}
-
 // ------------------------------------------------------------------ arrival counter
 // The per-tensor maximum finishes inside one launch: every block publishes its partial maximum,
 // then takes a ticket from an arrival counter; the block that draws the last ticket folds the
@@ -187,8 +158,8 @@ __global__ __launch_bounds__(BLOCK) void absmax_tensor_kernel(const T* __restric
                                                               float* inv_scale, float* amax_opt, float* partial_sq,
                                                               float* sumsq_opt)
 {
-    __shared__ float  lds[16];
-    __shared__ double lds_d[1024];
+    __shared__ float  lds[32];
+    __shared__ double lds_d[16];
     __shared__ bool   flag;
     RunMax<T>         rm;
     RunSq<T>          sq;                 // only when sumsq_opt is given
@@ -239,19 +210,26 @@ __global__ __launch_bounds__(BLOCK) void absmax_tensor_kernel(const T* __restric
     if(threadIdx.x == 0) st_partial(partial + blockIdx.x, m);
     if(want_sq)
     {
-        __syncthreads();
-        const float bs = block_reduce_sum(sq.s, lds);
+        const float bs = block_reduce_sum(sq.s, lds + 16);
         if(threadIdx.x == 0) st_partial(partial_sq + blockIdx.x, bs);
     }
     if(!ctr) return;
     if(!last_arrival(ctr, gridDim.x, &flag)) return;
+    // (Both partials of a block requested together, the sums of squares added up by all threads in a fixed order: by one thread in block
+    // order, behind the maxima, 16384x4096 binary16 40.0 -> 32.6 us with cold inputs between other passes.)
+    float  mm = 0.0f;
+    double d  = 0.0;
+    for(int i = threadIdx.x; i < static_cast<int>(gridDim.x); i += BLOCK)
+    {
+        const float pm = ld_partial(partial + i), ps = want_sq ? ld_partial(partial_sq + i) : 0.0f;
+        mm = fmaxf(mm, pm);
+        d += static_cast<double>(ps);
+    }
     if(want_sq)
     {
-        fold_sumsq(partial_sq, gridDim.x, sumsq_opt, lds_d, 1024u);
-        __syncthreads();
+        d = block_reduce_sum(d, lds_d);
+        if(threadIdx.x == 0) *sumsq_opt = static_cast<float>(d);
     }
-    float mm = 0.0f;
-    for(int i = threadIdx.x; i < static_cast<int>(gridDim.x); i += BLOCK) mm = fmaxf(mm, ld_partial(partial + i));
     mm = block_reduce_max(mm, lds);
     if(threadIdx.x == 0)
     {
@@ -515,12 +493,21 @@ __global__ __launch_bounds__(kBlock) void colreduce_finalize_kernel(const float*
     if constexpr(OP == OP_SUMMAX)
         if(blockIdx.x == gridDim.x - 1)
         {
-            __shared__ double lds_d[kAbsmaxMaxBlocks];
+            __shared__ double lds_d[16];
             float             mm = 0.0f;
-            for(int i = threadIdx.x; i < nmax; i += kBlock) mm = fmaxf(mm, partial_max[i]);
+            double            d  = 0.0;
+            for(int i = threadIdx.x; i < nmax; i += kBlock)
+            {
+                mm = fmaxf(mm, partial_max[i]);
+                if(fin.sumsq_opt) d += static_cast<double>(fin.partial_sq[i]);
+            }
             mm = block_reduce_max(mm, lds);
             if(threadIdx.x == 0) write_scale(mm, fin.qmax, fin.scale, fin.inv_scale, fin.amax_opt, 0);
-            if(fin.sumsq_opt) fold_sumsq(fin.partial_sq, static_cast<unsigned int>(nmax), fin.sumsq_opt, lds_d, kAbsmaxMaxBlocks);
+            if(fin.sumsq_opt)
+            {
+                d = block_reduce_sum(d, lds_d);
+                if(threadIdx.x == 0) *fin.sumsq_opt = static_cast<float>(d);
+            }
             return;
         }
     const int     tc = threadIdx.x % 16, q = threadIdx.x / 16;
@@ -1173,6 +1160,32 @@ template <typename T, int RND, int SRC> struct QuantizeStream
     }
 };
 
+// The code of element i by itself
+template <typename T> __device__ __forceinline__ int8_t code_of(float v, float f, int qmax, int rnd, uint64_t seed, uint64_t offset, int64_t i)
+{
+    if(rnd == kStochastic)
+    {
+        const uint4 blk = philox_group(seed, offset, static_cast<uint64_t>(i) >> 3);
+        return static_cast<int8_t>(quantize_code<kStochastic>(v, f, qmax, philox_draw16(blk, static_cast<int>(i & 7))));
+    }
+    return static_cast<int8_t>(rnd == kFloor ? quantize_code<kFloor>(v, f, qmax, 0u) : quantize_code<kNearest>(v, f, qmax, 0u));
+}
+
+// QuantizeStream of any number of elements: those behind the last whole group one to a thread.  A group is 8 consecutive elements of the
+// contiguous tensor, whatever its rows are: odd row lengths used to go an element per thread (8524x2955 binary16, stochastic,
+// with its maximum and dequantization 108 -> 48 us)
+template <typename T, int RND> struct QuantizeStreamAny : QuantizeStream<T, RND, kInv>
+{
+    int tail;
+    __device__ __forceinline__ void run(uint32_t block, uint8_t* lds) const
+    {
+        QuantizeStream<T, RND, kInv>::run(block, lds);
+        const int64_t i = this->ngroups * 8 + threadIdx.x;
+        if(block == 0 && static_cast<int>(threadIdx.x) < tail)
+            this->q[i] = code_of<T>(to_f32(this->x[i]), *this->ts.inv, this->qmax, RND, this->seed, this->offset, i);
+    }
+};
+
 // Any shape, any alignment: one element per thread.
 template <typename T>
 __global__ __launch_bounds__(kBlock) void quantize_generic_kernel(const T* __restrict__ x, int64_t rows, int64_t cols,
@@ -1188,18 +1201,9 @@ __global__ __launch_bounds__(kBlock) void quantize_generic_kernel(const T* __res
         const int64_t r = i / cols, c = i - r * cols;
         const float   f = inv_scale[gran == kPerTensor ? 0 : (gran == kPerRow ? r : c)];
         const float   v = to_f32(x[r * ld + c]);
-        int           code;
-        if(rnd == kStochastic)
-        {
-            const uint4 blk = philox_group(seed, offset, static_cast<uint64_t>(i) >> 3);
-            code            = quantize_code<kStochastic>(v, f, qmax, philox_draw16(blk, static_cast<int>(i & 7)));
-        }
-        else if(rnd == kFloor)
-            code = quantize_code<kFloor>(v, f, qmax, 0u);
-        else
-            code = quantize_code<kNearest>(v, f, qmax, 0u);
-        if(q) q[i] = static_cast<int8_t>(code);
-        if(qT) qT[c * rows + r] = static_cast<int8_t>(code);
+        const int8_t  code = code_of<T>(v, f, qmax, rnd, seed, offset, i);
+        if(q) q[i] = code;
+        if(qT) qT[c * rows + r] = code;
     }
 }
 
@@ -1702,6 +1706,43 @@ __global__ __launch_bounds__(kBlock) void dequantize_cols_kernel(const Ti* __res
     }
 }
 
+// Contiguous int8 codes with one scale, any row length: vectors of 16 OUTPUT bytes, so that a wavefront's store is 1 KB of consecutive
+// memory.  Bound by HBM.  With 16 codes to a thread a store instruction filled every other 16 bytes: 16384x4096 to binary16 43.8 -> 32.4 us
+// (6.2 TB/s) inside a maximum + quantize + dequantize sequence, with streaming stores from 2^24 elements on (an output that the
+// L2s do not hold anyway; 35.9 without); 10740x1569 from an element a thread.
+template <typename To, int U, bool STREAM>
+__global__ __launch_bounds__(kBlock) void dequantize_flat_kernel(const int8_t* __restrict__ a, int64_t n, float ts_host,
+                                                                 const float* __restrict__ ts_dev, To* __restrict__ y)
+{
+    constexpr int V = 16 / sizeof(To);
+    typedef typename std::conditional<V == 8, uint2, uint32_t>::type in_t;
+    const float   ts = ts_dev ? ts_host * ts_dev[0] : ts_host;
+    const int64_t nvec = n / V, i0 = static_cast<int64_t>(blockIdx.x) * (kBlock * U) + threadIdx.x;
+    in_t          raw[U];
+#pragma unroll
+    for(int u = 0; u < U; ++u)
+    {
+        const int64_t i = i0 + u * kBlock < nvec ? i0 + u * kBlock : nvec - 1;      // (past the end the last one again, not stored)
+        raw[u]          = reinterpret_cast<const in_t*>(a)[i];
+    }
+#pragma unroll
+    for(int u = 0; u < U; ++u)
+    {
+        const int64_t i = i0 + u * kBlock;
+        if(i >= nvec) break;
+        alignas(8) int8_t in[V];
+        *reinterpret_cast<in_t*>(in) = raw[u];
+        alignas(16) To out[V];
+#pragma unroll
+        for(int e = 0; e < V; ++e) out[e] = scaled_code<To>(static_cast<float>(in[e]), ts, 0.0f, false);
+        typedef unsigned v4u __attribute__((ext_vector_type(4)));
+        if constexpr(STREAM) __builtin_nontemporal_store(*reinterpret_cast<const v4u*>(out), reinterpret_cast<v4u*>(y) + i);
+        else                 reinterpret_cast<v4u*>(y)[i] = *reinterpret_cast<const v4u*>(out);
+    }
+    const int64_t rest = nvec * V + threadIdx.x;
+    if(blockIdx.x == 0 && rest < n) y[rest] = scaled_code<To>(static_cast<float>(a[rest]), ts, 0.0f, false);
+}
+
 int next_pow2(int64_t v)
 {
     int p = 1;
@@ -2013,6 +2054,13 @@ static hipError_t quantize_typed(const T* x, int64_t rows, int64_t cols, int64_t
         const TensorScale ts{inv, nullptr, 0, nullptr, nullptr, nullptr};
         quantize_tensor_launch<T, kInv>(x, rows, cols, ld, qmax, rnd, seed, offset, ts, q, qT, st);
     }
+    else if(gran == kPerTensor && q && !qT && ld == cols && rows * cols >= 8 && rows * cols < (int64_t(1) << 40) && aligned16(x) && (reinterpret_cast<uintptr_t>(q) & 7) == 0)
+        with_rounding(rnd, [&](auto r) {      // (any row length)
+            const int64_t     ngroups = rows * cols / 8;
+            const TensorScale ts{inv, nullptr, 0, nullptr, nullptr, nullptr};
+            launch_part(QuantizeStreamAny<T, decltype(r)::value>{{x, ngroups, qmax, seed, offset, ts, q}, static_cast<int>(rows * cols % 8)},
+                        (ngroups + kBlock * 4 - 1) / (kBlock * 4), st);
+        });
     else if(fast && gran != kPerTensor)
         with_rounding(rnd, [&](auto r) {
             quantize_patch_launch<T, decltype(r)::value>(x, rows, cols, ld, qmax, gran, seed, offset, inv, q, qT, st);
@@ -2402,6 +2450,24 @@ template <typename Ti, typename To>
 static hipError_t dequantize_typed(const void* a, int64_t rows, int64_t cols, int64_t ld, const float* rs,
                                    const float* cs, float ts, const float* tsd, const float* cb, void* y, hipStream_t st)
 {
+    if constexpr(std::is_same<Ti, int8_t>::value)
+    {
+        constexpr int V = 16 / sizeof(To);
+        const int64_t n = rows * cols;
+        if(ld == cols && !rs && !cs && !cb && n >= V && aligned16(y) && reinterpret_cast<uintptr_t>(a) % V == 0)
+        {
+            auto go = [&](auto u, auto stream) {
+                constexpr int U = decltype(u)::value;
+                const int64_t nb = (n / V + kBlock * U - 1) / (kBlock * U);
+                dequantize_flat_kernel<To, U, decltype(stream)::value><<<dim3(static_cast<unsigned>(nb)), dim3(kBlock), 0, st>>>(
+                    static_cast<const int8_t*>(a), n, ts, tsd, static_cast<To*>(y));
+            };
+            if(n < (int64_t(1) << 20)) go(std::integral_constant<int, 1>{}, std::false_type{});
+            else if(n < (int64_t(1) << 24)) go(std::integral_constant<int, 4>{}, std::false_type{});
+            else go(std::integral_constant<int, 8>{}, std::true_type{});
+            return hipGetLastError();
+        }
+    }
     constexpr int V16 = 16 / sizeof(Ti);
     const bool    wide = cols % V16 == 0 && (ld * sizeof(Ti)) % 16 == 0 && aligned16(a) && aligned16(y)
                       && (!cs || aligned16(cs)) && (!cb || aligned16(cb));

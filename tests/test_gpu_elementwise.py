@@ -358,6 +358,47 @@ def test_dequantize(adt, ydt):
     assert_close(host(y), a[:, 4:44] * 0.5, "dequantize strided")
 
 
+@pytest.mark.parametrize("ydt", [np.float32, np.float16])
+@pytest.mark.parametrize("rows,cols", [(1, 3), (1, 4), (1, 8), (3, 5), (1, 1023), (255, 8), (257, 31), (1, (1 << 20) - 1), (1, 1 << 20), (1025, 1031), (4099, 4093),
+                                       (4096, 4096)])
+def test_dequantize_contiguous_codes_of_any_length(ydt, rows, cols):
+    """Contiguous int8 codes with one scale, around a vector, a workgroup and the sizes where more vectors go to a thread; at addresses
+    that are vectors and that are not: bits of the oracle's single rounding."""
+    rng = np.random.default_rng(rows * cols)
+    a = rng.integers(-127, 128, size=(rows, cols)).astype(np.int8)
+    scale = np.float32(0.0123456789)
+    want = orc.dequantize(a, float(scale), out_dtype=ydt)
+    for off_a, off_y in ((0, 0), (1, 0), (4, 0), (0, 1)):
+        say("dequantize flat", ydt.__name__, rows, cols, off_a, off_y)
+        src = torch.zeros(rows * cols + off_a, dtype=torch.int8, device="cuda")
+        src[off_a:] = dev(a.reshape(-1))
+        y = torch.full((rows * cols + off_y + 8,), 7.0, dtype=TORCH[ydt], device="cuda")
+        Q.qsync_dequantize(src[off_a:], rows, cols, cols, None, None, 1.0, None, y[off_y:], tensor_scale_dev_opt=dev(np.array([scale])))
+        assert_bits_equal(host(y)[off_y:off_y + rows * cols].reshape(rows, cols), want, "dequantize")
+        assert (host(y)[:off_y] == 7.0).all() and (host(y)[off_y + rows * cols:] == 7.0).all()
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float16])
+@pytest.mark.parametrize("rnd", ["nearest", "stochastic", "floor"])
+@pytest.mark.parametrize("rows,cols", [(1, 7), (1, 8), (1, 9), (3, 5), (5, 3), (91, 11), (1, 8191), (8193, 1), (1024, 9), (33, 999)])
+def test_quantize_contiguous_rows_of_any_length(dtype, rnd, rows, cols):
+    """Codes of a contiguous tensor whose rows are no multiple of eight, around a group and a workgroup's groups, at addresses that are
+    vectors and that are not: bits of the oracle."""
+    rng = np.random.default_rng(rows + cols)
+    x = _data(rng, (rows, cols), dtype, 0.7)
+    _, io = orc.scales_from_amax(orc.absmax(x, "tensor"))
+    want = orc.quantize_int(x, io, "tensor", rnd, 77, (1 << 64) - 3)
+    codes = {"nearest": Q.ROUND_NEAREST, "stochastic": Q.ROUND_STOCHASTIC, "floor": Q.ROUND_FLOOR}[rnd]
+    for off_x, off_q in ((0, 0), (1, 0), (0, 3)):
+        say("quantize flat", dtype.__name__, rnd, rows, cols, off_x, off_q)
+        src = torch.zeros(rows * cols + off_x, dtype=TORCH[dtype], device="cuda")
+        src[off_x:] = dev(x.reshape(-1))
+        q = torch.full((rows * cols + off_q + 8,), 99, dtype=torch.int8, device="cuda")
+        Q.qsync_quantize(src[off_x:], rows, cols, cols, Q.INT8, 8, Q.PER_TENSOR, codes, 77, (1 << 64) - 3, dev(io), q[off_q:], None)
+        assert_bits_equal(host(q)[off_q:off_q + rows * cols].reshape(rows, cols), want, "codes")
+        assert (host(q)[:off_q] == 99).all() and (host(q)[off_q + rows * cols:] == 99).all()
+
+
 def test_dequantize_to_binary16_rounds_the_exact_product_once():
     """int8 codes times one binary32 scale, binary16 output: the result is the exact product rounded once, bit
     for bit, also on inputs where rounding to binary32 first would give the other neighbour."""
