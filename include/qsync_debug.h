@@ -49,9 +49,13 @@ void qsync_debug_set_gemm_persistent(int mode);
 /*
  * qsync_debug_last_gradient_pair - for tests: how the calling thread's last qsync_qlinear_bwd, qsync_qlinear_bwd_rm or
  * qsync_qlinear_bwd_fp16_of_int8 that passed its argument checks ran its GEMMs: the tile shape (numbered as above) on
- * which data and weight gradient shared one launch, or -1 when they were launched apart or only one was asked for.
+ * which data and weight gradient shared one launch, both of them whole, or -1 when they were launched apart, one of them was in K
+ * splits or only one was asked for.
+ * qsync_debug_last_gradient_splits - of the same call: the K splits in which the longer contraction was where they shared one launch
+ * (1: whole), or 0 when they did not.
  */
 int qsync_debug_last_gradient_pair(void);
+int qsync_debug_last_gradient_splits(void);
 
 #ifdef __cplusplus
 }

@@ -13,6 +13,7 @@ namespace {
 
 thread_local int g_last_hip_error = 0;
 thread_local int g_last_pair_tile = -1;      // see qsync_debug_last_gradient_pair
+thread_local int g_last_pair_splits = 0;     // see qsync_debug_last_gradient_splits
 
 int hip_status(hipError_t e)
 {
@@ -81,12 +82,13 @@ int run_gradients(const GemmProblem* dx, const GemmPlan& plan_dx, void* ws_dx, c
                      || overlap(fold.out, n, p->s0, 4) || overlap(fold.out, n, p->s1, 4) || overlap(fold.out, n, p->col_scale, p->N * 4));
     };
     const bool beside = fold.out && !touches(dx) && !touches(dw);
-    const int  pair   = dx && dw ? gradient_pair_tile(*dx, plan_dx, *dw, plan_dw) : -1;
-    g_last_pair_tile  = pair;
+    const GradientPair pair = dx && dw ? gradient_pair(*dx, plan_dx, *dw, plan_dw) : GradientPair{};
+    g_last_pair_tile   = pair.splits == 1 ? pair.tile : -1;
+    g_last_pair_splits = pair.tile >= 0 ? pair.splits : 0;
     int rc = QSYNC_OK;
-    if(pair >= 0)
+    if(pair.tile >= 0)
     {
-        rc = hip_status(launch_gradient_pair(*dx, *dw, pair, beside ? fold : ColumnFoldArgs{}, st));
+        rc = hip_status(launch_gradient_pair(*dx, ws_dx, *dw, ws_dw, pair, beside ? fold : ColumnFoldArgs{}, st));
         if(beside) fold = ColumnFoldArgs{};
     }
     else
@@ -804,6 +806,7 @@ int qsync_probe_mfma(int tag, int random_operands, int iters, void* out, double*
 void qsync_debug_set_gemm_tile(int tile) { set_gemm_tile_override(tile); }
 void qsync_debug_set_gemm_persistent(int mode) { set_gemm_persistent_mode(mode); }
 int qsync_debug_last_gradient_pair(void) { return g_last_pair_tile; }
+int qsync_debug_last_gradient_splits(void) { return g_last_pair_splits; }
 
 static int conv3x3_fwd_impl(int tag, int64_t nimg, int64_t H, int64_t W, int64_t C, int64_t N, const void* xq,
                             const float* sx, const void* wq, const float* sw, int wgran, const float* bias_opt, void* y,

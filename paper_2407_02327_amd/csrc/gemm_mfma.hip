@@ -126,9 +126,12 @@ __device__ __forceinline__ void dma_sequence_short(std::integer_sequence<int, Ds
 // that the lanes of one access pass touch all banks once.  Everything behind the fragments
 // (matrix instructions, epilogue, split K) is shared with the NT form.  Kb is the contraction length P here.
 // `lin` is the workgroup's index among the `splits` x tiles workgroups of the problem.
-template <typename TR, int BM, int BN, int WGM, int WGN, int ST, int NL, bool SPLIT, bool CONV, bool TN>
-__device__ __forceinline__ void gemm_tile(const GemmKernelArgs& p, int lin, int splits)
+// MIXED: whether the workgroup leaves raw sums (its problem is in K splits) is known at run time only (`raw`).
+template <typename TR, int BM, int BN, int WGM, int WGN, int ST, int NL, bool SPLIT, bool CONV, bool TN, bool MIXED = false>
+__device__ __forceinline__ void gemm_tile(const GemmKernelArgs& p, int lin, int splits, bool raw = SPLIT)
 {
+    static_assert(!MIXED || SPLIT, "one body for both");
+    constexpr bool WHOLE = !SPLIT || MIXED;      // the epilogue may be this workgroup's
     static_assert(!(SPLIT && CONV && !TN), "the implicit patch matrix of the forward is not combined with split K");
     static_assert(!TN || (TR::kElemBytes <= 2 && BM == BN && BM >= 64), "TN: int8 or binary16 operands, square tiles");
     constexpr bool CONVA  = CONV && !TN;       // NT form: the A operand is the implicit patch matrix (forward, data gradient)
@@ -368,7 +371,7 @@ __device__ __forceinline__ void gemm_tile(const GemmKernelArgs& p, int lin, int 
     // Nothing in front of the K loop waits for global memory except that wait (a load into a register here would make the
     // compiler drain the queue before its use).
     auto request_first = [&]() {
-        if(!SPLIT && lwave < BN / 64)
+        if(WHOLE && lwave < BN / 64)
         {
             const int64_t c = n0 + lwave * 64 + lane, col = c < p.N ? c : p.N - 1;       // columns past N: any valid one, never stored
             if(p.col_scale) column_param_issue(p.col_scale + col, lds + ST * STAGE_BYTES + lwave * 256);
@@ -519,8 +522,8 @@ __device__ __forceinline__ void gemm_tile(const GemmKernelArgs& p, int lin, int 
     // at once): there the upper half requests behind the first of two rows.
     const bool late_loader = wave >= WC / 2 && (FM > 2 || (!TN && p.Kb % kRowBytes != 0));
     // (scalar loads: in front of the first direct load, used by the epilogue)
-    const float scale0 = *(!SPLIT && p.s0 ? p.s0 : &g_one), scale1 = *(!SPLIT && p.s1 ? p.s1 : &g_one);
-    const float code_inv = *(!SPLIT && p.codes ? p.code_inv : &g_one);
+    const float scale0 = *(WHOLE && p.s0 ? p.s0 : &g_one), scale1 = *(WHOLE && p.s1 ? p.s1 : &g_one);
+    const float code_inv = *(WHOLE && p.codes ? p.code_inv : &g_one);
     if constexpr(NL == 0) request_first();
     // (What the K loop starts from is formed while the first loads are in flight, not behind the wait for them: 4096x3072x768 on the
     // 128 tile int8 15.3 -> 14.8 us)
@@ -652,9 +655,11 @@ __device__ __forceinline__ void gemm_tile(const GemmKernelArgs& p, int lin, int 
     const float    alpha     = scale0 * scale1;
     // (by the wavefront that publishes: loads of the word stand in line with the atomics on it, and with some hundred workgroups that end
     // together the line is what they wait for.  Every wavefront -> one, int8 912x3008x752 28.5 -> 20.4 us, 12896x576x368 24.4 -> 17.3)
-    const uint32_t amax_seen = (!SPLIT && p.amax_bits && wave == 0) ? __hip_atomic_load(p.amax_bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+    const uint32_t amax_seen = (WHOLE && p.amax_bits && wave == 0) ? __hip_atomic_load(p.amax_bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
 
-    store_tile<TR, BM, BN, WGM, WGN, 2 * STAGE_BYTES / (WGM * WGN), SPLIT>(p, acc, lds, colp, m0, n0, split, alpha, code_inv, amax_seen);
+    constexpr int STG = 2 * STAGE_BYTES / (WGM * WGN);
+    if(MIXED ? raw : SPLIT) store_tile<TR, BM, BN, WGM, WGN, STG, true>(p, acc, lds, colp, m0, n0, split, alpha, code_inv, amax_seen);
+    else if constexpr(WHOLE) store_tile<TR, BM, BN, WGM, WGN, STG, false>(p, acc, lds, colp, m0, n0, split, alpha, code_inv, amax_seen);
 }
 
 // (Two wavefronts a SIMD at least, i.e. at most 256 registers each: with more allowed the compiler keeps the accumulators in the other
@@ -673,10 +678,11 @@ struct GemmPairArgs
 {
     GemmKernelArgs g[2];
     int            na, total;      // workgroups of the first, of both; behind them those of the fold
+    int            splits;         // K splits of the first (SPLITA)
     ColumnFoldArgs fold;
 };
 // (No loading wavefronts of their own here: with them 2048x1024x1024 int8 10.1 -> 10.4 us, 2056x1000x1032 binary16 24.8 -> 25.5.)
-template <typename TR, int BM, int BN, int WGM, int WGN, int ST, bool TNA>
+template <typename TR, int BM, int BN, int WGM, int WGN, int ST, bool TNA, bool SPLITA>
 __global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm_nt_pair_kernel(const GemmPairArgs p)
 {
     const int blk = static_cast<int>(blockIdx.x);
@@ -686,10 +692,12 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm_nt_pair_kernel(const G
         fold_columns(p.fold, static_cast<uint32_t>(blk - p.total), reinterpret_cast<float*>(lds));
         return;
     }
-    if constexpr(!TNA)
+    if constexpr(!TNA && !SPLITA)
         gemm_tile<TR, BM, BN, WGM, WGN, ST, 0, false, false, false>(p.g[blk < p.na ? 0 : 1], blk < p.na ? blk : blk - p.na, 1);
+    else if constexpr(!TNA)
+        gemm_tile<TR, BM, BN, WGM, WGN, ST, 0, true, false, false, true>(p.g[blk < p.na ? 0 : 1], blk < p.na ? blk : blk - p.na, blk < p.na ? p.splits : 1, blk < p.na);
     else if(blk < p.na)
-        gemm_tile<TR, BM, BN, WGM, WGN, ST, 0, false, false, TNA>(p.g[0], blk, 1);
+        gemm_tile<TR, BM, BN, WGM, WGN, ST, 0, SPLITA, false, TNA>(p.g[0], blk, p.splits);
     else
         gemm_tile<TR, BM, BN, WGM, WGN, ST, 0, false, false, false>(p.g[1], blk - p.na, 1);
 }
@@ -1213,29 +1221,29 @@ hipError_t launch_traits(int tile, const GemmKernelArgs& a, int splits, hipStrea
     }
 }
 
-template <typename TR, int BM, int BN, int WGM, int WGN, int ST, bool TNA>
-hipError_t launch_pair_tile(const GemmPairArgs& p, int workgroups, hipStream_t st)
+template <typename TR, int BM, int BN, int WGM, int WGN, int ST, bool TNA, bool SPLITA>
+hipError_t launch_pair_tile(const GemmPairArgs& p, hipStream_t st)
 {
     constexpr size_t lds_bytes = ST * static_cast<size_t>(BM + BN) * kRowBytes + 2 * BN * sizeof(float) + 64;
+    const auto       kernel = &gemm_nt_pair_kernel<TR, BM, BN, WGM, WGN, ST, TNA, SPLITA>;
     static bool      attr_set[kMaxDevices] = {};      // per instantiation and device; benign if set twice
     const int        slot = current_device_slot();
     if(slot < 0 || !attr_set[slot])
     {
-        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_nt_pair_kernel<TR, BM, BN, WGM, WGN, ST, TNA>),
-                                                 hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds_bytes));
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds_bytes));
         if(e != hipSuccess) return e;
         if(slot >= 0) attr_set[slot] = true;
     }
-    gemm_nt_pair_kernel<TR, BM, BN, WGM, WGN, ST, TNA><<<dim3(static_cast<unsigned>(workgroups + p.fold.blocks())), dim3(64 * WGM * WGN), lds_bytes, st>>>(p);
+    kernel<<<dim3(static_cast<unsigned>(p.total + p.fold.blocks())), dim3(64 * WGM * WGN), lds_bytes, st>>>(p);
     return hipGetLastError();
 }
-template <typename TR, bool TNA>
-hipError_t launch_pair_traits(int tile, const GemmPairArgs& p, int workgroups, hipStream_t st)
+template <typename TR, bool TNA, bool SPLITA>
+hipError_t launch_pair_traits(int tile, const GemmPairArgs& p, hipStream_t st)
 {
     if(tile == 1)
-        return workgroups <= kNumCu ? launch_pair_tile<TR, 128, 128, 2, 4, 3, TNA>(p, workgroups, st)
-                                    : launch_pair_tile<TR, 128, 128, 2, 4, 2, TNA>(p, workgroups, st);
-    return launch_pair_tile<TR, 64, 64, 2, 2, 2, TNA>(p, workgroups, st);
+        return p.total <= kNumCu ? launch_pair_tile<TR, 128, 128, 2, 4, 3, TNA, SPLITA>(p, st)
+                                 : launch_pair_tile<TR, 128, 128, 2, 4, 2, TNA, SPLITA>(p, st);
+    return launch_pair_tile<TR, 64, 64, 2, 2, 2, TNA, SPLITA>(p, st);
 }
 
 // The persistent kernel serves full 256x256 tiles with binary16 output and nothing optional in the epilogue.
@@ -1535,30 +1543,57 @@ static double unit_time(const TileModel& m, double mop, const double* rounds, in
 // average against the best of the three and more than 10 % in ten cases (binary16 384x1744x1168 left apart, 19.5 us against
 // 14.2, is the worst); it errs towards two launches: the 114 pairs run 1.48 times as fast as apart, the worst of them
 // 2.4 % slower.
-static int pair_tile(const GemmProblem& a, const GemmProblem& b, double separate_us)
+static double pair_us(const GemmProblem& a, const GemmProblem& b, int t, int splits)
 {
     constexpr int kMaxRounds = 16;
+    TileModel m = kTileModel[t];
+    if(a.prec == 16) m.r1 *= t == 1 ? 0.83 : 0.6;       // a long binary16 contraction left over alone, fitted
+    auto tiles  = [&](const GemmProblem& p) { return ((p.M + kTiles[t].bm - 1) / kTiles[t].bm) * ((p.N + kTiles[t].bn - 1) / kTiles[t].bn); };
+    auto ktiles = [&](const GemmProblem& p, int s) { return std::ceil(std::ceil(static_cast<double>(p.K * (p.prec / 8)) / kRowBytes) / s) / tn_factor(t, p.prec, p.tn); };
+    const int64_t wa = tiles(a) * splits, wgs = wa + tiles(b);
+    if(wgs > kMaxRounds * kNumCu) return -1.0;
+    const double ka = ktiles(a, splits), kb = ktiles(b, 1), mop = 2.0 * kTiles[t].bm * kTiles[t].bn * kRowBytes * 1e-6;
+    double rounds[kMaxRounds];
+    int    n = 0;
+    for(int64_t at = 0; at < wgs; at += kNumCu) rounds[n++] = at < wa ? ka : kb;
+    const double unit = unit_time(m, mop, rounds, n), chip = (wa * ka + (wgs - wa) * kb) * mop / m.cap;
+    const double full = std::ceil(static_cast<double>(wgs) / (kNumCu * m.occ));      // rounds of co-resident workgroups
+    const double us   = (unit > chip ? unit : chip) + m.ovh * (full > 1.0 ? full - 0.5 : full);
+    return splits > 1 ? us + 4.0 + static_cast<double>(splits + 1) * static_cast<double>(a.M) * static_cast<double>(a.N) * 4.0 / 6.24e6 : us;
+}
+static int pair_tile(const GemmProblem& a, const GemmProblem& b, double separate_us)
+{
     int    tile = -1;
     double best = 0.93 * separate_us;
     for(int t = 1; t < kNumTiles; ++t)
     {
         if(g_tile_override >= 0 && t != g_tile_override) continue;
-        TileModel m = kTileModel[t];
-        if(a.prec == 16) m.r1 *= t == 1 ? 0.83 : 0.6;       // a long binary16 contraction left over alone, fitted
-        auto tiles  = [&](const GemmProblem& p) { return ((p.M + kTiles[t].bm - 1) / kTiles[t].bm) * ((p.N + kTiles[t].bn - 1) / kTiles[t].bn); };
-        auto ktiles = [&](const GemmProblem& p) { return std::ceil(static_cast<double>(p.K * (p.prec / 8)) / kRowBytes) / tn_factor(t, p.prec, p.tn); };
-        const int64_t wa = tiles(a), wgs = wa + tiles(b);
-        if(wgs > kMaxRounds * kNumCu) continue;
-        const double ka = ktiles(a), kb = ktiles(b), mop = 2.0 * kTiles[t].bm * kTiles[t].bn * kRowBytes * 1e-6;
-        double rounds[kMaxRounds];
-        int    n = 0;
-        for(int64_t at = 0; at < wgs; at += kNumCu) rounds[n++] = at < wa ? ka : kb;
-        const double unit = unit_time(m, mop, rounds, n), chip = (wa * ka + (wgs - wa) * kb) * mop / m.cap;
-        const double full = std::ceil(static_cast<double>(wgs) / (kNumCu * m.occ));      // rounds of co-resident workgroups
-        const double us   = (unit > chip ? unit : chip) + m.ovh * (full > 1.0 ? full - 0.5 : full);
-        if(us < (tile < 0 ? 1.0 : 0.95) * best) { best = us; tile = t; }      // (the smaller tile must win by 5 %)
+        const double us = pair_us(a, b, t, 1);
+        if(us >= 0.0 && us < (tile < 0 ? 1.0 : 0.95) * best) { best = us; tile = t; }      // (the smaller tile must win by 5 %)
     }
     return tile;
+}
+// Where the two would go apart, the first (the longer contraction) in K splits: the tile and the splits, up to as many, on which they share
+// a launch all the same, with the sum of the splits behind it.  Few outputs over a long contraction leave units idle, and the parts of
+// both together fill them: three launches become two.  Over 92 backward passes of 64..16384 by 64..4096 that went apart (both types, both
+// forms, replayed from a graph) 66 share a launch now, all of them 1.18 times as fast on average: binary16 6144x192x768 22.1 -> 15.4 us,
+// 14592x160x336 23.0 -> 17.0, 4096x768x3072 59.8 -> 54.8 (unsplit), int8 15744x2288x112 32.2 -> 22.9, 8576x320x1520 36.6 -> 26.3; the worst
+// 61.0 -> 61.9 (binary16 10624x992x808).  The estimate does not know how the second's contraction drags on over the small tile: with
+// more than 36 K tiles of it the pair may lose (binary16 3200x3656x128 30.7, 39.8 together), nor of gemm_rows_kernel
+// (2112x1696x96 13.0, 20.0).
+static GradientPair split_pair(const GemmProblem& a, const GemmPlan& plan_a, const GemmProblem& b, double separate_us)
+{
+    GradientPair pair;
+    const int64_t kb = (b.K * (b.prec / 8) + kRowBytes - 1) / kRowBytes;
+    if(plan_a.splits < 2 || kb > 36 || g_tile_override >= 0 || gemm_rows_takes(a) || gemm_rows_takes(b)) return pair;
+    double best = separate_us;
+    for(int t = 1; t < kNumTiles; ++t)
+        for(int s = 1; s <= plan_a.splits; ++s)
+        {
+            const double us = pair_us(a, b, t, s);
+            if(us >= 0.0 && us < best) { best = us; pair = GradientPair{t, s}; }
+        }
+    return pair;
 }
 
 // The weight gradient lands in memory that the data gradient reads (a caller that stores dW over the transposed weights or
@@ -1577,36 +1612,49 @@ static bool dw_over_dx_operands(const GemmProblem& dx, const GemmProblem& dw)
         || written(dx.col_scale, dx.N * 4);
 }
 
-int gradient_pair_tile(const GemmProblem& dx, const GemmPlan& plan_dx, const GemmProblem& dw, const GemmPlan& plan_dw)
+static bool dw_is_first(const GemmProblem& dx, const GemmProblem& dw) { return dw.tn || dw.K >= dx.K; }      // the longer contraction, or the row-major one
+
+GradientPair gradient_pair(const GemmProblem& dx, const GemmPlan& plan_dx, const GemmProblem& dw, const GemmPlan& plan_dw)
 {
     auto plain = [](const GemmProblem& p) {
         return (p.prec == 8 || p.prec == 16) && p.M > 0 && p.N > 0 && p.K > 0 && p.conv_H == 0 && p.b_remap_C == 0
             && !p.out_amax_bits && !p.out_codes;
     };
-    if(dx.prec != dw.prec || !plain(dx) || !plain(dw) || dx.tn || g_persistent_mode == 1 || dw_over_dx_operands(dx, dw)) return -1;
+    if(dx.prec != dw.prec || !plain(dx) || !plain(dw) || dx.tn || g_persistent_mode == 1 || dw_over_dx_operands(dx, dw)) return GradientPair{};
     // (The estimates are the tiles', also of a product that by itself would go to gemm_rows_kernel.  One shared launch -> that kernel for
     // what it takes, replayed from a graph: 64x128x128 int8 4.2 us, apart 6.3, 512^3 4.8 and 8.1, 128x1024x2048 8.2 and 8.8;
     // binary16 4.0 and 6.1, 5.8 and 9.1, but 128x1024x2048 11.0 and 9.7, 256x1024x1024 10.8 and 9.7: the worst of 32.)
-    const double us = plan_dx.us + plan_dw.us;
-    return dw.tn || dw.K >= dx.K ? pair_tile(dw, dx, us) : pair_tile(dx, dw, us);
+    const double       us = plan_dx.us + plan_dw.us;
+    const bool         dw_first = dw_is_first(dx, dw);
+    const GemmProblem &a = dw_first ? dw : dx, &b = dw_first ? dx : dw;
+    GradientPair       pair;
+    pair.tile = pair_tile(a, b, us);
+    return pair.tile >= 0 ? pair : split_pair(a, dw_first ? plan_dw : plan_dx, b, us);
 }
 
-hipError_t launch_gradient_pair(const GemmProblem& dx, const GemmProblem& dw, int tile, const ColumnFoldArgs& fold, hipStream_t stream)
+hipError_t launch_gradient_pair(const GemmProblem& dx, void* ws_dx, const GemmProblem& dw, void* ws_dw, const GradientPair& pair, const ColumnFoldArgs& fold, hipStream_t stream)
 {
-    const bool         dw_first = dw.tn || dw.K >= dx.K;      // the longer contraction, or the row-major one
+    const bool         dw_first = dw_is_first(dx, dw);
     const GemmProblem &a = dw_first ? dw : dx, &b = dw_first ? dx : dw;
-    const GemmPlan     plan{tile, 1, 0, 0.0};
+    void* const        workspace = dw_first ? ws_dw : ws_dx;
     GemmPairArgs       args;
-    hipError_t         e = kernel_args(a, plan, nullptr, args.g[0]);
-    if(e == hipSuccess) e = kernel_args(b, plan, nullptr, args.g[1]);
+    hipError_t         e = kernel_args(a, GemmPlan{pair.tile, pair.splits, 0, 0.0}, workspace, args.g[0]);
+    if(e == hipSuccess) e = kernel_args(b, GemmPlan{pair.tile, 1, 0, 0.0}, nullptr, args.g[1]);
     if(e != hipSuccess) return e;
-    args.na = args.g[0].tiles_m * args.g[0].tiles_n;
-    args.total = args.na + args.g[1].tiles_m * args.g[1].tiles_n;
-    args.fold  = fold;
-    const int workgroups = args.total;
-    if(a.prec == 8)
-        return a.tn ? launch_pair_traits<I8Traits, true>(tile, args, workgroups, stream) : launch_pair_traits<I8Traits, false>(tile, args, workgroups, stream);
-    return a.tn ? launch_pair_traits<F16Traits, true>(tile, args, workgroups, stream) : launch_pair_traits<F16Traits, false>(tile, args, workgroups, stream);
+    args.splits = pair.splits;
+    args.na     = args.g[0].tiles_m * args.g[0].tiles_n * pair.splits;
+    args.total  = args.na + args.g[1].tiles_m * args.g[1].tiles_n;
+    if(pair.splits == 1) args.fold = fold;
+    auto go = [&](auto tn, auto split) {
+        constexpr bool TNA = decltype(tn)::value, SPLITA = decltype(split)::value;
+        return a.prec == 8 ? launch_pair_traits<I8Traits, TNA, SPLITA>(pair.tile, args, stream) : launch_pair_traits<F16Traits, TNA, SPLITA>(pair.tile, args, stream);
+    };
+    constexpr std::true_type  yes{};
+    constexpr std::false_type no{};
+    if(pair.splits == 1) return a.tn ? go(yes, no) : go(no, no);
+    e = a.tn ? go(yes, yes) : go(no, yes);
+    ColumnFoldArgs beside = fold;
+    return e != hipSuccess ? e : reduce_splits(a, pair.splits, workspace, stream, &beside);
 }
 
 }  // namespace qsync

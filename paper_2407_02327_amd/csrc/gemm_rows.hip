@@ -173,19 +173,23 @@ int rows_columns(const GemmProblem& p)
 
 }  // namespace
 
+bool gemm_rows_takes(const GemmProblem& p)
+{
+    if((p.prec != 8 && p.prec != 16) || p.tn || p.conv_H > 0 || p.b_remap_C > 0 || p.acc_dump || p.out_amax_bits || p.out_codes) return false;
+    return rows_columns(p) != 0;
+}
+
 hipError_t launch_gemm_rows(const GemmProblem& p, bool* taken, hipStream_t st)
 {
-    *taken = false;
-    if((p.prec != 8 && p.prec != 16) || p.tn || p.conv_H > 0 || p.b_remap_C > 0 || p.acc_dump || p.out_amax_bits || p.out_codes) return hipSuccess;
+    *taken = gemm_rows_takes(p);
+    if(!*taken) return hipSuccess;
     const int columns = rows_columns(p);
-    if(columns == 0) return hipSuccess;
     GemmKernelArgs a{};
     a.A = static_cast<const uint8_t*>(p.A);
     a.B = static_cast<const uint8_t*>(p.B);
     a.M = p.M; a.N = p.N; a.Kb = p.K * (p.prec / 8);
     a.C = p.C; a.c_is_f16 = p.c_dtype == kF16;
     a.s0 = p.s0; a.s1 = p.s1; a.col_scale = p.col_scale; a.col_bias = p.col_bias;
-    *taken = true;
     return p.prec == 8 ? launch_rows<I8Traits>(a, columns, st) : launch_rows<F16Traits>(a, columns, st);
 }
 

@@ -177,13 +177,16 @@ void set_gemm_persistent_mode(int mode);
 hipError_t launch_conv3x3(const GemmProblem& p, int force_tile, bool* taken, hipStream_t stream);
 // Few rows or a small product, plain epilogue (gemm_rows.hip); *taken is false, and nothing launched, for any other problem.
 hipError_t launch_gemm_rows(const GemmProblem& p, bool* taken, hipStream_t stream);
+bool gemm_rows_takes(const GemmProblem& p);
 // fold (optional): column sums to be finished beside the reduction of K splits; cleared when that was done.
 hipError_t launch_gemm(const GemmProblem& p, const GemmPlan& plan, void* workspace, hipStream_t stream, ColumnFoldArgs* fold = nullptr);
 // Data and weight gradient of one operator in one launch: the tile to run both on, or -1 when their own plans are
-// estimated to be about as fast one after the other, or when dw writes what dx reads.
-int gradient_pair_tile(const GemmProblem& dx, const GemmPlan& plan_dx, const GemmProblem& dw, const GemmPlan& plan_dw);
-// (in workgroups behind theirs: the fold of column sums)
-hipError_t launch_gradient_pair(const GemmProblem& dx, const GemmProblem& dw, int tile, const ColumnFoldArgs& fold, hipStream_t stream);
+// estimated to be about as fast one after the other, or when dw writes what dx reads; and the K splits of the longer contraction,
+// never more than its own plan has (the partial products take that plan's place in the workspace).
+struct GradientPair { int tile = -1; int splits = 1; };
+GradientPair gradient_pair(const GemmProblem& dx, const GemmPlan& plan_dx, const GemmProblem& dw, const GemmPlan& plan_dw);
+// (in workgroups behind theirs, or beside the sum of the splits: the fold of column sums)
+hipError_t launch_gradient_pair(const GemmProblem& dx, void* ws_dx, const GemmProblem& dw, void* ws_dw, const GradientPair& pair, const ColumnFoldArgs& fold, hipStream_t stream);
 
 // ---- measurement probe (probe.hip): matrix instructions on register operands, no memory traffic
 constexpr int kProbeBlocks = 512;       // workgroups of 4 wavefronts, 8 matrix instructions per wavefront and iteration

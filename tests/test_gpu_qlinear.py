@@ -193,6 +193,40 @@ def test_both_gradients_of_one_call_equal_the_separate_calls(pair, dxdt):
                 assert ((got - want).abs() <= bound).all()
 
 
+@pytest.mark.parametrize("tag,M,N,K,rowmajor,splits", [
+    (Q.INT8, 5120, 64, 400, True, 5), (Q.INT8, 8960, 672, 384, True, 7), (Q.INT8, 8832, 176, 544, False, 8), (Q.FP16, 2944, 504, 856, True, 3),
+    (Q.FP16, 6144, 192, 768, True, 12), (Q.FP16, 5336, 272, 936, False, 6),
+    # the data gradient is the longer contraction, in splits
+    (Q.FP16, 80, 3200, 512, False, 6), (Q.FP16, 1024, 4096, 512, False, 4)])
+def test_gradients_share_a_launch_with_one_in_k_splits(tag, M, N, K, rowmajor, splits):
+    """One launch for both with the longer contraction in K splits (last splits shorter, tiles of 64 and 128, K tiles that end inside a
+    row), its sum and the bias gradient's fold behind it.  Small integers: every sum is exact in
+    any order."""
+    say("pair in splits", tag, M, N, K, rowmajor)
+    rng = np.random.default_rng(M + N)
+    dt = np.int8 if tag == Q.INT8 else np.float16
+    dy, x, w = (rng.integers(-3, 4, s).astype(dt) for s in ((M, N), (M, K), (N, K)))
+    want_dx, want_dw = dy.astype(np.float32) @ w.astype(np.float32), dy.astype(np.float32).T @ x.astype(np.float32)
+    dyf = rng.integers(-3, 4, (M, N)).astype(np.float32)
+    s = dev(np.ones(1, np.float32)) if tag == Q.INT8 else None
+    wT = dev(np.ascontiguousarray(w.T))
+    query = Q.qsync_qlinear_bwd_rm_workspace_bytes if rowmajor else Q.qsync_qlinear_bwd_workspace_bytes
+    room = torch.full((query(tag, M, N, K),), 255, dtype=torch.uint8, device="cuda")
+    for dxdt, with_db in ((torch.float32, True), (torch.float16, False)):
+        dx, dw, db = (torch.full(sh, float("nan"), dtype=d, device="cuda") for sh, d in (((M, K), dxdt), ((N, K), torch.float32), ((N,), torch.float32)))
+        bias = (db, dev(dyf)) if with_db else (None, None)
+        if rowmajor:
+            Q.qsync_qlinear_bwd_rm(tag, M, N, K, dev(dy), s, dev(x), s, wT, s, Q.PER_TENSOR, dx, dw, *bias, None, None, room)
+        else:
+            Q.qsync_qlinear_bwd(tag, M, N, K, dev(dy), dev(np.ascontiguousarray(dy.T)), s, dev(np.ascontiguousarray(x.T)), s, wT, s, Q.PER_TENSOR,
+                                dx, dw, *bias, None, None, room)
+        assert Q.qsync_debug_last_gradient_splits() == splits and Q.qsync_debug_last_gradient_pair() == -1
+        assert_bits_equal(host(dx), want_dx.astype(np.float32 if dxdt == torch.float32 else np.float16), "dX")
+        assert_bits_equal(host(dw), want_dw, "dW")
+        if with_db:
+            assert_bits_equal(host(db), dyf.sum(0), "db")
+
+
 @pytest.mark.parametrize("rowmajor,over", [(False, "weights"), (False, "gradient"), (True, "weights")])
 def test_weight_gradient_stored_over_an_operand_of_the_data_gradient(rowmajor, over):
     """dW written where the transposed weight codes or the gradient codes lay: the data gradient has read them by then."""
