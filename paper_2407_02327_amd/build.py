@@ -14,7 +14,7 @@ PKG_DIR = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(PKG_DIR, "csrc")
 LIB_PATH = os.path.join(PKG_DIR, "libqsync.so")
 BINDING_PATH = os.path.join(PKG_DIR, "_native.so")      # CPython module over the library's C ABI and torch's tensors
-SOURCES = ["api.hip", "elementwise.hip", "gemm_mfma.hip", "conv3x3.hip", "gemm_rows.hip", "gemm_f32.hip", "probe.hip", "indicator.hip"]
+SOURCES = ["api.hip", "elementwise.hip", "gemm_mfma.hip", "conv3x3.hip", "conv_wgrad.hip", "gemm_rows.hip", "gemm_f32.hip", "probe.hip", "indicator.hip"]
 
 # -ffp-contract=off: the quantizer's multiply and subtract must stay separately rounded.
 # packed fp32 VALU ops are disabled for the device pass (hipcc's host pass warns that it

@@ -1496,6 +1496,12 @@ hipError_t launch_gemm(const GemmProblem& p, const GemmPlan& plan, void* workspa
         const hipError_t e     = launch_conv3x3(p, g_tile_override, &taken, stream);
         if(taken || e != hipSuccess) return e;
     }
+    if(p.conv_H > 0 && p.tn && splits > 1 && g_tile_override < 0)
+    {
+        hipError_t e   = hipSuccess;
+        const int  own = launch_conv3x3_wgrad(p, splits, workspace, stream, &e);
+        if(own > 0) return e != hipSuccess ? e : reduce_splits(p, own, workspace, stream, fold);
+    }
     // The persistent kernel is opt-in.  Its write-back of a tile overlaps the next tile's K loop, which on 32x32 instructions gained
     // 7-20 % launched alone and back to back; the present K loop leaves its wavefronts no registers for a second set of the columns'
     // fragments, and it loses there too: 16384x4096x1024 int8 75.1 us per tile, 80.5 persistent, binary16 124.4 and 127.1, 16384x1024x4096 53.0

@@ -325,3 +325,26 @@ def test_weight_gradient_with_more_output_channels_than_the_gather_addresses(tag
     for n0 in range(0, n, 1 << 22):
         want = dy[:, n0:n0 + (1 << 22)].float().t().contiguous() @ patches
         assert torch.equal(dw[n0:n0 + (1 << 22)].float(), want), n0
+
+
+@pytest.mark.parametrize("tag,b,H,W,C,N", [
+    (Q.FP16, 24, 14, 14, 256, 256), (Q.FP16, 28, 23, 9, 296, 168), (Q.FP16, 25, 41, 51, 80, 56), (Q.FP16, 58, 45, 34, 272, 16), (Q.FP16, 20, 20, 95, 64, 120), (Q.FP16, 20, 20, 96, 64, 120),
+    (Q.FP16, 3, 1, 31, 4096, 1032), (Q.FP16, 9000, 2, 2, 88, 80), (Q.INT8, 64, 56, 56, 64, 64), (Q.INT8, 50, 33, 38, 272, 64), (Q.INT8, 46, 8, 191, 96, 96),
+    (Q.INT8, 46, 8, 192, 96, 96), (Q.INT8, 65, 300, 1, 96, 336)])
+def test_weight_gradient_of_large_convolutions(tag, b, H, W, C, N):
+    """The sizes that go through the ring of pixels (pixels x C x N from 2.3e8 binary16 and 6e8 int8): last chunks that are partial, last
+    groups of eight channels and of few outputs, images of one row or one or two columns, as wide as the ring reaches (W + 1 pixels in three
+    chunks of 32 or 64) and one wider, which the gathering GEMM does.  Small integers: every sum is exact in any order."""
+    say("wgrad ring", tag, b, H, W, C, N)
+    g = torch.Generator(device="cuda").manual_seed(b + C)
+    dt = torch.int8 if tag == Q.INT8 else torch.float16
+    x = torch.randint(-3, 4, (b, H, W, C), generator=g, device="cuda")
+    dy = torch.randint(-3, 4, (b * H * W, N), generator=g, device="cuda")
+    pad = torch.nn.functional.pad(x.double(), (0, 0, 1, 1, 1, 1))
+    dyT = dy.double().t().contiguous()
+    want = torch.cat([dyT @ pad[:, kh:kh + H, kw:kw + W].reshape(b * H * W, C) for kh in range(3) for kw in range(3)], 1).float()
+    s = torch.ones(1, device="cuda") if tag == Q.INT8 else None
+    room = torch.full((max(256, Q.qsync_conv3x3_wgrad_workspace_bytes(tag, b, H, W, C, N)),), 255, dtype=torch.uint8, device="cuda")
+    dw = torch.full((N, 9 * C), float("nan"), device="cuda")
+    Q.qsync_conv3x3_wgrad(tag, b, H, W, C, N, x.to(dt), s, dy.to(dt), s, dw, None, room)
+    assert torch.equal(dw, want)
