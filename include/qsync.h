@@ -231,7 +231,7 @@ int qsync_convert_operands(int tag, const void* x, int xdt, int64_t M, int64_t C
  * acc_dump_opt  INT8 only: if non-NULL, also receives the raw int32 accumulators [M,N]
  *     (verification aid; NULL in production).
  * workspace     at least qsync_qlinear_workspace_bytes(tag, M, N, K) bytes, 16-byte aligned
- *     (may be NULL if that is 0).
+ *     (may be NULL if that is 0).  FP32 with less, or none, runs without K splits: slower, sums in another order.
  * INT8 needs K % 16 == 0 and FP16 needs K % 8 == 0 (rows of 16-byte vectors feed the matrix
  * cores); otherwise QSYNC_ERR_ALIGN.  M and N are arbitrary.  A row of K elements may take at most
  * 16 MiB (QSYNC_ERR_UNSUPPORTED beyond; the same bound holds for N in the dX GEMM and M in the dW GEMM
@@ -328,7 +328,8 @@ int qsync_scale_from_amax(float* amax, int bits, float* scale, float* inv_scale,
  * the time they are written.
  * With dx_opt and dw_opt both given the two GEMMs may otherwise share one launch.  INT8 results are the same bits as those of two
  * calls with one of them each; FP16 and FP32 sums may then run in another order (other K splits).
- * workspace  at least qsync_qlinear_bwd_workspace_bytes(tag, M, N, K) bytes.
+ * workspace  at least qsync_qlinear_bwd_workspace_bytes(tag, M, N, K) bytes (FP32 with fewer, but enough
+ *            for the column sums of db_opt, runs without K splits).
  * Alignment: INT8 needs N % 16 == 0 (for dX) and M % 16 == 0 (for dW); FP16 needs % 8.
  */
 int qsync_qlinear_bwd(int tag, int64_t M, int64_t N, int64_t K,
@@ -443,7 +444,8 @@ int qsync_prepare_weights(const void* w, int wdt, int64_t N, int64_t K, int bits
  *   dw[n, (kh*3+kw)*C + c] = sdy * sx * sum_{b,h,w} dyq[b,h,w,n] * xq[b, h+kh-1, w+kw-1, c]   (0 outside the image)
  * (tag FP16: the same sum over binary16 operands with fp32 accumulation, no scales).
  * The contraction runs over the pixels.  The GEMM reads both operands as they are:
- * the row-major gradient, and the patch matrix [pixels, 9*C] formed by its own loads from the NHWC activation (padding
+ * the row-major gradient, and the patch matrix [pixels, 9*C] formed by its own loads from the NHWC activation (large
+ * products: from a ring of its pixels in LDS; padding
  * taps, and the pixels missing from a last partial tile, read a zero block); transposing LDS reads feed the matrix
  * instructions and no copy of either operand is made; the workspace holds split-K partials only.
  * From N = 2^24 on (rows too long for the loads' 32-bit offsets) the operands are instead written to the workspace
