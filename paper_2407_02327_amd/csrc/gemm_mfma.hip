@@ -1581,10 +1581,11 @@ static int pair_tile(const GemmProblem& a, const GemmProblem& b, double separate
 }
 // Where the two would go apart, the first (the longer contraction) in K splits: the tile and the splits, up to as many, on which they share
 // a launch all the same, with the sum of the splits behind it.  Few outputs over a long contraction leave units idle, and the parts of
-// both together fill them: three launches become two.  Over 92 backward passes of 64..16384 by 64..4096 that went apart (both types, both
-// forms, replayed from a graph) 66 share a launch now, all of them 1.18 times as fast on average: binary16 6144x192x768 22.1 -> 15.4 us,
-// 14592x160x336 23.0 -> 17.0, 4096x768x3072 59.8 -> 54.8 (unsplit), int8 15744x2288x112 32.2 -> 22.9, 8576x320x1520 36.6 -> 26.3; the worst
-// 61.0 -> 61.9 (binary16 10624x992x808).  The estimate does not know how the second's contraction drags on over the small tile: with
+// both together fill them: three launches become two.  Binary16 keeps the plan's splits, not fewer: a sum over a longer piece has more roundings
+// (4096x768x3072 unsplit 59.8 -> 54.8 us, but the error of dW against 64 bits 2.4e-7 -> 4.1e-7); int8 sums are exact.  Backward passes of 64..16384 by
+// 64..4096 (both types, both forms, replayed from a graph), apart -> this, us: binary16 6784x912x592 41.5 -> 31.2, 13536x1360x240 42.1 -> 37.6,
+// 4224x312x160 13.5 -> 9.7, int8 15744x2288x112 32.2 -> 22.9, 14640x128x2608 54.9 -> 42.0; of 120 drawn 26 gain, 1.25 times on
+// average.  The estimate does not know how the second's contraction drags on over the small tile: with
 // more than 36 K tiles of it the pair may lose (binary16 3200x3656x128 30.7, 39.8 together), nor of gemm_rows_kernel
 // (2112x1696x96 13.0, 20.0).
 static GradientPair split_pair(const GemmProblem& a, const GemmPlan& plan_a, const GemmProblem& b, double separate_us)
@@ -1594,7 +1595,7 @@ static GradientPair split_pair(const GemmProblem& a, const GemmPlan& plan_a, con
     if(plan_a.splits < 2 || kb > 36 || g_tile_override >= 0 || gemm_rows_takes(a) || gemm_rows_takes(b)) return pair;
     double best = separate_us;
     for(int t = 1; t < kNumTiles; ++t)
-        for(int s = 1; s <= plan_a.splits; ++s)
+        for(int s = a.prec == 8 ? 1 : plan_a.splits; s <= plan_a.splits; ++s)
         {
             const double us = pair_us(a, b, t, s);
             if(us >= 0.0 && us < best) { best = us; pair = GradientPair{t, s}; }
