@@ -1,12 +1,18 @@
 // FP32 GEMM:  C[M,N] = epilogue( sum_k A[m,k] B[n,k] ), fp32 operands of any row length, on the bf16 matrix instructions.
 //
-// An fp32 value is the exact sum of three bf16 values: its upper eight significant bits (cut off), the next eight (to nearest), the
-// rest.  Of the nine products of two such sums the six largest are added up in fp32, smallest first; what is left out is below 2^-24
-// of a product, of random sign.  Six bf16 instructions of 16x16x32 take 96 clocks where the eight fp32 ones of 16x16x4 take 256, and
-// fewer roundings fall on the sum: an instruction adds 32 products to it, not four.  Error against 64 bits in the 2-norm, values
-// N(0,1), fp32 instructions -> this: K 32 1.0e-7 -> 0.4e-7, 64 1.4e-7 -> 0.9e-7, 256 2.9e-7 -> 2.3e-7, 1024 5.7e-7 -> 4.8e-7, 4096
-// 1.14e-6 -> 1.00e-6, without the sums in parts of the smaller tiles, which halve it (2.4e-7 at 1024 and 2048); over 120 drawn products 1.5
-// times smaller on average, at most 1.05 times larger (832x2696x2096, once on the small tile in splits, now on the large).
+// An fp32 value is the exact sum of three bf16 values: the nearest one, the nearest one to what remains, and the rest.  The second is at
+// most 2^-8 of the value, the third 2^-17.  Of the nine products of two such sums the six largest are added up in fp32, smallest first;
+// what is left out is up to 2^-24 of a product (2^-26.8 in the mean square over random mantissas), and of one sign where all products of a
+// sum are alike.  (With a first part that is cut off instead it was up to 2^-22, at the same time.)  Six bf16 instructions of 16x16x32 take
+// 96 clocks where the eight fp32 ones of 16x16x4 take 256, and
+// fewer roundings fall on the sum: an instruction adds 32 products to it, not four.  It cuts off what it shifts out, though, so that a sum
+// comes out -1 to 1/2 ulp off, -1/4 on average (measured), where the fp32 instructions round to nearest.  Error against 64 bits in
+// the 2-norm, fp32 instructions -> this, values N(0,1): K 24 0.89e-7 -> 0.36e-7, 33 1.04e-7 -> 0.65e-7, 64 1.44e-7 -> 0.92e-7, 256 2.9e-7 ->
+// 2.3e-7, 1024 5.7e-7 -> 4.8e-7, 4096 1.14e-6 -> 1.00e-6, without the sums in parts of the smaller tiles, which halve it (2.4e-7 at 1024
+// and 2048); products all positive 0.71e-7 -> 0.26e-7 at 24, 2.4e-7 -> 1.6e-7 at 256, all equal 1.66e-7 -> 0.30e-7 and 1.9e-6 -> 0.6e-6.
+// Over 120 drawn products 1.5 times smaller on average, at most 1.05 times larger (832x2696x2096, once on the small tile in splits,
+// now on the large).  What grows is the error of a sum that rounds little on the fp32 instructions: of up to 16 products (one: 2.5e-8 -> 3.6e-8), which
+// therefore stay on those (kF32ShortK), and of longer ones of one product other than zero (at most 1/2 -> 1.4 ulp).
 //
 // Bound by the matrix instructions, power and the splitting's share of the issue slots: a K tile of 32 takes the 256x128 tile 1.75 us where
 // its instructions take 1.28 at 2.4 GHz (1.60 without the splitting, 1.68 without its LDS writes).  Operands go through registers, split
@@ -44,8 +50,8 @@ template <int BM, int BN> constexpr int f32_lds_bytes() { return 2 * (BM + BN) /
 // anything smaller would have bits below those of a bf16 number).
 __device__ __forceinline__ void split2(float x0, float x1, uint32_t mask, uint32_t& hi, uint32_t& mid, uint32_t& lo, uint32_t& rest)
 {
-    hi             = __builtin_amdgcn_perm(__float_as_uint(x1), __float_as_uint(x0), 0x07060302u);
-    const float r0 = x0 - __uint_as_float(__float_as_uint(x0) & mask), r1 = x1 - __uint_as_float(__float_as_uint(x1) & mask);
+    hi             = __builtin_bit_cast(uint32_t, __builtin_convertvector((v2f32){x0, x1}, v2bf16));
+    const float r0 = x0 - __uint_as_float(hi << 16), r1 = x1 - __uint_as_float(hi & mask);
     mid            = __builtin_bit_cast(uint32_t, __builtin_convertvector((v2f32){r0, r1}, v2bf16));
     const float    s0 = r0 - __uint_as_float(mid << 16), s1 = r1 - __uint_as_float(mid & mask);
     const uint32_t u0 = __float_as_uint(s0), u1 = __float_as_uint(s1);
@@ -219,58 +225,62 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm_f32_kernel(const GemmK
     constexpr std::integral_constant<int, kAll>     all{};
     constexpr std::integral_constant<int, kNoLoads> no_loads{};
     constexpr std::integral_constant<int, kLast>    last_one{};
-    if(whole > 0)
+    const bool short_sum = !SPLIT && K <= kF32ShortK;      // the fp32 instructions below
+    if(!short_sum)
     {
-        static_for<D>([&](auto c) {
-#pragma unroll
-            for(int i = 0; i < U; ++i) load(c, i, decltype(c)::value);
-            __builtin_amdgcn_sched_barrier(0);
-        });
-        put_first();
-        // (straight-line, no way from one of the D steps to another's place: the compiler then knows which load each of its waits is for)
-        int t = 0, since = 0;
-        for(; t + D < whole; t += D)
+        if(whole > 0)
         {
-            static_for<D>([&](auto c) { step(all, std::integral_constant<int, (decltype(c)::value + 1) % D>{}, t + decltype(c)::value); });
-            if constexpr(kFold)
-                if((since += D) >= kFoldSteps)
-                {
-                    since = 0;
+            static_for<D>([&](auto c) {
 #pragma unroll
-                    for(int i = 0; i < FM; ++i)
-#pragma unroll
-                        for(int j = 0; j < FN; ++j)
-                        {
-                            total[i][j] += acc[i][j];
-                            acc[i][j] = v4f32{0.0f, 0.0f, 0.0f, 0.0f};
-                        }
-                }
-        }
-        static_for<D - 1>([&](auto c) {
-            if(t + 1 < whole)
+                for(int i = 0; i < U; ++i) load(c, i, decltype(c)::value);
+                __builtin_amdgcn_sched_barrier(0);
+            });
+            put_first();
+            // (straight-line, no way from one of the D steps to another's place: the compiler then knows which load each of its waits is for)
+            int t = 0, since = 0;
+            for(; t + D < whole; t += D)
             {
-                step(all, std::integral_constant<int, (decltype(c)::value + 1) % D>{}, t);
+                static_for<D>([&](auto c) { step(all, std::integral_constant<int, (decltype(c)::value + 1) % D>{}, t + decltype(c)::value); });
+                if constexpr(kFold)
+                    if((since += D) >= kFoldSteps)
+                    {
+                        since = 0;
+#pragma unroll
+                        for(int i = 0; i < FM; ++i)
+#pragma unroll
+                            for(int j = 0; j < FN; ++j)
+                            {
+                                total[i][j] += acc[i][j];
+                                acc[i][j] = v4f32{0.0f, 0.0f, 0.0f, 0.0f};
+                            }
+                    }
+            }
+            static_for<D - 1>([&](auto c) {
+                if(t + 1 < whole)
+                {
+                    step(all, std::integral_constant<int, (decltype(c)::value + 1) % D>{}, t);
+                    ++t;
+                }
+            });
+            if(whole < tiles)
+            {
+                load_tail();
+                step(no_loads, c0, t);
                 ++t;
             }
-        });
-        if(whole < tiles)
+            step(last_one, c0, t);
+            if constexpr(kFold)
+#pragma unroll
+                for(int i = 0; i < FM; ++i)
+#pragma unroll
+                    for(int j = 0; j < FN; ++j) acc[i][j] += total[i][j];
+        }
+        else if(tiles > 0)
         {
             load_tail();
-            step(no_loads, c0, t);
-            ++t;
+            put_first();
+            step(last_one, c0, 0);
         }
-        step(last_one, c0, t);
-        if constexpr(kFold)
-#pragma unroll
-            for(int i = 0; i < FM; ++i)
-#pragma unroll
-                for(int j = 0; j < FN; ++j) acc[i][j] += total[i][j];
-    }
-    else if(tiles > 0)
-    {
-        load_tail();
-        put_first();
-        step(last_one, c0, 0);
     }
     if constexpr(!SPLIT)
         if(tid < BN)
@@ -281,7 +291,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm_f32_kernel(const GemmK
 
     // Sums that are not finite, and those with operands that three bf16 numbers do not hold, are formed again by the fp32 instructions.  An
     // infinite value is a NaN in its lower parts, so it shows in every sum that it is part of.
-    bool again = (rest & 0xFFFFu) != 0u;
+    bool again = short_sum || (rest & 0xFFFFu) != 0u;
 #pragma unroll
     for(int i = 0; i < FM; ++i)
 #pragma unroll
@@ -306,49 +316,54 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm_f32_kernel(const GemmK
         for(int i = 0; i < FM; ++i)
         {
             const int64_t at = m0 + wm * (BM / WGM) + 16 * i + fr;
-            ra[i] = A + (at < p.M ? at : p.M - 1) * K;
+            ra[i] = A + (at < p.M ? at : p.M - 1) * K + 4 * q;
         }
 #pragma unroll
         for(int j = 0; j < FN; ++j)
         {
             const int64_t at = n0 + wn * (BN / WGN) + 16 * j + fr;
-            rb[j] = B + (at < p.N ? at : p.N - 1) * K;
+            rb[j] = B + (at < p.N ? at : p.N - 1) * K + 4 * q;
         }
-        auto fetch = [&](v4f32 (&fa)[FM], v4f32 (&fb)[FN], int64_t k) {
-            if(k + 16 <= end)
+        v4f32 fa[FM], fb[FN], ga[FM], gb[FN];
+        auto fetch = [&](v4f32 (&va)[FM], v4f32 (&vb)[FN], int64_t k) {      // (K indices behind the end give zeros)
+            const int left = static_cast<int>(end - k) - 4 * q;
+#pragma unroll
+            for(int i = 0; i < FM; ++i) va[i] = v4f32{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+            for(int j = 0; j < FN; ++j) vb[j] = v4f32{0.0f, 0.0f, 0.0f, 0.0f};
+            if(left >= 4)
             {
 #pragma unroll
-                for(int i = 0; i < FM; ++i) fa[i] = *reinterpret_cast<const v4f32_any*>(ra[i] + k + 4 * q);
+                for(int i = 0; i < FM; ++i) va[i] = *reinterpret_cast<const v4f32_any*>(ra[i] + k);
 #pragma unroll
-                for(int j = 0; j < FN; ++j) fb[j] = *reinterpret_cast<const v4f32_any*>(rb[j] + k + 4 * q);
+                for(int j = 0; j < FN; ++j) vb[j] = *reinterpret_cast<const v4f32_any*>(rb[j] + k);
             }
             else
 #pragma unroll
-                for(int e = 0; e < 4; ++e)
-                {
-                    const bool in = k + 4 * q + e < end;
+                for(int e = 0; e < 3; ++e)
+                    if(e < left)
+                    {
 #pragma unroll
-                    for(int i = 0; i < FM; ++i) fa[i][e] = in ? ra[i][k + 4 * q + e] : 0.0f;
+                        for(int i = 0; i < FM; ++i) va[i][e] = ra[i][k + e];
 #pragma unroll
-                    for(int j = 0; j < FN; ++j) fb[j][e] = in ? rb[j][k + 4 * q + e] : 0.0f;
-                }
+                        for(int j = 0; j < FN; ++j) vb[j][e] = rb[j][k + e];
+                    }
         };
-        v4f32 fa[FM], fb[FN], ga[FM], gb[FN];
-        fetch(fa, fb, first);
-#pragma unroll 1
-        for(int64_t k = first; k < end; k += 16)
-        {
-            fetch(ga, gb, k + 16);
+        auto products = [&](const v4f32 (&va)[FM], const v4f32 (&vb)[FN]) {
 #pragma unroll
             for(int e = 0; e < 4; ++e)
 #pragma unroll
                 for(int i = 0; i < FM; ++i)
 #pragma unroll
-                    for(int j = 0; j < FN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[j][e], fa[i][e], acc[i][j], 0, 0, 0);
-#pragma unroll
-            for(int i = 0; i < FM; ++i) fa[i] = ga[i];
-#pragma unroll
-            for(int j = 0; j < FN; ++j) fb[j] = gb[j];
+                    for(int j = 0; j < FN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(vb[j][e], va[i][e], acc[i][j], 0, 0, 0);
+        };
+#pragma unroll 1
+        for(int64_t k = first; k < end; k += 32)
+        {
+            fetch(fa, fb, k);
+            if(k + 16 < end) fetch(ga, gb, k + 16);
+            products(fa, fb);
+            if(k + 16 < end) products(ga, gb);
         }
     }
     const uint32_t seen = (!SPLIT && p.amax_bits && wave == 0) ? __hip_atomic_load(p.amax_bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;

@@ -1343,6 +1343,7 @@ GemmPlan plan_gemm(int prec, int64_t M, int64_t N, int64_t K, int force_tile, in
         if(s > 1) us += (prec == 32 ? 1.9 : 4.0) + (prec == 32 ? 2.7 : 1.0) * static_cast<double>(s + 1) * static_cast<double>(M) * static_cast<double>(N) * 4.0 / 6.24e6;
         return us;
     };
+    // (fp32 up to kF32ShortK is latency and stores: the small tile, 2584x3144x4 14.7 us, 256 tile 20.4, 128 tile 19.7; 5960x1804x4 19.0, 23.7, 23.6)
     // Candidates: no split, and the split counts that fill the units once, twice or up to their co-residency.  Tiles are
     // visited from large to small and splits from few to many; a later candidate must win by 5 % (the larger tile
     // moves fewer bytes per operation, and estimates that close are inside the model's error) -- unless the
@@ -1353,6 +1354,7 @@ GemmPlan plan_gemm(int prec, int64_t M, int64_t N, int64_t K, int force_tile, in
     for(int t = 0; t < kNumTiles; ++t)
     {
         if(force_tile >= 0 && force_tile < kNumTiles && t != force_tile) continue;
+        if(force_tile < 0 && prec == 32 && K <= kF32ShortK && t + 1 < kNumTiles) continue;      // (below)
         int64_t cand[4] = {1, 1, 1, 1};
         int     ncand   = 1;
         if(allow_split && !(force_tile >= 0 && force_splits < 0))

@@ -164,6 +164,8 @@ struct GemmPlan {
     double  us;            // estimated time
 };
 struct TileShape { int bm, bn; };
+// fp32 contractions of so few products keep the fp32 instructions, whose error against 64 bits is the smaller there (gemm_f32.hip)
+constexpr int64_t kF32ShortK = 16;
 TileShape gemm_tile_shape(int prec, int tile);
 // force_tile / force_splits < 0 leave the choice to the heuristic; tn: plan for GemmProblem::tn operands.
 GemmPlan plan_gemm(int prec, int64_t M, int64_t N, int64_t K, int force_tile = -1, int force_splits = -1,

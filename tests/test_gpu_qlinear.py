@@ -483,8 +483,9 @@ def test_few_rows_equal_the_tiled_product(tag, M):
 @pytest.mark.parametrize("M, N, K", [(1, 1, 1), (3, 130, 31), (65, 63, 33), (130, 70, 97), (64, 64, 64), (257, 129, 1023), (70, 6, 4099), (1, 300, 20001)])
 def test_fp32_operands_that_are_no_16_byte_rows(M, N, K):
     """Odd contractions and operands off 16 bytes, on both tiles, in K splits and, without a workspace, in one; against the
-    product in double.  A dot product of K fp32 terms in any order is off by at most (K + 1) 2^-24 sum |a b| (the products are
-    fused; scale and bias add two roundings), a binary16 output by another 2^-11 of itself."""
+    product in double.  Up to K = 16 the products are fused: K roundings of at most 2^-24 sum |a b|, and scale and bias add two.  Longer sums
+    leave out 1.01 times 2^-24 of a product, and each of the six instructions for 32 of them adds less than an ulp of the sum: 12 times 2^-24 where
+    fused products have 32.  A binary16 output is off by another 2^-11 of itself."""
     rng = np.random.default_rng(K)
     a, b, bias = rng.standard_normal((M, K)).astype(np.float32), rng.standard_normal((N, K)).astype(np.float32), rng.standard_normal(N).astype(np.float32)
     want = a.astype(np.float64) @ b.astype(np.float64).T + bias
@@ -529,6 +530,38 @@ def test_fp32_products_around_the_k_tiles(tile, K):
             assert_bits_equal(host(y), (a.astype(np.float64) @ b.astype(np.float64).T + bias).astype(np.float32), "Y")
     finally:
         Q.qsync_debug_set_gemm_tile(-1)
+
+
+@pytest.mark.parametrize("tile", [0, 1, 2])
+@pytest.mark.parametrize("K", [1, 3, 4, 7, 15, 16, 17, 32, 33, 64, 97, 160])
+def test_fp32_products_of_full_mantissas(tile, K):
+    """One nonzero a row of A, so that every output is one product, with mantissas that leave the most out of the six bf16 products (all
+    ones behind the first part) and random ones.  Contractions of up to 16 give the product's nearest fp32 value.  Longer ones leave out less than
+    2^-24 (1 + 2^-9) of it, and the instructions, which cut off what they shift out (measured: -1 to 1/2 ulp), add less than 2^-23 in the last
+    sum and 2^-6 of that in those of smaller parts: together less than 2^-23 (1.5 + 2^-5)."""
+    say("fp32 full mantissas", tile, K)
+    rng = np.random.default_rng(K)
+    M, N = 300, 140
+    def values(n):
+        bits = rng.integers(0, 1 << 23, n).astype(np.uint32)
+        bits[: n // 2] = (rng.integers(0, 128, n // 2) << 16 | 0x7F80 | rng.integers(0, 512, n // 2)).astype(np.uint32)
+        bits[: 12] = [0x00FF80, 0x007FBF, 0x007FC0, 0x00FF7F, 0x007F7F, 0x007F80, 0x008080, 0x7FFFFF, 0x7F7FFF, 0x7F8000, 0x7FFF80, 0x000001]
+        return (bits | 0x3F800000).view(np.float32) * np.float32(2.0) ** rng.integers(-9, 9, n).astype(np.float32) * rng.choice(np.float32([-1, 1]), n)
+    a, b = np.zeros((M, K), np.float32), np.stack([values(N) for _ in range(K)], 1)
+    one = values(M)
+    a[np.arange(M), np.arange(M) % K] = one
+    want = one.astype(np.float64)[:, None] * b[:, np.arange(M) % K].T.astype(np.float64)
+    y = torch.full((M, N), float("nan"), device="cuda")
+    Q.qsync_debug_set_gemm_tile(tile)
+    try:
+        w = torch.empty(max(256, Q.qsync_qlinear_workspace_bytes(Q.FP32, M, N, K)), dtype=torch.uint8, device="cuda")
+        Q.qsync_qlinear_fwd(Q.FP32, M, N, K, dev(a), None, dev(b), None, Q.PER_TENSOR, None, y, None, w)
+    finally:
+        Q.qsync_debug_set_gemm_tile(-1)
+    if K <= 16:
+        assert_bits_equal(host(y), want.astype(np.float32), "Y")
+    else:
+        assert (np.abs(host(y) - want) <= 2.0 ** -23 * (1.5 + 2.0 ** -5) * np.abs(want)).all()
 
 
 @pytest.mark.parametrize("tile", [0, 1, 2])
