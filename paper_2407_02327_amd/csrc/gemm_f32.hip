@@ -46,8 +46,8 @@ constexpr int kFragment = 3 * kPlane;
 
 template <int BM, int BN> constexpr int f32_lds_bytes() { return 2 * (BM + BN) / 16 * kFragment + 2 * BN * 4 + 128; }
 
-// Two values as three pairs of bf16 parts.  `rest` collects the bits behind the third part's: none, down to 2^-110 (the parts of
-// anything smaller would have bits below those of a bf16 number).
+// Two values as three pairs of bf16 parts.  `rest` collects the bits behind the third part's: none, down to 2^-110.  A part of anything
+// smaller may have bits below 2^-133, the smallest bf16 number, and loses those.
 __device__ __forceinline__ void split2(float x0, float x1, uint32_t mask, uint32_t& hi, uint32_t& mid, uint32_t& lo, uint32_t& rest)
 {
     hi             = __builtin_bit_cast(uint32_t, __builtin_convertvector((v2f32){x0, x1}, v2bf16));
@@ -109,7 +109,9 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm_f32_kernel(const GemmK
     // whole K tiles, D of them on their way in registers; behind the last one it is loaded again (and not looked at)
     const int whole = tiles > 0 ? static_cast<int>((end - first) / kStepK) : 0;
     float     raw[D][U][8];
-    uint32_t  rest = 0u, mask = 0xFFFF0000u;
+    uint32_t  rest[U], mask = 0xFFFF0000u;      // (the rest of a row's values: a piece stays in its row)
+#pragma unroll
+    for(int i = 0; i < U; ++i) rest[i] = 0u;
     asm volatile("" : "+s"(mask));      // (a scalar register: the instructions that use it are half as long)
     auto load = [&](auto set, int i, int t) {
         const v4f32_any lo = *reinterpret_cast<const v4f32_any*>(src[i]), hi = *reinterpret_cast<const v4f32_any*>(src[i] + 4);
@@ -134,7 +136,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm_f32_kernel(const GemmK
     v4u32 part[3];
     auto split = [&](auto set, int i, int e) {
         uint32_t hi, mid, lo;
-        split2(raw[decltype(set)::value][i][2 * e], raw[decltype(set)::value][i][2 * e + 1], mask, hi, mid, lo, rest);
+        split2(raw[decltype(set)::value][i][2 * e], raw[decltype(set)::value][i][2 * e + 1], mask, hi, mid, lo, rest[i]);
         part[0][e] = hi; part[1][e] = mid; part[2][e] = lo;
     };
     auto put = [&](int i, int t) {
@@ -225,8 +227,80 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm_f32_kernel(const GemmK
     constexpr std::integral_constant<int, kAll>     all{};
     constexpr std::integral_constant<int, kNoLoads> no_loads{};
     constexpr std::integral_constant<int, kLast>    last_one{};
-    const bool short_sum = !SPLIT && K <= kF32ShortK;      // the fp32 instructions below
-    if(!short_sum)
+    // ---- on the fp32 instructions, operands straight from memory: a lane's four K indices of sixteen, of both operands in the same order
+    struct Piece { v4f32 a[FM], b[FN]; };
+    const float *ra[FM], *rb[FN];
+    uint32_t     redo = 0u;      // bit i: the wavefront's sums of rows 16 i and on
+    auto point = [&]() {
+#pragma unroll
+        for(int i = 0; i < FM; ++i)
+        {
+            const int64_t at = m0 + wm * (BM / WGM) + 16 * i + fr;
+            ra[i] = A + (at < p.M ? at : p.M - 1) * K + 4 * q;
+        }
+#pragma unroll
+        for(int j = 0; j < FN; ++j)
+        {
+            const int64_t at = n0 + wn * (BN / WGN) + 16 * j + fr;
+            rb[j] = B + (at < p.N ? at : p.N - 1) * K + 4 * q;
+        }
+    };
+    auto fetch = [&](auto every, Piece& v, int64_t k) {      // (K indices behind the end give zeros)
+        const int left = static_cast<int>(end - k) - 4 * q;
+#pragma unroll
+        for(int i = 0; i < FM; ++i) v.a[i] = v4f32{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for(int j = 0; j < FN; ++j) v.b[j] = v4f32{0.0f, 0.0f, 0.0f, 0.0f};
+        if(left >= 4)
+        {
+#pragma unroll
+            for(int i = 0; i < FM; ++i)
+                if(decltype(every)::value || redo >> i & 1u) v.a[i] = *reinterpret_cast<const v4f32_any*>(ra[i] + k);
+#pragma unroll
+            for(int j = 0; j < FN; ++j) v.b[j] = *reinterpret_cast<const v4f32_any*>(rb[j] + k);
+        }
+        else
+#pragma unroll
+            for(int e = 0; e < 3; ++e)
+                if(e < left)
+                {
+#pragma unroll
+                    for(int i = 0; i < FM; ++i) v.a[i][e] = ra[i][k + e];
+#pragma unroll
+                    for(int j = 0; j < FN; ++j) v.b[j][e] = rb[j][k + e];
+                }
+    };
+    auto products = [&](auto every, const Piece& v) {
+#pragma unroll
+        for(int i = 0; i < FM; ++i)
+            if(decltype(every)::value || redo >> i & 1u)
+#pragma unroll
+                for(int e = 0; e < 4; ++e)
+#pragma unroll
+                    for(int j = 0; j < FN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(v.b[j][e], v.a[i][e], acc[i][j], 0, 0, 0);
+    };
+    auto put_columns = [&]() {
+        if constexpr(!SPLIT)
+            if(tid < BN)
+            {
+                colp[tid]      = scale;
+                colp[BN + tid] = bias;
+            }
+    };
+    if(!SPLIT && K <= kF32ShortK)
+    {
+        constexpr std::true_type every{};
+        point();
+        if(K > 0)
+        {
+            Piece v;
+            fetch(every, v, 0);
+            products(every, v);
+        }
+        put_columns();
+        __syncthreads();
+    }
+    else
     {
         if(whole > 0)
         {
@@ -281,89 +355,117 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm_f32_kernel(const GemmK
             put_first();
             step(last_one, c0, 0);
         }
-    }
-    if constexpr(!SPLIT)
-        if(tid < BN)
-        {
-            colp[tid]      = scale;
-            colp[BN + tid] = bias;
-        }
+        put_columns();
 
-    // Sums that are not finite, and those with operands that three bf16 numbers do not hold, are formed again by the fp32 instructions.  An
-    // infinite value is a NaN in its lower parts, so it shows in every sum that it is part of.
-    bool again = short_sum || (rest & 0xFFFFu) != 0u;
+        // Sums that the bf16 parts do not give as the fp32 instructions would are formed again by those, sixteen rows at a time: sums that
+        // are not finite (an infinite value is a NaN in its lower parts, so it shows in every sum that it is part of), denormal ones, and
+        // those that the lost bits of a value below 2^-110 may have moved by more than 2^-26: n products with up to the other row's
+        // largest value, each off by less than 2^-133 of it.  So such values here and there cost a pass over the other operand, for the
+        // largest values of its rows; rows of nothing else, a second turn of sixteen, without LDS; operands of nothing else, all of them.  All
+        // of a workgroup's sums again because of one value (before) -> this, us, 8192x4096x1024 (353; on fp32 instructions alone 488): one
+        // value in 256 rows 955 -> 381, 5 % of all values 958 -> 382, one row in 256 946 -> 538, an infinity 676 -> 437, all values 941 -> 936;
+        // 2048^3 (85; 131) 280 -> 96, 280 -> 95, 281 -> 168, 285 -> 160, 281 -> 272.
+        bool odd = false, lost[2] = {false, false};
+        auto no_number = [](float v) { return __builtin_amdgcn_classf(v, 0x297); };      // (NaN, infinite or denormal)
 #pragma unroll
-    for(int i = 0; i < FM; ++i)
-#pragma unroll
-        for(int j = 0; j < FN; ++j)
-#pragma unroll
-            for(int e = 0; e < 4; ++e) again |= !(fabsf(acc[i][j][e]) < __builtin_inff());
-    const bool any = __any(again);
-    if(lane == 0) flags[wave] = any ? 1u : 0u;
-    __syncthreads();
-    uint32_t redo = 0u;
-#pragma unroll
-    for(int w = 0; w < WGM * WGN; ++w) redo |= flags[w];
-    if(__builtin_amdgcn_readfirstlane(static_cast<int>(redo)))
-    {
+        for(int i = 0; i < U; ++i) lost[i * kUnitRows < BM ? 0 : 1] |= (rest[i] & 0xFFFFu) != 0u;
 #pragma unroll
         for(int i = 0; i < FM; ++i)
 #pragma unroll
-            for(int j = 0; j < FN; ++j) acc[i][j] = v4f32{0.0f, 0.0f, 0.0f, 0.0f};
-        // (a lane's four K indices of sixteen, of both operands in the same order)
-        const float *ra[FM], *rb[FN];
+            for(int j = 0; j < FN; ++j)
 #pragma unroll
-        for(int i = 0; i < FM; ++i)
+                for(int e = 0; e < 4; ++e) odd |= no_number(acc[i][j][e]);
+        // bit 0: a sum to look at; 1, 2: lost bits in A, in B
+        const uint32_t mine = (__any(odd) ? 1u : 0u) | (__any(lost[0]) ? 2u : 0u) | (__any(lost[1]) ? 4u : 0u);
+        if(lane == 0) flags[wave] = mine;
+        __syncthreads();
+        uint32_t looks = 0u;
+#pragma unroll
+        for(int w = 0; w < WGM * WGN; ++w) looks |= flags[w];
+        looks = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(looks)));
+        if(looks)
         {
-            const int64_t at = m0 + wm * (BM / WGM) + 16 * i + fr;
-            ra[i] = A + (at < p.M ? at : p.M - 1) * K + 4 * q;
-        }
-#pragma unroll
-        for(int j = 0; j < FN; ++j)
-        {
-            const int64_t at = n0 + wn * (BN / WGN) + 16 * j + fr;
-            rb[j] = B + (at < p.N ? at : p.N - 1) * K + 4 * q;
-        }
-        v4f32 fa[FM], fb[FN], ga[FM], gb[FN];
-        auto fetch = [&](v4f32 (&va)[FM], v4f32 (&vb)[FN], int64_t k) {      // (K indices behind the end give zeros)
-            const int left = static_cast<int>(end - k) - 4 * q;
-#pragma unroll
-            for(int i = 0; i < FM; ++i) va[i] = v4f32{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-            for(int j = 0; j < FN; ++j) vb[j] = v4f32{0.0f, 0.0f, 0.0f, 0.0f};
-            if(left >= 4)
+            float* const largest = reinterpret_cast<float*>(lds);      // of a row of A, then of B; with the sign bit where bits of the row are lost
+            if(looks & 6u)
             {
 #pragma unroll
-                for(int i = 0; i < FM; ++i) va[i] = *reinterpret_cast<const v4f32_any*>(ra[i] + k);
-#pragma unroll
-                for(int j = 0; j < FN; ++j) vb[j] = *reinterpret_cast<const v4f32_any*>(rb[j] + k);
-            }
-            else
-#pragma unroll
-                for(int e = 0; e < 3; ++e)
-                    if(e < left)
+                for(int i = 0; i < U; ++i)
+                {
+                    float m = 0.0f;
+                    if(looks & (i * kUnitRows < BM ? 4u : 2u))
                     {
+#pragma unroll 8
+                        for(int64_t k = first; k + kStepK <= end; k += kStepK)
+                        {
+                            const float* const at = row[i] + k + 8 * (tid % 4);
+                            const v4f32_any    u = *reinterpret_cast<const v4f32_any*>(at), v = *reinterpret_cast<const v4f32_any*>(at + 4);
 #pragma unroll
-                        for(int i = 0; i < FM; ++i) va[i][e] = ra[i][k + e];
-#pragma unroll
-                        for(int j = 0; j < FN; ++j) vb[j][e] = rb[j][k + e];
+                            for(int e = 0; e < 4; ++e) m = fmaxf(m, fmaxf(fabsf(u[e]), fabsf(v[e])));
+                        }
+                        for(int64_t k = end - (end - first) % kStepK + tid % 4; k < end; k += 4) m = fmaxf(m, fabsf(row[i][k]));
                     }
-        };
-        auto products = [&](const v4f32 (&va)[FM], const v4f32 (&vb)[FN]) {
+                    uint32_t r = rest[i] & 0xFFFFu;
 #pragma unroll
-            for(int e = 0; e < 4; ++e)
+                    for(int off = 1; off <= 2; off *= 2)
+                    {
+                        m = fmaxf(m, __shfl_xor(m, off));
+                        r |= static_cast<uint32_t>(__shfl_xor(static_cast<int>(r), off));
+                    }
+                    if(tid % 4 == 0) largest[tid / 4 + i * kUnitRows] = r ? -m : m;
+                }
+                __syncthreads();
+            }
+            const float n = static_cast<float>(end - first) * 0x1p-107f;
+            float       lb[FN][4];
+#pragma unroll
+            for(int j = 0; j < FN; ++j)
+#pragma unroll
+                for(int e = 0; e < 4; ++e) lb[j][e] = looks & 6u ? largest[BM + wn * (BN / WGN) + 16 * j + 4 * q + e] : 0.0f;
+#pragma unroll
+            for(int i = 0; i < FM; ++i)
+            {
+                const float la  = looks & 6u ? largest[wm * (BM / WGM) + 16 * i + fr] : 0.0f;
+                bool        bad = false;
+#pragma unroll
+                for(int j = 0; j < FN; ++j)
+#pragma unroll
+                    for(int e = 0; e < 4; ++e)
+                    {
+                        const float off = (__builtin_signbitf(la) ? fabsf(lb[j][e]) : 0.0f) + (__builtin_signbitf(lb[j][e]) ? fabsf(la) : 0.0f);
+                        bad |= no_number(acc[i][j][e]) || !(fabsf(acc[i][j][e]) >= off * n);
+                    }
+                if(__any(bad)) redo |= 1u << i;
+            }
+            redo = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(redo)));
+            if(looks & 6u) __syncthreads();      // (the epilogue stages its rows where the largest values are)
+            if(redo)
+            {
+                constexpr std::false_type some{};
+                constexpr int             kPieces = FM + FN > 4 ? 2 : 3;      // (two sets of them in registers)
+                point();
 #pragma unroll
                 for(int i = 0; i < FM; ++i)
+                    if(redo >> i & 1u)
 #pragma unroll
-                    for(int j = 0; j < FN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(vb[j][e], va[i][e], acc[i][j], 0, 0, 0);
-        };
+                        for(int j = 0; j < FN; ++j) acc[i][j] = v4f32{0.0f, 0.0f, 0.0f, 0.0f};
+                Piece now[kPieces], next[kPieces];
+#pragma unroll
+                for(int s = 0; s < kPieces; ++s)
+                    if(first + 16 * s < end) fetch(some, now[s], first + 16 * s);
 #pragma unroll 1
-        for(int64_t k = first; k < end; k += 32)
-        {
-            fetch(fa, fb, k);
-            if(k + 16 < end) fetch(ga, gb, k + 16);
-            products(fa, fb);
-            if(k + 16 < end) products(ga, gb);
+                for(int64_t k = first;; k += 16 * kPieces)
+                {
+#pragma unroll
+                    for(int s = 0; s < kPieces; ++s)
+                        if(k + 16 * (kPieces + s) < end) fetch(some, next[s], k + 16 * (kPieces + s));
+#pragma unroll
+                    for(int s = 0; s < kPieces; ++s)
+                        if(k + 16 * s < end) products(some, now[s]);
+                    if(k + 16 * kPieces >= end) break;
+#pragma unroll
+                    for(int s = 0; s < kPieces; ++s) now[s] = next[s];
+                }
+            }
         }
     }
     const uint32_t seen = (!SPLIT && p.amax_bits && wave == 0) ? __hip_atomic_load(p.amax_bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;

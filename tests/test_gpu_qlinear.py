@@ -600,6 +600,76 @@ def test_fp32_products_of_values_that_have_no_three_parts(tile, K):
         Q.qsync_debug_set_gemm_tile(-1)
 
 
+def _fp32_product(a, b, tile):
+    (M, K), N = a.shape, b.shape[0]
+    Q.qsync_debug_set_gemm_tile(tile)
+    try:
+        y = torch.full((M, N), 7.0, device="cuda")
+        w = torch.empty(max(256, Q.qsync_qlinear_workspace_bytes(Q.FP32, M, N, K)), dtype=torch.uint8, device="cuda")
+        Q.qsync_qlinear_fwd(Q.FP32, M, N, K, dev(a), None, dev(b), None, Q.PER_TENSOR, None, y, None, w)
+        return host(y)
+    finally:
+        Q.qsync_debug_set_gemm_tile(-1)
+
+
+@pytest.mark.parametrize("tile", [0, 1, 2])
+@pytest.mark.parametrize("K", [16, 17, 64, 75, 4100])
+def test_fp32_products_with_one_cause_to_be_formed_again(tile, K):
+    """One matrix for each thing that bf16 parts do not hold: values of either operand from 2^-100, which they do, down past 2^-110, where they
+    lose bits, to the smallest denormal, also beside an ordinary value that meets a zero; denormal products of ordinary values; a finite
+    overflow; an infinity; a NaN.  A 4100 long contraction runs in K splits.  One other nonzero a row and powers of two in the other operand
+    make every product exact, of the rows that are formed again and of those that are not."""
+    rng = np.random.default_rng(K)
+    M, N = 290, 150
+    full = lambda n: (rng.integers(0, 1 << 23, n).astype(np.uint32) | 0x3F800000).view(np.float32)
+    rows = np.array([0, 15, 16, 63, 64, 100, 129, 255, 256, 289])
+    cols = np.arange(M) % K
+    def ordinary():
+        a, b = np.zeros((M, K), np.float32), np.empty((N, K), np.float32)
+        a[np.arange(M), cols] = full(M)
+        b[:] = np.float32(2.0) ** rng.integers(-3, 4, (N, 1)).astype(np.float32)
+        return a, b
+    def check(what, a, b, swap=False):
+        say("fp32 formed again", what, tile, K, swap)
+        with np.errstate(over="ignore", invalid="ignore", under="ignore"):
+            want = np.zeros((M, N))
+            for m in range(M):
+                for k in np.flatnonzero(a[m]):
+                    want[m] += a[m, k].astype(np.float64) * b[:, k].astype(np.float64)
+            want = want.astype(np.float32)
+        got = _fp32_product(b, a, tile).T if swap else _fp32_product(a, b, tile)
+        np.testing.assert_array_equal(got, want, err_msg=what)
+        return want
+    for swap in (False, True):
+        for top in (-100, -109, -110, -111, -118, -126, -127, -140, -149):
+            a, b = ordinary()
+            x = np.ldexp(full(len(rows)).astype(np.float64) if top > -127 else np.ones(len(rows)), top).astype(np.float32)
+            a[rows, cols[rows]] = x
+            check(f"2^{top}", a, b, swap)
+            even = 2 * (rows % (K // 2))
+            a[rows] = 0.0
+            a[rows, even], a[rows, even + 1] = x, 1.0      # (the 1 meets a zero)
+            b[:, 1::2] = 0.0
+            assert (check(f"2^{top} beside 1", a, b, swap)[rows] < 2.0 ** -90).all()
+        a, b = ordinary()
+        a[rows, cols[rows]] = np.float32(2.0 ** -70) * full(len(rows))
+        b[::7] = np.float32(2.0 ** -64)                  # (products down to 2^-134; exact where their bits end above 2^-149)
+        a.view(np.uint32)[...] &= 0xFFFC0000
+        assert (np.abs(check("denormal products", a, b, swap)[rows][:, ::7]) < 2.0 ** -126).all()
+    a, b = ordinary()
+    a[rows, cols[rows]] = np.float32(3.0e38)
+    b[::7] = 2.0
+    assert np.isinf(check("overflow", a, b)[rows][:, ::7]).all()
+    for value in (np.inf, -np.inf, np.nan):
+        a, b = ordinary()
+        a[rows[3], cols[rows[3]]] = value
+        check(str(value), a, b)
+        check(str(value), a, b, True)
+    a, b = ordinary()
+    a[rows, cols[rows]] = np.finfo(np.float32).max
+    check("largest", a, np.minimum(b, 1.0))
+
+
 def test_bias_gradient_from_the_backward_call():
     """db requested from qsync_qlinear_bwd itself (not from the fused absmax pass)."""
     case = wl.ragged_case(208, 144, 80, seed=31, dtype=np.float16)
