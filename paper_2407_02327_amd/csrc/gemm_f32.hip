@@ -18,9 +18,12 @@
 // its instructions take 1.28 at 2.4 GHz (1.60 without the splitting, 1.68 without its LDS writes).  Operands go through registers, split
 // once a workgroup: each wavefront splitting its own fragments would repeat that two to four times.  fp32 instructions (16-byte rows
 // direct to LDS; others through registers) -> this, us: 8192x4096x1024 490 -> 306, 8192x1024x4096 479 -> 286, 4096x1024x8192 490 -> 300,
-// 2048^3 132 -> 87, 1000x1000x1001 36 -> 23, 1024^3 23.2 -> 23.4, 512^3 12.1 -> 10.5; over 60 shapes of 64..16384 by 64..4096 by 64..16384
-// 1.17 times faster on average, up to 15 % slower with K < 200 and a remainder (121x1232x112 6.5 -> 7.4); 40 operator steps 1.12 times
+// 2048^3 132 -> 87, 1000x1000x1001 36 -> 23, 1024^3 23.2 -> 23.4, 512^3 12.1 -> 10.5; over 142 shapes of 64..8192 by 64..4096 by 17..4096
+// 1.12 times faster on average; slower are some small ones of up to 100 and rows of fours (by 0.2 us, 503x73x36 5.1 -> 5.5) and large
+// outputs of few products for which the plan takes a larger tile than is best (3708x3160x29 23.7 -> 25.3).  40 operator steps 1.12 times
 // faster (0.97 to 1.49).
+// A remainder behind whole K tiles is loaded like those, as the row's last 32 floats; behind them and float by float, its loads were waited for
+// (263x343x80 6.8 -> 6.0 us, 7167x311x43 12.9 -> 10.1; alone, in fours: 3289x72x31 5.4 -> 4.8).
 #include "gemm_device.h"
 
 namespace qsync {
@@ -106,8 +109,9 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm_f32_kernel(const GemmK
         src[i]    = row[i] + first + 8 * g;
         put_at[i] = static_cast<uint32_t>(line / 16 * kFragment + ((line % 16 ^ 2 * g) + 16 * g) * 16);
     }
-    // whole K tiles, D of them on their way in registers; behind the last one it is loaded again (and not looked at)
-    const int whole = tiles > 0 ? static_cast<int>((end - first) / kStepK) : 0;
+    // whole K tiles, D of them on their way in registers; behind them the partial one that ends the row, as the row's last 32 floats
+    // (those that the tile before has already are taken as zeros); behind the last one it is loaded again (and not looked at)
+    const int whole = tiles > 0 ? static_cast<int>((end - first) / kStepK) : 0, tail = tiles > whole ? static_cast<int>((end - first) % kStepK) : 0;
     float     raw[D][U][8];
     uint32_t  rest[U], mask = 0xFFFF0000u;      // (the rest of a row's values: a piece stays in its row)
 #pragma unroll
@@ -117,20 +121,35 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm_f32_kernel(const GemmK
         const v4f32_any lo = *reinterpret_cast<const v4f32_any*>(src[i]), hi = *reinterpret_cast<const v4f32_any*>(src[i] + 4);
 #pragma unroll
         for(int e = 0; e < 4; ++e) { raw[decltype(set)::value][i][e] = lo[e]; raw[decltype(set)::value][i][4 + e] = hi[e]; }
-        src[i] += t + 1 < whole ? kStepK : 0;
+        src[i] += t + 1 < whole ? kStepK : (t + 1 == whole ? tail : 0);
     };
-    // The partial K tile that ends the row: every float by itself, behind the row's end the last one of it.  (Requested in front of the
-    // other tiles it is no faster, 60 shapes 1.170 instead of 1.174 times the fp32 instructions' rate.)
-    auto load_tail = [&]() {
-        const int64_t at   = first + static_cast<int64_t>(whole) * kStepK + 8 * (tid % 4);
-        const int64_t mine = end - at;
+    auto take_tail = [&]() __attribute__((always_inline)) {      // (into the first set)
+        static_assert(D <= 2);
+        const int  had = kStepK - tail - 8 * (tid % 4);
+        const bool odd = whole % D != 0;
 #pragma unroll
         for(int i = 0; i < U; ++i)
 #pragma unroll
             for(int e = 0; e < 8; ++e)
             {
-                const float v = row[i][at + e < K ? at + e : K - 1];
-                raw[0][i][e]  = e < mine ? v : 0.0f;
+                const float even = raw[0][i][e], other = raw[D - 1][i][e];
+                raw[0][i][e] = e < had ? 0.0f : (odd ? other : even);
+            }
+    };
+    // A partial tile that is all there is (of more than kF32ShortK floats): in fours, the last of which ends with the row.
+    auto load_tail = [&]() __attribute__((always_inline)) {
+        const int k0 = static_cast<int>(first) + 8 * (tid % 4), ends = static_cast<int>(end), last = static_cast<int>(K) - 4;
+#pragma unroll
+        for(int i = 0; i < U; ++i)
+#pragma unroll
+            for(int h = 0; h < 8; h += 4)
+            {
+                const int from = k0 + h < last ? k0 + h : last, by = k0 + h - from;      // (by four and more: nothing left)
+                v4f32     v    = *reinterpret_cast<const v4f32_any*>(row[i] + from);
+                v = by & 1 ? v4f32{v[1], v[2], v[3], 0.0f} : v;
+                v = by & 2 ? v4f32{v[2], v[3], 0.0f, 0.0f} : v;
+#pragma unroll
+                for(int e = 0; e < 4; ++e) raw[0][i][h + e] = k0 + h + e < ends ? v[e] : 0.0f;
             }
     };
     v4u32 part[3];
@@ -175,7 +194,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm_f32_kernel(const GemmK
     // of a piece as soon as its registers are free, and the next row's fragments.  Then the workgroup meets, and between the last
     // row's products the next tile's first fragments are read.
     enum { kAll, kNoLoads, kLast };
-    auto step = [&](auto mode, auto set, int t) {
+    auto step = [&](auto mode, auto set, int t) __attribute__((always_inline)) {
         constexpr int        MODE = decltype(mode)::value;
         const uint8_t* const cur = lds + (t & 1) * kStage;
         const uint8_t* const nxt = lds + (~t & 1) * kStage;
@@ -207,7 +226,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm_f32_kernel(const GemmK
             }
         });
     };
-    auto put_first = [&]() {
+    auto put_first = [&]() __attribute__((always_inline)) {
 #pragma unroll
         for(int i = 0; i < U; ++i)
         {
@@ -338,7 +357,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm_f32_kernel(const GemmK
             });
             if(whole < tiles)
             {
-                load_tail();
+                take_tail();
                 step(no_loads, c0, t);
                 ++t;
             }

@@ -533,6 +533,30 @@ def test_fp32_products_around_the_k_tiles(tile, K):
 
 
 @pytest.mark.parametrize("tile", [0, 1, 2])
+@pytest.mark.parametrize("whole", [0, 1, 2, 3, 40])
+def test_fp32_remainders(tile, whole):
+    """Every remainder behind 0 to 3 whole K tiles, whose floats are loaded with some that the tile before has already or, alone, shifted into
+    place; behind 40, in K splits the last of which is that remainder alone.  Operands off 16 bytes; integers, whose sums are exact, bit for bit."""
+    rng = np.random.default_rng(whole)
+    M, N = 70, 37
+    at = lambda v: torch.cat([torch.full((1,), float("nan"), device="cuda"), dev(v.reshape(-1)), torch.full((1,), float("nan"), device="cuda")])[1:-1]
+    Q.qsync_debug_set_gemm_tile(tile)
+    try:
+        for tail in (range(1, 32) if whole < 40 else (5, 20, 31)):
+            K = 32 * whole + tail
+            say("fp32 remainder", tile, K)
+            a, b = rng.integers(-2047, 2048, (M, K)).astype(np.float32), rng.integers(-15, 16, (N, K)).astype(np.float32)
+            need = Q.qsync_qlinear_workspace_bytes(Q.FP32, M, N, K)
+            assert (need > 0) == (whole == 40)
+            y = torch.full((M, N), float("nan"), device="cuda")
+            w = torch.empty(max(256, need), dtype=torch.uint8, device="cuda")
+            Q.qsync_qlinear_fwd(Q.FP32, M, N, K, at(a), None, at(b), None, Q.PER_TENSOR, None, y, None, w)
+            assert_bits_equal(host(y), (a.astype(np.float64) @ b.astype(np.float64).T).astype(np.float32), "Y")
+    finally:
+        Q.qsync_debug_set_gemm_tile(-1)
+
+
+@pytest.mark.parametrize("tile", [0, 1, 2])
 @pytest.mark.parametrize("K", [1, 3, 4, 7, 15, 16, 17, 32, 33, 64, 97, 160])
 def test_fp32_products_of_full_mantissas(tile, K):
     """One nonzero a row of A, so that every output is one product, with mantissas that leave the most out of the six bf16 products (all
