@@ -1707,9 +1707,13 @@ __global__ __launch_bounds__(kBlock) void dequantize_cols_kernel(const Ti* __res
 }
 
 // Contiguous int8 codes with one scale, any row length: vectors of 16 OUTPUT bytes, so that a wavefront's store is 1 KB of consecutive
-// memory.  Bound by HBM.  With 16 codes to a thread a store instruction filled every other 16 bytes: 16384x4096 to binary16 43.8 -> 32.4 us
-// (6.2 TB/s) inside a maximum + quantize + dequantize sequence, with streaming stores from 2^24 elements on (an output that the
-// L2s do not hold anyway; 35.9 without); 10740x1569 from an element a thread.
+// memory.  Bound by HBM.  With 16 codes to a thread a store instruction filled every other 16 bytes: 16384x4096 to binary16 alone 38.4 -> 31.6
+// us (6.4 TB/s), 4096x4096 15.4 -> 10.9; 10740x1569 from an element a thread.
+// Streaming stores from 128 MB of output on: with its codes and the tensor that those came from it no longer fits the memory-side cache of
+// 256 MB, and plain stores push that tensor out.  Maximum + quantize + dequantize, plain and streamed, to binary16 of 80 MB 61.8 and 63.8 us, with
+// an addition that reads the output 102.4 and 108.3; of 128 MB 95.3 and 91.7, 177.1 and 169.8; to fp32 of 192 MB 126 and 110, 239 and 223.
+// Smaller outputs are what the next call finds there (64 MB with a GEMM behind it 52.5 and 69.2, 16 codes to a thread 56.7).  It costs
+// whoever dequantizes codes of that size alone and reads them at once: 128 MB to binary16 with an addition 93.6 and 109.
 template <typename To, int U, bool STREAM>
 __global__ __launch_bounds__(kBlock) void dequantize_flat_kernel(const int8_t* __restrict__ a, int64_t n, float ts_host,
                                                                  const float* __restrict__ ts_dev, To* __restrict__ y)
@@ -2464,6 +2468,7 @@ static hipError_t dequantize_typed(const void* a, int64_t rows, int64_t cols, in
             };
             if(n < (int64_t(1) << 20)) go(std::integral_constant<int, 1>{}, std::false_type{});
             else if(n < (int64_t(1) << 24)) go(std::integral_constant<int, 4>{}, std::false_type{});
+            else if(n * static_cast<int64_t>(sizeof(To)) < (int64_t(1) << 27)) go(std::integral_constant<int, 2>{}, std::false_type{});
             else go(std::integral_constant<int, 8>{}, std::true_type{});
             return hipGetLastError();
         }

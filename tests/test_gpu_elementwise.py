@@ -378,6 +378,22 @@ def test_dequantize_contiguous_codes_of_any_length(ydt, rows, cols):
         assert (host(y)[:off_y] == 7.0).all() and (host(y)[off_y + rows * cols:] == 7.0).all()
 
 
+@pytest.mark.parametrize("ydt", [torch.float32, torch.float16])
+@pytest.mark.parametrize("more", [-1, 0, 13])
+def test_dequantize_outputs_around_128_MB(ydt, more):
+    """The size from which outputs are streamed: bits of the same codes dequantized in pieces, which are not."""
+    n = (1 << 27) // (4 if ydt == torch.float32 else 2) + more
+    say("dequantize around 128 MB", ydt, more)
+    a = torch.randint(-127, 128, (n,), dtype=torch.int8, device="cuda", generator=torch.Generator(device="cuda").manual_seed(more + 5))
+    scale = torch.full((1,), 0.0123456789, device="cuda")
+    y, want = (torch.full((n + 8,), 7.0, dtype=ydt, device="cuda") for _ in range(2))
+    Q.qsync_dequantize(a, 1, n, n, None, None, 1.0, None, y, tensor_scale_dev_opt=scale)
+    for at in range(0, n, 1 << 22):
+        k = min(1 << 22, n - at)
+        Q.qsync_dequantize(a[at:], 1, k, k, None, None, 1.0, None, want[at:], tensor_scale_dev_opt=scale)
+    assert torch.equal(y.view(torch.uint8), want.view(torch.uint8)) and (y[n:] == 7.0).all()
+
+
 @pytest.mark.parametrize("dtype", [np.float32, np.float16])
 @pytest.mark.parametrize("rnd", ["nearest", "stochastic", "floor"])
 @pytest.mark.parametrize("rows,cols", [(1, 7), (1, 8), (1, 9), (3, 5), (5, 3), (91, 11), (1, 8191), (8193, 1), (1024, 9), (33, 999)])
