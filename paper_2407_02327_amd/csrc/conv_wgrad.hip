@@ -310,11 +310,14 @@ int launch_conv3x3_wgrad(const GemmProblem& p, int max_splits, void* workspace, 
     if(splits > a.chunks / (4 * kWgradWaves)) splits = a.chunks / (4 * kWgradWaves);      // ... of four chunks a wavefront at least
     if(splits > max_splits) splits = max_splits;
     if(splits < 1) splits = 1;
-    // Small products are over before a ring pays, int8 ones later than binary16 (45 drawn shapes, pixels x C x N: binary16 from 2.3e8 on 1.12
-    // times as fast on average, below it 0.97; int8 from 6e8 on 1.11, below it 0.91), and nothing makes up for idle units (binary16
-    // 21x9x40 480->264, 150 workgroups, 50.7 -> 54.2).
-    const int64_t work = p.K * p.conv_C * p.M;
-    if(work < (p.prec == 16 ? 230000000 : 600000000) || tiles * splits < 160) return 0;
+    // Whole training steps, in which both operands are in cache behind their conversion (320 drawn shapes, gathering -> ring): the ring pays
+    // from a size on, counted in whole rows of tiles, int8 only over many pixels, as a wavefront's start and the sum of eight weigh more against
+    // its faster instructions (10206 pixels 128->240 62.0 -> 65.2 us, 38016 448->32 104.8 -> 97.8), and not with idle units (binary16 4x47x33
+    // 424->336, 162 workgroups, 8 us slower).  Binary16 61 shapes 341 us faster in sum, eight of fewer than 5000 pixels or 230 workgroups up to
+    // 1.3 us slower, with dW closer to 64 bits (24x14x14 256->256 59.2 -> 59.7 us, error 1.7e-7 -> 1.0e-7); int8 23 shapes 115 us faster, two 0.7
+    // slower.  Of 260 others 72 go to the ring, 379 us faster in sum, 1.8 us slower at most.
+    const int64_t work = p.K * p.conv_C * a.tiles_m * kWgradRows;
+    if(work < (p.prec == 16 ? 250000000 : 800000000) || (p.prec == 8 && p.K < 20000) || tiles * splits < 190) return 0;
     a.splits  = static_cast<int>(splits);
     a.per     = (a.chunks + a.splits * kWgradWaves - 1) / (a.splits * kWgradWaves);
     a.partial = workspace;

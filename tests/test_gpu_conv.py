@@ -332,7 +332,7 @@ def test_weight_gradient_with_more_output_channels_than_the_gather_addresses(tag
     (Q.FP16, 3, 1, 31, 4096, 1032), (Q.FP16, 9000, 2, 2, 88, 80), (Q.INT8, 64, 56, 56, 64, 64), (Q.INT8, 50, 33, 38, 272, 64), (Q.INT8, 46, 8, 191, 96, 96),
     (Q.INT8, 46, 8, 192, 96, 96), (Q.INT8, 65, 300, 1, 96, 336)])
 def test_weight_gradient_of_large_convolutions(tag, b, H, W, C, N):
-    """The sizes that go through the ring of pixels (pixels x C x N from 2.3e8 binary16 and 6e8 int8): last chunks that are partial, last
+    """Sizes that go through the ring of pixels and some that do not: last chunks that are partial, last
     groups of eight channels and of few outputs, images of one row or one or two columns, as wide as the ring reaches (W + 1 pixels in three
     chunks of 32 or 64) and one wider, which the gathering GEMM does.  Small integers: every sum is exact in any order."""
     say("wgrad ring", tag, b, H, W, C, N)
