@@ -57,6 +57,12 @@ void qsync_debug_set_gemm_persistent(int mode);
 int qsync_debug_last_gradient_pair(void);
 int qsync_debug_last_gradient_splits(void);
 
+/*
+ * qsync_debug_last_wgrad_ring - for tests: the K splits that the pixel ring left of the calling thread's last qsync_conv3x3_wgrad
+ * that passed its argument checks, or 0 when a GEMM (gathering, or over transposed copies) did it.
+ */
+int qsync_debug_last_wgrad_ring(void);
+
 #ifdef __cplusplus
 }
 #endif

@@ -735,6 +735,7 @@ int qsync_conv3x3_wgrad(int tag, int64_t nimg, int64_t H, int64_t W, int64_t C, 
     const int esz = tag == QSYNC_INT8 ? 1 : 2;
     if((C * esz) % 16 != 0 || (N * esz) % 16 != 0 || !aligned16(xq) || !aligned16(dyq)) return QSYNC_ERR_ALIGN;
     hipStream_t st  = static_cast<hipStream_t>(stream);
+    last_wgrad_ring() = 0;
     if(wgrad_gathers(N))
     {
         const int64_t  M    = nimg * H * W;
@@ -807,6 +808,7 @@ void qsync_debug_set_gemm_tile(int tile) { set_gemm_tile_override(tile); }
 void qsync_debug_set_gemm_persistent(int mode) { set_gemm_persistent_mode(mode); }
 int qsync_debug_last_gradient_pair(void) { return g_last_pair_tile; }
 int qsync_debug_last_gradient_splits(void) { return g_last_pair_splits; }
+int qsync_debug_last_wgrad_ring(void) { return last_wgrad_ring(); }
 
 static int conv3x3_fwd_impl(int tag, int64_t nimg, int64_t H, int64_t W, int64_t C, int64_t N, const void* xq,
                             const float* sx, const void* wq, const float* sw, int wgran, const float* bias_opt, void* y,

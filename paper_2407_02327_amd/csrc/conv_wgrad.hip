@@ -288,6 +288,12 @@ template <typename TR> hipError_t launch_wgrad(const ConvWgradArgs& a, hipStream
 
 }  // namespace
 
+int& last_wgrad_ring()
+{
+    static thread_local int splits = 0;
+    return splits;
+}
+
 // `p`: a weight gradient as launch_gemm takes it (conv_H > 0, tn), checked; at most max_splits partial products fit in `workspace`.  Returns
 // the number of splits left there, 0 (nothing launched) where the image is too wide for the ring or the gathering GEMM is the faster.
 int launch_conv3x3_wgrad(const GemmProblem& p, int max_splits, void* workspace, hipStream_t stream, hipError_t* error)
@@ -321,6 +327,7 @@ int launch_conv3x3_wgrad(const GemmProblem& p, int max_splits, void* workspace, 
     a.splits  = static_cast<int>(splits);
     a.per     = (a.chunks + a.splits * kWgradWaves - 1) / (a.splits * kWgradWaves);
     a.partial = workspace;
+    last_wgrad_ring() = a.splits;
     *error = p.prec == 8 ? launch_wgrad<I8Traits>(a, stream) : launch_wgrad<F16Traits>(a, stream);
     return a.splits;
 }

@@ -179,6 +179,7 @@ void set_gemm_persistent_mode(int mode);
 hipError_t launch_conv3x3(const GemmProblem& p, int force_tile, bool* taken, hipStream_t stream);
 // Weight gradient of a convolution by a kernel of its own (conv_wgrad.hip): partial products in `workspace`, as many splits as are returned.
 int launch_conv3x3_wgrad(const GemmProblem& p, int max_splits, void* workspace, hipStream_t stream, hipError_t* error);
+int& last_wgrad_ring();      // the calling thread's last such splits, see qsync_debug_last_wgrad_ring
 // Few rows or a small product, plain epilogue (gemm_rows.hip); *taken is false, and nothing launched, for any other problem.
 hipError_t launch_gemm_rows(const GemmProblem& p, bool* taken, hipStream_t stream);
 bool gemm_rows_takes(const GemmProblem& p);

@@ -65,6 +65,7 @@ SIGNATURES = {
     "qsync_debug_set_gemm_persistent": (None, [_i]),
     "qsync_debug_last_gradient_pair": (_i, []),
     "qsync_debug_last_gradient_splits": (_i, []),
+    "qsync_debug_last_wgrad_ring": (_i, []),
     "qsync_conv3x3_wgrad": (_i, [_i, _i64, _i64, _i64, _i64, _i64, _vp, _vp, _vp, _vp, _vp, _i, _vp, _vp, _sz, _vp]),
     "qsync_conv3x3_wgrad_workspace_bytes": (_sz, [_i, _i64, _i64, _i64, _i64, _i64]),
     "qsync_conv3x3_prepare_weights": (_i, [_vp, _i, _i64, _i64, _i, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _sz, _vp]),
@@ -285,6 +286,10 @@ def qsync_debug_last_gradient_pair() -> int:
 
 def qsync_debug_last_gradient_splits() -> int:
     return lib.qsync_debug_last_gradient_splits()
+
+
+def qsync_debug_last_wgrad_ring() -> int:
+    return lib.qsync_debug_last_wgrad_ring()
 
 
 def qsync_conv3x3_wflip(w, N, C, wflip, stream=None) -> None:

@@ -327,14 +327,16 @@ def test_weight_gradient_with_more_output_channels_than_the_gather_addresses(tag
         assert torch.equal(dw[n0:n0 + (1 << 22)].float(), want), n0
 
 
-@pytest.mark.parametrize("tag,b,H,W,C,N", [
-    (Q.FP16, 24, 14, 14, 256, 256), (Q.FP16, 28, 23, 9, 296, 168), (Q.FP16, 25, 41, 51, 80, 56), (Q.FP16, 58, 45, 34, 272, 16), (Q.FP16, 20, 20, 95, 64, 120), (Q.FP16, 20, 20, 96, 64, 120),
-    (Q.FP16, 3, 1, 31, 4096, 1032), (Q.FP16, 9000, 2, 2, 88, 80), (Q.INT8, 64, 56, 56, 64, 64), (Q.INT8, 50, 33, 38, 272, 64), (Q.INT8, 46, 8, 191, 96, 96),
-    (Q.INT8, 46, 8, 192, 96, 96), (Q.INT8, 65, 300, 1, 96, 336)])
-def test_weight_gradient_of_large_convolutions(tag, b, H, W, C, N):
-    """Sizes that go through the ring of pixels and some that do not: last chunks that are partial, last
-    groups of eight channels and of few outputs, images of one row or one or two columns, as wide as the ring reaches (W + 1 pixels in three
-    chunks of 32 or 64) and one wider, which the gathering GEMM does.  Small integers: every sum is exact in any order."""
+@pytest.mark.parametrize("tag,b,H,W,C,N,splits", [
+    (Q.FP16, 24, 14, 14, 256, 256, 4), (Q.FP16, 28, 23, 9, 296, 168, 4), (Q.FP16, 25, 41, 51, 80, 56, 42), (Q.FP16, 58, 45, 34, 272, 16, 13),
+    (Q.FP16, 20, 20, 95, 64, 120, 28), (Q.FP16, 20, 20, 96, 64, 120, 0), (Q.FP16, 3, 1, 31, 4096, 1032, 0), (Q.FP16, 500, 1, 31, 128, 136, 9),
+    (Q.FP16, 9000, 2, 2, 88, 80, 21), (Q.FP16, 50, 20, 20, 512, 400, 1), (Q.INT8, 64, 56, 56, 64, 64, 56), (Q.INT8, 50, 33, 38, 272, 64, 13),
+    (Q.INT8, 46, 8, 191, 96, 96, 21), (Q.INT8, 46, 8, 192, 96, 96, 0), (Q.INT8, 65, 300, 1, 96, 336, 0), (Q.INT8, 90, 300, 1, 96, 336, 7),
+    (Q.INT8, 1000, 1, 50, 64, 320, 12), (Q.INT8, 30000, 1, 1, 192, 160, 7), (Q.INT8, 50, 20, 20, 512, 400, 1)])
+def test_weight_gradient_of_large_convolutions(tag, b, H, W, C, N, splits):
+    """Sizes that go through the ring of pixels, in that many splits, and some that do not: last chunks that are partial, last
+    groups of eight channels and of few outputs, images of one row, of one or two columns and of one pixel, as wide as the ring reaches (W + 1
+    pixels in three chunks of 32 or 64) and one wider, which the gathering GEMM does.  Small integers: every sum is exact in any order."""
     say("wgrad ring", tag, b, H, W, C, N)
     g = torch.Generator(device="cuda").manual_seed(b + C)
     dt = torch.int8 if tag == Q.INT8 else torch.float16
@@ -347,4 +349,5 @@ def test_weight_gradient_of_large_convolutions(tag, b, H, W, C, N):
     room = torch.full((max(256, Q.qsync_conv3x3_wgrad_workspace_bytes(tag, b, H, W, C, N)),), 255, dtype=torch.uint8, device="cuda")
     dw = torch.full((N, 9 * C), float("nan"), device="cuda")
     Q.qsync_conv3x3_wgrad(tag, b, H, W, C, N, x.to(dt), s, dy.to(dt), s, dw, None, room)
+    assert Q.qsync_debug_last_wgrad_ring() == splits
     assert torch.equal(dw, want)
