@@ -496,7 +496,7 @@ def test_fp32_operands_that_are_no_16_byte_rows(M, N, K):
         Q.qsync_debug_set_gemm_tile(tile)
         try:
             need = Q.qsync_qlinear_workspace_bytes(Q.FP32, M, N, K)
-            rooms = [need] + ([0] if K % 4 else [])
+            rooms = [need, 0]
             for dt, room in [(d, r) for d in (torch.float32, torch.float16) for r in rooms]:
                 say("odd fp32", M, N, K, tile, dt, room)
                 y = torch.full((M, N), float("nan"), dtype=dt, device="cuda")
@@ -530,6 +530,51 @@ def test_fp32_products_around_the_k_tiles(tile, K):
             assert_bits_equal(host(y), (a.astype(np.float64) @ b.astype(np.float64).T + bias).astype(np.float32), "Y")
     finally:
         Q.qsync_debug_set_gemm_tile(-1)
+
+
+@pytest.mark.parametrize("M, N, K", [(64, 64, 4096), (130, 68, 5004)])
+def test_fp32_forward_with_less_room_than_its_splits_ask_for(M, N, K):
+    """Rows of whole 16 bytes without a workspace, with some and with one byte too few: unsplit, the output's maximum and codes from the
+    product itself instead of the sum of the splits.  Integers: the same bits as in splits."""
+    need = Q.qsync_qlinear_workspace_bytes(Q.FP32, M, N, K)
+    assert need > 1024
+    rng = np.random.default_rng(K)
+    a, b = rng.integers(-31, 32, (M, K)).astype(np.float32), rng.integers(-15, 16, (N, K)).astype(np.float32)
+    bias = rng.integers(-99, 100, N).astype(np.float32)
+    want = (a.astype(np.float64) @ b.astype(np.float64).T + bias).astype(np.float32)
+    inv = dev(np.array([127.0 / np.abs(want).max()], np.float32))
+    codes = []
+    for room in (need, need - 1, 1024, 0):
+        say("fp32 forward, room", M, N, K, room)
+        w = torch.full((room,), 255, dtype=torch.uint8, device="cuda") if room else None
+        y, yq, amax = torch.full((M, N), float("nan"), device="cuda"), torch.full((M, N), 99, dtype=torch.int8, device="cuda"), torch.zeros(1, device="cuda")
+        Q.qsync_qlinear_fwd_codes(Q.FP32, M, N, K, dev(a), None, dev(b), None, Q.PER_TENSOR, dev(bias), y, 8, inv, yq, amax, w)
+        assert_bits_equal(host(y), want, "Y")
+        assert float(amax) == np.abs(want).max()
+        codes.append(host(yq))
+        assert_bits_equal(codes[-1], codes[0], "codes")
+
+
+@pytest.mark.parametrize("M, N, K", [(64, 4096, 64), (4096, 64, 68), (2048, 2052, 36)])
+def test_fp32_backward_with_less_room_than_its_splits_ask_for(M, N, K):
+    """Either gradient's contraction, or both, in K splits by the plan; without a workspace, and with room for the column sums only, unsplit."""
+    r256 = lambda v: (v + 255) // 256 * 256
+    full = Q.qsync_qlinear_bwd_workspace_bytes(Q.FP32, M, N, K)
+    parts = r256(Q.qsync_qlinear_workspace_bytes(Q.FP32, M, K, N)) + r256(Q.qsync_qlinear_workspace_bytes(Q.FP32, N, K, M))
+    assert parts > 0 and full > parts
+    rng = np.random.default_rng(N)
+    dy, x, w = (rng.integers(-7, 8, sh).astype(np.float32) for sh in ((M, N), (M, K), (N, K)))
+    t = lambda v: dev(np.ascontiguousarray(v.T))
+    for room, with_db in ((full, True), (full - 1, True), (full - parts, True), (0, False)):
+        say("fp32 backward, room", M, N, K, room, with_db)
+        ws = torch.full((room,), 255, dtype=torch.uint8, device="cuda") if room else None
+        dx, dw, db = (torch.full(sh, float("nan"), device="cuda") for sh in ((M, K), (N, K), (N,)))
+        Q.qsync_qlinear_bwd(Q.FP32, M, N, K, dev(dy), t(dy), None, t(x), None, t(w), None, Q.PER_TENSOR, dx, dw, db if with_db else None,
+                            dev(dy) if with_db else None, None, None, ws)
+        assert_bits_equal(host(dx), dy @ w, "dX")
+        assert_bits_equal(host(dw), dy.T @ x, "dW")
+        if with_db:
+            assert_bits_equal(host(db), dy.sum(0), "db")
 
 
 @pytest.mark.parametrize("tile", [0, 1, 2])
@@ -718,8 +763,8 @@ def test_fp32_tag_equals_plain_matmul():
 
 
 def test_fp32_tag_on_the_matrix_cores_stays_fp32_accurate():
-    """Rows that are 16-byte multiples run the fp32 matrix instructions (the K axis is summed in another order
-    than the textbook loop): the result must stay within fp32 rounding of the naive fp32 product."""
+    """fp32 products are sums of bf16 products in another order than the textbook loop's: the result must stay within
+    fp32 rounding of the naive fp32 product."""
     case = wl.ragged_case(96, 80, 256, seed=8)
     say("fp32 on matrix cores")
     op = QLinear(Q.FP32, 96, 80, 256, x_dtype=torch.float32, y_dtype=torch.float32, dx_dtype=torch.float32)
@@ -980,7 +1025,7 @@ def test_forward_epilogue_collects_the_output_maximum(tile, tag, ydt):
     try:
         shapes = [(300, 264, 272), (257, 131, 144), (64, 128, 128), (192, 264, 4096), (96, 101, 4096)]   # the last two split K
         if tag == Q.FP32:
-            shapes.append((130, 70, 50))          # rows that are not 16-byte multiples: the any-shape kernel
+            shapes.append((130, 70, 50))          # rows that are not 16-byte multiples
         for (M, N, K) in shapes:
             rng = np.random.default_rng(M * 7 + N)
             x = rng.standard_normal((M, K)).astype(np.float32)
