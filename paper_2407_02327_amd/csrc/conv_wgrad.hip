@@ -14,6 +14,8 @@
 // 24 KB, 31.3 us at the first shape), four wavefronts (30.2; 1 % to 10 % slower beyond 9e8, faster below), one chunk ahead (31.0).
 #include "gemm_device.h"
 
+#include <cmath>
+
 namespace qsync {
 
 namespace {
@@ -295,8 +297,8 @@ int& last_wgrad_ring()
 }
 
 // `p`: a weight gradient as launch_gemm takes it (conv_H > 0, tn), checked; at most max_splits partial products fit in `workspace`.  Returns
-// the number of splits left there, 0 (nothing launched) where the image is too wide for the ring or the gathering GEMM is the faster.
-int launch_conv3x3_wgrad(const GemmProblem& p, int max_splits, void* workspace, hipStream_t stream, hipError_t* error)
+// the number of splits left there, 0 (nothing launched) where the image is too wide for the ring or the gathering GEMM, `gemm_us`, is the faster.
+int launch_conv3x3_wgrad(const GemmProblem& p, int max_splits, double gemm_us, void* workspace, hipStream_t stream, hipError_t* error)
 {
     const int esz = p.prec / 8, ch = 64 / esz;
     ConvWgradArgs a{};
@@ -316,16 +318,18 @@ int launch_conv3x3_wgrad(const GemmProblem& p, int max_splits, void* workspace, 
     if(splits > a.chunks / (4 * kWgradWaves)) splits = a.chunks / (4 * kWgradWaves);      // ... of four chunks a wavefront at least
     if(splits > max_splits) splits = max_splits;
     if(splits < 1) splits = 1;
-    // Whole training steps, in which both operands are in cache behind their conversion (320 drawn shapes, gathering -> ring): the ring pays
-    // from a size on, counted in whole rows of tiles, int8 only over many pixels, as a wavefront's start and the sum of eight weigh more against
-    // its faster instructions (10206 pixels 128->240 62.0 -> 65.2 us, 38016 448->32 104.8 -> 97.8), and not with idle units (binary16 4x47x33
-    // 424->336, 162 workgroups, 8 us slower).  Binary16 61 shapes 341 us faster in sum, eight of fewer than 5000 pixels or 230 workgroups up to
-    // 1.3 us slower, with dW closer to 64 bits (24x14x14 256->256 59.2 -> 59.7 us, error 1.7e-7 -> 1.0e-7); int8 23 shapes 115 us faster, two 0.7
-    // slower.  Of 260 others 72 go to the ring, 379 us faster in sum, 1.8 us slower at most.
-    const int64_t work = p.K * p.conv_C * a.tiles_m * kWgradRows;
-    if(work < (p.prec == 16 ? 250000000 : 800000000) || (p.prec == 8 && p.K < 20000) || tiles * splits < 190) return 0;
-    a.splits  = static_cast<int>(splits);
-    a.per     = (a.chunks + a.splits * kWgradWaves - 1) / (a.splits * kWgradWaves);
+    a.splits = static_cast<int>(splits);
+    a.per    = (a.chunks + a.splits * kWgradWaves - 1) / (a.splits * kWgradWaves);
+    // The ring's time against the plan's for the gathering GEMM: a start and an end, a wavefront's chunks one after the other, and the partial
+    // products' way to memory and back, as in plan_gemm.  Fitted to 843 whole training steps, in which both operands are in cache behind their
+    // conversion.  int8 122 of 576 go to the ring, 717 us faster in sum, four slower, by 2 us at most; binary16 208 of 267, 1191 us faster, 29
+    // slower, by 1.8 us at most and with dW closer to 64 bits (24x14x14 256->256 59.0 -> 59.7 us, error 1.7e-7 -> 1.0e-7).  A rule on sizes, pixels
+    // x C x N from 6e8 and 2.3e8, left 72 and 28 slower, by up to 8 us, and 206 and 109 us ungained.  Of 300 other steps 101 go to the ring, 613 us
+    // faster in sum, eleven slower, by 2.3 us at most.
+    const double rounds = std::ceil(static_cast<double>(tiles * splits) / 256.0);
+    const double parts  = static_cast<double>(splits + 1) * a.N * 9.0 * a.C * 4.0 / 6.24e6;
+    const double us     = p.prec == 16 ? 6.2 + 1.05 * a.per * rounds + 3.0 * parts : 11.0 + 1.0 * a.per * rounds + 2.5 * parts;
+    if(us >= gemm_us) return 0;
     a.partial = workspace;
     last_wgrad_ring() = a.splits;
     *error = p.prec == 8 ? launch_wgrad<I8Traits>(a, stream) : launch_wgrad<F16Traits>(a, stream);

@@ -1501,7 +1501,7 @@ hipError_t launch_gemm(const GemmProblem& p, const GemmPlan& plan, void* workspa
     if(p.conv_H > 0 && p.tn && splits > 1 && g_tile_override < 0)
     {
         hipError_t e   = hipSuccess;
-        const int  own = launch_conv3x3_wgrad(p, splits, workspace, stream, &e);
+        const int  own = launch_conv3x3_wgrad(p, splits, plan.us, workspace, stream, &e);
         if(own > 0) return e != hipSuccess ? e : reduce_splits(p, own, workspace, stream, fold);
     }
     // The persistent kernel is opt-in.  Its write-back of a tile overlaps the next tile's K loop, which on 32x32 instructions gained

@@ -177,8 +177,9 @@ void set_gemm_persistent_mode(int mode);
 // GemmProblem with conv_H > 0, not tn, checked by launch_gemm: input tile kept in LDS (conv3x3.hip); *taken is false, and nothing
 // launched, where that does not fit.  force_tile >= 0: pixels of a workgroup, 256 >> force_tile.
 hipError_t launch_conv3x3(const GemmProblem& p, int force_tile, bool* taken, hipStream_t stream);
-// Weight gradient of a convolution by a kernel of its own (conv_wgrad.hip): partial products in `workspace`, as many splits as are returned.
-int launch_conv3x3_wgrad(const GemmProblem& p, int max_splits, void* workspace, hipStream_t stream, hipError_t* error);
+// Weight gradient of a convolution by a kernel of its own (conv_wgrad.hip), where it is estimated to take no longer than the GEMM's
+// `gemm_us`: partial products in `workspace`, as many splits as are returned.
+int launch_conv3x3_wgrad(const GemmProblem& p, int max_splits, double gemm_us, void* workspace, hipStream_t stream, hipError_t* error);
 int& last_wgrad_ring();      // the calling thread's last such splits, see qsync_debug_last_wgrad_ring
 // Few rows or a small product, plain epilogue (gemm_rows.hip); *taken is false, and nothing launched, for any other problem.
 hipError_t launch_gemm_rows(const GemmProblem& p, bool* taken, hipStream_t stream);

@@ -599,17 +599,16 @@ def test_conv_forward_with_maximum_validation():
 
 
 def test_weight_gradient_path_of_a_convolution():
-    """Which sizes the pixel ring takes: from so much work, counted in whole rows of 64 outputs, over so many pixels (int8), with units enough;
-    the next call of any kind starts from none."""
+    """Which sizes the pixel ring takes: many pixels for the outputs, units enough, images it is wide enough for; every call starts from none."""
     def ring(tag, b, H, W, C, N):
         at = lambda v: P(v << 30)
         rc = lib.qsync_conv3x3_wgrad(tag, b, H, W, C, N, at(1), at(2), at(3), at(4), at(5), qsync.F32, None, at(6), 1 << 34, None)
         assert rc == qsync.ERR_HIP                                # (no GPU here; the arguments themselves are fine)
         return lib.qsync_debug_last_wgrad_ring()
 
-    assert ring(qsync.FP16, 64, 56, 56, 64, 64) > 0
-    assert ring(qsync.FP16, 64, 56, 56, 64, 96) == ring(qsync.FP16, 64, 56, 56, 64, 128) > 0
-    assert ring(qsync.FP16, 3, 47, 33, 424, 336) == 0             # 162 workgroups
-    assert ring(qsync.FP16, 64, 56, 17, 64, 64) == 0 and ring(qsync.FP16, 64, 56, 18, 64, 64) > 0      # 2.5e8
-    assert ring(qsync.INT8, 64, 56, 54, 64, 64) == 0 and ring(qsync.INT8, 64, 56, 55, 64, 64) > 0      # 8e8
-    assert ring(qsync.INT8, 1, 199, 100, 512, 448) == 0 and ring(qsync.INT8, 1, 200, 100, 512, 448) == 1
+    for tag, wide in ((qsync.FP16, 95), (qsync.INT8, 191)):
+        assert ring(tag, 64, 56, 56, 64, 64) > 0
+        assert ring(tag, 8, 14, 14, 64, 64) == 0
+        assert ring(tag, 3, 47, 33, 432, 336) == 0                # 162 workgroups
+        assert ring(tag, 50, 20, 20, 512, 400) == 1
+        assert ring(tag, 100, 16, wide, 96, 96) > 0 and ring(tag, 100, 16, wide + 1, 96, 96) == 0

@@ -331,7 +331,7 @@ def test_weight_gradient_with_more_output_channels_than_the_gather_addresses(tag
     (Q.FP16, 24, 14, 14, 256, 256, 4), (Q.FP16, 28, 23, 9, 296, 168, 4), (Q.FP16, 25, 41, 51, 80, 56, 42), (Q.FP16, 58, 45, 34, 272, 16, 13),
     (Q.FP16, 20, 20, 95, 64, 120, 28), (Q.FP16, 20, 20, 96, 64, 120, 0), (Q.FP16, 3, 1, 31, 4096, 1032, 0), (Q.FP16, 500, 1, 31, 128, 136, 9),
     (Q.FP16, 9000, 2, 2, 88, 80, 21), (Q.FP16, 50, 20, 20, 512, 400, 1), (Q.INT8, 64, 56, 56, 64, 64, 56), (Q.INT8, 50, 33, 38, 272, 64, 13),
-    (Q.INT8, 46, 8, 191, 96, 96, 21), (Q.INT8, 46, 8, 192, 96, 96, 0), (Q.INT8, 65, 300, 1, 96, 336, 0), (Q.INT8, 90, 300, 1, 96, 336, 7),
+    (Q.INT8, 100, 8, 191, 96, 96, 21), (Q.INT8, 100, 8, 192, 96, 96, 0), (Q.INT8, 65, 300, 1, 96, 336, 0), (Q.INT8, 220, 300, 1, 96, 336, 7),
     (Q.INT8, 1000, 1, 50, 64, 320, 12), (Q.INT8, 30000, 1, 1, 192, 160, 7), (Q.INT8, 50, 20, 20, 512, 400, 1)])
 def test_weight_gradient_of_large_convolutions(tag, b, H, W, C, N, splits):
     """Sizes that go through the ring of pixels, in that many splits, and some that do not: last chunks that are partial, last
