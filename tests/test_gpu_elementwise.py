@@ -396,10 +396,11 @@ def test_dequantize_outputs_around_128_MB(ydt, more):
 
 @pytest.mark.parametrize("dtype", [np.float32, np.float16])
 @pytest.mark.parametrize("rnd", ["nearest", "stochastic", "floor"])
-@pytest.mark.parametrize("rows,cols", [(1, 7), (1, 8), (1, 9), (3, 5), (5, 3), (91, 11), (1, 8191), (8193, 1), (1024, 9), (33, 999)])
+@pytest.mark.parametrize("rows,cols", [(1, 7), (1, 8), (1, 9), (3, 5), (5, 3), (91, 11), (1, 8191), (8193, 1), (1024, 9), (33, 999), (1, 249999), (1, 250001),
+                                       (8195, 31), (389999, 1), (1, 390001), (399, 1001), (515, 777)])
 def test_quantize_contiguous_rows_of_any_length(dtype, rnd, rows, cols):
-    """Codes of a contiguous tensor whose rows are no multiple of eight, around a group and a workgroup's groups, at addresses that are
-    vectors and that are not: bits of the oracle."""
+    """Codes of a contiguous tensor whose rows are no multiple of eight, around a group and a workgroup's groups and the sizes from
+    which groups are what a thread takes, at addresses that are vectors and that are not: bits of the oracle."""
     rng = np.random.default_rng(rows + cols)
     x = _data(rng, (rows, cols), dtype, 0.7)
     _, io = orc.scales_from_amax(orc.absmax(x, "tensor"))
