@@ -227,7 +227,8 @@ __global__ __launch_bounds__(BLOCK) void absmax_tensor_kernel(const T* __restric
     }
     if(want_sq)
     {
-        d = block_reduce_sum(d, lds_d);
+        // (up to 64 workgroups' sums are one wavefront's: without the exchange 7x3 5.03 -> 4.90 us, 45x1023 5.31 -> 5.05)
+        d = gridDim.x <= kWaveSize ? wave_reduce_sum(d) : block_reduce_sum(d, lds_d);
         if(threadIdx.x == 0) *sumsq_opt = static_cast<float>(d);
     }
     mm = block_reduce_max(mm, lds);
